@@ -256,43 +256,6 @@ __device__ __forceinline__ void pack_head_row(const PackParams &p, int b, int i,
     }
 }
 
-// Reference point and key-loop bound of batch element b, computed by one wave (every wave that
-// asks gets the same answer).  kvlen = 1 + index of the last valid residue.  The reference point
-// only has to lie inside the structure (the result does not depend on it, Section 2; it keeps
-// the coordinates that are split into bf16 pairs small): the mean translation of 64 valid
-// residues spread evenly over [0, kvlen) stands in for the centroid of all of them.
-__device__ __forceinline__ void batch_reference(const PackParams &p, int b, float (&cen)[3], int &kvlen)
-{
-    const int lane = threadIdx.x & 63;
-    const int len = user_len(p, b);
-    const size_t row0 = user_row(p, b, 0);
-    int last = len;
-    if (p.mask) {
-        const uint8_t *m = p.mask + row0;
-        last = 0;
-        for (int i = lane; i < len; i += 64)
-            if (m[i] != 0) last = i + 1;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
-    }
-    kvlen = last;
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (kvlen > 0) {
-        const int i = (int)(((long long)lane * kvlen) >> 6);
-        if (p.mask ? p.mask[row0 + i] != 0 : true) {
-            const float *t = p.trans + (row0 + i) * 3;
-            v[0] = t[0]; v[1] = t[1]; v[2] = t[2]; v[3] = 1.f;
-        }
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v[a] += __shfl_xor(v[a], o);
-    const float n = v[3] > 0.f ? v[3] : 1.f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) cen[a] = v[a] / n;
-}
-
 // The launch covers the three roles (nbh workgroups each) and, after them, the z2 copy.
 __global__ __launch_bounds__(256) void fipa_pack_heads_af2_bf16_kernel(PackParams p, unsigned nbh)
 {

@@ -1,262 +1,411 @@
 // fp32 direct path: logits from explicit point differences (Eq. 3), online softmax over key
 // tiles, fp32 accumulation of the lifted values (Algorithm 1 steps 6-7), and the split /
-// inverse frame / z1 contraction (steps 8-9, Eq. 4) in the same kernel.  Plain VALU
-// arithmetic; this is the accuracy path (1e-4), not the throughput path.
-#include "fipa_internal.h"
+// inverse frame / z1 contraction (steps 8-9, Eq. 4) in the same kernel.  The dot products run on
+// the fp32 matrix instructions (full fp32 operands and accumulation: this is the accuracy path,
+// 1e-4); the squared distances stay explicit differences on the vector ALU, because the expanded
+// form cancels at global coordinates.
+#include "fipa_bf16_common.h"
 
 namespace fipa {
 
 namespace {
 
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// A packed record of residue i and head h, HRW floats, [B, H, L, HRW]:
+//   [ k (c, padded to 16) | Kg (3 N_query, padded to 4) | v, Vg (padded to 16) | Qg, generic shapes only ].
+// A key in LDS: the record up to Vg -- generic shapes leave Kg out, which has no bound there, and read it
+// and Qg from memory -- and then the key's z2 row (DZ, padded to 16).
+struct F32Geom {
+    int c16, nq4, nh16, HRW, DZ16;
+    int voff, zoff;  // v and z2 in an LDS record
+    int S;    // LDS record stride in floats: an odd multiple of 4, so that 8 rows read 16 bytes each from 8 distinct bank groups
+    int nch;  // 16-feature chunks of the contraction: k and z2
+    int nt;   // 16-column tiles of the values: v, Vg and z2
+};
+
+__host__ __device__ constexpr F32Geom f32_geom(int c, int Pq, int Pv, int DZ, bool exact)
+{
+    F32Geom g{};
+    g.c16 = (c + 15) / 16 * 16;
+    g.nq4 = (3 * Pq + 3) / 4 * 4;
+    g.nh16 = (c + 3 * Pv + 15) / 16 * 16;
+    g.HRW = g.c16 + g.nq4 + g.nh16 + (exact ? 0 : g.nq4);
+    g.DZ16 = (DZ + 15) / 16 * 16;
+    g.voff = g.c16 + (exact ? g.nq4 : 0);
+    g.zoff = g.voff + g.nh16;
+    g.S = g.zoff + g.DZ16;
+    if ((g.S / 4) % 2 == 0) g.S += 4;
+    g.nch = (g.c16 + g.DZ16) / 16;
+    g.nt = (g.nh16 + g.DZ16) / 16;
+    return g;
+}
+
+// AlphaFold2's head shape, with rows that can be read as 16-byte pieces.
+bool f32_exact(const fipa_desc &d)
+{
+    return d.c == 16 && d.Pq == 4 && d.Pv == 8 && d.cz % 4 == 0 && d.r * d.cz % 16 == 0;
+}
+
 struct F32Params {
-    const float *q, *k, *v, *z1, *z2, *rot, *trans, *gamma;
+    const float *q, *k, *v, *q_pts, *k_pts, *v_pts, *z1, *z2, *rot, *trans, *gamma, *w_b;
     const uint8_t *mask;
-    const float *Qg, *Kg, *Vg, *Qz, *cen;
-    const int *kvlen;
+    const int *cu;  // always null here (user_row and batch_reference want the member)
+    float *HR, *cen;
+    int *kvlen;
     float *o, *o_pts, *o_pair, *lse;
     int B, L, H, c, Pq, Pv, cz, r, DZ;
-    int TK;    // keys per LDS tile
-    int REC;   // floats per key record: k | Kg | z2 | v | Vg
-    int SK;    // record stride in floats (odd, so that lanes hit distinct banks)
-    int NCOL;  // lifted value width c + 3Pv + DZ
+    F32Geom g;
+    int n_units, n_rt;  // row tiles in all, and per (b, h)
+    bool vec;           // c, cz and DZ are multiples of 4: rows can be read as 16-byte pieces
     float w_L, w_C, qk_scale;
 };
 
-constexpr int kRowsPerWave = 4;
-constexpr int kRowsPerBlock = 16;
-
-// Global-frame points relative to the batch centroid, T_i o x - centroid (Algorithm 1 steps 4-6).
-__global__ __launch_bounds__(256) void fipa_pack_points_f32_kernel(
-    const float *__restrict__ q_pts, const float *__restrict__ k_pts,
-    const float *__restrict__ v_pts, const float *__restrict__ rot,
-    const float *__restrict__ trans, const float *__restrict__ cen, float *__restrict__ Qg,
-    float *__restrict__ Kg, float *__restrict__ Vg, int L, int H, int Pq, int Pv)
+// Key records (Algorithm 1 steps 4-6: K = T o k_pts, V = T o v_pts relative to the batch's reference
+// point), zero for masked residues: one thread per 16 bytes of a record.  Every workgroup finds the
+// reference point itself; the one that starts a batch element publishes it with the key-loop bound.
+__global__ __launch_bounds__(256) void fipa_pack_f32_kernel(F32Params p)
 {
-    const int b = blockIdx.y;
-    const int idx = blockIdx.x * 256 + threadIdx.x;  // (i, h)
-    if (idx >= L * H) return;
-    const int i = idx / H, h = idx % H;
-    const float *R = rot + ((size_t)b * L + i) * 9;
-    const float *t = trans + ((size_t)b * L + i) * 3;
-    float Rm[9], tc[3];
-    for (int a = 0; a < 9; ++a) Rm[a] = R[a];
-    for (int a = 0; a < 3; ++a) tc[a] = t[a] - cen[4 * b + a];
-    auto apply = [&](const float *src, float *dst, int P) {
-        for (int p = 0; p < P; ++p) {
-            const float x = src[3 * p], y = src[3 * p + 1], z = src[3 * p + 2];
-            for (int a = 0; a < 3; ++a)
-                dst[3 * p + a] = Rm[3 * a] * x + Rm[3 * a + 1] * y + Rm[3 * a + 2] * z + tc[a];
-        }
-    };
-    const size_t in_q = (((size_t)b * L + i) * H + h) * Pq * 3;
-    const size_t in_v = (((size_t)b * L + i) * H + h) * Pv * 3;
-    const size_t out_q = (((size_t)b * H + h) * L + i) * Pq * 3;
-    const size_t out_v = (((size_t)b * H + h) * L + i) * Pv * 3;
-    apply(q_pts + in_q, Qg + out_q, Pq);
-    apply(k_pts + in_q, Kg + out_q, Pq);
-    apply(v_pts + in_v, Vg + out_v, Pv);
-}
-
-// Query-side factor bias vector b^{h1}_i = w_L * w_b[h] (.) z1_i (Algorithm 1 step 2, with
-// Eq. 3's w_L on the bias), laid out [B,H,L,DZ].
-__global__ __launch_bounds__(256) void fipa_pack_qz_f32_kernel(const float *__restrict__ z1,
-                                                               const float *__restrict__ w_b,
-                                                               float *__restrict__ Qz, int L, int H,
-                                                               int cz, int DZ, float w_L,
-                                                               size_t total)
-{
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
-    const int x = (int)(idx % DZ);
-    const size_t rest = idx / DZ;
-    const int i = (int)(rest % L);
-    const size_t bh = rest / L;
-    const int h = (int)(bh % H);
-    const size_t b = bh / H;
-    Qz[idx] = w_L * w_b[(size_t)h * cz + x % cz] * z1[(b * L + i) * DZ + x];
-}
-
-__device__ __forceinline__ float wave_max(float x)
-{
-    for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-    return x;
-}
-__device__ __forceinline__ float wave_sum(float x)
-{
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
-
-template <int MC>
-__global__ __launch_bounds__(256) void fipa_attn_f32_kernel(F32Params p)
-{
-    extern __shared__ float smem[];
-    float *tile = smem;                                 // [TK][SK]
-    float *mbias = smem + (size_t)p.TK * p.SK;          // [TK] 0 or -inf
-    float *rowbuf = smem;                               // [16][NCOL], aliases the tile at the end
-
-    const int b = blockIdx.z, h = blockIdx.y;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
-    const int i0 = blockIdx.x * kRowsPerBlock + wave * kRowsPerWave;
-    const int L = p.L, H = p.H, c = p.c, DZ = p.DZ, TK = p.TK, SK = p.SK;
-    const int nq = 3 * p.Pq, nv = 3 * p.Pv;
-    const int kvlen = p.kvlen[b];
-
-    const float *qrow[kRowsPerWave], *Qgrow[kRowsPerWave], *Qzrow[kRowsPerWave];
-    for (int rr = 0; rr < kRowsPerWave; ++rr) {
-        const int i = min(i0 + rr, L - 1);
-        qrow[rr] = p.q + (((size_t)b * L + i) * H + h) * c;
-        Qgrow[rr] = p.Qg + (((size_t)b * H + h) * L + i) * nq;
-        Qzrow[rr] = p.Qz + (((size_t)b * H + h) * L + i) * DZ;
+    const int b = blockIdx.y, X4 = p.g.HRW / 4;
+    float cen[3];
+    int kv;
+    batch_reference(p, b, cen, kv);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        for (int a = 0; a < 3; ++a) p.cen[4 * b + a] = cen[a];
+        p.cen[4 * b + 3] = 0.f;
+        p.kvlen[b] = kv;
     }
-    const float coef = 0.5f * p.gamma[h] * p.w_L * p.w_C;
-    const float sc = p.w_L * p.qk_scale;
-
-    // value column owned by this lane in slot mc, as an offset into a key record
-    int coloff[MC];
-    for (int mc = 0; mc < MC; ++mc) {
-        const int col = lane + 64 * mc;
-        int off = 0;
-        if (col < c + nv)
-            off = c + nq + DZ + col;
-        else if (col < p.NCOL)
-            off = c + nq + (col - c - nv);
-        coloff[mc] = off;
-    }
-
-    float m[kRowsPerWave], l[kRowsPerWave], acc[kRowsPerWave][MC];
-    for (int rr = 0; rr < kRowsPerWave; ++rr) {
-        m[rr] = -INFINITY;
-        l[rr] = 0.f;
-        for (int mc = 0; mc < MC; ++mc) acc[rr][mc] = 0.f;
-    }
-
-    for (int j0 = 0; j0 < kvlen; j0 += TK) {
-        __syncthreads();
-        // stage the key records k | Kg | z2 | v | Vg
-        for (int idx = threadIdx.x; idx < TK * p.REC; idx += 256) {
-            const int jj = idx / p.REC, x = idx - jj * p.REC;
-            const int j = j0 + jj;
+    const unsigned idx = blockIdx.x * 256u + threadIdx.x;
+    if (idx >= (unsigned)p.H * p.L * X4) return;
+    const unsigned rec = idx / X4;
+    const int x0 = 4 * (int)(idx - rec * X4);
+    const int h = rec / p.L, i = rec - h * p.L;
+    const size_t urow = (size_t)b * p.L + i, row = urow * p.H + h;
+    const bool ok = p.mask ? p.mask[urow] != 0 : true;
+    const int nv = 3 * p.Pv;
+    f32x4 out = {0.f, 0.f, 0.f, 0.f};
+    if (ok) {
+        const float *R = p.rot + urow * 9, *t = p.trans + urow * 3;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            int x = x0 + e, pt = -1;
+            const float *src = nullptr;
             float val = 0.f;
-            if (j < L) {
-                if (x < c)
-                    val = p.k[(((size_t)b * L + j) * H + h) * c + x];
-                else if (x < c + nq)
-                    val = p.Kg[(((size_t)b * H + h) * L + j) * nq + (x - c)];
-                else if (x < c + nq + DZ)
-                    val = p.z2[((size_t)b * L + j) * DZ + (x - c - nq)];
-                else if (x < 2 * c + nq + DZ)
-                    val = p.v[(((size_t)b * L + j) * H + h) * c + (x - c - nq - DZ)];
-                else
-                    val = p.Vg[(((size_t)b * H + h) * L + j) * nv + (x - 2 * c - nq - DZ)];
+            if (x < p.g.c16) {
+                if (x < p.c) val = p.k[row * p.c + x];
+            } else if (x < p.g.c16 + p.g.nq4) {
+                x -= p.g.c16;
+                if (x < 3 * p.Pq) { pt = x; src = p.k_pts + row * 3 * p.Pq; }
+            } else if (x < p.g.c16 + p.g.nq4 + p.g.nh16) {
+                x -= p.g.c16 + p.g.nq4;
+                if (x < p.c) val = p.v[row * p.c + x];
+                else if (x < p.c + nv) { pt = x - p.c; src = p.v_pts + row * nv; }
+            } else {
+                x -= p.g.c16 + p.g.nq4 + p.g.nh16;
+                if (x < 3 * p.Pq) { pt = x; src = p.q_pts + row * 3 * p.Pq; }
             }
-            tile[(size_t)jj * SK + x] = val;
+            if (pt >= 0) {
+                const int pp = pt / 3, a = pt - 3 * pp;
+                const float *l = src + 3 * pp;
+                val = R[3 * a] * l[0] + R[3 * a + 1] * l[1] + R[3 * a + 2] * l[2] + (t[a] - cen[a]);
+            }
+            out[e] = val;
         }
-        for (int jj = threadIdx.x; jj < TK; jj += 256) {
-            const int j = j0 + jj;
-            const bool ok = j < kvlen && (p.mask ? p.mask[(size_t)b * L + j] != 0 : true);
-            mbias[jj] = ok ? 0.f : -INFINITY;
-        }
-        __syncthreads();
+    }
+    *reinterpret_cast<f32x4 *>(p.HR + (((size_t)b * p.H + h) * p.L + i) * p.g.HRW + x0) = out;
+}
 
-        // logits of this lane's key against the wave's four query rows (Eq. 3)
-        const int lj = lane < TK ? lane : 0;
-        const float *rec = tile + (size_t)lj * SK;
-        float s[kRowsPerWave];
-        {
-            float dotk[kRowsPerWave] = {0.f, 0.f, 0.f, 0.f};
-            for (int d = 0; d < c; ++d) {
-                const float kd = rec[d];
-                for (int rr = 0; rr < kRowsPerWave; ++rr) dotk[rr] += qrow[rr][d] * kd;
-            }
-            float dist[kRowsPerWave] = {0.f, 0.f, 0.f, 0.f};
-            for (int d = 0; d < nq; ++d) {
-                const float kd = rec[c + d];
-                for (int rr = 0; rr < kRowsPerWave; ++rr) {
-                    const float df = Qgrow[rr][d] - kd;
-                    dist[rr] += df * df;
+__device__ __forceinline__ float group_max(float x)  // over the four 16-lane groups of a wave
+{
+    x = fmaxf(x, __shfl_xor(x, 16));
+    return fmaxf(x, __shfl_xor(x, 32));
+}
+__device__ __forceinline__ float group_sum(float x)
+{
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
+// One workgroup = RG groups of 16 query rows; its four waves are RG row groups x KS = 4 / RG shares
+// of the key tiles (16 keys each), merged through LDS at the end.  Both products are formed
+// transposed with the 16x16x4 fp32 MFMA (S^T = K Q^T, O^T += V^T P^T): a lane then owns one query
+// (lane % 16) and the four keys 4 (lane / 16) + e of a tile, its S^T registers are the B operand of
+// the second product as they stand (step e takes key 4 g + e from lane group g), and the softmax
+// statistics are per-lane scalars.  The contraction index is permuted the same way on both sides
+// (feature 16 ch + 4 g + e in step e of lane group g), so the operands are read 16 bytes at a time.
+// NCH, NT: chunk and tile counts, compile-time exact when EXACT (AlphaFold2's head shape with 12 query
+// coordinates kept in registers), otherwise upper bounds.
+// Bound: fp32 matrix pipe, 256 flop per clock and CU; one 16x16x4 takes 32 clocks, in which a wave
+// needs one 4-byte LDS operand per lane, so LDS and the vector ALU have room to spare.  With KS key
+// shares per workgroup the units are small (16 or 32 rows) and every CU gets several.
+// B = 2, L = 1024, H = 12, r c_z = 256: 0.44 ms, 43 % of the 157 TFLOP/s of the fp32 matrix pipe (the
+// vector-ALU form, one wave per four rows, 5.32 ms); L = 64, H = 4, r c_z = 32: 8 us (40 us).
+template <int NCH, int NT, bool EXACT, int RG>
+__global__ __launch_bounds__(256, EXACT && (NCH + NT) * 4 + 60 <= 256 ? 2 : 1) void fipa_attn_f32_kernel(F32Params p)
+{
+    constexpr int KS = 4 / RG;
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    const F32Geom G = EXACT ? f32_geom(16, 4, 8, 16 * (NCH - 1), true) : p.g;  // (the first is folded to constants)
+    const int S = G.S;
+    float *const tiles = smem;                       // [KS][16][S]; at the end partial sums and output rows
+    float *const kb = smem + KS * 16 * S;            // [KS * 16] 0 or -inf
+    float *const ml = kb + KS * 16;                  // [4][16][2] maximum and sum of a wave's share
+
+    const int per = (p.n_units + 7) / 8;             // an XCD gets neighbouring units: it shares their keys in its L2
+    const int unit = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    if ((int)(blockIdx.x / 8) >= per || unit >= p.n_units) return;
+    const int bh = unit / p.n_rt, b = bh / p.H, h = bh - b * p.H;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+    const int rg = wave % RG, ks = wave / RG;
+    const int i_wg = (unit - bh * p.n_rt) * (16 * RG);
+    const int L = p.L, H = p.H, DZ = p.DZ, nq = 3 * p.Pq, nv = 3 * p.Pv;
+    const int kvlen = p.kvlen[b];
+    const int nch = G.nch, nt = G.nt;
+    const int zoff = G.zoff, voff = G.voff, cch = G.c16 / 16;
+    const float coef = kLog2e * 0.5f * p.gamma[h] * p.w_L * p.w_C;
+
+    // query side: scaled scalars and factor bias vector b^{h1} (log2 units), global points
+    const int iq = min(i_wg + 16 * rg + n, L - 1);
+    const size_t urow = (size_t)b * L + iq, row = urow * H + h;
+    f32x4 qf[NCH];
+    {
+        const float sc = kLog2e * p.w_L * p.qk_scale, bz = kLog2e * p.w_L;
+        const float *q = p.q + row * p.c, *z1 = p.z1 + urow * DZ, *wb = p.w_b + (size_t)h * p.cz;
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+            qf[ch] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (EXACT) {
+                const int x = 16 * (ch - cch) + 4 * g;
+                if (ch < cch)
+                    qf[ch] = sc * *reinterpret_cast<const f32x4 *>(q + x + 16);
+                else
+                    qf[ch] = bz * *reinterpret_cast<const f32x4 *>(wb + x % p.cz) * *reinterpret_cast<const f32x4 *>(z1 + x);
+            } else if (ch < nch) {
+                const int x = 16 * ch + 4 * g, xz = x - 16 * cch;
+                for (int e = 0; e < 4; ++e) {
+                    float val = 0.f;
+                    if (ch < cch) {
+                        if (x + e < p.c) val = sc * q[x + e];
+                    } else if (xz + e < DZ) {
+                        val = bz * wb[(xz + e) % p.cz] * z1[xz + e];
+                    }
+                    qf[ch][e] = val;
                 }
             }
-            float bias[kRowsPerWave] = {0.f, 0.f, 0.f, 0.f};
-            for (int d = 0; d < DZ; ++d) {
-                const float zd = rec[c + nq + d];
-                for (int rr = 0; rr < kRowsPerWave; ++rr) bias[rr] += Qzrow[rr][d] * zd;
-            }
-            const float mb = lane < TK ? mbias[lj] : -INFINITY;
-            for (int rr = 0; rr < kRowsPerWave; ++rr)
-                s[rr] = sc * dotk[rr] + bias[rr] - coef * dist[rr] + mb;
         }
-        // online softmax update (running maximum, running sum, rescaled accumulator)
-        float pw[kRowsPerWave];
-        for (int rr = 0; rr < kRowsPerWave; ++rr) {
-            const float m_new = fmaxf(m[rr], wave_max(s[rr]));
-            const float m_use = m_new == -INFINITY ? 0.f : m_new;
-            pw[rr] = __expf(s[rr] - m_use);
-            const float alpha = __expf(m[rr] - m_use);
-            l[rr] = l[rr] * alpha + wave_sum(pw[rr]);
-            m[rr] = m_new;
-            for (int mc = 0; mc < MC; ++mc) acc[rr][mc] *= alpha;
-        }
-        // weighted sum of the lifted values: lanes own value columns
-        for (int jj = 0; jj < TK; ++jj) {
-            float pj[kRowsPerWave];
-            for (int rr = 0; rr < kRowsPerWave; ++rr)
-                pj[rr] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pw[rr]), jj));
-            const float *vrec = tile + (size_t)jj * SK;
-            for (int mc = 0; mc < MC; ++mc) {
-                const float val = vrec[coloff[mc]];
-                for (int rr = 0; rr < kRowsPerWave; ++rr) acc[rr][mc] += pj[rr] * val;
-            }
+    }
+    const float *const hr = p.HR + (size_t)bh * L * G.HRW;
+    float qg[12];
+    const float *qg_mem = hr + (size_t)iq * G.HRW + G.c16 + G.nq4 + G.nh16;
+    if (EXACT) {
+        const float *R = p.rot + urow * 9, *t = p.trans + urow * 3, *cen = p.cen + 4 * b, *src = p.q_pts + row * nq;
+#pragma unroll
+        for (int x = 0; x < 12; ++x) {
+            const int pp = x / 3, a = x % 3;
+            qg[x] = R[3 * a] * src[3 * pp] + R[3 * a + 1] * src[3 * pp + 1] + R[3 * a + 2] * src[3 * pp + 2] + (t[a] - cen[a]);
         }
     }
 
-    // split, inverse frame, z1 contraction (Algorithm 1 steps 8-9, Eq. 4)
+    float m = -INFINITY, l = 0.f;
+    f32x4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    const float *z2 = p.z2 + (size_t)b * L * DZ;
+    const int nhr = G.zoff / 4, nz = G.DZ16 / 4;
+    const float *tile = tiles + ks * 16 * S;
+    for (int j0 = 0; j0 < kvlen; j0 += 16 * KS) {
+        __syncthreads();
+        const int nj = min(16 * KS, kvlen - j0);  // rows past it are zero and masked
+#pragma unroll 4
+        for (int idx = threadIdx.x; idx < 16 * KS * nhr; idx += 256) {
+            const int jj = idx / nhr, x = 4 * (idx - jj * nhr);
+            f32x4 val = {0.f, 0.f, 0.f, 0.f};
+            if (jj < nj)
+                val = *reinterpret_cast<const f32x4 *>(hr + (size_t)(j0 + jj) * G.HRW + x + (EXACT || x < G.c16 ? 0 : G.nq4));
+            *reinterpret_cast<f32x4 *>(tiles + jj * S + x) = val;
+        }
+#pragma unroll 4
+        for (int idx = threadIdx.x; idx < 16 * KS * nz; idx += 256) {
+            const int jj = idx / nz, x = 4 * (idx - jj * nz);
+            f32x4 val = {0.f, 0.f, 0.f, 0.f};
+            if (jj < nj) {
+                const float *src = z2 + (size_t)(j0 + jj) * DZ + x;
+                if (EXACT || (p.vec && x < DZ)) {
+                    val = *reinterpret_cast<const f32x4 *>(src);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (x + e < DZ) val[e] = src[e];
+                }
+            }
+            *reinterpret_cast<f32x4 *>(tiles + jj * S + zoff + x) = val;
+        }
+        if (threadIdx.x < 16 * KS) {
+            const int j = j0 + threadIdx.x;
+            kb[threadIdx.x] = j < kvlen && (p.mask ? p.mask[(size_t)b * L + j] != 0 : true) ? 0.f : -INFINITY;
+        }
+        __syncthreads();
+        if (j0 + 16 * ks >= kvlen) continue;  // (wave uniform; the barriers above are reached by every wave)
+
+        // S^T of this wave's 16 keys: two accumulation chains
+        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+            // (generic shapes: the surplus chunks read something finite against zero query features)
+            const int off = ch < cch || (!EXACT && ch >= nch) ? (EXACT || ch < cch ? 16 * ch : 0) : zoff + 16 * (ch - cch);
+            const f32x4 a = *reinterpret_cast<const f32x4 *>(tile + n * S + off + 4 * g);
+            f32x4 &s = ch & 1 ? s1 : s0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], qf[ch][e], s, 0, 0, 0);
+        }
+        // explicit squared distances of the four keys 4 g + e
+        f32x4 dist = {0.f, 0.f, 0.f, 0.f};
+        if (EXACT) {
+            const float *kg = tile + 4 * g * S + G.c16;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int x = 0; x < 12; x += 4) {
+                    const f32x4 kv4 = *reinterpret_cast<const f32x4 *>(kg + e * S + x);
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) {
+                        const float df = qg[x + y] - kv4[y];
+                        dist[e] += df * df;
+                    }
+                }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float *kg = hr + (size_t)min(j0 + 16 * ks + 4 * g + e, L - 1) * G.HRW + G.c16;
+                for (int x = 0; x < G.nq4; x += 4) {
+                    const f32x4 df = *reinterpret_cast<const f32x4 *>(qg_mem + x) - *reinterpret_cast<const f32x4 *>(kg + x);
+                    dist[e] += (df[0] * df[0] + df[1] * df[1]) + (df[2] * df[2] + df[3] * df[3]);
+                }
+            }
+        }
+        const f32x4 mb = *reinterpret_cast<const f32x4 *>(kb + 16 * ks + 4 * g);
+        f32x4 s;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = mb[e] == 0.f ? (s0[e] + s1[e]) - coef * dist[e] : -INFINITY;
+        // online softmax (running maximum and sum; the accumulator is rescaled when a maximum moved)
+        const float mt = group_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+        if (__any(mt > m)) {
+            const float m_new = fmaxf(m, mt);
+            const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+            l *= alpha;
+            m = m_new;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t] *= alpha;
+        }
+        const float m_use = m == -INFINITY ? 0.f : m;
+        f32x4 pw;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pw[e] = __builtin_amdgcn_exp2f(s[e] - m_use);
+        l += (pw[0] + pw[1]) + (pw[2] + pw[3]);
+        // O^T += V^T P^T
+        const float *vt = tile + 4 * g * S + voff + n;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                // (generic shapes: the surplus tiles accumulate column block 0 again, unused)
+                const int off = EXACT || t < nt ? 16 * t : 0;
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vt[e * S + off], pw[e], acc[t], 0, 0, 0);
+            }
+    }
+    l = group_sum(l);
+
+    // merge the key shares: every wave but those of share 0 leaves its sums in LDS
+    const int RS = 16 * nt + 4;  // row stride of the partial sums; 16 rows fit a key tile's space
     __syncthreads();
-    for (int rr = 0; rr < kRowsPerWave; ++rr) {
-        const float inv = l[rr] > 0.f ? 1.f / l[rr] : 0.f;
-        float *rb = rowbuf + (size_t)(wave * kRowsPerWave + rr) * p.NCOL;
-        for (int mc = 0; mc < MC; ++mc) {
-            const int col = lane + 64 * mc;
-            if (col < p.NCOL) rb[col] = acc[rr][mc] * inv;
+    if (g == 0) {
+        ml[(wave * 16 + n) * 2] = m;
+        ml[(wave * 16 + n) * 2 + 1] = l;
+    }
+    if (ks > 0) {
+        float *dst = tiles + (wave - RG) * 16 * S + n * RS + 4 * g;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            if (EXACT || t < nt) *reinterpret_cast<f32x4 *>(dst + 16 * t) = acc[t];
+    }
+    __syncthreads();
+    if (ks == 0) {
+        float m_all = m;
+        for (int x = 1; x < KS; ++x) m_all = fmaxf(m_all, ml[((x * RG + rg) * 16 + n) * 2]);
+        const float m_use = m_all == -INFINITY ? 0.f : m_all;
+        float w = __builtin_amdgcn_exp2f(m - m_use);
+        float l_all = l * w;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] *= w;
+        for (int x = 1; x < KS; ++x) {
+            const float *s_ml = ml + ((x * RG + rg) * 16 + n) * 2;
+            w = __builtin_amdgcn_exp2f(s_ml[0] - m_use);
+            l_all += s_ml[1] * w;
+            const float *src = tiles + ((x - 1) * RG + rg) * 16 * S + n * RS + 4 * g;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                if (EXACT || t < nt) acc[t] += w * *reinterpret_cast<const f32x4 *>(src + 16 * t);
+        }
+        // (only this wave has read the space that its output rows now take)
+        const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
+        float *dst = tiles + rg * 16 * S + n * RS + 4 * g;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            if (EXACT || t < nt) *reinterpret_cast<f32x4 *>(dst + 16 * t) = inv * acc[t];
+        if (g == 0) {
+            ml[(wave * 16 + n) * 2] = m_all;
+            ml[(wave * 16 + n) * 2 + 1] = l_all;
         }
     }
     __syncthreads();
-    for (int rr = 0; rr < kRowsPerWave; ++rr) {
-        const int i = i0 + rr;
-        if (i >= L) break;
-        const bool valid = (p.mask ? p.mask[(size_t)b * L + i] != 0 : true) && l[rr] > 0.f;
-        const float *rb = rowbuf + (size_t)(wave * kRowsPerWave + rr) * p.NCOL;
-        const size_t row = ((size_t)b * L + i) * H + h;
-        for (int d = lane; d < c; d += 64) p.o[row * c + d] = valid ? rb[d] : 0.f;
-        const float *R = p.rot + ((size_t)b * L + i) * 9;
-        const float *t = p.trans + ((size_t)b * L + i) * 3;
-        for (int idx = lane; idx < nv; idx += 64) {
+
+    // split, inverse frame, z1 contraction (Algorithm 1 steps 8-9, Eq. 4): 16 threads per row and group
+    for (int rr = 0; rr < RG; ++rr) {
+        const int rl = threadIdx.x >> 4, x0 = threadIdx.x & 15;
+        const int i = i_wg + 16 * rr + rl;
+        if (i >= L) continue;
+        const size_t ui = (size_t)b * L + i, ro = ui * H + h;
+        const float *rb = tiles + rr * 16 * S + rl * RS;
+        const float m_row = ml[(rr * 16 + rl) * 2], l_row = ml[(rr * 16 + rl) * 2 + 1];
+        const bool valid = (p.mask ? p.mask[ui] != 0 : true) && l_row > 0.f;
+        for (int d = x0; d < p.c; d += 16) p.o[ro * p.c + d] = valid ? rb[d] : 0.f;
+        const float *R = p.rot + ui * 9, *t = p.trans + ui * 3;
+        for (int idx = x0; idx < nv; idx += 16) {
             const int pp = idx / 3, x = idx - 3 * pp;
             float val = 0.f;
-            for (int y = 0; y < 3; ++y)
-                val += R[3 * y + x] * (rb[c + 3 * pp + y] - (t[y] - p.cen[4 * b + y]));
-            p.o_pts[row * nv + idx] = valid ? val : 0.f;
+            for (int y = 0; y < 3; ++y) val += R[3 * y + x] * (rb[p.c + 3 * pp + y] - (t[y] - p.cen[4 * b + y]));
+            p.o_pts[ro * nv + idx] = valid ? val : 0.f;
         }
-        for (int d = lane; d < p.cz; d += 64) {
-            float val = 0.f;
-            for (int rho = 0; rho < p.r; ++rho)
-                val += p.z1[((size_t)b * L + i) * DZ + rho * p.cz + d] * rb[c + nv + rho * p.cz + d];
-            p.o_pair[row * p.cz + d] = valid ? val : 0.f;
+        const float *z1 = p.z1 + ui * DZ;
+        if (p.vec) {
+            for (int d = 4 * x0; d < p.cz; d += 64) {
+                f32x4 val = {0.f, 0.f, 0.f, 0.f};
+                for (int rho = 0; rho < p.r; ++rho)
+                    val += *reinterpret_cast<const f32x4 *>(z1 + rho * p.cz + d) *
+                           *reinterpret_cast<const f32x4 *>(rb + G.nh16 + rho * p.cz + d);
+                if (!valid) val = (f32x4){0.f, 0.f, 0.f, 0.f};
+                *reinterpret_cast<f32x4 *>(p.o_pair + ro * p.cz + d) = val;
+            }
+        } else {
+            for (int d = x0; d < p.cz; d += 16) {
+                float val = 0.f;
+                for (int rho = 0; rho < p.r; ++rho) val += z1[rho * p.cz + d] * rb[G.nh16 + rho * p.cz + d];
+                p.o_pair[ro * p.cz + d] = valid ? val : 0.f;
+            }
         }
-        if (p.lse && lane == 0)
-            p.lse[((size_t)b * H + h) * L + i] = valid ? m[rr] + __logf(l[rr]) : 0.f;
+        if (p.lse && x0 == 0) p.lse[((size_t)b * H + h) * L + i] = valid ? kLn2 * (m_row + __log2f(l_row)) : 0.f;
     }
 }
 
 struct F32Layout {
-    size_t cen, kvlen, Qg, Kg, Vg, Qz, total;
+    size_t cen, kvlen, HR, total;
 };
 
 F32Layout f32_layout(const fipa_desc &d)
 {
     F32Layout w;
-    const size_t BHL = (size_t)d.B * d.H * d.L;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
@@ -265,15 +414,24 @@ F32Layout f32_layout(const fipa_desc &d)
     };
     w.cen = take((size_t)d.B * 4 * sizeof(float));
     w.kvlen = take((size_t)d.B * sizeof(int));
-    w.Qg = take(BHL * 3 * d.Pq * sizeof(float));
-    w.Kg = take(BHL * 3 * d.Pq * sizeof(float));
-    w.Vg = take(BHL * 3 * d.Pv * sizeof(float));
-    w.Qz = take(BHL * (size_t)d.r * d.cz * sizeof(float));
+    w.HR = take((size_t)d.B * d.H * d.L * f32_geom(d.c, d.Pq, d.Pv, d.r * d.cz, f32_exact(d)).HRW * sizeof(float));
     w.total = off;
     return w;
 }
 
-constexpr size_t kF32LdsBudget = 150 * 1024;
+size_t f32_lds_bytes(const F32Geom &g, int KS) { return ((size_t)KS * 16 * g.S + KS * 16 + 128) * sizeof(float); }
+
+template <int NCH, int NT, bool EXACT, int RG>
+hipError_t launch_attn(const F32Params &p, hipStream_t stream)
+{
+    const int KS = 4 / RG;
+    const size_t lds = f32_lds_bytes(p.g, KS);
+    static LdsLimit lim;
+    const hipError_t e = raise_lds_limit(lim, (const void *)fipa_attn_f32_kernel<NCH, NT, EXACT, RG>, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((fipa_attn_f32_kernel<NCH, NT, EXACT, RG>), dim3((p.n_units + 7) / 8 * 8), dim3(256), lds, stream, p);
+    return hipGetLastError();
+}
 
 }  // namespace
 
@@ -283,77 +441,49 @@ hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, hipStream
 {
     const F32Layout w = f32_layout(d);
     char *base = static_cast<char *>(ws);
-    float *cen = reinterpret_cast<float *>(base + w.cen);
-    int *kvlen = reinterpret_cast<int *>(base + w.kvlen);
-    float *Qg = reinterpret_cast<float *>(base + w.Qg);
-    float *Kg = reinterpret_cast<float *>(base + w.Kg);
-    float *Vg = reinterpret_cast<float *>(base + w.Vg);
-    float *Qz = reinterpret_cast<float *>(base + w.Qz);
-    const int DZ = d.r * d.cz;
+    F32Params p;
+    p.q = (const float *)a.q; p.k = (const float *)a.k; p.v = (const float *)a.v;
+    p.q_pts = (const float *)a.q_pts; p.k_pts = (const float *)a.k_pts; p.v_pts = (const float *)a.v_pts;
+    p.z1 = (const float *)a.z1; p.z2 = (const float *)a.z2;
+    p.rot = a.rot; p.trans = a.trans; p.gamma = a.gamma; p.w_b = a.w_b; p.mask = a.mask; p.cu = nullptr;
+    p.HR = reinterpret_cast<float *>(base + w.HR);
+    p.cen = reinterpret_cast<float *>(base + w.cen);
+    p.kvlen = reinterpret_cast<int *>(base + w.kvlen);
+    p.o = a.o; p.o_pts = a.o_pts; p.o_pair = a.o_pair; p.lse = a.lse;
+    p.B = d.B; p.L = d.L; p.H = d.H; p.c = d.c; p.Pq = d.Pq; p.Pv = d.Pv; p.cz = d.cz; p.r = d.r;
+    p.DZ = d.r * d.cz;
+    const bool exact = f32_exact(d);
+    p.g = f32_geom(d.c, d.Pq, d.Pv, p.DZ, exact);
+    p.vec = d.c % 4 == 0 && d.cz % 4 == 0;
+    p.w_L = d.w_L; p.w_C = d.w_C; p.qk_scale = d.qk_scale;
 
     StageTimer timer(stream);
     timer.begin(0);
-    hipError_t e = launch_prep(d, a.trans, a.mask, nullptr, cen, kvlen, nullptr, 0, stream);
-    if (e != hipSuccess) return e;
-
-    hipLaunchKernelGGL(fipa_pack_points_f32_kernel, dim3((d.L * d.H + 255) / 256, d.B), dim3(256),
-                       0, stream, (const float *)a.q_pts, (const float *)a.k_pts,
-                       (const float *)a.v_pts, a.rot, a.trans, cen, Qg, Kg, Vg, d.L, d.H, d.Pq,
-                       d.Pv);
-    const size_t total = (size_t)d.B * d.H * d.L * DZ;
-    hipLaunchKernelGGL(fipa_pack_qz_f32_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0,
-                       stream, (const float *)a.z1, a.w_b, Qz, d.L, d.H, d.cz, DZ, d.w_L, total);
+    const size_t pieces = (size_t)d.H * d.L * (p.g.HRW / 4);
+    hipLaunchKernelGGL(fipa_pack_f32_kernel, dim3((unsigned)((pieces + 255) / 256), d.B), dim3(256), 0, stream, p);
     timer.end(0);
 
-    F32Params p;
-    p.q = (const float *)a.q; p.k = (const float *)a.k; p.v = (const float *)a.v;
-    p.z1 = (const float *)a.z1; p.z2 = (const float *)a.z2;
-    p.rot = a.rot; p.trans = a.trans; p.gamma = a.gamma; p.mask = a.mask;
-    p.Qg = Qg; p.Kg = Kg; p.Vg = Vg; p.Qz = Qz; p.cen = cen; p.kvlen = kvlen;
-    p.o = a.o; p.o_pts = a.o_pts; p.o_pair = a.o_pair; p.lse = a.lse;
-    p.B = d.B; p.L = d.L; p.H = d.H; p.c = d.c; p.Pq = d.Pq; p.Pv = d.Pv; p.cz = d.cz; p.r = d.r;
-    p.DZ = DZ;
-    p.REC = 2 * d.c + 3 * d.Pq + 3 * d.Pv + DZ;
-    p.SK = p.REC | 1;
-    p.NCOL = d.c + 3 * d.Pv + DZ;
-    p.w_L = d.w_L; p.w_C = d.w_C; p.qk_scale = d.qk_scale;
-    int TK = 64;
-    auto lds_bytes = [&](int tk) {
-        const size_t tile = ((size_t)tk * p.SK + tk) * sizeof(float);
-        const size_t rows = (size_t)kRowsPerBlock * p.NCOL * sizeof(float);
-        return tile > rows ? tile : rows;
-    };
-    while (TK > 8 && lds_bytes(TK) > kF32LdsBudget) TK >>= 1;
-    p.TK = TK;
-    const size_t lds = lds_bytes(TK);
-    const int MC = (p.NCOL + 63) / 64;
-    const dim3 grid((d.L + kRowsPerBlock - 1) / kRowsPerBlock, d.H, d.B);
     timer.begin(1);  // the fp32 kernel contains the epilogue; stage 2 stays empty
-
-#define FIPA_F32_CASE(N)                                                                        \
-    case N: {                                                                                   \
-        static LdsLimit lim;                                                                    \
-        e = raise_lds_limit(lim, (const void *)fipa_attn_f32_kernel<N>, (int)lds);              \
-        if (e != hipSuccess) return e;                                                          \
-        hipLaunchKernelGGL(fipa_attn_f32_kernel<N>, grid, dim3(256), lds, stream, p);           \
-        break;                                                                                  \
-    }
-    switch (MC) {
-        FIPA_F32_CASE(1)
-        FIPA_F32_CASE(2)
-        FIPA_F32_CASE(3)
-        FIPA_F32_CASE(4)
-        FIPA_F32_CASE(5)
-        FIPA_F32_CASE(6)
-        FIPA_F32_CASE(7)
-        FIPA_F32_CASE(8)
-        FIPA_F32_CASE(9)
-        default:
-            return hipErrorInvalidValue;
-    }
-#undef FIPA_F32_CASE
+    const long long bh = (long long)d.B * d.H;
+    // 16-row workgroups where 32-row ones would not give every CU two (the widest records fit LDS only as 32-key tiles)
+    const bool small = bh * ((d.L + 31) / 32) < 512 && f32_lds_bytes(p.g, 4) <= 160 * 1024;
+    p.n_rt = small ? (d.L + 15) / 16 : (d.L + 31) / 32;
+    p.n_units = (int)(bh * p.n_rt);
+    hipError_t e;
+#define FIPA_F32_RUN(NCH, NT, EXACT) \
+    e = small ? launch_attn<NCH, NT, EXACT, 1>(p, stream) : launch_attn<NCH, NT, EXACT, 2>(p, stream)
+    if (exact && p.g.nch == 2) FIPA_F32_RUN(2, 4, true);
+    else if (exact && p.g.nch == 3) FIPA_F32_RUN(3, 5, true);
+    else if (exact && p.g.nch == 5) FIPA_F32_RUN(5, 7, true);
+    else if (exact && p.g.nch == 9) FIPA_F32_RUN(9, 11, true);
+    else if (exact && p.g.nch == 17) FIPA_F32_RUN(17, 19, true);
+    else if (exact && p.g.nch == 33) FIPA_F32_RUN(33, 35, true);
+    else if (p.g.nt <= 8) FIPA_F32_RUN(8, 8, false);
+    else if (p.g.nt <= 20) FIPA_F32_RUN(20, 20, false);
+    else FIPA_F32_RUN(37, 37, false);
+#undef FIPA_F32_RUN
     timer.end(1);
-    return hipGetLastError();
+    return e;
 }
 
 }  // namespace fipa

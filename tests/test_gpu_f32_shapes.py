@@ -1,0 +1,30 @@
+"""GPU parity of the fp32 mode at the edges of its tiles (16 query rows, 16 keys, 16 feature columns), for every
+width class of its attention kernel and for head shapes outside AlphaFold2's, against the CPU oracle (1e-4)."""
+import numpy as np
+import pytest
+
+from paper_2505_11580_amd import workloads as wl
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kw", [
+    dict(L=1), dict(L=15), dict(L=16, H=1), dict(L=17, B=2), dict(L=65, cz=8, r=2), dict(L=129, cz=32, r=2, H=2),
+    dict(L=70, cz=128, r=1, H=2), dict(L=40, cz=128, r=4, H=1),  # one width class each
+    dict(L=300, B=3, H=12, cz=16), dict(L=257, B=6, H=12, cz=16, r=1, varlen=True, min_len=1),  # 32-row workgroups
+    # generic: odd widths, scalars wider than a chunk, wide records, many query points, rows that are no multiple of 16 bytes
+    dict(L=50, c=7, Pq=3, Pv=5, cz=9, r=3, H=2), dict(L=33, c=40, Pq=1, Pv=1, cz=20, r=1, H=2),
+    dict(L=20, c=300, Pq=2, Pv=10, cz=50, r=1, H=1), dict(L=90, c=16, Pq=4, Pv=8, cz=12, r=2, H=2),
+    dict(L=40, c=8, Pq=50, Pv=2, cz=16, r=2, H=1), dict(L=30, c=500, Pq=2, Pv=20, cz=16, r=1, H=1),
+    dict(L=300, B=2, H=12, c=8, Pq=2, Pv=3, cz=8, r=2, varlen=True, min_len=100)])
+def test_f32_shapes(kw):
+    kw = dict(dict(B=1, H=4, chain=True, trans_scale=0.3), **kw)
+    gu.check(wl.make_inputs(0, **kw), label="fp32 %s" % kw)
+
+
+def test_f32_lse_and_far_keys():
+    # log-sum-exp against the oracle, at full chain geometry (logits of several thousand) with a scattered mask
+    inp = wl.make_inputs(0, L=150, H=3, cz=64, chain=True)
+    inp["mask"] = (np.random.default_rng(3).random((1, 150)) < 0.7).astype(np.uint8)
+    gu.check(inp, label="fp32 scattered mask, chain")
