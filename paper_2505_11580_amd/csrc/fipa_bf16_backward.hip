@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void fipa_bwd_pack_bf16_kernel(BwdPackParams p
     for (int off = 32; off > 0; off >>= 1) dsum += __shfl_xor(dsum, off);
     if (lane == 0) {
         const float l2 = p.lse2[row_id];
-        p.Dvec[row_id] = dsum;
+        p.Dvec[row_id] = p.neg_d ? -dsum : dsum;
         p.nlse[row_id] = (valid && l2 > -INFINITY && l2 < INFINITY) ? -l2 : -INFINITY;
     }
 }
@@ -135,9 +135,9 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
                 const bool isq = tk < Pq;
                 const float sc = isq ? 1.f : kLog2e * pscale, inv_sc = sc != 0.f ? 1.f / sc : 0.f;
                 const int pt = isq ? tk : tk - Pq;
-                const float *dX = (isq ? p.dQhat : p.dKhat) + (bh * p.Lp + i) * D + c + 3 * pt;  // hi columns of this point
+                const float *dX = (isq ? p.dQhat + (bh * p.Lp + i) * D : p.dKh + (bh * p.Lp + i) * p.h_pitch) + c + 3 * pt;  // hi columns of this point
                 const int lo_off = isq ? nq : 2 * nq;                                             // to its lo columns
-                const float ws = (isq ? p.rowsum : p.colsum)[bh * p.Lp + i];
+                const float ws = p.ds_inv * (isq ? p.rowsum : p.colsum)[bh * p.Lp + i];
                 const bf16_t *src = (isq ? p.q_pts : p.k_pts) + (rec * Pq + pt) * 3;
                 const float lc[3] = {bf2f(src[0]), bf2f(src[1]), bf2f(src[2])};
                 float grad[3];
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
                     const float G0 = Rm[3 * a] * lc[0] + Rm[3 * a + 1] * lc[1] + Rm[3 * a + 2] * lc[2] + tc[a];
-                    const float X = dX[a] + dX[lo_off + a];  // sum over the other side of dS times its hi and lo coordinates
+                    const float X = p.ds_inv * (dX[a] + dX[lo_off + a]);  // sum over the other side of dS times its hi and lo coordinates
                     // the effective (hi + lo) global coordinate the kernels used: the query's as it is, the
                     // key's scaled by log2e gamma w_L w_C before the split
                     const float Gs = sc * G0;
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
             const int h = tsk / Pv, pt = tsk - h * Pv;
             const size_t bh = (size_t)b * p.H + h;
             const size_t rec = urow * p.H + h;
-            const float *dV = p.dVhat + (bh * p.Lp + i) * D;
+            const float *dV = p.dVh + (bh * p.Lp + i) * p.h_pitch;
             float grad[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) grad[a] = dV[v_pt_col(c, Pv, pt, a, 0)];
@@ -218,9 +218,9 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
             if (tsk < p.H * per) {
                 const int h = tsk / per, rem = tsk - h * per;
                 const int which = rem / nchunk, x = 8 * (rem - which * nchunk);  // 0: d_q, 1: d_k, 2: d_v
-                const size_t row = (((size_t)b * p.H + h) * p.Lp + i) * D + x;
-                const float *src = (which == 0 ? p.dQhat : (which == 1 ? p.dKhat : p.dVhat)) + row;
-                const float scale = which == 0 ? kLn2 : (which == 1 ? p.w_L * p.qk_scale : 1.f);
+                const size_t row = ((size_t)b * p.H + h) * p.Lp + i;
+                const float *src = (which == 0 ? p.dQhat + row * D : (which == 1 ? p.dKh : p.dVh) + row * p.h_pitch) + x;
+                const float scale = which == 0 ? kLn2 * p.ds_inv : (which == 1 ? p.w_L * p.qk_scale * p.ds_inv : 1.f);
                 bf16_t *dst = (which == 0 ? p.d_q : (which == 1 ? p.d_k : p.d_v)) + (urow * p.H + h) * c + x;
                 const f32x4 v0 = *reinterpret_cast<const f32x4 *>(src);
                 const f32x4 v1 = *reinterpret_cast<const f32x4 *>(src + 4);
@@ -241,23 +241,26 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
         for (int x0 = 4 * grp; x0 < p.DZ; x0 += 256) {
             const int d0 = x0 % p.cz;
             f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
+            const float kscale = p.dVz ? kLn2 : 1.f, qscale = p.w_L * p.ds_inv;
 #pragma unroll 2
             for (int h = hg; h < p.H; h += HG) {
                 const size_t bh = (size_t)b * p.H + h;
                 const size_t row = (bh * p.Lp + i) * D + kDH + x0;
                 const size_t rec = urow * p.H + h;
                 const f32x4 dq = *reinterpret_cast<const f32x4 *>(p.dQhat + row);
-                const f32x4 dk = *reinterpret_cast<const f32x4 *>(p.dKhat + row);
-                const f32x4 dv = *reinterpret_cast<const f32x4 *>(p.dVhat + row);
+                const size_t zrow = (bh * p.Lp + i) * p.z_pitch + x0;
+                const f32x4 dk = *reinterpret_cast<const f32x4 *>(p.dKz + zrow);
+                f32x4 dv = {0.f, 0.f, 0.f, 0.f};
+                if (p.dVz) dv = *reinterpret_cast<const f32x4 *>(p.dVz + zrow);
                 const f32x4 oh = *reinterpret_cast<const f32x4 *>(p.Ohat + row);
                 const f32x4 wb = *reinterpret_cast<const f32x4 *>(p.w_b + (size_t)h * p.cz + d0);
                 const f32x4 dop = *reinterpret_cast<const f32x4 *>(p.d_o_pair + rec * p.cz + d0);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     // z1: through the bias vector b^{h1} = w_L w_b z1, and through o~ = z1^T U
-                    s1[e] += p.w_L * wb[e] * dq[e] + dop[e] * oh[e];
+                    s1[e] += qscale * wb[e] * dq[e] + dop[e] * oh[e];
                     // z2: as key feature (the log2e sits on the query side) and as value feature
-                    s2[e] += kLn2 * dk[e] + dv[e];
+                    s2[e] += kscale * dk[e] + dv[e];
                 }
             }
             for (int o = NG; o < 64; o <<= 1)  // (HG > 1: the head groups, added pairwise in a fixed order)
@@ -405,13 +408,29 @@ __global__ __launch_bounds__(1024) void fipa_bwd_wb_reduce_kernel(BwdUnpackParam
     for (int d = threadIdx.x; d < p.cz; d += 1024) {
         float t = 0.f;
         for (int rho = 0; rho < p.r; ++rho) t += col[rho * p.cz + d];
-        p.d_w_b[(size_t)h * p.cz + d] = p.w_L * t;
+        p.d_w_b[(size_t)h * p.cz + d] = p.w_L * p.ds_inv * t;
     }
+}
+
+// The lifted widths whose gradients go through stored weights (fipa_bf16_bwd_stored.hip).
+bool bwd_stored(int DZ) { return DZ == 256 || DZ == 512; }
+
+// Query rows whose weights the workspace holds at a time: a constant, so that the workspace stays affine in L.  Every
+// range but the first adds its key-side sums to memory: 2048 / 4096 / 8192 rows measured 14.4 / 13.8 / 13.6 ms per training
+// step on four chains of up to 8192 residues (r c_z = 512), 2.24 / 2.15 / 2.15 ms at B = 2, L = 4096 (r c_z = 256).
+int stored_query_rows(int Lp)
+{
+    long long nq = 4096;
+    const long long most = (1ll << 30) / (long long)align_up(Lp, 256) / 256 * 256;  // one pair's weights: 31-bit byte offsets
+    if (nq > most) nq = most < 256 ? 256 : most;
+    return nq < Lp ? (int)nq : Lp;
 }
 
 struct BwdLayout {
     Bf16Layout f;
     size_t dOhat, Dvec, nlse, dQhat, dKhat, dVhat, rowsum, colsum, gpart, wpart, total;
+    size_t dKh, dVh, dZ, Wp, Ws;  // stored weights (in the place of dKhat and dVhat)
+    int Lk, nq;
 };
 
 BwdLayout bwd_layout(const fipa_desc &d)
@@ -427,11 +446,22 @@ BwdLayout bwd_layout(const fipa_desc &d)
         return at;
     };
     w.dOhat = take(BHL * D * 2);
-    w.Dvec = take(BHL * 4);
     w.nlse = take(BHL * 4);
+    w.Dvec = take(BHL * 4);
     w.dQhat = take(BHL * D * 4);
-    w.dKhat = take(BHL * D * 4);
-    w.dVhat = take(BHL * D * 4);
+    w.dKhat = w.dVhat = w.dKh = w.dVh = w.dZ = w.Wp = w.Ws = 0;
+    w.Lk = (int)align_up(w.f.Lp, 256);
+    w.nq = stored_query_rows(w.f.Lp);
+    if (bwd_stored(w.f.DZ)) {
+        w.dKh = take(BHL * kDH * 4);
+        w.dVh = take(BHL * kDH * 4);
+        w.dZ = take(BHL * w.f.DZ * 4);
+        w.Wp = take((size_t)d.B * d.H * w.nq * w.Lk * 2);
+        w.Ws = take((size_t)d.B * d.H * w.nq * w.Lk * 2);
+    } else {
+        w.dKhat = take(BHL * D * 4);
+        w.dVhat = take(BHL * D * 4);
+    }
     w.rowsum = take(BHL * 4);
     w.colsum = take(BHL * 4);
     w.gpart = take(BHL * 4);
@@ -548,26 +578,41 @@ hipError_t backward_gradient_part(const fipa_desc &d, const BwdArgs &a, const Bw
     bp.dOhat = (bf16_t *)(base + w.dOhat); bp.Dvec = (float *)(base + w.Dvec); bp.nlse = (float *)(base + w.nlse);
     bp.B = d.B; bp.L = d.L; bp.Lp = w.f.Lp; bp.H = d.H; bp.c = d.c; bp.Pv = d.Pv; bp.cz = d.cz; bp.r = d.r;
     bp.DZ = w.f.DZ;
+    const bool stored = bwd_stored(w.f.DZ);
+    bp.neg_d = stored;
     hipError_t e = launch_bwd_pack_bf16(bp, stream);
     if (e != hipSuccess) return e;
     timer.end(0);
 
     // ---- dQ^, dK^, dV^ --------------------------------------------------------------------------------
     timer.begin(1);
-    BwdParams bw;
-    bw.Qh = pk.Qh; bw.Qz = pk.Qz; bw.Kh = pk.Kh; bw.Vh = pk.Vh; bw.Z2 = pk.Z2; bw.dOhat = bp.dOhat;
-    bw.kbias = pk.kbias; bw.nlse = bp.nlse; bw.Dvec = bp.Dvec; bw.kvlen = kvlen;
-    bw.B = d.B; bw.L = d.L; bw.Lp = w.f.Lp; bw.H = d.H; bw.total_tiles = (w.f.Lp / kTileQ) * d.B * d.H;
-    bw.deal = a.f.mask != nullptr || a.f.cu != nullptr;
-    bw.out = (float *)(base + w.dQhat); bw.wsum = (float *)(base + w.rowsum);
-    e = launch_bwd_bf16(bw, w.f.DZ, FIPA_BWD_DQ, stream);
-    if (e != hipSuccess) return e;
-    bw.out = (float *)(base + w.dKhat); bw.wsum = (float *)(base + w.colsum);
-    e = launch_bwd_bf16(bw, w.f.DZ, FIPA_BWD_DK, stream);
-    if (e != hipSuccess) return e;
-    bw.out = (float *)(base + w.dVhat); bw.wsum = nullptr;
-    e = launch_bwd_bf16(bw, w.f.DZ, FIPA_BWD_DV, stream);
-    if (e != hipSuccess) return e;
+    if (stored) {
+        BwdStoredParams sp;
+        sp.Qh = pk.Qh; sp.Qz = pk.Qz; sp.Kh = pk.Kh; sp.Vh = pk.Vh; sp.Z2 = pk.Z2; sp.dOhat = bp.dOhat;
+        sp.kbias = pk.kbias; sp.nlse = bp.nlse; sp.d_minus_nlse = (int)((w.Dvec - w.nlse)); sp.kvlen = kvlen;
+        sp.Wp = (bf16_t *)(base + w.Wp); sp.Ws = (bf16_t *)(base + w.Ws);
+        sp.dQ = (float *)(base + w.dQhat); sp.dKh = (float *)(base + w.dKh); sp.dVh = (float *)(base + w.dVh);
+        sp.dZ = (float *)(base + w.dZ); sp.rowsum = (float *)(base + w.rowsum); sp.colsum = (float *)(base + w.colsum);
+        sp.B = d.B; sp.L = d.L; sp.Lp = w.f.Lp; sp.H = d.H; sp.deal = a.f.mask != nullptr || a.f.cu != nullptr;
+        sp.Lk = w.Lk; sp.nq_alloc = w.nq; sp.i0 = 0; sp.nq = 0; sp.units = sp.nseg = sp.seg_blocks = 0;
+        e = launch_bwd_stored_bf16(sp, w.f.DZ, stream);
+        if (e != hipSuccess) return e;
+    } else {
+        BwdParams bw;
+        bw.Qh = pk.Qh; bw.Qz = pk.Qz; bw.Kh = pk.Kh; bw.Vh = pk.Vh; bw.Z2 = pk.Z2; bw.dOhat = bp.dOhat;
+        bw.kbias = pk.kbias; bw.nlse = bp.nlse; bw.Dvec = bp.Dvec; bw.kvlen = kvlen;
+        bw.B = d.B; bw.L = d.L; bw.Lp = w.f.Lp; bw.H = d.H; bw.total_tiles = (w.f.Lp / kTileQ) * d.B * d.H;
+        bw.deal = a.f.mask != nullptr || a.f.cu != nullptr;
+        bw.out = (float *)(base + w.dQhat); bw.wsum = (float *)(base + w.rowsum);
+        e = launch_bwd_bf16(bw, w.f.DZ, FIPA_BWD_DQ, stream);
+        if (e != hipSuccess) return e;
+        bw.out = (float *)(base + w.dKhat); bw.wsum = (float *)(base + w.colsum);
+        e = launch_bwd_bf16(bw, w.f.DZ, FIPA_BWD_DK, stream);
+        if (e != hipSuccess) return e;
+        bw.out = (float *)(base + w.dVhat); bw.wsum = nullptr;
+        e = launch_bwd_bf16(bw, w.f.DZ, FIPA_BWD_DV, stream);
+        if (e != hipSuccess) return e;
+    }
     timer.end(1);
 
     // ---- back to the inputs ----------------------------------------------------------------------------
@@ -578,8 +623,15 @@ hipError_t backward_gradient_part(const fipa_desc &d, const BwdArgs &a, const Bw
     up.rot = a.f.rot; up.trans = a.f.trans; up.cen = cen; up.gamma = a.f.gamma; up.w_b = a.f.w_b;
     up.d_o_pair = a.d_o_pair; up.mask = a.f.mask; up.cu = a.f.cu;
     up.total_rows = total_rows;
-    up.dQhat = (const float *)(base + w.dQhat); up.dKhat = (const float *)(base + w.dKhat);
-    up.dVhat = (const float *)(base + w.dVhat); up.Ohat = Ohat;
+    up.dQhat = (const float *)(base + w.dQhat); up.Ohat = Ohat;
+    const int D = kDH + w.f.DZ;
+    up.dKh = (const float *)(base + (stored ? w.dKh : w.dKhat));
+    up.dVh = (const float *)(base + (stored ? w.dVh : w.dVhat));
+    up.dKz = stored ? (const float *)(base + w.dZ) : up.dKh + kDH;
+    up.dVz = stored ? nullptr : up.dVh + kDH;
+    up.h_pitch = stored ? kDH : D;
+    up.z_pitch = stored ? w.f.DZ : D;
+    up.ds_inv = stored ? kLog2e : 1.f;
     up.rowsum = (const float *)(base + w.rowsum); up.colsum = (const float *)(base + w.colsum);
     up.d_q = (bf16_t *)a.d_q; up.d_k = (bf16_t *)a.d_k; up.d_v = (bf16_t *)a.d_v;
     up.d_q_pts = (bf16_t *)a.d_q_pts; up.d_k_pts = (bf16_t *)a.d_k_pts; up.d_v_pts = (bf16_t *)a.d_v_pts;

@@ -19,12 +19,8 @@
 // The streamed blocks arrive in a ring of three LDS stages by direct global -> LDS loads issued
 // one block ahead; one barrier per block publishes the new stage and releases the oldest.
 //
-// Lifted width 576 (r*c_z = 512): the two sets of stationary fragments take 288 registers per lane,
-// so a workgroup accumulates one of three windows of 192 output columns (template parameters NWIN,
-// WIN; DV, with one set of fragments, one of two windows of 288) and the small products are formed once
-// per window; a streamed block of queries (q^ and dO^,
-// 78 KB) fits LDS twice only, so DK and DV run without the pipeline across blocks (everything of
-// block n while block n+1 loads).  Plain forms that make the shape trainable; not tuned.
+// r c_z <= 128.  The wider shapes form the weights once and keep them in memory (fipa_bf16_bwd_stored.hip); here, with
+// half the matrix work per pair or less, writing and reading them would cost more than forming S again.
 #include "fipa_gfx950.h"
 
 namespace fipa {
@@ -34,15 +30,13 @@ namespace {
 constexpr int kSB = 32;              // streamed rows per block
 constexpr int kHS = kDH * 2 + 16;    // LDS row stride (bytes) of a 64-column head-specific tile
 
-template <int DZ, int MODE, int NWIN = 1, int WIN = 0>
+template <int DZ, int MODE>
 struct BwdCfg {
     static constexpr int D = kDH + DZ;           // lifted width
     static constexpr int KS = D / 16;            // k-steps of the small products
     static constexpr int KSH = kDH / 16;
     static constexpr int NB = D / 32;            // 32-row blocks of the accumulator
     static constexpr int NBH = kDH / 32;
-    static_assert(NB % NWIN == 0, "windows must tile the output columns");
-    static constexpr int NBW = NB / NWIN;        // blocks this workgroup accumulates: WIN * NBW .. + NBW - 1
     static constexpr int ZS = DZ * 2 + 48;       // LDS row stride of a pair-part tile: conflict free for row reads and transposing reads
     static constexpr int Z_SPR = ZS / 16, H_SPR = kHS / 16;   // 16-byte slots per row
     static constexpr int NZ = (kSB * Z_SPR + 63) / 64;         // wave-wide 1 KiB loads per pair-part tile
@@ -57,14 +51,9 @@ struct BwdCfg {
     static constexpr int NI = (kSharedZ ? NZ : 2 * NZ) + 2 * NH;
     static constexpr int NIW = (NI + 3) / 4;     // per wave
     static constexpr int NSC = MODE == FIPA_BWD_DK ? 2 : 1;   // per-streamed-row scalars: logit term (+ D for DK)
-    // Three stages where they fit.  Otherwise two, without the spare KiB for the surplus entries of
-    // the last round of loads (the waves that would issue them skip them; every wait in this kernel
-    // is for all outstanding loads, so the waves need not issue the same number).
-    static constexpr bool PIPELINED = 3 * (NIW * 4 * 1024 + 2 * 1024) <= 160 * 1024;
-    static constexpr bool kSkipSurplus = !PIPELINED;
-    static constexpr int SC_OFF = (PIPELINED ? NIW * 4 : NI) * 1024;   // each scalar load covers 1 KiB (its first 128 bytes are data)
+    static constexpr int SC_OFF = NIW * 4 * 1024;   // each scalar load covers 1 KiB (its first 128 bytes are data)
     static constexpr int STAGE = SC_OFF + 2 * 1024;
-    static constexpr int NSTAGE = PIPELINED ? 3 : 2;
+    static constexpr int NSTAGE = 3;
     static constexpr int LDS_BYTES = NSTAGE * STAGE;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
     static constexpr int VM_PER_BLOCK = NIW + NSC;             // vector-memory ops one wave issues per block
@@ -87,7 +76,6 @@ template <class C, int K>
 __device__ __forceinline__ void bwd_issue_one(BwdDma<C> &d, unsigned stage)
 {
     if constexpr (K < C::NIW) {
-        if (C::kSkipSurplus && d.wave + 4 * K >= C::NI) return;
         dma16<4096 * K>(d.src[K], d.voff[K], d.step[K], stage + d.wave_lds);
     } else {
         dma16<C::SC_OFF + 1024 * (K - C::NIW)>(d.src[K], d.voff[K], d.step[K], stage);
@@ -128,7 +116,7 @@ template <class C, int MODE>
 struct BwdOps {
     static constexpr bool kNeedDP = MODE != FIPA_BWD_DV;
     static constexpr int KS = C::KS;
-    static constexpr int NACC = 2 * C::NBW;  // accumulation MFMAs of a block (= KS when there is one window)
+    static constexpr int NACC = 2 * C::NB;  // accumulation MFMAs of a block
     static constexpr int kTail = NACC >= 16 ? 8 : NACC / 2;  // (8, 12 and 16 measured: 1.96, 2.00, 2.00 ms of gradient kernels at L = 4096)
     static constexpr int kInLoop = NACC - kTail;
     static constexpr int NL = (kNeedDP ? 2 : 1) * KS + kInLoop;  // before the weights
@@ -161,11 +149,11 @@ struct BwdOps {
 // operand of every MFMA is requested kLA MFMAs ahead, in order of use, into a small ring; one
 // load entry of the next block goes out per k-step; the weights of the current block are formed
 // pair by pair between the held-back accumulation MFMAs.
-template <class C, int MODE, int WIN>
+template <class C, int MODE>
 __device__ __forceinline__ void bwd_step_steady(const char *__restrict__ st, const char *__restrict__ st_prev, const BwdLane &ln,
                                                 const bf16x8 (&y1f)[C::KS],
                                                 const bf16x8 (&y2f)[MODE != FIPA_BWD_DV ? C::KS : 1],
-                                                f32x16 (&acc)[C::NBW], bf16x8 (&wf)[2], float &wsum,
+                                                f32x16 (&acc)[C::NB], bf16x8 (&wf)[2], float &wsum,
                                                 BwdDma<C> &dma, unsigned next_stage)
 {
     using O = BwdOps<C, MODE>;
@@ -191,7 +179,7 @@ __device__ __forceinline__ void bwd_step_steady(const char *__restrict__ st, con
             const char *s2 = ks < C::KSH ? st + C::X2H_OFF + ln.ka_h + ks * 32 : st + C::X2Z_OFF + ln.ka_z + (ks - C::KSH) * 32;
             return *reinterpret_cast<const bf16x8 *>(s2);
         } else {
-            const int nb = WIN * C::NBW + (o.idx >> 1), tt = o.idx & 1;  // block of the whole lifted row
+            const int nb = o.idx >> 1, tt = o.idx & 1;
             const char *src = nb < C::NBH ? st_prev + AH_OFF + ln.va_h + 16 * tt * kHS + nb * 64
                                           : st_prev + AZ_OFF + ln.va_z + 16 * tt * C::ZS + (nb - C::NBH) * 64;
             const int rs = nb < C::NBH ? kHS : C::ZS;
@@ -264,11 +252,11 @@ __device__ __forceinline__ void bwd_step_steady(const char *__restrict__ st, con
 // `st` (CUR: the first block, nothing to accumulate yet) or the accumulation of the last block
 // (PREV: stage `st_prev`, weights `wf`).  On exit of a CUR step `wf` holds the block's weights.
 // The loads of the next block (stage `next_stage`) are issued spread over the k-steps.
-template <class C, int MODE, int WIN, bool CUR, bool PREV>
+template <class C, int MODE, bool CUR, bool PREV>
 __device__ __forceinline__ void bwd_step(const char *__restrict__ st, const char *__restrict__ st_prev, const BwdLane &ln,
                                          const bf16x8 (&y1f)[C::KS],
                                          const bf16x8 (&y2f)[MODE != FIPA_BWD_DV ? C::KS : 1],
-                                         f32x16 (&acc)[C::NBW], bf16x8 (&wf)[2], float &wsum,
+                                         f32x16 (&acc)[C::NB], bf16x8 (&wf)[2], float &wsum,
                                          BwdDma<C> &dma, unsigned next_stage)
 {
     static_assert(CUR != PREV, "the steady step is bwd_step_steady");
@@ -325,9 +313,9 @@ __device__ __forceinline__ void bwd_step(const char *__restrict__ st, const char
     }
     if constexpr (PREV) {
 #pragma unroll
-        for (int i = 0; i < 2 * C::NBW; ++i) {
+        for (int i = 0; i < 2 * C::NB; ++i) {
             // acc^T[feature, stationary row] += X^T[feature, streamed row] W[streamed row, stationary row]
-            const int nb = WIN * C::NBW + (i >> 1), tt = i & 1;  // block of the whole lifted row
+            const int nb = i >> 1, tt = i & 1;
             const char *src = nb < C::NBH ? st_prev + AH_OFF + ln.va_h + 16 * tt * kHS + nb * 64
                                           : st_prev + AZ_OFF + ln.va_z + 16 * tt * C::ZS + (nb - C::NBH) * 64;
             const int rs = nb < C::NBH ? kHS : C::ZS;
@@ -344,11 +332,11 @@ __device__ __forceinline__ void bwd_step(const char *__restrict__ st, const char
     }
 }
 
-// One window (of NWIN) of the output columns of one tile of stationary rows.
-template <int DZ, int MODE, int NWIN, int WIN>
-__device__ __forceinline__ void bwd_window(const BwdParams &p, char *smem, int logical)
+// One tile of stationary rows.
+template <int DZ, int MODE>
+__device__ __forceinline__ void bwd_tile(const BwdParams &p, char *smem, int logical)
 {
-    using C = BwdCfg<DZ, MODE, NWIN, WIN>;
+    using C = BwdCfg<DZ, MODE>;
     constexpr bool kNeedDP = MODE != FIPA_BWD_DV;
     const int nT = p.Lp / kTileQ;
     const int bh_pos = logical / nT, tile = logical - bh_pos * nT;
@@ -364,13 +352,13 @@ __device__ __forceinline__ void bwd_window(const BwdParams &p, char *smem, int l
     // Stationary rows past the last valid residue of the chain (padding of a ragged batch) take
     // part in nothing: zero gradient.
     if (tile * kTileQ >= kvlen) {
-        float *orow = p.out + ((size_t)bh * p.Lp + srow) * C::D + 32 * WIN * C::NBW;
+        float *orow = p.out + ((size_t)bh * p.Lp + srow) * C::D;
 #pragma unroll
-        for (int nb = 0; nb < C::NBW; ++nb)
+        for (int nb = 0; nb < C::NB; ++nb)
 #pragma unroll
             for (int a = 0; a < 4; ++a)
                 *reinterpret_cast<f32x4 *>(orow + 32 * nb + 8 * a + 4 * g) = (f32x4){0.f, 0.f, 0.f, 0.f};
-        if (WIN == 0 && p.wsum && g == 0) p.wsum[(size_t)bh * p.Lp + srow] = 0.f;
+        if (p.wsum && g == 0) p.wsum[(size_t)bh * p.Lp + srow] = 0.f;
         return;
     }
 
@@ -447,19 +435,17 @@ __device__ __forceinline__ void bwd_window(const BwdParams &p, char *smem, int l
     // operand directly; the accumulators and the small products, which the vector ALU works on,
     // are left to the register allocator (this file is compiled with the MFMA results in the
     // general vector-register class: see build.py).
-    // (At width 576 the two sets are 288 registers: 64 fragments fill the accumulation registers.)
-    constexpr int kPin2 = !kNeedDP ? 0 : (2 * C::KS <= 64 ? C::KS : 64 - C::KS);
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks) {
         asm volatile("" : "+a"(y1f[ks]));
-        if (ks < kPin2) asm volatile("" : "+a"(y2f[ks]));
+        if (kNeedDP) asm volatile("" : "+a"(y2f[kNeedDP ? ks : 0]));
     }
     const float slane = slane_src[srow];
     const float dlane = dlane_src ? dlane_src[srow] : 0.f;
 
-    f32x16 acc[C::NBW];
+    f32x16 acc[C::NB];
 #pragma unroll
-    for (int nb = 0; nb < C::NBW; ++nb)
+    for (int nb = 0; nb < C::NB; ++nb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[nb][r] = 0.f;
     float wsum = 0.f;  // sum over streamed rows of the rounded dS (DQ: row sums, DK: column sums)
@@ -490,25 +476,19 @@ __device__ __forceinline__ void bwd_window(const BwdParams &p, char *smem, int l
         sidx = sidx + 1 < C::NSTAGE ? sidx + 1 : 0;
         // (0xFFFFFFFF: no next block)
         const unsigned next_stage = n + 1 < nblk ? smem_lds + sidx * C::STAGE : 0xFFFFFFFFu;
-        if constexpr (C::PIPELINED) {
-            if (n == 0)
-                bwd_step<C, MODE, WIN, true, false>(st, st_prev, ln, y1f, y2f, acc, wf, wsum, dma, next_stage);
-            else
-                bwd_step_steady<C, MODE, WIN>(st, st_prev, ln, y1f, y2f, acc, wf, wsum, dma, next_stage);
-        } else {
-            // two stages: everything of block n now, while block n+1 loads into the other stage
-            bwd_step<C, MODE, WIN, true, false>(st, st, ln, y1f, y2f, acc, wf, wsum, dma, next_stage);
-            bwd_step<C, MODE, WIN, false, true>(st, st, ln, y1f, y2f, acc, wf, wsum, dma, 0xFFFFFFFFu);
-        }
+        if (n == 0)
+            bwd_step<C, MODE, true, false>(st, st_prev, ln, y1f, y2f, acc, wf, wsum, dma, next_stage);
+        else
+            bwd_step_steady<C, MODE>(st, st_prev, ln, y1f, y2f, acc, wf, wsum, dma, next_stage);
         st_prev = st;
     }
-    if (C::PIPELINED && nblk > 0)
-        bwd_step<C, MODE, WIN, false, true>(st_prev, st_prev, ln, y1f, y2f, acc, wf, wsum, dma, 0xFFFFFFFFu);
+    if (nblk > 0)
+        bwd_step<C, MODE, false, true>(st_prev, st_prev, ln, y1f, y2f, acc, wf, wsum, dma, 0xFFFFFFFFu);
 
     // ---- write acc^T: row srow, columns 32*nb + 8*(r/4) + 4*g + r%4 -------------------------------
-    float *orow = p.out + ((size_t)bh * p.Lp + srow) * C::D + 32 * WIN * C::NBW;
+    float *orow = p.out + ((size_t)bh * p.Lp + srow) * C::D;
 #pragma unroll
-    for (int nb = 0; nb < C::NBW; ++nb)
+    for (int nb = 0; nb < C::NB; ++nb)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
             f32x4 out;
@@ -516,46 +496,32 @@ __device__ __forceinline__ void bwd_window(const BwdParams &p, char *smem, int l
             for (int x = 0; x < 4; ++x) out[x] = acc[nb][4 * a + x];
             *reinterpret_cast<f32x4 *>(orow + 32 * nb + 8 * a + 4 * g) = out;
         }
-    if (WIN == 0 && p.wsum) {  // (every window forms the same sums)
+    if (p.wsum) {
         const float tot = wsum + __shfl_xor(wsum, 32);
         if (g == 0) p.wsum[(size_t)bh * p.Lp + srow] = tot;
     }
 }
 
-template <int DZ, int MODE, int NWIN>
+template <int DZ, int MODE>
 __global__ __launch_bounds__(256, 1) void fipa_bwd_kernel(BwdParams p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    // each XCD gets a contiguous run of tiles; the windows of a tile are neighbours in its launch order
+    // each XCD gets a contiguous run of tiles
     const int chunk = (p.total_tiles + 7) / 8;
-    const int slot = blockIdx.x / 8;
-    const int logical = (blockIdx.x % 8) * chunk + slot / NWIN;
+    const int logical = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
     if (logical >= p.total_tiles) return;
-    if constexpr (NWIN == 1) {
-        bwd_window<DZ, MODE, 1, 0>(p, smem, logical);
-    } else {
-        static_assert(NWIN == 2 || NWIN == 3, "window dispatch");
-        const int win = slot % NWIN;
-        if (win == 0)
-            bwd_window<DZ, MODE, NWIN, 0>(p, smem, logical);
-        else if (NWIN == 2 || win == 1)
-            bwd_window<DZ, MODE, NWIN, 1>(p, smem, logical);
-        else if constexpr (NWIN == 3)
-            bwd_window<DZ, MODE, NWIN, 2>(p, smem, logical);
-    }
+    bwd_tile<DZ, MODE>(p, smem, logical);
 }
 
 template <int DZ, int MODE>
 hipError_t launch(const BwdParams &p, hipStream_t stream)
 {
-    // (DV keeps one set of stationary fragments: half of the output columns fit beside it)
-    constexpr int NWIN = DZ > 256 ? (MODE == FIPA_BWD_DV ? 2 : 3) : 1;
-    using C = BwdCfg<DZ, MODE, NWIN, 0>;
+    using C = BwdCfg<DZ, MODE>;
     static LdsLimit lds_limit;
-    hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_bwd_kernel<DZ, MODE, NWIN>, C::LDS_BYTES);
+    hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_bwd_kernel<DZ, MODE>, C::LDS_BYTES);
     if (e != hipSuccess) return e;
     const int chunk = (p.total_tiles + 7) / 8;
-    hipLaunchKernelGGL((fipa_bwd_kernel<DZ, MODE, NWIN>), dim3(chunk * 8 * NWIN), dim3(256), C::LDS_BYTES, stream, p);
+    hipLaunchKernelGGL((fipa_bwd_kernel<DZ, MODE>), dim3(chunk * 8), dim3(256), C::LDS_BYTES, stream, p);
     return hipGetLastError();
 }
 
@@ -578,8 +544,6 @@ hipError_t launch_bwd_bf16(const BwdParams &p, int DZ, int mode, hipStream_t str
         case 32: return launch_mode<32>(p, mode, stream);
         case 64: return launch_mode<64>(p, mode, stream);
         case 128: return launch_mode<128>(p, mode, stream);
-        case 256: return launch_mode<256>(p, mode, stream);
-        case 512: return launch_mode<512>(p, mode, stream);
         default: return hipErrorInvalidValue;
     }
 }

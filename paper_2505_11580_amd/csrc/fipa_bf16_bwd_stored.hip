@@ -1,0 +1,622 @@
+// Gradient kernels of the backward for r c_z = 256 and 512: the attention weights and their
+// gradients are formed once, kept in memory for a range of query rows, and the three gradients are
+// plain matrix products with them.  Same formulas as fipa_bf16_bwd_kernel.hip:
+//     P_ij  = exp2(S_ij - lse_i),   dS_ij = P_ij (dP_ij - D_i),
+//     dQ^_i = sum_j dS_ij K^_j,   dK^_j = sum_i dS_ij Q^_i,   dV^_j = sum_i P_ij dO^_i.
+//
+//   fipa_bwd_weights_kernel  P and dS' = ln2 dS of 256 keys x (a run of query blocks), bf16
+//   fipa_bwd_accum_kernel    KV: dK^ and dV^ of a key tile;  otherwise dQ^ of a query tile
+//
+// The gradient of z2 wants ln2 dK^_z + dV^_z only, and with dS' both terms are products of stored
+// weights with streamed rows: they share one accumulator, so a key tile's whole gradient is 12 column
+// blocks (r c_z = 256) instead of 20.  The other consumers undo the factor ln2 (see the unpack kernel).
+//
+// Weights of query rows i0 .. i0 + nq - 1, per (batch, head) pair:
+//     W[(i - i0) / 16][key < Lk][16]    bf16, 16 queries 4 g + x | 8 + 4 g + x  (g = 0, 1; x = 0..3) at g 8 + x | g 8 + 4 + x
+// i.e. the MFMA operand order: a lane's share of a 32 x 32 block of S^T is 16 contiguous bytes per 16
+// queries, which the key side reads back as its B operand unchanged and the query side with the
+// transposing LDS read.
+//
+// Why: forming S and dP inside each of the three accumulations costs 612 matrix instructions per 32 x 32 pairs at
+// r c_z = 512 (the accumulators of a window of the columns and two sets of stationary fragments fill the registers, so
+// the small products were formed once per window: S eight times, dP six), 160 at r c_z = 256; with stored weights it is 180
+// and 100, and the products reuse every operand they read from LDS twice.  The price is 10 bytes of memory traffic per
+// pair.  Gradient kernels together, recomputing -> stored:
+//     four chains of 2.7k to 7.1k residues, H = 12, r c_z = 512   29.8 -> 7.7 ms
+//     B = 2, L = 4096, H = 12, r c_z = 256                        1.89 -> 1.38 ms (bound by the weights' 1.6 GB, written
+//                                                                 at 2.7 TB/s; the reason why narrower widths recompute)
+#include "fipa_gfx950.h"
+
+namespace fipa {
+
+namespace {
+
+constexpr float kNegInf = -INFINITY;
+
+__device__ __forceinline__ u32x4 buffer_desc(const void *base)
+{
+    const uint64_t a = (uint64_t)(uintptr_t)base;
+    u32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
+    r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xFFFFu);
+    r[2] = 0x7FFFFFFFu;
+    r[3] = 0x00020000u;
+    return r;
+}
+
+// One direct global -> LDS load, 16 bytes per lane: lane l fetches base + voff + soff and writes LDS byte
+// lds + 16 l.  (s_nop: the wait state between the write of m0 and its use.)
+__device__ __forceinline__ void dma16b(const u32x4 &rsrc, int voff, int soff, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+
+// Completion of everything but the newest N vector-memory operations, and of all LDS reads, before the barrier.
+template <int N>
+__device__ __forceinline__ void wait_and_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+    wg_barrier();
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// P and dS'
+// ---------------------------------------------------------------------------------------------------------------
+// Eight waves of 32 keys each, two per SIMD: the vector work of a block (32 x 32 weights: exponentials, two roundings)
+// is half of the matrix work, and a lone wave does not overlap the two (36 % of the matrix rate with four waves of 64
+// keys); two waves do.
+template <int DZ>
+struct WtCfg {
+    static constexpr int NW = 8, TK = 32 * NW;                // waves, keys of a tile
+    static constexpr int D = kDH + DZ, KS = D / 16, KSH = kDH / 16;
+    static constexpr int ZB = DZ * 2;                         // bytes of a pair-part row
+    static constexpr int ZROWS = 1024 / ZB;                   // rows per 1 KiB load
+    static constexpr int NZW = 32 / ZROWS / NW;               // loads of a pair-part tile per wave
+    // LDS: the pieces of one load ZP bytes apart, so that 16 rows start in 16 different 16-byte slots of the banks; with two
+    // rows per load the odd one has its neighbouring slots exchanged
+    static constexpr int ZP = 1024 + 16 * ZROWS;
+    static constexpr int Q_Z = 0, O_Z = 32 / ZROWS * ZP, Q_H = 2 * O_Z, O_H = Q_H + 4096, SC = O_H + 4096;
+    static constexpr int STAGE = SC + 1024;
+    static constexpr int NST = 3 * STAGE <= 160 * 1024 ? 3 : 2;
+    static constexpr int LDS_BYTES = NST * STAGE;
+    static constexpr int NDMA = 2 * NZW + 1 + 1;
+    static_assert((ZROWS == 1 || ZROWS == 2) && LDS_BYTES <= 160 * 1024, "one load covers whole rows");
+};
+
+template <class C>
+struct WtDma {
+    u32x4 qz, oz, h, sc;
+    int vz, vzo, vh, vsc;  // per-lane offsets
+    int wave, hp;                          // wave; pitch of its head-specific rows (waves 0-3: q^, 4-7: dO^)
+};
+
+template <class C, int DZ, int K>
+__device__ __forceinline__ void wt_issue(const WtDma<C> &d, int row0, unsigned stage)
+{
+    constexpr int ZP = DZ * 2, OP = (kDH + DZ) * 2;
+    if constexpr (K < C::NZW) {
+        const int e = d.wave + C::NW * K;
+        dma16b(d.qz, d.vz, (row0 + e * C::ZROWS) * ZP, stage + C::Q_Z + C::ZP * e);
+    } else if constexpr (K < 2 * C::NZW) {
+        const int e = d.wave + C::NW * (K - C::NZW);
+        dma16b(d.oz, d.vzo, (row0 + e * C::ZROWS) * OP, stage + C::O_Z + C::ZP * e);
+    } else if constexpr (K == 2 * C::NZW) {
+        dma16b(d.h, d.vh, (row0 + 8 * (d.wave & 3)) * d.hp, stage + C::Q_H + 1024 * d.wave);  // (O_H follows Q_H)
+    } else {
+        dma16b(d.sc, d.vsc, row0 * 4, stage + C::SC);  // (every wave: the same values)
+    }
+}
+
+template <int DZ>
+__global__ __launch_bounds__(512, 2) void fipa_bwd_weights_kernel(BwdStoredParams p)
+{
+    using C = WtCfg<DZ>;
+    constexpr int KS = C::KS, KSH = C::KSH, TK = C::TK;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    // units in the order (pair, run of query blocks, key tile), a contiguous run per XCD: neighbours stream the same queries
+    const int per_xcd = (p.units + 7) / 8;
+    const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= (unsigned)per_xcd || logical >= p.units) return;
+    const int nkt = (p.Lp + TK - 1) / TK;
+    const int bh_pos = logical / (nkt * p.nseg), rem = logical - bh_pos * nkt * p.nseg;
+    const int seg = rem / nkt, tile = rem - seg * nkt;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bh = p.deal ? dealt_pair_by_length(bh_pos, p.kvlen, p.B, p.H, lane) : bh_pos;
+    const int b = bh / p.H;
+    const int kvlen = p.deal ? p.kvlen[b] : p.L;
+    // query blocks of this unit, relative to i0
+    const int qb_end = min(p.nq / 32, (kvlen - p.i0 + 31) / 32);
+    const int qb0 = seg * p.seg_blocks;
+    const int nblk = min(p.seg_blocks, qb_end - qb0);
+    if (tile * TK >= kvlen || nblk <= 0) return;
+
+    const size_t rows0 = (size_t)bh * p.Lp;
+    WtDma<C> dma;
+    dma.qz = buffer_desc(p.Qz + rows0 * DZ);
+    dma.oz = buffer_desc(p.dOhat + rows0 * C::D + kDH);
+    dma.h = wave < 4 ? buffer_desc(p.Qh + rows0 * kDH) : buffer_desc(p.dOhat + rows0 * C::D);
+    dma.hp = wave < 4 ? kDH * 2 : C::D * 2;
+    dma.sc = buffer_desc(p.nlse + rows0);
+    dma.wave = wave;
+    {
+        constexpr int SPR = C::ZB / 16;  // slots per row
+        const int rz = lane / SPR, sz = (lane % SPR) ^ (C::ZROWS == 2 ? rz : 0);
+        dma.vz = rz * (DZ * 2) + sz * 16;
+        dma.vzo = rz * (C::D * 2) + sz * 16;
+        const int r = lane >> 3, row = 8 * wave + r, slot = (lane & 7) ^ ((row >> 1) & 7);
+        dma.vh = r * dma.hp + slot * 16;
+        // (lanes 0-7: 32 values of -lse; lanes 8-15: 32 values of D; the others repeat lane 0)
+        dma.vsc = lane < 8 ? lane * 16 : (lane < 16 ? p.d_minus_nlse + (lane - 8) * 16 : 0);
+    }
+    const unsigned lds0 = lds_address(smem);
+    const int first_row = p.i0 + 32 * qb0;
+    auto issue_all = [&](int n, unsigned stage) {
+        static_for<C::NDMA>([&](auto K) { wt_issue<C, DZ, decltype(K)::value>(dma, first_row + 32 * min(n, nblk - 1), stage); });
+    };
+    issue_all(0, lds0);
+    if (C::NST == 3) issue_all(1, lds0 + C::STAGE);
+
+    // stationary fragments: key tile * TK + 32 wave + li
+    bf16x8 kf[KSH], vf[KSH], zf[KS - KSH];
+    const int key = tile * TK + 32 * wave + li;
+    const size_t row = min(key, p.Lp - 1);
+    {
+        const bf16_t *kr = p.Kh + (rows0 + row) * kDH + 8 * g, *vr = p.Vh + (rows0 + row) * kDH + 8 * g;
+        const bf16_t *zr = p.Z2 + ((size_t)b * p.Lp + row) * DZ + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < KSH; ++ks) {
+            kf[ks] = *reinterpret_cast<const bf16x8 *>(kr + 16 * ks);
+            vf[ks] = *reinterpret_cast<const bf16x8 *>(vr + 16 * ks);
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS - KSH; ++ks) zf[ks] = *reinterpret_cast<const bf16x8 *>(zr + 16 * ks);
+    }
+    const float slane = key < p.Lp ? p.kbias[rows0 + row] : kNegInf;
+    // (to accumulation registers, where the MFMAs read their B operand as well)
+#pragma unroll
+    for (int ks = 0; ks < KS - KSH; ++ks) asm volatile("" : "+a"(zf[ks]));
+
+    // per-lane LDS offsets: row li, 16-byte slot 2 ks + g (head-specific rows: XOR-ed with the row)
+    const int az = (li / C::ZROWS) * C::ZP + (li % C::ZROWS) * C::ZB + (C::ZROWS == 2 ? g ^ (li & 1) : g) * 16;
+    int ah[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) ah[x] = li * 128 + ((2 * x + g) ^ ((li >> 1) & 7)) * 16;
+
+    // destination: [16-query group][key][16], a uniform base per block and this lane's bytes
+    const size_t grp_bytes = (size_t)p.Lk * 32;
+    const size_t wofs = ((size_t)bh * (p.nq_alloc / 16) + 2 * (size_t)qb0) * grp_bytes + (size_t)tile * TK * 32;
+    char *wp = reinterpret_cast<char *>(p.Wp) + wofs, *ws = reinterpret_cast<char *>(p.Ws) + wofs;
+    const unsigned wlane = (32 * wave + li) * 32 + 16 * g;
+
+    f32x16 s, pr, dp;
+    bf16x8 fr[4];
+    unsigned pk[4];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) pr[r] = dp[r] = 0.f;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) fr[x] = bf16x8{};  // (the first block has no predecessor: products with zero)
+
+    // The 2 KS operand reads of a block (first of q^, then of dO^) run kLA ahead of the MFMAs that use them,
+    // across the block boundary too.  The weights P of a block are formed among the dP MFMAs, its dS'
+    // among the S MFMAs of the next block.
+    constexpr int kLA = 3, NF = 2 * KS, NP = 8;  // NP: pairs of neighbouring weights of a lane
+    static_assert(NF % 4 == 0, "operand ring");
+    auto p_pair = [&](int t) {  // pair t of P: exponentials, rounding, and the store of a finished 16 bytes
+        const int r = 2 * t;
+        const float e0 = __builtin_amdgcn_exp2f(s[r]), e1 = __builtin_amdgcn_exp2f(s[r + 1]);
+        pr[r] = kLn2 * e0;
+        pr[r + 1] = kLn2 * e1;
+        pk[t & 3] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){e0, e1}, bf16x2));
+        if ((t & 3) == 3) *reinterpret_cast<u32x4 *>(wp + (t >> 2) * grp_bytes + wlane) = (u32x4){pk[0], pk[1], pk[2], pk[3]};
+    };
+    auto s_pair = [&](int t) {
+        const int r = 2 * t;
+        const f32x2 d = {pr[r] * dp[r], pr[r + 1] * dp[r + 1]};
+        pk[t & 3] = __builtin_bit_cast(unsigned, __builtin_convertvector(d, bf16x2));
+        if ((t & 3) == 3) *reinterpret_cast<u32x4 *>(ws + (t >> 2) * grp_bytes + wlane) = (u32x4){pk[0], pk[1], pk[2], pk[3]};
+    };
+    auto mfma_of = [&](auto F) {  // the MFMA of operand F
+        constexpr int f = decltype(F)::value, ks = f % KS;
+        if constexpr (f < KS) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[f % 4], ks < KSH ? kf[ks % KSH] : zf[ks < KSH ? 0 : ks - KSH], s, 0, 0, 0);
+        else dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[f % 4], ks < KSH ? vf[ks % KSH] : zf[ks < KSH ? 0 : ks - KSH], dp, 0, 0, 0);
+    };
+    // Vector-memory operations complete in the order they are issued: per block first the loads of a later one, then
+    // kStores stores (of the weights, which may take their time: a block waits only for what is older than its loads).
+    constexpr int kStores = 4, kDmaOps = (C::NDMA + 1) / 2;  // loads go out two per operand
+    static_assert(kDmaOps + NP <= KS, "loads, then dS' among the S MFMAs");
+    int sidx = 0;
+    for (int n = 0; n < nblk; ++n) {
+        if (n == 0) wait_and_barrier<(C::NST - 2) * C::NDMA>();
+        else if (n == 1 || C::NST == 2) wait_and_barrier<(C::NST - 2) * C::NDMA + kStores>();
+        else wait_and_barrier<(C::NST - 2) * (C::NDMA + kStores) + kStores>();
+        const char *st = smem + sidx * C::STAGE;
+        int nidx = sidx + C::NST - 1;
+        nidx = nidx >= C::NST ? nidx - C::NST : nidx;
+        const unsigned next = lds0 + nidx * C::STAGE;
+        const int next_row = first_row + 32 * min(n + C::NST - 1, nblk - 1);
+        const bool prev = n > 0;
+        static_for<NF>([&](auto J) {
+            constexpr int j = decltype(J)::value, ks = j % KS;
+            {
+                const char *a = ks < KSH ? st + (j < KS ? C::Q_H : C::O_H) + ah[ks & 3]
+                                         : st + (j < KS ? C::Q_Z : C::O_Z) + az + (ks - KSH) * 32;
+                fr[j % 4] = *reinterpret_cast<const bf16x8 *>(a);
+            }
+            if constexpr (j < kLA) {
+                mfma_of(std::integral_constant<int, NF + j - kLA>{});
+            } else {
+                constexpr int f = j - kLA;
+                if constexpr (f == 0 || f == KS) {  // start values of S / dP
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        const f32x4 sv = *reinterpret_cast<const f32x4 *>(st + C::SC + (f == 0 ? 0 : 128) + (8 * a + 4 * g) * 4);
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) {
+                            if constexpr (f == 0) s[4 * a + x] = sv[x] + slane;
+                            else dp[4 * a + x] = sv[x];  // (-D)
+                        }
+                    }
+                }
+                mfma_of(std::integral_constant<int, f>{});
+                if constexpr (f < kDmaOps) {
+                    wt_issue<C, DZ, 2 * f>(dma, next_row, next);
+                    if constexpr (2 * f + 1 < C::NDMA) wt_issue<C, DZ, 2 * f + 1>(dma, next_row, next);
+                }
+                if constexpr (f >= kDmaOps && f < KS) {  // (first block: zeros, where the second one's turn writes the values)
+#pragma unroll
+                    for (int t = (f - kDmaOps) * NP / (KS - kDmaOps); t < (f - kDmaOps + 1) * NP / (KS - kDmaOps); ++t) s_pair(t);
+                    if constexpr (f == KS - 1) ws += prev ? 2 * grp_bytes : 0;
+                }
+                if constexpr (f >= KS + 2)  // (the last kLA operands of the block are multiplied after the next barrier)
+#pragma unroll
+                    for (int t = (f - KS - 2) * NP / (KS - 2 - kLA); t < (f - KS - 1) * NP / (KS - 2 - kLA); ++t)
+                        if (t < NP) p_pair(t);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        wp += 2 * grp_bytes;
+        sidx = sidx + 1 < C::NST ? sidx + 1 : 0;
+    }
+    static_for<kLA>([&](auto J) { mfma_of(std::integral_constant<int, NF + decltype(J)::value - kLA>{}); });
+#pragma unroll
+    for (int t = 0; t < NP; ++t) s_pair(t);
+    wait_vmem<0>();  // (the loads of blocks past the last one still write LDS)
+}
+
+// acc += A B with the accumulator in accumulation (a) or architectural (v) registers.  Up to 20 accumulators are live:
+// left to the register allocator, it moved them between the two files inside the loop (500 of its 670 instructions).
+// (s_nop: an operand may come out of a vector instruction right before.)
+__device__ __forceinline__ void mfma_a(f32x16 &acc, const bf16x8 &a, const bf16x8 &b)
+{
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_v(f32x16 &acc, const bf16x8 &a, const bf16x8 &b)
+{
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+// Results of these may be read by vector instructions only some cycles later, which the compiler does not know.
+__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+// ---------------------------------------------------------------------------------------------------------------
+// The three gradients
+// ---------------------------------------------------------------------------------------------------------------
+// A step multiplies 32 streamed rows: KV: 16 queries, as rows 0-15 from q^ (against dS') and rows 16-31 from dO^
+// (against P); else 32 keys, rows of k^ (against dS').  Per stage: 32 rows of ZBL 32-column blocks of the pair
+// part, 32 rows of the head-specific part, and the weights of the tile's stationary rows.
+template <bool KV, int DZ, int HV, int ZBLOCKS, int WIN>
+struct AcCfg {
+    static constexpr int ZBL = ZBLOCKS;                        // pair-part blocks of a window
+    static constexpr int NWIN = DZ / 32 / ZBL;
+    static constexpr int Z0 = 32 * ZBL * WIN;                  // first pair-part column
+    static constexpr bool HA = WIN == 0;                       // head-specific columns of dQ^, or of dK^
+    static constexpr bool HB = KV && WIN == NWIN - 1;          // ... of dV^
+    static constexpr int RB = 64 * ZBL;                        // bytes of a pair-part row
+    static constexpr int ER = 1024 / RB;                       // rows per load
+    static constexpr int NZW = 32 * RB / 1024 / 4;             // pair-part loads per wave
+    static constexpr int NWW = 2 * HV;                         // weight loads per wave (8 KiB per half tile and 16 rows)
+    static constexpr int Z_OFF = 0, H_OFF = 32 * RB, W_OFF = H_OFF + 4096;
+    static constexpr int STAGE = W_OFF + 8192 * HV;
+    static constexpr int NST = 4, LDS_BYTES = NST * STAGE;
+    static constexpr int NDMA = NZW + 1 + NWW;
+    static constexpr int N0 = (HA ? 2 : 0) + ZBL, N1 = ((KV ? HB : HA) ? 2 : 0) + ZBL;  // operands of the two k-steps
+    static constexpr int NF = N0 + N1;
+    static constexpr int RING = NF % 4 == 0 ? 4 : (NF % 5 == 0 ? 5 : 6);
+    static constexpr int NHB = (HA ? 2 : 0) + (HB ? 2 : 0);    // head-specific accumulator blocks
+    static_assert(NF % RING == 0 && LDS_BYTES <= 160 * 1024, "ring and LDS");
+};
+
+template <bool KV, int DZ, int HV, int ZBL, int WIN>
+__device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *smem, int logical)
+{
+    using C = AcCfg<KV, DZ, HV, ZBL, WIN>;
+    constexpr int D = kDH + DZ, TS = 128 * HV;  // stationary rows of a tile
+    const int nt = ((KV ? p.Lp : p.nq) + TS - 1) / TS;
+    const int bh_pos = logical / nt, tile = logical - bh_pos * nt;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bh = p.deal ? dealt_pair_by_length(bh_pos, p.kvlen, p.B, p.H, lane) : bh_pos;
+    const int b = bh / p.H;
+    const int kvlen = p.deal ? p.kvlen[b] : p.L;
+    const int row_lo = (KV ? 0 : p.i0) + tile * TS;         // first stationary row
+    const int nvalid = min(kvlen, p.i0 + p.nq);             // (KV: end of the queries of this range)
+    // steps of 16 queries (whole blocks of 32), or of 32 keys
+    const int nstep = row_lo >= kvlen ? 0 : (KV ? max(0, (nvalid - p.i0 + 31) / 32) * 2 : (kvlen + 31) / 32);
+    if (KV && p.i0 > 0 && nstep == 0) return;               // (a later range of queries adds nothing)
+
+    const size_t rows0 = (size_t)bh * p.Lp;
+    f32x16 acch[C::NHB > 0 ? C::NHB : 1][HV], accz[C::ZBL][HV];
+    float wsum[HV];
+    auto outputs = [&](auto &&f) {  // f(pointer of the lane's row, accumulator) of every block
+#pragma unroll
+        for (int hv = 0; hv < HV; ++hv) {
+            const int row = row_lo + 32 * (HV * wave + hv) + li;
+            const size_t r = rows0 + min(row, p.Lp - 1);
+            if constexpr (KV) {
+                if constexpr (C::HA)
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) f(p.dKh + r * kDH + 32 * nb, acch[nb][hv], row);
+                if constexpr (C::HB)
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) f(p.dVh + r * kDH + 32 * nb, acch[C::NHB - 2 + nb][hv], row);
+#pragma unroll
+                for (int nb = 0; nb < C::ZBL; ++nb) f(p.dZ + r * DZ + C::Z0 + 32 * nb, accz[nb][hv], row);
+            } else {
+                if constexpr (C::HA)
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) f(p.dQ + r * D + 32 * nb, acch[nb][hv], row);
+#pragma unroll
+                for (int nb = 0; nb < C::ZBL; ++nb) f(p.dQ + r * D + kDH + C::Z0 + 32 * nb, accz[nb][hv], row);
+            }
+        }
+    };
+    float *const sums = KV ? p.colsum : p.rowsum;
+#pragma unroll
+    for (int hv = 0; hv < HV; ++hv) wsum[hv] = 0.f;
+    outputs([&](const float *, f32x16 &a, int) {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) a[x] = 0.f;
+    });
+
+    if (nstep > 0) {
+        // ---- direct loads: sources, per-lane offsets -----------------------------------------------------------
+        const size_t wpair = (size_t)bh * (p.nq_alloc / 16) * p.Lk * 16;
+        const u32x4 r_z0 = buffer_desc(KV ? p.Qz + rows0 * DZ + C::Z0 : p.Z2 + (size_t)b * p.Lp * DZ + C::Z0);
+        const u32x4 r_z1 = buffer_desc(p.dOhat + rows0 * D + kDH + C::Z0);  // KV only
+        const u32x4 r_h = KV ? (wave < 2 ? buffer_desc(p.Qh + rows0 * kDH) : buffer_desc(p.dOhat + rows0 * D))
+                             : buffer_desc(p.Kh + rows0 * kDH);
+        const u32x4 r_w0 = buffer_desc(p.Ws + wpair), r_w1 = buffer_desc(p.Wp + wpair);
+        constexpr int ZP0 = DZ * 2, ZP1 = D * 2;
+        const int hp = KV && wave >= 2 ? D * 2 : kDH * 2;
+        int vz0, vz1, vh;
+        {
+            constexpr int SPR = C::RB / 16;
+            const int r = lane / SPR, vr = wave * C::ER + r;  // (the other loads of the wave: 4 ER k rows further, same row mod 4)
+            const int slot = (lane % SPR) ^ ((vr & 3 & (C::ZBL - 1)) << 2);
+            vz0 = r * ZP0 + slot * 16;
+            vz1 = r * ZP1 + slot * 16;
+            const int rh = lane >> 3, slh = (lane & 7) ^ (((rh >> 1) & 1) << 2);
+            vh = rh * hp + slh * 16;
+        }
+        const int vw = lane * 16;
+        const unsigned lds0 = lds_address(smem);
+        const int grp_bytes = p.Lk * 32;                                  // one group of 16 queries
+        const int wrow = KV ? row_lo * 32 : (row_lo - p.i0) / 16 * grp_bytes;  // this tile's first weight
+        const int max_grp = p.nq_alloc / 16 - 1 - (row_lo - p.i0) / 16;   // (dQ^: last group of the range, relative to the tile)
+        auto issue = [&](auto Kc, int n, unsigned stage) {
+            constexpr int K = decltype(Kc)::value;
+            if constexpr (K < C::NZW) {
+                const int e = wave + 4 * K, vr = e * C::ER;
+                constexpr bool second = KV && K >= C::NZW / 2;  // rows 16-31
+                const int row = KV ? p.i0 + 16 * n + (vr & 15) : 32 * n + vr;
+                if constexpr (second) dma16b(r_z1, vz1, row * ZP1, stage + C::Z_OFF + 1024 * e);
+                else dma16b(r_z0, vz0, row * ZP0, stage + C::Z_OFF + 1024 * e);
+            } else if constexpr (K == C::NZW) {
+                const int row = KV ? p.i0 + 16 * n + (8 * wave & 15) : 32 * n + 8 * wave;
+                dma16b(r_h, vh, row * hp, stage + C::H_OFF + 1024 * wave);
+            } else {
+                constexpr int k = K - C::NZW - 1;
+                const int e = wave + 4 * k;  // 1 KiB pieces
+                if constexpr (KV) {
+                    constexpr bool second = k >= C::NWW / 2;
+                    const int o = wrow + n * grp_bytes + 1024 * (second ? e - 4 * HV : e);
+                    if constexpr (second) dma16b(r_w1, vw, o, stage + C::W_OFF + 1024 * e);
+                    else dma16b(r_w0, vw, o, stage + C::W_OFF + 1024 * e);
+                } else {
+                    dma16b(r_w0, vw, wrow + min(e, max_grp) * grp_bytes + n * 1024, stage + C::W_OFF + 1024 * e);
+                }
+            }
+        };
+        auto issue_all = [&](int n, unsigned stage) { static_for<C::NDMA>([&](auto K) { issue(K, min(n, nstep - 1), stage); }); };
+#pragma unroll
+        for (int n = 0; n < C::NST - 1; ++n) issue_all(n, lds0 + n * C::STAGE);
+
+        // ---- per-lane LDS offsets --------------------------------------------------------------------------------
+        const int l16 = lane & 15, grp2 = (lane >> 4) & 1, e4 = l16 >> 2, j4 = l16 & 3;
+        int az[4], ah[2];
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+            az[x] = C::Z_OFF + (4 * g + e4) * C::RB + ((x ^ e4) & (C::ZBL < 4 ? C::ZBL - 1 : 3)) * 64 + (16 * grp2 + 4 * j4) * 2;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) ah[x] = C::H_OFF + (4 * g + e4) * 128 + (x ^ (e4 >> 1)) * 64 + (16 * grp2 + 4 * j4) * 2;
+        // weights: KV: one 16-byte read per half; else two transposing reads (queries 4 j4 .. of group grp2, stored in the order 0, 8, 4, 12)
+        const int aw = C::W_OFF + (KV ? (HV * wave * 32 + li) * 32 + g * 16
+                                      : (2 * HV * wave + grp2) * 1024 + (4 * g + e4) * 32 + ((j4 & 1) * 2 + (j4 >> 1)) * 8);
+
+        bf16x8 fr[C::RING] = {}, w0[HV], w1[HV] = {};  // (the first step has no predecessor: products with zero)
+        auto join = [](bf16x4 lo, bf16x4 hi) {
+            bf16x8 v;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                v[x] = lo[x];
+                v[4 + x] = hi[x];
+            }
+            return v;
+        };
+        auto weights = [&](const char *st, int t, int hv) -> bf16x8 {
+            if constexpr (KV) return *reinterpret_cast<const bf16x8 *>(st + aw + t * 4096 * HV + hv * 1024);
+            const char *a = st + aw + hv * 2048 + t * 512;
+            return join(lds_read_tr(a), lds_read_tr(a + 256));
+        };
+        // operand f: k-step 0 (head-specific blocks first), then k-step 1
+        auto fetch = [&](const char *st, auto F) -> bf16x8 {
+            constexpr int f = decltype(F)::value, t = f >= C::N0 ? 1 : 0, x = f - t * C::N0;
+            constexpr int nh = t == 0 ? C::N0 - C::ZBL : C::N1 - C::ZBL;
+            if constexpr (x < nh) {
+                const char *a = st + ah[x] + 16 * t * 128;
+                return join(lds_read_tr(a), lds_read_tr(a + 8 * 128));
+            } else {
+                constexpr int nb = x - nh;
+                const char *a = st + az[nb & 3] + (nb & ~3) * 64 + 16 * t * C::RB;
+                return join(lds_read_tr(a), lds_read_tr(a + 8 * C::RB));
+            }
+        };
+        auto mfma_of = [&](auto F) {
+            constexpr int f = decltype(F)::value, t = f >= C::N0 ? 1 : 0, x = f - t * C::N0;
+            constexpr int nh = t == 0 ? C::N0 - C::ZBL : C::N1 - C::ZBL;
+#pragma unroll
+            for (int hv = 0; hv < HV; ++hv) {
+                const bf16x8 &w = t ? w1[hv] : w0[hv];
+                if constexpr (x < nh) mfma_v(acch[(KV && t == 1 ? C::NHB - 2 : 0) + x][hv], fr[f % C::RING], w);
+                else mfma_a(accz[x - nh][hv], fr[f % C::RING], w);
+            }
+        };
+        const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+        auto add_sums = [&](const bf16x8 (&w)[HV]) {
+#pragma unroll
+            for (int hv = 0; hv < HV; ++hv)
+#pragma unroll
+                for (int x = 0; x < 8; x += 2) wsum[hv] = __builtin_amdgcn_fdot2_f32_bf16((bf16x2){w[hv][x], w[hv][x + 1]}, ones, wsum[hv], false);
+        };
+        constexpr int kLA = 3;
+        for (int n = 0; n < nstep; ++n) {
+            wait_and_barrier<(C::NST - 2) * C::NDMA>();  // step n has landed; the stage of step n - 1 is free
+            const char *st = smem + (n & 3) * C::STAGE;
+            const unsigned next = lds0 + ((n + 3) & 3) * C::STAGE;
+            const int nn = min(n + 3, nstep - 1);
+#pragma unroll
+            for (int hv = 0; hv < HV; ++hv) w0[hv] = weights(st, 0, hv);
+            static_for<C::NF>([&](auto J) {
+                constexpr int j = decltype(J)::value;
+                fr[j % C::RING] = fetch(st, J);
+                if constexpr (j < kLA) {
+                    mfma_of(std::integral_constant<int, C::NF + j - kLA>{});
+                } else {
+                    mfma_of(std::integral_constant<int, j - kLA>{});
+                }
+                if constexpr (j == kLA)
+#pragma unroll
+                    for (int hv = 0; hv < HV; ++hv) w1[hv] = weights(st, 1, hv);
+                if constexpr (j >= kLA && j - kLA < C::NDMA) issue(std::integral_constant<int, j - kLA>{}, nn, next);
+                if constexpr (C::HA && j == kLA + 2) add_sums(w0);
+                if constexpr (C::HA && !KV && j == kLA + 6) add_sums(w1);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+        static_for<kLA>([&](auto J) { mfma_of(std::integral_constant<int, C::NF + decltype(J)::value - kLA>{}); });
+        wait_vmem<0>();  // (the loads past the last step still write LDS)
+        mfma_drain();
+#pragma unroll
+        for (int hv = 0; hv < HV; ++hv) {  // (orders every use of the accumulators behind the wait)
+#pragma unroll
+            for (int nb = 0; nb < C::ZBL; ++nb) asm volatile("" : "+a"(accz[nb][hv]));
+#pragma unroll
+            for (int nb = 0; nb < C::NHB; ++nb) asm volatile("" : "+v"(acch[nb][hv]));
+        }
+    }
+
+    const bool add = KV && p.i0 > 0;  // later ranges of queries add to the sums of the earlier ones
+    outputs([&](float *dst, f32x16 &a, int row) {
+        if (row >= p.Lp) return;
+        const bool in = row < kvlen;  // (rows past the chain: whatever the tile held there)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (add) v = *reinterpret_cast<const f32x4 *>(dst + 8 * q + 4 * g);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[x] = in ? v[x] + a[4 * q + x] : 0.f;
+            *reinterpret_cast<f32x4 *>(dst + 8 * q + 4 * g) = v;
+        }
+    });
+    if (C::HA)
+#pragma unroll
+        for (int hv = 0; hv < HV; ++hv) {
+            const int row = row_lo + 32 * (HV * wave + hv) + li;
+            const float tot = wsum[hv] + __shfl_xor(wsum[hv], 32);
+            if (g == 0 && row < p.Lp) sums[rows0 + row] = row < kvlen ? (add ? sums[rows0 + row] : 0.f) + tot : 0.f;
+        }
+}
+
+template <bool KV, int DZ, int HV, int ZBL>
+__global__ __launch_bounds__(256, 1) void fipa_bwd_accum_kernel(BwdStoredParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    constexpr int NWIN = AcCfg<KV, DZ, HV, ZBL, 0>::NWIN;
+    // each XCD gets a contiguous run of tiles; the windows of a tile are neighbours in its launch order
+    const int per_xcd = (p.units + 7) / 8;
+    const int slot = blockIdx.x / 8;
+    const int logical = (blockIdx.x % 8) * per_xcd + slot / NWIN;
+    if (slot / NWIN >= per_xcd || logical >= p.units) return;
+    if (NWIN == 1 || slot % NWIN == 0) accum_window<KV, DZ, HV, ZBL, 0>(p, smem, logical);
+    else accum_window<KV, DZ, HV, ZBL, NWIN - 1>(p, smem, logical);
+}
+
+template <class K>
+hipError_t launch_kernel(K kernel, LdsLimit &limit, int threads, int lds, int blocks, const BwdStoredParams &p, hipStream_t stream)
+{
+    const hipError_t e = raise_lds_limit(limit, (const void *)kernel, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), lds, stream, p);
+    return hipGetLastError();
+}
+
+constexpr int kCU = 256;
+
+template <bool KV, int DZ, int HV, int ZBL>
+hipError_t launch_accum(BwdStoredParams p, hipStream_t stream)
+{
+    using C = AcCfg<KV, DZ, HV, ZBL, 0>;
+    static LdsLimit limit;
+    p.units = p.B * p.H * (((KV ? p.Lp : p.nq) + 128 * HV - 1) / (128 * HV));
+    return launch_kernel(fipa_bwd_accum_kernel<KV, DZ, HV, ZBL>, limit, 256, C::LDS_BYTES, (p.units + 7) / 8 * 8 * C::NWIN, p, stream);
+}
+
+template <int DZ>
+hipError_t launch_weights(BwdStoredParams p, hipStream_t stream)
+{
+    static LdsLimit limit;
+    const int tiles = p.B * p.H * ((p.Lp + WtCfg<DZ>::TK - 1) / WtCfg<DZ>::TK);
+    // no sums across query blocks here, so a key tile's queries may be cut into runs; each run loads its keys again
+    // (about 10 us).  Runs of 64 blocks, shorter while they leave the chip less than three rounds.  Measured (runs of
+    // 16 / 32 / 64 / 128 blocks): B = 2, L = 4096, r c_z = 256: 674 / 614 / 589 / 676 us; L = 2048: 168 / 182 / 178 / 177 us.
+    const int qblocks = p.nq / 32;
+    int run = 64;
+    while (run > 16 && tiles * ((qblocks + run - 1) / run) < 3 * kCU) run /= 2;
+    p.nseg = (qblocks + run - 1) / run;
+    p.seg_blocks = (qblocks + p.nseg - 1) / p.nseg;
+    p.units = tiles * p.nseg;
+    return launch_kernel(fipa_bwd_weights_kernel<DZ>, limit, 512, WtCfg<DZ>::LDS_BYTES, (p.units + 7) / 8 * 8, p, stream);
+}
+
+}  // namespace
+
+hipError_t launch_bwd_stored_bf16(const BwdStoredParams &p0, int DZ, hipStream_t stream)
+{
+    for (int i0 = 0; i0 < p0.Lp; i0 += p0.nq_alloc) {
+        BwdStoredParams p = p0;
+        p.i0 = i0;
+        p.nq = p0.Lp - i0 < p0.nq_alloc ? p0.Lp - i0 : p0.nq_alloc;
+        hipError_t e = DZ == 256 ? launch_weights<256>(p, stream) : launch_weights<512>(p, stream);
+        if (e != hipSuccess) return e;
+        e = DZ == 256 ? launch_accum<true, 256, 2, 8>(p, stream) : launch_accum<true, 512, 2, 8>(p, stream);
+        if (e != hipSuccess) return e;
+        e = DZ == 256 ? launch_accum<false, 256, 2, 8>(p, stream) : launch_accum<false, 512, 2, 8>(p, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace fipa

@@ -311,6 +311,24 @@ struct BwdParams {
     int deal;     // set for masked batches: chain lengths come from kvlen, and the (batch, head) pairs are renumbered (see dealt_pair_by_length)
 };
 
+// The gradient kernels that keep the weights of a range of query rows in memory (fipa_bf16_bwd_stored.hip).
+// dS' = ln2 dS throughout, so dQ, dKh and the two sums come out times ln2, and dZ = ln2 dK^_z + dV^_z.
+struct BwdStoredParams {
+    const bf16_t *Qh, *Qz, *Kh, *Vh, *Z2, *dOhat;
+    const float *kbias, *nlse;
+    const int *kvlen;
+    bf16_t *Wp, *Ws;      // P and dS' of query rows i0 .. i0 + nq - 1 of every pair: [B H][nq_alloc / 16][Lk][16]
+    float *dQ;            // [B,H,Lp,64+DZ]
+    float *dKh, *dVh;     // [B,H,Lp,64] head-specific columns
+    float *dZ;            // [B,H,Lp,DZ]
+    float *rowsum, *colsum;
+    int d_minus_nlse;     // bytes from nlse to the vector D
+    int B, L, Lp, H, deal;
+    int Lk;               // Lp rounded up to 256: keys per group of weights
+    int nq_alloc, i0, nq; // query rows the buffers hold; this range
+    int units, nseg, seg_blocks;
+};
+
 struct BwdPackParams {
     const float *d_o, *d_o_pts, *d_o_pair, *rot, *Ohat, *lse2;
     const bf16_t *z1;
@@ -319,6 +337,7 @@ struct BwdPackParams {
     bf16_t *dOhat;
     float *Dvec, *nlse;
     int B, L, Lp, H, c, Pv, cz, r, DZ;
+    bool neg_d;  // store -D
 };
 
 struct BwdUnpackParams {
@@ -326,7 +345,11 @@ struct BwdUnpackParams {
     const float *rot, *trans, *cen, *gamma, *w_b, *d_o_pair, *d_o_pts;
     const uint8_t *mask;
     const int *cu;  // packed batch: row offsets of the chains (see user_row), else null
-    const float *dQhat, *dKhat, *dVhat, *Ohat, *rowsum, *colsum;
+    const float *dQhat, *Ohat, *rowsum, *colsum;
+    const float *dKh, *dVh;  // head-specific columns of dK^, dV^, rows `h_pitch` apart
+    const float *dKz, *dVz;  // pair columns, rows `z_pitch` apart; dVz null: dKz holds ln2 dK^_z + dV^_z
+    int h_pitch, z_pitch;
+    float ds_inv;            // dS over the stored dS' (1, or log2e where dQ^, dK^ and the sums carry a factor ln2)
     bf16_t *d_q, *d_k, *d_v, *d_q_pts, *d_k_pts, *d_v_pts, *d_z1, *d_z2;
     float *gpart;   // [B,H,Lp] per-(b,h,i) contribution to d gamma
     float *d_gamma; // [H]
@@ -339,6 +362,7 @@ struct BwdUnpackParams {
 };
 
 hipError_t launch_bwd_bf16(const BwdParams &p, int DZ, int mode, hipStream_t stream);
+hipError_t launch_bwd_stored_bf16(const BwdStoredParams &p, int DZ, hipStream_t stream);
 hipError_t launch_bwd_pack_bf16(const BwdPackParams &p, hipStream_t stream);
 hipError_t launch_bwd_unpack_bf16(const BwdUnpackParams &p, hipStream_t stream);
 
