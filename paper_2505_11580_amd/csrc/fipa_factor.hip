@@ -80,154 +80,218 @@ __global__ __launch_bounds__(256) void fipa_factor_project_kernel(const int *__r
 // LDS float atomics 8.6 ms) or loses the fixed summation order.  Here it is the contraction it
 // also is, over the residue axis: dE_s [rows, 64 columns] = X_s^T [rows, residues] . dZ [residues, 64],
 // with X_s the one-hot features of slot s -- exact in bf16 -- on the matrix pipe with float32
-// accumulation in a fixed order (the same bits on every run).  One workgroup per (slot, 64 output
-// columns) walks the residues in tiles of 128: every thread fetches 64 bytes of d_z (16-byte loads, in
-// flight while the two tiles before it are multiplied) and hands them over through LDS as they are
-// ([residue][column]; the matrix operand is taken from there with the transposing read); one
-// thread per residue marks that residue's (up to three) rows in the one-hot tile ([row][residue]) and
-// takes back the marks it made two tiles earlier, so the tile never needs clearing as a whole; one
-// barrier per tile; the 2 x ceil(rows / 32) output tiles are dealt to the four waves.  0.32 ms at 32768
-// residues, 20 slots, 82 rows, 512 columns.
+// accumulation in a fixed order (the same bits on every run).
+//
+// One workgroup per (slot, 64 output columns), eight waves, each of which takes every eighth tile of 32
+// residues with all rows of the tables: nothing is shared between waves until their sums are added at the
+// end, so there is no barrier in the loop, and two waves per SIMD cover each other.  A tile's d_z rows,
+// indices, bins and mask arrive by direct loads three tiles ahead; d_z is read with the transposing LDS
+// read, and the one-hot operand is formed in registers: a lane owns a table row and compares it with the
+// 16-bit codes of its eight residues (three packed instructions per two residues).
+// 32768 residues (half of them valid), 20 slots, 82 rows, 512 columns: 555 us with four waves that shared each tile and marked
+// a one-hot tile in LDS (one barrier per tile, the mask on the way of every load) -> 137 us.
 // rows = n_bins + n_pos + 1 (the last one collects the bias gradient, in slot 0's workgroups).
-constexpr int kFbTile = 128;
-constexpr int kFbStride = kFbTile * 2 + 16;  // bytes per row of the one-hot tile ([row][residue])
-constexpr int kFbZStride = 64 * 2 + 16;      // bytes per row of the d_z tile ([residue][column])
-constexpr int kFbMaxRowBlocks = 5, kFbMaxOwn = (2 * kFbMaxRowBlocks + 3) / 4;
+constexpr int kFbWaves = 8, kFbStages = 4, kFbMaxRowBlocks = 5;
+constexpr int kFbZ = 32 * 128;                          // a tile's d_z: 32 rows of 64 columns, the 64-byte halves of a row exchanged in every other pair of rows
+constexpr int kFbStage = kFbZ + 256 + 256;              // | 32 indices, 32 bins | 64 mask values
+constexpr int kFbCodes = kFbStages * kFbStage;          // 3 x 32 16-bit row numbers: by bin, by position code, bias
+constexpr int kFbWaveBytes = kFbCodes + 256;
+static_assert(kFbWaves * kFbWaveBytes <= 160 * 1024, "LDS");
 
-template <bool HAS_POS>
-__global__ __launch_bounds__(256) void fipa_factor_backward_kernel(const int *__restrict__ nbr_idx, const int *__restrict__ nbr_bin,
-                                                                   const bf16_t *__restrict__ d_z, const uint8_t *__restrict__ mask,
-                                                                   float *__restrict__ d_e_bin, float *__restrict__ d_e_pos,
-                                                                   float *__restrict__ d_bias, int rows, int L, int k, int n_bins,
-                                                                   int n_pos, int pos_mode, int n_out, int RB)
+typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+
+// One direct load of 4 bytes (BYTES = 1: a byte, zero-extended) per lane to LDS bytes lds + 4 lane; of 16 bytes to lds + 16 lane.
+template <int BYTES>
+__device__ __forceinline__ void fb_load(const void *addr, unsigned lds)
 {
-    extern __shared__ __attribute__((aligned(16))) char fb_smem[];  // d_z tiles [2][128][z stride], one-hot tiles [2][32 RB][stride]
-    const int s = blockIdx.x, col0 = blockIdx.y * 64, tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6, li = lane & 31, g = lane >> 5;
-    const int R = n_bins + n_pos + 1, Rpad = 32 * RB;
-    char *const zt = fb_smem, *const xt = fb_smem + 2 * kFbTile * kFbZStride;
-    for (int x = tid * 16; x < 2 * Rpad * kFbStride; x += 256 * 16) *reinterpret_cast<uint4 *>(xt + x) = (uint4){0u, 0u, 0u, 0u};
-    const int half = (n_pos - 1) >> 1;
-    const int ntiles = (rows + kFbTile - 1) / kFbTile;
-    const int n_own = (2 * RB - wave + 3) / 4;  // output tiles wave, wave + 4, ... of the 2 RB (row block, column block) pairs
+    if constexpr (BYTES == 16)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr) : "memory", "m0");
+    else if constexpr (BYTES == 4)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(addr) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_ubyte %1, off" ::"s"(lds), "v"(addr) : "memory", "m0");
+}
 
-    f32x16 acc[kFbMaxOwn];
-#pragma unroll
-    for (int o = 0; o < kFbMaxOwn; ++o)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[o][r] = 0.f;
+template <int RB>
+__global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(const int *__restrict__ nbr_idx, const int *__restrict__ nbr_bin,
+                                                                               const bf16_t *__restrict__ d_z, const uint8_t *__restrict__ mask,
+                                                                               float *__restrict__ d_e_bin, float *__restrict__ d_e_pos,
+                                                                               float *__restrict__ d_bias, int rows, int L, int k, int n_bins,
+                                                                               int n_pos, int pos_mode, int n_out)
+{
+    extern __shared__ __attribute__((aligned(16))) char fb_smem[];
+    const int s = blockIdx.x, col0 = blockIdx.y * 64;
+    const int lane = threadIdx.x & 63, li = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int R = n_bins + n_pos + 1, half = (n_pos - 1) >> 1;
+    char *const mine = fb_smem + wave * kFbWaveBytes;
+    const unsigned mine_lds = lds_address(mine);
+    const int ntiles = (rows + 31) / 32;
+    const int own = wave < ntiles ? (ntiles - wave + kFbWaves - 1) / kFbWaves : 0;  // tiles wave, wave + 8, ...
 
-    // what a thread holds of a tile between its fetch and its hand-over: 64 bytes of d_z, and (threads
-    // 128..255: the waves that own fewer output tiles when their number is not a multiple of four) one
-    // residue's slot-s neighbour, bin and validity
-    const int mr = tid - (256 - kFbTile);  // that residue
-    struct Held {
-        uint4 rz[4];
-        int rj, rb;
-        bool rv;
-    };
-    auto fetch = [&](int tile, Held &hd) {
-        const int res0 = tile * kFbTile;
+    // The kLoads loads of this wave's tile n (past the last one: the last one again, so that every tile has as many).
+    constexpr int kLoads = 6;
+    auto issue = [&](int n) {
+        const unsigned st = mine_lds + (n % kFbStages) * kFbStage;
+        const int res0 = 32 * (wave + kFbWaves * min(n, own - 1));
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int c = tid + 256 * q, rr = c >> 3, part = c & 7;
-            const int res = min(res0 + rr, rows - 1), col = col0 + 8 * part;
-            const bool ok = res0 + rr < rows && col < n_out && (mask ? mask[res] != 0 : true);
-            // (what a masked or missing residue holds never reaches the products: 0 x NaN would)
-            hd.rz[q] = ok ? *reinterpret_cast<const uint4 *>(d_z + (size_t)res * n_out + col) : (uint4){0u, 0u, 0u, 0u};
+            const int rr = 8 * q + (lane >> 3), slot = (lane & 7) ^ (((rr >> 1) & 1) << 2);
+            // (rows and columns past the end: addresses of existing ones; what they bring is not used)
+            const size_t res = min(res0 + rr, rows - 1);
+            fb_load<16>(d_z + res * n_out + min(col0 + 8 * slot, n_out - 8), st + 1024 * q);
         }
-        if (tid >= 256 - kFbTile) {  // this thread's residue of the tile
-            const int res = min(res0 + mr, rows - 1);
-            hd.rj = nbr_idx[(size_t)res * k + s];
-            hd.rb = nbr_bin[(size_t)res * k + s];
-            hd.rv = res0 + mr < rows && (mask ? mask[res] != 0 : true);
-        }
+        const size_t res = min(res0 + li, rows - 1);
+        fb_load<4>((g ? nbr_bin : nbr_idx) + res * k + s, st + kFbZ);
+        if (mask) fb_load<1>(mask + res, st + kFbZ + 256);
+        else fb_load<4>(nbr_idx + res * k + s, st + kFbZ + 256);  // (not used)
     };
-    int marked[2][3] = {{-1, -1, -1}, {-1, -1, -1}};  // rows this thread marked in either one-hot tile
-    // One tile: hand over what `hd` holds into stage b (= tile % 2, a literal at both call sites), fetch
-    // the tile after next into `hd`, multiply.
-    auto step = [&](int tile, int b, Held &hd) {
-        char *zs = zt + b * kFbTile * kFbZStride, *xs = xt + b * Rpad * kFbStride;
+
+    f32x16 acc[RB][2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int c = tid + 256 * q, rr = c >> 3, part = c & 7;
-            *reinterpret_cast<uint4 *>(zs + rr * kFbZStride + 16 * part) = hd.rz[q];
+    for (int mb = 0; mb < RB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
+
+    // which of the three code arrays decides about this lane's row of each row block
+    int code_off[RB];
+    u16x2 row2[RB];
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb) {
+        const int row = 32 * mb + li;
+        code_off[mb] = kFbCodes + (row < n_bins ? 0 : (row < R - 1 ? 64 : 128)) + 8 * g;
+        row2[mb] = (u16x2){(unsigned short)row, (unsigned short)row};
+    }
+    const int e4 = (lane & 15) >> 2, grp2 = (lane >> 4) & 1, j4 = lane & 3;
+    int az[2];
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) az[nb] = (4 * g + e4) * 128 + (nb ^ (e4 >> 1)) * 64 + (16 * grp2 + 4 * j4) * 2;
+
+    if (own > 0)
+        for (int n = 0; n < kFbStages - 1; ++n) issue(n);
+    for (int n = 0; n < own; ++n) {
+        // tile n has landed; the reads of tile n - 1, whose stage the next loads take, are done
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kFbStages - 2) * kLoads) : "memory");
+        issue(n + kFbStages - 1);
+        char *const st = mine + (n % kFbStages) * kFbStage;
+        const int res = 32 * (wave + kFbWaves * n) + li;
+        const int j = *reinterpret_cast<const int *>(st + kFbZ + 4 * li);
+        const int bn = *reinterpret_cast<const int *>(st + kFbZ + 128 + 4 * li);
+        const bool valid = res < rows && (mask ? *reinterpret_cast<const int *>(st + kFbZ + 256 + 4 * li) != 0 : true);
+        const unsigned vmask = (unsigned)__ballot(valid);  // (the two halves agree)
+        if (vmask == 0u) continue;
+        const bool filled = valid && j >= 0 && j < L;
+        const int i = res % L;
+        const int pc = pos_mode == 0 ? min(j, n_pos - 1) : min(max(j - i, -half), half) + half;
+        // (0xFFFF: no row)
+        const int c_bin = filled ? min(max(bn, 0), n_bins - 1) : 0xFFFF;
+        const int c_pos = filled && n_pos > 0 ? n_bins + pc : 0xFFFF;
+        *reinterpret_cast<bf16_t *>(mine + kFbCodes + g * 64 + 2 * li) = (bf16_t)(g ? c_pos : c_bin);
+        if (g == 0) *reinterpret_cast<bf16_t *>(mine + kFbCodes + 128 + 2 * li) = (bf16_t)(valid && s == 0 ? R - 1 : 0xFFFF);
+        if (vmask != 0xFFFFFFFFu) {
+            // what a masked or missing residue holds must not reach the products: 0 x NaN would
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (!((vmask >> (8 * q + (lane >> 3))) & 1u)) *reinterpret_cast<uint4 *>(st + 1024 * q + 16 * lane) = (uint4){0u, 0u, 0u, 0u};
         }
-        if (tid >= 256 - kFbTile) {
-            int now[3] = {-1, -1, -1};
-            if (hd.rv) {
-                if (s == 0) now[2] = R - 1;
-                if (hd.rj >= 0 && hd.rj < L) {
-                    now[0] = min(max(hd.rb, 0), n_bins - 1);
-                    if constexpr (HAS_POS) {
-                        const int i = (tile * kFbTile + mr) % L;
-                        now[1] = n_bins + (pos_mode == 0 ? min(hd.rj, n_pos - 1) : min(max(hd.rj - i, -half), half) + half);
-                    }
-                }
-            }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-            for (int x = 0; x < 3; ++x) {
-                const int was = marked[b][x];
-                if (was >= 0 && was != now[x]) *reinterpret_cast<bf16_t *>(xs + was * kFbStride + mr * 2) = 0;
-                if (now[x] >= 0) *reinterpret_cast<bf16_t *>(xs + now[x] * kFbStride + mr * 2) = 0x3F80;  // bf16 1.0
-                marked[b][x] = now[x];
-            }
-        }
-        __syncthreads();
-        if (tile + 2 < ntiles) fetch(tile + 2, hd);
+        for (int t = 0; t < 2; ++t) {
+            bf16x8 bz[2];
 #pragma unroll
-        for (int o = 0; o < kFbMaxOwn; ++o) {
-            if (o >= n_own) break;
-            const int t = wave + 4 * o, mb = t >> 1, nb = t & 1;
-            // The d_z operand comes through the transposing LDS read, which hands lane group g the residues
-            // 16 ks + 4 g .. + 3 and 16 ks + 8 + 4 g .. + 3 of column 32 nb + li; the one-hot operand
-            // takes the same residues of row 32 mb + li.
-            const char *xa = xs + (32 * mb + li) * kFbStride + 8 * g;
-            const char *zb = zs + (4 * g + ((lane & 15) >> 2)) * kFbZStride + (32 * nb + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
-#pragma unroll
-            for (int ks = 0; ks < kFbTile / 16; ++ks) {
-                const bf16x4 alo = *reinterpret_cast<const bf16x4 *>(xa + 32 * ks);
-                const bf16x4 ahi = *reinterpret_cast<const bf16x4 *>(xa + 32 * ks + 16);
-                const bf16x4 zlo = lds_read_tr(zb + 16 * ks * kFbZStride);
-                const bf16x4 zhi = lds_read_tr(zb + (16 * ks + 8) * kFbZStride);
-                bf16x8 a, bz;
+            for (int nb = 0; nb < 2; ++nb) {
+                const bf16x4 lo = lds_read_tr(st + az[nb] + 16 * t * 128), hi = lds_read_tr(st + az[nb] + (16 * t + 8) * 128);
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
-                    a[x] = alo[x];
-                    a[4 + x] = ahi[x];
-                    bz[x] = zlo[x];
-                    bz[4 + x] = zhi[x];
+                    bz[nb][x] = lo[x];
+                    bz[nb][4 + x] = hi[x];
                 }
-                acc[o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bz, acc[o], 0, 0, 0);
+            }
+#pragma unroll
+            for (int mb = 0; mb < RB; ++mb) {
+                // codes of residues 16 t + 4 g .. + 3 and 16 t + 8 + 4 g .. + 3 (the order of the transposing read)
+                const uint2 lo = *reinterpret_cast<const uint2 *>(mine + code_off[mb] + 32 * t);
+                const uint2 hi = *reinterpret_cast<const uint2 *>(mine + code_off[mb] + 32 * t + 16);
+                const unsigned cw[4] = {lo.x, lo.y, hi.x, hi.y};
+                u32x4 a;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const u16x2 diff = __builtin_bit_cast(u16x2, cw[x]) ^ row2[mb];
+                    const u16x2 ne = __builtin_elementwise_min(diff, (u16x2){1, 1});
+                    a[x] = __builtin_bit_cast(unsigned, (u16x2)((u16x2){0x3F80, 0x3F80} - ne * (u16x2){0x3F80, 0x3F80}));  // bf16 1.0 where equal
+                }
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), bz[nb], acc[mb][nb], 0, 0, 0);
             }
         }
-    };
-    Held h0 = {}, h1 = {};
-    fetch(0, h0);
-    if (ntiles > 1) fetch(1, h1);
-    __syncthreads();  // (the one-hot tiles are clear)
-    for (int tile = 0; tile < ntiles; tile += 2) {
-        step(tile, 0, h0);
-        if (tile + 1 < ntiles) step(tile + 1, 1, h1);
     }
+    wait_vmem<0>();  // (loads past the last tile still write LDS)
+    // the waves' sums, in a fixed order: 4..7 to 0..3, 2..3 to 0..1, 1 to 0
+    constexpr int kSum = RB * 2 * 16 * 64 * 4;  // bytes of a wave's sums
+    static_assert(kSum * (kFbWaves / 2) <= 160 * 1024, "LDS");
+#pragma unroll
+    for (int w = kFbWaves / 2; w >= 1; w >>= 1) {
+        __syncthreads();
+        if (wave >= w && wave < 2 * w)
+#pragma unroll
+            for (int mb = 0; mb < RB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<f32x4 *>(fb_smem + (wave - w) * kSum + ((mb * 2 + nb) * 4 + q) * 1024 + 16 * lane) =
+                            (f32x4){acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]};
+        __syncthreads();
+        if (wave < w)
+#pragma unroll
+            for (int mb = 0; mb < RB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(fb_smem + wave * kSum + ((mb * 2 + nb) * 4 + q) * 1024 + 16 * lane);
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) acc[mb][nb][4 * q + x] += v[x];
+                    }
+    }
+    if (wave != 0) return;
     // accumulator register r of a lane: row 8 (r / 4) + 4 g + r % 4 of the row block, column li of the column block
 #pragma unroll
-    for (int o = 0; o < kFbMaxOwn; ++o) {
-        if (o >= n_own) break;
-        const int t = wave + 4 * o, mb = t >> 1, nb = t & 1;
-        const int col = col0 + 32 * nb + li;
-        if (col >= n_out) continue;
+    for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = 32 * mb + 8 * (r >> 2) + 4 * g + (r & 3);
-            if (row < n_bins)
-                d_e_bin[((size_t)s * n_bins + row) * n_out + col] = acc[o][r];
-            else if (row < n_bins + n_pos)
-                d_e_pos[((size_t)s * n_pos + (row - n_bins)) * n_out + col] = acc[o][r];
-            else if (row == R - 1 && s == 0 && d_bias)
-                d_bias[col] = acc[o][r];
+        for (int nb = 0; nb < 2; ++nb) {
+            const int col = col0 + 32 * nb + li;
+            if (col >= n_out) continue;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = 32 * mb + 8 * (r >> 2) + 4 * g + (r & 3);
+                if (row < n_bins)
+                    d_e_bin[((size_t)s * n_bins + row) * n_out + col] = acc[mb][nb][r];
+                else if (row < n_bins + n_pos)
+                    d_e_pos[((size_t)s * n_pos + (row - n_bins)) * n_out + col] = acc[mb][nb][r];
+                else if (row == R - 1 && s == 0 && d_bias)
+                    d_bias[col] = acc[mb][nb][r];
+            }
         }
-    }
+}
+
+template <int RB>
+hipError_t launch_factor_backward(dim3 grid, hipStream_t stream, const int *nbr_idx, const int *nbr_bin, const bf16_t *d_z, const uint8_t *mask,
+                                  float *d_e_bin, float *d_e_pos, float *d_bias, int rows, int L, int k, int n_bins, int n_pos, int pos_mode,
+                                  int n_out)
+{
+    constexpr int sums = RB * 2 * 16 * 64 * 4 * (kFbWaves / 2), tiles = kFbWaves * kFbWaveBytes, lds = sums > tiles ? sums : tiles;
+    static LdsLimit limit;
+    const hipError_t e = raise_lds_limit(limit, (const void *)fipa_factor_backward_kernel<RB>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fipa_factor_backward_kernel<RB>, grid, dim3(64 * kFbWaves), lds, stream, nbr_idx, nbr_bin, d_z, mask, d_e_bin, d_e_pos,
+                       d_bias, rows, L, k, n_bins, n_pos, pos_mode, n_out);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -280,23 +344,15 @@ extern "C" int fipa_factor_project_backward(int32_t B, int32_t L, int32_t k, int
     for (const void *ptr : al16)
         if (ptr && !fipa::aligned16(ptr)) return FIPA_ERR_ALIGNMENT;
     if ((reinterpret_cast<uintptr_t>(nbr_idx) & 3u) != 0 || (reinterpret_cast<uintptr_t>(nbr_bin) & 3u) != 0) return FIPA_ERR_ALIGNMENT;
-    const int lds = 2 * fipa::kFbTile * fipa::kFbZStride + 2 * 32 * RB * fipa::kFbStride;
     const dim3 grid((unsigned)k, (unsigned)((n_out + 63) / 64));
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const int rows = B * L;
-    hipError_t e;
-    if (n_pos > 0) {
-        static fipa::LdsLimit lim;
-        e = fipa::raise_lds_limit(lim, (const void *)fipa::fipa_factor_backward_kernel<true>, lds);
-        if (e != hipSuccess) return FIPA_ERR_LAUNCH;
-        hipLaunchKernelGGL(fipa::fipa_factor_backward_kernel<true>, grid, dim3(256), lds, stream, nbr_idx, nbr_bin,
-                           (const fipa::bf16_t *)d_z, mask, d_e_bin, d_e_pos, d_bias, rows, L, k, n_bins, n_pos, pos_mode, n_out, RB);
-    } else {
-        static fipa::LdsLimit lim;
-        e = fipa::raise_lds_limit(lim, (const void *)fipa::fipa_factor_backward_kernel<false>, lds);
-        if (e != hipSuccess) return FIPA_ERR_LAUNCH;
-        hipLaunchKernelGGL(fipa::fipa_factor_backward_kernel<false>, grid, dim3(256), lds, stream, nbr_idx, nbr_bin,
-                           (const fipa::bf16_t *)d_z, mask, d_e_bin, (float *)nullptr, d_bias, rows, L, k, n_bins, 0, pos_mode, n_out, RB);
-    }
-    return hipGetLastError() == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
+    const auto launch = RB == 1   ? fipa::launch_factor_backward<1>
+                        : RB == 2 ? fipa::launch_factor_backward<2>
+                        : RB == 3 ? fipa::launch_factor_backward<3>
+                        : RB == 4 ? fipa::launch_factor_backward<4>
+                                  : fipa::launch_factor_backward<5>;
+    return launch(grid, stream, nbr_idx, nbr_bin, (const fipa::bf16_t *)d_z, mask, d_e_bin, n_pos > 0 ? d_e_pos : nullptr, d_bias, B * L, L, k,
+                  n_bins, n_pos, pos_mode, n_out) == hipSuccess
+               ? FIPA_OK
+               : FIPA_ERR_LAUNCH;
 }

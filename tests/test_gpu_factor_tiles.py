@@ -1,0 +1,38 @@
+"""GPU parity of fipa_factor_project_backward at the edges of its residue tiles (32 per wave, eight waves) and row
+blocks (32 table rows), with masked residues that hold NaN, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import factor_ref
+from paper_2505_11580_amd import binding
+from tests.test_gpu_factor import _bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,L,k,n_bins,n_pos,n_out,masked", [
+    (1, 1, 1, 1, 0, 8, False), (1, 31, 2, 16, 15, 64, True), (1, 33, 3, 16, 33, 72, True), (2, 257, 2, 22, 33, 128, True),
+    (1, 513, 2, 30, 95, 56, False), (3, 300, 1, 16, 111, 200, True)])
+def test_factor_backward_tiles(B, L, k, n_bins, n_pos, n_out, masked):
+    import torch
+    rng = np.random.default_rng(900 + L)
+    idx = rng.integers(-1, L, size=(B, L, k))
+    bins = np.where(idx < 0, -1, rng.integers(0, n_bins, size=(B, L, k)))
+    mask = (rng.random((B, L)) > 0.3).astype(np.uint8) if masked else None
+    if masked:
+        mask[:, L // 3:L // 3 + 40] = 0  # whole tiles without a valid residue
+    d_z = _bf16(rng.standard_normal((B, L, n_out)))
+    want = factor_ref.factor_project_backward(idx, bins, d_z.float().numpy(), n_bins, n_pos, 1, mask)
+    scale = float(np.abs(d_z.float().numpy()).sum(axis=(0, 1)).max())
+    if masked:
+        d_z[torch.from_numpy(mask == 0)] = float("nan")
+    f = dict(dtype=torch.float32, device="cuda:0")
+    got = [torch.full((k, n_bins, n_out), float("nan"), **f),
+           torch.full((k, n_pos, n_out), float("nan"), **f) if n_pos else None, torch.full((n_out,), float("nan"), **f)]
+    binding.fipa_factor_project_backward(1, torch.from_numpy(idx.astype(np.int32)).cuda(), torch.from_numpy(bins.astype(np.int32)).cuda(),
+                                         d_z.cuda(), torch.from_numpy(mask).cuda() if masked else None, *got)
+    torch.cuda.synchronize()
+    for g, w in zip(got, want):
+        if g is not None:
+            # float32 sums against float64: a few 1e-7 of the largest sum of magnitudes (the bound of test_gpu_factor)
+            assert np.abs(g.cpu().numpy().astype(np.float64) - w).max() <= 2e-6 * scale
