@@ -48,9 +48,9 @@ int check_forward_args(const fipa_desc *desc, const FwdArgs &a)
     return FIPA_OK;
 }
 
-hipError_t enqueue_forward(const fipa_desc &desc, const FwdArgs &a, void *workspace, hipStream_t stream)
+hipError_t enqueue_forward(const fipa_desc &desc, const FwdArgs &a, void *workspace, size_t workspace_bytes, hipStream_t stream)
 {
-    return desc.dtype == FIPA_DTYPE_F32 ? f32_forward(desc, a, workspace, stream) : bf16_forward(desc, a, workspace, stream);
+    return desc.dtype == FIPA_DTYPE_F32 ? f32_forward(desc, a, workspace, stream) : bf16_forward(desc, a, workspace, workspace_bytes, stream);
 }
 
 }  // namespace fipa
@@ -107,9 +107,9 @@ int fipa_forward(const fipa_desc *desc, const void *q, const void *k, const void
         return bf16_backward_begin(*desc, a, workspace, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? FIPA_OK
                                                                                                            : FIPA_ERR_LAUNCH;
     }
-    fipa_workspace_bytes(desc, &need, nullptr);
+    need = desc->dtype == FIPA_DTYPE_F32 ? f32_forward_workspace(*desc) : bf16_forward_workspace_min(*desc);
     if (workspace_bytes < need) return FIPA_ERR_WORKSPACE;
-    return enqueue_forward(*desc, a, workspace, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? FIPA_OK
+    return enqueue_forward(*desc, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? FIPA_OK
                                                                                                   : FIPA_ERR_LAUNCH;
 }
 

@@ -1,0 +1,683 @@
+// Fused attention for r c_z = 512 and 1024 (lifted widths 576 and 1088) in two kernels: the weights of a range of
+// query rows are formed once and kept in memory, the output is a plain matrix product with them.  The windowed kernel
+// (fipa_bf16_attn_fwd_wide.hip) forms S^T once per window of the output columns, because a wave's output accumulator
+// does not fit the register file: 108 matrix instructions per 32 x 32 pairs at width 576, 308 at width 1088, where 72
+// and 136 would do, and these are what the two kernels here execute.
+//
+//   fipa_fwd_weights_kernel  S^T = K^ Q^^T, softmax reference and sum, weights P (bf16) of 32 queries per wave
+//   fipa_fwd_values_kernel   O^ = P V^ for 256 queries and a window of the columns; steps 8-9 of Algorithm 1
+//
+// Softmax: the reference of a row starts as the largest logit of the 32 keys around its own residue, where
+// distance-dominated logits have their maximum (whose weight is then exactly 1), and is raised only where a block holds
+// a logit more than kRaise above it (far inside the range of bf16 and fp32), by a whole number of log2 units, so that
+// weights move from one reference to the next exactly.  A raise is recorded for its (32 queries, key block) as a flag and the 32 references before it; the values
+// kernel, which knows the last reference of every row, scales the weights of the blocks before a raise down to it (and
+// never touches its accumulator); both walk the key blocks in the same order.  Sums are of the rounded weights, as
+// everywhere.
+//
+// Weights, per (batch, head) pair and tile of 256 queries: W[key / 16][query][16], the 16 keys in the order of the
+// matrix operand (4 g + x | 8 + 4 g + x at g 8 + x | g 8 + 4 + x).
+//
+// Measured, whole call, windowed -> here: four chains of 2.7k to 7.1k residues, H = 12, width 576: 4.54 -> 3.52 ms;
+// B = 2, L = 2048, H = 12, width 1088: 1.45 -> 0.53 ms.  Bound by the rate at which LDS and L2 feed the matrix pipe (half of
+// it is busy in either kernel) and, where chains differ in length, by the last workgroups of a range.
+#include "fipa_gfx950.h"
+
+namespace fipa {
+
+namespace {
+
+constexpr float kRaise = 32.f;
+constexpr float kNegInf = -INFINITY;
+
+__device__ __forceinline__ u32x4 buffer_desc(const void *base)
+{
+    const uint64_t a = (uint64_t)(uintptr_t)base;
+    u32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
+    r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xFFFFu);
+    r[2] = 0x7FFFFFFFu;
+    r[3] = 0x00020000u;
+    return r;
+}
+
+__device__ __forceinline__ void dma16b(const u32x4 &rsrc, int voff, int soff, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+
+template <int N>
+__device__ __forceinline__ void wait_and_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+    wg_barrier();
+}
+
+constexpr int kTile = 256;                 // queries of a weights tile
+constexpr int kGrpBytes = kTile * 32;      // 16 keys of a tile
+// Both kernels start a tile at the block group that holds its own residues (tiles that start at the same block share the
+// key stream in L2) and wrap around.
+__device__ __forceinline__ int first_block(int row0, int nblk) { return min((row0 / kTile) * (kTile / 32) / 16 * 16, nblk - 1); }
+
+// ---------------------------------------------------------------------------------------------------------------
+// weights
+// ---------------------------------------------------------------------------------------------------------------
+template <int DZ>
+struct FwCfg {
+    // width 576: two waves per SIMD; at 1088 the query fragments alone are 272 registers
+    static constexpr int NW = DZ <= 512 ? 8 : 4, TQ = 32 * NW;
+    static constexpr int D = kDH + DZ, KS = D / 16, KSH = kDH / 16;
+    static constexpr int ZB = DZ * 2, EPR = ZB / 1024;        // bytes of a pair-part row, 1 KiB loads per row
+    static constexpr int NZW = 32 * EPR / NW;
+    static constexpr int ZP = ZB + 16;                        // LDS row pitch: 16 rows start in 16 different slots of the banks
+    static constexpr int H_OFF = 32 * ZP, KB_OFF = H_OFF + 4096;
+    static constexpr int STAGE = KB_OFF + 1024;
+    static constexpr int NST = 4 * STAGE + DZ * 4 <= 160 * 1024 ? 4 : (3 * STAGE + DZ * 4 <= 160 * 1024 ? 3 : 2);
+    static constexpr int CW_OFF = NST * STAGE;                // per-head scale vector of the query-side factors
+    static constexpr int LDS_BYTES = CW_OFF + DZ * 4;
+    static constexpr int NDMA = NZW + 2;
+    static_assert(EPR >= 1 && LDS_BYTES <= 160 * 1024, "LDS");
+};
+
+template <int DZ>
+__global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fwd_weights_kernel(FwdStoredParams p)
+{
+    using C = FwCfg<DZ>;
+    constexpr int KS = C::KS, KSH = C::KSH;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int per_xcd = (p.units + 7) / 8;
+    const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= (unsigned)per_xcd || logical >= p.units) return;
+    const int nt = (p.nq + C::TQ - 1) / C::TQ;
+    const int bh_pos = logical / nt, tile = logical - bh_pos * nt;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bh = p.deal ? dealt_pair_by_length(bh_pos, p.kvlen, p.B, p.H, lane) : bh_pos;
+    const int b = bh / p.H, h = bh - b * p.H;
+    const int kvlen = p.deal ? p.kvlen[b] : p.L;
+    const int nblk = (kvlen + 31) / 32;
+    const int row0 = p.i0 + tile * C::TQ;  // first query of the workgroup
+    if (row0 >= kvlen) return;
+    const size_t rows0 = (size_t)bh * p.Lp;
+    const int first = first_block(row0, nblk);
+    auto block = [&](int n) { const int x = first + n; return x >= nblk ? x - nblk : x; };  // n-th block of the walk, n < nblk
+
+    // ---- direct loads ---------------------------------------------------------------------------------------------
+    const u32x4 r_z = buffer_desc(p.Z2 + (size_t)b * p.Lp * DZ), r_h = buffer_desc(p.Kh + rows0 * kDH), r_b = buffer_desc(p.kbias + rows0);
+    const int vz = lane * 16, vb = min(lane, 7) * 16;
+    const int hrow = 8 * (wave & 3) + (lane >> 3);
+    const int vh = hrow * 128 + ((lane & 7) ^ ((hrow >> 1) & 7)) * 16;
+    const unsigned lds0 = lds_address(smem);
+    auto issue = [&](auto Kc, int kb, unsigned stage) {
+        constexpr int K = decltype(Kc)::value;
+        if constexpr (K < C::NZW) {
+            const int e = wave + C::NW * K, row = e / C::EPR, part = e % C::EPR;
+            dma16b(r_z, vz, (32 * kb + row) * C::ZB + 1024 * part, stage + row * C::ZP + 1024 * part);
+        } else if constexpr (K == C::NZW) {
+            dma16b(r_h, vh, 32 * kb * 128, stage + C::H_OFF + 1024 * (wave & 3));  // (eight waves: twice the same)
+        } else {
+            dma16b(r_b, vb, 32 * kb * 4, stage + C::KB_OFF);
+        }
+    };
+    auto issue_all = [&](int n, unsigned stage) {
+        const int kb = block(min(n, nblk - 1));
+        static_for<C::NDMA>([&](auto K) { issue(K, kb, stage); });
+    };
+#pragma unroll
+    for (int n = 0; n < C::NST - 1; ++n) issue_all(n, lds0 + n * C::STAGE);
+
+    // ---- query fragments (b^{h1} of Algorithm 1 steps 2-3 formed from z1, see the windowed kernel), first reference ----
+    const int ulen = user_len(p, b);
+    const size_t urow0 = user_row(p, b, 0);
+    const int irow = row0 + 32 * wave + li, irow_p = min(irow, p.Lp - 1);
+    bf16x8 qf[KS];
+    float m = 0.f;
+    {
+        float *cw = reinterpret_cast<float *>(smem + C::CW_OFF);
+        for (int x = tid; x < DZ; x += 64 * C::NW) cw[x] = kLog2e * p.w_L * p.w_b[(size_t)h * p.cz + x % p.cz];
+        __syncthreads();
+        // S^T of the wave's own 32 keys: row li of that block is this lane's residue
+        f32x16 own;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int key = row0 + 32 * wave + 8 * (r >> 2) + 4 * g + (r & 3);
+            const float kb = p.kbias[rows0 + min(key, p.Lp - 1)];
+            own[r] = key < kvlen ? kb : kNegInf;
+        }
+        auto dot = [&](const bf16x8 &q, const bf16x8 &k) { own = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, q, own, 0, 0, 0); };
+        const bf16_t *qh = p.Qh + (rows0 + irow_p) * kDH + 8 * g, *kh = p.Kh + (rows0 + irow_p) * kDH + 8 * g;
+        const bf16_t *z2 = p.Z2 + ((size_t)b * p.Lp + irow_p) * DZ + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < KSH; ++ks) {
+            qf[ks] = *reinterpret_cast<const bf16x8 *>(qh + 16 * ks);
+            dot(qf[ks], *reinterpret_cast<const bf16x8 *>(kh + 16 * ks));
+        }
+        const bool ok = irow < ulen && (p.mask ? p.mask[urow0 + irow] != 0 : true);
+        const unsigned keep = ok ? 0xFFFFFFFFu : 0u;
+        const bf16_t *z1row = p.z1 + (urow0 + min(irow, ulen - 1)) * DZ + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < KS - KSH; ++ks) {
+            const uint4 zr = *reinterpret_cast<const uint4 *>(z1row + 16 * ks);
+            const f32x4 w0 = *reinterpret_cast<const f32x4 *>(cw + 16 * ks + 8 * g);
+            const f32x4 w1 = *reinterpret_cast<const f32x4 *>(cw + 16 * ks + 8 * g + 4);
+            const unsigned zw[4] = {zr.x, zr.y, zr.z, zr.w};
+            unsigned pk[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const float wl = x < 2 ? w0[2 * x] : w1[2 * x - 4], wh = x < 2 ? w0[2 * x + 1] : w1[2 * x - 3];
+                const float lo = wl * __uint_as_float(zw[x] << 16), hi = wh * __uint_as_float(zw[x] & 0xFFFF0000u);
+                pk[x] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){lo, hi}, bf16x2)) & keep;
+            }
+            qf[KSH + ks] = __builtin_bit_cast(bf16x8, (u32x4){pk[0], pk[1], pk[2], pk[3]});
+            dot(qf[KSH + ks], *reinterpret_cast<const bf16x8 *>(z2 + 16 * ks));
+        }
+        m = own[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) m = fmaxf(m, own[r]);
+        m = fmaxf(m, __shfl_xor(m, 32));
+    }
+    constexpr int kPin = KS - KSH < 64 ? KS - KSH : 64;
+#pragma unroll
+    for (int ks = 0; ks < kPin; ++ks) asm volatile("" : "+a"(qf[KSH + ks]));
+
+    // per-lane LDS offsets: row li, 16-byte slot 2 ks + g
+    const int az = li * C::ZP + g * 16;
+    const int ah = C::H_OFF + li * 128 + (g ^ ((li >> 1) & 7)) * 16;  // (head-specific: slot XOR-ed with the row; 32 ks by XOR)
+    static_assert(C::H_OFF % 128 == 0, "XOR of the slot");
+
+    // destinations
+    const int trow = row0 - p.i0;                                        // rows before this workgroup in the range
+    const size_t tile256 = (size_t)bh * p.nqt + trow / kTile;
+    char *const wbase = reinterpret_cast<char *>(p.W) + tile256 * (p.Lp / 16) * kGrpBytes;
+    const unsigned wlane = (trow % kTile + 32 * wave + li) * 32 + 16 * g;
+    const size_t sub = tile256 * (kTile / 32) + trow % kTile / 32 + wave;  // this wave's 32 queries
+    unsigned *const flags = p.flags + sub * p.nwords;
+    float *const before = p.before + sub * (size_t)p.Lp;
+
+    f32x16 sacc, sold;  // S^T of the current block; of the previous one, whose softmax runs meanwhile
+    bf16x8 fr[4];
+    float l = 0.f;
+    unsigned flag = 0u;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) fr[x] = bf16x8{};
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sacc[r] = sold[r] = 0.f;
+    constexpr int kLA = 3;
+    static_assert(KS % 4 == 0, "operand ring");
+    constexpr int kStores = 2;
+
+    // softmax of the block at position n (its S^T in `s`): part 1 the reference, part 2 pair t of the weights
+    unsigned pk[4];
+    float mu = 0.f;
+    auto reference = [&](const f32x16 &s, int n) {
+        float mx = s[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        if (__any(mx > m + kRaise)) {
+            if (g == 0) before[(size_t)n * 32 + li] = m;
+            const float mn = mx > m + kRaise ? (m > kNegInf ? m + ceilf(mx - m) : mx) : m;
+            l *= mn > m ? (m > kNegInf ? __builtin_amdgcn_exp2f(m - mn) : 0.f) : 1.f;
+            m = mn;
+            flag |= 1u << (n & 31);
+        }
+        mu = m > kNegInf ? m : 0.f;  // (nothing but masked keys so far: all weights 0)
+        if ((n & 31) == 31) {
+            if (lane == 0) flags[n >> 5] = flag;
+            flag = 0u;
+        }
+    };
+    auto pair = [&](const f32x16 &s, int t, char *dst) {
+        const float e0 = __builtin_amdgcn_exp2f(s[2 * t] - mu), e1 = __builtin_amdgcn_exp2f(s[2 * t + 1] - mu);
+        pk[t & 3] = pack_pair(e0, e1, l);
+        if ((t & 3) == 3) *reinterpret_cast<u32x4 *>(dst + (t >> 2) * kGrpBytes + wlane) = (u32x4){pk[0], pk[1], pk[2], pk[3]};
+    };
+    auto mfma_of = [&](auto F, f32x16 &s) {
+        constexpr int f = decltype(F)::value;
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[f % 4], qf[f], s, 0, 0, 0);
+    };
+    int sidx = 0;
+    auto step = [&](auto FIRST, int n) {
+        constexpr bool firstb = decltype(FIRST)::value;
+        const char *st = smem + sidx * C::STAGE;
+        int nidx = sidx + C::NST - 1;
+        nidx = nidx >= C::NST ? nidx - C::NST : nidx;
+        const unsigned next = lds0 + nidx * C::STAGE;
+        const int next_kb = block(min(n + C::NST - 1, nblk - 1));
+        char *const dst = wbase + (size_t)(2 * block(n > 0 ? n - 1 : 0)) * kGrpBytes;
+        static_for<KS>([&](auto J) {
+            constexpr int j = decltype(J)::value;
+            const char *a = j < KSH ? st + (ah ^ (32 * (j & 3))) : st + az + (j - KSH) * 32;
+            fr[j % 4] = *reinterpret_cast<const bf16x8 *>(a);
+            if constexpr (j < kLA) {
+                if constexpr (!firstb) mfma_of(std::integral_constant<int, KS + j - kLA>{}, sacc);
+            } else {
+                constexpr int f = j - kLA;
+                if constexpr (f == 0) {
+                    if constexpr (!firstb) sold = sacc;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 kb4 = *reinterpret_cast<const f32x4 *>(st + C::KB_OFF + (8 * q + 4 * g) * 4);
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) sacc[4 * q + x] = kb4[x];
+                    }
+                }
+                mfma_of(std::integral_constant<int, f>{}, sacc);
+                if constexpr (f < C::NDMA) issue(std::integral_constant<int, f>{}, next_kb, next);
+                // the softmax of the previous block, behind the loads (in the order of vector-memory operations)
+                constexpr int kS0 = C::NDMA > 4 ? C::NDMA : 4;
+                if constexpr (!firstb && f == kS0) reference(sold, n - 1);
+                if constexpr (!firstb && f > kS0) {
+                    constexpr int slots = KS - kLA - 1 - kS0;
+#pragma unroll
+                    for (int t = (f - kS0 - 1) * 8 / slots; t < (f - kS0) * 8 / slots; ++t) pair(sold, t, dst);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        sidx = sidx + 1 < C::NST ? sidx + 1 : 0;
+    };
+    using T = std::true_type;
+    using F = std::false_type;
+    constexpr int kAhead = (C::NST - 2) * C::NDMA;
+    wait_and_barrier<kAhead>();
+    step(T{}, 0);
+    for (int n = 1; n < nblk; ++n) {
+        if (n == 1) wait_and_barrier<kAhead>();
+        else wait_and_barrier<kAhead + kStores>();  // (the newest operations are the stores of the block before last)
+        step(F{}, n);
+    }
+    // the last block
+    {
+        const int n = nblk - 1;
+        char *const dst = wbase + (size_t)(2 * block(n)) * kGrpBytes;
+        static_for<kLA>([&](auto J) { mfma_of(std::integral_constant<int, KS + decltype(J)::value - kLA>{}, sacc); });
+        reference(sacc, n);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) pair(sacc, t, dst);
+        if ((n & 31) != 31 && lane == 0) flags[n >> 5] = flag;
+    }
+    wait_vmem<0>();  // (the loads past the last block still write LDS)
+    const float lt = l + __shfl_xor(l, 32);
+    if (g == 0 && irow < p.Lp) {
+        p.linv[rows0 + irow] = lt > 0.f ? 1.f / lt : 0.f;
+        p.lse2[rows0 + irow] = lt > 0.f ? m + __log2f(lt) : kNegInf;
+        p.mref[rows0 + irow] = m;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// values
+// ---------------------------------------------------------------------------------------------------------------
+// acc += A B with the accumulator in accumulation (a) or architectural (v) registers (see fipa_bf16_bwd_stored.hip).
+__device__ __forceinline__ void mfma_a(f32x16 &acc, const bf16x8 &a, const bf16x8 &b)
+{
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_v(f32x16 &acc, const bf16x8 &a, const bf16x8 &b)
+{
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+
+// Windows of 256 pair columns, the first with the head-specific 64 as well.  HB = 0: the columns in their natural order,
+// O^ is written.  HB > 0: of every factor slice HB blocks of 32 columns, so that the contraction over the slices stays in a
+// window and steps 8-9 run on the accumulator (AlphaFold2 head shape; HB = c_z / (32 windows)).
+template <int DZ, int HB, bool HEAD>
+struct FvCfg {
+    static constexpr int NWIN = DZ / 256, ZBL = 8;
+    static constexpr int CZ = HB * 32 * NWIN;
+    static constexpr int RB = 64 * ZBL, NZW = 32 * RB / 1024 / 4, NWW = 4;
+    static constexpr int H_OFF = 32 * RB, W_OFF = H_OFF + 4096, STAGE = W_OFF + 2 * kGrpBytes;
+    static constexpr int NST = 4, LDS_BYTES = NST * STAGE, NDMA = NZW + 1 + NWW;
+    static constexpr int NH = HEAD ? 2 : 0, NF = 2 * (NH + ZBL);
+    static_assert(NF % 4 == 0 && LDS_BYTES <= 160 * 1024, "ring and LDS");
+};
+
+template <int DZ, int HB, bool HEAD>
+__device__ __forceinline__ void values_window(const FwdStoredParams &p, char *smem, int logical, int win)
+{
+    using C = FvCfg<DZ, HB, HEAD>;
+    constexpr int D = kDH + DZ, HV = 2;
+    const int nt = (p.nq + kTile - 1) / kTile;
+    const int bh_pos = logical / nt, tile = logical - bh_pos * nt;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bh = p.deal ? dealt_pair_by_length(bh_pos, p.kvlen, p.B, p.H, lane) : bh_pos;
+    const int b = bh / p.H, h = bh - b * p.H;
+    const int kvlen = p.deal ? p.kvlen[b] : p.L;
+    const int row0 = p.i0 + tile * kTile;
+    const int nblk = row0 >= kvlen ? 0 : (kvlen + 31) / 32;
+    const size_t rows0 = (size_t)bh * p.Lp;
+
+    f32x16 acch[C::NH > 0 ? C::NH : 1][HV], accz[C::ZBL][HV];
+#pragma unroll
+    for (int hv = 0; hv < HV; ++hv) {
+#pragma unroll
+        for (int nb = 0; nb < C::NH; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acch[nb][hv][r] = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < C::ZBL; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) accz[nb][hv][r] = 0.f;
+    }
+    // first column of pair block nb of this window
+    auto column = [&](int nb) { return HB == 0 ? 256 * win + 32 * nb : (nb / (HB ? HB : 1)) * C::CZ + 32 * (win * HB + nb % (HB ? HB : 1)); };
+    // results of the matrix instructions become readable (asm: the compiler does not count the cycles)
+    auto settle = [&]() {
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+        for (int hv = 0; hv < HV; ++hv) {
+#pragma unroll
+            for (int nb = 0; nb < C::ZBL; ++nb) asm volatile("" : "+a"(accz[nb][hv]));
+#pragma unroll
+            for (int nb = 0; nb < C::NH; ++nb) asm volatile("" : "+v"(acch[nb][hv]));
+        }
+    };
+
+    if (nblk > 0) {
+        const int first = first_block(row0, nblk);
+        auto block = [&](int n) { const int x = first + n; return x >= nblk ? x - nblk : x; };
+        const size_t tile256 = (size_t)bh * p.nqt + tile;
+        const u32x4 r_z = buffer_desc(p.Z2 + (size_t)b * p.Lp * DZ), r_h = buffer_desc(p.Vh + rows0 * kDH);
+        const u32x4 r_w = buffer_desc(reinterpret_cast<const char *>(p.W) + tile256 * (p.Lp / 16) * kGrpBytes);
+        int vz, vh;
+        {
+            // (LDS: the 64-byte blocks of row r at block ^ (r mod 4); of a head-specific row, at half ^ (r / 2 mod 2))
+            const int r = lane >> 5, vr = 2 * wave + r, slot = (lane & 31) ^ ((vr & 3) << 2);
+            vz = r * (DZ * 2) + column(slot >> 2) * 2 + (slot & 3) * 16;
+            const int rh = lane >> 3, slh = (lane & 7) ^ (((rh >> 1) & 1) << 2);
+            vh = rh * 128 + slh * 16;
+        }
+        const int vw = lane * 16;
+        const unsigned lds0 = lds_address(smem);
+        auto issue = [&](auto Kc, int kb, unsigned stage) {
+            constexpr int K = decltype(Kc)::value;
+            if constexpr (K < C::NZW) {
+                const int e = wave + 4 * K;
+                dma16b(r_z, vz, (32 * kb + 2 * e) * (DZ * 2), stage + 1024 * e);
+            } else if constexpr (K == C::NZW) {
+                dma16b(r_h, vh, (32 * kb + 8 * wave) * 128, stage + C::H_OFF + 1024 * wave);
+            } else {
+                const int e = wave + 4 * (K - C::NZW - 1);
+                dma16b(r_w, vw, 2 * kb * kGrpBytes + 1024 * e, stage + C::W_OFF + 1024 * e);
+            }
+        };
+#pragma unroll
+        for (int n = 0; n < C::NST - 1; ++n)
+            static_for<C::NDMA>([&](auto K) { issue(K, block(min(n, nblk - 1)), lds0 + n * C::STAGE); });
+
+        const int l16 = lane & 15, grp2 = (lane >> 4) & 1, e4 = l16 >> 2, j4 = l16 & 3;
+        int az[4], ah[2];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) az[x] = (4 * g + e4) * C::RB + (x ^ e4) * 64 + (16 * grp2 + 4 * j4) * 2;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) ah[x] = C::H_OFF + (4 * g + e4) * 128 + (x ^ (e4 >> 1)) * 64 + (16 * grp2 + 4 * j4) * 2;
+        const int aw = C::W_OFF + (HV * wave * 32 + li) * 32 + g * 16;
+
+        bf16x8 fr[4] = {}, w0[HV], w1[HV] = {};  // (the first step has no predecessor: products with zero)
+        auto fetch = [&](const char *st, auto Fc) -> bf16x8 {
+            constexpr int f = decltype(Fc)::value, t = f / (C::NF / 2), x = f % (C::NF / 2);
+            const char *a;
+            int rs;
+            if constexpr (x < C::NH) {
+                a = st + ah[x & 1] + 16 * t * 128;
+                rs = 128;
+            } else {
+                constexpr int nb = x - C::NH;
+                a = st + az[nb & 3] + (nb & ~3) * 64 + 16 * t * C::RB;
+                rs = C::RB;
+            }
+            const bf16x4 lo = lds_read_tr(a), hi = lds_read_tr(a + 8 * rs);
+            bf16x8 v;
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                v[y] = lo[y];
+                v[4 + y] = hi[y];
+            }
+            return v;
+        };
+        auto mfma_of = [&](auto Fc) {
+            constexpr int f = decltype(Fc)::value, t = f / (C::NF / 2), x = f % (C::NF / 2);
+#pragma unroll
+            for (int hv = 0; hv < HV; ++hv) {
+                const bf16x8 &w = t ? w1[hv] : w0[hv];
+                if constexpr (x < C::NH) mfma_v(acch[x][hv], fr[f % 4], w);
+                else mfma_a(accz[x - C::NH][hv], fr[f % 4], w);
+            }
+        };
+        constexpr int kLA = 3;
+        auto held = [&]() { static_for<kLA>([&](auto J) { mfma_of(std::integral_constant<int, C::NF + decltype(J)::value - kLA>{}); }); };
+        // Raises: blocks from the last one to the one before block `until` carry weights relative to the references
+        // recorded there; `scale` takes them to the last reference of the row (1 behind the last raise).
+        const size_t sub = tile256 * (kTile / 32) + HV * wave;
+        const unsigned *flags = p.flags + sub * p.nwords;
+        int until[HV];
+        float scale[HV];
+        auto next_raise = [&](int hv, int from) {  // first raise at block `from` or later
+            int w = from >> 5;
+            unsigned bits = __builtin_amdgcn_readfirstlane(flags[hv * p.nwords + min(w, p.nwords - 1)]) & (0xFFFFFFFFu << (from & 31));
+            while (bits == 0u && 32 * (w + 1) < nblk) bits = __builtin_amdgcn_readfirstlane(flags[hv * p.nwords + ++w]);
+            const int at = bits ? 32 * w + __ffs((int)bits) - 1 : nblk;
+            until[hv] = at;
+            scale[hv] = 1.f;
+            if (at < nblk) {
+                const float mb = p.before[(sub + hv) * (size_t)p.Lp + (size_t)at * 32 + li];
+                const float ml = p.mref[rows0 + min(row0 + 32 * (HV * wave + hv) + li, p.Lp - 1)];
+                scale[hv] = mb > kNegInf ? __builtin_amdgcn_exp2f(mb - ml) : 0.f;
+            }
+        };
+#pragma unroll
+        for (int hv = 0; hv < HV; ++hv) next_raise(hv, 1);
+        auto scaled = [&](const bf16x8 &w, float f) {
+            bf16x8 r;
+#pragma unroll
+            for (int x = 0; x < 8; x += 2) {
+                const bf16x2 v = __builtin_convertvector((f32x2){(float)w[x] * f, (float)w[x + 1] * f}, bf16x2);
+                r[x] = v[0];
+                r[x + 1] = v[1];
+            }
+            return r;
+        };
+        for (int n = 0; n < nblk; ++n) {
+            wait_and_barrier<(C::NST - 2) * C::NDMA>();
+            const char *st = smem + (n & 3) * C::STAGE;
+            const unsigned next = lds0 + ((n + 3) & 3) * C::STAGE;
+            const int next_kb = block(min(n + 3, nblk - 1));
+            bf16x8 w1n[HV];
+#pragma unroll
+            for (int hv = 0; hv < HV; ++hv) {
+                w0[hv] = *reinterpret_cast<const bf16x8 *>(st + aw + hv * 1024);
+                w1n[hv] = *reinterpret_cast<const bf16x8 *>(st + aw + kGrpBytes + hv * 1024);
+            }
+            if (until[0] < nblk || until[1] < nblk) {
+#pragma unroll
+                for (int hv = 0; hv < HV; ++hv) {
+                    if (n == until[hv]) next_raise(hv, n + 1);
+                    w0[hv] = scaled(w0[hv], scale[hv]);
+                    w1n[hv] = scaled(w1n[hv], scale[hv]);
+                }
+            }
+            static_for<C::NF>([&](auto J) {
+                constexpr int j = decltype(J)::value;
+                fr[j % 4] = fetch(st, J);
+                if constexpr (j < kLA) mfma_of(std::integral_constant<int, C::NF + j - kLA>{});
+                else mfma_of(std::integral_constant<int, j - kLA>{});
+                if constexpr (j == kLA - 1)  // (the last products of the previous step are issued)
+#pragma unroll
+                    for (int hv = 0; hv < HV; ++hv) w1[hv] = w1n[hv];
+                if constexpr (j >= kLA && j - kLA < C::NDMA) issue(std::integral_constant<int, j - kLA>{}, next_kb, next);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+        held();
+        wait_vmem<0>();  // (the loads past the last block still write LDS)
+        settle();
+    }
+
+    // ---- results --------------------------------------------------------------------------------------------------
+    const int ulen = user_len(p, b);
+    const size_t urow0 = user_row(p, b, 0);
+#pragma unroll
+    for (int hv = 0; hv < HV; ++hv) {
+        const int irow = row0 + 32 * (HV * wave + hv) + li;
+        if (irow >= p.Lp) continue;
+        const bool live = nblk > 0 && irow < kvlen;
+        const float inv = live ? p.linv[rows0 + irow] : 0.f;
+        if constexpr (HB == 0) {
+            float *orow = p.Ohat + (rows0 + irow) * D;
+#pragma unroll
+            for (int nb = 0; nb < C::NH + C::ZBL; ++nb) {
+                const f32x16 &a = nb < C::NH ? acch[nb < C::NH ? nb : 0][hv] : accz[nb < C::NH ? 0 : nb - C::NH][hv];
+                float *dst = orow + (nb < C::NH ? 32 * nb : kDH + column(nb - C::NH)) + 4 * g;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    f32x4 v;
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) v[x] = live ? a[4 * q + x] * inv : 0.f;
+                    *reinterpret_cast<f32x4 *>(dst + 8 * q) = v;
+                }
+            }
+            if (HEAD && g == 0 && !live) p.lse2[rows0 + irow] = kNegInf;
+        } else {
+            if (irow >= ulen) continue;
+            const bool valid = live && inv > 0.f && (p.mask ? p.mask[urow0 + irow] != 0 : true);
+            const float sc = valid ? inv : 0.f;
+            const size_t row = (urow0 + irow) * p.H + h;
+            // z1 contraction over the factor slices (step 9): block rho HB + q is slice rho, columns 32 (win HB + q) ..
+            constexpr int R = HB ? C::ZBL / HB : 1;
+            const bf16_t *z1row = p.z1 + (urow0 + irow) * DZ + 32 * win * HB + 4 * g;
+            float *dst = p.o_pair + row * C::CZ + 32 * win * HB + 4 * g;
+#pragma unroll
+            for (int q = 0; q < HB; ++q)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int rho = 0; rho < R; ++rho) {
+                        const uint2 zr = *reinterpret_cast<const uint2 *>(z1row + rho * C::CZ + 32 * q + 8 * a);
+                        const f32x16 &ac = accz[rho * HB + q][hv];
+                        sum[0] += ac[4 * a] * __uint_as_float(zr.x << 16);
+                        sum[1] += ac[4 * a + 1] * __uint_as_float(zr.x & 0xFFFF0000u);
+                        sum[2] += ac[4 * a + 2] * __uint_as_float(zr.y << 16);
+                        sum[3] += ac[4 * a + 3] * __uint_as_float(zr.y & 0xFFFF0000u);
+                    }
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) sum[x] = valid ? sum[x] * sc : 0.f;
+                    *reinterpret_cast<f32x4 *>(dst + 32 * q + 8 * a) = sum;
+                }
+            if constexpr (HEAD) {
+                constexpr int c = 16, Pv = 8;
+                // points 4 g .. 4 g + 3 of this half (columns: see v_pt_col)
+                float Gv[12];
+#pragma unroll
+                for (int u = 0; u < 12; ++u) {
+                    const int dh = 16 + 8 * (u >> 2) + (u & 3), dl = 16 + 8 * ((u + 12) >> 2) + ((u + 12) & 3);
+                    Gv[u] = acch[dh >> 5][hv][4 * ((dh & 31) >> 3) + (dh & 3)] + acch[dl >> 5][hv][4 * ((dl & 31) >> 3) + (dl & 3)];
+                }
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    f32x4 out;
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) out[x] = valid ? acch[0][hv][4 * a + x] * sc : 0.f;
+                    *reinterpret_cast<f32x4 *>(p.o + row * c + 8 * a + 4 * g) = out;
+                }
+                const float *Rp = p.rot + (urow0 + irow) * 9, *tr = p.trans + (urow0 + irow) * 3;
+                float outp[12];
+#pragma unroll
+                for (int pp = 0; pp < 4; ++pp) {
+                    const float rx = Gv[3 * pp] * inv - (tr[0] - p.cen[4 * b]), ry = Gv[3 * pp + 1] * inv - (tr[1] - p.cen[4 * b + 1]),
+                                rz = Gv[3 * pp + 2] * inv - (tr[2] - p.cen[4 * b + 2]);
+#pragma unroll
+                    for (int x = 0; x < 3; ++x) outp[3 * pp + x] = valid ? Rp[x] * rx + Rp[3 + x] * ry + Rp[6 + x] * rz : 0.f;  // R^T
+                }
+#pragma unroll
+                for (int a = 0; a < 3; ++a)
+                    *reinterpret_cast<f32x4 *>(p.o_pts + row * (Pv * 3) + 12 * g + 4 * a) =
+                        (f32x4){outp[4 * a], outp[4 * a + 1], outp[4 * a + 2], outp[4 * a + 3]};
+                if (p.lse && g == 0)
+                    p.lse[user_lse_index(p, b, h, irow)] = valid ? p.lse2[rows0 + irow] * kLn2 - p.qbias[rows0 + irow] : 0.f;
+            }
+        }
+    }
+}
+
+template <int DZ, int HB>
+__global__ __launch_bounds__(256, 1) void fipa_fwd_values_kernel(FwdStoredParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    // each XCD gets a contiguous run of tiles; the windows of a tile, which read the same weights, are neighbours
+    constexpr int NWIN = DZ / 256;
+    const int per_xcd = (p.units + 7) / 8;
+    const int slot = blockIdx.x / 8;
+    const int logical = (blockIdx.x % 8) * per_xcd + slot / NWIN;
+    if (slot / NWIN >= per_xcd || logical >= p.units) return;
+    const int win = slot % NWIN;
+    if (win == 0) values_window<DZ, HB, true>(p, smem, logical, 0);
+    else values_window<DZ, HB, false>(p, smem, logical, win);
+}
+
+template <int DZ, int HB>
+hipError_t launch_values(const FwdStoredParams &p, hipStream_t stream)
+{
+    constexpr int lds = FvCfg<DZ, HB, true>::LDS_BYTES;
+    static LdsLimit limit;
+    const hipError_t e = raise_lds_limit(limit, (const void *)fipa_fwd_values_kernel<DZ, HB>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((fipa_fwd_values_kernel<DZ, HB>), dim3((p.units + 7) / 8 * 8 * (DZ / 256)), dim3(256), lds, stream, p);
+    return hipGetLastError();
+}
+
+template <int DZ>
+hipError_t launch_weights(const FwdStoredParams &p, hipStream_t stream)
+{
+    using C = FwCfg<DZ>;
+    static LdsLimit limit;
+    const hipError_t e = raise_lds_limit(limit, (const void *)fipa_fwd_weights_kernel<DZ>, C::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fipa_fwd_weights_kernel<DZ>, dim3((p.units + 7) / 8 * 8), dim3(64 * C::NW), C::LDS_BYTES, stream, p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// Blocks of 32 pair columns per factor slice and window where steps 8-9 can run on the accumulator, else 0.
+int fwd_stored_slice_blocks(int DZ, int cz)
+{
+    const int hb = (DZ == 512 || DZ == 1024) && cz % (DZ / 8) == 0 ? cz / (DZ / 8) : 0;
+    return hb == 1 || hb == 2 || hb == 4 ? hb : 0;
+}
+
+// fused: outputs of the call (AlphaFold2 head shape, fwd_stored_slice_blocks() > 0); otherwise O^ and lse2.
+hipError_t launch_attn_fwd_stored_bf16(const FwdStoredParams &p0, int DZ, bool fused, hipStream_t stream)
+{
+    const int hb = fused ? fwd_stored_slice_blocks(DZ, p0.cz) : 0;
+    if ((DZ != 512 && DZ != 1024) || (fused && hb == 0)) return hipErrorInvalidValue;
+    for (int i0 = 0; i0 < p0.Lp; i0 += p0.nq_alloc) {
+        FwdStoredParams p = p0;
+        p.i0 = i0;
+        p.nq = p0.Lp - i0 < p0.nq_alloc ? p0.Lp - i0 : p0.nq_alloc;
+        const int tq = DZ == 512 ? FwCfg<512>::TQ : FwCfg<1024>::TQ;
+        p.units = p.B * p.H * ((p.nq + tq - 1) / tq);
+        hipError_t e = DZ == 512 ? launch_weights<512>(p, stream) : launch_weights<1024>(p, stream);
+        if (e != hipSuccess) return e;
+        p.units = p.B * p.H * ((p.nq + kTile - 1) / kTile);
+        if (DZ == 512)
+            e = hb == 1   ? launch_values<512, 1>(p, stream)
+                : hb == 2 ? launch_values<512, 2>(p, stream)
+                : hb == 4 ? launch_values<512, 4>(p, stream)
+                          : launch_values<512, 0>(p, stream);
+        else
+            e = hb == 1   ? launch_values<1024, 1>(p, stream)
+                : hb == 2 ? launch_values<1024, 2>(p, stream)
+                : hb == 4 ? launch_values<1024, 4>(p, stream)
+                          : launch_values<1024, 0>(p, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace fipa

@@ -296,6 +296,64 @@ struct EpiParams {
     int B, L, Lp, H, c, Pv, cz, r, DZ;
 };
 
+// The forward of r c_z = 512 and 1024 with the weights of a range of query rows in memory (fipa_bf16_attn_fwd_stored.hip).
+struct FwdStoredParams {
+    const bf16_t *Qh, *Kh, *Vh, *Z2;
+    const float *kbias, *qbias;
+    const int *kvlen;
+    bf16_t *W;             // [B H][nqt][Lp / 16][256][16] weights of query rows i0 .. i0 + nq - 1
+    unsigned *flags;       // [B H][nqt][8][nwords] key blocks (in the order of the walk) at which 32 queries raise their reference
+    float *before;         // [B H][nqt][8][Lp / 32][32] the references before those raises
+    float *mref, *linv, *lse2;  // [B,H,Lp] last reference, one over the sum of the weights, log2 log-sum-exp
+    float *Ohat;           // not fused
+    const float *rot, *trans, *cen, *w_b;
+    const bf16_t *z1;
+    const uint8_t *mask;
+    const int *cu;         // packed batch: row offsets of the chains (see user_row), else null
+    float *o, *o_pts, *o_pair, *lse;
+    int B, L, Lp, H, cz, deal;
+    float w_L;
+    int nq_alloc, nqt;     // query rows the buffers hold, in tiles of 256
+    int nwords;            // words of flags per 32 queries
+    int i0, nq, units;     // this range
+};
+
+// Its buffers, carved from `off` on.
+struct FwdStoredLayout {
+    size_t W, flags, before, mref, linv, total;
+    int nq, nqt, nwords;
+};
+inline FwdStoredLayout fwd_stored_layout(const fipa_desc &d, int Lp, size_t off)
+{
+    FwdStoredLayout w;
+    const size_t BH = (size_t)d.B * d.H;
+    // A constant number of query rows over all pairs (768 tiles of 256), so that the buffers stay affine in L; a range ends
+    // with its longest chains while most of the chip has nothing left.  Four chains of 2.7k to 7.1k residues, 48 pairs:
+    // 98304 / 196608 / 393216 rows 4.00 / 3.52 / 3.35 ms.
+    size_t nq = (196608 / BH + 255) / 256 * 256;
+    if (nq < 256) nq = 256;
+    if (nq > 16384) nq = 16384;
+    if (nq > (size_t)Lp) nq = align_up((size_t)Lp, 256);
+    w.nq = (int)nq;
+    w.nqt = (int)(nq / 256);
+    w.nwords = (Lp / 32 + 31) / 32;
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off = align_up(off + bytes, 256);
+        return at;
+    };
+    w.W = take(BH * nq * Lp * 2);
+    w.flags = take(BH * w.nqt * 8 * w.nwords * 4);
+    w.before = take(BH * w.nqt * 8 * (size_t)Lp * 4);
+    w.mref = take(BH * Lp * 4);
+    w.linv = take(BH * Lp * 4);
+    w.total = off;
+    return w;
+}
+int fwd_stored_slice_blocks(int DZ, int cz);
+struct AttnParams;
+FwdStoredParams fwd_stored_params(const fipa_desc &d, const AttnParams &at, const FwdStoredLayout &st, char *ws);
+
 // ---- backward -----------------------------------------------------------------------------------
 enum { FIPA_BWD_DQ = 0, FIPA_BWD_DK = 1, FIPA_BWD_DV = 2 };
 
@@ -371,6 +429,7 @@ hipError_t launch_attn_fwd_bf16(const AttnParams &p, int DZ, bool fused, hipStre
 bool attn_fwd_ws_supported(int DZ, int cz);  // shapes of the wave-specialised fused kernel
 hipError_t launch_attn_fwd_ws_bf16(const AttnParams &p, int DZ, hipStream_t stream);
 hipError_t launch_attn_fwd_wide_bf16(const AttnParams &p, int DZ, bool fused, hipStream_t stream);  // r*cz = 512
+hipError_t launch_attn_fwd_stored_bf16(const FwdStoredParams &p, int DZ, bool fused, hipStream_t stream);
 hipError_t launch_epilogue_bf16(const EpiParams &p, hipStream_t stream);
 
 }  // namespace fipa

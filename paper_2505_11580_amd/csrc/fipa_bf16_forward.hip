@@ -3,14 +3,49 @@
 
 namespace fipa {
 
-size_t bf16_forward_workspace(const fipa_desc &d)
+namespace {
+
+// r c_z = 512 and 1024: with the weights of a range of query rows in memory (fipa_bf16_attn_fwd_stored.hip) where the
+// workspace holds them, else with S^T formed again for every window of the columns.
+bool stored_width(const fipa_desc &d) { return d.r * d.cz == 512 || d.r * d.cz == 1024; }
+bool stored_fused(const fipa_desc &d) { return d.c == 16 && d.Pv == 8 && fwd_stored_slice_blocks(d.r * d.cz, d.cz) > 0; }
+bool windowed_fused(const fipa_desc &d) { return bf16_fused_epilogue(d) || bf16_wide_fused_epilogue(d); }
+
+size_t stored_workspace(const fipa_desc &d)
 {
-    return bf16_layout(d, !(bf16_fused_epilogue(d) || bf16_wide_fused_epilogue(d))).total;
+    const Bf16Layout w = bf16_layout(d, !stored_fused(d));
+    return fwd_stored_layout(d, w.Lp, w.total).total;
 }
 
-hipError_t bf16_forward(const fipa_desc &d, const FwdArgs &a, void *ws, hipStream_t stream)
+}  // namespace
+
+size_t bf16_forward_workspace_min(const fipa_desc &d) { return bf16_layout(d, !windowed_fused(d)).total; }
+
+size_t bf16_forward_workspace(const fipa_desc &d)
 {
-    const bool wide_fused = bf16_wide_fused_epilogue(d);
+    const size_t least = bf16_forward_workspace_min(d), stored = stored_width(d) ? stored_workspace(d) : 0;
+    return stored > least ? stored : least;
+}
+
+// The description's buffers of the stored-weights forward at `ws` (carved by `st`), and its other arguments from `at`.
+FwdStoredParams fwd_stored_params(const fipa_desc &d, const AttnParams &at, const FwdStoredLayout &st, char *ws)
+{
+    FwdStoredParams p;
+    p.Qh = at.Qh; p.Kh = at.Kh; p.Vh = at.Vh; p.Z2 = at.Z2; p.kbias = at.kbias; p.qbias = at.qbias; p.kvlen = at.kvlen;
+    p.W = (bf16_t *)(ws + st.W); p.flags = (unsigned *)(ws + st.flags); p.before = (float *)(ws + st.before);
+    p.mref = (float *)(ws + st.mref); p.linv = (float *)(ws + st.linv); p.lse2 = at.lse2; p.Ohat = at.Ohat;
+    p.rot = at.rot; p.trans = at.trans; p.cen = at.cen; p.w_b = at.w_b; p.z1 = at.z1; p.mask = at.mask; p.cu = at.cu;
+    p.o = at.o; p.o_pts = at.o_pts; p.o_pair = at.o_pair; p.lse = at.lse;
+    p.B = d.B; p.L = d.L; p.Lp = at.Lp; p.H = d.H; p.cz = d.cz; p.deal = at.deal; p.w_L = d.w_L;
+    p.nq_alloc = st.nq; p.nqt = st.nqt; p.nwords = st.nwords;
+    p.i0 = p.nq = p.units = 0;
+    return p;
+}
+
+hipError_t bf16_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
+{
+    const bool stored = stored_width(d) && ws_bytes >= stored_workspace(d);
+    const bool wide_fused = stored ? stored_fused(d) : bf16_wide_fused_epilogue(d);
     const bool fused = bf16_fused_epilogue(d);
     const Bf16Layout w = bf16_layout(d, !(fused || wide_fused));
     char *base = static_cast<char *>(ws);
@@ -65,9 +100,12 @@ hipError_t bf16_forward(const fipa_desc &d, const FwdArgs &a, void *ws, hipStrea
     const bool ws_kernel = (d.flags & FIPA_FLAG_WAVE_SPECIALISED) && fused && attn_fwd_ws_supported(w.DZ, d.cz) &&
                            w.total < (1ull << 32) && !a.cu;
     timer.begin(1);
-    e = w.DZ > 256 ? launch_attn_fwd_wide_bf16(at, w.DZ, wide_fused, stream)
-        : ws_kernel ? launch_attn_fwd_ws_bf16(at, w.DZ, stream)
-                    : launch_attn_fwd_bf16(at, w.DZ, fused, stream);
+    if (stored)
+        e = launch_attn_fwd_stored_bf16(fwd_stored_params(d, at, fwd_stored_layout(d, w.Lp, w.total), base), w.DZ, wide_fused, stream);
+    else
+        e = w.DZ > 256 ? launch_attn_fwd_wide_bf16(at, w.DZ, wide_fused, stream)
+            : ws_kernel ? launch_attn_fwd_ws_bf16(at, w.DZ, stream)
+                        : launch_attn_fwd_bf16(at, w.DZ, fused, stream);
     if (e != hipSuccess) return e;
     timer.end(1);
     if (fused || wide_fused) return hipSuccess;  // steps 8-9 ran inside the attention kernel

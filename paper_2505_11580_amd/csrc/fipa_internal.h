@@ -87,7 +87,8 @@ bool aligned16(const void *p);
 // Host-side checks of fipa_forward's description and tensor pointers (null, alignment; the
 // workspace is the caller's business), and the dispatch to the fp32 or bf16 chain.
 int check_forward_args(const fipa_desc *desc, const FwdArgs &a);
-hipError_t enqueue_forward(const fipa_desc &desc, const FwdArgs &a, void *workspace, hipStream_t stream);
+// (`workspace_bytes` decides between kernels where a shape has one that needs more scratch than the least)
+hipError_t enqueue_forward(const fipa_desc &desc, const FwdArgs &a, void *workspace, size_t workspace_bytes, hipStream_t stream);
 
 // Stage timing (fipa_profile_begin / fipa_profile_end).  A StageTimer is created per API call;
 // when profiling is inactive every method is a no-op.
@@ -118,7 +119,8 @@ hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, hipStream
 
 // bf16 MFMA path (fipa_bf16_*.hip)
 size_t bf16_forward_workspace(const fipa_desc &d);
-hipError_t bf16_forward(const fipa_desc &d, const FwdArgs &a, void *ws, hipStream_t stream);
+size_t bf16_forward_workspace_min(const fipa_desc &d);  // what the forward runs in, if not at its best
+hipError_t bf16_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream);
 size_t bf16_backward_workspace(const fipa_desc &d);
 
 // IPA module around the core (fipa_module.hip)

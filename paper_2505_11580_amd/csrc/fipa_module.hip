@@ -557,7 +557,7 @@ hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void
     FwdArgs f{base + w.q, base + w.k, base + w.v, base + w.q_pts, base + w.k_pts, base + w.v_pts,
               a.rot, a.trans, a.z1, a.z2, a.w_b, a.gamma, a.mask,
               (float *)(base + w.o), (float *)(base + w.o_pts), (float *)(base + w.o_pair), nullptr};
-    e = keep ? bf16_backward_begin(d, f, base + w.core, stream) : bf16_forward(d, f, base + w.core, stream);
+    e = keep ? bf16_backward_begin(d, f, base + w.core, stream) : bf16_forward(d, f, base + w.core, bf16_forward_workspace(d), stream);
     if (e != hipSuccess) return e;
 
     // ---- Eq. 5: s_out = concat(o_pair, o, o_pts, |o_pts|) W_out^T + b_out --------------------------

@@ -160,7 +160,7 @@ int fipa_forward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const 
         FwdArgs a{q, k, v, q_pts, k_pts, v_pts, rot, trans, z1, z2, w_b, gamma, mask, o, o_pts, o_pair, lse};
         a.cu = cu_dev;
         a.total_rows = pl.total;
-        const hipError_t e = keep ? bf16_backward_begin(pl.d, a, workspace, stream) : bf16_forward(pl.d, a, workspace, stream);
+        const hipError_t e = keep ? bf16_backward_begin(pl.d, a, workspace, stream) : bf16_forward(pl.d, a, workspace, pl.cu_fwd, stream);
         return e == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
     }
 
@@ -178,7 +178,7 @@ int fipa_forward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const 
                         rot + r0 * 9, trans + r0 * 3, at_row(z1, r0, n_z * es), at_row(z2, r0, n_z * es), w_b, gamma,
                         mask ? mask + r0 : nullptr,
                         o + r0 * n_s, o_pts + r0 * n_v, o_pair + r0 * H * desc->cz, lse ? lse + r0 * H : nullptr};
-        if (enqueue_forward(one, a, workspace, stream) != hipSuccess) return FIPA_ERR_LAUNCH;
+        if (enqueue_forward(one, a, workspace, workspace_bytes, stream) != hipSuccess) return FIPA_ERR_LAUNCH;
     }
     return FIPA_OK;
 }

@@ -54,14 +54,13 @@ extern "C" int fipa_forward_static(const fipa_desc *desc, const void *q, const v
     const int rc = fipa::check_forward_args(desc, a);
     if (rc != FIPA_OK) return rc;
     if (desc->flags & FIPA_FLAG_KEEP_FORWARD) return FIPA_ERR_UNSUPPORTED;  // (nothing is kept in the shared scratch)
-    size_t need = 0;
-    fipa_workspace_bytes(desc, &need, nullptr);
+    const size_t need = desc->dtype == FIPA_DTYPE_F32 ? fipa::f32_forward_workspace(*desc) : fipa::bf16_forward_workspace_min(*desc);
     if (need > (size_t)FIPA_STATIC_SCRATCH_BYTES) return FIPA_ERR_WORKSPACE;  // problem too large for the static scratch
     hipError_t e = hipSuccess;
     void *ws = scratch_address(&e);
     if (!ws) return FIPA_ERR_LAUNCH;
     // Everything the kernels expect to start at zero (the arrival counters of the key-range split)
     // is cleared by the first kernel of every call, so the previous call's contents do not matter.
-    e = fipa::enqueue_forward(*desc, a, ws, static_cast<hipStream_t>(hip_stream));
+    e = fipa::enqueue_forward(*desc, a, ws, (size_t)FIPA_STATIC_SCRATCH_BYTES, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
 }
