@@ -601,7 +601,7 @@ hipError_t backward_gradient_part(const fipa_desc &d, const BwdArgs &a, const Bw
         sp.dQ = (float *)(base + w.dQhat); sp.dKh = (float *)(base + w.dKh); sp.dVh = (float *)(base + w.dVh);
         sp.dZ = (float *)(base + w.dZ); sp.rowsum = (float *)(base + w.rowsum); sp.colsum = (float *)(base + w.colsum);
         sp.B = d.B; sp.L = d.L; sp.Lp = w.f.Lp; sp.H = d.H; sp.deal = a.f.mask != nullptr || a.f.cu != nullptr;
-        sp.Lk = w.Lk; sp.nq_alloc = w.nq; sp.i0 = 0; sp.nq = 0; sp.units = sp.nseg = sp.seg_blocks = 0;
+        sp.Lk = w.Lk; sp.nq_alloc = w.nq; sp.i0 = 0; sp.nq = 0; sp.units = sp.q_units = sp.nseg = sp.seg_blocks = 0;
         e = launch_bwd_stored_bf16(sp, w.f.DZ, stream);
         if (e != hipSuccess) return e;
     } else {

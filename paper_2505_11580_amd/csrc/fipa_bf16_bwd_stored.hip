@@ -550,18 +550,30 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
         }
 }
 
-template <bool KV, int DZ, int HV, int ZBL>
-__global__ __launch_bounds__(256, 1) void fipa_bwd_accum_kernel(BwdStoredParams p)
+// Both products of a range in one launch, the key side (whose workgroups take longer) first: with one workgroup per compute
+// unit and few rounds of them, the query side's workgroups fill what the last round of the key side leaves idle.
+// Two launches -> one: B = 2, L = 4096, r c_z = 256 820 -> 720 us; B = 2, L = 2048 230 -> 220 us; four chains of 2.7k to 7.1k
+// residues, r c_z = 512, 4.6 -> 4.4 ms.
+template <int DZ>
+__global__ __launch_bounds__(256, 1) void fipa_bwd_products_kernel(BwdStoredParams p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    constexpr int NWIN = AcCfg<KV, DZ, HV, ZBL, 0>::NWIN;
+    constexpr int NWIN = AcCfg<true, DZ, 2, 8, 0>::NWIN;
     // each XCD gets a contiguous run of tiles; the windows of a tile are neighbours in its launch order
-    const int per_xcd = (p.units + 7) / 8;
-    const int slot = blockIdx.x / 8;
-    const int logical = (blockIdx.x % 8) * per_xcd + slot / NWIN;
-    if (slot / NWIN >= per_xcd || logical >= p.units) return;
-    if (NWIN == 1 || slot % NWIN == 0) accum_window<KV, DZ, HV, ZBL, 0>(p, smem, logical);
-    else accum_window<KV, DZ, HV, ZBL, NWIN - 1>(p, smem, logical);
+    const int kv_xcd = (p.units + 7) / 8, q_xcd = (p.q_units + 7) / 8;
+    const bool kv = (int)blockIdx.x < 8 * kv_xcd * NWIN;
+    const int blk = kv ? blockIdx.x : blockIdx.x - 8 * kv_xcd * NWIN;
+    const int slot = blk / 8, win = slot % NWIN;
+    const int per_xcd = kv ? kv_xcd : q_xcd, units = kv ? p.units : p.q_units;
+    const int logical = (blk % 8) * per_xcd + slot / NWIN;
+    if (slot / NWIN >= per_xcd || logical >= units) return;
+    if (kv) {
+        if (NWIN == 1 || win == 0) accum_window<true, DZ, 2, 8, 0>(p, smem, logical);
+        else accum_window<true, DZ, 2, 8, NWIN - 1>(p, smem, logical);
+    } else {
+        if (NWIN == 1 || win == 0) accum_window<false, DZ, 2, 8, 0>(p, smem, logical);
+        else accum_window<false, DZ, 2, 8, NWIN - 1>(p, smem, logical);
+    }
 }
 
 template <class K>
@@ -575,13 +587,15 @@ hipError_t launch_kernel(K kernel, LdsLimit &limit, int threads, int lds, int bl
 
 constexpr int kCU = 256;
 
-template <bool KV, int DZ, int HV, int ZBL>
-hipError_t launch_accum(BwdStoredParams p, hipStream_t stream)
+template <int DZ>
+hipError_t launch_products(BwdStoredParams p, hipStream_t stream)
 {
-    using C = AcCfg<KV, DZ, HV, ZBL, 0>;
+    using C = AcCfg<true, DZ, 2, 8, 0>;
+    static_assert(C::LDS_BYTES == AcCfg<false, DZ, 2, 8, 0>::LDS_BYTES && C::NWIN == AcCfg<false, DZ, 2, 8, 0>::NWIN, "one launch");
     static LdsLimit limit;
-    p.units = p.B * p.H * (((KV ? p.Lp : p.nq) + 128 * HV - 1) / (128 * HV));
-    return launch_kernel(fipa_bwd_accum_kernel<KV, DZ, HV, ZBL>, limit, 256, C::LDS_BYTES, (p.units + 7) / 8 * 8 * C::NWIN, p, stream);
+    p.units = p.B * p.H * ((p.Lp + 255) / 256);
+    p.q_units = p.B * p.H * ((p.nq + 255) / 256);
+    return launch_kernel(fipa_bwd_products_kernel<DZ>, limit, 256, C::LDS_BYTES, ((p.units + 7) / 8 + (p.q_units + 7) / 8) * 8 * C::NWIN, p, stream);
 }
 
 template <int DZ>
@@ -611,9 +625,7 @@ hipError_t launch_bwd_stored_bf16(const BwdStoredParams &p0, int DZ, hipStream_t
         p.nq = p0.Lp - i0 < p0.nq_alloc ? p0.Lp - i0 : p0.nq_alloc;
         hipError_t e = DZ == 256 ? launch_weights<256>(p, stream) : launch_weights<512>(p, stream);
         if (e != hipSuccess) return e;
-        e = DZ == 256 ? launch_accum<true, 256, 2, 8>(p, stream) : launch_accum<true, 512, 2, 8>(p, stream);
-        if (e != hipSuccess) return e;
-        e = DZ == 256 ? launch_accum<false, 256, 2, 8>(p, stream) : launch_accum<false, 512, 2, 8>(p, stream);
+        e = DZ == 256 ? launch_products<256>(p, stream) : launch_products<512>(p, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -384,7 +384,7 @@ struct BwdStoredParams {
     int B, L, Lp, H, deal;
     int Lk;               // Lp rounded up to 256: keys per group of weights
     int nq_alloc, i0, nq; // query rows the buffers hold; this range
-    int units, nseg, seg_blocks;
+    int units, q_units, nseg, seg_blocks;
 };
 
 struct BwdPackParams {
