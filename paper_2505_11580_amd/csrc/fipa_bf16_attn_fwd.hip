@@ -450,15 +450,8 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
     // A tile whose rows all lie past the last valid residue of its chain (padding of a ragged
     // batch) has nothing to attend from: its outputs are zero by definition.
     if (qt * kTileQ >= kvlen) {
-        if constexpr (!FUSED) {
-            float *orow = p.Ohat + ((size_t)bh * p.Lp + irow) * C::DV;
-#pragma unroll
-            for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-                for (int a = 0; a < 4; ++a)
-                    *reinterpret_cast<f32x4 *>(orow + 32 * nb + 8 * a + 4 * g) = (f32x4){0.f, 0.f, 0.f, 0.f};
-            if (g == 0) p.lse2[(size_t)bh * p.Lp + irow] = -INFINITY;
-        } else if (irow < ulen && part == 0) {
+        if (!FUSED) return;  // (nothing reads the lifted output of rows past the last valid one)
+        if (irow < ulen && part == 0) {
             const size_t row = (urow0 + irow) * p.H + (bh - b * p.H);
             const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll

@@ -178,6 +178,7 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
 #pragma unroll
         for (int r = 1; r < 16; ++r) m = fmaxf(m, own[r]);
         m = fmaxf(m, __shfl_xor(m, 32));
+        if (irow >= kvlen) m = INFINITY;  // (a row past the chain: whatever its memory holds, weights 0 and no raise)
     }
     constexpr int kPin = KS - KSH < 64 ? KS - KSH : 64;
 #pragma unroll
@@ -350,6 +351,7 @@ __device__ __forceinline__ void values_window(const FwdStoredParams &p, char *sm
     const int kvlen = p.deal ? p.kvlen[b] : p.L;
     const int row0 = p.i0 + tile * kTile;
     const int nblk = row0 >= kvlen ? 0 : (kvlen + 31) / 32;
+    if (HB == 0 && nblk == 0) return;  // (nothing reads the lifted output of rows past the last valid one)
     const size_t rows0 = (size_t)bh * p.Lp;
 
     f32x16 acch[C::NH > 0 ? C::NH : 1][HV], accz[C::ZBL][HV];
@@ -528,6 +530,7 @@ __device__ __forceinline__ void values_window(const FwdStoredParams &p, char *sm
         const bool live = nblk > 0 && irow < kvlen;
         const float inv = live ? p.linv[rows0 + irow] : 0.f;
         if constexpr (HB == 0) {
+            if (!live) continue;
             float *orow = p.Ohat + (rows0 + irow) * D;
 #pragma unroll
             for (int nb = 0; nb < C::NH + C::ZBL; ++nb) {
@@ -537,11 +540,10 @@ __device__ __forceinline__ void values_window(const FwdStoredParams &p, char *sm
                 for (int q = 0; q < 4; ++q) {
                     f32x4 v;
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) v[x] = live ? a[4 * q + x] * inv : 0.f;
+                    for (int x = 0; x < 4; ++x) v[x] = a[4 * q + x] * inv;
                     *reinterpret_cast<f32x4 *>(dst + 8 * q) = v;
                 }
             }
-            if (HEAD && g == 0 && !live) p.lse2[rows0 + irow] = kNegInf;
         } else {
             if (irow >= ulen) continue;
             const bool valid = live && inv > 0.f && (p.mask ? p.mask[urow0 + irow] != 0 : true);

@@ -23,6 +23,7 @@ __global__ __launch_bounds__(256) void fipa_bwd_pack_bf16_kernel(BwdPackParams p
     const int i = (int)(row_id % p.Lp);
     const size_t bh = row_id / p.Lp;
     const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    if (i >= ((p.kvlen[b] + 31) & ~31)) return;  // (the gradient kernels stream whole blocks of 32 rows and no further)
     const int c = p.c, D = kDH + p.DZ, PH = (p.Pv + 1) / 2;
     const size_t urow = user_row(p, b, i);  // (only used where i < the chain's length)
     const bool valid = i < user_len(p, b) && (p.mask ? p.mask[urow] != 0 : true);
@@ -309,7 +310,18 @@ __global__ __launch_bounds__(1024) void fipa_bwd_gamma_kernel(const float *gpart
     __shared__ float red[1024];
     const int h = blockIdx.x, tid = threadIdx.x;
     float s4[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int b = 0; b < B; ++b) {
+    if (B >= 16) {  // many chains: a wave each (one after the other they are a chain of B dependent loads: 16 us at B = 32)
+        for (int b = tid >> 6; b < B; b += 16) {
+            const int len = cu ? cu[b + 1] - cu[b] : L;
+            const float *g = gpart + ((size_t)b * H + h) * Lp;
+            for (int i0 = tid & 63; i0 < len; i0 += 256)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + 64 * u;
+                    s4[u] += i < len ? g[i] : 0.f;
+                }
+        }
+    } else for (int b = 0; b < B; ++b) {
         const int len = cu ? cu[b + 1] - cu[b] : L;
         const float *g = gpart + ((size_t)b * H + h) * Lp;
         for (int i0 = tid; i0 < len; i0 += 4096)
@@ -345,17 +357,21 @@ __global__ __launch_bounds__(256) void fipa_bwd_wb_partial_kernel(BwdUnpackParam
     const int NG = p.DZ / 4, NRG = 256 / NG;
     const int cg = threadIdx.x % NG, rg = threadIdx.x / NG, x0 = 4 * cg;
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    int b0 = 0;  // packed batch: the chain that holds the chunk's first row, the last b with cu[b] <= it
+    if (p.cu) {
+        int hi = p.B - 1;
+        while (b0 < hi) {
+            const int mid = (b0 + hi + 1) >> 1;
+            if (p.cu[mid] <= chunk * kWbChunk) b0 = mid; else hi = mid - 1;
+        }
+    }
 #pragma unroll 4
     for (int t = rg; t < kWbChunk; t += NRG) {
         const int bi = min(chunk * kWbChunk + t, nres - 1);
         int b, i;
-        if (p.cu) {  // the chain that holds row bi: last b with cu[b] <= bi
-            int lo = 0, hi = p.B - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (p.cu[mid] <= bi) lo = mid; else hi = mid - 1;
-            }
-            b = lo;
+        if (p.cu) {
+            b = b0;
+            while (b + 1 < p.B && p.cu[b + 1] <= bi) ++b;
             i = bi - p.cu[b];
         } else {
             b = bi / p.L;
@@ -524,6 +540,7 @@ PackParams bwd_pack_params(const fipa_desc &d, const FwdArgs &f, const BwdLayout
     pk.cen_out = prep_in_pack ? reinterpret_cast<float *>(base + w.f.cen) : nullptr;
     pk.kvlen_out = prep_in_pack ? reinterpret_cast<int *>(base + w.f.kvlen) : nullptr;
     pk.counters = nullptr; pk.n_counters = 0;
+    pk.kvlen = reinterpret_cast<const int *>(base + w.f.kvlen);
     return pk;
 }
 
@@ -586,7 +603,7 @@ hipError_t backward_gradient_part(const fipa_desc &d, const BwdArgs &a, const Bw
     bp.B = d.B; bp.L = d.L; bp.Lp = w.f.Lp; bp.H = d.H; bp.c = d.c; bp.Pv = d.Pv; bp.cz = d.cz; bp.r = d.r;
     bp.DZ = w.f.DZ;
     const bool stored = bwd_stored(w.f.DZ);
-    bp.neg_d = stored;
+    bp.neg_d = stored; bp.kvlen = kvlen;
     hipError_t e = launch_bwd_pack_bf16(bp, stream);
     if (e != hipSuccess) return e;
     timer.end(0);

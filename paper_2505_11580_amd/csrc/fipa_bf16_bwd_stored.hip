@@ -344,8 +344,8 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
     const int row_lo = (KV ? 0 : p.i0) + tile * TS;         // first stationary row
     const int nvalid = min(kvlen, p.i0 + p.nq);             // (KV: end of the queries of this range)
     // steps of 16 queries (whole blocks of 32), or of 32 keys
-    const int nstep = row_lo >= kvlen ? 0 : (KV ? max(0, (nvalid - p.i0 + 31) / 32) * 2 : (kvlen + 31) / 32);
-    if (KV && p.i0 > 0 && nstep == 0) return;               // (a later range of queries adds nothing)
+    const int nstep = (KV ? max(0, (nvalid - p.i0 + 31) / 32) * 2 : (kvlen + 31) / 32);
+    if (row_lo >= kvlen || (KV && p.i0 > 0 && nstep == 0)) return;  // (rows past the chain are not read; a range without queries adds nothing)
 
     const size_t rows0 = (size_t)bh * p.Lp;
     f32x16 acch[C::NHB > 0 ? C::NHB : 1][HV], accz[C::ZBL][HV];
@@ -530,14 +530,13 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
 
     const bool add = KV && p.i0 > 0;  // later ranges of queries add to the sums of the earlier ones
     outputs([&](float *dst, f32x16 &a, int row) {
-        if (row >= p.Lp) return;
-        const bool in = row < kvlen;  // (rows past the chain: whatever the tile held there)
+        if (row >= kvlen) return;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             f32x4 v = {0.f, 0.f, 0.f, 0.f};
             if (add) v = *reinterpret_cast<const f32x4 *>(dst + 8 * q + 4 * g);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) v[x] = in ? v[x] + a[4 * q + x] : 0.f;
+            for (int x = 0; x < 4; ++x) v[x] += a[4 * q + x];
             *reinterpret_cast<f32x4 *>(dst + 8 * q + 4 * g) = v;
         }
     });
@@ -546,7 +545,7 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
         for (int hv = 0; hv < HV; ++hv) {
             const int row = row_lo + 32 * (HV * wave + hv) + li;
             const float tot = wsum[hv] + __shfl_xor(wsum[hv], 32);
-            if (g == 0 && row < p.Lp) sums[rows0 + row] = row < kvlen ? (add ? sums[rows0 + row] : 0.f) + tot : 0.f;
+            if (g == 0 && row < kvlen) sums[rows0 + row] = (add ? sums[rows0 + row] : 0.f) + tot;
         }
 }
 

@@ -262,6 +262,7 @@ struct PackParams {
     int *kvlen_out;
     int *counters;
     int n_counters;
+    const int *kvlen;  // the same bounds for the kernels behind it
 };
 
 struct AttnParams {
@@ -396,6 +397,7 @@ struct BwdPackParams {
     float *Dvec, *nlse;
     int B, L, Lp, H, c, Pv, cz, r, DZ;
     bool neg_d;  // store -D
+    const int *kvlen;
 };
 
 struct BwdUnpackParams {

@@ -138,6 +138,7 @@ __global__ __launch_bounds__(256) void fipa_pack_qz_bf16_kernel(PackParams p)
     const int i = (int)(rest % p.Lp);
     rest /= p.Lp;
     const int h = (int)(rest % p.H), b = (int)(rest / p.H);
+    if (i >= ((p.kvlen[b] + kTileQ - 1) & ~(kTileQ - 1))) return;  // (no kernel reads a tile past the last valid residue)
     const size_t urow = user_row(p, b, i);
     const bool ok = i < user_len(p, b) && (p.mask ? p.mask[urow] != 0 : true);
     __attribute__((aligned(16))) bf16_t out[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -268,6 +269,7 @@ __global__ __launch_bounds__(256) void fipa_pack_heads_af2_bf16_kernel(PackParam
     const size_t idx0 = (size_t)(blockIdx.x - role * nbh) * 256;
     const size_t idx = idx0 + threadIdx.x;  // (b, i, h), h fastest
     float cen[3] = {0.f, 0.f, 0.f};
+    int kvmine = p.Lp;
     if (p.cen_out) {
         if (role == 0)
             for (int i = (int)idx; i < p.n_counters; i += (int)nbh * 256) p.counters[i] = 0;
@@ -280,9 +282,11 @@ __global__ __launch_bounds__(256) void fipa_pack_heads_af2_bf16_kernel(PackParam
             float cb[3];
             int kv;
             batch_reference(p, bb, cb, kv);
-            if (bb == bmine)
+            if (bb == bmine) {
+                kvmine = kv;
 #pragma unroll
                 for (int a = 0; a < 3; ++a) cen[a] = cb[a];
+            }
             if (role == 0 && idx == (size_t)bb * per_batch) {  // the thread that packs (bb, 0, 0) publishes
                 p.cen_out[4 * bb + 0] = cb[0];
                 p.cen_out[4 * bb + 1] = cb[1];
@@ -293,11 +297,12 @@ __global__ __launch_bounds__(256) void fipa_pack_heads_af2_bf16_kernel(PackParam
         }
     }
     // (whole waves stay together from here on: the rows leave through LDS, wave by wave)
-    const bool active = idx < total;
-    const size_t idc = active ? idx : total - 1;
+    const size_t idc = idx < total ? idx : total - 1;
     const int h = (int)(idc % p.H);
     const size_t bi = idc / p.H;
     const int i = (int)(bi % p.Lp), b = (int)(bi / p.Lp);
+    // (no kernel reads a tile past the last valid residue of its chain)
+    const bool active = idx < total && i < ((kvmine + kTileQ - 1) & ~(kTileQ - 1));
     if (!p.cen_out)
 #pragma unroll
         for (int a = 0; a < 3; ++a) cen[a] = p.cen[4 * b + a];
