@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(con
 // read, and the one-hot operand is formed in registers: a lane owns a table row and compares it with the
 // 16-bit codes of its eight residues (three packed instructions per two residues).
 // 32768 residues (half of them valid), 20 slots, 82 rows, 512 columns: 555 us with four waves that shared each tile and marked
-// a one-hot tile in LDS (one barrier per tile, the mask on the way of every load) -> 137 us.
+// a one-hot tile in LDS (one barrier per tile, the mask on the way of every load) -> 131 us.
 // rows = n_bins + n_pos + 1 (the last one collects the bias gradient, in slot 0's workgroups).
 constexpr int kFbWaves = 8, kFbStages = 4, kFbMaxRowBlocks = 5;
 constexpr int kFbZ = 32 * 128;                          // a tile's d_z: 32 rows of 64 columns, the 64-byte halves of a row exchanged in every other pair of rows
@@ -348,25 +348,29 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
                         for (int x = 0; x < 4; ++x) acc[mb][nb][4 * q + x] += v[x];
                     }
     }
-    if (wave != 0) return;
-    // accumulator register r of a lane: row 8 (r / 4) + 4 g + r % 4 of the row block, column li of the column block
+    // out through LDS, all threads storing: accumulator register r of a lane is row 8 (r / 4) + 4 g + r % 4 of the row block,
+    // column li of the column block
+    constexpr int kOutStride = 68 * 4;
+    __syncthreads();
+    if (wave == 0)
 #pragma unroll
-    for (int mb = 0; mb < RB; ++mb)
+        for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            const int col = col0 + 32 * nb + li;
-            if (col >= n_out) continue;
+            for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = 32 * mb + 8 * (r >> 2) + 4 * g + (r & 3);
-                if (row < n_bins)
-                    d_e_bin[((size_t)s * n_bins + row) * n_out + col] = acc[mb][nb][r];
-                else if (row < n_bins + n_pos)
-                    d_e_pos[((size_t)s * n_pos + (row - n_bins)) * n_out + col] = acc[mb][nb][r];
-                else if (row == R - 1 && s == 0 && d_bias)
-                    d_bias[col] = acc[mb][nb][r];
-            }
-        }
+                for (int r = 0; r < 16; ++r)
+                    *reinterpret_cast<float *>(fb_smem + (32 * mb + 8 * (r >> 2) + 4 * g + (r & 3)) * kOutStride + (32 * nb + li) * 4) = acc[mb][nb][r];
+    __syncthreads();
+    for (int x = threadIdx.x; x < 16 * R; x += 64 * kFbWaves) {
+        const int row = x >> 4, c = 4 * (x & 15), col = col0 + c;
+        if (col >= n_out) continue;  // (n_out is a multiple of 8)
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(fb_smem + row * kOutStride + 4 * c);
+        float *dst = nullptr;
+        if (row < n_bins) dst = d_e_bin + ((size_t)s * n_bins + row) * n_out;
+        else if (row < R - 1) dst = d_e_pos + ((size_t)s * n_pos + (row - n_bins)) * n_out;
+        else if (s == 0) dst = d_bias;
+        if (dst) *reinterpret_cast<f32x4 *>(dst + col) = v;
+    }
 }
 
 template <int RB>
