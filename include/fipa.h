@@ -100,8 +100,11 @@ const char *fipa_status_string(int status);
 
 /*
  * Scratch sizes in bytes for fipa_forward / fipa_backward with this description.  Both are
- * affine in L (the linear-memory property of Section 2.3).  Either output pointer may be
- * NULL.  Host-only, touches no device.
+ * affine in L once L exceeds a constant (the linear-memory property of Section 2.3): the forward at
+ * r c_z >= 512 and the backward at r c_z >= 256 hold the attention weights of a constant number of
+ * query rows (at most 16384, respectively 4096 per (batch, head) pair) against all keys.  fipa_forward
+ * also runs, more slowly, in a workspace without those weights (and fipa_forward_static does where its
+ * scratch is too small for them).  Either output pointer may be NULL.  Host-only, touches no device.
  */
 int fipa_workspace_bytes(const fipa_desc *desc, size_t *forward_bytes, size_t *backward_bytes);
 

@@ -397,34 +397,35 @@ __global__ __launch_bounds__(256) void fipa_bwd_wb_partial_kernel(BwdUnpackParam
     }
 }
 
-// One workgroup of 1024 threads per head: the chunks are dealt to 1024 / DZ groups of threads
-// (four independent chains of loads each); groups, then rho, are added in a fixed order.
+// One workgroup of 1024 threads per head and 32 (where c_z is no multiple of 32: 8) of its c_z columns, of every factor slice: the
+// chunks are dealt to the groups of threads that hold those columns (four independent chains of loads each); groups and
+// slices are added in a fixed order.  (One workgroup per head: 82 us for 12 heads of 1024 chunks of 512 columns -> 25 us.)
+__host__ __device__ inline int wb_columns(int cz) { return cz % 32 == 0 ? 32 : 8; }
+
 __global__ __launch_bounds__(1024) void fipa_bwd_wb_reduce_kernel(BwdUnpackParams p, int nchunk)
 {
-    __shared__ float part[1024];  // [chunk group][DZ]
-    __shared__ float col[512];    // per lifted pair column: sum over the chunks
-    const int h = blockIdx.x;
-    const int NCG = 1024 / p.DZ, x = threadIdx.x % p.DZ, cgp = threadIdx.x / p.DZ;
-    float s4[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int ch0 = cgp; ch0 < nchunk; ch0 += 4 * NCG)
+    __shared__ float part[1024];  // [chunk group][slice][column]
+    const int h = blockIdx.x, CB = wb_columns(p.cz), d0 = blockIdx.y * CB;
+    const int NCOL = CB * p.r, NCG = 1024 / NCOL;  // (r c_z <= 512 here)
+    const int cidx = threadIdx.x % NCOL, grp = threadIdx.x / NCOL;
+    if (grp < NCG) {
+        const int x = cidx / CB * p.cz + d0 + cidx % CB;
+        float s4[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int ch0 = grp; ch0 < nchunk; ch0 += 4 * NCG)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int ch = ch0 + u * NCG;
-            const float v = p.wpart[((size_t)h * nchunk + min(ch, nchunk - 1)) * p.DZ + x];
-            s4[u] += ch < nchunk ? v : 0.f;
-        }
-    part[cgp * p.DZ + x] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-    __syncthreads();
-    if (threadIdx.x < p.DZ) {
-        float t = 0.f;
-        for (int g = 0; g < NCG; ++g) t += part[g * p.DZ + threadIdx.x];
-        col[threadIdx.x] = t;
+            for (int u = 0; u < 4; ++u) {
+                const int ch = ch0 + u * NCG;
+                const float v = p.wpart[((size_t)h * nchunk + min(ch, nchunk - 1)) * p.DZ + x];
+                s4[u] += ch < nchunk ? v : 0.f;
+            }
+        part[grp * NCOL + cidx] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
     }
     __syncthreads();
-    for (int d = threadIdx.x; d < p.cz; d += 1024) {
+    if (threadIdx.x < CB) {
         float t = 0.f;
-        for (int rho = 0; rho < p.r; ++rho) t += col[rho * p.cz + d];
-        p.d_w_b[(size_t)h * p.cz + d] = p.w_L * p.ds_inv * t;
+        for (int rho = 0; rho < p.r; ++rho)
+            for (int g = 0; g < NCG; ++g) t += part[g * NCOL + rho * CB + threadIdx.x];
+        p.d_w_b[(size_t)h * p.cz + d0 + threadIdx.x] = p.w_L * p.ds_inv * t;
     }
 }
 
@@ -509,7 +510,7 @@ hipError_t launch_bwd_unpack_bf16(const BwdUnpackParams &p, hipStream_t stream)
     if (p.d_w_b) {
         const int nchunk = (p.total_rows + kWbChunk - 1) / kWbChunk;
         hipLaunchKernelGGL(fipa_bwd_wb_partial_kernel, dim3(nchunk, p.H), dim3(256), 0, stream, p);
-        hipLaunchKernelGGL(fipa_bwd_wb_reduce_kernel, dim3(p.H), dim3(1024), 0, stream, p, nchunk);
+        hipLaunchKernelGGL(fipa_bwd_wb_reduce_kernel, dim3(p.H, p.cz / wb_columns(p.cz)), dim3(1024), 0, stream, p, nchunk);
     }
     return hipGetLastError();
 }
