@@ -129,7 +129,7 @@ struct SplitPlan {
     int units() const { return full + rem * S; }
 };
 
-inline SplitPlan attn_split_plan(int total_tiles, int Lp, int DZ, int cz, bool fused)
+inline SplitPlan attn_split_plan(int total_tiles, int Lp, int DZ, int cz, bool fused, bool wave_specialised)
 {
     constexpr int kCU = 256;
     SplitPlan s;
@@ -137,7 +137,11 @@ inline SplitPlan attn_split_plan(int total_tiles, int Lp, int DZ, int cz, bool f
     s.rem = total_tiles - s.full;
     s.S = 1;
     if (fused && DZ <= 256 && cz >= 32 && s.rem > 0 && s.rem <= kCU / 2) {
-        const int by_blocks = (Lp / 32) / 4;  // at least four 32-key blocks per part
+        // At least four 32-key blocks per part; below 16 blocks the exchange and the second start-up cost more than the
+        // shorter loops give.  One chain, H = 12, r c_z = 256, attention split / whole: 131 residues 20.8 / 18.2 us,
+        // 200 22.4 / 19.9, 300 24.3 / 22.6; 400 (16 blocks) in four / two parts 25.2 / 25.7, 600 28.1 / 29.4.
+        // (The wave-specialised variant keeps its parts: it is not right on whole tiles of so few blocks.)
+        const int blocks = Lp / 32, by_blocks = blocks < 16 && !wave_specialised ? 1 : blocks / 4;
         s.S = kCU / s.rem;
         if (s.S > 4) s.S = 4;
         if (s.S > by_blocks) s.S = by_blocks;
@@ -227,7 +231,7 @@ inline Bf16Layout bf16_layout(const fipa_desc &d, bool with_ohat, bool with_qz =
     w.qbias = take(BH * w.Lp * sizeof(float));
     w.lse2 = take(BH * w.Lp * sizeof(float));
     w.Ohat = with_ohat ? take(BH * w.Lp * (size_t)(kDH + w.DZ) * sizeof(float)) : 0;
-    w.plan = attn_split_plan((int)(BH * (w.Lp / kTileQ)), w.Lp, w.DZ, d.cz, !with_ohat);
+    w.plan = attn_split_plan((int)(BH * (w.Lp / kTileQ)), w.Lp, w.DZ, d.cz, !with_ohat, (d.flags & FIPA_FLAG_WAVE_SPECIALISED) != 0);
     // (sized for the largest split any length can give, so that the total stays affine in L)
     const bool can_split = !with_ohat && w.DZ <= 256 && d.cz >= 32;
     w.partial = can_split ? take((size_t)kMaxSplitUnits * 4 * attn_partial_groups(d.cz) * 64 * 16) : 0;
