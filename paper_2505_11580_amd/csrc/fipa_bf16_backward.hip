@@ -484,7 +484,7 @@ BwdLayout bwd_layout(const fipa_desc &d)
     w.gpart = take(BHL * 4);
     w.wpart = take((size_t)d.H * (((size_t)d.B * d.L + kWbChunk - 1) / kWbChunk) * w.f.DZ * 4);
     w.total = off;
-    if (w.f.DZ > 256) {
+    if (fwd_stored_pays(d)) {
         const size_t fwd = fwd_stored_layout(d, w.f.Lp, w.f.total).total;
         if (fwd > w.total) w.total = fwd;
     }
@@ -571,10 +571,10 @@ hipError_t backward_forward_part(const fipa_desc &d, const FwdArgs &f, const Bwd
     at.plan = w.f.plan; at.partial = nullptr; at.counters = nullptr;  // (unfused: never split)
     at.deal = f.mask != nullptr || f.cu != nullptr;
     // (width 576: its weights lie where the gradient part begins, which is not yet in use)
-    if (w.f.DZ > 256)
+    if (fwd_stored_pays(d))
         e = launch_attn_fwd_stored_bf16(fwd_stored_params(d, at, fwd_stored_layout(d, w.f.Lp, w.f.total), base), w.f.DZ, false, stream);
     else
-        e = launch_attn_fwd_bf16(at, w.f.DZ, false, stream);
+        e = w.f.DZ > 256 ? launch_attn_fwd_wide_bf16(at, w.f.DZ, false, stream) : launch_attn_fwd_bf16(at, w.f.DZ, false, stream);
     if (e != hipSuccess || !f.o) return e;
 
     EpiParams ep;

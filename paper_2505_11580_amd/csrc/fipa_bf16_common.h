@@ -355,6 +355,15 @@ inline FwdStoredLayout fwd_stored_layout(const fipa_desc &d, int Lp, size_t off)
     w.total = off;
     return w;
 }
+// Whether the call has enough work for it: two launches whose workgroups hold a compute unit each against one.  In units of
+// (256 queries) x (32 keys) over all pairs, stored against windowed at width 576, H = 12: 1536 (one chain of 1024) 129 / 72 us,
+// 2304 (8 x 384) 115 / 109, 3072 (8 x 512) 132 / 134, 3600 (5 x 631) 141 / 143, 6144 (4 x 1024) 183 / 204, 6144 (one of 2048) 204 / 223.
+// At width 1088, stored against windowed: 48 (one chain of 128) 53 / 48 us, 96 (256) 68 / 66, 384 (8 x 128) 76 / 101, 384 (512) 90 / 95.
+inline bool fwd_stored_pays(const fipa_desc &d)
+{
+    const long long Lp = (long long)align_up((size_t)d.L, kTileQ), work = (long long)d.B * d.H * ((Lp + 255) / 256) * (Lp / 32);
+    return d.r * d.cz == 512 ? work >= 4096 : d.r * d.cz == 1024 && work >= 256;
+}
 int fwd_stored_slice_blocks(int DZ, int cz);
 struct AttnParams;
 FwdStoredParams fwd_stored_params(const fipa_desc &d, const AttnParams &at, const FwdStoredLayout &st, char *ws);

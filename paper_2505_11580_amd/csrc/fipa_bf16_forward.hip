@@ -6,8 +6,7 @@ namespace fipa {
 namespace {
 
 // r c_z = 512 and 1024: with the weights of a range of query rows in memory (fipa_bf16_attn_fwd_stored.hip) where the
-// workspace holds them, else with S^T formed again for every window of the columns.
-bool stored_width(const fipa_desc &d) { return d.r * d.cz == 512 || d.r * d.cz == 1024; }
+// workspace holds them and the call is large enough, else with S^T formed again for every window of the columns.
 bool stored_fused(const fipa_desc &d) { return d.c == 16 && d.Pv == 8 && fwd_stored_slice_blocks(d.r * d.cz, d.cz) > 0; }
 bool windowed_fused(const fipa_desc &d) { return bf16_fused_epilogue(d) || bf16_wide_fused_epilogue(d); }
 
@@ -23,7 +22,7 @@ size_t bf16_forward_workspace_min(const fipa_desc &d) { return bf16_layout(d, !w
 
 size_t bf16_forward_workspace(const fipa_desc &d)
 {
-    const size_t least = bf16_forward_workspace_min(d), stored = stored_width(d) ? stored_workspace(d) : 0;
+    const size_t least = bf16_forward_workspace_min(d), stored = fwd_stored_pays(d) ? stored_workspace(d) : 0;
     return stored > least ? stored : least;
 }
 
@@ -44,7 +43,7 @@ FwdStoredParams fwd_stored_params(const fipa_desc &d, const AttnParams &at, cons
 
 hipError_t bf16_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
 {
-    const bool stored = stored_width(d) && ws_bytes >= stored_workspace(d);
+    const bool stored = fwd_stored_pays(d) && ws_bytes >= stored_workspace(d);
     const bool wide_fused = stored ? stored_fused(d) : bf16_wide_fused_epilogue(d);
     const bool fused = bf16_fused_epilogue(d);
     const Bf16Layout w = bf16_layout(d, !(fused || wide_fused));

@@ -12,25 +12,30 @@ from tests.test_zz_no_alloc import OUT, _both
 pytestmark = pytest.mark.gpu
 
 
+# (enough pairs that the library takes this path; 6 sampled rows of every batch element)
 @pytest.mark.parametrize("kw", [
-    dict(L=1, H=1), dict(L=31), dict(L=33, r=8), dict(L=129), dict(L=257), dict(L=257, r=8, H=1),
-    dict(L=300, cz=64, r=8), dict(L=300, cz=256, r=2, H=1), dict(L=140, cz=256, r=4, H=1), dict(L=140, cz=512, r=1, H=1),
-    dict(L=600, H=1, B=3, varlen=True, min_len=1), dict(L=600, r=8, H=1, B=3, varlen=True, min_len=1),
-    dict(L=300, c=8, Pq=2, Pv=3)])
+    dict(L=257, B=15), dict(L=385, B=9, cz=64, r=8), dict(L=600, B=6, cz=256, r=2, varlen=True, min_len=1), dict(L=300, B=16, c=8, Pq=2, Pv=3),
+    dict(L=257, r=8), dict(L=129, B=4, r=8), dict(L=140, B=3, cz=256, r=4), dict(L=140, B=3, cz=512, r=2), dict(L=300, B=2, cz=64, r=16),
+    dict(L=600, r=8, H=4, B=3, varlen=True, min_len=1)])
 def test_forward_stored_weights(kw):
-    inp = wl.make_inputs(3, **dict(dict(B=1, H=2, cz=128, r=4, varlen=False, trans_scale=0.3), **kw))
-    gu.check(inp, label="fwd stored %s" % kw)
+    inp = wl.make_inputs(3, **dict(dict(B=1, H=12, cz=128, r=4, varlen=False, trans_scale=0.3), **kw))
+    gu.check(inp, rows=wl.select_rows(inp, 6), label="fwd stored %s" % kw)
 
 
-@pytest.mark.parametrize("r", [4, 8])
-def test_forward_stored_weights_raised_references(r):
+@pytest.mark.parametrize("kw", [dict(L=1, H=1), dict(L=31), dict(L=33, r=8), dict(L=129)])
+def test_forward_wide_small(kw):  # (below the line: the windowed kernel)
+    gu.check(wl.make_inputs(3, **dict(dict(B=1, H=2, cz=128, r=4, varlen=False, trans_scale=0.3), **kw)), label="fwd wide small %s" % kw)
+
+
+@pytest.mark.parametrize("r,B", [(4, 5), (8, 1)])
+def test_forward_stored_weights_raised_references(r, B):
     # a chain in random order: the nearest residue of a row lies in any block, hundreds of log2 units above the first ones
-    inp = wl.make_inputs(3, B=1, L=700, H=2, cz=128, r=r, varlen=False)
+    inp = wl.make_inputs(3, B=B, L=700, H=12, cz=128, r=r, varlen=False)
     perm = np.random.default_rng(5).permutation(700)
     for n in ("rot", "trans"):
         inp[n] = np.ascontiguousarray(inp[n][:, perm])
     inp["k_pts"] = np.ascontiguousarray(inp["k_pts"] * 0 + 8.0)  # keys far from their own queries
-    gu.check(inp, label="fwd stored, raised references r=%d" % r)
+    gu.check(inp, rows=wl.select_rows(inp, 24), label="fwd stored, raised references r=%d" % r)
 
 
 def test_forward_stored_weights_several_ranges():
