@@ -12,14 +12,14 @@ from tests.test_zz_no_alloc import OUT, _both
 pytestmark = pytest.mark.gpu
 
 
-# (enough pairs that the library takes this path; 6 sampled rows of every batch element)
+# (enough pairs that the library takes this path; 12 sampled rows of every batch element)
 @pytest.mark.parametrize("kw", [
     dict(L=257, B=15), dict(L=385, B=9, cz=64, r=8), dict(L=600, B=6, cz=256, r=2, varlen=True, min_len=1), dict(L=300, B=16, c=8, Pq=2, Pv=3),
     dict(L=257, r=8), dict(L=129, B=4, r=8), dict(L=140, B=3, cz=256, r=4), dict(L=140, B=3, cz=512, r=2), dict(L=300, B=2, cz=64, r=16),
     dict(L=600, r=8, H=4, B=3, varlen=True, min_len=1)])
 def test_forward_stored_weights(kw):
     inp = wl.make_inputs(3, **dict(dict(B=1, H=12, cz=128, r=4, varlen=False, trans_scale=0.3), **kw))
-    gu.check(inp, rows=wl.select_rows(inp, 6), label="fwd stored %s" % kw)
+    gu.check(inp, rows=wl.select_rows(inp, 12), label="fwd stored %s" % kw)
 
 
 @pytest.mark.parametrize("kw", [dict(L=1, H=1), dict(L=31), dict(L=33, r=8), dict(L=129)])
