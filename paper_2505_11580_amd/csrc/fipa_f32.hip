@@ -41,10 +41,13 @@ __host__ __device__ constexpr F32Geom f32_geom(int c, int Pq, int Pv, int DZ, bo
     return g;
 }
 
-// AlphaFold2's head shape, with rows that can be read as 16-byte pieces.
+// AlphaFold2's head shape, with rows that can be read as 16-byte pieces, at the widths that f32_forward has an EXACT kernel
+// for (16, 32, .. 512).  The record, the workspace and the choice of the kernel all follow this one predicate: every other
+// width (rank 3, say) takes the generic kernel, whose record also holds Qg.
 bool f32_exact(const fipa_desc &d)
 {
-    return d.c == 16 && d.Pq == 4 && d.Pv == 8 && d.cz % 4 == 0 && d.r * d.cz % 16 == 0;
+    const int DZ = d.r * d.cz;
+    return d.c == 16 && d.Pq == 4 && d.Pv == 8 && d.cz % 4 == 0 && DZ >= 16 && (DZ & (DZ - 1)) == 0;
 }
 
 struct F32Params {

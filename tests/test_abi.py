@@ -41,6 +41,17 @@ def test_workspace_is_affine_in_length():
         assert len(set(steps)) == 1 and steps[0] > 0, sizes
 
 
+def test_f32_workspace_holds_the_record_of_the_kernel_that_runs():
+    # AlphaFold2's heads: k | Kg | v, Vg at the widths that have an exact kernel; at any other the generic kernel's record
+    # with Qg (12 floats) behind it
+    B, L, H = 2, 64, 4
+    for cz, r in ((16, 1), (16, 2), (64, 1), (128, 1), (128, 2), (128, 4), (16, 3), (80, 1), (32, 3), (64, 3), (128, 3), (12, 4)):
+        DZ = r * cz
+        record = 76 if DZ in (16, 32, 64, 128, 256, 512) else 88
+        need = binding.workspace_bytes(binding.make_desc(B, L, H, 16, 4, 8, cz, r, binding.FIPA_DTYPE_F32))[0]
+        assert need == B * H * L * record * 4 + 2 * 256, (cz, r, need)
+
+
 def test_bad_descriptions_are_rejected_on_the_host():
     lib = binding.lib()
     sz = ctypes.c_size_t(0)

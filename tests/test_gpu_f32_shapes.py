@@ -17,7 +17,10 @@ pytestmark = pytest.mark.gpu
     dict(L=50, c=7, Pq=3, Pv=5, cz=9, r=3, H=2), dict(L=33, c=40, Pq=1, Pv=1, cz=20, r=1, H=2),
     dict(L=20, c=300, Pq=2, Pv=10, cz=50, r=1, H=1), dict(L=90, c=16, Pq=4, Pv=8, cz=12, r=2, H=2),
     dict(L=40, c=8, Pq=50, Pv=2, cz=16, r=2, H=1), dict(L=30, c=500, Pq=2, Pv=20, cz=16, r=1, H=1),
-    dict(L=300, B=2, H=12, c=8, Pq=2, Pv=3, cz=8, r=2, varlen=True, min_len=100)])
+    dict(L=300, B=2, H=12, c=8, Pq=2, Pv=3, cz=8, r=2, varlen=True, min_len=100),
+    # AlphaFold2's heads at widths without an exact kernel (48, 80, 96, 192, 384; 32-row workgroups in the last)
+    dict(L=37, cz=16, r=3, H=2), dict(L=50, cz=80, r=1), dict(L=131, B=2, cz=32, r=3, varlen=True, min_len=20),
+    dict(L=65, cz=64, r=3, H=2), dict(L=33, cz=128, r=3, H=1), dict(L=161, B=8, H=12, cz=16, r=3, varlen=True, min_len=9)])
 def test_f32_shapes(kw):
     kw = dict(dict(B=1, H=4, chain=True, trans_scale=0.3), **kw)
     gu.check(wl.make_inputs(0, **kw), label="fp32 %s" % kw)
