@@ -76,8 +76,11 @@ struct WsCfg {
     static constexpr int LA_PV = 3 < KS ? 3 : KS - 1;  // (3, 5, 8 and 12 measured the same)
     static constexpr int RING_S = LA_S + 1;  // operand buffers
     static constexpr int RING_PV = LA_PV + 1;
-    static constexpr int DMA_EVERY = NPV / NEW;  // one load entry every DMA_EVERY P V MFMAs
-    static_assert(DMA_EVERY >= 1, "more load entries than MFMAs");
+    static constexpr int HOLD_S = 2;   // held-back S^T MFMAs per block (see s_start)
+    static constexpr int HOLD_PV = 2;  // held-back P V MFMAs per block
+    // One load entry every DMA_EVERY of the P V MFMAs that a step issues between its loads, the held-back ones apart.
+    static constexpr int DMA_EVERY = (NPV - HOLD_PV) / NEW;
+    static_assert(DMA_EVERY >= 1 && (NEW - 1) * DMA_EVERY < NPV - HOLD_PV, "every load entry of a block has its MFMA");
 };
 
 __device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xC07F); }  // s_waitcnt lgkmcnt(0) only
@@ -284,11 +287,10 @@ __device__ __forceinline__ float raise_reference(SWave<DZ> &w, float mx)
     return alpha;
 }
 
-// The MFMAs of a key block are not all issued in the iteration that forms the block: the last HB of
-// them are held back, with their LDS operands already in registers, and issued right after the
+// The MFMAs of a key block are not all issued in the iteration that forms the block: the last
+// (WsCfg::HOLD_S, HOLD_PV) of them are held back, with their LDS operands already in registers, and issued right after the
 // next workgroup barrier, where they cover the time the first LDS reads of the new block take.
-constexpr int kHoldS = 2;   // held-back S^T MFMAs per block
-constexpr int kHoldPV = 2;  // held-back P V MFMAs per block
+constexpr int kHoldS = WsCfg<32>::HOLD_S, kHoldPV = WsCfg<32>::HOLD_PV;  // (the same at every width)
 
 // First part of S^T of the block in stage `st` (no softmax work interleaved): the accumulation chain
 // up to the held-back MFMAs, whose operands go to `hold`.

@@ -140,7 +140,7 @@ inline SplitPlan attn_split_plan(int total_tiles, int Lp, int DZ, int cz, bool f
         // At least four 32-key blocks per part; below 16 blocks the exchange and the second start-up cost more than the
         // shorter loops give.  One chain, H = 12, r c_z = 256, attention split / whole: 131 residues 20.8 / 18.2 us,
         // 200 22.4 / 19.9, 300 24.3 / 22.6; 400 (16 blocks) in four / two parts 25.2 / 25.7, 600 28.1 / 29.4.
-        // (The wave-specialised variant keeps its parts: it is not right on whole tiles of so few blocks.)
+        // (Measured for the default kernel; the wave-specialised variant keeps its parts.)
         const int blocks = Lp / 32, by_blocks = blocks < 16 && !wave_specialised ? 1 : blocks / 4;
         s.S = kCU / s.rem;
         if (s.S > 4) s.S = 4;

@@ -97,6 +97,17 @@ def test_bf16_wave_specialised_kernel(cz, r):
     gu.check(wl.make_inputs(1, B=1, L=256, H=4, cz=cz, r=r, chain=False), label="ws iid DZ=%d" % (cz * r), flags=ws)
 
 
+@pytest.mark.parametrize("cz,r", [(32, 1), (32, 2), (64, 1), (128, 1), (128, 2)])
+def test_bf16_wave_specialised_kernel_whole_tiles(cz, r):
+    # more than half a round of query tiles, which are then not cut along the keys: 5 to 15 key blocks in one workgroup (the
+    # loop requests block 4 and later ones itself), ragged chains in a masked batch too
+    ws = binding.FIPA_FLAG_WAVE_SPECIALISED
+    for B, H, L in ((5, 13, 131), (5, 13, 192), (5, 13, 225), (4, 11, 300), (3, 15, 352), (3, 11, 400), (3, 11, 480)):
+        assert 128 < B * H * (-(-L // 128)) <= 256
+        gu.check(wl.make_inputs(1, B=B, H=H, L=L, cz=cz, r=r, trans_scale=0.3), label="ws whole L=%d DZ=%d" % (L, cz * r), flags=ws)
+    gu.check(wl.make_inputs(1, B=4, H=11, L=384, cz=cz, r=r, varlen=True, min_len=100), label="ws whole varlen DZ=%d" % (cz * r), flags=ws)
+
+
 def test_bf16_wave_specialised_kernel_workload2_sampled_rows():
     inp = wl.make_inputs(2)
     rows = wl.select_rows(inp, 256)
