@@ -104,8 +104,9 @@ int fipa_forward(const fipa_desc *desc, const void *q, const void *k, const void
         if (check_desc(desc, true) != FIPA_OK || desc->dtype != FIPA_DTYPE_BF16) return FIPA_ERR_UNSUPPORTED;
         fipa_workspace_bytes(desc, nullptr, &need);
         if (workspace_bytes < need) return FIPA_ERR_WORKSPACE;
-        return bf16_backward_begin(*desc, a, workspace, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? FIPA_OK
-                                                                                                           : FIPA_ERR_LAUNCH;
+        return bf16_backward_begin(*desc, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess
+                   ? FIPA_OK
+                   : FIPA_ERR_LAUNCH;
     }
     need = desc->dtype == FIPA_DTYPE_F32 ? f32_forward_workspace(*desc) : bf16_forward_workspace_min(*desc);
     if (workspace_bytes < need) return FIPA_ERR_WORKSPACE;
@@ -152,8 +153,8 @@ int fipa_backward(const fipa_desc *desc, const void *q, const void *k, const voi
     a.d_rot = d_rot; a.d_trans = d_trans;
     // (with FIPA_FLAG_KEEP_FORWARD the workspace still holds what the forward call left there)
     const hipError_t e = (desc->flags & FIPA_FLAG_KEEP_FORWARD)
-                             ? bf16_backward_finish(*desc, a, workspace, static_cast<hipStream_t>(hip_stream))
-                             : bf16_backward(*desc, a, workspace, static_cast<hipStream_t>(hip_stream));
+                             ? bf16_backward_finish(*desc, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream))
+                             : bf16_backward(*desc, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
 }
 

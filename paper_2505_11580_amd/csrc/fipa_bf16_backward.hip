@@ -432,25 +432,34 @@ __global__ __launch_bounds__(1024) void fipa_bwd_wb_reduce_kernel(BwdUnpackParam
 // The lifted widths whose gradients go through stored weights (fipa_bf16_bwd_stored.hip).
 bool bwd_stored(int DZ) { return DZ == 256 || DZ == 512; }
 
-// Query rows whose weights the workspace holds at a time: a constant, so that the workspace stays affine in L.  Every
-// range but the first adds its key-side sums to memory: 2048 / 4096 / 8192 rows measured 14.4 / 13.8 / 13.6 ms per training
-// step on four chains of up to 8192 residues (r c_z = 512), 2.24 / 2.15 / 2.15 ms at B = 2, L = 4096 (r c_z = 256).
-int stored_query_rows(int Lp)
+// Bytes of stored weights (P and dS', 4 per query row, key and pair) that the workspace query asks for: of 4096 query rows --
+// every range of rows but the first adds its key-side sums to memory: 2048 / 4096 / 8192 rows measured 14.4 / 13.8 / 13.6 ms per
+// training step on four chains of up to 8192 residues (r c_z = 512), 2.24 / 2.15 / 2.15 ms at B = 2, L = 4096 (r c_z = 256) --
+// and of fewer where a pair's weights would pass the 31-bit byte offsets of the kernels (262144 residues).  Grows with the
+// length throughout: chains that run one after the other share a workspace of the longest one's size.
+constexpr size_t kPairBytes = 0x7FFFFFFF;  // of either weight of a pair
+size_t stored_weight_bytes(size_t BH, int Lp, int Lk)
 {
-    long long nq = 4096;
-    const long long most = (1ll << 30) / (long long)align_up(Lp, 256) / 256 * 256;  // one pair's weights: 31-bit byte offsets
-    if (nq > most) nq = most < 256 ? 256 : most;
-    return nq < Lp ? (int)nq : Lp;
+    const size_t rows = Lp < 4096 ? Lp : 4096, pair = rows * Lk * 2;
+    return BH * 2 * (pair < kPairBytes ? pair : kPairBytes);
+}
+// Query rows whose weights fit: all of them, or whole tiles of 256.
+int stored_query_rows(size_t bytes, size_t BH, int Lp, int Lk)
+{
+    const size_t most = kPairBytes / ((size_t)Lk * 2), cap = most < 4096 ? most : 4096, fit = bytes / (BH * Lk * 4);
+    const size_t rows = fit < cap ? fit : cap;
+    return rows >= (size_t)Lp ? Lp : (int)(rows / 256 * 256);
 }
 
 struct BwdLayout {
     Bf16Layout f;
     size_t dOhat, Dvec, nlse, dQhat, dKhat, dVhat, rowsum, colsum, gpart, wpart, total;
     size_t dKh, dVh, dZ, Wp, Ws;  // stored weights (in the place of dKhat and dVhat)
-    int Lk, nq;
+    int Lk, nq;           // keys per group of weights; query rows of which the given workspace holds the weights
 };
 
-BwdLayout bwd_layout(const fipa_desc &d)
+// `bytes`: the workspace that is laid out; the query lays out what it asks for (total).
+BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
 {
     BwdLayout w;
     w.f = bf16_layout(d, true, true);
@@ -468,13 +477,11 @@ BwdLayout bwd_layout(const fipa_desc &d)
     w.dQhat = take(BHL * D * 4);
     w.dKhat = w.dVhat = w.dKh = w.dVh = w.dZ = w.Wp = w.Ws = 0;
     w.Lk = (int)align_up(w.f.Lp, 256);
-    w.nq = stored_query_rows(w.f.Lp);
+    w.nq = 0;
     if (bwd_stored(w.f.DZ)) {
         w.dKh = take(BHL * kDH * 4);
         w.dVh = take(BHL * kDH * 4);
         w.dZ = take(BHL * w.f.DZ * 4);
-        w.Wp = take((size_t)d.B * d.H * w.nq * w.Lk * 2);
-        w.Ws = take((size_t)d.B * d.H * w.nq * w.Lk * 2);
     } else {
         w.dKhat = take(BHL * D * 4);
         w.dVhat = take(BHL * D * 4);
@@ -483,6 +490,14 @@ BwdLayout bwd_layout(const fipa_desc &d)
     w.colsum = take(BHL * 4);
     w.gpart = take(BHL * 4);
     w.wpart = take((size_t)d.H * (((size_t)d.B * d.L + kWbChunk - 1) / kWbChunk) * w.f.DZ * 4);
+    if (bwd_stored(w.f.DZ)) {  // (last: as many rows as the workspace has left)
+        const size_t BH = (size_t)d.B * d.H, want = stored_weight_bytes(BH, w.f.Lp, w.Lk);
+        const size_t have = bytes < off ? 0 : (bytes - off < want ? bytes - off : want);
+        w.nq = stored_query_rows(have, BH, w.f.Lp, w.Lk);
+        w.Wp = off;
+        w.Ws = off + BH * w.nq * w.Lk * 2;
+        take(want);
+    }
     w.total = off;
     if (fwd_stored_pays(d)) {
         const size_t fwd = fwd_stored_layout(d, w.f.Lp, w.f.total).total;
@@ -515,7 +530,7 @@ hipError_t launch_bwd_unpack_bf16(const BwdUnpackParams &p, hipStream_t stream)
     return hipGetLastError();
 }
 
-size_t bf16_backward_workspace(const fipa_desc &d) { return bwd_layout(d).total; }
+size_t bf16_backward_workspace(const fipa_desc &d) { return bwd_layout(d, SIZE_MAX).total; }
 
 namespace {
 
@@ -673,9 +688,10 @@ hipError_t backward_gradient_part(const fipa_desc &d, const BwdArgs &a, const Bw
 
 }  // namespace
 
-hipError_t bf16_backward(const fipa_desc &d, const BwdArgs &a, void *ws, hipStream_t stream)
+hipError_t bf16_backward(const fipa_desc &d, const BwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
 {
-    const BwdLayout w = bwd_layout(d);
+    const BwdLayout w = bwd_layout(d, ws_bytes);
+    if (ws_bytes < w.total) return hipErrorInvalidValue;
     char *base = static_cast<char *>(ws);
     StageTimer timer(stream);
     timer.begin(0);
@@ -689,16 +705,19 @@ hipError_t bf16_backward(const fipa_desc &d, const BwdArgs &a, void *ws, hipStre
 // The same in two calls on one workspace, for a caller that needs the core's outputs before it
 // can form the upstream gradients (the module's backward): the first call also writes f.o,
 // f.o_pts, f.o_pair; the workspace must not be touched in between.
-hipError_t bf16_backward_begin(const fipa_desc &d, const FwdArgs &f, void *ws, hipStream_t stream)
+hipError_t bf16_backward_begin(const fipa_desc &d, const FwdArgs &f, void *ws, size_t ws_bytes, hipStream_t stream)
 {
-    if (!f.o || !f.o_pts || !f.o_pair) return hipErrorInvalidValue;
-    return backward_forward_part(d, f, bwd_layout(d), static_cast<char *>(ws), stream);
+    const BwdLayout w = bwd_layout(d, ws_bytes);
+    if (!f.o || !f.o_pts || !f.o_pair || ws_bytes < w.total) return hipErrorInvalidValue;
+    return backward_forward_part(d, f, w, static_cast<char *>(ws), stream);
 }
 
-hipError_t bf16_backward_finish(const fipa_desc &d, const BwdArgs &a, void *ws, hipStream_t stream)
+hipError_t bf16_backward_finish(const fipa_desc &d, const BwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
 {
+    const BwdLayout w = bwd_layout(d, ws_bytes);
+    if (ws_bytes < w.total) return hipErrorInvalidValue;
     StageTimer timer;  // (not timed)
-    return backward_gradient_part(d, a, bwd_layout(d), static_cast<char *>(ws), stream, timer);
+    return backward_gradient_part(d, a, w, static_cast<char *>(ws), stream, timer);
 }
 
 }  // namespace fipa

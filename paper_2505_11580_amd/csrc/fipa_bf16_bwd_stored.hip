@@ -618,6 +618,7 @@ hipError_t launch_weights(BwdStoredParams p, hipStream_t stream)
 
 hipError_t launch_bwd_stored_bf16(const BwdStoredParams &p0, int DZ, hipStream_t stream)
 {
+    if (p0.nq_alloc <= 0) return hipErrorInvalidValue;
     for (int i0 = 0; i0 < p0.Lp; i0 += p0.nq_alloc) {
         BwdStoredParams p = p0;
         p.i0 = i0;

@@ -131,10 +131,11 @@ hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void
 size_t module_backward_workspace(const fipa_desc &d, int d_s);
 hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, const ModuleBwdArgs &g, void *ws,
                            hipStream_t stream);
-hipError_t bf16_backward(const fipa_desc &d, const BwdArgs &a, void *ws, hipStream_t stream);
+// (`ws_bytes`: what the caller gave, at least bf16_backward_workspace())
+hipError_t bf16_backward(const fipa_desc &d, const BwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream);
 // bf16_backward in two calls on one workspace: `begin` runs the forward part and also writes the
 // core's outputs f.o, f.o_pts, f.o_pair; `finish` takes the upstream gradients.
-hipError_t bf16_backward_begin(const fipa_desc &d, const FwdArgs &f, void *ws, hipStream_t stream);
-hipError_t bf16_backward_finish(const fipa_desc &d, const BwdArgs &a, void *ws, hipStream_t stream);
+hipError_t bf16_backward_begin(const fipa_desc &d, const FwdArgs &f, void *ws, size_t ws_bytes, hipStream_t stream);
+hipError_t bf16_backward_finish(const fipa_desc &d, const BwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream);
 
 }  // namespace fipa

@@ -160,7 +160,7 @@ int fipa_forward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const 
         FwdArgs a{q, k, v, q_pts, k_pts, v_pts, rot, trans, z1, z2, w_b, gamma, mask, o, o_pts, o_pair, lse};
         a.cu = cu_dev;
         a.total_rows = pl.total;
-        const hipError_t e = keep ? bf16_backward_begin(pl.d, a, workspace, stream) : bf16_forward(pl.d, a, workspace, pl.cu_fwd, stream);
+        const hipError_t e = keep ? bf16_backward_begin(pl.d, a, workspace, pl.cu_fwd, stream) : bf16_forward(pl.d, a, workspace, pl.cu_fwd, stream);
         return e == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
     }
 
@@ -222,7 +222,8 @@ int fipa_backward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const
         if (upload_ints(cu_seqlens, desc->B + 1, cu_dev, stream) != hipSuccess) return FIPA_ERR_LAUNCH;
         a.f.cu = cu_dev;
         a.f.total_rows = pl.total;
-        const hipError_t e = keep ? bf16_backward_finish(pl.d, a, workspace, stream) : bf16_backward(pl.d, a, workspace, stream);
+        const hipError_t e = keep ? bf16_backward_finish(pl.d, a, workspace, pl.cu_bwd, stream)
+                                  : bf16_backward(pl.d, a, workspace, pl.cu_bwd, stream);
         return e == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
     }
 
@@ -250,7 +251,7 @@ int fipa_backward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const
         c.d_w_b = d_w_b ? c.d_gamma + H : nullptr;
         c.d_rot = d_rot ? d_rot + r0 * 9 : nullptr;
         c.d_trans = d_trans ? d_trans + r0 * 3 : nullptr;
-        if (bf16_backward(one, c, workspace, stream) != hipSuccess) return FIPA_ERR_LAUNCH;
+        if (bf16_backward(one, c, workspace, pl.part_bwd, stream) != hipSuccess) return FIPA_ERR_LAUNCH;  // (the partial sums lie behind)
         j += 1;
     }
     hipLaunchKernelGGL(fipa_sum_rows_kernel, dim3((H + 255) / 256), dim3(256), 0, stream, part, j, pl.part_stride, H, d_gamma);

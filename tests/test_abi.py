@@ -41,6 +41,31 @@ def test_workspace_is_affine_in_length():
         assert len(set(steps)) == 1 and steps[0] > 0, sizes
 
 
+@pytest.mark.parametrize("cz,r", [(128, 1), (128, 2), (64, 4), (128, 4), (128, 8)])
+def test_workspaces_grow_with_the_length(cz, r):
+    # chains that run one after the other share a workspace of the longest one's size, so no shorter chain may need more:
+    # around every size at which the number of stored query rows changes
+    lengths = sorted({1, 127, 128, 129, 256, 384, 4000, 4096, 4097, 9000, 20000, 65536, 100000, 1000000, 2000000}
+                     | {x + e for rows in range(256, 4097, 256) for x in ((1 << 30) // rows // 128 * 128,) for e in (-256, -128, 0, 128, 256)})
+    for H in (1, 12):
+        last = (0, 0)
+        for L in lengths:
+            if H * (L + 128) >= 1 << 31:
+                continue
+            now = binding.workspace_bytes(binding.make_desc(1, L, H, 16, 4, 8, cz, r, binding.FIPA_DTYPE_BF16))
+            assert now[0] >= last[0] and now[1] >= last[1], (H, L, now, last)
+            last = now
+
+
+def test_packed_chain_by_chain_workspace_holds_every_chain():
+    desc = binding.make_desc(2, 262400, 1, 16, 4, 8, 128, 2, binding.FIPA_DTYPE_BF16)
+    desc.flags = binding.FIPA_FLAG_PACKED_PER_CHAIN
+    bwd = binding.packed_workspace_bytes(desc, [0, 262400, 524544])[1]
+    for L in (262400, 262144):
+        one = binding.make_desc(1, L, 1, 16, 4, 8, 128, 2, binding.FIPA_DTYPE_BF16)
+        assert binding.workspace_bytes(one)[1] <= bwd, L
+
+
 def test_f32_workspace_holds_the_record_of_the_kernel_that_runs():
     # AlphaFold2's heads: k | Kg | v, Vg at the widths that have an exact kernel; at any other the generic kernel's record
     # with Qg (12 floats) behind it
