@@ -36,7 +36,7 @@ extern "C" {
 #define FIPA_OK 0
 #define FIPA_ERR_INVALID_ARG (-1) /* null pointer, non-positive size, bad dtype               */
 #define FIPA_ERR_UNSUPPORTED (-2) /* shape outside what the kernels are built for (see below) */
-#define FIPA_ERR_WORKSPACE (-3)   /* workspace_bytes smaller than fipa_workspace_bytes()      */
+#define FIPA_ERR_WORKSPACE (-3)   /* workspace_bytes smaller than the least (fipa_workspace_bytes) */
 #define FIPA_ERR_ALIGNMENT (-4)   /* a tensor pointer is not 16-byte aligned                  */
 #define FIPA_ERR_LAUNCH (-5)      /* HIP reported an error when a kernel was enqueued         */
 
@@ -99,12 +99,17 @@ int fipa_version(void);
 const char *fipa_status_string(int status);
 
 /*
- * Scratch sizes in bytes for fipa_forward / fipa_backward with this description.  Both are
- * affine in L once L exceeds a constant (the linear-memory property of Section 2.3): the forward at
- * r c_z >= 512 and the backward at r c_z >= 256 hold the attention weights of a constant number of
- * query rows (at most 16384, respectively 4096 per (batch, head) pair) against all keys.  fipa_forward
- * also runs, more slowly, in a workspace without those weights (and fipa_forward_static does where its
- * scratch is too small for them).  Either output pointer may be NULL.  Host-only, touches no device.
+ * Scratch sizes in bytes for fipa_forward / fipa_backward with this description.  Both grow with L
+ * and stay below an affine function of it (the linear-memory property of Section 2.3): besides what
+ * is affine in L, the forward at r c_z >= 512 and the backward at r c_z >= 256 hold the attention
+ * weights of a number of query rows against all keys -- of at most 16384, respectively 4096 rows per
+ * (batch, head) pair, and of no more than 32 GiB in all unless the backward's least is more.
+ * Every call also runs, more slowly, in less (FIPA_ERR_WORKSPACE below its least): the forward without
+ * those weights, the backward -- alone, with FIPA_FLAG_KEEP_FORWARD, packed or in the module -- with
+ * 4 B H L' r c_z bytes of them (L' = L rounded up to 128) or all of them, whichever is less; the rows
+ * whose weights are held follow the size that is given.  A training step of two chains of 4096
+ * residues, H = 12, r c_z = 256: 2.0 ms in 2.2 GB (the query), 4.4 ms in 0.67 GB (the least).
+ * Either output pointer may be NULL.  Host-only, touches no device.
  */
 int fipa_workspace_bytes(const fipa_desc *desc, size_t *forward_bytes, size_t *backward_bytes);
 
@@ -141,7 +146,7 @@ int fipa_forward(const fipa_desc *desc,
  * arguments, same kernels and same results as fipa_forward, with the scratch memory taken from an
  * array of FIPA_STATIC_SCRATCH_BYTES that is part of the library's device image (every GPU the
  * library is used on holds one copy until the process ends).  Calls nothing that allocates.
- *   - FIPA_ERR_WORKSPACE when fipa_workspace_bytes(desc) exceeds FIPA_STATIC_SCRATCH_BYTES
+ *   - FIPA_ERR_WORKSPACE when the least workspace of the call exceeds FIPA_STATIC_SCRATCH_BYTES
  *     (bf16, H = 12, c_z = 128, r = 2: up to about 8000 residues in total over the batch);
  *     FIPA_ERR_LAUNCH when the array's device address cannot be obtained.
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different

@@ -97,18 +97,16 @@ int fipa_forward(const fipa_desc *desc, const void *q, const void *k, const void
     if (rc != FIPA_OK) return rc;
     if (!workspace) return FIPA_ERR_INVALID_ARG;
     if (!aligned16(workspace)) return FIPA_ERR_ALIGNMENT;
-    size_t need = 0;
     if (desc->flags & FIPA_FLAG_KEEP_FORWARD) {
         // the forward part of the backward, which leaves the lifted operands, O^ and the
         // log-sum-exp in a workspace of the backward's size, gives the same outputs
         if (check_desc(desc, true) != FIPA_OK || desc->dtype != FIPA_DTYPE_BF16) return FIPA_ERR_UNSUPPORTED;
-        fipa_workspace_bytes(desc, nullptr, &need);
-        if (workspace_bytes < need) return FIPA_ERR_WORKSPACE;
+        if (workspace_bytes < bf16_backward_workspace_min(*desc)) return FIPA_ERR_WORKSPACE;
         return bf16_backward_begin(*desc, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                    ? FIPA_OK
                    : FIPA_ERR_LAUNCH;
     }
-    need = desc->dtype == FIPA_DTYPE_F32 ? f32_forward_workspace(*desc) : bf16_forward_workspace_min(*desc);
+    const size_t need = desc->dtype == FIPA_DTYPE_F32 ? f32_forward_workspace(*desc) : bf16_forward_workspace_min(*desc);
     if (workspace_bytes < need) return FIPA_ERR_WORKSPACE;
     return enqueue_forward(*desc, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? FIPA_OK
                                                                                                   : FIPA_ERR_LAUNCH;
@@ -140,9 +138,7 @@ int fipa_backward(const fipa_desc *desc, const void *q, const void *k, const voi
     if (d_w_b && !aligned16(d_w_b)) return FIPA_ERR_ALIGNMENT;
     if ((d_rot == nullptr) != (d_trans == nullptr)) return FIPA_ERR_INVALID_ARG;
     if (d_rot && (!aligned16(d_rot) || !aligned16(d_trans))) return FIPA_ERR_ALIGNMENT;
-    size_t need = 0;
-    fipa_workspace_bytes(desc, nullptr, &need);
-    if (workspace_bytes < need) return FIPA_ERR_WORKSPACE;
+    if (workspace_bytes < bf16_backward_workspace_min(*desc)) return FIPA_ERR_WORKSPACE;
     BwdArgs a;
     a.f = FwdArgs{q, k, v, q_pts, k_pts, v_pts, rot, trans, z1, z2, w_b, gamma, mask,
                   const_cast<float *>(o), const_cast<float *>(o_pts), const_cast<float *>(o_pair),
@@ -182,9 +178,10 @@ int fipa_module_forward(const fipa_desc *desc, int32_t d_s, const void *s, const
         if (!ptr) return FIPA_ERR_INVALID_ARG;
         if (!aligned16(ptr)) return FIPA_ERR_ALIGNMENT;
     }
+    need = keep ? module_backward_workspace(*desc, d_s, true) : module_forward_workspace(*desc, d_s, true);
     if (workspace_bytes < need) return FIPA_ERR_WORKSPACE;
     const ModuleArgs a{s, w_in, b_in, rot, trans, z1, z2, w_b, gamma, mask, w_out, b_out, s_out};
-    const hipError_t e = module_forward(*desc, d_s, a, workspace, static_cast<hipStream_t>(hip_stream));
+    const hipError_t e = module_forward(*desc, d_s, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
 }
 
@@ -218,10 +215,10 @@ int fipa_module_backward(const fipa_desc *desc, int32_t d_s, const void *s, cons
     const void *opt[] = {b_in, b_out, d_b_in, d_b_out, d_w_b, d_rot, d_trans};
     for (const void *ptr : opt)
         if (ptr && !aligned16(ptr)) return FIPA_ERR_ALIGNMENT;
-    if (workspace_bytes < need) return FIPA_ERR_WORKSPACE;
+    if (workspace_bytes < module_backward_workspace(*desc, d_s, true)) return FIPA_ERR_WORKSPACE;
     const ModuleArgs a{s, w_in, b_in, rot, trans, z1, z2, w_b, gamma, mask, w_out, b_out, nullptr};
     const ModuleBwdArgs g{d_s_out, d_s_in, d_w_in, d_b_in, d_w_out, d_b_out, d_z1, d_z2, d_gamma, d_w_b, d_rot, d_trans};
-    const hipError_t e = module_backward(*desc, d_s, a, g, workspace, static_cast<hipStream_t>(hip_stream));
+    const hipError_t e = module_backward(*desc, d_s, a, g, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
 }
 

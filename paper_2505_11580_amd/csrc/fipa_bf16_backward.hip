@@ -435,20 +435,25 @@ bool bwd_stored(int DZ) { return DZ == 256 || DZ == 512; }
 // Bytes of stored weights (P and dS', 4 per query row, key and pair) that the workspace query asks for: of 4096 query rows --
 // every range of rows but the first adds its key-side sums to memory: 2048 / 4096 / 8192 rows measured 14.4 / 13.8 / 13.6 ms per
 // training step on four chains of up to 8192 residues (r c_z = 512), 2.24 / 2.15 / 2.15 ms at B = 2, L = 4096 (r c_z = 256) --
-// and of fewer where a pair's weights would pass the 31-bit byte offsets of the kernels (262144 residues).  Grows with the
-// length throughout: chains that run one after the other share a workspace of the longest one's size.
+// and of fewer where a pair's weights would pass the 31-bit byte offsets of the kernels (262144 residues) or all of them
+// kStoredBytes.  Grows with the length throughout: chains that run one after the other share a workspace of the longest one's size.
 constexpr size_t kPairBytes = 0x7FFFFFFF;  // of either weight of a pair
-size_t stored_weight_bytes(size_t BH, int Lp, int Lk)
+// The least: as much as key-side gradients of the full width (dK^_z and dV^_z apart) would take more than dZ, so that the
+// calls run in any workspace that is large enough to form the weights again in every product.
+size_t stored_weight_least(size_t BH, int Lp, int DZ) { return BH * Lp * DZ * 4; }
+size_t stored_weight_bytes(size_t BH, int Lp, int Lk, int DZ)
 {
-    const size_t rows = Lp < 4096 ? Lp : 4096, pair = rows * Lk * 2;
-    return BH * 2 * (pair < kPairBytes ? pair : kPairBytes);
+    const size_t rows = Lp < 4096 ? Lp : 4096, pair = rows * Lk * 2, least = stored_weight_least(BH, Lp, DZ);
+    const size_t all = BH * 2 * (pair < kPairBytes ? pair : kPairBytes), cap = least > kStoredBytes ? least : kStoredBytes;
+    return all < cap ? all : cap;
 }
-// Query rows whose weights fit: all of them, or whole tiles of 256.
+// Query rows whose weights fit: all of them, or whole tiles of 256, at the least half a tile (which every workspace of the
+// least size holds: its DZ Lp / Lk rows are at least 128, as Lk < 2 Lp and DZ >= 256).
 int stored_query_rows(size_t bytes, size_t BH, int Lp, int Lk)
 {
     const size_t most = kPairBytes / ((size_t)Lk * 2), cap = most < 4096 ? most : 4096, fit = bytes / (BH * Lk * 4);
     const size_t rows = fit < cap ? fit : cap;
-    return rows >= (size_t)Lp ? Lp : (int)(rows / 256 * 256);
+    return rows >= (size_t)Lp ? Lp : (int)(rows >= 256 ? rows / 256 * 256 : rows / 128 * 128);
 }
 
 struct BwdLayout {
@@ -456,9 +461,11 @@ struct BwdLayout {
     size_t dOhat, Dvec, nlse, dQhat, dKhat, dVhat, rowsum, colsum, gpart, wpart, total;
     size_t dKh, dVh, dZ, Wp, Ws;  // stored weights (in the place of dKhat and dVhat)
     int Lk, nq;           // keys per group of weights; query rows of which the given workspace holds the weights
+    size_t least;         // what the calls run in (total: what the query asks for)
+    bool fwd_stored;      // the given workspace holds the forward's weights too
 };
 
-// `bytes`: the workspace that is laid out; the query lays out what it asks for (total).
+// `bytes`: the workspace that is laid out.
 BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
 {
     BwdLayout w;
@@ -491,17 +498,23 @@ BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
     w.gpart = take(BHL * 4);
     w.wpart = take((size_t)d.H * (((size_t)d.B * d.L + kWbChunk - 1) / kWbChunk) * w.f.DZ * 4);
     if (bwd_stored(w.f.DZ)) {  // (last: as many rows as the workspace has left)
-        const size_t BH = (size_t)d.B * d.H, want = stored_weight_bytes(BH, w.f.Lp, w.Lk);
+        const size_t BH = (size_t)d.B * d.H, want = stored_weight_bytes(BH, w.f.Lp, w.Lk, w.f.DZ);
         const size_t have = bytes < off ? 0 : (bytes - off < want ? bytes - off : want);
         w.nq = stored_query_rows(have, BH, w.f.Lp, w.Lk);
         w.Wp = off;
         w.Ws = off + BH * w.nq * w.Lk * 2;
+        const size_t least = stored_weight_least(BH, w.f.Lp, w.f.DZ);
+        w.least = align_up(off + (least < want ? least : want), 256);
         take(want);
+    } else {
+        w.least = off;
     }
     w.total = off;
-    if (fwd_stored_pays(d)) {
+    w.fwd_stored = false;
+    if (fwd_stored_pays(d)) {  // (its weights lie where the gradient part begins, which is not yet in use)
         const size_t fwd = fwd_stored_layout(d, w.f.Lp, w.f.total).total;
         if (fwd > w.total) w.total = fwd;
+        w.fwd_stored = bytes >= fwd;
     }
     return w;
 }
@@ -531,6 +544,7 @@ hipError_t launch_bwd_unpack_bf16(const BwdUnpackParams &p, hipStream_t stream)
 }
 
 size_t bf16_backward_workspace(const fipa_desc &d) { return bwd_layout(d, SIZE_MAX).total; }
+size_t bf16_backward_workspace_min(const fipa_desc &d) { return bwd_layout(d, SIZE_MAX).least; }
 
 namespace {
 
@@ -585,8 +599,7 @@ hipError_t backward_forward_part(const fipa_desc &d, const FwdArgs &f, const Bwd
     at.nQT = w.f.Lp / kTileQ; at.total_tiles = at.nQT * d.B * d.H; at.cz = d.cz; at.r = d.r; at.w_b = f.w_b; at.w_L = d.w_L;
     at.plan = w.f.plan; at.partial = nullptr; at.counters = nullptr;  // (unfused: never split)
     at.deal = f.mask != nullptr || f.cu != nullptr;
-    // (width 576: its weights lie where the gradient part begins, which is not yet in use)
-    if (fwd_stored_pays(d))
+    if (w.fwd_stored)
         e = launch_attn_fwd_stored_bf16(fwd_stored_params(d, at, fwd_stored_layout(d, w.f.Lp, w.f.total), base), w.f.DZ, false, stream);
     else
         e = w.f.DZ > 256 ? launch_attn_fwd_wide_bf16(at, w.f.DZ, false, stream) : launch_attn_fwd_bf16(at, w.f.DZ, false, stream);
@@ -691,7 +704,7 @@ hipError_t backward_gradient_part(const fipa_desc &d, const BwdArgs &a, const Bw
 hipError_t bf16_backward(const fipa_desc &d, const BwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
 {
     const BwdLayout w = bwd_layout(d, ws_bytes);
-    if (ws_bytes < w.total) return hipErrorInvalidValue;
+    if (ws_bytes < w.least) return hipErrorInvalidValue;
     char *base = static_cast<char *>(ws);
     StageTimer timer(stream);
     timer.begin(0);
@@ -708,14 +721,14 @@ hipError_t bf16_backward(const fipa_desc &d, const BwdArgs &a, void *ws, size_t 
 hipError_t bf16_backward_begin(const fipa_desc &d, const FwdArgs &f, void *ws, size_t ws_bytes, hipStream_t stream)
 {
     const BwdLayout w = bwd_layout(d, ws_bytes);
-    if (!f.o || !f.o_pts || !f.o_pair || ws_bytes < w.total) return hipErrorInvalidValue;
+    if (!f.o || !f.o_pts || !f.o_pair || ws_bytes < w.least) return hipErrorInvalidValue;
     return backward_forward_part(d, f, w, static_cast<char *>(ws), stream);
 }
 
 hipError_t bf16_backward_finish(const fipa_desc &d, const BwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
 {
     const BwdLayout w = bwd_layout(d, ws_bytes);
-    if (ws_bytes < w.total) return hipErrorInvalidValue;
+    if (ws_bytes < w.least) return hipErrorInvalidValue;
     StageTimer timer;  // (not timed)
     return backward_gradient_part(d, a, w, static_cast<char *>(ws), stream, timer);
 }

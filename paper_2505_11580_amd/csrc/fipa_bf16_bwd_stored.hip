@@ -529,8 +529,9 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
     }
 
     const bool add = KV && p.i0 > 0;  // later ranges of queries add to the sums of the earlier ones
+    const int row_end = KV ? kvlen : nvalid;  // (a range may end inside a tile)
     outputs([&](float *dst, f32x16 &a, int row) {
-        if (row >= kvlen) return;
+        if (row >= row_end) return;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -545,7 +546,7 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
         for (int hv = 0; hv < HV; ++hv) {
             const int row = row_lo + 32 * (HV * wave + hv) + li;
             const float tot = wsum[hv] + __shfl_xor(wsum[hv], 32);
-            if (g == 0 && row < kvlen) sums[rows0 + row] = (add ? sums[rows0 + row] : 0.f) + tot;
+            if (g == 0 && row < row_end) sums[rows0 + row] = (add ? sums[rows0 + row] : 0.f) + tot;
         }
 }
 

@@ -323,7 +323,14 @@ struct FwdStoredParams {
     int i0, nq, units;     // this range
 };
 
-// Its buffers, carved from `off` on.
+// Stored weights (here and in the backward): what the workspace query asks for them at most, unless the least that runs is
+// more -- a bound that leaves every call that fits the 288 GB device without stored weights fitting it with them.  Only the
+// largest batches meet it (64 chains of 4096 residues, H = 12, r c_z = 256, all weights 51.5 GB: a training step takes 61.6 ms
+// with all of them, 64.0 with 32 GiB, 69.6 with 16 GiB).
+constexpr size_t kStoredBytes = 32ull << 30;
+
+// Its buffers, carved from `off` on.  Grows with the length throughout (chains that run one after the other share a workspace of
+// the longest one's size).
 struct FwdStoredLayout {
     size_t W, flags, before, mref, linv, total;
     int nq, nqt, nwords;
@@ -332,27 +339,31 @@ inline FwdStoredLayout fwd_stored_layout(const fipa_desc &d, int Lp, size_t off)
 {
     FwdStoredLayout w;
     const size_t BH = (size_t)d.B * d.H;
-    // A constant number of query rows over all pairs (768 tiles of 256), so that the buffers stay affine in L; a range ends
-    // with its longest chains while most of the chip has nothing left.  Four chains of 2.7k to 7.1k residues, 48 pairs:
-    // 98304 / 196608 / 393216 rows 4.00 / 3.52 / 3.35 ms.
-    size_t nq = (196608 / BH + 255) / 256 * 256;
-    if (nq < 256) nq = 256;
-    if (nq > 16384) nq = 16384;
-    if (nq > (size_t)Lp) nq = align_up((size_t)Lp, 256);
-    w.nq = (int)nq;
-    w.nqt = (int)(nq / 256);
+    // A constant number of query rows over all pairs (768 tiles of 256), so that the buffers stay affine in L up to
+    // kStoredBytes; a range ends with its longest chains while most of the chip has nothing left.  Four chains of 2.7k to
+    // 7.1k residues, 48 pairs: 98304 / 196608 / 393216 rows 4.00 / 3.52 / 3.35 ms.
+    const size_t most = ((size_t)Lp + 255) / 256;
+    size_t tiles = (196608 / BH + 255) / 256;
+    tiles = tiles < 1 ? 1 : (tiles > 64 ? 64 : tiles);
+    if (tiles > most) tiles = most;
     w.nwords = (Lp / 32 + 31) / 32;
-    auto take = [&](size_t bytes) {
+    const size_t tile = BH * ((size_t)256 * Lp * 2 + 8 * w.nwords * 4 + 8 * (size_t)Lp * 4);  // 256 rows of every pair
+    size_t bytes = tiles * tile;
+    if (bytes > kStoredBytes) bytes = tile > kStoredBytes ? tile : kStoredBytes;
+    w.nqt = (int)(bytes / tile);
+    w.nq = 256 * w.nqt;
+    const size_t nq = w.nq;
+    auto take = [&](size_t n) {
         const size_t at = off;
-        off = align_up(off + bytes, 256);
+        off = align_up(off + n, 256);
         return at;
     };
-    w.W = take(BH * nq * Lp * 2);
-    w.flags = take(BH * w.nqt * 8 * w.nwords * 4);
-    w.before = take(BH * w.nqt * 8 * (size_t)Lp * 4);
     w.mref = take(BH * Lp * 4);
     w.linv = take(BH * Lp * 4);
-    w.total = off;
+    w.total = align_up(off + bytes, 256) + 2 * 256;
+    w.flags = take(BH * w.nqt * 8 * w.nwords * 4);
+    w.before = take(BH * w.nqt * 8 * (size_t)Lp * 4);
+    w.W = take(BH * nq * Lp * 2);
     return w;
 }
 // Whether the call has enough work for it: two launches whose workgroups hold a compute unit each against one.  In units of
@@ -362,6 +373,8 @@ inline FwdStoredLayout fwd_stored_layout(const fipa_desc &d, int Lp, size_t off)
 inline bool fwd_stored_pays(const fipa_desc &d)
 {
     const long long Lp = (long long)align_up((size_t)d.L, kTileQ), work = (long long)d.B * d.H * ((Lp + 255) / 256) * (Lp / 32);
+    // (and not where 256 rows of every pair alone are beyond all proportion: a workspace of the least size serves those calls)
+    if ((size_t)d.B * d.H * 256 * Lp * 2 > 2 * kStoredBytes) return false;
     return d.r * d.cz == 512 ? work >= 4096 : d.r * d.cz == 1024 && work >= 256;
 }
 int fwd_stored_slice_blocks(int DZ, int cz);

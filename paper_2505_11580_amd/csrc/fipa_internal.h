@@ -122,16 +122,18 @@ size_t bf16_forward_workspace(const fipa_desc &d);
 size_t bf16_forward_workspace_min(const fipa_desc &d);  // what the forward runs in, if not at its best
 hipError_t bf16_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream);
 size_t bf16_backward_workspace(const fipa_desc &d);
+size_t bf16_backward_workspace_min(const fipa_desc &d);  // likewise
 
 // IPA module around the core (fipa_module.hip)
 bool module_shape_supported(const fipa_desc &d, int d_s);
 bool module_backward_shape_supported(const fipa_desc &d, int d_s);
-size_t module_forward_workspace(const fipa_desc &d, int d_s);
-hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void *ws, hipStream_t stream);
-size_t module_backward_workspace(const fipa_desc &d, int d_s);
-hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, const ModuleBwdArgs &g, void *ws,
+// (least: what the calls run in, else what the query asks for)
+size_t module_forward_workspace(const fipa_desc &d, int d_s, bool least = false);
+hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void *ws, size_t ws_bytes, hipStream_t stream);
+size_t module_backward_workspace(const fipa_desc &d, int d_s, bool least = false);
+hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, const ModuleBwdArgs &g, void *ws, size_t ws_bytes,
                            hipStream_t stream);
-// (`ws_bytes`: what the caller gave, at least bf16_backward_workspace())
+// (`ws_bytes`: what the caller gave, at least bf16_backward_workspace_min())
 hipError_t bf16_backward(const fipa_desc &d, const BwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream);
 // bf16_backward in two calls on one workspace: `begin` runs the forward part and also writes the
 // core's outputs f.o, f.o_pts, f.o_pair; `finish` takes the upstream gradients.

@@ -282,7 +282,7 @@ hipError_t launch_gemm(const GemmParams &g, hipStream_t stream)
 }
 
 struct ModuleLayout {
-    size_t core, q, k, v, q_pts, k_pts, v_pts, o, o_pts, o_pair, part, total;
+    size_t core, q, k, v, q_pts, k_pts, v_pts, o, o_pts, o_pair, part;
 };
 
 // The output projection (Eq. 5) at B*L rows has few output tiles for 256 compute units (N = d_s
@@ -316,7 +316,6 @@ ModuleLayout module_layout(const fipa_desc &d, int d_s)
         off = align_up(off + bytes, 256);
         return at;
     };
-    w.core = take(bf16_forward_workspace(d));
     w.q = take(M * d.H * d.c * 2);
     w.k = take(M * d.H * d.c * 2);
     w.v = take(M * d.H * d.c * 2);
@@ -328,7 +327,7 @@ ModuleLayout module_layout(const fipa_desc &d, int d_s)
     w.o_pair = take(M * d.H * d.cz * 4);
     const OutSplit os = out_projection_split((int)M, d_s, d.H * (d.cz + d.c + 4 * d.Pv));
     w.part = os.nsplit > 1 ? take((size_t)os.nsplit * M * d_s * 4) : 0;
-    w.total = off;
+    w.core = off;  // (last: the core's workspace is what the caller's has left)
     return w;
 }
 
@@ -453,9 +452,9 @@ __global__ __launch_bounds__(256) void fipa_rowsum_bf16_kernel(const bf16_t *__r
 constexpr int kWgradChunks = 8;  // K chunks (of 64 rows of the batch) per workgroup of a weight-gradient product
 
 struct ModuleBwdLayout {
-    ModuleLayout f;   // forward part: core workspace slot (sized for the backward), core inputs and outputs
+    ModuleLayout f;   // forward part: core inputs and outputs, and the core's workspace (of the backward's size, last)
     size_t g16, gT, w_outT, w_inT, sT, dcat, d_o, d_o_pts, d_o_pair, dq, dk, dv, dq_pts, dk_pts, dv_pts, dX, dXT, cat,
-        catT, part, total;
+        catT, part;
 };
 
 ModuleBwdLayout module_bwd_layout(const fipa_desc &d, int d_s)
@@ -470,9 +469,6 @@ ModuleBwdLayout module_bwd_layout(const fipa_desc &d, int d_s)
         off = align_up(off + bytes, 256);
         return at;
     };
-    // the forward layout with the core slot enlarged to what the core's backward needs
-    w.f.core = take(bf16_backward_workspace(d) > bf16_forward_workspace(d) ? bf16_backward_workspace(d)
-                                                                           : bf16_forward_workspace(d));
     w.f.q = take(M * d.H * d.c * 2);
     w.f.k = take(M * d.H * d.c * 2);
     w.f.v = take(M * d.H * d.c * 2);
@@ -485,7 +481,6 @@ ModuleBwdLayout module_bwd_layout(const fipa_desc &d, int d_s)
     // (for a forward call that runs in this layout, FIPA_FLAG_KEEP_FORWARD: its partial products)
     const OutSplit os = out_projection_split((int)M, d_s, (int)n_cat);
     w.f.part = os.nsplit > 1 ? take((size_t)os.nsplit * M * d_s * 4) : 0;
-    w.f.total = 0;
     w.g16 = take(M * d_s * 2);
     w.gT = take(Mp * d_s * 2);
     w.w_outT = take(n_cat * d_s * 2);
@@ -507,7 +502,7 @@ ModuleBwdLayout module_bwd_layout(const fipa_desc &d, int d_s)
     w.catT = take(Mp * n_cat * 2);
     const size_t nsplit = ((M + kGK - 1) / kGK + kWgradChunks - 1) / kWgradChunks;
     w.part = take(nsplit * (n_cat > n_in ? n_cat : n_in) * d_s * 4);
-    w.total = off;
+    w.f.core = off;
     return w;
 }
 
@@ -526,9 +521,12 @@ bool module_shape_supported(const fipa_desc &d, int d_s)
            n_cat % 16 == 0;
 }
 
-size_t module_forward_workspace(const fipa_desc &d, int d_s) { return module_layout(d, d_s).total; }
+size_t module_forward_workspace(const fipa_desc &d, int d_s, bool least)
+{
+    return module_layout(d, d_s).core + (least ? bf16_forward_workspace_min(d) : bf16_forward_workspace(d));
+}
 
-hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void *ws, hipStream_t stream)
+hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
 {
     // With FIPA_FLAG_KEEP_FORWARD the call runs in the backward's layout and leaves there what the
     // backward call would otherwise compute again: the projected inputs, the core's outputs, and
@@ -557,7 +555,8 @@ hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void
     FwdArgs f{base + w.q, base + w.k, base + w.v, base + w.q_pts, base + w.k_pts, base + w.v_pts,
               a.rot, a.trans, a.z1, a.z2, a.w_b, a.gamma, a.mask,
               (float *)(base + w.o), (float *)(base + w.o_pts), (float *)(base + w.o_pair), nullptr};
-    e = keep ? bf16_backward_begin(d, f, base + w.core, bf16_backward_workspace(d), stream) : bf16_forward(d, f, base + w.core, bf16_forward_workspace(d), stream);
+    e = keep ? bf16_backward_begin(d, f, base + w.core, ws_bytes - w.core, stream)
+             : bf16_forward(d, f, base + w.core, ws_bytes - w.core, stream);
     if (e != hipSuccess) return e;
 
     // ---- Eq. 5: s_out = concat(o_pair, o, o_pts, |o_pts|) W_out^T + b_out --------------------------
@@ -581,9 +580,15 @@ hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void
     return hipGetLastError();
 }
 
-size_t module_backward_workspace(const fipa_desc &d, int d_s) { return module_bwd_layout(d, d_s).total; }
+size_t module_backward_workspace(const fipa_desc &d, int d_s, bool least)
+{
+    // (the core's workspace: of either direction)
+    const size_t bwd = least ? bf16_backward_workspace_min(d) : bf16_backward_workspace(d);
+    const size_t fwd = least ? bf16_forward_workspace_min(d) : bf16_forward_workspace(d);
+    return module_bwd_layout(d, d_s).f.core + (bwd > fwd ? bwd : fwd);
+}
 
-hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, const ModuleBwdArgs &g, void *ws,
+hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, const ModuleBwdArgs &g, void *ws, size_t ws_bytes,
                            hipStream_t stream)
 {
     const ModuleBwdLayout w = module_bwd_layout(d, d_s);
@@ -618,7 +623,7 @@ hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, con
               (float *)(base + w.f.o), (float *)(base + w.f.o_pts), (float *)(base + w.f.o_pair), nullptr};
     // (the forward part of the core's backward, which leaves O^ and the log-sum-exp for the gradient
     // kernels, also gives the core's outputs: no separate forward call)
-    if (!kept) FIPA_TRY(bf16_backward_begin(d, f, base + w.f.core, bf16_backward_workspace(d), stream));
+    if (!kept) FIPA_TRY(bf16_backward_begin(d, f, base + w.f.core, ws_bytes - w.f.core, stream));
 
     // ---- through Eq. 5: d cat = d s_out W_out; d W_out = d s_out^T cat; d b_out = column sums ----------
     bf16_t *g16 = (bf16_t *)(base + w.g16), *gT = (bf16_t *)(base + w.gT);
@@ -655,7 +660,7 @@ hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, con
     b.d_q = base + w.dq; b.d_k = base + w.dk; b.d_v = base + w.dv;
     b.d_q_pts = base + w.dq_pts; b.d_k_pts = base + w.dk_pts; b.d_v_pts = base + w.dv_pts;
     b.d_z1 = g.d_z1; b.d_z2 = g.d_z2; b.d_gamma = g.d_gamma; b.d_w_b = g.d_w_b; b.d_rot = g.d_rot; b.d_trans = g.d_trans;
-    FIPA_TRY(bf16_backward_finish(d, b, base + w.f.core, bf16_backward_workspace(d), stream));
+    FIPA_TRY(bf16_backward_finish(d, b, base + w.f.core, ws_bytes - w.f.core, stream));
 
     // ---- through Eq. 1: d s = dX W_in; d W_in = dX^T s; d b_in = column sums of dX ---------------------
     GemmParams gx = {};

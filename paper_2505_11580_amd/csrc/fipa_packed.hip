@@ -50,10 +50,12 @@ struct PackedPlan {
     int total;       // rows of the packed tensors, cu_seqlens[B]
     int n_nonempty;  // chains with at least one residue
     fipa_desc d;     // what the kernels run with: one launch: B chains, L = longest chain; else B = 1, L = longest chain
-    size_t fwd_bytes, bwd_bytes;
-    size_t cu_fwd, cu_bwd;  // one launch: offset of the device copy of the row offsets
-    size_t part_bwd;        // chain by chain: offset of the per-chain d_gamma | d_w_b partial sums
-    int part_stride;        // floats per chain there
+    // The workspace starts with what the batch shares -- one launch: the device copy of the row offsets; chain by chain: the
+    // chains' d_gamma | d_w_b partial sums (backward) -- and the core has the rest.
+    size_t fwd_head, bwd_head;
+    size_t fwd_bytes, bwd_bytes;  // what the query asks for
+    size_t fwd_least, bwd_least;  // what the calls run in
+    int part_stride;              // floats per chain of the partial sums
 };
 
 // One set of launches pays when the chains are many or short (a chain of 300 residues fills 36 of
@@ -88,20 +90,18 @@ int packed_plan(const fipa_desc *desc, const int32_t *cu, bool backward, PackedP
     if (!pl.one_launch) pl.d.B = 1;
     rc = fipa_workspace_bytes(&pl.d, &pl.fwd_bytes, backward ? &pl.bwd_bytes : nullptr);
     if (rc != FIPA_OK) return rc;
-    if (!backward) pl.bwd_bytes = 0;
-    pl.cu_fwd = pl.cu_bwd = pl.part_bwd = 0;
+    pl.fwd_least = desc->dtype == FIPA_DTYPE_F32 ? f32_forward_workspace(pl.d) : bf16_forward_workspace_min(pl.d);
     pl.part_stride = (desc->H + desc->H * desc->cz + 3) / 4 * 4;
-    if (pl.one_launch) {
-        const size_t cu_bytes = align_up((size_t)(desc->B + 1) * sizeof(int), 256);
-        pl.cu_fwd = align_up(pl.fwd_bytes, 256);
-        pl.fwd_bytes = pl.cu_fwd + cu_bytes;
-        if (backward) {
-            pl.cu_bwd = align_up(pl.bwd_bytes, 256);
-            pl.bwd_bytes = pl.cu_bwd + cu_bytes;
-        }
-    } else if (backward) {
-        pl.part_bwd = align_up(pl.bwd_bytes, 256);
-        pl.bwd_bytes = pl.part_bwd + align_up((size_t)(pl.n_nonempty > 0 ? pl.n_nonempty : 1) * pl.part_stride * sizeof(float), 256);
+    const size_t cu_bytes = align_up((size_t)(desc->B + 1) * sizeof(int), 256);
+    pl.fwd_head = pl.one_launch ? cu_bytes : 0;
+    pl.bwd_head = pl.one_launch ? cu_bytes : align_up((size_t)(pl.n_nonempty > 0 ? pl.n_nonempty : 1) * pl.part_stride * sizeof(float), 256);
+    pl.fwd_bytes += pl.fwd_head;
+    pl.fwd_least += pl.fwd_head;
+    if (backward) {
+        pl.bwd_bytes += pl.bwd_head;
+        pl.bwd_least = pl.bwd_head + bf16_backward_workspace_min(pl.d);
+    } else {
+        pl.bwd_bytes = pl.bwd_least = 0;
     }
     return FIPA_OK;
 }
@@ -141,8 +141,7 @@ int fipa_forward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const 
     if (rc != FIPA_OK) return rc;
     if (keep) {  // one workspace for the whole batch, of the backward's size and layout
         if (!pl.one_launch && pl.total > 0) return FIPA_ERR_UNSUPPORTED;
-        pl.fwd_bytes = pl.bwd_bytes;
-        pl.cu_fwd = pl.cu_bwd;
+        pl.fwd_least = pl.bwd_least;
     }
     const void *req[] = {q, k, v, q_pts, k_pts, v_pts, rot, trans, z1, z2, w_b, gamma, o, o_pts, o_pair, workspace};
     for (const void *ptr : req)
@@ -150,17 +149,19 @@ int fipa_forward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const 
     const void *al[] = {q, k, v, q_pts, k_pts, v_pts, rot, trans, z1, z2, w_b, gamma, o, o_pts, o_pair, lse, workspace};
     for (const void *ptr : al)
         if (!aligned16(ptr)) return FIPA_ERR_ALIGNMENT;
-    if (workspace_bytes < pl.fwd_bytes) return FIPA_ERR_WORKSPACE;
+    if (workspace_bytes < pl.fwd_least) return FIPA_ERR_WORKSPACE;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (pl.total == 0) return FIPA_OK;  // no residue, no output row
 
     if (pl.one_launch) {
-        int *cu_dev = reinterpret_cast<int *>(static_cast<char *>(workspace) + pl.cu_fwd);
+        int *cu_dev = static_cast<int *>(workspace);
         if (upload_ints(cu_seqlens, desc->B + 1, cu_dev, stream) != hipSuccess) return FIPA_ERR_LAUNCH;
         FwdArgs a{q, k, v, q_pts, k_pts, v_pts, rot, trans, z1, z2, w_b, gamma, mask, o, o_pts, o_pair, lse};
         a.cu = cu_dev;
         a.total_rows = pl.total;
-        const hipError_t e = keep ? bf16_backward_begin(pl.d, a, workspace, pl.cu_fwd, stream) : bf16_forward(pl.d, a, workspace, pl.cu_fwd, stream);
+        void *core = static_cast<char *>(workspace) + pl.fwd_head;  // (at the same place in both calls of a kept step)
+        const size_t core_bytes = workspace_bytes - pl.fwd_head;
+        const hipError_t e = keep ? bf16_backward_begin(pl.d, a, core, core_bytes, stream) : bf16_forward(pl.d, a, core, core_bytes, stream);
         return e == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
     }
 
@@ -206,9 +207,11 @@ int fipa_backward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const
     if (d_w_b && !aligned16(d_w_b)) return FIPA_ERR_ALIGNMENT;
     if ((d_rot == nullptr) != (d_trans == nullptr)) return FIPA_ERR_INVALID_ARG;
     if (d_rot && (!aligned16(d_rot) || !aligned16(d_trans))) return FIPA_ERR_ALIGNMENT;
-    if (workspace_bytes < pl.bwd_bytes) return FIPA_ERR_WORKSPACE;
+    if (workspace_bytes < pl.bwd_least) return FIPA_ERR_WORKSPACE;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int H = desc->H, n_wb = H * desc->cz;
+    void *core = static_cast<char *>(workspace) + pl.bwd_head;
+    const size_t core_bytes = workspace_bytes - pl.bwd_head;
 
     BwdArgs a;
     a.f = FwdArgs{q, k, v, q_pts, k_pts, v_pts, rot, trans, z1, z2, w_b, gamma, mask, nullptr, nullptr, nullptr, nullptr};
@@ -218,19 +221,19 @@ int fipa_backward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const
     a.d_rot = d_rot; a.d_trans = d_trans;
 
     if (pl.one_launch && pl.total > 0) {
-        int *cu_dev = reinterpret_cast<int *>(static_cast<char *>(workspace) + pl.cu_bwd);
+        int *cu_dev = static_cast<int *>(workspace);
         if (upload_ints(cu_seqlens, desc->B + 1, cu_dev, stream) != hipSuccess) return FIPA_ERR_LAUNCH;
         a.f.cu = cu_dev;
         a.f.total_rows = pl.total;
-        const hipError_t e = keep ? bf16_backward_finish(pl.d, a, workspace, pl.cu_bwd, stream)
-                                  : bf16_backward(pl.d, a, workspace, pl.cu_bwd, stream);
+        const hipError_t e = keep ? bf16_backward_finish(pl.d, a, core, core_bytes, stream)
+                                  : bf16_backward(pl.d, a, core, core_bytes, stream);
         return e == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
     }
 
     // chain by chain; gamma and w_b are shared by the chains, so each chain leaves its own sums in
     // the workspace and a last kernel adds them in chain order
     const size_t Hs = H, n_s = Hs * desc->c, n_q = Hs * desc->Pq * 3, n_v = Hs * desc->Pv * 3, n_z = (size_t)desc->r * desc->cz;
-    float *part = reinterpret_cast<float *>(static_cast<char *>(workspace) + pl.part_bwd);
+    float *part = static_cast<float *>(workspace);
     fipa_desc one = pl.d;
     int j = 0;
     for (int b = 0; b < desc->B && pl.total > 0; ++b) {
@@ -251,7 +254,7 @@ int fipa_backward_packed(const fipa_desc *desc, const int32_t *cu_seqlens, const
         c.d_w_b = d_w_b ? c.d_gamma + H : nullptr;
         c.d_rot = d_rot ? d_rot + r0 * 9 : nullptr;
         c.d_trans = d_trans ? d_trans + r0 * 3 : nullptr;
-        if (bf16_backward(one, c, workspace, pl.part_bwd, stream) != hipSuccess) return FIPA_ERR_LAUNCH;  // (the partial sums lie behind)
+        if (bf16_backward(one, c, core, core_bytes, stream) != hipSuccess) return FIPA_ERR_LAUNCH;
         j += 1;
     }
     hipLaunchKernelGGL(fipa_sum_rows_kernel, dim3((H + 255) / 256), dim3(256), 0, stream, part, j, pl.part_stride, H, d_gamma);

@@ -227,3 +227,16 @@ def test_bench_refuses_more_than_one_gpu():
     res = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert res.returncode == 2
     assert "single-GPU" in res.stderr
+
+
+def test_stored_weights_add_at_most_32_gib_to_a_workspace():
+    # against what the calls take that form the weights again in every product (r c_z = 256: sizes of such a build; forward:
+    # that of a call too small to store weights, times the length)
+    for B, L, again in ((64, 2048, 10636756224), (64, 4096, 21273511168), (8, 16384, 10636755456), (128, 8192, 85094042112),
+                        (1, 1000000, 81157169664)):
+        bwd = binding.workspace_bytes(binding.make_desc(B, L, 12, 16, 4, 8, 128, 2, binding.FIPA_DTYPE_BF16))[1]
+        assert again <= bwd <= again + (32 << 30), (B, L, bwd)
+    for L in (65536, 262144, 1000000):
+        small = binding.workspace_bytes(binding.make_desc(1, 128, 12, 16, 4, 8, 128, 4, binding.FIPA_DTYPE_BF16))[0]
+        fwd = binding.workspace_bytes(binding.make_desc(1, L, 12, 16, 4, 8, 128, 4, binding.FIPA_DTYPE_BF16))[0]
+        assert fwd <= (L // 128 + 1) * small + (32 << 30) + L * 128, (L, fwd)

@@ -1,0 +1,190 @@
+"""GPU tests of the training calls in the least workspace they run in (the stored weights of 128 to 512 query rows instead of
+all rows): same results as in the workspace that the query asks for, nothing written past the end, and less is refused.
+Sums over the key side are added up range by range, in another order: one bf16 rounding of a tensor's largest gradient (2^-8)."""
+import numpy as np
+import pytest
+
+from paper_2505_11580_amd import binding
+from paper_2505_11580_amd import workloads as wl
+from tests import gpu_util as gu
+from tests.test_gpu_backward import GRADS
+from tests.test_gpu_module import MODULE_GRADS
+from tests.test_gpu_packed import PACKED_IN, _pack, _setup
+
+pytestmark = pytest.mark.gpu
+TAIL = 1 << 20
+QUERY_SIDE = ("d_q", "d_q_pts", "d_z1")
+
+
+def up(x, n):
+    return -(-x // n) * n
+
+
+def saved(desc):
+    """What the least backward workspace is smaller by: P and dS' of all query rows (at most 4096) against one float32 of
+    gradient per row and pair column."""
+    Lp, BH = up(desc.L, 128), desc.B * desc.H
+    return max(0, BH * min(Lp, 4096) * up(Lp, 256) * 4 - BH * Lp * desc.r * desc.cz * 4)
+
+
+def guarded(n):
+    """(workspace of n bytes, the bytes behind it), all of them NaN patterns"""
+    import torch
+    buf = torch.full((n + TAIL,), 0xFF, dtype=torch.uint8, device="cuda:0")
+    return buf[:n], buf[n:]
+
+
+def untouched(tail):
+    return bool((tail == 0xFF).all())
+
+
+def same_gradients(got, want, names, label):
+    for n in names:
+        g, w = got[n].double(), want[n].double()
+        assert bool(g.isfinite().all()), (label, n)
+        if n in QUERY_SIDE:
+            assert bool((g == w).all()), (label, n)
+        else:
+            assert float((g - w).abs().max()) <= 2.0 ** -8 * float(w.abs().max()), (label, n, float((g - w).abs().max()))
+
+
+@pytest.mark.parametrize("keep", [False, True])
+@pytest.mark.parametrize("kw", [dict(L=300), dict(L=520, B=2, varlen=True, min_len=100), dict(L=1000, H=1), dict(L=700, H=1, r=4),
+                                dict(L=600, B=15, H=12, r=4, varlen=True, min_len=200)])
+def test_backward_in_the_least_workspace(kw, keep):
+    # (the last one: with rows enough for the forward to store its weights, in the larger workspace only; its lse differs by a
+    # rounding, and so do the gradients)
+    import torch
+    inp = wl.make_inputs(4, **dict(dict(B=1, H=2, cz=128, r=2, trans_scale=0.3), **kw))
+    desc, dev = binding.upload(inp)
+    desc.flags = binding.FIPA_FLAG_KEEP_FORWARD if keep else 0
+
+    def step(bytes_):
+        out, grads = binding.alloc_outputs(desc), binding.alloc_grads(desc)
+        grads["workspace"], tail = guarded(bytes_)
+        for n, _ in GRADS:
+            grads[n].fill_(float("nan"))
+        if keep:
+            out["workspace"] = grads["workspace"]
+            binding.forward(desc, dev, out)
+        binding.backward(desc, dev, out, grads)
+        torch.cuda.synchronize()
+        assert untouched(tail), kw
+        return out, grads
+
+    full = binding.workspace_bytes(desc)[1]
+    assert saved(desc) > 0
+    (o0, want), (o1, got) = step(full), step(full - saved(desc))
+    if "B" in kw and kw["B"] == 15:
+        for n, _ in GRADS:
+            if n != "d_gamma":
+                w = want[n].double()
+                assert float((got[n].double() - w).abs().max()) <= 2e-2 * float(w.abs().max()), n
+    else:
+        same_gradients(got, want, [n for n, _ in GRADS], kw)
+        if keep:
+            for n in gu.NAMES:
+                assert bool((o0[n] == o1[n]).all()), n
+    with pytest.raises(binding.FipaError) as e:
+        step(full - saved(desc) - 256)
+    assert e.value.code == binding.FIPA_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("flags", [0, binding.FIPA_FLAG_KEEP_FORWARD, binding.FIPA_FLAG_PACKED_PER_CHAIN])
+def test_packed_step_in_the_least_workspace(flags):
+    import torch
+    inp = wl.make_inputs(4, B=3, L=520, H=2, cz=128, r=2, varlen=True, min_len=300, trans_scale=0.3)
+    desc, dev, pk, cu, lengths = _setup(inp, flags)
+    total, H, f = int(cu[-1]), desc.H, dict(dtype=torch.float32, device="cuda:0")
+    ups = [_pack(dev[n], lengths) for n in ("d_o", "d_o_pts", "d_o_pair")]
+    ins = [pk[n] for n in PACKED_IN] + [dev["w_b"], dev["gamma"], None]
+
+    def step(bytes_):
+        ws, tail = guarded(bytes_)
+        if flags == binding.FIPA_FLAG_KEEP_FORWARD:
+            binding.fipa_forward_packed(desc, cu, *ins, torch.empty(total, H, desc.c, **f), torch.empty(total, H, desc.Pv, 3, **f),
+                                        torch.empty(total, H, desc.cz, **f), None, ws)
+        g = {n: torch.full_like(pk[n[2:]], float("nan")) for n, _ in GRADS if n not in ("d_gamma", "d_w_b")}
+        g["d_gamma"], g["d_w_b"] = torch.full((H,), float("nan"), **f), torch.full((H, desc.cz), float("nan"), **f)
+        binding.fipa_backward_packed(desc, cu, *ins, *ups, *[g[n] for n, _ in GRADS], ws)
+        torch.cuda.synchronize()
+        assert untouched(tail)
+        return g
+
+    d = binding.make_desc(1 if flags == binding.FIPA_FLAG_PACKED_PER_CHAIN else 3, max(lengths), H, 16, 4, 8, 128, 2, desc.dtype)
+    full = binding.packed_workspace_bytes(desc, cu)[1]
+    assert saved(d) > 0
+    same_gradients(step(full - saved(d)), step(full), [n for n, _ in GRADS], flags)
+    with pytest.raises(binding.FipaError) as e:
+        step(full - saved(d) - 256)
+    assert e.value.code == binding.FIPA_ERR_WORKSPACE
+
+
+def test_packed_forward_in_the_least_workspace():
+    # rank 4 with rows enough for stored weights: the least size is what shorter chains, which do not store them, extrapolate to
+    import torch
+    inp = wl.make_inputs(3, B=15, L=300, H=12, cz=128, r=4, varlen=True, min_len=250, trans_scale=0.3)
+    inp["lengths"][0] = 300
+    inp["mask"][0, :] = 1
+    for n in ("q", "k", "v", "q_pts", "k_pts", "v_pts", "z1", "z2", "trans"):
+        inp[n][0][np.abs(inp[n][0]) > 1e3] = 0.0  # (the first chain's former padding)
+    desc, dev, pk, cu, lengths = _setup(inp, 0)
+    total, H, f = int(cu[-1]), desc.H, dict(dtype=torch.float32, device="cuda:0")
+    q128, q256 = (binding.workspace_bytes(binding.make_desc(15, L, 12, 16, 4, 8, 128, 4, desc.dtype))[0] for L in (128, 256))
+    least = 2 * q256 - q128 + 256
+    full = binding.packed_workspace_bytes(desc, cu)[0]
+    assert least < full
+
+    def forward(bytes_):
+        out = dict(o=torch.full((total, H, desc.c), float("nan"), **f), o_pts=torch.full((total, H, desc.Pv, 3), float("nan"), **f),
+                   o_pair=torch.full((total, H, desc.cz), float("nan"), **f))
+        ws, tail = guarded(bytes_)
+        binding.fipa_forward_packed(desc, cu, *[pk[n] for n in PACKED_IN], dev["w_b"], dev["gamma"], None, *out.values(), None, ws)
+        torch.cuda.synchronize()
+        assert untouched(tail)
+        return {n: t.cpu().numpy().astype(np.float64) for n, t in out.items()}
+
+    rows = wl.select_rows(inp, 8)
+    want = gu.oracle_forward_chunked(inp, rows=rows)
+    for got in (forward(full), forward(least)):
+        for n in gu.NAMES:
+            g = np.stack([got[n][cu[b]:cu[b + 1]][np.minimum(rows[b], lengths[b] - 1)] for b in range(15)])
+            live = np.stack([rows[b] < lengths[b] for b in range(15)])
+            assert np.all(np.isfinite(got[n])) and gu.rel_err(g[live], want[n][live]) <= gu.TOL["bf16"], n
+    with pytest.raises(binding.FipaError) as e:
+        forward(least - 256)
+    assert e.value.code == binding.FIPA_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("keep", [False, True])
+def test_module_backward_in_the_least_workspace(keep):
+    import torch
+    m = wl.make_module_inputs(4, d_s=64, B=2, L=520, H=4, varlen=True, min_len=300, trans_scale=0.3)
+    desc, dev = binding.upload_module(m)
+    desc.flags = binding.FIPA_FLAG_KEEP_FORWARD if keep else 0
+    g = torch.from_numpy(np.random.default_rng(5).standard_normal((2, 520, 64)).astype(np.float32)).to("cuda:0")
+    full = binding.alloc_module_grads(desc, 64)["workspace"].numel()
+
+    def step(bytes_):
+        grads = binding.alloc_module_grads(desc, 64)
+        for n, _ in MODULE_GRADS:
+            grads[n].fill_(float("nan"))
+        grads["workspace"], tail = guarded(bytes_)
+        if keep:
+            dev["workspace"] = grads["workspace"]
+            binding.module_forward(desc, 64, dev)
+        binding.module_backward(desc, 64, dev, g, grads)
+        torch.cuda.synchronize()
+        assert untouched(tail)
+        return grads
+
+    # (the core's key gradients are rounded to bf16 on their way into the products of Eq. 1)
+    fwd, bwd = binding.workspace_bytes(desc)
+    assert bwd - saved(desc) > fwd  # (the module holds a core workspace of either direction)
+    want, got = step(full), step(full - saved(desc))
+    for n, _ in MODULE_GRADS:
+        w = want[n].double()
+        assert bool(got[n].isfinite().all()) and float((got[n].double() - w).abs().max()) <= 2.0 ** -8 * float(w.abs().max()), n
+    with pytest.raises(binding.FipaError) as e:
+        step(full - saved(desc) - 256)
+    assert e.value.code == binding.FIPA_ERR_WORKSPACE
