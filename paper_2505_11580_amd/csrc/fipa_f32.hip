@@ -78,11 +78,12 @@ __global__ __launch_bounds__(256) void fipa_pack_f32_kernel(F32Params p)
         p.cen[4 * b + 3] = 0.f;
         p.kvlen[b] = kv;
     }
-    const unsigned idx = blockIdx.x * 256u + threadIdx.x;
-    if (idx >= (unsigned)p.H * p.L * X4) return;
-    const unsigned rec = idx / X4;
-    const int x0 = 4 * (int)(idx - rec * X4);
-    const int h = rec / p.L, i = rec - h * p.L;
+    // (whole workgroups per head: the pieces of all heads pass 32 bits at 64 GiB of records)
+    const unsigned pieces = (unsigned)p.L * X4, per_head = (pieces + 255u) / 256u;
+    const int h = blockIdx.x / per_head;
+    const unsigned idx = (blockIdx.x - h * per_head) * 256u + threadIdx.x;
+    if (idx >= pieces) return;
+    const int i = idx / X4, x0 = 4 * (int)(idx - i * X4);
     const size_t urow = (size_t)b * p.L + i, row = urow * p.H + h;
     const bool ok = p.mask ? p.mask[urow] != 0 : true;
     const int nv = 3 * p.Pv;
@@ -462,8 +463,8 @@ hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, hipStream
 
     StageTimer timer(stream);
     timer.begin(0);
-    const size_t pieces = (size_t)d.H * d.L * (p.g.HRW / 4);
-    hipLaunchKernelGGL(fipa_pack_f32_kernel, dim3((unsigned)((pieces + 255) / 256), d.B), dim3(256), 0, stream, p);
+    const unsigned per_head = ((unsigned)d.L * (p.g.HRW / 4) + 255u) / 256u;
+    hipLaunchKernelGGL(fipa_pack_f32_kernel, dim3(d.H * per_head, d.B), dim3(256), 0, stream, p);
     timer.end(0);
 
     timer.begin(1);  // the fp32 kernel contains the epilogue; stage 2 stays empty
