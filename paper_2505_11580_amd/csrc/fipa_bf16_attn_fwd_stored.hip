@@ -7,10 +7,12 @@
 //   fipa_fwd_weights_kernel  S^T = K^ Q^^T, softmax reference and sum, weights P (bf16) of 32 queries per wave
 //   fipa_fwd_values_kernel   O^ = P V^ for 256 queries and a window of the columns; steps 8-9 of Algorithm 1
 //
-// Softmax: the reference of a row starts as the largest logit of the keys of its own workgroup (256, at width 1088 128
-// residues around it), where distance-dominated logits have their maximum (whose weight is then exactly 1): those blocks go
-// through the pipeline first, for their maxima alone.  (With the wave's own 32 keys, multiplied from global memory in the
-// prologue, the same time and 1.0 to 1.3 % more distance from float64: 9.24e-4 against 9.16e-4 at B = 2, L = 2048, width 1088.)
+// Softmax: the reference of a row starts as the largest logit of the 96 keys around its own residue (its wave's block and the
+// two beside it), where distance-dominated logits have their maximum, whose weight is then exactly 1: the blocks around the
+// workgroup's residues go through the LDS ring first, for these maxima alone.  (With the wave's own 32 keys, multiplied from
+// global memory in the prologue, the same time and 1.0 % more distance from float64, 8.73e-4 against 8.65e-4 on four chains of up
+// to 1500 residues; every block for every wave, 8.64e-4 but 2 % more time on the ragged batch below.  Width 1088 takes its own 32
+// keys: with one wave per SIMD and two LDS stages the blocks took 7 % of the call at B = 2, L = 2048, 530 -> 567 us, for 0.8 %.)
 // It is raised only where a block holds
 // a logit more than kRaise above it (far inside the range of bf16 and fp32), by a whole number of log2 units, so that
 // weights move from one reference to the next exactly.  A raise is recorded for its (32 queries, key block) as a flag and the 32 references before it; the values
@@ -82,6 +84,7 @@ struct FwCfg {
     static constexpr int CW_OFF = NST * STAGE;                // per-head scale vector of the query-side factors
     static constexpr int LDS_BYTES = CW_OFF + DZ * 4;
     static constexpr int NDMA = NZW + 2;
+    static constexpr bool REF = NW == 8;                      // first references from the blocks in the ring, else from the wave's own
     static_assert(EPR >= 1 && LDS_BYTES <= 160 * 1024, "LDS");
 };
 
@@ -107,9 +110,12 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
     const size_t rows0 = (size_t)bh * p.Lp;
     const int first = first_block(row0, nblk);
     auto block = [&](int n) { const int x = first + n; return x >= nblk ? x - nblk : x; };  // n-th block of the walk, n < nblk
-    // The blocks that hold the workgroup's own residues come first, for the references alone; then the walk.
-    const int nref = min(C::NW, nblk - row0 / 32), total = nref + nblk;
-    auto key_block = [&](int n) { return n < nref ? row0 / 32 + n : block(n - nref); };  // n < total
+    // The blocks around the workgroup's own residues come first, for the references alone (REF); then the walk.
+    const int ref0 = max(row0 / 32 - 1, 0), nref = C::REF ? min(row0 / 32 + C::NW + 1, nblk) - ref0 : 0, total = nref + nblk;
+    auto key_block = [&](int n) {  // n < total
+        if constexpr (!C::REF) return block(n);
+        else return n < nref ? ref0 + n : block(n - nref);
+    };
 
     // ---- direct loads ---------------------------------------------------------------------------------------------
     const u32x4 r_z = buffer_desc(p.Z2 + (size_t)b * p.Lp * DZ), r_h = buffer_desc(p.Kh + rows0 * kDH), r_b = buffer_desc(p.kbias + rows0);
@@ -140,14 +146,36 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
     const size_t urow0 = user_row(p, b, 0);
     const int irow = row0 + 32 * wave + li, irow_p = min(irow, p.Lp - 1);
     bf16x8 qf[KS];
-    float m = irow < kvlen ? kNegInf : INFINITY;  // (a row past the chain: whatever its memory holds, weights 0 and no raise)
+    auto largest = [&](const f32x16 &s) {
+        float mx = s[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+        return fmaxf(mx, __shfl_xor(mx, 32));
+    };
+    float m = kNegInf;
     {
         float *cw = reinterpret_cast<float *>(smem + C::CW_OFF);
         for (int x = tid; x < DZ; x += 64 * C::NW) cw[x] = kLog2e * p.w_L * p.w_b[(size_t)h * p.cz + x % p.cz];
         __syncthreads();
-        const bf16_t *qh = p.Qh + (rows0 + irow_p) * kDH + 8 * g;
+        // (!REF: S^T of the wave's own 32 keys, row li of that block is this lane's residue)
+        f32x16 own;
+        if constexpr (!C::REF)
 #pragma unroll
-        for (int ks = 0; ks < KSH; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qh + 16 * ks);
+            for (int r = 0; r < 16; ++r) {
+                const int key = row0 + 32 * wave + 8 * (r >> 2) + 4 * g + (r & 3);
+                const float kb = p.kbias[rows0 + min(key, p.Lp - 1)];
+                own[r] = key < kvlen ? kb : kNegInf;
+            }
+        const bf16_t *qh = p.Qh + (rows0 + irow_p) * kDH + 8 * g, *kh = p.Kh + (rows0 + irow_p) * kDH + 8 * g;
+        const bf16_t *z2 = p.Z2 + ((size_t)b * p.Lp + irow_p) * DZ + 8 * g;
+        auto dot = [&](int ks, const bf16_t *k) {
+            if constexpr (!C::REF) own = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(k), qf[ks], own, 0, 0, 0);
+        };
+#pragma unroll
+        for (int ks = 0; ks < KSH; ++ks) {
+            qf[ks] = *reinterpret_cast<const bf16x8 *>(qh + 16 * ks);
+            dot(ks, kh + 16 * ks);
+        }
         const bool ok = irow < ulen && (p.mask ? p.mask[urow0 + irow] != 0 : true);
         const unsigned keep = ok ? 0xFFFFFFFFu : 0u;
         const bf16_t *z1row = p.z1 + (urow0 + min(irow, ulen - 1)) * DZ + 8 * g;
@@ -165,7 +193,10 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
                 pk[x] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){lo, hi}, bf16x2)) & keep;
             }
             qf[KSH + ks] = __builtin_bit_cast(bf16x8, (u32x4){pk[0], pk[1], pk[2], pk[3]});
+            dot(KSH + ks, z2 + 16 * ks);
         }
+        if constexpr (!C::REF) m = largest(own);
+        if (irow >= kvlen) m = INFINITY;  // (a row past the chain: whatever its memory holds, weights 0 and no raise)
     }
     constexpr int kPin = KS - KSH < 64 ? KS - KSH : 64;
 #pragma unroll
@@ -200,12 +231,6 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
     // softmax of the block at position n (its S^T in `s`): part 1 the reference, part 2 pair t of the weights
     unsigned pk[4];
     float mu = 0.f;
-    auto largest = [&](const f32x16 &s) {
-        float mx = s[0];
-#pragma unroll
-        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-        return fmaxf(mx, __shfl_xor(mx, 32));
-    };
     auto reference = [&](const f32x16 &s, int n) {
         const float mx = largest(s);
         if (__any(mx > m + kRaise)) {
@@ -231,16 +256,14 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[f % 4], qf[f], s, 0, 0, 0);
     };
     int sidx = 0;
-    // S^T of block n and, of the block before: nothing (the first step), its largest logits (a reference block), its softmax.
-    auto step = [&](auto PREV, int n) {
-        constexpr int prev = decltype(PREV)::value;
-        constexpr bool firstb = prev == 0;
+    auto step = [&](auto FIRST, int n) {
+        constexpr bool firstb = decltype(FIRST)::value;
         const char *st = smem + sidx * C::STAGE;
         int nidx = sidx + C::NST - 1;
         nidx = nidx >= C::NST ? nidx - C::NST : nidx;
         const unsigned next = lds0 + nidx * C::STAGE;
         const int next_kb = key_block(min(n + C::NST - 1, total - 1));
-        const int before_n = prev == 2 ? n - 1 - nref : 0;  // position of the block before in the walk
+        const int before_n = firstb ? 0 : n - 1 - nref;  // position of the block before in the walk
         char *const dst = wbase + (size_t)(2 * block(before_n)) * kGrpBytes;
         static_for<KS>([&](auto J) {
             constexpr int j = decltype(J)::value;
@@ -263,9 +286,8 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
                 if constexpr (f < C::NDMA) issue(std::integral_constant<int, f>{}, next_kb, next);
                 // the softmax of the previous block, behind the loads (in the order of vector-memory operations)
                 constexpr int kS0 = C::NDMA > 4 ? C::NDMA : 4;
-                if constexpr (prev == 1 && f == kS0) m = fmaxf(m, largest(sold));
-                if constexpr (prev == 2 && f == kS0) reference(sold, before_n);
-                if constexpr (prev == 2 && f > kS0) {
+                if constexpr (!firstb && f == kS0) reference(sold, before_n);
+                if constexpr (!firstb && f > kS0) {
                     constexpr int slots = KS - kLA - 1 - kS0;
 #pragma unroll
                     for (int t = (f - kS0 - 1) * 8 / slots; t < (f - kS0) * 8 / slots; ++t) pair(sold, t, dst);
@@ -275,17 +297,39 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
         });
         sidx = sidx + 1 < C::NST ? sidx + 1 : 0;
     };
+    using T = std::true_type;
+    using F = std::false_type;
     constexpr int kAhead = (C::NST - 2) * C::NDMA;
+    if constexpr (C::REF)  // each wave takes its own block and the two beside it
+        for (int n = 0; n < nref; ++n) {
+            wait_and_barrier<kAhead>();
+            const char *st = smem + sidx * C::STAGE;
+            int nidx = sidx + C::NST - 1;
+            nidx = nidx >= C::NST ? nidx - C::NST : nidx;
+            issue_all(n + C::NST - 1, lds0 + nidx * C::STAGE);
+            const int apart = ref0 + n - (row0 / 32 + wave);
+            if (apart >= -1 && apart <= 1) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 kb4 = *reinterpret_cast<const f32x4 *>(st + C::KB_OFF + (8 * q + 4 * g) * 4);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) sacc[4 * q + x] = kb4[x];
+                }
+                static_for<KS>([&](auto J) {
+                    constexpr int j = decltype(J)::value;
+                    const char *a = j < KSH ? st + (ah ^ (32 * (j & 3))) : st + az + (j - KSH) * 32;
+                    sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(a), qf[j], sacc, 0, 0, 0);
+                });
+                m = fmaxf(m, largest(sacc));
+            }
+            sidx = sidx + 1 < C::NST ? sidx + 1 : 0;
+        }
     wait_and_barrier<kAhead>();
-    step(std::integral_constant<int, 0>{}, 0);
-    for (int n = 1; n <= nref; ++n) {
-        wait_and_barrier<kAhead>();
-        step(std::integral_constant<int, 1>{}, n);
-    }
+    step(T{}, nref);
     for (int n = nref + 1; n < total; ++n) {
         if (n == nref + 1) wait_and_barrier<kAhead>();
         else wait_and_barrier<kAhead + kStores>();  // (the newest operations are the stores of the block before last)
-        step(std::integral_constant<int, 2>{}, n);
+        step(F{}, n);
     }
     // the last block
     {

@@ -55,35 +55,38 @@ def test_static_scratch_too_small_for_the_weights():
 
 
 def test_forward_stored_weights_dominant_weight_is_exact():
-    # Three residues at one place, in three key blocks of one tile; the first one's key is out of reach, so that its query has
+    # Three residues at one place, in three neighbouring key blocks; the middle one's key is out of reach, so that its query has
     # two weights, neither in its own block.  The larger one is the reference, exactly 1, and a row's error is the rounding of
     # the smaller one alone: 0.72 2^-8 / sqrt(3) = 1.62e-3 in the mean square (mantissas uniform in the logarithm).  Against any
     # other reference both are rounded: 2.3e-3.
-    L, H, r = 256, 32, 8
-    inp = wl.make_inputs(3, B=1, L=L, H=H, cz=128, r=r, varlen=False)
+    B, L, H = 43, 256, 12
+    inp = wl.make_inputs(3, B=B, L=L, H=H, cz=128, r=4, varlen=False)
     i = np.arange(L)
     place = (i // 128) * 32 + i % 32
-    inp["trans"] = (8.0 * np.stack([place % 4 - 1.5, place // 4 % 4 - 1.5, place // 16 - 1.5], -1))[None].astype(np.float32)
+    at = 8.0 * np.stack([place % 4 - 1.5, place // 4 % 4 - 1.5, place // 16 - 1.5], -1)
+    inp["trans"] = np.broadcast_to(at, (B, L, 3)).astype(np.float32)
     inp["gamma"] = np.full(H, 4.0, dtype=np.float32)
     inp["q_pts"], inp["k_pts"] = wl.round_to_bf16(0.5 * inp["q_pts"]), wl.round_to_bf16(0.5 * inp["k_pts"])
-    inp["k_pts"][:, (i // 32) % 4 == 0] = 64.0
+    inp["k_pts"][:, (i // 32) % 4 == 1] = 64.0
     inp["k_pts"][:, (i // 32) % 4 == 3] = 64.0
     inp["q"] = 0.0 * inp["q"]      # (logits of the points alone, whose features are split in two: the features of the scalars and
     inp["w_b"] = 0.0 * inp["w_b"]  # of the pair bias are rounded to bf16 once, which moves a weight as much as its own rounding)
-    f = {n: inp[n][0].astype(np.float64) for n in ("v", "q_pts", "k_pts", "rot")}
-    first = i[(i // 32) % 4 == 0]
+    f = {n: inp[n].astype(np.float64) for n in ("v", "q_pts", "k_pts", "rot")}
+    mid = i[(i // 32) % 4 == 1]
 
-    def logit(j):  # of keys first + j for the queries `first`, at the same place
-        Q, K = (np.einsum("lxy,lhpy->lhpx", R, P) for R, P in ((f["rot"][first], f["q_pts"][first]), (f["rot"][first + j], f["k_pts"][first + j])))
-        return -0.5 * inp["w_L"] * inp["w_C"] * 4.0 * ((Q - K) ** 2).sum((-1, -2))
+    def glob(pts, rows):
+        return np.einsum("blxy,blhpy->blhpx", f["rot"][:, rows], f[pts][:, rows])
 
-    gap = logit(64) - logit(32)                       # [rows, H]
-    p = 1.0 / (1.0 + np.exp(gap))                     # weight of key first + 32
-    dv = f["v"][first + 32] - f["v"][first + 64]
-    want = f["v"][first + 64] + p[..., None] * dv
-    got = gu.run_gpu(inp)["o"][0][first]
+    def logit(j):  # of keys mid + j for the queries `mid`, at the same place
+        return -0.5 * inp["w_L"] * inp["w_C"] * 4.0 * ((glob("q_pts", mid) - glob("k_pts", mid + j)) ** 2).sum((-1, -2))
+
+    gap = logit(32) - logit(-32)                      # [B, rows, H]
+    p = 1.0 / (1.0 + np.exp(gap))                     # weight of key mid - 32
+    dv = f["v"][:, mid - 32] - f["v"][:, mid + 32]
+    want = f["v"][:, mid + 32] + p[..., None] * dv
+    got = gu.run_gpu(inp)["o"][:, mid]
     rows = (np.abs(gap) > 0.1) & (np.abs(gap) < 3.0)
     err = (((got - want) * dv).sum(-1) / (dv ** 2).sum(-1) / (p * (1 - p)))[rows]
     print("dominant weight: %d rows, rms %.2e, max %.2e" % (rows.sum(), np.sqrt((err ** 2).mean()), np.abs(err).max()), flush=True)
-    assert rows.sum() > 1000
+    assert rows.sum() > 10000
     assert np.sqrt((err ** 2).mean()) <= 1.9e-3
