@@ -7,6 +7,7 @@ import pytest
 from paper_2505_11580_amd import binding
 from paper_2505_11580_amd import workloads as wl
 from tests import gpu_util as gu
+from tests.test_gpu_module import check_module
 from tests.test_zz_no_alloc import OUT, _both
 
 pytestmark = pytest.mark.gpu
@@ -36,6 +37,57 @@ def test_forward_stored_weights_raised_references(r, B):
         inp[n] = np.ascontiguousarray(inp[n][:, perm])
     inp["k_pts"] = np.ascontiguousarray(inp["k_pts"] * 0 + 8.0)  # keys far from their own queries
     gu.check(inp, rows=wl.select_rows(inp, 24), label="fwd stored, raised references r=%d" % r)
+
+
+def _late_raises(inp, near):
+    """Rows whose reference is raised, by the position in the walk over the key blocks: lists of rows at 31, 32, 63 and behind, and
+    the 32-query groups that raise in the third word of 32 positions but not in the second.  (near: key blocks on either
+    side of a row's own that its first reference is taken from.)"""
+    L, H = inp["dims"]["L"], inp["dims"]["H"]
+    f = {n: inp[n][0].astype(np.float64) for n in ("q", "k", "q_pts", "k_pts", "rot", "trans", "z1", "z2")}
+    Q, K = (np.einsum("lxy,lhpy->lhpx", f["rot"], f[n]) + f["trans"][:, None, None] for n in ("q_pts", "k_pts"))
+    nblk = -(-L // 32)
+    late, empty = {31: set(), 32: set(), 63: set(), 64: set()}, 0
+    for h in range(H):
+        Qh, Kh = Q[:, h].reshape(L, -1), K[:, h].reshape(L, -1)
+        d2 = (Qh ** 2).sum(1)[:, None] + (Kh ** 2).sum(1)[None] - 2 * Qh @ Kh.T
+        s = f["q"][:, h] @ f["k"][:, h].T / 4.0 + np.einsum("ird,jrd->ij", f["z1"] * inp["w_b"][h].astype(np.float64), f["z2"])
+        s = np.log2(np.e) * inp["w_L"] * (s - 0.5 * inp["w_C"] * inp["gamma"][h] * d2)
+        s = np.pad(s, ((0, 0), (0, nblk * 32 - L)), constant_values=-np.inf).reshape(L, nblk, 32).max(2)
+        for g in range(nblk):
+            rows = np.arange(32 * g, min(32 * g + 32, L))
+            first = min(g // 16 * 16, nblk - 1)
+            m = s[rows][:, max(0, g - near):g + near + 1].max(1)
+            words = np.zeros(nblk // 32 + 1, dtype=bool)
+            for n in range(nblk):
+                mx = s[rows, (first + n) % nblk]
+                up = mx > m + 32.0
+                words[n // 32] |= up.any()
+                m = np.where(up, m + np.ceil(mx - m), m)
+                if n >= 64 or n in late:
+                    late[min(n, 64)] |= set(rows[up].tolist())
+            empty += bool(words[0] and not words[1] and words[2])
+    return late, empty
+
+
+@pytest.mark.parametrize("r,H", [(4, 8), (8, 1)])
+def test_forward_stored_weights_raises_in_later_words(r, H):
+    # 69 key blocks: the flags of a wave's raises fill two words and part of a third; rows that are raised at the ends of a word
+    # and in the third, some after a word without a raise
+    inp = wl.make_inputs(3, B=1, L=2200, H=H, cz=128, r=r, varlen=False)
+    perm = np.random.default_rng(5).permutation(2200)
+    for n in ("rot", "trans"):
+        inp[n] = np.ascontiguousarray(inp[n][:, perm])
+    inp["k_pts"] = np.ascontiguousarray(inp["k_pts"] * 0 + 8.0)
+    late, empty = _late_raises(inp, 1 if r == 4 else 0)
+    assert all(len(x) > 2 for x in late.values()) and (empty > 2 or H == 1), ({n: len(x) for n, x in late.items()}, empty)
+    rows = sorted(set().union(*(sorted(x)[:24] for x in late.values())))
+    gu.check(inp, rows=[np.array(rows, dtype=np.int32)], label="fwd stored, late raises r=%d" % r, chunk=32)
+
+
+def test_forward_stored_weights_in_the_module():
+    m = wl.make_module_inputs(3, d_s=64, B=15, L=257, H=12, min_len=200, trans_scale=0.3)
+    check_module(m, "module, stored forward", rows=wl.select_rows(m, 8))
 
 
 def test_forward_stored_weights_several_ranges():

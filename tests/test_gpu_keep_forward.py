@@ -80,6 +80,32 @@ def test_keep_forward_packed():
         assert np.array_equal(g[n].float().cpu().numpy().astype(np.float64), plain[n]), n
 
 
+@pytest.mark.parametrize("kw", [dict(B=4, L=300, H=2, cz=128, r=2, min_len=20), dict(B=3, L=200, H=2, cz=128, r=4, min_len=60)])
+def test_keep_forward_packed_stored_weights(kw):
+    # the widths whose gradients go through stored weights, in a workspace of NaN patterns (rows past a chain's last tile are
+    # neither written nor read)
+    import torch
+    inp = wl.make_inputs(4, varlen=True, trans_scale=0.5, **kw)
+    desc, dev, pk, cu, lengths = _setup(inp, binding.FIPA_FLAG_KEEP_FORWARD)
+    total, H = int(cu[-1]), desc.H
+    f = dict(dtype=torch.float32, device="cuda:0")
+    ins = [pk[n] for n in PACKED_IN] + [dev["w_b"], dev["gamma"], None]
+    out = [torch.full(s, float("nan"), **f) for s in ((total, H, desc.c), (total, H, desc.Pv, 3), (total, H, desc.cz))]
+    g = {n: torch.full_like(pk[n[2:]], float("nan")) for n, _ in GRADS if n not in ("d_gamma", "d_w_b")}
+    g["d_gamma"], g["d_w_b"] = torch.full((H,), float("nan"), **f), torch.full((H, desc.cz), float("nan"), **f)
+    ws = torch.full((binding.packed_workspace_bytes(desc, cu)[1],), 0xFF, dtype=torch.uint8, device="cuda:0")
+    binding.fipa_forward_packed(desc, cu, *ins, *out, None, ws)
+    binding.fipa_backward_packed(desc, cu, *ins, *[_pack(dev[n], lengths) for n in ("d_o", "d_o_pts", "d_o_pair")],
+                                 *[g[n] for n, _ in GRADS], ws)
+    torch.cuda.synchronize()
+    want = gu.oracle_forward_chunked(inp)
+    for n, t in zip(gu.NAMES, out):
+        assert gu.rel_err(t.cpu().numpy().astype(np.float64), _pack(want[n], lengths)) <= gu.TOL["bf16"], n
+    plain, _ = packed_backward(inp)  # (held to the oracle by tests/test_gpu_packed.py)
+    for n, _ in GRADS:
+        assert np.array_equal(g[n].float().cpu().numpy().astype(np.float64), plain[n]), n
+
+
 def test_keep_forward_refusals():
     import torch
     inp = wl.make_inputs(4, B=3, L=140, H=2, cz=32, varlen=True, min_len=30)
