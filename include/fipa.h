@@ -53,7 +53,7 @@ extern "C" {
  *                    FIPA_DTYPE_BF16: c % 8 == 0, cz % 8 == 0, c + 12*Pq <= 64,
  *                    c + 8*ceil(3*ceil(Pv/2)/2) <= 64, r*cz in {32, 64, 128, 256, 512, 1024}
  *                    (1024, e.g. rank 8 at cz = 128 -- the larger lifted widths that Section 4.1 names as
- *                    the way to higher rank: forward only, a plain kernel that is not tuned).
+ *                    the way to higher rank: forward only).
  */
 typedef struct fipa_desc {
     int32_t B, L, H, c, Pq, Pv, cz, r;
@@ -295,8 +295,8 @@ int fipa_factor_project_backward(int32_t B, int32_t L, int32_t k, int32_t n_bins
  * FIPA_FLAG_KEEP_FORWARD taken from the workspace the forward call filled); each may be NULL.
  * d_gamma, d_w_b, d_rot and d_trans are overwritten (not accumulated).  The paper gives no backward; it is the chain
  * rule through Eqs. 3-4 and z_ij = z1_i^T z2_j.
- * Supported for FIPA_DTYPE_BF16 with r*cz <= 512 (512, the rank-4 shape at cz = 128, on plain gradient
- * kernels that are not tuned); otherwise FIPA_ERR_UNSUPPORTED.
+ * Supported for FIPA_DTYPE_BF16 with r*cz <= 512 (512: the rank-4 shape at cz = 128); otherwise
+ * FIPA_ERR_UNSUPPORTED.
  */
 int fipa_backward(const fipa_desc *desc,
                   const void *q, const void *k, const void *v,
@@ -329,7 +329,8 @@ int fipa_backward(const fipa_desc *desc,
  *   rot, trans, z1, z2, w_b, gamma, mask: as for fipa_forward.
  * Shapes: d_s % 16 == 0, H*Pv % 8 == 0, N_cat % 16 == 0, else FIPA_ERR_UNSUPPORTED.
  * The workspace holds the core's workspace, its six bfloat16 inputs and its float32 outputs
- * (affine in L).  Device pointers, caller's stream, nothing allocated, as for fipa_forward.
+ * (see fipa_workspace_bytes for how it grows and for the least).  Device pointers, caller's stream,
+ * nothing allocated, as for fipa_forward.
  */
 int fipa_module_workspace_bytes(const fipa_desc *desc, int32_t d_s, size_t *bytes);
 int fipa_module_forward(const fipa_desc *desc, int32_t d_s,

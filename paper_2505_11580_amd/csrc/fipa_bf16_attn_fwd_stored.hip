@@ -23,9 +23,10 @@
 // Weights, per (batch, head) pair and tile of 256 queries: W[key / 16][query][16], the 16 keys in the order of the
 // matrix operand (4 g + x | 8 + 4 g + x at g 8 + x | g 8 + 4 + x).
 //
-// Measured, whole call, windowed -> here: four chains of 2.7k to 7.1k residues, H = 12, width 576: 4.54 -> 3.52 ms;
-// B = 2, L = 2048, H = 12, width 1088: 1.45 -> 0.53 ms.  Bound by the rate at which LDS and L2 feed the matrix pipe (half of
-// it is busy in either kernel) and, where chains differ in length, by the last workgroups of a range.
+// Measured, whole call, windowed -> here: four chains of 2.7k to 7.1k residues, H = 12, width 576: 4.68 -> 3.37 ms;
+// B = 2, L = 2048, H = 12, width 1088: 1.45 -> 0.53 ms.  The matrix pipe is busy for 41 % of either kernel's time at width 576
+// (where chains differ in length also because of the last workgroups of a range), for 27 / 38 % at width 1088 (weights / values:
+// 1.5 rounds of weight tiles, one wave per SIMD); waves spend 64 to 72 % of their cycles in waits for LDS, L2 and the barrier.
 #include "fipa_gfx950.h"
 
 namespace fipa {

@@ -24,7 +24,7 @@
 // not pipelined across blocks (S^T, softmax and P V of a block one after the other while the next block
 // loads), and the epilogue is the separate kernel.  It makes the shape usable; it is not tuned.
 // These shapes run here where the caller's scratch does not hold the weights of a range of query rows
-// (fipa_bf16_attn_fwd_stored.hip: 1.3 times as fast at width 576, 2.8 times at 1088).
+// (fipa_bf16_attn_fwd_stored.hip: 1.4 times as fast at width 576, 2.7 times at 1088), or the call is too small for two launches.
 #include "fipa_gfx950.h"
 
 namespace fipa {

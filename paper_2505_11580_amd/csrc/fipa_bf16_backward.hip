@@ -429,7 +429,10 @@ __global__ __launch_bounds__(1024) void fipa_bwd_wb_reduce_kernel(BwdUnpackParam
     }
 }
 
-// The lifted widths whose gradients go through stored weights (fipa_bf16_bwd_stored.hip).
+// The lifted widths whose gradients go through stored weights (fipa_bf16_bwd_stored.hip), at any length.  Kept training step,
+// forming the weights in every product / stored, us: r c_z = 256, H = 12: one chain of 64 residues 103 / 90, 131 120 / 109,
+// 256 138 / 125, 512 174 / 159, 1024 258 / 210, 16 chains of 130 310 / 226; H = 4, one of 64 93 / 82; r c_z = 512, H = 12: one chain
+// of 64 130 / 101, 131 163 / 130, 512 262 / 194, 1024 582 / 257.
 bool bwd_stored(int DZ) { return DZ == 256 || DZ == 512; }
 
 // Bytes of stored weights (P and dS', 4 per query row, key and pair) that the workspace query asks for: of 4096 query rows --

@@ -22,8 +22,8 @@
 // the small products were formed once per window: S eight times, dP six), 160 at r c_z = 256; with stored weights it is 180
 // and 100, and the products reuse every operand they read from LDS twice.  The price is 10 bytes of memory traffic per
 // pair.  Gradient kernels together, recomputing -> stored:
-//     four chains of 2.7k to 7.1k residues, H = 12, r c_z = 512   29.8 -> 7.7 ms
-//     B = 2, L = 4096, H = 12, r c_z = 256                        1.89 -> 1.38 ms (bound by the weights' 1.6 GB, written
+//     four chains of 2.7k to 7.1k residues, H = 12, r c_z = 512   29.8 -> 7.4 ms
+//     B = 2, L = 4096, H = 12, r c_z = 256                        1.89 -> 1.36 ms (bound by the weights' 1.6 GB, written
 //                                                                 at 2.7 TB/s; the reason why narrower widths recompute)
 #include "fipa_gfx950.h"
 

@@ -341,7 +341,7 @@ inline FwdStoredLayout fwd_stored_layout(const fipa_desc &d, int Lp, size_t off)
     const size_t BH = (size_t)d.B * d.H;
     // A constant number of query rows over all pairs (768 tiles of 256), so that the buffers stay affine in L up to
     // kStoredBytes; a range ends with its longest chains while most of the chip has nothing left.  Four chains of 2.7k to
-    // 7.1k residues, 48 pairs: 98304 / 196608 / 393216 rows 4.00 / 3.52 / 3.35 ms.
+    // 7.1k residues, 48 pairs: 98304 / 196608 / 393216 rows 3.63 / 3.33 / 3.08 ms.
     const size_t most = ((size_t)Lp + 255) / 256;
     size_t tiles = (196608 / BH + 255) / 256;
     tiles = tiles < 1 ? 1 : (tiles > 64 ? 64 : tiles);
@@ -370,6 +370,7 @@ inline FwdStoredLayout fwd_stored_layout(const fipa_desc &d, int Lp, size_t off)
 // (256 queries) x (32 keys) over all pairs, stored against windowed at width 576, H = 12: 1536 (one chain of 1024) 129 / 72 us,
 // 2304 (8 x 384) 115 / 109, 3072 (8 x 512) 132 / 134, 3600 (5 x 631) 141 / 143, 6144 (4 x 1024) 183 / 204, 6144 (one of 2048) 204 / 223.
 // At width 1088, stored against windowed: 48 (one chain of 128) 53 / 48 us, 96 (256) 68 / 66, 384 (8 x 128) 76 / 101, 384 (512) 90 / 95.
+// (All at H = 12; the heads enter through the number of pairs alone.)
 inline bool fwd_stored_pays(const fipa_desc &d)
 {
     const long long Lp = (long long)align_up((size_t)d.L, kTileQ), work = (long long)d.B * d.H * ((Lp + 255) / 256) * (Lp / 32);
