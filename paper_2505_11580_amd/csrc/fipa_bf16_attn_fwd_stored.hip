@@ -36,32 +36,6 @@ namespace {
 constexpr float kRaise = 32.f;
 constexpr float kNegInf = -INFINITY;
 
-__device__ __forceinline__ u32x4 buffer_desc(const void *base)
-{
-    const uint64_t a = (uint64_t)(uintptr_t)base;
-    u32x4 r;
-    r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
-    r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xFFFFu);
-    r[2] = 0x7FFFFFFFu;
-    r[3] = 0x00020000u;
-    return r;
-}
-
-__device__ __forceinline__ void dma16b(const u32x4 &rsrc, int voff, int soff, unsigned lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory", "m0");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_and_barrier()
-{
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
-    wg_barrier();
-}
-
 constexpr int kTile = 256;                 // queries of a weights tile
 constexpr int kGrpBytes = kTile * 32;      // 16 keys of a tile
 // Both kernels start a tile at the block group that holds its own residues (tiles that start at the same block share the
@@ -354,16 +328,6 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
 // ---------------------------------------------------------------------------------------------------------------
 // values
 // ---------------------------------------------------------------------------------------------------------------
-// acc += A B with the accumulator in accumulation (a) or architectural (v) registers (see fipa_bf16_bwd_stored.hip).
-__device__ __forceinline__ void mfma_a(f32x16 &acc, const bf16x8 &a, const bf16x8 &b)
-{
-    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma_v(f32x16 &acc, const bf16x8 &a, const bf16x8 &b)
-{
-    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
-}
-
 // Windows of 256 pair columns, the first with the head-specific 64 as well.  HB = 0: the columns in their natural order,
 // O^ is written.  HB > 0: of every factor slice HB blocks of 32 columns, so that the contraction over the slices stays in a
 // window and steps 8-9 run on the accumulator (AlphaFold2 head shape; HB = c_z / (32 windows)).
@@ -411,7 +375,7 @@ __device__ __forceinline__ void values_window(const FwdStoredParams &p, char *sm
     auto column = [&](int nb) { return HB == 0 ? 256 * win + 32 * nb : (nb / (HB ? HB : 1)) * C::CZ + 32 * (win * HB + nb % (HB ? HB : 1)); };
     // results of the matrix instructions become readable (asm: the compiler does not count the cycles)
     auto settle = [&]() {
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+        mfma_drain();
 #pragma unroll
         for (int hv = 0; hv < HV; ++hv) {
 #pragma unroll

@@ -73,6 +73,50 @@ __device__ __forceinline__ void wait_vmem()  // s_waitcnt vmcnt(N) only
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
 }
 
+// Buffer of 2^31 - 1 bytes at `base` for the loads below (raw bytes; a load past it brings zeros).
+__device__ __forceinline__ u32x4 buffer_desc(const void *base)
+{
+    const uint64_t a = (uint64_t)(uintptr_t)base;
+    u32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
+    r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xFFFFu);
+    r[2] = 0x7FFFFFFFu;
+    r[3] = 0x00020000u;
+    return r;
+}
+
+// One direct global -> LDS load, 16 bytes per lane: lane l fetches base + voff + soff and writes LDS byte
+// lds + 16 l.  (s_nop: the wait state between the write of m0 and its use.)
+__device__ __forceinline__ void dma16b(const u32x4 &rsrc, int voff, int soff, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+
+// Completion of everything but the newest N vector-memory operations, and of all LDS reads, before the barrier.
+template <int N>
+__device__ __forceinline__ void wait_and_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+    wg_barrier();
+}
+
+// acc += A B with the accumulator in accumulation (a) or architectural (v) registers, where many accumulators are live:
+// left to the register allocator, up to 20 of them were moved between the two files inside the loop (500 of its 670
+// instructions).  (s_nop: an operand may come out of a vector instruction right before.)
+__device__ __forceinline__ void mfma_a(f32x16 &acc, const bf16x8 &a, const bf16x8 &b)
+{
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_v(f32x16 &acc, const bf16x8 &a, const bf16x8 &b)
+{
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+// Results of these may be read by vector instructions only some cycles later, which the compiler does not know.
+__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
 // Calls f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}) in order:
 // a loop whose index is a constant expression inside the body.
 template <class F, int... Is>
