@@ -143,7 +143,8 @@ int fipa_forward(const fipa_desc *desc,
 /*
  * fipa_forward without a workspace argument, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): same
- * arguments, same kernels and same results as fipa_forward, with the scratch memory taken from an
+ * arguments and results as fipa_forward, and the kernels that fipa_forward runs in a workspace of
+ * this size (its least, where the weights of r*cz >= 512 do not fit), with the scratch memory taken from an
  * array of FIPA_STATIC_SCRATCH_BYTES that is part of the library's device image (every GPU the
  * library is used on holds one copy until the process ends).  Calls nothing that allocates.
  *   - FIPA_ERR_WORKSPACE when the least workspace of the call exceeds FIPA_STATIC_SCRATCH_BYTES

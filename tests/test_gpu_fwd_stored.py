@@ -96,6 +96,34 @@ def test_forward_stored_weights_several_ranges():
     gu.check(inp, rows=wl.select_rows(inp, 12), label="fwd stored, two ranges")
 
 
+@pytest.mark.parametrize("kw", [dict(L=257, r=8), dict(L=257, B=15, varlen=True, min_len=100)])
+def test_forward_stored_weights_replays_from_a_graph(kw):
+    import torch
+    inp = wl.make_inputs(3, **dict(dict(B=1, H=12, cz=128, r=4, varlen=False, trans_scale=0.3), **kw))
+    desc, dev = binding.upload(inp)
+    out = binding.alloc_outputs(desc)
+    names = gu.NAMES + ("lse",)
+    binding.forward(desc, dev, out)
+    torch.cuda.synchronize()
+    want = {n: out[n].clone() for n in names}
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        binding.forward(desc, dev, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        binding.forward(desc, dev, out)
+    for rep in range(3):
+        for n in names:
+            out[n].fill_(float("nan"))
+        out["workspace"].fill_(0xFF)  # eager work between the replays
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for n in names:
+            assert torch.equal(out[n], want[n]), (rep, n)
+
+
 def test_static_scratch_too_small_for_the_weights():
     inp = wl.make_inputs(3, B=1, L=2048, H=12, cz=128, r=4, varlen=False)
     desc, _ = binding.upload(inp)
