@@ -429,13 +429,15 @@ __global__ __launch_bounds__(1024) void fipa_bwd_wb_reduce_kernel(BwdUnpackParam
     }
 }
 
-// The lifted widths whose gradients go through stored weights (fipa_bf16_bwd_stored.hip), at any length.  Kept training step,
-// forming the weights in every product / stored, us: r c_z = 256, H = 12: one chain of 64 residues 103 / 90, 131 120 / 109,
-// 256 138 / 125, 512 174 / 159, 1024 258 / 210, 16 chains of 130 310 / 226; H = 4, one of 64 93 / 82; r c_z = 512, H = 12: one chain
-// of 64 130 / 101, 131 163 / 130, 512 262 / 194, 1024 582 / 257.
-bool bwd_stored(int DZ) { return DZ == 256 || DZ == 512; }
+// The lifted widths whose gradients go through stored weights (fipa_bf16_bwd_keys.hip, fipa_bf16_bwd_stored.hip), at any length.  Kept
+// training step, forming the weights in every product / stored, us: r c_z = 128, H = 12: one chain of 300 residues 111 / 98, four
+// of up to 1000 306 / 255, 32 packed ones of 64 to 512 805 / 650, B = 2, L = 4096 1643 / 1298; r c_z = 256: one chain
+// of 64 residues 103 / 90, 131 120 / 109, 256 138 / 125, 512 174 / 159, 1024 258 / 210, 16 chains of 130 310 / 226; H = 4, one of 64 93 / 82;
+// r c_z = 512, H = 12: one chain of 64 130 / 101, 131 163 / 130, 512 262 / 194, 1024 582 / 257.
+bool bwd_stored(int DZ) { return bwd_keys_fused(DZ) || DZ == 512; }
 
-// Bytes of stored weights (P and dS', 4 per query row, key and pair) that the workspace query asks for: of 4096 query rows --
+// Bytes of stored weights (P and dS', 4 per query row, key and pair) that the workspace query asks for: of 4096 query rows (where
+// dS' alone is stored, of twice as many, or the rest holds the sums of tiles that are cut in parts) --
 // every range of rows but the first adds its key-side sums to memory: 2048 / 4096 / 8192 rows measured 14.4 / 13.8 / 13.6 ms per
 // training step on four chains of up to 8192 residues (r c_z = 512), 2.24 / 2.15 / 2.15 ms at B = 2, L = 4096 (r c_z = 256) --
 // and of fewer where a pair's weights would pass the 31-bit byte offsets of the kernels (262144 residues) or all of them
@@ -452,9 +454,11 @@ size_t stored_weight_bytes(size_t BH, int Lp, int Lk, int DZ)
 }
 // Query rows whose weights fit: all of them, or whole tiles of 256, at the least half a tile (which every workspace of the
 // least size holds: its DZ Lp / Lk rows are at least 128, as Lk < 2 Lp and DZ >= 256).
-int stored_query_rows(size_t bytes, size_t BH, int Lp, int Lk)
+int stored_query_rows(size_t bytes, size_t BH, int Lp, int Lk, int DZ)
 {
-    const size_t most = kPairBytes / ((size_t)Lk * 2), cap = most < 4096 ? most : 4096, fit = bytes / (BH * Lk * 4);
+    const bool both = !bwd_keys_fused(DZ);  // P and dS', else dS' alone
+    const size_t most = kPairBytes / ((size_t)Lk * 2), rows_max = both ? 4096 : 8192, cap = most < rows_max ? most : rows_max;
+    const size_t fit = bytes / (BH * Lk * (both ? 4 : 2));
     const size_t rows = fit < cap ? fit : cap;
     return rows >= (size_t)Lp ? Lp : (int)(rows >= 256 ? rows / 256 * 256 : rows / 128 * 128);
 }
@@ -464,6 +468,7 @@ struct BwdLayout {
     size_t dOhat, Dvec, nlse, dQhat, dKhat, dVhat, rowsum, colsum, gpart, wpart, total;
     size_t dKh, dVh, dZ, Wp, Ws;  // stored weights (in the place of dKhat and dVhat)
     int Lk, nq;           // keys per group of weights; query rows of which the given workspace holds the weights
+    size_t parts, parts_bytes;  // what dS' alone leaves of the room of the weights: sums of the parts of a tile (see split_tiles)
     size_t least;         // what the calls run in (total: what the query asks for)
     bool fwd_stored;      // the given workspace holds the forward's weights too
 };
@@ -488,6 +493,7 @@ BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
     w.dKhat = w.dVhat = w.dKh = w.dVh = w.dZ = w.Wp = w.Ws = 0;
     w.Lk = (int)align_up(w.f.Lp, 256);
     w.nq = 0;
+    w.parts = w.parts_bytes = 0;
     if (bwd_stored(w.f.DZ)) {
         w.dKh = take(BHL * kDH * 4);
         w.dVh = take(BHL * kDH * 4);
@@ -503,9 +509,11 @@ BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
     if (bwd_stored(w.f.DZ)) {  // (last: as many rows as the workspace has left)
         const size_t BH = (size_t)d.B * d.H, want = stored_weight_bytes(BH, w.f.Lp, w.Lk, w.f.DZ);
         const size_t have = bytes < off ? 0 : (bytes - off < want ? bytes - off : want);
-        w.nq = stored_query_rows(have, BH, w.f.Lp, w.Lk);
+        w.nq = stored_query_rows(have, BH, w.f.Lp, w.Lk, w.f.DZ);
         w.Wp = off;
-        w.Ws = off + BH * w.nq * w.Lk * 2;
+        w.Ws = bwd_keys_fused(w.f.DZ) ? off : off + BH * w.nq * w.Lk * 2;
+        w.parts = align_up(w.Ws + BH * w.nq * w.Lk * 2, 256);
+        w.parts_bytes = off + have > w.parts ? off + have - w.parts : 0;
         const size_t least = stored_weight_least(BH, w.f.Lp, w.f.DZ);
         w.least = align_up(off + (least < want ? least : want), 256);
         take(want);
@@ -650,7 +658,8 @@ hipError_t backward_gradient_part(const fipa_desc &d, const BwdArgs &a, const Bw
         sp.dQ = (float *)(base + w.dQhat); sp.dKh = (float *)(base + w.dKh); sp.dVh = (float *)(base + w.dVh);
         sp.dZ = (float *)(base + w.dZ); sp.rowsum = (float *)(base + w.rowsum); sp.colsum = (float *)(base + w.colsum);
         sp.B = d.B; sp.L = d.L; sp.Lp = w.f.Lp; sp.H = d.H; sp.deal = a.f.mask != nullptr || a.f.cu != nullptr;
-        sp.Lk = w.Lk; sp.nq_alloc = w.nq; sp.i0 = 0; sp.nq = 0; sp.units = sp.q_units = sp.nseg = sp.seg_blocks = 0;
+        sp.Lk = w.Lk; sp.nq_alloc = w.nq; sp.i0 = 0; sp.nq = 0; sp.parts = sp.q_parts = (float *)(base + w.parts); sp.parts_bytes = w.parts_bytes; sp.k_full = sp.q_full = 0;
+        sp.k_S = sp.q_S = 1; sp.units = sp.q_units = sp.nseg = sp.seg_blocks = 0;
         e = launch_bwd_stored_bf16(sp, w.f.DZ, stream);
         if (e != hipSuccess) return e;
     } else {

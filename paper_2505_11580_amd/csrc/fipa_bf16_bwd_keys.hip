@@ -1,0 +1,354 @@
+// Key side of the backward for r c_z = 128 and 256 in one kernel: a workgroup keeps 128 keys, streams the queries, forms
+//     P_ij  = exp2(S_ij - lse_i),   dS'_ij = ln2 P_ij (dP_ij - D_i)
+// once and accumulates the whole key-side gradient from them in registers,
+//     dK^_j = sum_i dS'_ij Q^_i,   dV^_j = sum_i P_ij dO^_i     (pair columns: their sum, see fipa_bf16_bwd_stored.hip)
+// and leaves dS' in memory (bf16) for the product that forms dQ^.
+//
+// A wave holds 32 keys: their lifted features as MFMA B fragments (k^ | v^ head parts, z2: DZ / 4 + 32 registers) and
+// kDH 2 / 32 + DZ / 32 accumulator blocks (192 registers at r c_z = 256): one wave per SIMD.  Both small products are formed
+// transposed (queries are the rows, the lane owns a key), so the rounded weights are the B operand of the accumulating
+// MFMAs as they stand; their A operand is read from the same row-major LDS tiles with the transposing read.
+//
+// Measured at B = 2, L = 4096, H = 12, r c_z = 256 (weights kernel + products of the key side before): 860 us = 1.2 PFLOP/s executed,
+// matrix pipe 56 % busy at 2.0 GHz (the clock gives way to the load: a large product of random bf16 numbers reaches 1.4 to 1.6
+// PFLOP/s here), no LDS bank conflicts.  Nothing alone holds it up: without the loads, the LDS reads of the accumulations or
+// the stores (results invalid) it takes 4 to 10 % less.  Operands five operations ahead instead of three: the same.
+//
+// Software pipeline over two blocks of 32 queries: step n forms S and dP of block n and accumulates block n - 1,
+//     first half:  S of block n            | dV^ part of block n - 1, dS' of block n - 1 rounded and stored
+//     second half: dP of block n, its P    | dK^ part of block n - 1
+// so that the exponentials and roundings sit between matrix instructions that do not depend on them.  Three LDS stages: the
+// two blocks and the one whose loads are in flight.
+//
+// LDS tiles: rows of the pair part in natural order, the 16-byte slot c of row r at c ^ f(r), f(r) = 4 (r mod 4) + r / 4 mod 4,
+// within each 256 bytes: the row reads (16 rows, one slot) and the transposing reads (4 rows, 64 bytes each) are both free of
+// bank conflicts.  (Head rows, 128 bytes: f(r) = 4 (r / 2 mod 2) + r / 4 mod 4.)
+#include "fipa_gfx950.h"
+
+namespace fipa {
+
+namespace {
+
+template <int DZ>
+struct KyCfg {
+    static constexpr int NW = 4, TK = 32 * NW;                // waves, keys of a tile
+    static constexpr int D = kDH + DZ, KS = D / 16, KSH = kDH / 16, KSZ = DZ / 16;
+    static constexpr int ZBL = DZ / 32;                       // pair-part accumulator blocks
+    static constexpr int ZB = DZ * 2;                         // bytes of a pair-part row
+    static constexpr int RPL = 1024 / ZB, SPR = 64 / RPL;     // rows per 1 KiB load, 16-byte slots per row
+    static constexpr int NZW = 32 / RPL / NW;                 // loads of a pair-part tile per wave
+    static constexpr int Q_Z = 0, O_Z = 32 * ZB, Q_H = 2 * O_Z, O_H = Q_H + 4096, SC = O_H + 4096;
+    static constexpr int STAGE = SC + 1024, NST = 3, LDS_BYTES = NST * STAGE;
+    static constexpr int NDMA = 2 * NZW + 3;
+    static constexpr int NA = 2 * (2 + ZBL);                  // accumulating MFMAs per weight (P or dS') and block
+    static constexpr int LA = 3, RING = 4, N = 4 * KS;        // operands are read LA operations ahead
+    static_assert(NA == KS && N % RING == 0 && (ZB == 256 || ZB == 512) && LDS_BYTES <= 160 * 1024, "schedule and LDS");
+    static constexpr int kStores = 2;
+};
+
+enum { kOpP, kOpS, kOpD, kOpT };  // accumulation with P; S; accumulation with dS'; dP
+
+template <int DZ>
+struct KyOps {  // operation j of a step: the first LA need nothing but the previous block's tile
+    static constexpr int KS = KyCfg<DZ>::KS, LA = KyCfg<DZ>::LA;
+    __host__ __device__ static constexpr int kind(int j)
+    {
+        if (j < 2 * KS) return j < LA ? kOpP : (j >= 2 * KS - LA ? kOpS : ((j - LA) % 2 == 0 ? kOpS : kOpP));
+        return (j - 2 * KS) % 2 == 0 ? kOpT : kOpD;
+    }
+    __host__ __device__ static constexpr int idx(int j)
+    {
+        if (j < 2 * KS) return j < LA ? j : (j >= 2 * KS - LA ? j - KS : ((j - LA) % 2 == 0 ? (j - LA) / 2 : LA + (j - LA) / 2));
+        return (j - 2 * KS) / 2;
+    }
+};
+
+__device__ __forceinline__ int swz_z(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+__device__ __forceinline__ int swz_h(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
+
+template <int DZ>
+__global__ __launch_bounds__(256, 1) void fipa_bwd_keys_kernel(BwdStoredParams p)
+{
+    using C = KyCfg<DZ>;
+    using O = KyOps<DZ>;
+    constexpr int KS = C::KS, KSH = C::KSH, KSZ = C::KSZ;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    // a contiguous run of tiles per XCD: neighbours stream the same queries
+    int logical, part;
+    if (!bwd_unit(p.units, p.k_full, p.k_S, logical, part)) return;
+    const int nkt = p.Lp / C::TK;
+    const int bh_pos = logical / nkt, tile = logical - bh_pos * nkt;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bh = p.deal ? dealt_pair_by_length(bh_pos, p.kvlen, p.B, p.H, lane) : bh_pos;
+    const int b = bh / p.H;
+    const int kvlen = p.deal ? p.kvlen[b] : p.L;
+    const int all = min(p.nq / 32, (kvlen - p.i0 + 31) / 32);  // query blocks of this range
+    if (tile * C::TK >= kvlen || all <= 0) return;  // (a range without queries adds nothing: the first one has some)
+    const int S = logical < p.k_full ? 1 : p.k_S;   // (a tile that is cut has S blocks at least)
+    const int blk0 = part * all / S, nblk = (part + 1) * all / S - blk0, i0 = p.i0 + 32 * blk0;
+
+    const size_t rows0 = (size_t)bh * p.Lp;
+    // ---- direct loads -------------------------------------------------------------------------------------------
+    constexpr int ZP = DZ * 2, OP = C::D * 2;
+    const u32x4 r_qz = buffer_desc(p.Qz + rows0 * DZ), r_oz = buffer_desc(p.dOhat + rows0 * C::D + kDH);
+    const u32x4 r_qh = buffer_desc(p.Qh + rows0 * kDH), r_oh = buffer_desc(p.dOhat + rows0 * C::D), r_sc = buffer_desc(p.nlse + rows0);
+    int vq[2], vo[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int rl = lane / C::SPR, slot = lane % C::SPR, row = (wave + 4 * k) * C::RPL + rl;
+        const int chunk = (slot & ~15) | ((slot & 15) ^ swz_z(row));
+        vq[k] = rl * ZP + chunk * 16;
+        vo[k] = rl * OP + chunk * 16;
+    }
+    const int hrow = lane >> 3, hslot = (lane & 7) ^ swz_h(8 * wave + hrow);
+    const int vqh = hrow * kDH * 2 + hslot * 16, voh = hrow * OP + hslot * 16;
+    // (lanes 0-7: 32 values of -lse; lanes 8-15: 32 values of -D; the others repeat lane 0)
+    const int vsc = lane < 8 ? lane * 16 : (lane < 16 ? p.d_minus_nlse + (lane - 8) * 16 : 0);
+    const unsigned lds0 = lds_address(smem);
+    auto issue = [&](auto Kc, int row0, unsigned stage) {
+        constexpr int K = decltype(Kc)::value;
+        if constexpr (K < C::NZW) {
+            const int e = wave + 4 * K;
+            dma16b(r_qz, vq[K & 1], (row0 + e * C::RPL) * ZP, stage + C::Q_Z + 1024 * e);
+        } else if constexpr (K < 2 * C::NZW) {
+            const int e = wave + 4 * (K - C::NZW);
+            dma16b(r_oz, vo[(K - C::NZW) & 1], (row0 + e * C::RPL) * OP, stage + C::O_Z + 1024 * e);
+        } else if constexpr (K == 2 * C::NZW) {
+            dma16b(r_qh, vqh, (row0 + 8 * wave) * kDH * 2, stage + C::Q_H + 1024 * wave);
+        } else if constexpr (K == 2 * C::NZW + 1) {
+            dma16b(r_oh, voh, (row0 + 8 * wave) * OP, stage + C::O_H + 1024 * wave);
+        } else {
+            dma16b(r_sc, vsc, row0 * 4, stage + C::SC);  // (every wave: the same values)
+        }
+    };
+    static_for<C::NDMA>([&](auto K) { issue(K, i0, lds0); });
+
+    // ---- stationary fragments: key tile * 128 + 32 wave + li ------------------------------------------------------
+    bf16x8 kf[KSH], vf[KSH], zf[KSZ];
+    const int key = tile * C::TK + 32 * wave + li;  // < Lp
+    {
+        const bf16_t *kr = p.Kh + (rows0 + key) * kDH + 8 * g, *vr = p.Vh + (rows0 + key) * kDH + 8 * g;
+        const bf16_t *zr = p.Z2 + ((size_t)b * p.Lp + key) * DZ + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < KSH; ++ks) {
+            kf[ks] = *reinterpret_cast<const bf16x8 *>(kr + 16 * ks);
+            vf[ks] = *reinterpret_cast<const bf16x8 *>(vr + 16 * ks);
+        }
+#pragma unroll
+        for (int ks = 0; ks < KSZ; ++ks) zf[ks] = *reinterpret_cast<const bf16x8 *>(zr + 16 * ks);
+    }
+    const float slane = p.kbias[rows0 + key];
+#pragma unroll
+    for (int ks = 0; ks < KSZ; ++ks) asm volatile("" : "+a"(zf[ks]));  // (the MFMAs read their B operand there as well)
+
+    // ---- per-lane LDS offsets --------------------------------------------------------------------------------------
+    const int rz = li * C::ZB + ((g ^ swz_z(li)) << 4), rh = li * 128 + ((g ^ swz_h(li)) << 4);  // row reads: slot 2 ks + g
+    const int l16 = lane & 15, grp2 = (lane >> 4) & 1, e4 = l16 >> 2, j4 = l16 & 3, c2 = 2 * grp2 + (j4 >> 1);
+    // transposing reads: rows 4 g + e4 (and 8 further: slot ^ 2), 64-byte block x = 0
+    const int tz = (4 * g + e4) * C::ZB + (((e4 << 2) | (c2 ^ g)) << 4) + 8 * (j4 & 1);
+    const int th = (4 * g + e4) * 128 + ((((e4 >> 1) << 2) | (c2 ^ g)) << 4) + 8 * (j4 & 1);
+
+    // destination of dS': [16-query group][key][16]
+    const size_t grp_bytes = (size_t)p.Lk * 32;
+    char *ws = reinterpret_cast<char *>(p.Ws) + ((size_t)bh * (p.nq_alloc / 16) + 2 * blk0) * grp_bytes + (size_t)tile * C::TK * 32;
+    const unsigned wlane = (32 * wave + li) * 32 + 16 * g;
+
+    f32x16 acck[2], accv[2], accz[C::ZBL];
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) acck[nb][x] = accv[nb][x] = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < C::ZBL; ++nb) accz[nb][x] = 0.f;
+    }
+    f32x16 s, pr, dp;
+    u32x4 pw[2], dw[2];  // rounded P and dS' of a block: B operands of its two k-steps
+    bf16x8 fr[C::RING];
+    float csum = 0.f;
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+
+    auto p_pair = [&](int t) {
+        const float e0 = __builtin_amdgcn_exp2f(s[2 * t]), e1 = __builtin_amdgcn_exp2f(s[2 * t + 1]);
+        pr[2 * t] = kLn2 * e0;
+        pr[2 * t + 1] = kLn2 * e1;
+        pw[t >> 2][t & 3] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){e0, e1}, bf16x2));
+    };
+    auto s_pair = [&](int t) {
+        const bf16x2 d = __builtin_convertvector((f32x2){pr[2 * t] * dp[2 * t], pr[2 * t + 1] * dp[2 * t + 1]}, bf16x2);
+        csum = __builtin_amdgcn_fdot2_f32_bf16(d, ones, csum, false);
+        dw[t >> 2][t & 3] = __builtin_bit_cast(unsigned, d);
+        if ((t & 3) == 3) *reinterpret_cast<u32x4 *>(ws + (t >> 2) * grp_bytes + wlane) = dw[t >> 2];
+    };
+    // operand of operation j: of the block in stage `sa` (accumulations), or of the one in `sn` (S, dP)
+    auto fetch = [&](auto J, const char *sa, const char *sn) -> bf16x8 {
+        constexpr int j = decltype(J)::value, kind = O::kind(j), x = O::idx(j);
+        if constexpr (kind == kOpS || kind == kOpT) {
+            constexpr bool second = kind == kOpT;
+            if constexpr (x < KSH) return *reinterpret_cast<const bf16x8 *>(sn + (second ? C::O_H : C::Q_H) + (rh ^ (32 * x)));
+            else {
+                constexpr int z = x - KSH;
+                return *reinterpret_cast<const bf16x8 *>(sn + (second ? C::O_Z : C::Q_Z) + (z >> 3) * 256 + (rz ^ (32 * (z & 7))));
+            }
+        } else {
+            constexpr bool first = kind == kOpP;
+            constexpr int t = x / (2 + C::ZBL), blk = x % (2 + C::ZBL);
+            bf16x4 lo, hi;
+            if constexpr (blk < 2) {
+                const char *a = sa + (first ? C::O_H : C::Q_H) + 16 * t * 128;
+                lo = lds_read_tr(a + (th ^ (64 * blk)));
+                hi = lds_read_tr(a + 8 * 128 + (th ^ (64 * blk) ^ 32));
+            } else {
+                constexpr int nb = blk - 2;
+                const char *a = sa + (first ? C::O_Z : C::Q_Z) + 16 * t * C::ZB + (nb >> 2) * 256;
+                lo = lds_read_tr(a + (tz ^ (64 * (nb & 3))));
+                hi = lds_read_tr(a + 8 * C::ZB + (tz ^ (64 * (nb & 3)) ^ 32));
+            }
+            bf16x8 v;
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                v[y] = lo[y];
+                v[4 + y] = hi[y];
+            }
+            return v;
+        }
+    };
+    auto mfma_of = [&](auto J) {
+        constexpr int j = decltype(J)::value, kind = O::kind(j), x = O::idx(j);
+        const bf16x8 &f = fr[j % C::RING];
+        if constexpr (kind == kOpS) {
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x < KSH ? kf[x < KSH ? x : 0] : zf[x < KSH ? 0 : x - KSH], s, 0, 0, 0);
+        } else if constexpr (kind == kOpT) {
+            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x < KSH ? vf[x < KSH ? x : 0] : zf[x < KSH ? 0 : x - KSH], dp, 0, 0, 0);
+        } else {
+            constexpr int t = x / (2 + C::ZBL), blk = x % (2 + C::ZBL);
+            const bf16x8 w = __builtin_bit_cast(bf16x8, kind == kOpP ? pw[t] : dw[t]);
+            if constexpr (blk >= 2) mfma_a(accz[blk >= 2 ? blk - 2 : 0], f, w);
+            else if constexpr (kind == kOpP) mfma_a(accv[blk < 2 ? blk : 0], f, w);
+            else mfma_a(acck[blk < 2 ? blk : 0], f, w);
+        }
+    };
+    auto start = [&](auto S, f32x16 &acc, const char *at) {  // -lse_i and the key's term, or -D_i
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(at + (8 * a + 4 * g) * 4);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) acc[4 * a + x] = decltype(S)::value ? v[x] + slane : v[x];
+        }
+    };
+    // HS: there is a block n; HA: there is a block n - 1
+    int sidx = 0;  // stage of block n
+    auto step = [&](auto HS, auto HA, int n) {
+        constexpr bool hs = decltype(HS)::value, ha = decltype(HA)::value;
+        const char *sn = smem + sidx * C::STAGE;
+        const char *sa = smem + (sidx == 0 ? C::NST - 1 : sidx - 1) * C::STAGE;
+        const unsigned next = lds0 + (sidx == C::NST - 1 ? 0 : sidx + 1) * C::STAGE;
+        const int next_row = i0 + 32 * min(n + 1, nblk - 1);
+        constexpr int d0 = C::NDMA + 1, d1 = 2 * KS - 4;              // operations among which dS' is formed
+        constexpr int p0 = 2 * KS + 3, p1 = 4 * KS - C::LA - 2;       // and P
+        static_for<C::N>([&](auto J) {
+            constexpr int j = decltype(J)::value, kind = O::kind(j);
+            constexpr bool acc_op = kind == kOpP || kind == kOpD;
+            if constexpr (j == 0) {
+                if constexpr (ha) mfma_of(J);
+                if constexpr (hs) {
+                    // the loads of block n are complete: the newest operations are the stores of dS' of the block before last
+                    // (each wave has used every operand that it read from the stage the next loads go to)
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (n < 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::kStores) : "memory");
+                    wg_barrier();
+                }
+            }
+            constexpr int jf = j + C::LA;
+            if constexpr (jf < C::N) {
+                constexpr int kf_ = O::kind(jf < C::N ? jf : 0);
+                constexpr bool acc_f = kf_ == kOpP || kf_ == kOpD;
+                if constexpr (acc_f ? ha : hs) fr[jf % C::RING] = fetch(std::integral_constant<int, jf>{}, sa, sn);
+            } else if constexpr (hs) {  // the first accumulations of the next step, of block n
+                fr[jf % C::RING] = fetch(std::integral_constant<int, jf % C::N>{}, sn, sn);
+            }
+            if constexpr (hs && j == C::LA - 1) start(std::true_type{}, s, sn + C::SC);
+            if constexpr (hs && j == 2 * KS - 1) start(std::false_type{}, dp, sn + C::SC + 128);
+            if constexpr (j > 0 && (acc_op ? ha : hs)) mfma_of(J);
+            if constexpr (hs && j >= 1 && j <= C::NDMA) issue(std::integral_constant<int, j - 1>{}, next_row, next);
+            if constexpr (ha && j >= d0 && j < d1) {
+#pragma unroll
+                for (int t = (j - d0) * 8 / (d1 - d0); t < (j - d0 + 1) * 8 / (d1 - d0); ++t) s_pair(t);
+            }
+            if constexpr (hs && j >= p0 && j < p1) {
+#pragma unroll
+                for (int t = (j - p0) * 8 / (p1 - p0); t < (j - p0 + 1) * 8 / (p1 - p0); ++t) p_pair(t);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (ha) ws += 2 * grp_bytes;
+        sidx = sidx == C::NST - 1 ? 0 : sidx + 1;
+    };
+    using T = std::true_type;
+    using F = std::false_type;
+    step(T{}, F{}, 0);
+    for (int n = 1; n < nblk; ++n) step(T{}, T{}, n);
+    step(F{}, T{}, nblk);
+    wait_vmem<0>();  // (the loads past the last block still write LDS)
+    mfma_drain();
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {  // (orders every use of the accumulators behind the wait)
+        asm volatile("" : "+a"(acck[nb]));
+        asm volatile("" : "+a"(accv[nb]));
+    }
+#pragma unroll
+    for (int nb = 0; nb < C::ZBL; ++nb) asm volatile("" : "+a"(accz[nb]));
+
+    // ---- results: later ranges of queries add to the sums of the earlier ones ----------------------------------------
+    if (key >= kvlen) return;
+    const bool add = p.i0 > 0;
+    const size_t r = rows0 + key;
+    auto out = [&](float *dst, const f32x16 &a) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (add) v = *reinterpret_cast<const f32x4 *>(dst + 8 * q + 4 * g);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[x] += a[4 * q + x];
+            *reinterpret_cast<f32x4 *>(dst + 8 * q + 4 * g) = v;
+        }
+    };
+    float *dk = p.dKh + r * kDH, *dv = p.dVh + r * kDH, *dz = p.dZ + r * DZ, *sum = p.colsum + r;
+    if (part > 0) {
+        const size_t at = ((size_t)(logical - p.k_full) * (S - 1) + part - 1) * C::TK + 32 * wave + li;
+        dk = p.parts + at * bwd_key_part_row(DZ);
+        dv = dk + kDH;
+        dz = dv + kDH;
+        sum = dz + DZ;
+    }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+        out(dk + 32 * nb, acck[nb]);
+        out(dv + 32 * nb, accv[nb]);
+    }
+#pragma unroll
+    for (int nb = 0; nb < C::ZBL; ++nb) out(dz + 32 * nb, accz[nb]);
+    const float tot = csum + __shfl_xor(csum, 32);
+    if (g == 0) *sum = (add ? *sum : 0.f) + tot;
+}
+
+template <int DZ>
+hipError_t launch(const BwdStoredParams &p, hipStream_t stream)
+{
+    static LdsLimit limit;
+    const hipError_t e = raise_lds_limit(limit, (const void *)fipa_bwd_keys_kernel<DZ>, KyCfg<DZ>::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fipa_bwd_keys_kernel<DZ>, dim3(bwd_unit_blocks(p.units, p.k_full)), dim3(256), KyCfg<DZ>::LDS_BYTES, stream, p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_bwd_keys_bf16(BwdStoredParams p, int DZ, hipStream_t stream)
+{
+    p.units = p.k_full + (p.B * p.H * (p.Lp / 128) - p.k_full) * p.k_S;
+    return DZ == 256 ? launch<256>(p, stream) : launch<128>(p, stream);
+}
+
+}  // namespace fipa

@@ -1,11 +1,12 @@
-// Gradient kernels of the backward for r c_z = 256 and 512: the attention weights and their
-// gradients are formed once, kept in memory for a range of query rows, and the three gradients are
-// plain matrix products with them.  Same formulas as fipa_bf16_bwd_kernel.hip:
+// Gradient kernels of the backward with the attention weights in memory, for a range of query rows at a time.  Same formulas as
+// fipa_bf16_bwd_kernel.hip:
 //     P_ij  = exp2(S_ij - lse_i),   dS_ij = P_ij (dP_ij - D_i),
 //     dQ^_i = sum_j dS_ij K^_j,   dK^_j = sum_i dS_ij Q^_i,   dV^_j = sum_i P_ij dO^_i.
 //
-//   fipa_bwd_weights_kernel  P and dS' = ln2 dS of 256 keys x (a run of query blocks), bf16
-//   fipa_bwd_accum_kernel    KV: dK^ and dV^ of a key tile;  otherwise dQ^ of a query tile
+//   r c_z = 512         fipa_bwd_weights_kernel   P and dS' = ln2 dS of 256 keys x (a run of query blocks), bf16
+//                       fipa_bwd_products_kernel  dK^ and dV^ of a key tile, and dQ^ of a query tile
+//   r c_z = 128, 256    (fipa_bf16_bwd_keys.hip   dS', dK^ and dV^ of a key tile)
+//                       fipa_bwd_query_kernel     dQ^ of a query tile
 //
 // The gradient of z2 wants ln2 dK^_z + dV^_z only, and with dS' both terms are products of stored
 // weights with streamed rows: they share one accumulator, so a key tile's whole gradient is 12 column
@@ -19,12 +20,13 @@
 //
 // Why: forming S and dP inside each of the three accumulations costs 612 matrix instructions per 32 x 32 pairs at
 // r c_z = 512 (the accumulators of a window of the columns and two sets of stationary fragments fill the registers, so
-// the small products were formed once per window: S eight times, dP six), 160 at r c_z = 256; with stored weights it is 180
-// and 100, and the products reuse every operand they read from LDS twice.  The price is 10 bytes of memory traffic per
-// pair.  Gradient kernels together, recomputing -> stored:
+// the small products were formed once per window: S eight times, dP six), 160 at r c_z = 256, 96 at 128; with stored weights it is
+// 180, 100 and 60, and the products here reuse every operand they read from LDS twice.  Where the key side's whole gradient fits a
+// wave's registers beside its keys (r c_z <= 256) it is accumulated where the weights are formed, and dS' alone goes to memory: 4 bytes
+// of traffic per pair instead of 10.  Gradient kernels together, recomputing -> P and dS' stored -> dS' alone:
 //     four chains of 2.7k to 7.1k residues, H = 12, r c_z = 512   29.8 -> 7.4 ms
-//     B = 2, L = 4096, H = 12, r c_z = 256                        1.89 -> 1.36 ms (bound by the weights' 1.6 GB, written
-//                                                                 at 2.7 TB/s; the reason why narrower widths recompute)
+//     B = 2, L = 4096, H = 12, r c_z = 256                        1.89 -> 1.30 -> 1.17 ms
+//     the same at r c_z = 128 (whole training step)               1.64 ->      -> 1.30 ms
 #include "fipa_gfx950.h"
 
 namespace fipa {
@@ -44,23 +46,20 @@ struct WtCfg {
     static constexpr int NW = 8, TK = 32 * NW;                // waves, keys of a tile
     static constexpr int D = kDH + DZ, KS = D / 16, KSH = kDH / 16;
     static constexpr int ZB = DZ * 2;                         // bytes of a pair-part row
-    static constexpr int ZROWS = 1024 / ZB;                   // rows per 1 KiB load
-    static constexpr int NZW = 32 / ZROWS / NW;               // loads of a pair-part tile per wave
-    // LDS: the pieces of one load ZP bytes apart, so that 16 rows start in 16 different 16-byte slots of the banks; with two
-    // rows per load the odd one has its neighbouring slots exchanged
-    static constexpr int ZP = 1024 + 16 * ZROWS;
-    static constexpr int Q_Z = 0, O_Z = 32 / ZROWS * ZP, Q_H = 2 * O_Z, O_H = Q_H + 4096, SC = O_H + 4096;
+    static constexpr int NZW = 32 / NW;                       // loads of a pair-part tile per wave, a row each
+    static constexpr int ZP = 1024 + 16;                      // LDS row pitch: 16 rows start in 16 different 16-byte slots of the banks
+    static constexpr int Q_Z = 0, O_Z = 32 * ZP, Q_H = 2 * O_Z, O_H = Q_H + 4096, SC = O_H + 4096;
     static constexpr int STAGE = SC + 1024;
     static constexpr int NST = 3 * STAGE <= 160 * 1024 ? 3 : 2;
     static constexpr int LDS_BYTES = NST * STAGE;
     static constexpr int NDMA = 2 * NZW + 1 + 1;
-    static_assert((ZROWS == 1 || ZROWS == 2) && LDS_BYTES <= 160 * 1024, "one load covers whole rows");
+    static_assert(ZB == 1024 && LDS_BYTES <= 160 * 1024, "one load covers a row");
 };
 
 template <class C>
 struct WtDma {
     u32x4 qz, oz, h, sc;
-    int vz, vzo, vh, vsc;  // per-lane offsets
+    int vz, vh, vsc;  // per-lane offsets
     int wave, hp;                          // wave; pitch of its head-specific rows (waves 0-3: q^, 4-7: dO^)
 };
 
@@ -70,10 +69,10 @@ __device__ __forceinline__ void wt_issue(const WtDma<C> &d, int row0, unsigned s
     constexpr int ZP = DZ * 2, OP = (kDH + DZ) * 2;
     if constexpr (K < C::NZW) {
         const int e = d.wave + C::NW * K;
-        dma16b(d.qz, d.vz, (row0 + e * C::ZROWS) * ZP, stage + C::Q_Z + C::ZP * e);
+        dma16b(d.qz, d.vz, (row0 + e) * ZP, stage + C::Q_Z + C::ZP * e);
     } else if constexpr (K < 2 * C::NZW) {
         const int e = d.wave + C::NW * (K - C::NZW);
-        dma16b(d.oz, d.vzo, (row0 + e * C::ZROWS) * OP, stage + C::O_Z + C::ZP * e);
+        dma16b(d.oz, d.vz, (row0 + e) * OP, stage + C::O_Z + C::ZP * e);
     } else if constexpr (K == 2 * C::NZW) {
         dma16b(d.h, d.vh, (row0 + 8 * (d.wave & 3)) * d.hp, stage + C::Q_H + 1024 * d.wave);  // (O_H follows Q_H)
     } else {
@@ -114,10 +113,7 @@ __global__ __launch_bounds__(512, 2) void fipa_bwd_weights_kernel(BwdStoredParam
     dma.sc = buffer_desc(p.nlse + rows0);
     dma.wave = wave;
     {
-        constexpr int SPR = C::ZB / 16;  // slots per row
-        const int rz = lane / SPR, sz = (lane % SPR) ^ (C::ZROWS == 2 ? rz : 0);
-        dma.vz = rz * (DZ * 2) + sz * 16;
-        dma.vzo = rz * (C::D * 2) + sz * 16;
+        dma.vz = lane * 16;
         const int r = lane >> 3, row = 8 * wave + r, slot = (lane & 7) ^ ((row >> 1) & 7);
         dma.vh = r * dma.hp + slot * 16;
         // (lanes 0-7: 32 values of -lse; lanes 8-15: 32 values of D; the others repeat lane 0)
@@ -152,7 +148,7 @@ __global__ __launch_bounds__(512, 2) void fipa_bwd_weights_kernel(BwdStoredParam
     for (int ks = 0; ks < KS - KSH; ++ks) asm volatile("" : "+a"(zf[ks]));
 
     // per-lane LDS offsets: row li, 16-byte slot 2 ks + g (head-specific rows: XOR-ed with the row)
-    const int az = (li / C::ZROWS) * C::ZP + (li % C::ZROWS) * C::ZB + (C::ZROWS == 2 ? g ^ (li & 1) : g) * 16;
+    const int az = li * C::ZP + g * 16;
     int ah[4];
 #pragma unroll
     for (int x = 0; x < 4; ++x) ah[x] = li * 128 + ((2 * x + g) ^ ((li >> 1) & 7)) * 16;
@@ -287,7 +283,7 @@ struct AcCfg {
 };
 
 template <bool KV, int DZ, int HV, int ZBL, int WIN>
-__device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *smem, int logical)
+__device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *smem, int logical, int part = 0)
 {
     using C = AcCfg<KV, DZ, HV, ZBL, WIN>;
     constexpr int D = kDH + DZ, TS = 128 * HV;  // stationary rows of a tile
@@ -301,17 +297,21 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
     const int row_lo = (KV ? 0 : p.i0) + tile * TS;         // first stationary row
     const int nvalid = min(kvlen, p.i0 + p.nq);             // (KV: end of the queries of this range)
     // steps of 16 queries (whole blocks of 32), or of 32 keys
-    const int nstep = (KV ? max(0, (nvalid - p.i0 + 31) / 32) * 2 : (kvlen + 31) / 32);
+    const int all = (KV ? max(0, (nvalid - p.i0 + 31) / 32) * 2 : (kvlen + 31) / 32);
+    const int S = KV || logical < p.q_full ? 1 : p.q_S;     // (dQ^: parts of the tile along the keys)
+    const int step0 = part * all / S, nstep = (part + 1) * all / S - step0;
     if (row_lo >= kvlen || (KV && p.i0 > 0 && nstep == 0)) return;  // (rows past the chain are not read; a range without queries adds nothing)
 
     const size_t rows0 = (size_t)bh * p.Lp;
     f32x16 acch[C::NHB > 0 ? C::NHB : 1][HV], accz[C::ZBL][HV];
     float wsum[HV];
+    const size_t part_row = part > 0 ? ((size_t)(logical - p.q_full) * (S - 1) + part - 1) * TS : 0;
     auto outputs = [&](auto &&f) {  // f(pointer of the lane's row, accumulator) of every block
 #pragma unroll
         for (int hv = 0; hv < HV; ++hv) {
             const int row = row_lo + 32 * (HV * wave + hv) + li;
             const size_t r = rows0 + min(row, p.Lp - 1);
+            float *const dq = !KV && part > 0 ? p.q_parts + (part_row + 32 * (HV * wave + hv) + li) * bwd_query_part_row(DZ) : p.dQ + r * D;
             if constexpr (KV) {
                 if constexpr (C::HA)
 #pragma unroll
@@ -324,9 +324,9 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
             } else {
                 if constexpr (C::HA)
 #pragma unroll
-                    for (int nb = 0; nb < 2; ++nb) f(p.dQ + r * D + 32 * nb, acch[nb][hv], row);
+                    for (int nb = 0; nb < 2; ++nb) f(dq + 32 * nb, acch[nb][hv], row);
 #pragma unroll
-                for (int nb = 0; nb < C::ZBL; ++nb) f(p.dQ + r * D + kDH + C::Z0 + 32 * nb, accz[nb][hv], row);
+                for (int nb = 0; nb < C::ZBL; ++nb) f(dq + kDH + C::Z0 + 32 * nb, accz[nb][hv], row);
             }
         }
     };
@@ -387,7 +387,15 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
                 }
             }
         };
-        auto issue_all = [&](int n, unsigned stage) { static_for<C::NDMA>([&](auto K) { issue(K, min(n, nstep - 1), stage); }); };
+        // dQ^: the 16 groups of a tile's weights lie a power of two apart where the length is one, and every workgroup would
+        // read the same offset of all of them at a time: the walk over the keys starts elsewhere in every tile.
+        const int turn = KV ? 0 : (row_lo / TS * 5 + bh * 3) % nstep;
+        auto at = [&](int n) {  // n-th step of the walk (past the last one: the last one again)
+            if constexpr (KV) return min(n, nstep - 1);
+            const int x = turn + min(n, nstep - 1);
+            return step0 + (x >= nstep ? x - nstep : x);
+        };
+        auto issue_all = [&](int n, unsigned stage) { const int s = at(n); static_for<C::NDMA>([&](auto K) { issue(K, s, stage); }); };
 #pragma unroll
         for (int n = 0; n < C::NST - 1; ++n) issue_all(n, lds0 + n * C::STAGE);
 
@@ -453,7 +461,7 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
             wait_and_barrier<(C::NST - 2) * C::NDMA>();  // step n has landed; the stage of step n - 1 is free
             const char *st = smem + (n & 3) * C::STAGE;
             const unsigned next = lds0 + ((n + 3) & 3) * C::STAGE;
-            const int nn = min(n + 3, nstep - 1);
+            const int nn = at(n + 3);
 #pragma unroll
             for (int hv = 0; hv < HV; ++hv) w0[hv] = weights(st, 0, hv);
             static_for<C::NF>([&](auto J) {
@@ -503,19 +511,63 @@ __device__ __forceinline__ void accum_window(const BwdStoredParams &p, char *sme
         for (int hv = 0; hv < HV; ++hv) {
             const int row = row_lo + 32 * (HV * wave + hv) + li;
             const float tot = wsum[hv] + __shfl_xor(wsum[hv], 32);
-            if (g == 0 && row < row_end) sums[rows0 + row] = (add ? sums[rows0 + row] : 0.f) + tot;
+            float *const sum = !KV && part > 0 ? p.q_parts + (part_row + 32 * (HV * wave + hv) + li) * bwd_query_part_row(DZ) + D : sums + rows0 + row;
+            if (g == 0 && row < row_end) *sum = (add ? *sum : 0.f) + tot;
         }
+}
+
+template <int DZ>
+__global__ __launch_bounds__(256, 1) void fipa_bwd_query_kernel(BwdStoredParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    int logical, part;
+    if (bwd_unit(p.q_units, p.q_full, p.q_S, logical, part)) accum_window<false, DZ, 2, DZ / 32, 0>(p, smem, logical, part);
+}
+
+// Adds the parts of the tiles that were cut (see split_tiles) to what the first of them left, in their order: a thread per four columns.
+template <int DZ>
+__global__ __launch_bounds__(256) void fipa_bwd_merge_kernel(BwdStoredParams p, int k_rows, int q_rows)
+{
+    constexpr int D = kDH + DZ, KR = bwd_key_part_row(DZ), QR = bwd_query_part_row(DZ);
+    constexpr int KV4 = (KR - 4) / 4 + 1, QV4 = (QR - 4) / 4 + 1;  // pieces of a row, the last one its sum
+    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const bool key = t < (size_t)k_rows * KV4;
+    const size_t u = key ? t : t - (size_t)k_rows * KV4;
+    const int row = (int)(u / (key ? KV4 : QV4)), x = 4 * (int)(u % (key ? KV4 : QV4));
+    if (!key && row >= q_rows) return;
+    const int TS = key ? 128 : 256, S = key ? p.k_S : p.q_S, per = (p.Lp + TS - 1) / TS;  // tiles of a pair
+    const int local = row / TS, tile = (key ? p.k_full : p.q_full) + local, at = row % TS;
+    const int i = tile % per * TS + at;
+    if (i >= p.L) return;  // (all chains have L residues here)
+    const size_t r = (size_t)(tile / per) * p.Lp + i;
+    const float *src = (key ? p.parts : p.q_parts) + ((size_t)local * (S - 1) * TS + at) * (key ? KR : QR) + x;
+    const size_t step = (size_t)TS * (key ? KR : QR);
+    if (x == (key ? KR : QR) - 4) {
+        float *const dst = (key ? p.colsum : p.rowsum) + r;
+        float v = *dst;
+        for (int s = 0; s < S - 1; ++s) v += src[s * step];
+        *dst = v;
+        return;
+    }
+    float *const dst = !key ? p.dQ + r * D + x : x < kDH ? p.dKh + r * kDH + x : x < 2 * kDH ? p.dVh + r * kDH + x - kDH : p.dZ + r * DZ + x - 2 * kDH;
+    f32x4 v = *reinterpret_cast<const f32x4 *>(dst);
+    for (int s = 0; s < S - 1; ++s) {
+        const f32x4 w = *reinterpret_cast<const f32x4 *>(src + s * step);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) v[y] += w[y];
+    }
+    *reinterpret_cast<f32x4 *>(dst) = v;
 }
 
 // Both products of a range in one launch, the key side (whose workgroups take longer) first: with one workgroup per compute
 // unit and few rounds of them, the query side's workgroups fill what the last round of the key side leaves idle.
-// Two launches -> one: B = 2, L = 4096, r c_z = 256 820 -> 720 us; B = 2, L = 2048 230 -> 220 us; four chains of 2.7k to 7.1k
-// residues, r c_z = 512, 4.6 -> 4.4 ms.
+// Two launches -> one: four chains of 2.7k to 7.1k residues, r c_z = 512, 4.6 -> 4.4 ms.
 template <int DZ>
 __global__ __launch_bounds__(256, 1) void fipa_bwd_products_kernel(BwdStoredParams p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int NWIN = AcCfg<true, DZ, 2, 8, 0>::NWIN;
+    static_assert(NWIN == 2, "windows");
     // each XCD gets a contiguous run of tiles; the windows of a tile are neighbours in its launch order
     const int kv_xcd = (p.units + 7) / 8, q_xcd = (p.q_units + 7) / 8;
     const bool kv = (int)blockIdx.x < 8 * kv_xcd * NWIN;
@@ -525,13 +577,15 @@ __global__ __launch_bounds__(256, 1) void fipa_bwd_products_kernel(BwdStoredPara
     const int logical = (blk % 8) * per_xcd + slot / NWIN;
     if (slot / NWIN >= per_xcd || logical >= units) return;
     if (kv) {
-        if (NWIN == 1 || win == 0) accum_window<true, DZ, 2, 8, 0>(p, smem, logical);
-        else accum_window<true, DZ, 2, 8, NWIN - 1>(p, smem, logical);
+        if (win == 0) accum_window<true, DZ, 2, 8, 0>(p, smem, logical);
+        else accum_window<true, DZ, 2, 8, 1>(p, smem, logical);
     } else {
-        if (NWIN == 1 || win == 0) accum_window<false, DZ, 2, 8, 0>(p, smem, logical);
-        else accum_window<false, DZ, 2, 8, NWIN - 1>(p, smem, logical);
+        if (win == 0) accum_window<false, DZ, 2, 8, 0>(p, smem, logical);
+        else accum_window<false, DZ, 2, 8, 1>(p, smem, logical);
     }
 }
+
+constexpr int kCU = 256;
 
 template <class K>
 hipError_t launch_kernel(K kernel, LdsLimit &limit, int threads, int lds, int blocks, const BwdStoredParams &p, hipStream_t stream)
@@ -541,8 +595,6 @@ hipError_t launch_kernel(K kernel, LdsLimit &limit, int threads, int lds, int bl
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), lds, stream, p);
     return hipGetLastError();
 }
-
-constexpr int kCU = 256;
 
 template <int DZ>
 hipError_t launch_products(BwdStoredParams p, hipStream_t stream)
@@ -556,13 +608,50 @@ hipError_t launch_products(BwdStoredParams p, hipStream_t stream)
 }
 
 template <int DZ>
+hipError_t launch_query(BwdStoredParams p, hipStream_t stream)
+{
+    using C = AcCfg<false, DZ, 2, DZ / 32, 0>;
+    static LdsLimit limit;
+    p.q_units = p.q_full + (p.B * p.H * ((p.nq + 255) / 256) - p.q_full) * p.q_S;
+    const hipError_t e = launch_kernel(fipa_bwd_query_kernel<DZ>, limit, 256, C::LDS_BYTES, bwd_unit_blocks(p.q_units, p.q_full), p, stream);
+    if (e != hipSuccess || (p.k_S == 1 && p.q_S == 1)) return e;
+    const int k_rows = p.k_S > 1 ? (p.B * p.H * (p.Lp / 128) - p.k_full) * 128 : 0;
+    const int q_rows = p.q_S > 1 ? (p.B * p.H * ((p.Lp + 255) / 256) - p.q_full) * 256 : 0;
+    const size_t threads = (size_t)k_rows * (bwd_key_part_row(DZ) / 4) + (size_t)q_rows * (bwd_query_part_row(DZ) / 4);
+    hipLaunchKernelGGL(fipa_bwd_merge_kernel<DZ>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, p, k_rows, q_rows);
+    return hipGetLastError();
+}
+
+// Cuts the tiles of an incomplete last round (256 workgroups, one per compute unit) along the streamed side, where that makes the
+// launch shorter, all in us: steps of the streamed side (`step`), the start and the end of a workgroup (12), the launch that
+// adds the parts up (10) and their way through memory (three times at 4 TB/s).  One range of rows, all chains of the same length, and
+// no more parts than `room` bytes hold.  Training step / module step, not cut and cut: B = 2, L = 1500 493 / 442 us, module B = 2,
+// L = 2048 858 / 825 us; a line that cut B = 2, L = 1024 at r c_z = 128 as well: 320 / 339 us.
+void split_tiles(int tiles, int steps, float step, size_t part_bytes, size_t room, int &full, int &S)
+{
+    full = tiles / kCU * kCU;
+    S = 1;
+    const int rem = tiles - full;
+    float best = steps * step + 12.f - 5.f;
+    for (int s = 2; s <= 8 && rem > 0; ++s) {
+        if (steps / s < 8 || (size_t)rem * (s - 1) * part_bytes > room) break;
+        const float t = (float)((rem * s + kCU - 1) / kCU) * (steps * step / s + 12.f) + 10.f + rem * (s - 1) * (part_bytes * 3e-6f / 4.f);
+        if (t < best) {
+            best = t;
+            S = s;
+        }
+    }
+    if (S == 1) full = tiles;
+}
+
+template <int DZ>
 hipError_t launch_weights(BwdStoredParams p, hipStream_t stream)
 {
     static LdsLimit limit;
     const int tiles = p.B * p.H * ((p.Lp + WtCfg<DZ>::TK - 1) / WtCfg<DZ>::TK);
     // no sums across query blocks here, so a key tile's queries may be cut into runs; each run loads its keys again
-    // (about 10 us).  Runs of 64 blocks, shorter while they leave the chip less than three rounds.  Measured (runs of
-    // 16 / 32 / 64 / 128 blocks): B = 2, L = 4096, r c_z = 256: 674 / 614 / 589 / 676 us; L = 2048: 168 / 182 / 178 / 177 us.
+    // (about 10 us).  Runs of 64 blocks, shorter while they leave the chip less than three rounds.  Measured at r c_z = 256 (runs of
+    // 16 / 32 / 64 / 128 blocks): B = 2, L = 4096: 674 / 614 / 589 / 676 us; L = 2048: 168 / 182 / 178 / 177 us.
     const int qblocks = p.nq / 32;
     int run = 64;
     while (run > 16 && tiles * ((qblocks + run - 1) / run) < 3 * kCU) run /= 2;
@@ -581,9 +670,20 @@ hipError_t launch_bwd_stored_bf16(const BwdStoredParams &p0, int DZ, hipStream_t
         BwdStoredParams p = p0;
         p.i0 = i0;
         p.nq = p0.Lp - i0 < p0.nq_alloc ? p0.Lp - i0 : p0.nq_alloc;
-        hipError_t e = DZ == 256 ? launch_weights<256>(p, stream) : launch_weights<512>(p, stream);
+        p.k_full = p.B * p.H * (p.Lp / 128);
+        p.q_full = p.B * p.H * ((p.nq + 255) / 256);
+        p.k_S = p.q_S = 1;
+        if (bwd_keys_fused(DZ) && !p.deal && p.nq == p.Lp) {
+            const int k_tiles = p.k_full, q_tiles = p.q_full, steps = (p.L + 31) / 32;
+            const size_t k_bytes = (size_t)128 * bwd_key_part_row(DZ) * 4, q_bytes = (size_t)256 * bwd_query_part_row(DZ) * 4;
+            split_tiles(k_tiles, steps, DZ == 256 ? 2.1f : 1.25f, k_bytes, p.parts_bytes, p.k_full, p.k_S);
+            const size_t used = (size_t)(k_tiles - p.k_full) * (p.k_S - 1) * k_bytes;
+            p.q_parts = p.parts + used / 4;
+            split_tiles(q_tiles, steps, DZ == 256 ? 1.05f : 0.65f, q_bytes, p.parts_bytes - used, p.q_full, p.q_S);
+        }
+        hipError_t e = bwd_keys_fused(DZ) ? launch_bwd_keys_bf16(p, DZ, stream) : launch_weights<512>(p, stream);
         if (e != hipSuccess) return e;
-        e = DZ == 256 ? launch_products<256>(p, stream) : launch_products<512>(p, stream);
+        e = DZ == 128 ? launch_query<128>(p, stream) : DZ == 256 ? launch_query<256>(p, stream) : launch_products<512>(p, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

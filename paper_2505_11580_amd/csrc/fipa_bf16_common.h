@@ -413,7 +413,32 @@ struct BwdStoredParams {
     int Lk;               // Lp rounded up to 256: keys per group of weights
     int nq_alloc, i0, nq; // query rows the buffers hold; this range
     int units, q_units, nseg, seg_blocks;
+    // Tiles from k_full (keys) and q_full (queries) on are cut into k_S, q_S parts along the streamed side, whose first writes the
+    // tile's place above and whose others write `parts` (see split_tiles); k_S = q_S = 1: none.
+    float *parts, *q_parts;
+    size_t parts_bytes;   // what there is
+    int k_full, k_S, q_full, q_S;
 };
+
+// Floats of a row of a part: dK^ and dV^ head | pair columns | sum, padded; dQ^ | sum, padded.
+__host__ __device__ constexpr int bwd_key_part_row(int DZ) { return 2 * kDH + DZ + 4; }
+__host__ __device__ constexpr int bwd_query_part_row(int DZ) { return kDH + DZ + 4; }
+
+// Work of a workgroup: tiles [0, full) whole, then the parts of the others (S each); a contiguous run of either per XCD.
+__device__ __forceinline__ bool bwd_unit(int units, int full, int S, int &logical, int &part)
+{
+    const int fx = (full + 7) / 8, wg = blockIdx.x;
+    part = 0;
+    if (wg < 8 * fx) {
+        logical = wg % 8 * fx + wg / 8;
+        return logical < full;
+    }
+    const int n = units - full, nx = (n + 7) / 8, u = wg - 8 * fx, lin = u % 8 * nx + u / 8;
+    logical = full + lin / S;
+    part = lin % S;
+    return lin < n;
+}
+inline int bwd_unit_blocks(int units, int full) { return ((full + 7) / 8 + (units - full + 7) / 8) * 8; }
 
 struct BwdPackParams {
     const float *d_o, *d_o_pts, *d_o_pair, *rot, *Ohat, *lse2;
@@ -450,6 +475,9 @@ struct BwdUnpackParams {
 
 hipError_t launch_bwd_bf16(const BwdParams &p, int DZ, int mode, hipStream_t stream);
 hipError_t launch_bwd_stored_bf16(const BwdStoredParams &p, int DZ, hipStream_t stream);
+// The widths whose key side forms the weights and uses them in one kernel (fipa_bf16_bwd_keys.hip): only dS' is stored.
+inline bool bwd_keys_fused(int DZ) { return DZ == 128 || DZ == 256; }
+hipError_t launch_bwd_keys_bf16(BwdStoredParams p, int DZ, hipStream_t stream);
 hipError_t launch_bwd_pack_bf16(const BwdPackParams &p, hipStream_t stream);
 hipError_t launch_bwd_unpack_bf16(const BwdUnpackParams &p, hipStream_t stream);
 

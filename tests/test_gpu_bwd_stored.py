@@ -1,8 +1,9 @@
-"""GPU parity of fipa_backward where its weights are kept in memory (r c_z = 256 and 512), at the edges of its tiles
+"""GPU parity of fipa_backward where its weights are kept in memory (r c_z = 128, 256 and 512), at the edges of its tiles
 (32 residues per block, 256 per tile, 128 per padded row group) and with more residues than the weights of one range of
 queries (4096), against the CPU oracle (2e-2, the tolerance of every bf16 gradient test)."""
 import pytest
 
+from paper_2505_11580_amd import binding
 from paper_2505_11580_amd import workloads as wl
 from tests.test_gpu_backward import check_backward
 
@@ -22,3 +23,45 @@ def test_backward_stored_weights(kw):
 def test_backward_two_query_ranges(kw):
     inp = wl.make_inputs(4, **dict(dict(B=1, H=1, cz=128), **kw))
     check_backward(inp, "bwd two ranges %s" % kw, samples=wl.select_rows(inp, 96))
+
+
+@pytest.mark.parametrize("kw", [
+    dict(L=1, H=1), dict(L=32), dict(L=33, cz=64, r=2), dict(L=127), dict(L=129, cz=32, r=4), dict(L=257, cz=64, r=2, H=1),
+    dict(L=400, B=3, H=3, varlen=True, min_len=1)])
+def test_backward_width128(kw):
+    kw = dict(dict(B=1, H=2, cz=128, r=1, trans_scale=0.3), **kw)
+    check_backward(wl.make_inputs(4, **kw), "bwd width 128 %s" % kw)
+
+
+@pytest.mark.parametrize("kw", [dict(L=1000, H=3, r=1), dict(L=1000, H=3, r=2), dict(L=577, H=5, cz=64, r=2), dict(L=1100, H=2, B=2, r=2)])
+def test_backward_tiles_in_parts(kw):
+    # few tiles of many blocks: cut along the streamed side, the parts added up behind the kernels
+    inp = wl.make_inputs(4, **dict(dict(B=1, cz=128, trans_scale=0.3), **kw))
+    check_backward(inp, "bwd parts %s" % kw, samples=wl.select_rows(inp, 96))
+
+
+@pytest.mark.parametrize("kw", [dict(L=300, r=1), dict(L=520, B=2, cz=64, r=2, varlen=True, min_len=100), dict(L=1000, H=1, r=1)])
+def test_backward_width128_in_the_least_workspace(kw):
+    import torch
+    inp = wl.make_inputs(4, **dict(dict(B=1, H=2, cz=128, trans_scale=0.3), **kw))
+    desc, dev = binding.upload(inp)
+    out, full = binding.alloc_outputs(desc), binding.workspace_bytes(desc)[1]
+    # (what it was before the weights were stored: dK^ and dV^ of the full width)
+    Lp, BH = -(-desc.L // 128) * 128, desc.B * desc.H
+    least = full - BH * min(Lp, 4096) * (-(-Lp // 256) * 256) * 4 + BH * Lp * 128 * 4
+    binding.forward(desc, dev, out)
+    res = []
+    for n_bytes in (full, least):
+        grads = binding.alloc_grads(desc)
+        buf = torch.full((n_bytes + 4096,), 0xFF, dtype=torch.uint8, device="cuda:0")
+        grads["workspace"] = buf[:n_bytes]
+        binding.backward(desc, dev, out, grads)
+        torch.cuda.synchronize()
+        assert bool((buf[n_bytes:] == 0xFF).all())
+        res.append({n: t.double() for n, t in grads.items() if n != "workspace"})
+    for n, w in res[0].items():  # (key-side sums range by range, in another order: one bf16 rounding of the largest gradient)
+        assert float((res[1][n] - w).abs().max()) <= 2.0 ** -8 * float(w.abs().max()), n
+    grads["workspace"] = buf[:least - 256]
+    with pytest.raises(binding.FipaError) as e:
+        binding.backward(desc, dev, out, grads)
+    assert e.value.code == binding.FIPA_ERR_WORKSPACE
