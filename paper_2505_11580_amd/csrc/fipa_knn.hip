@@ -3,13 +3,17 @@
 // distances and distogram bins -- [L, k] instead of the [L, L] distogram.  The paper gives one
 // paragraph and no formula; the readings are stated in include/fipa.h.
 //
-// One wave per query residue or four of them.  The wave keeps its 64 best candidates so far as a sorted list, one
-// entry per lane (lane s holds the s-th nearest), scans the chain 64 residues at a time, and
+// One wave per query residue or two of them.  The wave keeps its 64 best candidates so far as a sorted list, one
+// entry per lane (lane s holds the s-th nearest), scans blocks of 64 residues, and
 // inserts the few candidates that beat the current k-th entry one by one (a shift by one lane
-// from the insertion point on); the scan starts at the residue's own block, which is ranked as a whole, and moves outwards.
+// from the insertion point on).  It starts with the 64 residues around its own, which are ranked as a whole (in a chain the neighbours
+// along the sequence are near in space, so the list is nearly final then), and visits the blocks whose
+// bounding box is no farther than the k-th entry.  The boxes of the whole chain are formed once per workgroup.
 // Order is by (squared distance, index), a strict total order, so the result does not depend on
 // the order of the scan.  Every decision is taken in float32 on
-// ((dx*dx + dy*dy) + dz*dz) with one rounding per operation (no fused multiply-add).
+// ((dx*dx + dy*dy) + dz*dz) with one rounding per operation (no fused multiply-add).  The distance to a box is formed by
+// the same operations in the same order, each of which is monotonic, so it is no larger than the computed distance of any residue
+// in the box: a block that is left out holds no residue that would enter the list.
 #include "fipa_internal.h"
 
 #include <climits>
@@ -24,25 +28,89 @@ namespace {
 
 __device__ __forceinline__ bool before(float ad, int aj, float bd, int bj) { return ad < bd || (ad == bd && aj < bj); }
 
-// One wave per R residues of a batch element (R = 4 where there are enough residues for it: the candidates'
-// coordinates are then loaded, and the loop run, once per four residues).
-// Four chains of up to 8192 residues, k = 20: 220 us with one residue per wave, every candidate of its own block inserted by
-// itself and validity and self tested per candidate (28 instructions per residue and block of candidates) -> 175 us.
-template <int R>
-__global__ __launch_bounds__(256) void fipa_knn_distogram_kernel(const float *__restrict__ trans,
+// The value of the lane before (0 in lane 0).
+__device__ __forceinline__ int lane_above(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, false); }  // wave_shr:1
+
+constexpr int kMaxBoxes = 1024;  // 24 KB of LDS; longer chains than 65536 residues: boxes of two, four, .. blocks
+
+// kWaves waves of R residues each (R = 2 where there are enough residues for it: the candidates'
+// coordinates are then loaded, and the loop run, once per two residues).  In a chain most blocks are far from a residue (3.8 A per
+// step: a block of 64 spans some 30 A, the 20 nearest lie within 10 A): of the 112 blocks of 7146 residues a wave visits five.
+// Four chains of up to 8192 residues (60 % valid), k = 20: every block visited, outwards from the residue's own, 175 us; boxes 70 us
+// (R = 4, 8 waves 75; R = 1 95).  What is left is the ranking of the window (a quarter) and waves with many near blocks.
+template <int R, int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void fipa_knn_distogram_kernel(const float *__restrict__ trans,
                                                                  const uint8_t *__restrict__ mask, int B, int L, int k,
                                                                  int n_bins, float d_min, float w,
                                                                  int *__restrict__ nbr_idx, float *__restrict__ nbr_d2,
                                                                  int *__restrict__ nbr_bin)
 {
     const int lane = threadIdx.x & 63;
-    // Workgroup g of every element side by side, the elements in a rotating order: chains of different lengths (a masked batch)
-    // then leave every compute unit about the same number of residues.
-    const int g = blockIdx.x / B, b = (blockIdx.x % B + (g >> 6)) % B;
-    const int i0 = (4 * g + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * R;  // uniform over the wave
-    if (i0 >= L) return;
+    // Workgroup g of every element side by side, the elements in an order that turns every 256 workgroups: chains of different
+    // lengths (a masked batch) then leave every compute unit about the same number of residues.
+    const int g = blockIdx.x / B, b = (blockIdx.x % B + (int)(((long long)g * B) >> 8)) % B;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i0 = (kWaves * g + wave) * R;  // uniform over the wave
     const float *t = trans + (size_t)b * L * 3;
     const uint8_t *m = mask ? mask + (size_t)b * L : nullptr;
+    __shared__ float lo[3][kMaxBoxes], hi[3][kMaxBoxes];
+    const int nblk = (L + 63) / 64;
+    int shift = 0;  // a box holds 2^shift blocks
+    while (((nblk - 1) >> shift) + 1 > kMaxBoxes) ++shift;
+    const int nbox = ((nblk - 1) >> shift) + 1;
+    {
+        const int i = kWaves * R * g + (int)threadIdx.x;
+        const bool on = threadIdx.x < kWaves * R && i < L && (!m || m[i] != 0);
+        if (!__syncthreads_or(on)) {  // nothing but padding: empty lists
+            for (int x = threadIdx.x; x < kWaves * R * k; x += 64 * kWaves) {
+                if (kWaves * R * g + x / k >= L) break;
+                const size_t at = ((size_t)b * L + kWaves * R * g) * k + x;
+                nbr_idx[at] = -1;
+                nbr_d2[at] = INFINITY;
+                nbr_bin[at] = -1;
+            }
+            return;
+        }
+    }
+    if (nblk > 3) {  // (else every block is visited)
+        // eight threads per box, 12 bytes of a residue at a time (a box per wave, reduced over its 64 lanes, takes 800 vector
+        // instructions of the 3100 of a wave at 8192 residues)
+        struct Xyz {
+            float v[3];
+        };
+        const int sub = 8 << shift;
+        for (int c0 = 64 * wave; c0 < 8 * nbox; c0 += 64 * kWaves) {
+            const int c = c0 + lane;
+            float a[3] = {INFINITY, INFINITY, INFINITY}, z[3] = {-INFINITY, -INFINITY, -INFINITY};
+            for (int j0 = 0; j0 < sub; j0 += 8)
+#pragma unroll
+                for (int y = 0; y < 8; ++y) {
+                    const long long j = (long long)c * sub + j0 + y;
+                    const int jc = (int)min(j, (long long)L - 1);
+                    const Xyz p = *reinterpret_cast<const Xyz *>(t + 3 * (size_t)jc);
+                    const bool ok = j < L && (!m || m[jc] != 0);
+#pragma unroll
+                    for (int x = 0; x < 3; ++x) {
+                        a[x] = fminf(a[x], ok ? p.v[x] : INFINITY);
+                        z[x] = fmaxf(z[x], ok ? p.v[x] : -INFINITY);
+                    }
+                }
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+#pragma unroll
+                for (int o = 1; o < 8; o <<= 1) {
+                    a[x] = fminf(a[x], __shfl_xor(a[x], o));
+                    z[x] = fmaxf(z[x], __shfl_xor(z[x], o));
+                }
+                if ((lane & 7) == 0 && c < 8 * nbox) {
+                    lo[x][c >> 3] = a[x];
+                    hi[x][c >> 3] = z[x];
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (i0 >= L) return;
 
     float best_d[R];  // lane s: the s-th nearest so far
     int best_j[R];
@@ -61,17 +129,13 @@ __global__ __launch_bounds__(256) void fipa_knn_distogram_kernel(const float *__
         thr_j[q] = INT_MAX;
     }
     if (any) {
-        // The blocks of 64 candidates are visited outwards from the residues' own: in a chain the
-        // neighbours along the sequence are near in space, so the list fills with near residues at
-        // once and few later candidates beat its k-th entry (in index order every residue before i
-        // arrives nearer than the one before it and is inserted, one at a time).
-        const int nblk = (L + 63) / 64, own = i0 / 64;
+        const int w0 = max(min(i0 + R / 2 - 32, L - 64), 0);  // the window: residues w0 .. w0 + 63 (those there are)
         struct Cand {
             float x, y, z;  // x: not a number where there is no candidate, so that no comparison holds
         };
-        auto load = [&](int j0) {
+        auto load = [&](int j0, bool window) {  // (the blocks: without the residues of the window)
             const int j = j0 + lane, jc = min(j, L - 1);
-            const bool ok = j < L && (!m || m[jc] != 0);
+            const bool ok = j < L && (!m || m[jc] != 0) && (window || (unsigned)(j - w0) >= 64u);
             Cand c = {t[3 * jc], t[3 * jc + 1], t[3 * jc + 2]};
             c.x = ok ? c.x : __builtin_nanf("");
             return c;
@@ -80,22 +144,24 @@ __global__ __launch_bounds__(256) void fipa_knn_distogram_kernel(const float *__
             const float dx = __fsub_rn(c.x, xi[q]), dy = __fsub_rn(c.y, yi[q]), dz = __fsub_rn(c.z, zi[q]);
             return __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
         };
-        // The residues' own block fills the empty lists: every candidate counts those before it and goes to that place.
-        // (i0 .. i0 + R - 1 lie in one block: R divides 64.)
+        // The window fills the empty lists: every candidate counts those before it and goes to that place.
         {
-            const Cand c = load(64 * own);
-            const int j = 64 * own + lane;
+            const Cand c = load(w0, true);
+            const int j = w0 + lane;
 #pragma unroll
             for (int q = 0; q < R; ++q) {
                 const float d2 = dist(c, q);
                 const bool cand = d2 <= thr_d[q] && j != i0 + q;
-                const unsigned long long cands = __ballot(cand), below = (1ull << lane) - 1ull;
-                int rank = cand ? 0 : __popcll(cands) + __popcll(~cands & below);
-                for (unsigned long long rest = cands; rest; rest &= rest - 1) {
-                    const int l = __ffsll((long long)rest) - 1;
-                    const float dl = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, d2), l));
-                    rank += cand && (dl < d2 || (dl == d2 && l < lane)) ? 1 : 0;
-                }
+                // (lanes without a candidate come behind all of them; distances are not negative, so their bits order them)
+                const unsigned key = cand ? __builtin_bit_cast(unsigned, d2) : 0x7F800001u + lane;
+                int rank = 0;
+#pragma unroll
+                for (int l = 0; l < 64; ++l) rank += (unsigned)__builtin_amdgcn_readlane(key, l) < key ? 1 : 0;
+                int sum = rank;
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+                if (sum != 63 * 32)  // equal distances: by index
+                    for (int l = 0; l < 64; ++l) rank += (unsigned)__builtin_amdgcn_readlane(key, l) == key && l < lane ? 1 : 0;
                 best_d[q] = __builtin_bit_cast(float, __builtin_amdgcn_ds_permute(4 * rank, __builtin_bit_cast(int, cand ? d2 : INFINITY)));
                 best_j[q] = __builtin_amdgcn_ds_permute(4 * rank, cand ? j : INT_MAX);
                 if (thr_d[q] >= 0.f) {
@@ -104,68 +170,89 @@ __global__ __launch_bounds__(256) void fipa_knn_distogram_kernel(const float *__
                 }
             }
         }
-        int up = own + 1, down = own - 1;
-        auto next = [&](int step) {  // alternately above and below while both sides have blocks left
-            const bool take_up = up < nblk && (down < 0 || (step & 1) == 0);
-            return 64 * (take_up ? up++ : down--);
-        };
-        int j0 = nblk > 1 ? next(0) : 0;
-        Cand c = load(j0);
-        for (int step = 1; step < nblk; ++step) {
-            const Cand now = c;
-            const int jnow = j0 + lane;
-            if (step + 1 < nblk) {
-                j0 = next(step);
-                c = load(j0);
-            }
+        auto scan = [&](const Cand &c, int j0) {  // block j0 .. j0 + 63
             float d2[R];
             unsigned long long todo[R], some = 0ull;
 #pragma unroll
             for (int q = 0; q < R; ++q) {
-                d2[q] = dist(now, q);
+                d2[q] = dist(c, q);
                 todo[q] = __ballot(d2[q] <= thr_d[q]);  // (candidates at the threshold itself are decided by their index)
                 some |= todo[q];
             }
-            if (some == 0ull) continue;
+            if (some == 0ull) return;
 #pragma unroll
             for (int q = 0; q < R; ++q)
                 while (todo[q]) {
                     const int l = __ffsll((long long)todo[q]) - 1;
                     todo[q] &= todo[q] - 1;
                     const float nd = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, d2[q]), l));
-                    const int nj = __builtin_amdgcn_readlane(jnow, l);
+                    const int nj = j0 + l;
                     if (!before(nd, nj, thr_d[q], thr_j[q])) continue;  // (also: the threshold has moved since the ballot)
                     // insert: the entries behind the new one move one lane up
                     const int behind = before(nd, nj, best_d[q], best_j[q]) ? 1 : 0;
-                    const float prev_d = __shfl_up(best_d[q], 1);
-                    const int prev_j = __shfl_up(best_j[q], 1);
-                    const int up_behind = __shfl_up(behind, 1);  // (every lane takes part in the exchange)
-                    const int prev_behind = lane > 0 ? up_behind : 0;
-                    if (behind) {
-                        best_d[q] = prev_behind ? prev_d : nd;
-                        best_j[q] = prev_behind ? prev_j : nj;
-                    }
+                    const int prev_d = lane_above(__builtin_bit_cast(int, best_d[q])), prev_j = lane_above(best_j[q]);
+                    const int prev_behind = lane_above(behind);  // (lane 0: 0)
+                    best_d[q] = behind ? (prev_behind ? __builtin_bit_cast(float, prev_d) : nd) : best_d[q];
+                    best_j[q] = behind ? (prev_behind ? prev_j : nj) : best_j[q];
                     thr_d[q] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, best_d[q]), k - 1));
                     thr_j[q] = __builtin_amdgcn_readlane(best_j[q], k - 1);
                 }
+        };
+        // (the coordinates of a block are requested before the one before it is looked at)
+        Cand c = {};
+        int j0 = -1;  // requested and not yet looked at
+        auto visit = [&](int blk) {
+            const Cand now = c;
+            const int jnow = j0;
+            c = load(j0 = 64 * blk, false);
+            if (jnow >= 0) scan(now, jnow);
+        };
+        if (nblk <= 3) {
+            for (int blk = 0; blk < (nblk > 1 ? nblk : 0); ++blk) visit(blk);  // (one block: the window is all there is)
+        } else {
+            for (int n0 = 0; n0 < nbox; n0 += 64) {
+                const int n = min(n0 + lane, nbox - 1);
+                float bl[3], bh[3];
+#pragma unroll
+                for (int x = 0; x < 3; ++x) {
+                    bl[x] = lo[x][n];
+                    bh[x] = hi[x][n];
+                }
+                bool near = false;
+#pragma unroll
+                for (int q = 0; q < R; ++q) {
+                    const float dx = fmaxf(fmaxf(__fsub_rn(bl[0], xi[q]), __fsub_rn(xi[q], bh[0])), 0.f);
+                    const float dy = fmaxf(fmaxf(__fsub_rn(bl[1], yi[q]), __fsub_rn(yi[q], bh[1])), 0.f);
+                    const float dz = fmaxf(fmaxf(__fsub_rn(bl[2], zi[q]), __fsub_rn(zi[q], bh[2])), 0.f);
+                    near |= __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz)) <= thr_d[q];
+                }
+                unsigned long long todo = __ballot(near && n0 + lane < nbox);
+                while (todo) {
+                    const int box = n0 + __ffsll((long long)todo) - 1;
+                    todo &= todo - 1;
+                    const int last = min((box + 1) << shift, nblk);
+                    for (int blk = box << shift; blk < last; ++blk) visit(blk);
+                }
+            }
         }
+        if (j0 >= 0) scan(c, j0);
+    }
+    int bin[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) bin[q] = 0;
+    for (int e = 0; e < n_bins - 1; ++e) {
+        const float edge = __fadd_rn(d_min, __fmul_rn((float)e, w)), edge2 = __fmul_rn(edge, edge);
+#pragma unroll
+        for (int q = 0; q < R; ++q) bin[q] += edge2 <= best_d[q] ? 1 : 0;
     }
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         if (i0 + q >= L || lane >= k) continue;
         const bool have = best_j[q] != INT_MAX;
-        int bin = -1;
-        if (have) {
-            bin = 0;
-            for (int e = 0; e < n_bins - 1; ++e) {
-                const float edge = __fadd_rn(d_min, __fmul_rn((float)e, w));
-                bin += __fmul_rn(edge, edge) <= best_d[q] ? 1 : 0;
-            }
-        }
         const size_t at = ((size_t)b * L + i0 + q) * k + lane;
         nbr_idx[at] = have ? best_j[q] : -1;
         nbr_d2[at] = have ? best_d[q] : INFINITY;
-        nbr_bin[at] = bin;
+        nbr_bin[at] = have ? bin[q] : -1;
     }
 }
 
@@ -184,10 +271,13 @@ extern "C" int fipa_knn_distogram(int32_t B, int32_t L, int32_t k, int32_t n_bin
     for (const void *ptr : al)
         if ((reinterpret_cast<uintptr_t>(ptr) & 3u) != 0) return FIPA_ERR_ALIGNMENT;
     const float w = (d_max - d_min) / (float)(n_bins - 1);
-    // four residues per wave once that leaves four waves per SIMD
-    const int R = (long long)B * ((L + 3) / 4) >= 4096 ? 4 : 1;
-    const dim3 grid((unsigned)(B * ((L + 4 * R - 1) / (4 * R))));
-    hipLaunchKernelGGL(R == 4 ? fipa::fipa_knn_distogram_kernel<4> : fipa::fipa_knn_distogram_kernel<1>, grid, dim3(256), 0,
-                       static_cast<hipStream_t>(hip_stream), trans, mask, B, L, k, n_bins, d_min, w, nbr_idx, nbr_d2, nbr_bin);
+    const auto launch = [&](auto kernel, int per_wg, int threads) {
+        const dim3 grid((unsigned)(B * ((L + per_wg - 1) / per_wg)));
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, static_cast<hipStream_t>(hip_stream), trans, mask, B, L, k, n_bins, d_min, w, nbr_idx,
+                           nbr_d2, nbr_bin);
+    };
+    // two residues per wave once that leaves eight waves per SIMD
+    if ((long long)B * L >= 16384) launch(fipa::fipa_knn_distogram_kernel<2, 16>, 32, 1024);
+    else launch(fipa::fipa_knn_distogram_kernel<1, 8>, 8, 512);
     return hipGetLastError() == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
 }

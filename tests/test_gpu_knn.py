@@ -65,3 +65,39 @@ def test_workload3_geometry_full_size():
     # four ragged chains of up to 8192 residues (the long-chain workload's frames), every row compared
     inp = wl.make_inputs(3)
     check(inp["trans"], inp["mask"], 20, 16, 2.0, 22.0, "knn workload 3 (B=4, L=8192, k=20)", time_it=True)
+
+
+@pytest.mark.parametrize("L,k,kind", [(192, 20, "walk"), (193, 20, "walk"), (257, 64, "clusters"), (1025, 3, "clusters"), (700, 20, "point"),
+                                      (2100, 5, "lattice")])
+def test_blocks_left_out_by_their_boxes(L, k, kind):
+    # from four blocks of 64 on a block is visited only where its bounding box is near enough: neighbours far along the chain,
+    # fewer candidates around a residue than it wants, equal distances on the boxes' faces
+    rng = np.random.default_rng(L)
+    if kind == "walk":
+        t = 3.8 * rng.standard_normal((2, L, 3)).cumsum(axis=1) / 3 ** 0.5
+    elif kind == "clusters":  # every residue's neighbours are spread over the chain
+        t = 50.0 * rng.integers(0, 4, size=(2, L, 1)) + rng.standard_normal((2, L, 3))
+    elif kind == "point":
+        t = np.zeros((2, L, 3))
+    else:
+        t = rng.integers(-4, 5, size=(2, L, 3))
+    mask = (rng.random((2, L)) > 0.5).astype(np.uint8)
+    mask[1, : L - 70] = 0
+    for m in (None, mask):
+        check(t.astype(np.float32), m, k, 16, 2.0, 22.0, "knn boxes %d %s" % (L, kind))
+
+
+def test_boxes_of_several_blocks():
+    # more than 65536 residues: a box holds more than one block; sampled rows
+    L, k = 70001, 20
+    rng = np.random.default_rng(3)
+    t = (3.8 * rng.standard_normal((1, L, 3)).cumsum(axis=1) / 3 ** 0.5).astype(np.float32)
+    idx, d2, bins, _ = run_gpu(t, None, k, 16, 2.0, 22.0)
+    e2 = knn_ref.bin_edges_squared(16, 2.0, 22.0)
+    for i in [0, 63, 64, 32767, L - 65, L - 1] + list(rng.integers(0, L, size=20)):
+        d = t[0] - t[0, i]
+        dist = (d[:, 0] * d[:, 0] + d[:, 1] * d[:, 1]) + d[:, 2] * d[:, 2]
+        js = np.delete(np.arange(L), i)
+        js = js[np.lexsort((js, dist[js]))[:k]]
+        assert np.array_equal(idx[0, i], js) and np.array_equal(d2[0, i], dist[js]), i
+        assert np.array_equal(bins[0, i], np.searchsorted(e2, dist[js], side="right")), i
