@@ -76,8 +76,8 @@ __global__ __launch_bounds__(256) void fipa_factor_project_kernel(const int *__r
 // The same with the tables of 32 columns (64 bytes per row) in LDS, where a workgroup then adds up many residues: the rows of
 // a residue come out of LDS instead of L2.  1024 threads, four per residue; the LDS rows of the next 256 residues are looked up while the
 // previous ones are added (one barrier per 256 residues); an empty slot takes a row of zeros.  Same sums in the same order.
-// 32768 residues, 20 slots, 81 rows per slot, 512 columns: 99 us from L2, 72 us here (bound by the vector unit: two
-// instructions per value).  Used where every workgroup has at least kFpRows residues to add for the table that it loads
+// 32768 residues, 20 slots, 81 rows per slot, 512 columns: 99 us from L2, 59 us here (bound by the vector unit, two
+// instructions per value, and by the loading of the table; 72 us while a thread looked up every slot by divisions).  Used where every workgroup has at least kFpRows residues to add for the table that it loads
 // and the table fits.
 constexpr int kFpThreads = 1024, kFpPass = kFpThreads / 4, kFpRows = 1024;
 inline size_t factor_lds_bytes(int k, int n_bins, int n_pos)
@@ -107,22 +107,28 @@ __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(con
         }
         *reinterpret_cast<uint4 *>(fp_smem + 16 * (size_t)x) = v;
     }
-    // rows (bin, position) of every slot of the pass that starts at residue r0: codes[buf][slot][residue]
+    // rows (bin, position) of every slot of the pass that starts at residue r0: codes[buf][slot][residue].  The thread's own residue, every
+    // fourth slot; whether any residue of the wave has a neighbour.
+    const int rr = tid >> 2, turn = kFpPass % L;
+    int i_next = (first + rr) % L;  // place in the chain of the residue that is looked up next
     auto look_up = [&](int r0, int buf) {
         unsigned *dst = codes + buf * kFpPass * k;
-        for (int x = tid; x < kFpPass * k; x += kFpThreads) {
-            const int rr = x / k, s = x - rr * k, res = min(r0 + rr, rows - 1);
-            const int j = nbr_idx[(size_t)res * k + s], bn = nbr_bin[(size_t)res * k + s];
+        const size_t at = (size_t)min(r0 + rr, rows - 1) * k;
+        const int i = r0 + rr < rows ? i_next : L - 1;
+        bool any = false;
+        for (int s = part; s < k; s += 4) {
+            const int j = nbr_idx[at + s], bn = nbr_bin[at + s];
             unsigned bin_row = nrow, pos_row = nrow;  // zeros
             if (j >= 0 && j < L) {
+                any = true;
                 bin_row = s * per + min(max(bn, 0), n_bins - 1);
-                if (n_pos > 0) {
-                    const int i = res % L;
-                    pos_row = s * per + n_bins + (pos_mode == 0 ? min(j, n_pos - 1) : min(max(j - i, -half), half) + half);
-                }
+                if (n_pos > 0) pos_row = s * per + n_bins + (pos_mode == 0 ? min(j, n_pos - 1) : min(max(j - i, -half), half) + half);
             }
             dst[s * kFpPass + rr] = bin_row | (pos_row << 16);
         }
+        i_next += turn;
+        if (i_next >= L) i_next -= L;
+        return __any(any) != 0;
     };
     float b8[8];
 #pragma unroll
@@ -136,19 +142,21 @@ __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(con
             acc[2 * q + 1] += __uint_as_float(w[q] & 0xffff0000u);
         }
     };
-    if (first < last) look_up(first, 0);
+    bool some = first < last && look_up(first, 0);
     int buf = 0;
     for (int r0 = first; r0 < last; r0 += kFpPass, buf ^= 1) {
         __syncthreads();  // this pass's rows are there, the pass before is done with the other buffer
-        if (r0 + kFpPass < last) look_up(r0 + kFpPass, buf ^ 1);
-        const int res = r0 + (tid >> 2);
+        const bool here = some;  // (a wave looks up the residues that it adds)
+        if (r0 + kFpPass < last) some = look_up(r0 + kFpPass, buf ^ 1);
+        const int res = r0 + rr;
         if (res >= last || col >= n_out) continue;
-        const unsigned *src = codes + buf * kFpPass * k + (tid >> 2);
+        const unsigned *src = codes + buf * kFpPass * k + rr;
         float acc[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[q] = b8[q];
+        const int slots = here ? k : 0;
 #pragma unroll 4
-        for (int s = 0; s < k; ++s) {
+        for (int s = 0; s < slots; ++s) {
             const unsigned c = src[s * kFpPass];
             add(acc, fp_smem + 64 * (c & 0xFFFFu) + 16 * part);
             add(acc, fp_smem + 64 * (c >> 16) + 16 * part);
@@ -173,21 +181,28 @@ __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(con
 //
 // One workgroup per (slot, 64 output columns), eight waves, each of which takes every eighth tile of 32
 // residues with all rows of the tables: nothing is shared between waves until their sums are added at the
-// end, so there is no barrier in the loop, and two waves per SIMD cover each other.  A tile's d_z rows,
-// indices, bins and mask arrive by direct loads three tiles ahead; d_z is read with the transposing LDS
-// read, and the one-hot operand is formed in registers: a lane owns a table row and compares it with the
-// 16-bit codes of its eight residues (three packed instructions per two residues).
-// 32768 residues (half of them valid), 20 slots, 82 rows, 512 columns: 555 us with four waves that shared each tile and marked
-// a one-hot tile in LDS (one barrier per tile, the mask on the way of every load) -> 131 us.
+// end, so there is no barrier in the loop, and two waves per SIMD cover each other.  A tile's d_z rows
+// arrive by direct loads two tiles ahead, its indices, bins and mask one tile earlier; d_z is read with the transposing LDS
+// read.  The one-hot operand is a tile of the wave in LDS, [table row][residue], read as it stands: a tile's residues set their
+// ones and take them back behind it.
+// 32768 residues (60 % of them valid), 20 slots, 82 rows, 512 columns: 555 us with four waves that shared each tile and its one-hot tile
+// (one barrier per tile, the mask on the way of every load) -> 131 us with the operand formed by comparing 16-bit codes in
+// registers (16 vector instructions per operand) -> 103 us, of which 36 go with the loads of d_z (every slot streams it again) and 25
+// with the matrix instructions.  A bit per residue and row, set with LDS or, and a table of
+// the 256 possible operands: 165 us (many residues share a row, and the or's on one address run one after the other).
 // rows = n_bins + n_pos + 1 (the last one collects the bias gradient, in slot 0's workgroups).
-constexpr int kFbWaves = 8, kFbStages = 4, kFbMaxRowBlocks = 5;
+constexpr int kFbWaves = 8, kFbMaxRowBlocks = 5;
 constexpr int kFbZ = 32 * 128;                          // a tile's d_z: 32 rows of 64 columns, the 64-byte halves of a row exchanged in every other pair of rows
-constexpr int kFbStage = kFbZ + 256 + 256;              // | 32 indices, 32 bins | 64 mask values
-constexpr int kFbCodes = kFbStages * kFbStage;          // 3 x 32 16-bit row numbers: by bin, by position code, bias
-constexpr int kFbWaveBytes = kFbCodes + 256;
-static_assert(kFbWaves * kFbWaveBytes <= 160 * 1024, "LDS");
-
-typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+constexpr int kFbCodes = 256 + 256;                     // 32 indices, 32 bins | 64 mask values
+template <int RB>
+struct FbCfg {
+    static constexpr int kStages = RB <= 3 ? 3 : 2, kCodeStages = kStages + 1;
+    static constexpr int kOnes = kStages * kFbZ + kCodeStages * kFbCodes;  // one-hot tile: 64 bytes per table row, its 16-byte slots c at c ^ (row / 4 mod 4)
+    static constexpr int kWaveBytes = kOnes + 32 * RB * 64;
+    static constexpr int kSum = RB * 2 * 16 * 64 * 4;   // bytes of a wave's sums
+    static constexpr int kBytes = kFbWaves * kWaveBytes > kSum * (kFbWaves / 2) ? kFbWaves * kWaveBytes : kSum * (kFbWaves / 2);
+    static_assert(kBytes <= 160 * 1024, "LDS");
+};
 
 // One direct load of 4 bytes (BYTES = 1: a byte, zero-extended) per lane to LDS bytes lds + 4 lane; of 16 bytes to lds + 16 lane.
 template <int BYTES>
@@ -201,6 +216,12 @@ __device__ __forceinline__ void fb_load(const void *addr, unsigned lds)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_ubyte %1, off" ::"s"(lds), "v"(addr) : "memory", "m0");
 }
 
+// 16 bytes per lane from base + voff to LDS bytes lds + 16 lane.
+__device__ __forceinline__ void fb_load_at(const void *base, unsigned voff, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+}
+
 template <int RB>
 __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(const int *__restrict__ nbr_idx, const int *__restrict__ nbr_bin,
                                                                                const bf16_t *__restrict__ d_z, const uint8_t *__restrict__ mask,
@@ -209,31 +230,46 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
                                                                                int n_pos, int pos_mode, int n_out)
 {
     extern __shared__ __attribute__((aligned(16))) char fb_smem[];
-    const int s = blockIdx.x, col0 = blockIdx.y * 64;
+    const int s = blockIdx.y, col0 = blockIdx.x * 64;  // (512 columns: each of the 8 XCDs streams the same 64 for every slot)
     const int lane = threadIdx.x & 63, li = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int R = n_bins + n_pos + 1, half = (n_pos - 1) >> 1;
-    char *const mine = fb_smem + wave * kFbWaveBytes;
+    using C = FbCfg<RB>;
+    char *const mine = fb_smem + wave * C::kWaveBytes;
     const unsigned mine_lds = lds_address(mine);
     const int ntiles = (rows + 31) / 32;
     const int own = wave < ntiles ? (ntiles - wave + kFbWaves - 1) / kFbWaves : 0;  // tiles wave, wave + 8, ...
 
-    // The kLoads loads of this wave's tile n (past the last one: the last one again, so that every tile has as many).
+    // Loads of this wave's tile n, d_z of it and the indices, bins and mask of the next one (past the last tile: the last one again, so that
+    // every tile has as many).  Tiles are kFbWaves apart; rows and columns past the end: addresses of existing ones, what they bring is
+    // not used.
     constexpr int kLoads = 6;
+    unsigned vz[4];
+    const int l8 = lane >> 3, l7 = lane & 7;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int rr = 8 * q + l8;
+        vz[q] = (unsigned)(rr * n_out + min(8 * (l7 ^ (((rr >> 1) & 1) << 2)), n_out - 8 - col0)) * 2;
+    }
+    const int *const codes = g ? nbr_bin : nbr_idx;
+    auto issue_codes = [&](int n) {
+        const unsigned st = mine_lds + (n % C::kCodeStages) * kFbCodes + C::kStages * kFbZ;
+        const size_t res = min(32 * (wave + kFbWaves * min(n, own - 1)) + li, rows - 1);
+        fb_load<4>(codes + res * k + s, st);
+        if (mask) fb_load<1>(mask + res, st + 256);
+        else fb_load<4>(nbr_idx + res * k + s, st + 256);  // (not used)
+    };
     auto issue = [&](int n) {
-        const unsigned st = mine_lds + (n % kFbStages) * kFbStage;
+        issue_codes(n + 1);
+        const unsigned st = mine_lds + (n % C::kStages) * kFbZ;
         const int res0 = 32 * (wave + kFbWaves * min(n, own - 1));
+        const bf16_t *base = d_z + (size_t)res0 * n_out + col0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int rr = 8 * q + (lane >> 3), slot = (lane & 7) ^ (((rr >> 1) & 1) << 2);
-            // (rows and columns past the end: addresses of existing ones; what they bring is not used)
-            const size_t res = min(res0 + rr, rows - 1);
-            fb_load<16>(d_z + res * n_out + min(col0 + 8 * slot, n_out - 8), st + 1024 * q);
+            unsigned v = vz[q];
+            if (res0 + 32 > rows) v -= (unsigned)(max(8 * q + l8 - (rows - 1 - res0), 0) * n_out) * 2;
+            fb_load_at(base, v, st + 1024 * q);
         }
-        const size_t res = min(res0 + li, rows - 1);
-        fb_load<4>((g ? nbr_bin : nbr_idx) + res * k + s, st + kFbZ);
-        if (mask) fb_load<1>(mask + res, st + kFbZ + 256);
-        else fb_load<4>(nbr_idx + res * k + s, st + kFbZ + 256);  // (not used)
     };
 
     f32x16 acc[RB][2];
@@ -244,85 +280,97 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
 
-    // which of the three code arrays decides about this lane's row of each row block
-    int code_off[RB];
-    u16x2 row2[RB];
-#pragma unroll
-    for (int mb = 0; mb < RB; ++mb) {
-        const int row = 32 * mb + li;
-        code_off[mb] = kFbCodes + (row < n_bins ? 0 : (row < R - 1 ? 64 : 128)) + 8 * g;
-        row2[mb] = (u16x2){(unsigned short)row, (unsigned short)row};
-    }
+    char *const ones = mine + C::kOnes;
+    for (int x = lane; x < 32 * RB * 4; x += 64) *reinterpret_cast<uint4 *>(ones + 16 * x) = (uint4){0u, 0u, 0u, 0u};
+    // residue q of a group of 16 is value q mod 4 + 4 (q / 8) of the lanes of half q / 4 mod 2 (the order of the transposing read)
+    const int slot = 2 * (li >> 4) + ((li >> 2) & 1), within = 2 * (4 * ((li >> 3) & 1) + (li & 3));
+    auto one_at = [&](int row) { return reinterpret_cast<bf16_t *>(ones + row * 64 + ((slot ^ ((row >> 2) & 3)) << 4) + within); };
+    const int aone = li * 64 + ((g ^ ((li >> 2) & 3)) << 4);  // (k-step t: slot 2 t + g)
+    const int turn = 32 * kFbWaves % L;
+    int i = (32 * wave + li) % L;  // place of this lane's residue in its chain
     const int e4 = (lane & 15) >> 2, grp2 = (lane >> 4) & 1, j4 = lane & 3;
     int az[2];
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) az[nb] = (4 * g + e4) * 128 + (nb ^ (e4 >> 1)) * 64 + (16 * grp2 + 4 * j4) * 2;
 
-    if (own > 0)
-        for (int n = 0; n < kFbStages - 1; ++n) issue(n);
-    for (int n = 0; n < own; ++n) {
-        // tile n has landed; the reads of tile n - 1, whose stage the next loads take, are done
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kFbStages - 2) * kLoads) : "memory");
-        issue(n + kFbStages - 1);
-        char *const st = mine + (n % kFbStages) * kFbStage;
+    // of tile n, from its indices, bins and mask: this lane's one, whether it is set, and which residues count
+    bf16_t *one = one_at(0), *const one_b = one_at(R - 1);
+    bool filled = false;
+    unsigned vmask = 0u;
+    int j, bn, mk;
+    auto read_codes = [&](int n) {
+        const char *const st = mine + C::kStages * kFbZ + (n % C::kCodeStages) * kFbCodes;
+        j = *reinterpret_cast<const int *>(st + 4 * li);
+        bn = *reinterpret_cast<const int *>(st + 128 + 4 * li);
+        mk = *reinterpret_cast<const int *>(st + 256 + 4 * li);
+    };
+    auto decode = [&](int n) {
         const int res = 32 * (wave + kFbWaves * n) + li;
-        const int j = *reinterpret_cast<const int *>(st + kFbZ + 4 * li);
-        const int bn = *reinterpret_cast<const int *>(st + kFbZ + 128 + 4 * li);
-        const bool valid = res < rows && (mask ? *reinterpret_cast<const int *>(st + kFbZ + 256 + 4 * li) != 0 : true);
-        const unsigned vmask = (unsigned)__ballot(valid);  // (the two halves agree)
-        if (vmask == 0u) continue;
-        const bool filled = valid && j >= 0 && j < L;
-        const int i = res % L;
+        const bool valid = res < rows && (mask ? mk != 0 : true);
+        vmask = (unsigned)__ballot(valid);  // (the two halves agree)
         const int pc = pos_mode == 0 ? min(j, n_pos - 1) : min(max(j - i, -half), half) + half;
-        // (0xFFFF: no row)
-        const int c_bin = filled ? min(max(bn, 0), n_bins - 1) : 0xFFFF;
-        const int c_pos = filled && n_pos > 0 ? n_bins + pc : 0xFFFF;
-        *reinterpret_cast<bf16_t *>(mine + kFbCodes + g * 64 + 2 * li) = (bf16_t)(g ? c_pos : c_bin);
-        if (g == 0) *reinterpret_cast<bf16_t *>(mine + kFbCodes + 128 + 2 * li) = (bf16_t)(valid && s == 0 ? R - 1 : 0xFFFF);
-        if (vmask != 0xFFFFFFFFu) {
-            // what a masked or missing residue holds must not reach the products: 0 x NaN would
+        i += turn;
+        if (i >= L) i -= L;
+        filled = valid && j >= 0 && j < L && (g == 0 || n_pos > 0);
+        one = one_at(filled ? (g ? n_bins + pc : min(max(bn, 0), n_bins - 1)) : 0);
+    };
+    if (own > 0) {
+        issue_codes(0);
+        for (int n = 0; n < C::kStages - 1; ++n) issue(n);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::kStages - 1) * kLoads) : "memory");
+        read_codes(0);
+        decode(0);
+    }
+    for (int n = 0; n < own; ++n) {
+        // d_z of tile n and the codes of tile n + 1 have landed; the reads of tile n - 1, whose stage the next loads take, are done
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((C::kStages - 2) * kLoads) : "memory");
+        issue(n + C::kStages - 1);
+        char *const st = mine + (n % C::kStages) * kFbZ;
+        read_codes(n + 1);  // (past the last tile: not used)
+        if (vmask != 0u) {
+            const bool counts = (vmask >> li) & 1u;
+            auto set = [&](bf16_t v) {
+                if (filled) *one = v;
+                if (s == 0 && g == 0 && counts) *one_b = v;
+                asm volatile("" ::: "memory");  // (the LDS accesses of a wave execute in order)
+            };
+            set(0x3F80);
+            if (vmask != 0xFFFFFFFFu) {
+                // what a masked or missing residue holds must not reach the products: 0 x NaN would
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (!((vmask >> (8 * q + (lane >> 3))) & 1u)) *reinterpret_cast<uint4 *>(st + 1024 * q + 16 * lane) = (uint4){0u, 0u, 0u, 0u};
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            bf16x8 bz[2];
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                const bf16x4 lo = lds_read_tr(st + az[nb] + 16 * t * 128), hi = lds_read_tr(st + az[nb] + (16 * t + 8) * 128);
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    bz[nb][x] = lo[x];
-                    bz[nb][4 + x] = hi[x];
-                }
+                for (int q = 0; q < 4; ++q)
+                    if (!((vmask >> (8 * q + l8)) & 1u)) *reinterpret_cast<uint4 *>(st + 1024 * q + 16 * lane) = (uint4){0u, 0u, 0u, 0u};
+                asm volatile("" ::: "memory");
             }
+            bf16x8 bz[2][2], a[2][RB];
 #pragma unroll
-            for (int mb = 0; mb < RB; ++mb) {
-                // codes of residues 16 t + 4 g .. + 3 and 16 t + 8 + 4 g .. + 3 (the order of the transposing read)
-                const uint2 lo = *reinterpret_cast<const uint2 *>(mine + code_off[mb] + 32 * t);
-                const uint2 hi = *reinterpret_cast<const uint2 *>(mine + code_off[mb] + 32 * t + 16);
-                const unsigned cw[4] = {lo.x, lo.y, hi.x, hi.y};
-                u32x4 a;
+            for (int t = 0; t < 2; ++t) {
 #pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const u16x2 diff = __builtin_bit_cast(u16x2, cw[x]) ^ row2[mb];
-                    const u16x2 ne = __builtin_elementwise_min(diff, (u16x2){1, 1});
-                    a[x] = __builtin_bit_cast(unsigned, (u16x2)((u16x2){0x3F80, 0x3F80} - ne * (u16x2){0x3F80, 0x3F80}));  // bf16 1.0 where equal
+                for (int nb = 0; nb < 2; ++nb) {
+                    const bf16x4 lo = lds_read_tr(st + az[nb] + 16 * t * 128), hi = lds_read_tr(st + az[nb] + (16 * t + 8) * 128);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        bz[t][nb][x] = lo[x];
+                        bz[t][nb][4 + x] = hi[x];
+                    }
                 }
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), bz[nb], acc[mb][nb], 0, 0, 0);
+                for (int mb = 0; mb < RB; ++mb) a[t][mb] = *reinterpret_cast<const bf16x8 *>(ones + 32 * 64 * mb + (aone ^ (32 * t)));
             }
+            asm volatile("" ::: "memory");
+            set(0);
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int mb = 0; mb < RB; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][mb], bz[t][nb], acc[mb][nb], 0, 0, 0);
         }
+        decode(n + 1);
     }
     wait_vmem<0>();  // (loads past the last tile still write LDS)
     // the waves' sums, in a fixed order: 4..7 to 0..3, 2..3 to 0..1, 1 to 0
-    constexpr int kSum = RB * 2 * 16 * 64 * 4;  // bytes of a wave's sums
-    static_assert(kSum * (kFbWaves / 2) <= 160 * 1024, "LDS");
+    constexpr int kSum = C::kSum;
 #pragma unroll
     for (int w = kFbWaves / 2; w >= 1; w >>= 1) {
         __syncthreads();
@@ -378,7 +426,7 @@ hipError_t launch_factor_backward(dim3 grid, hipStream_t stream, const int *nbr_
                                   float *d_e_bin, float *d_e_pos, float *d_bias, int rows, int L, int k, int n_bins, int n_pos, int pos_mode,
                                   int n_out)
 {
-    constexpr int sums = RB * 2 * 16 * 64 * 4 * (kFbWaves / 2), tiles = kFbWaves * kFbWaveBytes, lds = sums > tiles ? sums : tiles;
+    constexpr int lds = FbCfg<RB>::kBytes;
     static LdsLimit limit;
     const hipError_t e = raise_lds_limit(limit, (const void *)fipa_factor_backward_kernel<RB>, lds);
     if (e != hipSuccess) return e;
@@ -448,7 +496,7 @@ extern "C" int fipa_factor_project_backward(int32_t B, int32_t L, int32_t k, int
     for (const void *ptr : al16)
         if (ptr && !fipa::aligned16(ptr)) return FIPA_ERR_ALIGNMENT;
     if ((reinterpret_cast<uintptr_t>(nbr_idx) & 3u) != 0 || (reinterpret_cast<uintptr_t>(nbr_bin) & 3u) != 0) return FIPA_ERR_ALIGNMENT;
-    const dim3 grid((unsigned)k, (unsigned)((n_out + 63) / 64));
+    const dim3 grid((unsigned)((n_out + 63) / 64), (unsigned)k);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const auto launch = RB == 1   ? fipa::launch_factor_backward<1>
                         : RB == 2 ? fipa::launch_factor_backward<2>
