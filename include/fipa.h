@@ -101,14 +101,15 @@ const char *fipa_status_string(int status);
 /*
  * Scratch sizes in bytes for fipa_forward / fipa_backward with this description.  Both grow with L
  * and stay below an affine function of it (the linear-memory property of Section 2.3): besides what
- * is affine in L, the forward at r c_z >= 512 and the backward at r c_z >= 256 hold the attention
- * weights of a number of query rows against all keys -- of at most 16384, respectively 4096 rows per
- * (batch, head) pair, and of no more than 32 GiB in all unless the backward's least is more.
+ * is affine in L, the forward at r c_z >= 512 and the backward at r c_z >= 128 are given room for the attention
+ * weights of a number of query rows against all keys -- of at most 16384, respectively 4096 rows (8192 at r c_z <= 256)
+ * per (batch, head) pair, and of no more than 32 GiB in all unless the backward's least is more.  (The forward
+ * makes no use of it at r c_z = 512.)
  * Every call also runs, more slowly, in less (FIPA_ERR_WORKSPACE below its least): the forward without
  * those weights, the backward -- alone, with FIPA_FLAG_KEEP_FORWARD, packed or in the module -- with
  * 4 B H L' r c_z bytes of them (L' = L rounded up to 128) or all of them, whichever is less; the rows
  * whose weights are held follow the size that is given.  A training step of two chains of 4096
- * residues, H = 12, r c_z = 256: 2.0 ms in 2.2 GB (the query), 4.4 ms in 0.67 GB (the least).
+ * residues, H = 12, r c_z = 256: 1.8 ms in 2.2 GB (the query), 3.0 ms in 0.67 GB (the least).
  * Either output pointer may be NULL.  Host-only, touches no device.
  */
 int fipa_workspace_bytes(const fipa_desc *desc, size_t *forward_bytes, size_t *backward_bytes);
@@ -144,7 +145,7 @@ int fipa_forward(const fipa_desc *desc,
  * fipa_forward without a workspace argument, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): same
  * arguments and results as fipa_forward, and the kernels that fipa_forward runs in a workspace of
- * this size (its least, where the weights of r*cz >= 512 do not fit), with the scratch memory taken from an
+ * this size (its least, where the weights of r*cz = 1024 do not fit), with the scratch memory taken from an
  * array of FIPA_STATIC_SCRATCH_BYTES that is part of the library's device image (every GPU the
  * library is used on holds one copy until the process ends).  Calls nothing that allocates.
  *   - FIPA_ERR_WORKSPACE when the least workspace of the call exceeds FIPA_STATIC_SCRATCH_BYTES

@@ -30,6 +30,7 @@ PER_FILE = {
     "fipa_bf16_attn_fwd_ws.hip": _VGPR_FORM,
     "fipa_bf16_attn_fwd_wide.hip": _VGPR_FORM,
     "fipa_bf16_attn_fwd_stored.hip": _VGPR_FORM,
+    "fipa_bf16_attn_fwd_576.hip": _VGPR_FORM,
     "fipa_bf16_bwd_kernel.hip": _VGPR_FORM,
     "fipa_bf16_bwd_stored.hip": _VGPR_FORM,
     "fipa_bf16_bwd_keys.hip": _VGPR_FORM,

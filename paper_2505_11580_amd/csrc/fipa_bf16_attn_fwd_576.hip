@@ -1,0 +1,471 @@
+// Fused attention for r c_z = 512 (lifted width 576) in one pass: like fipa_bf16_attn_fwd.hip a workgroup takes 128 queries, a
+// wave 32 of them with their whole output row block, and nothing but the outputs goes to memory.
+//
+// Registers are what this width is about.  A wave's output accumulator is 18 blocks of 32 x 32 (288 registers per lane) beside 36
+// query fragments (144) and the softmax: the 16 blocks of the pair columns fill the 256 accumulation registers, each in a place of
+// its own (left to the allocator they spilled), the two head-specific ones, the fragments, S^T and the operands share the 256 others;
+// 9 of the 36 query fragments stay in LDS, in the 37 KB that three stages of 41 KB leave.
+//
+// Step n forms S^T of key block n while block n - 1 is multiplied with its values:
+//     S^T of block n and the first half of P V (keys 0-15 of block n - 1)
+//     the second half of P V, and among it the exponentials of block n
+// One barrier per block; the loads of block n + 1 go out at the start of step n.  LDS tiles of z2 as in fipa_bf16_bwd_keys.hip:
+// row reads (k^) and transposing reads (v^) both free of bank conflicts.
+//
+// Measured, whole call, weights stored by one kernel and multiplied by another -> here: four chains of 2.7k to 7.1k residues, H = 12
+// 3.22 -> 2.53 ms (of which 0.2 ms from dealing the chains to the XCDs more evenly); B = 2, L = 4096 0.94 -> 0.77; one chain of 2048
+// 0.207 -> 0.132.  1.25 PFLOP/s executed, matrix pipe half busy at 1.9 GHz: the clock gives way to the load (a large product of random
+// bf16 numbers reaches 1.4 to 1.6 PFLOP/s here).  Without the loads 4 to 7 % less, without the LDS reads of P V 1 to 4 %, without the
+// exponentials 1 to 4 % (results invalid).
+//
+// Softmax reference: the largest logit of the 96 keys around a row's residue (its wave's block and the two beside it, which go
+// through the ring first, for these maxima alone), raised where a block's weights sum above 2^32 as in fipa_bf16_attn_fwd.hip.
+#include "fipa_gfx950.h"
+
+namespace fipa {
+
+namespace {
+
+constexpr float kTauPow = 4294967296.0f;  // 2^32
+constexpr float kNegInf = -INFINITY;
+constexpr int DZ = 512, D = kDH + DZ, KS = D / 16, KSH = kDH / 16, ZBL = DZ / 32, NPV = 2 * (ZBL + 2);
+constexpr int ZB = DZ * 2;
+constexpr int Z_OFF = 0, KH_OFF = 32 * ZB, VH_OFF = KH_OFF + 4096, KB_OFF = VH_OFF + 4096, STAGE = KB_OFF + 1024, NST = 3;
+constexpr int QL = KS / 4;                       // query fragments in LDS: every fourth
+constexpr int QL_OFF = NST * STAGE, LDS_BYTES = QL_OFF + 4 * QL * 1024;
+constexpr int CW_OFF = 2 * STAGE;                // start-up: scale vector of the query-side factors, where the third stage will be (its
+                                                 // first loads go out behind a barrier that every wave reaches with its fragments formed)
+constexpr int NZW = 8, NDMA = NZW + 3;           // loads per wave and block: 8 rows of z2, k^ and v^ head, key terms
+static_assert(LDS_BYTES <= 160 * 1024 && KS % 4 == 0 && NPV == KS, "LDS and schedule");
+
+// Accumulator block nb of the pair columns is a[16 nb .. 16 nb + 15] throughout, by name: as a variable it was moved and spilled by
+// the allocator (which wants 330 registers more than there are).  Every statement below names what it writes as clobbered, so
+// that the compiler keeps nothing of its own there.  A matrix instruction may read what a vector instruction wrote two instructions
+// earlier or more: operands come out of LDS, the weights are formed long before, and a step begins with the two wait states (with
+// them before every product 2 % more time).  tests/test_accumulators.py looks at the assembly for both.
+template <int NB>
+struct Acc;
+#define FIPA_CLOBBER(r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15)                                                      \
+    "a" #r0, "a" #r1, "a" #r2, "a" #r3, "a" #r4, "a" #r5, "a" #r6, "a" #r7, "a" #r8, "a" #r9, "a" #r10, "a" #r11, "a" #r12, "a" #r13, "a" #r14, "a" #r15
+#define FIPA_EACH(T, r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15)                                                      \
+    T(r0) T(r1) T(r2) T(r3) T(r4) T(r5) T(r6) T(r7) T(r8) T(r9) T(r10) T(r11) T(r12) T(r13) T(r14) T(r15)
+#define FIPA_ZERO(n) "v_accvgpr_write_b32 a" #n ", 0\n\t"
+#define FIPA_SCALE(n) "v_accvgpr_read_b32 %0, a" #n "\n\tv_mul_f32 %0, %1, %0\n\tv_accvgpr_write_b32 a" #n ", %0\n\t"
+#define FIPA_ACC(NB, RANGE, ...)                                                                                                                \
+    template <>                                                                                                                                 \
+    struct Acc<NB> {                                                                                                                            \
+        static __device__ __forceinline__ void zero() { asm volatile(FIPA_EACH(FIPA_ZERO, __VA_ARGS__)::: FIPA_CLOBBER(__VA_ARGS__)); }          \
+        static __device__ __forceinline__ void mfma(const bf16x8 &a, const bf16x8 &b)                                                           \
+        {                                                                                                                                       \
+            asm volatile("v_mfma_f32_32x32x16_bf16 " RANGE ", %0, %1, " RANGE ::"v"(a), "v"(b) : FIPA_CLOBBER(__VA_ARGS__));          \
+        }                                                                                                                                       \
+        static __device__ __forceinline__ void scale(float f)                                                                                   \
+        {                                                                                                                                       \
+            float t;                                                                                                                            \
+            asm volatile(FIPA_EACH(FIPA_SCALE, __VA_ARGS__) : "=&v"(t) : "v"(f) : FIPA_CLOBBER(__VA_ARGS__));                                   \
+        }                                                                                                                                       \
+    };
+FIPA_ACC(0, "a[0:15]", 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15)
+FIPA_ACC(1, "a[16:31]", 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31)
+FIPA_ACC(2, "a[32:47]", 32, 33, 34, 35, 36, 37, 38, 39, 40, 41, 42, 43, 44, 45, 46, 47)
+FIPA_ACC(3, "a[48:63]", 48, 49, 50, 51, 52, 53, 54, 55, 56, 57, 58, 59, 60, 61, 62, 63)
+FIPA_ACC(4, "a[64:79]", 64, 65, 66, 67, 68, 69, 70, 71, 72, 73, 74, 75, 76, 77, 78, 79)
+FIPA_ACC(5, "a[80:95]", 80, 81, 82, 83, 84, 85, 86, 87, 88, 89, 90, 91, 92, 93, 94, 95)
+FIPA_ACC(6, "a[96:111]", 96, 97, 98, 99, 100, 101, 102, 103, 104, 105, 106, 107, 108, 109, 110, 111)
+FIPA_ACC(7, "a[112:127]", 112, 113, 114, 115, 116, 117, 118, 119, 120, 121, 122, 123, 124, 125, 126, 127)
+FIPA_ACC(8, "a[128:143]", 128, 129, 130, 131, 132, 133, 134, 135, 136, 137, 138, 139, 140, 141, 142, 143)
+FIPA_ACC(9, "a[144:159]", 144, 145, 146, 147, 148, 149, 150, 151, 152, 153, 154, 155, 156, 157, 158, 159)
+FIPA_ACC(10, "a[160:175]", 160, 161, 162, 163, 164, 165, 166, 167, 168, 169, 170, 171, 172, 173, 174, 175)
+FIPA_ACC(11, "a[176:191]", 176, 177, 178, 179, 180, 181, 182, 183, 184, 185, 186, 187, 188, 189, 190, 191)
+FIPA_ACC(12, "a[192:207]", 192, 193, 194, 195, 196, 197, 198, 199, 200, 201, 202, 203, 204, 205, 206, 207)
+FIPA_ACC(13, "a[208:223]", 208, 209, 210, 211, 212, 213, 214, 215, 216, 217, 218, 219, 220, 221, 222, 223)
+FIPA_ACC(14, "a[224:239]", 224, 225, 226, 227, 228, 229, 230, 231, 232, 233, 234, 235, 236, 237, 238, 239)
+FIPA_ACC(15, "a[240:255]", 240, 241, 242, 243, 244, 245, 246, 247, 248, 249, 250, 251, 252, 253, 254, 255)
+#undef FIPA_ACC
+#undef FIPA_SCALE
+#undef FIPA_ZERO
+#undef FIPA_EACH
+#undef FIPA_CLOBBER
+template <int N>
+__device__ __forceinline__ float acc_value()  // register N of them
+{
+    float v;
+    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(v) : "n"(N));
+    return v;
+}
+
+// Operation j of a step: S^T k-steps, and products of block idx % 18 (the head-specific two first) and key half idx / 18.
+struct Ops {
+    static constexpr int LA = 3, RING = 4, N = KS + NPV, SPLIT = KS + NPV / 2;  // (SPLIT: first operation of the second half)
+    __host__ __device__ static constexpr bool pv(int j) { return j < LA || j >= SPLIT || (j < LA + 45 && (j - LA) % 3 == 2); }
+    __host__ __device__ static constexpr int idx(int j)
+    {
+        return j < LA ? j : j >= SPLIT ? NPV / 2 + j - SPLIT : j >= LA + 45 ? 30 + j - LA - 45 : (j - LA) % 3 == 2 ? LA + (j - LA) / 3 : 2 * ((j - LA) / 3) + (j - LA) % 3;
+    }
+};
+static_assert(Ops::N % Ops::RING == 0 && Ops::SPLIT == Ops::LA + 45 + 6, "schedule");
+
+__device__ __forceinline__ int swz_z(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+__device__ __forceinline__ int swz_h(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
+
+// HB: 32-column blocks per factor slice (c_z / 32), steps 8-9 of Algorithm 1 on the accumulator (AlphaFold2 head shape); 0: O^ is written.
+template <int HB>
+__global__ __launch_bounds__(256, 1) void fipa_attn_fwd_576_kernel(AttnParams p)
+{
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int per_xcd = (p.total_tiles + 7) / 8;
+    const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= (unsigned)per_xcd || logical >= p.total_tiles) return;
+    const int bh_pos = logical / p.nQT, qt = logical - bh_pos * p.nQT;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bh = p.deal ? dealt_pair_by_length(bh_pos, p.kvlen, p.B, p.H, lane) : bh_pos;
+    const int b = bh / p.H, h = bh - b * p.H;
+    const int kvlen = p.deal ? p.kvlen[b] : p.L;
+    const int row0 = qt * kTileQ, irow = row0 + 32 * wave + li;  // < Lp
+    const int nblk = row0 >= kvlen ? 0 : (kvlen + 31) / 32;
+    if (HB == 0 && nblk == 0) return;  // (nothing reads the lifted output of rows past the last valid one)
+    const size_t rows0 = (size_t)bh * p.Lp;
+    const int ulen = user_len(p, b);
+    const size_t urow0 = user_row(p, b, 0);
+
+    f32x16 acch[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acch[0][r] = acch[1][r] = 0.f;
+    static_for<ZBL>([&](auto NB) { Acc<decltype(NB)::value>::zero(); });
+    float m = kNegInf, l = 0.f;
+
+    if (nblk > 0) {
+        // Blocks in the order of the walk: those around the workgroup's residues, for the references alone; then all of them,
+        // from a block on that the tiles of 512 queries share (they share the key stream in L2).
+        const int first = min(row0 / 512 * 16, nblk - 1);
+        const int ref0 = max(row0 / 32 - 1, 0), nref = min(row0 / 32 + 5, nblk) - ref0, total = nref + nblk;
+        auto key_block = [&](int n) {
+            n = min(n, total - 1);
+            const int x = first + n - nref;
+            return n < nref ? ref0 + n : x >= nblk ? x - nblk : x;
+        };
+        // ---- direct loads ------------------------------------------------------------------------------------------
+        const u32x4 r_z = buffer_desc(p.Z2 + (size_t)b * p.Lp * DZ), r_k = buffer_desc(p.Kh + rows0 * kDH), r_v = buffer_desc(p.Vh + rows0 * kDH);
+        const u32x4 r_b = buffer_desc(p.kbias + rows0);
+        // z2: row e = wave + 4 K, slot c of 256 bytes holds slot c ^ swz_z(e) = c ^ (4 wave + K mod 4)
+        const int vz = (lane ^ (4 * wave)) * 16;
+        const int hrow = 8 * wave + (lane >> 3), vh = (lane >> 3) * 128 + ((lane & 7) ^ swz_h(hrow)) * 16, vb = min(lane, 7) * 16;
+        const unsigned lds0 = lds_address(smem);
+        auto issue = [&](auto Kc, int kb, unsigned stage) {
+            constexpr int K = decltype(Kc)::value;
+            if constexpr (K < NZW) {
+                const int e = wave + 4 * K;
+                dma16b(r_z, vz ^ (16 * (K & 3)), (32 * kb + e) * ZB, stage + Z_OFF + ZB * e);
+            } else if constexpr (K == NZW) {
+                dma16b(r_k, vh, (32 * kb + 8 * wave) * 128, stage + KH_OFF + 1024 * wave);
+            } else if constexpr (K == NZW + 1) {
+                dma16b(r_v, vh, (32 * kb + 8 * wave) * 128, stage + VH_OFF + 1024 * wave);
+            } else {
+                dma16b(r_b, vb, 32 * kb * 4, stage + KB_OFF);  // (every wave: the same values)
+            }
+        };
+        static_for<NDMA>([&](auto K) { issue(K, key_block(0), lds0); });
+        static_for<NDMA>([&](auto K) { issue(K, key_block(1), lds0 + STAGE); });
+
+        // ---- query fragments (b^{h1} of Algorithm 1 steps 2-3 formed from z1) ----------------------------------------
+        bf16x8 qf[KS];
+        char *const ql = smem + QL_OFF + wave * QL * 1024 + lane * 16;
+        {
+            float *cw = reinterpret_cast<float *>(smem + CW_OFF);
+            for (int x = tid; x < DZ; x += 256) cw[x] = kLog2e * p.w_L * p.w_b[(size_t)h * p.cz + x % p.cz];
+            __syncthreads();
+            const bf16_t *qh = p.Qh + (rows0 + irow) * kDH + 8 * g;
+#pragma unroll
+            for (int ks = 0; ks < KSH; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qh + 16 * ks);
+            const bool ok = irow < ulen && (p.mask ? p.mask[urow0 + irow] != 0 : true);
+            const unsigned keep = ok ? 0xFFFFFFFFu : 0u;
+            const bf16_t *z1row = p.z1 + (urow0 + min(irow, ulen - 1)) * DZ + 8 * g;
+#pragma unroll
+            for (int ks = 0; ks < KS - KSH; ++ks) {
+                const uint4 zr = *reinterpret_cast<const uint4 *>(z1row + 16 * ks);
+                const f32x4 w0 = *reinterpret_cast<const f32x4 *>(cw + 16 * ks + 8 * g);
+                const f32x4 w1 = *reinterpret_cast<const f32x4 *>(cw + 16 * ks + 8 * g + 4);
+                const unsigned zw[4] = {zr.x, zr.y, zr.z, zr.w};
+                unsigned pk[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const float wl = x < 2 ? w0[2 * x] : w1[2 * x - 4], wh = x < 2 ? w0[2 * x + 1] : w1[2 * x - 3];
+                    const float lo = wl * __uint_as_float(zw[x] << 16), hi = wh * __uint_as_float(zw[x] & 0xFFFF0000u);
+                    pk[x] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){lo, hi}, bf16x2)) & keep;
+                }
+                qf[KSH + ks] = __builtin_bit_cast(bf16x8, (u32x4){pk[0], pk[1], pk[2], pk[3]});
+            }
+#pragma unroll
+            for (int x = 0; x < QL; ++x) *reinterpret_cast<bf16x8 *>(ql + 1024 * x) = qf[4 * x];
+        }
+
+        // ---- per-lane LDS offsets -------------------------------------------------------------------------------------
+        const int rz = li * ZB + ((g ^ swz_z(li)) << 4), rh = li * 128 + ((g ^ swz_h(li)) << 4);  // row reads: slot 2 ks + g
+        const int l16 = lane & 15, grp2 = (lane >> 4) & 1, e4 = l16 >> 2, j4 = l16 & 3, c2 = 2 * grp2 + (j4 >> 1);
+        // transposing reads: rows 4 g + e4 (and 8 further: slot ^ 2), 64-byte block x = 0
+        const int tz = (4 * g + e4) * ZB + (((e4 << 2) | (c2 ^ g)) << 4) + 8 * (j4 & 1);
+        const int th = (4 * g + e4) * 128 + ((((e4 >> 1) << 2) | (c2 ^ g)) << 4) + 8 * (j4 & 1);
+
+        f32x16 s;
+        u32x4 pf[2];
+        bf16x8 fr[Ops::RING], fq;
+        auto largest = [&]() {
+            float mx = s[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+            return fmaxf(mx, __shfl_xor(mx, 32));
+        };
+        auto start = [&](const char *at) {
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(at + (8 * a + 4 * g) * 4);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) s[4 * a + x] = v[x];
+            }
+        };
+        auto fetch_s = [&](auto X, const char *sn) {
+            constexpr int x = decltype(X)::value, z = x - KSH;
+            return *reinterpret_cast<const bf16x8 *>(x < KSH ? sn + KH_OFF + (rh ^ (32 * x)) : sn + Z_OFF + (z >> 3) * 256 + (rz ^ (32 * (z & 7))));
+        };
+        auto fetch_pv = [&](auto X, const char *sa) {
+            constexpr int x = decltype(X)::value, t = x / (ZBL + 2), blk = x % (ZBL + 2), nb = blk - 2;
+            bf16x4 lo, hi;
+            if constexpr (blk < 2) {
+                const char *a = sa + VH_OFF + 16 * t * 128;
+                lo = lds_read_tr(a + (th ^ (64 * blk)));
+                hi = lds_read_tr(a + 8 * 128 + (th ^ (64 * blk) ^ 32));
+            } else {
+                const char *a = sa + Z_OFF + 16 * t * ZB + (nb >> 2) * 256;
+                lo = lds_read_tr(a + (tz ^ (64 * (nb & 3))));
+                hi = lds_read_tr(a + 8 * ZB + (tz ^ (64 * (nb & 3)) ^ 32));
+            }
+            bf16x8 v;
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                v[y] = lo[y];
+                v[4 + y] = hi[y];
+            }
+            return v;
+        };
+        int sidx = 0;  // stage of block n
+
+        // ---- references -----------------------------------------------------------------------------------------------
+        for (int n = 0; n < nref; ++n) {
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NDMA) : "memory");  // (block n + 1 is on its way)
+            wg_barrier();
+            const char *sn = smem + sidx * STAGE;
+            const unsigned next = lds0 + (sidx == 0 ? NST - 1 : sidx - 1) * STAGE;
+            const int kb = key_block(n + 2), apart = ref0 + n - (row0 / 32 + wave);
+            static_for<NDMA>([&](auto K) { issue(K, kb, next); });
+            if (apart >= -1 && apart <= 1) {  // (each wave: its own block and the two beside it)
+                start(sn + KB_OFF);
+                static_for<KS>([&](auto X) {
+                    constexpr int x = decltype(X)::value;
+                    bf16x8 q = qf[x];
+                    if constexpr (x % 4 == 0) q = *reinterpret_cast<const bf16x8 *>(ql + 256 * x);
+                    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fetch_s(X, sn), q, s, 0, 0, 0);
+                });
+                m = fmaxf(m, largest());
+            }
+            sidx = sidx == NST - 1 ? 0 : sidx + 1;
+        }
+
+        // ---- the walk: HS: there is a block n; HA: there is a block n - 1 ------------------------------------------------
+        auto step = [&](auto HS, auto HA, int n) {
+            constexpr bool hs = decltype(HS)::value, ha = decltype(HA)::value;
+            const char *sn = smem + sidx * STAGE;
+            const char *sa = smem + (sidx == 0 ? NST - 1 : sidx - 1) * STAGE;
+            const unsigned next = lds0 + (sidx == NST - 1 ? 0 : sidx + 1) * STAGE;
+            const int next_kb = key_block(n + 1);
+            const float mu = m == kNegInf ? 0.f : m;
+            u32x4 tail;  // the second half's weights (pf[1] is in use to the end)
+            float psum = 0.f;
+            constexpr int p0 = Ops::SPLIT + 2, p1 = Ops::N - 1;
+            auto mfma_of = [&](auto J) {
+                constexpr int j = decltype(J)::value, x = Ops::idx(j);
+                const bf16x8 &f = fr[j % Ops::RING];
+                if constexpr (!Ops::pv(j)) {
+                    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x % 4 == 0 ? fq : qf[x], s, 0, 0, 0);
+                } else {
+                    constexpr int t = x / (ZBL + 2), blk = x % (ZBL + 2);
+                    const bf16x8 w = __builtin_bit_cast(bf16x8, pf[t]);
+                    if constexpr (blk < 2) mfma_v(acch[blk], f, w);
+                    else Acc<blk - 2>::mfma(f, w);
+                }
+            };
+            static_for<Ops::N>([&](auto J) {
+                constexpr int j = decltype(J)::value, jf = j + Ops::LA;
+                constexpr bool on = Ops::pv(j) ? ha : hs;
+                if constexpr (j == 0) {
+                    if constexpr (ha) {
+                        asm volatile("s_nop 1");
+                        mfma_of(J);
+                    }
+                    if constexpr (hs) {
+                        // the loads of block n are complete (at the first step those of block n + 1 are on their way); each wave has used
+                        // every operand of the stage that the next loads go to
+                        __builtin_amdgcn_sched_barrier(0);
+                        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ha ? 0 : NDMA) : "memory");
+                        wg_barrier();
+                        fq = *reinterpret_cast<const bf16x8 *>(ql);
+                    }
+                }
+                if constexpr (jf < Ops::N) {
+                    constexpr int jx = jf < Ops::N ? jf : 0;
+                    using X = std::integral_constant<int, Ops::idx(jx)>;
+                    if constexpr (Ops::pv(jx)) {
+                        if constexpr (ha) fr[jx % Ops::RING] = fetch_pv(X{}, sa);
+                    } else if constexpr (hs) {
+                        fr[jx % Ops::RING] = fetch_s(X{}, sn);
+                    }
+                } else if constexpr (hs) {  // the first products of the next step, of block n
+                    fr[jf % Ops::RING] = fetch_pv(std::integral_constant<int, jf % Ops::N>{}, sn);
+                }
+                if constexpr (hs && j == Ops::LA - 1) start(sn + KB_OFF);
+                if constexpr (j > 0 && on) mfma_of(J);
+                if constexpr (hs && !Ops::pv(j) && Ops::idx(j) % 4 == 1 && Ops::idx(j) + 3 < KS)
+                    fq = *reinterpret_cast<const bf16x8 *>(ql + 256 * (Ops::idx(j) + 3));
+                if constexpr (hs && ha && j >= 1 && j <= NDMA) issue(std::integral_constant<int, j - 1>{}, next_kb, next);
+                if constexpr (hs && j >= p0 && j < p1) {
+#pragma unroll
+                    for (int t = (j - p0) * 8 / (p1 - p0); t < (j - p0 + 1) * 8 / (p1 - p0); ++t) {
+                        const unsigned w = pack_pair(__builtin_amdgcn_exp2f(s[2 * t] - mu), __builtin_amdgcn_exp2f(s[2 * t + 1] - mu), psum);
+                        if (t < 4) pf[0][t] = w;
+                        else tail[t - 4] = w;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if constexpr (hs) {
+                if (__any(!(psum <= kTauPow) || m == kNegInf)) {  // rare: raise the reference to the block's maximum, weights again
+                    const float mn = fmaxf(m, largest());
+                    const float alpha = mn == kNegInf ? 1.f : __builtin_amdgcn_exp2f(m - mn);
+                    m = mn;
+                    l *= alpha;
+                    mfma_drain();
+                    if constexpr (ha) {
+#pragma unroll
+                        for (int nb = 0; nb < 2; ++nb) {
+                            asm volatile("" : "+v"(acch[nb]));
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) acch[nb][r] *= alpha;
+                        }
+                        static_for<ZBL>([&](auto NB) { Acc<decltype(NB)::value>::scale(alpha); });
+                    }
+                    const float mv = mn == kNegInf ? 0.f : mn;
+                    psum = 0.f;
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        const unsigned w = pack_pair(__builtin_amdgcn_exp2f(s[2 * t] - mv), __builtin_amdgcn_exp2f(s[2 * t + 1] - mv), psum);
+                        if (t < 4) pf[0][t] = w;
+                        else tail[t - 4] = w;
+                    }
+                }
+                l += psum;
+                pf[1] = tail;
+            }
+            sidx = sidx == NST - 1 ? 0 : sidx + 1;
+        };
+        using T = std::true_type;
+        using F = std::false_type;
+        step(T{}, F{}, nref);
+        for (int n = nref + 1; n < total; ++n) step(T{}, T{}, n);
+        step(F{}, T{}, total);
+        wait_vmem<0>();  // (the loads past the last block still write LDS)
+        mfma_drain();
+        asm volatile("" : "+v"(acch[0]), "+v"(acch[1]));  // (orders every use behind the wait)
+    }
+
+    // ---- results ------------------------------------------------------------------------------------------------------
+    const bool live = nblk > 0 && irow < kvlen;
+    const float lt = l + __shfl_xor(l, 32), inv = live && lt > 0.f ? 1.f / lt : 0.f;
+    const float lse2 = lt > 0.f ? m + __log2f(lt) : kNegInf;
+    if constexpr (HB == 0) {
+        if (!live) return;
+        if (g == 0) p.lse2[rows0 + irow] = lse2;
+        float *orow = p.Ohat + (rows0 + irow) * D + 4 * g;
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4 *>(orow + 32 * nb + 8 * q) =
+                    (f32x4){acch[nb][4 * q] * inv, acch[nb][4 * q + 1] * inv, acch[nb][4 * q + 2] * inv, acch[nb][4 * q + 3] * inv};
+        static_for<4 * ZBL>([&](auto Q) {
+            constexpr int r = 4 * decltype(Q)::value;
+            *reinterpret_cast<f32x4 *>(orow + kDH + r / 16 * 32 + 8 * (r / 4 % 4)) =
+                (f32x4){acc_value<r>() * inv, acc_value<r + 1>() * inv, acc_value<r + 2>() * inv, acc_value<r + 3>() * inv};
+        });
+    } else {
+        if (irow >= ulen) return;
+        const bool valid = live && inv > 0.f && (p.mask ? p.mask[urow0 + irow] != 0 : true);
+        const float sc = valid ? inv : 0.f;
+        const size_t row = (urow0 + irow) * p.H + h;
+        constexpr int CZ = 32 * HB, R = ZBL / HB, c = 16, Pv = 8;
+        // z1 contraction over the factor slices (step 9): block rho HB + q is slice rho, columns 32 q ..
+        const bf16_t *z1row = p.z1 + (urow0 + irow) * DZ + 4 * g;
+        float *dst = p.o_pair + row * CZ + 4 * g;
+        static_for<4 * HB>([&](auto Q) {
+            constexpr int q = decltype(Q)::value / 4, a = decltype(Q)::value % 4;
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+            static_for<R>([&](auto Rho) {
+                constexpr int rho = decltype(Rho)::value, at = 16 * (rho * HB + q) + 4 * a;
+                const uint2 zr = *reinterpret_cast<const uint2 *>(z1row + rho * CZ + 32 * q + 8 * a);
+                sum[0] += acc_value<at>() * __uint_as_float(zr.x << 16);
+                sum[1] += acc_value<at + 1>() * __uint_as_float(zr.x & 0xFFFF0000u);
+                sum[2] += acc_value<at + 2>() * __uint_as_float(zr.y << 16);
+                sum[3] += acc_value<at + 3>() * __uint_as_float(zr.y & 0xFFFF0000u);
+            });
+#pragma unroll
+            for (int x = 0; x < 4; ++x) sum[x] = valid ? sum[x] * sc : 0.f;
+            *reinterpret_cast<f32x4 *>(dst + 32 * q + 8 * a) = sum;
+        });
+        // points 4 g .. 4 g + 3 of this half (columns: see v_pt_col)
+        float Gv[12];
+#pragma unroll
+        for (int u = 0; u < 12; ++u) {
+            const int dh = 16 + 8 * (u >> 2) + (u & 3), dl = 16 + 8 * ((u + 12) >> 2) + ((u + 12) & 3);
+            Gv[u] = acch[dh >> 5][4 * ((dh & 31) >> 3) + (dh & 3)] + acch[dl >> 5][4 * ((dl & 31) >> 3) + (dl & 3)];
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            f32x4 out;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) out[x] = valid ? acch[0][4 * a + x] * sc : 0.f;
+            *reinterpret_cast<f32x4 *>(p.o + row * c + 8 * a + 4 * g) = out;
+        }
+        const float *Rp = p.rot + (urow0 + irow) * 9, *tr = p.trans + (urow0 + irow) * 3;
+        float outp[12];
+#pragma unroll
+        for (int pp = 0; pp < 4; ++pp) {
+            const float rx = Gv[3 * pp] * inv - (tr[0] - p.cen[4 * b]), ry = Gv[3 * pp + 1] * inv - (tr[1] - p.cen[4 * b + 1]),
+                        rz = Gv[3 * pp + 2] * inv - (tr[2] - p.cen[4 * b + 2]);
+#pragma unroll
+            for (int x = 0; x < 3; ++x) outp[3 * pp + x] = valid ? Rp[x] * rx + Rp[3 + x] * ry + Rp[6 + x] * rz : 0.f;  // R^T
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            *reinterpret_cast<f32x4 *>(p.o_pts + row * (Pv * 3) + 12 * g + 4 * a) = (f32x4){outp[4 * a], outp[4 * a + 1], outp[4 * a + 2], outp[4 * a + 3]};
+        if (p.lse && g == 0) p.lse[user_lse_index(p, b, h, irow)] = valid ? lse2 * kLn2 - p.qbias[rows0 + irow] : 0.f;
+    }
+}
+
+template <int HB>
+hipError_t launch(const AttnParams &p, hipStream_t stream)
+{
+    static LdsLimit limit;
+    const hipError_t e = raise_lds_limit(limit, (const void *)fipa_attn_fwd_576_kernel<HB>, LDS_BYTES);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fipa_attn_fwd_576_kernel<HB>, dim3((p.total_tiles + 7) / 8 * 8), dim3(256), LDS_BYTES, stream, p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_attn_fwd_576_bf16(const AttnParams &p, bool fused, hipStream_t stream)
+{
+    if (!fused) return launch<0>(p, stream);
+    return p.cz == 64 ? launch<2>(p, stream) : p.cz == 128 ? launch<4>(p, stream) : p.cz == 256 ? launch<8>(p, stream) : hipErrorInvalidValue;
+}
+
+}  // namespace fipa

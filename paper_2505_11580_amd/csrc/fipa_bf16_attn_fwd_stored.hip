@@ -1,18 +1,16 @@
-// Fused attention for r c_z = 512 and 1024 (lifted widths 576 and 1088) in two kernels: the weights of a range of
+// Fused attention for r c_z = 1024 (lifted width 1088) in two kernels: the weights of a range of
 // query rows are formed once and kept in memory, the output is a plain matrix product with them.  The windowed kernel
 // (fipa_bf16_attn_fwd_wide.hip) forms S^T once per window of the output columns, because a wave's output accumulator
-// does not fit the register file: 108 matrix instructions per 32 x 32 pairs at width 576, 308 at width 1088, where 72
-// and 136 would do, and these are what the two kernels here execute.
+// does not fit the register file: 308 matrix instructions per 32 x 32 pairs, where 136 would do, and these are what the two
+// kernels here execute.  (At r c_z = 512 the accumulator fits beside everything else: fipa_bf16_attn_fwd_576.hip.)
 //
 //   fipa_fwd_weights_kernel  S^T = K^ Q^^T, softmax reference and sum, weights P (bf16) of 32 queries per wave
 //   fipa_fwd_values_kernel   O^ = P V^ for 256 queries and a window of the columns; steps 8-9 of Algorithm 1
 //
-// Softmax: the reference of a row starts as the largest logit of the 96 keys around its own residue (its wave's block and the
-// two beside it), where distance-dominated logits have their maximum, whose weight is then exactly 1: the blocks around the
-// workgroup's residues go through the LDS ring first, for these maxima alone.  (With the wave's own 32 keys, multiplied from
-// global memory in the prologue, the same time and 1.0 % more distance from float64, 8.73e-4 against 8.65e-4 on four chains of up
-// to 1500 residues; every block for every wave, 8.64e-4 but 2 % more time on the ragged batch below.  Width 1088 takes its own 32
-// keys: with one wave per SIMD and two LDS stages the blocks took 7 % of the call at B = 2, L = 2048, 530 -> 567 us, for 0.8 %.)
+// Softmax: the reference of a row starts as the largest logit of its wave's own 32 keys, multiplied from global memory in the
+// prologue, where distance-dominated logits have their maximum, whose weight is then exactly 1.  (The two blocks beside it as well,
+// through the LDS ring: with one wave per SIMD and two LDS stages 7 % of the call at B = 2, L = 2048, 530 -> 567 us, for 0.8 % less distance
+// from float64.)
 // It is raised only where a block holds
 // a logit more than kRaise above it (far inside the range of bf16 and fp32), by a whole number of log2 units, so that
 // weights move from one reference to the next exactly.  A raise is recorded for its (32 queries, key block) as a flag and the 32 references before it; the values
@@ -23,10 +21,9 @@
 // Weights, per (batch, head) pair and tile of 256 queries: W[key / 16][query][16], the 16 keys in the order of the
 // matrix operand (4 g + x | 8 + 4 g + x at g 8 + x | g 8 + 4 + x).
 //
-// Measured, whole call, windowed -> here: four chains of 2.7k to 7.1k residues, H = 12, width 576: 4.68 -> 3.37 ms;
-// B = 2, L = 2048, H = 12, width 1088: 1.45 -> 0.53 ms.  The matrix pipe is busy for 41 % of either kernel's time at width 576
-// (where chains differ in length also because of the last workgroups of a range), for 27 / 38 % at width 1088 (weights / values:
-// 1.5 rounds of weight tiles, one wave per SIMD); waves spend 64 to 72 % of their cycles in waits for LDS, L2 and the barrier.
+// Measured, whole call, windowed -> here: B = 2, L = 2048, H = 12: 1.45 -> 0.53 ms.  The matrix pipe is busy for 27 / 38 % of the
+// time (weights / values: 1.5 rounds of weight tiles, one wave per SIMD); waves spend 64 to 72 % of their cycles in waits for LDS,
+// L2 and the barrier.
 #include "fipa_gfx950.h"
 
 namespace fipa {
@@ -47,19 +44,17 @@ __device__ __forceinline__ int first_block(int row0, int nblk) { return min((row
 // ---------------------------------------------------------------------------------------------------------------
 template <int DZ>
 struct FwCfg {
-    // width 576: two waves per SIMD; at 1088 the query fragments alone are 272 registers
-    static constexpr int NW = DZ <= 512 ? 8 : 4, TQ = 32 * NW;
+    static constexpr int NW = 4, TQ = 32 * NW;                // (the query fragments alone are 272 registers)
     static constexpr int D = kDH + DZ, KS = D / 16, KSH = kDH / 16;
     static constexpr int ZB = DZ * 2, EPR = ZB / 1024;        // bytes of a pair-part row, 1 KiB loads per row
     static constexpr int NZW = 32 * EPR / NW;
     static constexpr int ZP = ZB + 16;                        // LDS row pitch: 16 rows start in 16 different slots of the banks
     static constexpr int H_OFF = 32 * ZP, KB_OFF = H_OFF + 4096;
     static constexpr int STAGE = KB_OFF + 1024;
-    static constexpr int NST = 4 * STAGE + DZ * 4 <= 160 * 1024 ? 4 : (3 * STAGE + DZ * 4 <= 160 * 1024 ? 3 : 2);
+    static constexpr int NST = 2;
     static constexpr int CW_OFF = NST * STAGE;                // per-head scale vector of the query-side factors
     static constexpr int LDS_BYTES = CW_OFF + DZ * 4;
     static constexpr int NDMA = NZW + 2;
-    static constexpr bool REF = NW == 8;                      // first references from the blocks in the ring, else from the wave's own
     static_assert(EPR >= 1 && LDS_BYTES <= 160 * 1024, "LDS");
 };
 
@@ -85,17 +80,11 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
     const size_t rows0 = (size_t)bh * p.Lp;
     const int first = first_block(row0, nblk);
     auto block = [&](int n) { const int x = first + n; return x >= nblk ? x - nblk : x; };  // n-th block of the walk, n < nblk
-    // The blocks around the workgroup's own residues come first, for the references alone (REF); then the walk.
-    const int ref0 = max(row0 / 32 - 1, 0), nref = C::REF ? min(row0 / 32 + C::NW + 1, nblk) - ref0 : 0, total = nref + nblk;
-    auto key_block = [&](int n) {  // n < total
-        if constexpr (!C::REF) return block(n);
-        else return n < nref ? ref0 + n : block(n - nref);
-    };
 
     // ---- direct loads ---------------------------------------------------------------------------------------------
     const u32x4 r_z = buffer_desc(p.Z2 + (size_t)b * p.Lp * DZ), r_h = buffer_desc(p.Kh + rows0 * kDH), r_b = buffer_desc(p.kbias + rows0);
     const int vz = lane * 16, vb = min(lane, 7) * 16;
-    const int hrow = 8 * (wave & 3) + (lane >> 3);
+    const int hrow = 8 * wave + (lane >> 3);
     const int vh = hrow * 128 + ((lane & 7) ^ ((hrow >> 1) & 7)) * 16;
     const unsigned lds0 = lds_address(smem);
     auto issue = [&](auto Kc, int kb, unsigned stage) {
@@ -104,13 +93,13 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
             const int e = wave + C::NW * K, row = e / C::EPR, part = e % C::EPR;
             dma16b(r_z, vz, (32 * kb + row) * C::ZB + 1024 * part, stage + row * C::ZP + 1024 * part);
         } else if constexpr (K == C::NZW) {
-            dma16b(r_h, vh, 32 * kb * 128, stage + C::H_OFF + 1024 * (wave & 3));  // (eight waves: twice the same)
+            dma16b(r_h, vh, 32 * kb * 128, stage + C::H_OFF + 1024 * wave);
         } else {
             dma16b(r_b, vb, 32 * kb * 4, stage + C::KB_OFF);
         }
     };
     auto issue_all = [&](int n, unsigned stage) {
-        const int kb = key_block(min(n, total - 1));
+        const int kb = block(min(n, nblk - 1));
         static_for<C::NDMA>([&](auto K) { issue(K, kb, stage); });
     };
 #pragma unroll
@@ -132,19 +121,18 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
         float *cw = reinterpret_cast<float *>(smem + C::CW_OFF);
         for (int x = tid; x < DZ; x += 64 * C::NW) cw[x] = kLog2e * p.w_L * p.w_b[(size_t)h * p.cz + x % p.cz];
         __syncthreads();
-        // (!REF: S^T of the wave's own 32 keys, row li of that block is this lane's residue)
+        // (S^T of the wave's own 32 keys, row li of that block is this lane's residue)
         f32x16 own;
-        if constexpr (!C::REF)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = row0 + 32 * wave + 8 * (r >> 2) + 4 * g + (r & 3);
-                const float kb = p.kbias[rows0 + min(key, p.Lp - 1)];
-                own[r] = key < kvlen ? kb : kNegInf;
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int key = row0 + 32 * wave + 8 * (r >> 2) + 4 * g + (r & 3);
+            const float kb = p.kbias[rows0 + min(key, p.Lp - 1)];
+            own[r] = key < kvlen ? kb : kNegInf;
+        }
         const bf16_t *qh = p.Qh + (rows0 + irow_p) * kDH + 8 * g, *kh = p.Kh + (rows0 + irow_p) * kDH + 8 * g;
         const bf16_t *z2 = p.Z2 + ((size_t)b * p.Lp + irow_p) * DZ + 8 * g;
         auto dot = [&](int ks, const bf16_t *k) {
-            if constexpr (!C::REF) own = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(k), qf[ks], own, 0, 0, 0);
+            own = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(k), qf[ks], own, 0, 0, 0);
         };
 #pragma unroll
         for (int ks = 0; ks < KSH; ++ks) {
@@ -170,7 +158,7 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
             qf[KSH + ks] = __builtin_bit_cast(bf16x8, (u32x4){pk[0], pk[1], pk[2], pk[3]});
             dot(KSH + ks, z2 + 16 * ks);
         }
-        if constexpr (!C::REF) m = largest(own);
+        m = largest(own);
         if (irow >= kvlen) m = INFINITY;  // (a row past the chain: whatever its memory holds, weights 0 and no raise)
     }
     constexpr int kPin = KS - KSH < 64 ? KS - KSH : 64;
@@ -237,8 +225,8 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
         int nidx = sidx + C::NST - 1;
         nidx = nidx >= C::NST ? nidx - C::NST : nidx;
         const unsigned next = lds0 + nidx * C::STAGE;
-        const int next_kb = key_block(min(n + C::NST - 1, total - 1));
-        const int before_n = firstb ? 0 : n - 1 - nref;  // position of the block before in the walk
+        const int next_kb = block(min(n + C::NST - 1, nblk - 1));
+        const int before_n = firstb ? 0 : n - 1;  // position of the block before in the walk
         char *const dst = wbase + (size_t)(2 * block(before_n)) * kGrpBytes;
         static_for<KS>([&](auto J) {
             constexpr int j = decltype(J)::value;
@@ -275,34 +263,10 @@ __global__ __launch_bounds__(64 * FwCfg<DZ>::NW, FwCfg<DZ>::NW / 4) void fipa_fw
     using T = std::true_type;
     using F = std::false_type;
     constexpr int kAhead = (C::NST - 2) * C::NDMA;
-    if constexpr (C::REF)  // each wave takes its own block and the two beside it
-        for (int n = 0; n < nref; ++n) {
-            wait_and_barrier<kAhead>();
-            const char *st = smem + sidx * C::STAGE;
-            int nidx = sidx + C::NST - 1;
-            nidx = nidx >= C::NST ? nidx - C::NST : nidx;
-            issue_all(n + C::NST - 1, lds0 + nidx * C::STAGE);
-            const int apart = ref0 + n - (row0 / 32 + wave);
-            if (apart >= -1 && apart <= 1) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 kb4 = *reinterpret_cast<const f32x4 *>(st + C::KB_OFF + (8 * q + 4 * g) * 4);
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) sacc[4 * q + x] = kb4[x];
-                }
-                static_for<KS>([&](auto J) {
-                    constexpr int j = decltype(J)::value;
-                    const char *a = j < KSH ? st + (ah ^ (32 * (j & 3))) : st + az + (j - KSH) * 32;
-                    sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(a), qf[j], sacc, 0, 0, 0);
-                });
-                m = fmaxf(m, largest(sacc));
-            }
-            sidx = sidx + 1 < C::NST ? sidx + 1 : 0;
-        }
     wait_and_barrier<kAhead>();
-    step(T{}, nref);
-    for (int n = nref + 1; n < total; ++n) {
-        if (n == nref + 1) wait_and_barrier<kAhead>();
+    step(T{}, 0);
+    for (int n = 1; n < nblk; ++n) {
+        if (n == 1) wait_and_barrier<kAhead>();
         else wait_and_barrier<kAhead + kStores>();  // (the newest operations are the stores of the block before last)
         step(F{}, n);
     }
@@ -662,26 +626,19 @@ int fwd_stored_slice_blocks(int DZ, int cz)
 hipError_t launch_attn_fwd_stored_bf16(const FwdStoredParams &p0, int DZ, bool fused, hipStream_t stream)
 {
     const int hb = fused ? fwd_stored_slice_blocks(DZ, p0.cz) : 0;
-    if ((DZ != 512 && DZ != 1024) || (fused && hb == 0)) return hipErrorInvalidValue;
+    if (DZ != 1024 || (fused && hb == 0)) return hipErrorInvalidValue;
     for (int i0 = 0; i0 < p0.Lp; i0 += p0.nq_alloc) {
         FwdStoredParams p = p0;
         p.i0 = i0;
         p.nq = p0.Lp - i0 < p0.nq_alloc ? p0.Lp - i0 : p0.nq_alloc;
-        const int tq = DZ == 512 ? FwCfg<512>::TQ : FwCfg<1024>::TQ;
-        p.units = p.B * p.H * ((p.nq + tq - 1) / tq);
-        hipError_t e = DZ == 512 ? launch_weights<512>(p, stream) : launch_weights<1024>(p, stream);
+        p.units = p.B * p.H * ((p.nq + FwCfg<1024>::TQ - 1) / FwCfg<1024>::TQ);
+        hipError_t e = launch_weights<1024>(p, stream);
         if (e != hipSuccess) return e;
         p.units = p.B * p.H * ((p.nq + kTile - 1) / kTile);
-        if (DZ == 512)
-            e = hb == 1   ? launch_values<512, 1>(p, stream)
-                : hb == 2 ? launch_values<512, 2>(p, stream)
-                : hb == 4 ? launch_values<512, 4>(p, stream)
-                          : launch_values<512, 0>(p, stream);
-        else
-            e = hb == 1   ? launch_values<1024, 1>(p, stream)
-                : hb == 2 ? launch_values<1024, 2>(p, stream)
-                : hb == 4 ? launch_values<1024, 4>(p, stream)
-                          : launch_values<1024, 0>(p, stream);
+        e = hb == 1   ? launch_values<1024, 1>(p, stream)
+            : hb == 2 ? launch_values<1024, 2>(p, stream)
+            : hb == 4 ? launch_values<1024, 4>(p, stream)
+                      : launch_values<1024, 0>(p, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

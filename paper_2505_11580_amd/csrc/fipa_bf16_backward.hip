@@ -525,7 +525,7 @@ BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
     if (fwd_stored_pays(d)) {  // (its weights lie where the gradient part begins, which is not yet in use)
         const size_t fwd = fwd_stored_layout(d, w.f.Lp, w.f.total).total;
         if (fwd > w.total) w.total = fwd;
-        w.fwd_stored = bytes >= fwd;
+        w.fwd_stored = w.f.DZ != 512 && bytes >= fwd;
     }
     return w;
 }
@@ -613,7 +613,9 @@ hipError_t backward_forward_part(const fipa_desc &d, const FwdArgs &f, const Bwd
     if (w.fwd_stored)
         e = launch_attn_fwd_stored_bf16(fwd_stored_params(d, at, fwd_stored_layout(d, w.f.Lp, w.f.total), base), w.f.DZ, false, stream);
     else
-        e = w.f.DZ > 256 ? launch_attn_fwd_wide_bf16(at, w.f.DZ, false, stream) : launch_attn_fwd_bf16(at, w.f.DZ, false, stream);
+        e = attn_fwd_576_pays(at, w.f.DZ) ? launch_attn_fwd_576_bf16(at, false, stream)
+            : w.f.DZ > 256               ? launch_attn_fwd_wide_bf16(at, w.f.DZ, false, stream)
+                                         : launch_attn_fwd_bf16(at, w.f.DZ, false, stream);
     if (e != hipSuccess || !f.o) return e;
 
     EpiParams ep;

@@ -156,17 +156,18 @@ inline SplitPlan attn_split_plan(int total_tiles, int Lp, int DZ, int cz, bool f
 // neighbours, and with chains of different lengths (a masked batch) whole XCDs would get only
 // long or only short chains (lengths 5.8k, 7.5k, 7.5k, 1.6k at H = 12: four XCDs with 1.5 times
 // the mean work, two with almost none).  deal_pair() renumbers the pairs so that position
-// `pos` of the contiguous order holds pair x, x + 8, x + 16, ... for the x-th run: every XCD
-// gets pairs of every batch element.  A bijection on [0, P) for any P.
+// `pos` of the contiguous order holds pair x, 15 - x, 16 + x, 31 - x, ... for the x-th run (a last incomplete group of 8
+// in order): every XCD gets pairs of every batch element, and none the longer one of every group (x, x + 8, x + 16, ..: four XCDs with
+// 1.10 times the mean work on four chains of 2.7k to 7.1k residues, now 1.03).  A bijection on [0, P) for any P.
 __device__ __forceinline__ int deal_pair(int pos, int P)
 {
     int x = 0;
     for (; x < 7; ++x) {
-        const int n = (P - x + 7) / 8;  // pairs with index = x (mod 8)
+        const int n = (P - x + 7) / 8;  // pairs of the x-th run
         if (pos < n) break;
         pos -= n;
     }
-    return x + 8 * pos;
+    return 8 * pos + ((pos & 1) && 8 * pos + 8 <= P ? 7 - x : x);
 }
 
 // The pair that a masked batch's position `pos` of the contiguous order works on: the batch
@@ -301,7 +302,7 @@ struct EpiParams {
     int B, L, Lp, H, c, Pv, cz, r, DZ;
 };
 
-// The forward of r c_z = 512 and 1024 with the weights of a range of query rows in memory (fipa_bf16_attn_fwd_stored.hip).
+// The forward of r c_z = 1024 with the weights of a range of query rows in memory (fipa_bf16_attn_fwd_stored.hip).
 struct FwdStoredParams {
     const bf16_t *Qh, *Kh, *Vh, *Z2;
     const float *kbias, *qbias;
@@ -367,10 +368,10 @@ inline FwdStoredLayout fwd_stored_layout(const fipa_desc &d, int Lp, size_t off)
     return w;
 }
 // Whether the call has enough work for it: two launches whose workgroups hold a compute unit each against one.  In units of
-// (256 queries) x (32 keys) over all pairs, stored against windowed at width 576, H = 12: 1536 (one chain of 1024) 129 / 72 us,
-// 2304 (8 x 384) 115 / 109, 3072 (8 x 512) 132 / 134, 3600 (5 x 631) 141 / 143, 6144 (4 x 1024) 183 / 204, 6144 (one of 2048) 204 / 223.
-// At width 1088, stored against windowed: 48 (one chain of 128) 53 / 48 us, 96 (256) 68 / 66, 384 (8 x 128) 76 / 101, 384 (512) 90 / 95.
-// (All at H = 12; the heads enter through the number of pairs alone.)
+// (256 queries) x (32 keys) over all pairs, stored against windowed: 48 (one chain of 128) 53 / 48 us, 96 (256) 68 / 66,
+// 384 (8 x 128) 76 / 101, 384 (512) 90 / 95.  (At H = 12; the heads enter through the number of pairs alone.)
+// At r c_z = 512 it only says how much workspace the query asks for: what it asked for when that width stored its weights
+// as well (callers size and share workspaces by it); the call runs in the least.
 inline bool fwd_stored_pays(const fipa_desc &d)
 {
     const long long Lp = (long long)align_up((size_t)d.L, kTileQ), work = (long long)d.B * d.H * ((Lp + 255) / 256) * (Lp / 32);
@@ -486,6 +487,11 @@ hipError_t launch_attn_fwd_bf16(const AttnParams &p, int DZ, bool fused, hipStre
 bool attn_fwd_ws_supported(int DZ, int cz);  // shapes of the wave-specialised fused kernel
 hipError_t launch_attn_fwd_ws_bf16(const AttnParams &p, int DZ, hipStream_t stream);
 hipError_t launch_attn_fwd_wide_bf16(const AttnParams &p, int DZ, bool fused, hipStream_t stream);  // r*cz = 512
+hipError_t launch_attn_fwd_576_bf16(const AttnParams &p, bool fused, hipStream_t stream);  // the same in one pass
+// Where it is the faster one of the two: the windowed kernel splits a tile of 128 queries over two workgroups, so that up to 128 tiles
+// take it one round of shorter workgroups.  Windowed / one pass, H = 12: one chain of 300 residues (36 tiles) 37 / 47 us, of 1024 (96)
+// 71 / 82; of 2048 (192) 223 / 132, 8 x 512 (384) 134 / 112.
+inline bool attn_fwd_576_pays(const AttnParams &p, int DZ) { return DZ == 512 && p.total_tiles > 128; }
 hipError_t launch_attn_fwd_stored_bf16(const FwdStoredParams &p, int DZ, bool fused, hipStream_t stream);
 hipError_t launch_epilogue_bf16(const EpiParams &p, hipStream_t stream);
 

@@ -5,8 +5,9 @@ namespace fipa {
 
 namespace {
 
-// r c_z = 512 and 1024: with the weights of a range of query rows in memory (fipa_bf16_attn_fwd_stored.hip) where the
+// r c_z = 1024: with the weights of a range of query rows in memory (fipa_bf16_attn_fwd_stored.hip) where the
 // workspace holds them and the call is large enough, else with S^T formed again for every window of the columns.
+// r c_z = 512: in one pass (fipa_bf16_attn_fwd_576.hip), small calls in windows.
 bool stored_fused(const fipa_desc &d) { return d.c == 16 && d.Pv == 8 && fwd_stored_slice_blocks(d.r * d.cz, d.cz) > 0; }
 bool windowed_fused(const fipa_desc &d) { return bf16_fused_epilogue(d) || bf16_wide_fused_epilogue(d); }
 
@@ -43,7 +44,7 @@ FwdStoredParams fwd_stored_params(const fipa_desc &d, const AttnParams &at, cons
 
 hipError_t bf16_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
 {
-    const bool stored = fwd_stored_pays(d) && ws_bytes >= stored_workspace(d);
+    const bool stored = d.r * d.cz == 1024 && fwd_stored_pays(d) && ws_bytes >= stored_workspace(d);
     const bool wide_fused = stored ? stored_fused(d) : bf16_wide_fused_epilogue(d);
     const bool fused = bf16_fused_epilogue(d);
     const Bf16Layout w = bf16_layout(d, !(fused || wide_fused));
@@ -102,7 +103,7 @@ hipError_t bf16_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t w
     if (stored)
         e = launch_attn_fwd_stored_bf16(fwd_stored_params(d, at, fwd_stored_layout(d, w.Lp, w.total), base), w.DZ, wide_fused, stream);
     else
-        e = w.DZ > 256 ? launch_attn_fwd_wide_bf16(at, w.DZ, wide_fused, stream)
+        e = attn_fwd_576_pays(at, w.DZ) ? launch_attn_fwd_576_bf16(at, wide_fused, stream) : w.DZ > 256 ? launch_attn_fwd_wide_bf16(at, w.DZ, wide_fused, stream)
             : ws_kernel ? launch_attn_fwd_ws_bf16(at, w.DZ, stream)
                         : launch_attn_fwd_bf16(at, w.DZ, fused, stream);
     if (e != hipSuccess) return e;

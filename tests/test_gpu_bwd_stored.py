@@ -65,3 +65,8 @@ def test_backward_width128_in_the_least_workspace(kw):
     with pytest.raises(binding.FipaError) as e:
         binding.backward(desc, dev, out, grads)
     assert e.value.code == binding.FIPA_ERR_WORKSPACE
+
+
+def test_backward_behind_the_one_pass_forward():
+    # r c_z = 512 with more than 128 tiles of queries: O^ and the log-sum-exp come from the one-pass forward
+    check_backward(wl.make_inputs(4, B=11, L=100, H=12, cz=128, r=4, varlen=True, min_len=40, trans_scale=0.3), "bwd behind the one-pass forward")

@@ -1,4 +1,4 @@
-"""GPU parity of the forward that keeps its weights in memory (r c_z = 512 and 1024): edges of its tiles (32 keys, 256
+"""GPU parity of the wide forwards (r c_z = 512 in one pass, 1024 with its weights in memory): edges of their tiles (32 keys, 128 and 256
 queries, 128 padded rows), rows whose softmax reference is raised many times, several ranges of query rows, and the
 static entry point where the scratch does not hold the weights, against the CPU oracle (2e-2, the bf16 tolerance)."""
 import numpy as np
@@ -170,3 +170,23 @@ def test_forward_stored_weights_dominant_weight_is_exact():
     print("dominant weight: %d rows, rms %.2e, max %.2e" % (rows.sum(), np.sqrt((err ** 2).mean()), np.abs(err).max()), flush=True)
     assert rows.sum() > 10000
     assert np.sqrt((err ** 2).mean()) <= 1.9e-3
+
+
+@pytest.mark.parametrize("kw", [
+    dict(L=1, B=12), dict(L=31, B=12), dict(L=32, B=11, cz=64, r=8), dict(L=33, B=11, cz=256, r=2), dict(L=97, B=11), dict(L=129, B=6, c=8, Pq=2, Pv=3),
+    dict(L=200, B=12, varlen=True, min_len=1)])
+def test_forward_one_pass(kw):
+    # more than 128 tiles of queries, of one to seven key blocks (of which up to six are looked at twice)
+    inp = wl.make_inputs(3, **dict(dict(B=1, H=12, cz=128, r=4, varlen=False, trans_scale=0.3), **kw))
+    gu.check(inp, rows=wl.select_rows(inp, 12), label="fwd one pass %s" % kw)
+
+
+def test_forward_one_pass_masked_blocks():
+    # rows whose own 96 keys are masked, or all but a few of the chain's: no reference until a block holds a valid key
+    inp = wl.make_inputs(3, B=6, L=300, H=12, cz=128, r=4, varlen=True, min_len=300)
+    inp["mask"][:, :] = 1
+    inp["mask"][0, :290] = 0
+    inp["mask"][1, 10:] = 0
+    inp["mask"][2, 64:200] = 0
+    inp["mask"][3, :] = np.random.default_rng(2).random(300) < 0.1
+    gu.check(inp, rows=wl.select_rows(inp, 24), label="fwd one pass, masked blocks")
