@@ -403,7 +403,8 @@ __device__ __forceinline__ f32x4 xchg_load(__amdgpu_buffer_rsrc_t rs, int off)
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kXchgPolicy));
 }
 
-template <int DZ, bool FUSED>
+// KEEP (with FUSED; never split): the lifted output and the log2 log-sum-exp are left in memory as well, for the gradients.
+template <int DZ, bool FUSED, bool KEEP = false>
 __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p)
 {
     using C = AttnCfg<DZ>;
@@ -781,6 +782,17 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
         // ---- split, inverse frame, z1 contraction (Algorithm 1 steps 8-9, Eq. 4); c = 16, Pv = 8
         // First everything that is linear in the accumulator, still unnormalised:
         //   the scalar columns, the global points (hi + lo parts), and the contraction with z1.
+        if constexpr (KEEP) {
+            const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+            float *orow = p.Ohat + ((size_t)bh * p.Lp + irow) * C::DV + 4 * g;
+#pragma unroll
+            for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    *reinterpret_cast<f32x4 *>(orow + 32 * nb + 8 * a) =
+                        (f32x4){oacc[nb][4 * a] * inv, oacc[nb][4 * a + 1] * inv, oacc[nb][4 * a + 2] * inv, oacc[nb][4 * a + 3] * inv};
+            if (g == 0) p.lse2[(size_t)bh * p.Lp + irow] = l_tot > 0.f ? w.m_ref + __log2f(l_tot) : -INFINITY;
+        }
         constexpr int c = 16, Pv = 8;
         constexpr int NZB = C::NB - C::NBH;  // 32-column blocks of the pair part
         const bool in_range = irow < ulen;
@@ -800,7 +812,10 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
         }
         // pair part: o~[d'] = sum_rho z1[rho, d'] * U[rho, d']; the lane holds columns 8a + 4g + x
         {
-            wait_vmem<0>();  // the z1 rows staged before the drain (this wave's own loads, no barrier needed)
+            // the z1 rows staged before the drain (this wave's own loads, no barrier needed; the stores behind them may take their time)
+            static_assert(4 * C::NB < 63, "counter");
+            if constexpr (KEEP) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * C::NB) : "memory");
+            else wait_vmem<0>();
             asm volatile("" ::: "memory");
             constexpr int kCpr = DZ / 8;
             const char *z1l = smem + z1_off + li * (DZ * 2) + 8 * g;
@@ -833,7 +848,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
         // arrives last merges all parts of the tile.  Every exchanged word is written and read
         // with device-scope atomic accesses (which go to the coherence point, not through the
         // non-coherent caches); a part's words are complete (vmcnt = 0) before it takes its ticket.
-        if (nparts > 1) {
+        if (!KEEP && nparts > 1) {
             // per lane: 2 groups of scalars, 3 of point coordinates, 1 of (m, l), 4 per pair block
             const int groups = attn_partial_groups(cz);
             // wave-uniform base: this wave's rows in part 0 of the tile; byte offsets within 32 bits
@@ -990,17 +1005,17 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
     }
 }
 
-template <int DZ, bool FUSED>
+template <int DZ, bool FUSED, bool KEEP = false>
 hipError_t launch(const AttnParams &p, hipStream_t stream)
 {
     using C = AttnCfg<DZ>;
     static LdsLimit lds_limit;
-    hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_attn_fwd_bf16_kernel<DZ, FUSED>, C::LDS_BYTES);
+    hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_attn_fwd_bf16_kernel<DZ, FUSED, KEEP>, C::LDS_BYTES);
     if (e != hipSuccess) return e;
     if (p.plan.full % 8 != 0 || p.plan.full + p.plan.rem != p.total_tiles || p.plan.S < 1 ||
-        (p.plan.S > 1 && (!FUSED || p.cz < 32)))
+        (p.plan.S > 1 && (!FUSED || KEEP || p.cz < 32)))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL((fipa_attn_fwd_bf16_kernel<DZ, FUSED>), dim3(p.plan.units()), dim3(256),
+    hipLaunchKernelGGL((fipa_attn_fwd_bf16_kernel<DZ, FUSED, KEEP>), dim3(p.plan.units()), dim3(256),
                        C::LDS_BYTES, stream, p);
     return hipGetLastError();
 }
@@ -1020,6 +1035,17 @@ hipError_t launch_attn_fwd_bf16(const AttnParams &p, int DZ, bool fused, hipStre
         case 64: return launch_dz<64>(p, fused, stream);
         case 128: return launch_dz<128>(p, fused, stream);
         case 256: return launch_dz<256>(p, fused, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_attn_fwd_keep_bf16(const AttnParams &p, int DZ, hipStream_t stream)
+{
+    switch (DZ) {
+        case 32: return launch<32, true, true>(p, stream);
+        case 64: return launch<64, true, true>(p, stream);
+        case 128: return launch<128, true, true>(p, stream);
+        case 256: return launch<256, true, true>(p, stream);
         default: return hipErrorInvalidValue;
     }
 }

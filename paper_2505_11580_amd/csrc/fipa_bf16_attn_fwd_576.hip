@@ -381,8 +381,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_576_kernel(AttnParams p)
     const bool live = nblk > 0 && irow < kvlen;
     const float lt = l + __shfl_xor(l, 32), inv = live && lt > 0.f ? 1.f / lt : 0.f;
     const float lse2 = lt > 0.f ? m + __log2f(lt) : kNegInf;
-    if constexpr (HB == 0) {
-        if (!live) return;
+    if ((HB == 0 || p.Ohat) && live) {  // the lifted output (HB > 0: beside the outputs, for the gradients)
         if (g == 0) p.lse2[rows0 + irow] = lse2;
         float *orow = p.Ohat + (rows0 + irow) * D + 4 * g;
 #pragma unroll
@@ -396,7 +395,8 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_576_kernel(AttnParams p)
             *reinterpret_cast<f32x4 *>(orow + kDH + r / 16 * 32 + 8 * (r / 4 % 4)) =
                 (f32x4){acc_value<r>() * inv, acc_value<r + 1>() * inv, acc_value<r + 2>() * inv, acc_value<r + 3>() * inv};
         });
-    } else {
+    }
+    if constexpr (HB > 0) {
         if (irow >= ulen) return;
         const bool valid = live && inv > 0.f && (p.mask ? p.mask[urow0 + irow] != 0 : true);
         const float sc = valid ? inv : 0.f;

@@ -11,76 +11,159 @@ namespace fipa {
 
 namespace {
 
-// One wave per (batch, head, residue < Lp): lifted upstream gradient row, D_i, and -lse.
-// Lane l takes head-specific column l and the four pair columns 4 l' .. 4 l' + 3 of each group of
-// 256 (l' = l), so that the pair part moves in 16-byte (fp32) and 8-byte (bf16) pieces and all loads
-// of a row are independent of each other.
-__global__ __launch_bounds__(256) void fipa_bwd_pack_bf16_kernel(BwdPackParams p)
+// Lanes of a wave that owns a residue: NG of them hold four neighbouring pair columns each (of every 256 where the lifted width
+// is larger), the 64 / NG groups take every (64 / NG)-th head.  NG = 64 where r c_z >= 256, else r c_z / 4 (at 64 the heads are the same
+// for all lanes, and the rows' addresses scalar).
+template <class F>
+hipError_t with_column_lanes(int DZ, F &&f)  // f(std::integral_constant<int, NG>{})
 {
-    const int lane = threadIdx.x & 63;
-    const size_t row_id = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // over B*H*Lp, i fastest
-    if (row_id >= (size_t)p.B * p.H * p.Lp) return;
-    const int i = (int)(row_id % p.Lp);
-    const size_t bh = row_id / p.Lp;
-    const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    switch (DZ) {
+        case 32: f(std::integral_constant<int, 8>{}); break;
+        case 64: f(std::integral_constant<int, 16>{}); break;
+        case 128: f(std::integral_constant<int, 32>{}); break;
+        default: f(std::integral_constant<int, 64>{}); break;
+    }
+    return hipGetLastError();
+}
+
+__device__ __forceinline__ f32x4 bf16x4_to_f32(uint2 v)
+{
+    return (f32x4){__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xFFFF0000u)};
+}
+__device__ __forceinline__ unsigned bf16_pair(float lo, float hi) { return (unsigned)f2bf(lo) | ((unsigned)f2bf(hi) << 16); }
+
+// One workgroup per (batch, residue < Lp): the lifted upstream gradient rows of its heads, D_i, -lse, and the part of the gradient of
+// z1 that comes through o~ = z1^T U, sum_h d_o_pair (.) U: the lifted output passes by here once.  That sum, float32, lies in the
+// residue's rows of the outputs d_z1 (upper halves) and d_z2 (lower halves) until the unpack kernel writes them.
+// Four waves with every fourth head (group of heads) each; all loads of a wave's three heads are independent of each other and in
+// flight together.  The heads' sums meet in LDS in a fixed order.  Bound by memory: 30 KB per residue at H = 12, r c_z = 256.
+// B = 2, L = 4096, r c_z = 256: 65 us, 32 packed chains of 64 to 512 residues 75, four chains of 2.7k to 7.1k at r c_z = 512 239 (one wave
+// per head and residue, the sum for z1 left to the unpack kernel, which read the lifted output again: 71, 111, 245; one wave per
+// residue, four heads at a time: 93, 127, 314).
+template <int NG>
+__global__ __launch_bounds__(256, 4) void fipa_bwd_pack_bf16_kernel(BwdPackParams p)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.y, i = blockIdx.x;
     if (i >= ((p.kvlen[b] + 31) & ~31)) return;  // (the gradient kernels stream whole blocks of 32 rows and no further)
     const int c = p.c, D = kDH + p.DZ, PH = (p.Pv + 1) / 2;
-    const size_t urow = user_row(p, b, i);  // (only used where i < the chain's length)
-    const bool valid = i < user_len(p, b) && (p.mask ? p.mask[urow] != 0 : true);
-    const size_t rec = valid ? urow * p.H + h : 0;
-    const float *R = p.rot + (valid ? urow * 9 : 0);
-    const float *oh = p.Ohat + row_id * D;
-    bf16_t *dst = p.dOhat + row_id * D;
-    float dsum = 0.f;
-    // ---- pair part: columns kDH + 4 q, q = lane, lane + 64, ...
-    for (int q = lane; 4 * q < p.DZ; q += 64) {
-        const int x = 4 * q;
-        f32x4 val = {0.f, 0.f, 0.f, 0.f}, o4 = {0.f, 0.f, 0.f, 0.f};
-        if (valid) {
-            const uint2 zr = *reinterpret_cast<const uint2 *>(p.z1 + urow * p.DZ + x);  // four bf16 values
-            const f32x4 g4 = *reinterpret_cast<const f32x4 *>(p.d_o_pair + rec * p.cz + x % p.cz);  // (cz is a multiple of 8)
-            o4 = *reinterpret_cast<const f32x4 *>(oh + kDH + x);
-            val[0] = __uint_as_float(zr.x << 16) * g4[0];
-            val[1] = __uint_as_float(zr.x & 0xFFFF0000u) * g4[1];
-            val[2] = __uint_as_float(zr.y << 16) * g4[2];
-            val[3] = __uint_as_float(zr.y & 0xFFFF0000u) * g4[3];
-        }
-        __attribute__((aligned(8))) bf16_t bv[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            bv[e] = f2bf(val[e]);
-            dsum += bf2f(bv[e]) * o4[e];  // D uses the rounded gradient the MFMAs will see
-        }
-        *reinterpret_cast<uint2 *>(dst + kDH + x) = *reinterpret_cast<const uint2 *>(bv);
-    }
-    // ---- head-specific part: column `lane`
-    {
-        const int col = lane;
-        float val = 0.f;
-        if (valid) {
-            if (col < c) {
-                val = p.d_o[rec * c + col];
-            } else {
-                // inverse of v_pt_col: which (point, axis) lives in this column, if any
-                const int cp = col - c, within = cp & 7;
-                const int gh = within >> 2, u = 4 * (cp >> 3) + (within & 3);
-                const int lo = u / (3 * PH), u2 = u - lo * 3 * PH;
-                const int pt = gh * PH + u2 / 3, ax = u2 % 3;
-                if (lo < 2 && pt < p.Pv) {
-                    const float *g = p.d_o_pts + (rec * p.Pv + pt) * 3;
-                    val = R[3 * ax] * g[0] + R[3 * ax + 1] * g[1] + R[3 * ax + 2] * g[2];  // dG = R_i d_o_pts
-                }
+    constexpr int HG = 64 / NG;
+    const int grp = lane % NG, hg = wave * HG + (HG == 1 ? 0 : lane / NG);
+    const bool inside = i < user_len(p, b);
+    const size_t urow = inside ? user_row(p, b, i) : 0;
+    const bool valid = inside && (p.mask ? p.mask[urow] != 0 : true);
+    const size_t row0 = (size_t)b * p.H * p.Lp + i;  // (row of head h: h Lp further)
+    if (!valid) {  // zeros; nothing reads the sum of such a residue
+        for (int h = hg; h < p.H; h += 4 * HG) {
+            bf16_t *dst = p.dOhat + (row0 + (size_t)h * p.Lp) * D;
+            for (int x = 4 * grp; x < D; x += 4 * NG) *reinterpret_cast<uint2 *>(dst + x) = (uint2){0u, 0u};
+            if (grp == 0) {
+                p.Dvec[row0 + (size_t)h * p.Lp] = 0.f;
+                p.nlse[row0 + (size_t)h * p.Lp] = -INFINITY;
             }
         }
-        const bf16_t bv = f2bf(val);
-        dst[col] = bv;
-        dsum += bf2f(bv) * (valid ? oh[col] : 0.f);
+        return;
     }
-    for (int off = 32; off > 0; off >>= 1) dsum += __shfl_xor(dsum, off);
-    if (lane == 0) {
-        const float l2 = p.lse2[row_id];
-        p.Dvec[row_id] = p.neg_d ? -dsum : dsum;
-        p.nlse[row_id] = (valid && l2 > -INFINITY && l2 < INFINITY) ? -l2 : -INFINITY;
+    float R[9];
+#pragma unroll
+    for (int a = 0; a < 9; ++a) R[a] = p.rot[urow * 9 + a];
+    constexpr int NH = 3;  // heads at a time
+    f32x4 s1[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    for (int h0 = hg; h0 < p.H; h0 += 4 * NH * HG) {
+        float dsum[NH];
+        bool on[NH];
+        size_t row[NH], rec[NH];
+#pragma unroll
+        for (int u = 0; u < NH; ++u) {
+            const int h = h0 + u * 4 * HG;
+            on[u] = h < p.H;
+            row[u] = row0 + (size_t)(on[u] ? h : h0) * p.Lp;
+            rec[u] = urow * p.H + (on[u] ? h : h0);
+            dsum[u] = 0.f;
+        }
+        // ---- pair part: columns kDH + x .. + 3
+#pragma unroll
+        for (int set = 0; set < 2; ++set) {  // (r c_z <= 512)
+            const int x = 4 * grp + 256 * set;
+            if (x >= p.DZ) break;
+            const f32x4 z = bf16x4_to_f32(*reinterpret_cast<const uint2 *>(p.z1 + urow * p.DZ + x));
+            f32x4 g4[NH], o4[NH];
+#pragma unroll
+            for (int u = 0; u < NH; ++u) {
+                g4[u] = *reinterpret_cast<const f32x4 *>(p.d_o_pair + rec[u] * p.cz + x % p.cz);  // (cz is a multiple of 8)
+                o4[u] = *reinterpret_cast<const f32x4 *>(p.Ohat + row[u] * D + kDH + x);
+            }
+#pragma unroll
+            for (int u = 0; u < NH; ++u) {
+                bf16_t bv[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    bv[e] = f2bf(z[e] * g4[u][e]);
+                    dsum[u] += bf2f(bv[e]) * o4[u][e];  // D uses the rounded gradient the MFMAs will see
+                    s1[set][e] += on[u] ? g4[u][e] * o4[u][e] : 0.f;
+                }
+                if (on[u])
+                    *reinterpret_cast<uint2 *>(p.dOhat + row[u] * D + kDH + x) =
+                        (uint2){(unsigned)bv[0] | ((unsigned)bv[1] << 16), (unsigned)bv[2] | ((unsigned)bv[3] << 16)};
+            }
+        }
+        // ---- head-specific part: columns grp, grp + NG, ..
+        for (int col = grp; col < kDH; col += NG) {
+            // inverse of v_pt_col: which (point, axis) lives in this column, if any
+            const int cp = col - c, within = cp & 7;
+            const int gh = within >> 2, u1 = 4 * (cp >> 3) + (within & 3);
+            const int lo = u1 / (3 * PH), u2 = u1 - lo * 3 * PH;
+            const int pt = gh * PH + u2 / 3, ax = u2 % 3;
+            const bool scalar = col < c, point = !scalar && lo < 2 && pt < p.Pv;
+            const float r0 = ax == 0 ? R[0] : (ax == 1 ? R[3] : R[6]), r1 = ax == 0 ? R[1] : (ax == 1 ? R[4] : R[7]),
+                        r2 = ax == 0 ? R[2] : (ax == 1 ? R[5] : R[8]);
+            float o[NH], g[NH][3];
+#pragma unroll
+            for (int u = 0; u < NH; ++u) {
+                // (a scalar column takes its one number three times, a column without either the first of d_o)
+                const float *src = point ? p.d_o_pts + (rec[u] * p.Pv + pt) * 3 : p.d_o + rec[u] * c + (scalar ? col : 0);
+                const int st = point ? 1 : 0;
+                o[u] = p.Ohat[row[u] * D + col];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) g[u][a] = src[a * st];
+            }
+#pragma unroll
+            for (int u = 0; u < NH; ++u) {
+                const float val = scalar ? g[u][0] : (point ? r0 * g[u][0] + r1 * g[u][1] + r2 * g[u][2] : 0.f);  // dG = R_i d_o_pts
+                const bf16_t bv = f2bf(val);
+                if (on[u]) p.dOhat[row[u] * D + col] = bv;
+                dsum[u] += bf2f(bv) * o[u];
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+            if (o < NG)
+#pragma unroll
+                for (int u = 0; u < NH; ++u) dsum[u] += __shfl_xor(dsum[u], o);
+#pragma unroll
+        for (int u = 0; u < NH; ++u)
+            if (on[u] && grp == 0) {
+                const float l2 = p.lse2[row[u]];
+                p.Dvec[row[u]] = p.neg_d ? -dsum[u] : dsum[u];
+                p.nlse[row[u]] = l2 > -INFINITY && l2 < INFINITY ? -l2 : -INFINITY;
+            }
+    }
+    __shared__ f32x4 part[4][2][64];
+#pragma unroll
+    for (int set = 0; set < 2; ++set) {
+        for (int o = NG; o < 64; o <<= 1)  // (the head groups of a wave, added pairwise in a fixed order)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s1[set][e] += __shfl_xor(s1[set][e], o);
+        part[wave][set][lane] = s1[set];
+    }
+    __syncthreads();
+    const int set = wave, x = 4 * lane + 256 * set;
+    if (set < 2 && lane < NG && x < p.DZ) {
+        unsigned w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = __float_as_uint(((part[0][set][lane][e] + part[1][set][lane][e]) + part[2][set][lane][e]) + part[3][set][lane][e]);
+        *reinterpret_cast<uint2 *>(p.d_z1 + urow * p.DZ + x) = (uint2){(w[0] >> 16) | (w[1] & 0xFFFF0000u), (w[2] >> 16) | (w[3] & 0xFFFF0000u)};
+        *reinterpret_cast<uint2 *>(p.d_z2 + urow * p.DZ + x) = (uint2){(w[0] & 0xFFFFu) | (w[1] << 16), (w[2] & 0xFFFFu) | (w[3] << 16)};
     }
 }
 
@@ -93,19 +176,42 @@ __global__ __launch_bounds__(256) void fipa_bwd_pack_bf16_kernel(BwdPackParams p
 //   adds up the heads one after the other (16-byte loads of the four big arrays, all independent);
 //   where the lifted width is below 256 the lanes form 64 / (DZ / 4) groups that take every
 //   group-th head and are added at the end, above it a lane takes DZ / 256 sets of columns.
-// Measured at B = 2, L = 4096, H = 12, r c_z = 256 (about 520 MB moved): 0.139 ms; the pair-factor part
-// alone 0.099 ms (5.1 TB/s); the earlier form, one workgroup per residue with the sums of its threads
-// meeting in LDS behind workgroup barriers, 0.191 ms.
+// A residue that does not count reads nothing and writes zeros.
+// Measured at B = 2, L = 4096, H = 12, r c_z = 256 (330 MB moved): 80 us; 32 packed chains of 64 to 512 residues 102; four chains of 2.7k to
+// 7.1k residues padded to 8192, r c_z = 512, 307 (with the lifted output read here as well, and for padding too: 108, 138, 670).
+// One workgroup per residue with the sums of its threads meeting in LDS behind workgroup barriers was slower (191 us against 139).
+template <int NG>
 __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackParams p)
 {
     const int lane = threadIdx.x & 63;
-    const long long rr = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);  // (b, i); uniform over the wave
+    const long long rr = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (b, i)
     if (rr >= (long long)p.B * p.L) return;
     const int b = (int)(rr / p.L), i = (int)(rr - (long long)b * p.L);
     const int c = p.c, Pq = p.Pq, Pv = p.Pv, nq = 3 * Pq, D = kDH + p.DZ;
     if (i >= user_len(p, b)) return;  // (packed batch: the grid covers the longest chain)
     const size_t urow = user_row(p, b, i);
     const bool valid = p.mask ? p.mask[urow] != 0 : true;
+    if (!valid) {  // (nothing was formed for it)
+        const int nc = p.H * c / 8, nk = p.H * Pq * 3, nv = p.H * Pv * 3;
+        for (int x = lane; x < nc; x += 64) {
+            const uint4 zero = {0u, 0u, 0u, 0u};
+            *reinterpret_cast<uint4 *>(p.d_q + urow * p.H * c + 8 * x) = zero;
+            *reinterpret_cast<uint4 *>(p.d_k + urow * p.H * c + 8 * x) = zero;
+            *reinterpret_cast<uint4 *>(p.d_v + urow * p.H * c + 8 * x) = zero;
+        }
+        for (int x = lane; x < nk; x += 64) p.d_q_pts[urow * nk + x] = p.d_k_pts[urow * nk + x] = 0;
+        for (int x = lane; x < nv; x += 64) p.d_v_pts[urow * nv + x] = 0;
+        for (int x = 4 * lane; x < p.DZ; x += 256) {
+            *reinterpret_cast<uint2 *>(p.d_z1 + urow * p.DZ + x) = (uint2){0u, 0u};
+            *reinterpret_cast<uint2 *>(p.d_z2 + urow * p.DZ + x) = (uint2){0u, 0u};
+        }
+        for (int h = lane; h < p.H; h += 64) p.gpart[((size_t)b * p.H + h) * p.Lp + i] = 0.f;
+        if (p.d_rot) {
+            if (lane < 3) p.d_trans[urow * 3 + lane] = 0.f;
+            if (lane < 9) p.d_rot[urow * 9 + lane] = 0.f;
+        }
+        return;
+    }
 
     // ---- per-head tasks ----------------------------------------------------------------------------
     const float *R = p.rot + urow * 9;
@@ -237,31 +343,28 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
 
     // ---- pair factors: sums over heads -------------------------------------------------------------
     {
-        const int NG = p.DZ >= 256 ? 64 : p.DZ / 4, HG = 64 / NG;  // lanes per set of columns, head groups
-        const int grp = lane % NG, hg = lane / NG;
+        constexpr int HG = 64 / NG;
+        const int grp = lane % NG, hg = HG == 1 ? 0 : lane / NG;
         for (int x0 = 4 * grp; x0 < p.DZ; x0 += 256) {
             const int d0 = x0 % p.cz;
             f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
             const float kscale = p.dVz ? kLn2 : 1.f, qscale = p.w_L * p.ds_inv;
-#pragma unroll 2
+            // through o~ = z1^T U (see the pack kernel)
+            const uint2 up = *reinterpret_cast<const uint2 *>(p.d_z1 + urow * p.DZ + x0), low = *reinterpret_cast<const uint2 *>(p.d_z2 + urow * p.DZ + x0);
+#pragma unroll 4
             for (int h = hg; h < p.H; h += HG) {
                 const size_t bh = (size_t)b * p.H + h;
                 const size_t row = (bh * p.Lp + i) * D + kDH + x0;
-                const size_t rec = urow * p.H + h;
                 const f32x4 dq = *reinterpret_cast<const f32x4 *>(p.dQhat + row);
                 const size_t zrow = (bh * p.Lp + i) * p.z_pitch + x0;
                 const f32x4 dk = *reinterpret_cast<const f32x4 *>(p.dKz + zrow);
                 f32x4 dv = {0.f, 0.f, 0.f, 0.f};
                 if (p.dVz) dv = *reinterpret_cast<const f32x4 *>(p.dVz + zrow);
-                const f32x4 oh = *reinterpret_cast<const f32x4 *>(p.Ohat + row);
                 const f32x4 wb = *reinterpret_cast<const f32x4 *>(p.w_b + (size_t)h * p.cz + d0);
-                const f32x4 dop = *reinterpret_cast<const f32x4 *>(p.d_o_pair + rec * p.cz + d0);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    // z1: through the bias vector b^{h1} = w_L w_b z1, and through o~ = z1^T U
-                    s1[e] += qscale * wb[e] * dq[e] + dop[e] * oh[e];
-                    // z2: as key feature (the log2e sits on the query side) and as value feature
-                    s2[e] += kscale * dk[e] + dv[e];
+                    s1[e] += qscale * wb[e] * dq[e];   // z1: through the bias vector b^{h1} = w_L w_b z1
+                    s2[e] += kscale * dk[e] + dv[e];   // z2: as key feature (the log2e sits on the query side) and as value feature
                 }
             }
             for (int o = NG; o < 64; o <<= 1)  // (HG > 1: the head groups, added pairwise in a fixed order)
@@ -271,13 +374,12 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
                     s2[e] += __shfl_xor(s2[e], o);
                 }
             if (hg == 0) {
-                uint2 o1, o2;
-                o1.x = (unsigned)f2bf(valid ? s1[0] : 0.f) | ((unsigned)f2bf(valid ? s1[1] : 0.f) << 16);
-                o1.y = (unsigned)f2bf(valid ? s1[2] : 0.f) | ((unsigned)f2bf(valid ? s1[3] : 0.f) << 16);
-                o2.x = (unsigned)f2bf(valid ? s2[0] : 0.f) | ((unsigned)f2bf(valid ? s2[1] : 0.f) << 16);
-                o2.y = (unsigned)f2bf(valid ? s2[2] : 0.f) | ((unsigned)f2bf(valid ? s2[3] : 0.f) << 16);
-                *reinterpret_cast<uint2 *>(p.d_z1 + urow * p.DZ + x0) = o1;
-                *reinterpret_cast<uint2 *>(p.d_z2 + urow * p.DZ + x0) = o2;
+                s1[0] += __uint_as_float((up.x << 16) | (low.x & 0xFFFFu));
+                s1[1] += __uint_as_float((up.x & 0xFFFF0000u) | (low.x >> 16));
+                s1[2] += __uint_as_float((up.y << 16) | (low.y & 0xFFFFu));
+                s1[3] += __uint_as_float((up.y & 0xFFFF0000u) | (low.y >> 16));
+                *reinterpret_cast<uint2 *>(p.d_z1 + urow * p.DZ + x0) = (uint2){bf16_pair(s1[0], s1[1]), bf16_pair(s1[2], s1[3])};
+                *reinterpret_cast<uint2 *>(p.d_z2 + urow * p.DZ + x0) = (uint2){bf16_pair(s2[0], s2[1]), bf16_pair(s2[2], s2[3])};
             }
         }
     }
@@ -378,8 +480,9 @@ __global__ __launch_bounds__(256) void fipa_bwd_wb_partial_kernel(BwdUnpackParam
             i = bi - b * p.L;
         }
         const bool valid = chunk * kWbChunk + t < nres && (p.mask ? p.mask[bi] != 0 : true);
-        const uint2 zr = *reinterpret_cast<const uint2 *>(p.z1 + (size_t)bi * p.DZ + x0);
-        const f32x4 dq = *reinterpret_cast<const f32x4 *>(p.dQhat + (((size_t)b * p.H + h) * p.Lp + i) * D + kDH + x0);
+        // (a residue that does not count takes the first row of all, so that the loads need no branch and padding costs no traffic)
+        const uint2 zr = *reinterpret_cast<const uint2 *>(p.z1 + (valid ? (size_t)bi * p.DZ : 0) + x0);
+        const f32x4 dq = *reinterpret_cast<const f32x4 *>(p.dQhat + (valid ? (((size_t)b * p.H + h) * p.Lp + i) * D : 0) + kDH + x0);
         if (valid) {
             s[0] += __uint_as_float(zr.x << 16) * dq[0];
             s[1] += __uint_as_float(zr.x & 0xFFFF0000u) * dq[1];
@@ -470,7 +573,6 @@ struct BwdLayout {
     int Lk, nq;           // keys per group of weights; query rows of which the given workspace holds the weights
     size_t parts, parts_bytes;  // what dS' alone leaves of the room of the weights: sums of the parts of a tile (see split_tiles)
     size_t least;         // what the calls run in (total: what the query asks for)
-    bool fwd_stored;      // the given workspace holds the forward's weights too
 };
 
 // `bytes`: the workspace that is laid out.
@@ -521,11 +623,9 @@ BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
         w.least = off;
     }
     w.total = off;
-    w.fwd_stored = false;
-    if (fwd_stored_pays(d)) {  // (its weights lie where the gradient part begins, which is not yet in use)
+    if (fwd_stored_pays(d)) {  // (no less than the forward's query)
         const size_t fwd = fwd_stored_layout(d, w.f.Lp, w.f.total).total;
         if (fwd > w.total) w.total = fwd;
-        w.fwd_stored = w.f.DZ != 512 && bytes >= fwd;
     }
     return w;
 }
@@ -534,15 +634,16 @@ BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
 
 hipError_t launch_bwd_pack_bf16(const BwdPackParams &p, hipStream_t stream)
 {
-    const size_t rows = (size_t)p.B * p.H * p.Lp;
-    hipLaunchKernelGGL(fipa_bwd_pack_bf16_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, p);
-    return hipGetLastError();
+    return with_column_lanes(p.DZ, [&](auto N) {
+        hipLaunchKernelGGL(fipa_bwd_pack_bf16_kernel<decltype(N)::value>, dim3(p.Lp, p.B), dim3(256), 0, stream, p);
+    });
 }
 
 hipError_t launch_bwd_unpack_bf16(const BwdUnpackParams &p, hipStream_t stream)
 {
-    hipLaunchKernelGGL(fipa_bwd_unpack_bf16_kernel, dim3((unsigned)(((long long)p.B * p.L + 3) / 4)), dim3(256), 0, stream, p);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = with_column_lanes(p.DZ, [&](auto N) {
+        hipLaunchKernelGGL(fipa_bwd_unpack_bf16_kernel<decltype(N)::value>, dim3((unsigned)(((long long)p.B * p.L + 3) / 4)), dim3(256), 0, stream, p);
+    });
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fipa_bwd_gamma_kernel, dim3(p.H), dim3(1024), 0, stream, p.gpart, p.d_gamma, p.B, p.H, p.L,
                        p.Lp, p.cu, -0.5f * p.w_L * p.w_C);
@@ -610,13 +711,17 @@ hipError_t backward_forward_part(const fipa_desc &d, const FwdArgs &f, const Bwd
     at.nQT = w.f.Lp / kTileQ; at.total_tiles = at.nQT * d.B * d.H; at.cz = d.cz; at.r = d.r; at.w_b = f.w_b; at.w_L = d.w_L;
     at.plan = w.f.plan; at.partial = nullptr; at.counters = nullptr;  // (unfused: never split)
     at.deal = f.mask != nullptr || f.cu != nullptr;
-    if (w.fwd_stored)
-        e = launch_attn_fwd_stored_bf16(fwd_stored_params(d, at, fwd_stored_layout(d, w.f.Lp, w.f.total), base), w.f.DZ, false, stream);
-    else
-        e = attn_fwd_576_pays(at, w.f.DZ) ? launch_attn_fwd_576_bf16(at, false, stream)
-            : w.f.DZ > 256               ? launch_attn_fwd_wide_bf16(at, w.f.DZ, false, stream)
-                                         : launch_attn_fwd_bf16(at, w.f.DZ, false, stream);
-    if (e != hipSuccess || !f.o) return e;
+    // Where steps 8-9 run on the accumulator the attention kernel leaves the outputs beside O^ (kept steps, module).
+    const bool one_pass = attn_fwd_576_pays(at, w.f.DZ);
+    const bool fused = f.o && (one_pass ? bf16_wide_fused_epilogue(d) : bf16_fused_epilogue(d));
+    if (fused) {
+        at.o = f.o; at.o_pts = f.o_pts; at.o_pair = f.o_pair; at.lse = f.lse;
+    }
+    e = one_pass          ? launch_attn_fwd_576_bf16(at, fused, stream)
+        : w.f.DZ > 256    ? launch_attn_fwd_wide_bf16(at, w.f.DZ, false, stream)
+        : fused           ? launch_attn_fwd_keep_bf16(at, w.f.DZ, stream)
+                          : launch_attn_fwd_bf16(at, w.f.DZ, false, stream);
+    if (e != hipSuccess || !f.o || fused) return e;
 
     EpiParams ep;
     ep.Ohat = at.Ohat; ep.lse2 = at.lse2; ep.qbias = pk.qbias; ep.rot = f.rot; ep.trans = f.trans;
@@ -643,7 +748,7 @@ hipError_t backward_gradient_part(const fipa_desc &d, const BwdArgs &a, const Bw
     bp.Ohat = Ohat; bp.lse2 = (float *)(base + w.f.lse2); bp.z1 = pk.z1; bp.mask = a.f.mask; bp.cu = a.f.cu;
     bp.dOhat = (bf16_t *)(base + w.dOhat); bp.Dvec = (float *)(base + w.Dvec); bp.nlse = (float *)(base + w.nlse);
     bp.B = d.B; bp.L = d.L; bp.Lp = w.f.Lp; bp.H = d.H; bp.c = d.c; bp.Pv = d.Pv; bp.cz = d.cz; bp.r = d.r;
-    bp.DZ = w.f.DZ;
+    bp.DZ = w.f.DZ; bp.d_z1 = (bf16_t *)a.d_z1; bp.d_z2 = (bf16_t *)a.d_z2;
     const bool stored = bwd_stored(w.f.DZ);
     bp.neg_d = stored; bp.kvlen = kvlen;
     hipError_t e = launch_bwd_pack_bf16(bp, stream);

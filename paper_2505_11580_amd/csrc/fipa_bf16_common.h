@@ -447,6 +447,7 @@ struct BwdPackParams {
     const uint8_t *mask;
     const int *cu;  // packed batch: row offsets of the chains (see user_row), else null
     bf16_t *dOhat;
+    bf16_t *d_z1, *d_z2;  // outputs of the call, which hold a float32 sum between them until the unpack kernel
     float *Dvec, *nlse;
     int B, L, Lp, H, c, Pv, cz, r, DZ;
     bool neg_d;  // store -D
@@ -484,6 +485,7 @@ hipError_t launch_bwd_unpack_bf16(const BwdUnpackParams &p, hipStream_t stream);
 
 hipError_t launch_pack_bf16(const PackParams &p, hipStream_t stream);
 hipError_t launch_attn_fwd_bf16(const AttnParams &p, int DZ, bool fused, hipStream_t stream);
+hipError_t launch_attn_fwd_keep_bf16(const AttnParams &p, int DZ, hipStream_t stream);  // fused, and O^ and lse2 as well
 bool attn_fwd_ws_supported(int DZ, int cz);  // shapes of the wave-specialised fused kernel
 hipError_t launch_attn_fwd_ws_bf16(const AttnParams &p, int DZ, hipStream_t stream);
 hipError_t launch_attn_fwd_wide_bf16(const AttnParams &p, int DZ, bool fused, hipStream_t stream);  // r*cz = 512

@@ -1,5 +1,6 @@
 // Split of the lifted output, inverse frame on the point part (Eq. 4) and contraction of the
-// pair part with z1 (Algorithm 1 steps 8-9).  Memory bound: one wave per (batch, head, row).
+// pair part with z1 (Algorithm 1 steps 8-9), for the shapes whose attention kernels do not do it on their accumulators.
+// Memory bound: one wave per (batch, head, row).
 #include "fipa_gfx950.h"
 
 namespace fipa {
