@@ -44,7 +44,7 @@ template <int NG>
 __global__ __launch_bounds__(256, 4) void fipa_bwd_pack_bf16_kernel(BwdPackParams p)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b = blockIdx.y, i = blockIdx.x;
+    const int b = blockIdx.x / (unsigned)p.Lp, i = blockIdx.x - (unsigned)b * p.Lp;
     if (i >= ((p.kvlen[b] + 31) & ~31)) return;  // (the gradient kernels stream whole blocks of 32 rows and no further)
     const int c = p.c, D = kDH + p.DZ, PH = (p.Pv + 1) / 2;
     constexpr int HG = 64 / NG;
@@ -635,7 +635,7 @@ BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
 hipError_t launch_bwd_pack_bf16(const BwdPackParams &p, hipStream_t stream)
 {
     return with_column_lanes(p.DZ, [&](auto N) {
-        hipLaunchKernelGGL(fipa_bwd_pack_bf16_kernel<decltype(N)::value>, dim3(p.Lp, p.B), dim3(256), 0, stream, p);
+        hipLaunchKernelGGL(fipa_bwd_pack_bf16_kernel<decltype(N)::value>, dim3((unsigned)p.Lp * p.B), dim3(256), 0, stream, p);
     });
 }
 
