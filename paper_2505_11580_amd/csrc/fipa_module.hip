@@ -4,7 +4,8 @@
 // against 117 GFLOP at B=2, L=2048, d_s=256), so one plain MFMA GEMM kernel serves them:
 //     C[M, N] = A[M, K] W[N, K]^T + bias[N]        (weights stored [out, in])
 // Two variations:
-//   - the input projection scatters its bf16 results into the six tensors the core takes;
+//   - the input projection scatters its bf16 results into the six tensors the core takes (the gradient
+//     of the concatenation its float32 results into the core's upstream gradients);
 //   - the output projection reads its A operand directly from the core's fp32 outputs, forming
 //     the concatenation (o_pair | o | o_pts | norms of o_pts) and the norms on the fly.
 #include "fipa_gfx950.h"
@@ -23,8 +24,8 @@ struct GemmParams {
     const float *o_pair, *o, *o_pts;  // [M, k_pair], [M, k_o], [M, k_pts]   (output projection)
     int k_pair, k_o, k_pts;           // K = k_pair + k_o + k_pts + k_pts / 3
     float *C;            // [M, N] float32                      (output projection)
-    bf16_t *seg_ptr[6];  // six row-major bf16 tensors [M, width] (input projection)
-    int seg_start[7];    // first column of each, and N
+    void *seg_ptr[6];    // up to six row-major tensors [M, width] that the columns go to (scattering products)
+    int seg_start[7];    // first column of each, and N (from the last one's end on)
     int chunks_per_split;  // 0: one workgroup sums all of K; else blockIdx.z takes this many K chunks
                            // and writes its partial product to C + blockIdx.z * M * N
 };
@@ -102,9 +103,11 @@ struct GemmTile {
     static constexpr int LDS_TOTAL = LDS_BYTES + TN * 4;   // + the tile's slice of the bias vector
 };
 
-template <class T, bool CONCAT_A, bool SCATTER>
+// Seg: type of the tensors that the columns are scattered to; void: one float32 matrix C.
+template <class T, bool CONCAT_A, class Seg>
 __global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
 {
+    constexpr bool SCATTER = !std::is_void_v<Seg>;
     extern __shared__ __attribute__((aligned(16))) char lds[];  // [buffer][A tile | W tile]
     constexpr int kBuf = (T::TM + T::TN) * kGRS;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -208,7 +211,7 @@ __global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
     // projection spent 6 of its 14 microseconds on them).  The tile goes through LDS instead, in
     // its final type, and leaves as 16-byte pieces that are neighbours along a row.
     // (The loop above ended with a barrier: both operand buffers are free.)
-    using OutT = std::conditional_t<SCATTER, bf16_t, float>;
+    using OutT = std::conditional_t<SCATTER, Seg, float>;
     constexpr int kPer = 16 / (int)sizeof(OutT);               // outputs per 16-byte piece
     constexpr int kORS = T::TN * (int)sizeof(OutT) + 16;       // LDS row stride of the staged tile
     static_assert(T::TM * kORS <= T::LDS_BYTES, "the staged output tile must fit the operand buffers");
@@ -224,7 +227,7 @@ __global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
 #pragma unroll
                 for (int x = 0; x < 4; ++x) val[x] = acc[a][b][4 * q + x] + bv[x];
                 char *dst = lds + rl * kORS + cl * (int)sizeof(OutT);
-                if constexpr (SCATTER) {
+                if constexpr (sizeof(OutT) == 2) {
                     const unsigned lo = (unsigned)f2bf(val[0]) | ((unsigned)f2bf(val[1]) << 16);
                     const unsigned hi = (unsigned)f2bf(val[2]) | ((unsigned)f2bf(val[3]) << 16);
                     *reinterpret_cast<uint2 *>(dst) = make_uint2(lo, hi);
@@ -247,13 +250,13 @@ __global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
                 if (col >= p.seg_start[sg]) seg = sg;
             const int start = p.seg_start[seg], width = p.seg_start[seg + 1] - start;
             if (col + kPer <= p.seg_start[seg + 1] && ((width | (col - start)) & (kPer - 1)) == 0) {
-                *reinterpret_cast<uint4 *>(p.seg_ptr[seg] + (size_t)row * width + (col - start)) = piece;
+                *reinterpret_cast<uint4 *>((OutT *)p.seg_ptr[seg] + (size_t)row * width + (col - start)) = piece;
             } else {
                 for (int x = 0; x < kPer && col + x < p.N; ++x) {  // a piece that crosses into the next tensor, or is not aligned
                     int sx = seg;
                     while (col + x >= p.seg_start[sx + 1]) ++sx;
                     const int wx = p.seg_start[sx + 1] - p.seg_start[sx];
-                    p.seg_ptr[sx][(size_t)row * wx + (col + x - p.seg_start[sx])] = vals[x];
+                    ((OutT *)p.seg_ptr[sx])[(size_t)row * wx + (col + x - p.seg_start[sx])] = vals[x];
                 }
             }
         } else {
@@ -267,15 +270,15 @@ __global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
     }
 }
 
-template <class T, bool CONCAT_A, bool SCATTER>
+template <class T, bool CONCAT_A, class Seg>
 hipError_t launch_gemm(const GemmParams &g, hipStream_t stream)
 {
     static LdsLimit lds_limit;
-    hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_gemm_kernel<T, CONCAT_A, SCATTER>, T::LDS_TOTAL);
+    hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_gemm_kernel<T, CONCAT_A, Seg>, T::LDS_TOTAL);
     if (e != hipSuccess) return e;
     const int nkc = (g.K + kGK - 1) / kGK;
     const int nsplit = g.chunks_per_split > 0 ? (nkc + g.chunks_per_split - 1) / g.chunks_per_split : 1;
-    hipLaunchKernelGGL((fipa_gemm_kernel<T, CONCAT_A, SCATTER>),
+    hipLaunchKernelGGL((fipa_gemm_kernel<T, CONCAT_A, Seg>),
                        dim3((g.M + T::TM - 1) / T::TM, (g.N + T::TN - 1) / T::TN, nsplit), dim3(256), T::LDS_TOTAL,
                        stream, g);
     return hipGetLastError();
@@ -333,88 +336,115 @@ ModuleLayout module_layout(const fipa_desc &d, int d_s)
 
 // ---- small memory-bound kernels of the module's backward ----------------------------------------
 
-// dst[c][r] = bf16(src[r][c]) for a row-major [R, C] matrix of float or bf16 (32 x 32 tiles through
-// LDS); dst has rows of length ld >= R, the tail of each row is set to zero.
-template <class SrcT>
-__global__ __launch_bounds__(256) void fipa_transpose_bf16_kernel(const SrcT *__restrict__ src, bf16_t *__restrict__ dst,
-                                                                  int R, int C, int ld)
+// Transposed bf16 copies dst[c][r] = src[r][c] of matrices [R, C] that come in four forms; dst has rows of length ld >= R, the tail of
+// each row is set to zero; C and ld are multiples of 8.  Tiles of 64 x 64 go through LDS, 16 bytes per thread on both sides; several
+// matrices share a launch, and the two that are also wanted as they stand (copy) are not formed a second time for it.
+// Bound by launches and latency more than by bytes: a tile has one round trip to memory.
+enum class TransposeSource { kBf16, kFloat, kConcat, kSegments };
+struct TransposeJob {
+    TransposeSource source;
+    const void *src;  // [R, C] bf16 or float; the concatenation of Eq. 5 and the side by side tensors come from GemmParams
+    bf16_t *copy;     // [R, C] or null
+    bf16_t *dst;      // [C, ld]
+    int R, C, ld;
+    int first_tile;   // in the launch
+};
+constexpr int kMaxTransposeJobs = 5;
+struct TransposeParams {
+    TransposeJob job[kMaxTransposeJobs];
+    int n, tiles;
+    GemmParams g;
+};
+
+// Eight consecutive columns of row `row` of the six bf16 gradient tensors of the core, side by side.
+__device__ __forceinline__ uint4 segments_chunk(const GemmParams &p, int row, int col)
 {
-    __shared__ bf16_t tile[32][33];
-    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-    for (int j = ty; j < 32; j += 8) {
-        const int r = r0 + j, c = c0 + tx;
-        bf16_t v = 0;
-        if (r < R && c < C) {
-            if constexpr (sizeof(SrcT) == 4)
-                v = f2bf(((const float *)src)[(size_t)r * C + c]);
-            else
-                v = ((const bf16_t *)src)[(size_t)r * C + c];
+    int seg = 0;
+#pragma unroll
+    for (int sg = 1; sg < 6; ++sg)
+        if (col >= p.seg_start[sg]) seg = sg;
+    const int start = p.seg_start[seg], width = p.seg_start[seg + 1] - start;
+    if (col + 8 <= p.seg_start[seg + 1] && ((width | (col - start)) & 7) == 0)
+        return *reinterpret_cast<const uint4 *>((const bf16_t *)p.seg_ptr[seg] + (size_t)row * width + (col - start));
+    unsigned w[4] = {0u, 0u, 0u, 0u};  // a piece that crosses into the next tensor, or is not aligned
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        while (col + x >= p.seg_start[seg + 1]) ++seg;  // (col + x < N = seg_start[6])
+        const int wx = p.seg_start[seg + 1] - p.seg_start[seg];
+        w[x / 2] |= (unsigned)((const bf16_t *)p.seg_ptr[seg])[(size_t)row * wx + (col + x - p.seg_start[seg])] << (16 * (x & 1));
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+__global__ __launch_bounds__(256) void fipa_transpose_bf16_kernel(TransposeParams p)
+{
+    constexpr int kStride = 33;  // words per row of the tile: the reads down a column fall on different banks
+    __shared__ unsigned tile[64 * kStride];
+    int jn = 0;
+#pragma unroll
+    for (int x = 1; x < kMaxTransposeJobs; ++x)
+        if (x < p.n && (int)blockIdx.x >= p.job[x].first_tile) jn = x;
+    const TransposeJob &j = p.job[jn];
+    const int tcols = (j.C + 63) / 64, t = blockIdx.x - j.first_tile, tr = t / tcols;
+    const int r0 = tr * 64, c0 = (t - tr * tcols) * 64;
+    const int sub = threadIdx.x & 7;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int rl = (threadIdx.x >> 3) + 32 * u, r = r0 + rl, c = c0 + 8 * sub;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (r < j.R && c < j.C) {
+            const size_t at = (size_t)r * j.C + c;
+            switch (j.source) {
+                case TransposeSource::kBf16: v = *reinterpret_cast<const uint4 *>((const bf16_t *)j.src + at); break;
+                case TransposeSource::kFloat: {
+                    const float *f = (const float *)j.src + at;
+                    v = __builtin_bit_cast(uint4, chunk_to_bf16(*reinterpret_cast<const f32x4 *>(f), *reinterpret_cast<const f32x4 *>(f + 4)));
+                    break;
+                }
+                case TransposeSource::kConcat: v = __builtin_bit_cast(uint4, concat_chunk(p.g, r, c)); break;
+                case TransposeSource::kSegments: v = segments_chunk(p.g, r, c); break;
+            }
+            if (j.copy) *reinterpret_cast<uint4 *>(j.copy + at) = v;
         }
-        tile[j][tx] = v;
+        unsigned *row = tile + rl * kStride + 4 * sub;
+        row[0] = v.x; row[1] = v.y; row[2] = v.z; row[3] = v.w;
     }
     __syncthreads();
-    for (int j = ty; j < 32; j += 8) {
-        const int c = c0 + j, r = r0 + tx;
-        if (r < ld && c < C) dst[(size_t)c * ld + r] = tile[tx][j];  // (tile entries with r >= R hold zero)
+    const bf16_t *entries = reinterpret_cast<const bf16_t *>(tile);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int cl = (threadIdx.x >> 3) + 32 * u, c = c0 + cl, r = r0 + 8 * sub;
+        if (c >= j.C || r >= j.ld) continue;  // (rows from R on hold zero)
+        unsigned w[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+            w[x] = (unsigned)entries[(8 * sub + 2 * x) * 2 * kStride + cl] | ((unsigned)entries[(8 * sub + 2 * x + 1) * 2 * kStride + cl] << 16);
+        *reinterpret_cast<uint4 *>(j.dst + (size_t)c * j.ld + r) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
 
-template <class SrcT>
-hipError_t launch_transpose(const SrcT *src, bf16_t *dst, int R, int C, int ld, hipStream_t stream)
+void add_transpose(TransposeParams &p, TransposeSource source, const void *src, bf16_t *copy, bf16_t *dst, int R, int C, int ld)
 {
-    hipLaunchKernelGGL((fipa_transpose_bf16_kernel<SrcT>), dim3((C + 31) / 32, (ld + 31) / 32), dim3(256), 0, stream, src, dst,
-                       R, C, ld);
+    p.job[p.n++] = TransposeJob{source, src, copy, dst, R, C, ld, p.tiles};
+    p.tiles += ((C + 63) / 64) * ((ld + 63) / 64);
+}
+
+hipError_t launch_transposes(const TransposeParams &p, hipStream_t stream)
+{
+    hipLaunchKernelGGL(fipa_transpose_bf16_kernel, dim3(p.tiles), dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 
-// float32 -> bf16 copy.
-__global__ __launch_bounds__(256) void fipa_to_bf16_kernel(const float *__restrict__ src, bf16_t *__restrict__ dst, size_t n)
+// The norms' part of the gradient of the concatenation: d_o_pts += d_norm * o_pts / |o_pts| (nothing at a zero vector).
+__global__ __launch_bounds__(256) void fipa_norm_gradient_kernel(const float *__restrict__ d_norm, const float *__restrict__ o_pts,
+                                                                  float *__restrict__ d_o_pts, size_t n)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) dst[i] = f2bf(src[i]);
-}
-
-// Row r of the concatenation of Eq. 5 as bf16: [o_pair | o | o_pts | norms].
-__global__ __launch_bounds__(256) void fipa_concat_bf16_kernel(GemmParams p, bf16_t *__restrict__ cat)
-{
-    const int row = blockIdx.x;
-    for (int k = 8 * threadIdx.x; k < p.K; k += 8 * 256)
-        *reinterpret_cast<bf16x8 *>(cat + (size_t)row * p.K + k) = concat_chunk(p, row, k);
-}
-
-// Gradient of the concatenation back to the core's upstream gradients:
-//   d_o_pair, d_o copied; d_o_pts = its own columns + d_norm * o_pts / |o_pts| (zero at a zero vector).
-__global__ __launch_bounds__(256) void fipa_split_dcat_kernel(const float *__restrict__ dcat, const float *__restrict__ o_pts,
-                                                               float *__restrict__ d_o_pair, float *__restrict__ d_o,
-                                                               float *__restrict__ d_o_pts, int k_pair, int k_o, int k_pts)
-{
-    const int row = blockIdx.x;
-    const int K = k_pair + k_o + k_pts + k_pts / 3;
-    const float *src = dcat + (size_t)row * K;
-    for (int k = threadIdx.x; k < k_pair; k += 256) d_o_pair[(size_t)row * k_pair + k] = src[k];
-    for (int k = threadIdx.x; k < k_o; k += 256) d_o[(size_t)row * k_o + k] = src[k_pair + k];
-    for (int pt = threadIdx.x; pt < k_pts / 3; pt += 256) {
-        const float *op = o_pts + (size_t)row * k_pts + 3 * pt;
-        const float nrm = sqrtf(op[0] * op[0] + op[1] * op[1] + op[2] * op[2]);
-        const float gn = nrm > 0.f ? src[k_pair + k_o + k_pts + pt] / nrm : 0.f;
-        for (int x = 0; x < 3; ++x)
-            d_o_pts[(size_t)row * k_pts + 3 * pt + x] = src[k_pair + k_o + 3 * pt + x] + gn * op[x];
-    }
-}
-
-// The six bf16 gradient tensors of the core, side by side: dX [M, N_in].
-__global__ __launch_bounds__(256) void fipa_gather6_kernel(GemmParams p, bf16_t *__restrict__ dst)
-{
-    const int row = blockIdx.x;
-    for (int col = threadIdx.x; col < p.N; col += 256) {
-        int seg = 0;
-#pragma unroll
-        for (int s = 1; s < 6; ++s)
-            if (col >= p.seg_start[s]) seg = s;
-        const int width = p.seg_start[seg + 1] - p.seg_start[seg];
-        dst[(size_t)row * p.N + col] = p.seg_ptr[seg][(size_t)row * width + (col - p.seg_start[seg])];
-    }
+    const size_t pt = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (pt >= n) return;
+    const float *op = o_pts + 3 * pt;
+    const float nrm = sqrtf(op[0] * op[0] + op[1] * op[1] + op[2] * op[2]);
+    const float gn = nrm > 0.f ? d_norm[pt] / nrm : 0.f;
+    for (int x = 0; x < 3; ++x) d_o_pts[3 * pt + x] += gn * op[x];
 }
 
 // out[i] = sum over the nsplit partial matrices (fixed order), n entries each; n is a multiple of 4
@@ -453,8 +483,7 @@ constexpr int kWgradChunks = 8;  // K chunks (of 64 rows of the batch) per workg
 
 struct ModuleBwdLayout {
     ModuleLayout f;   // forward part: core inputs and outputs, and the core's workspace (of the backward's size, last)
-    size_t g16, gT, w_outT, w_inT, sT, dcat, d_o, d_o_pts, d_o_pair, dq, dk, dv, dq_pts, dk_pts, dv_pts, dX, dXT, cat,
-        catT, part;
+    size_t g16, gT, w_outT, w_inT, sT, d_norm, d_o, d_o_pts, d_o_pair, dq, dk, dv, dq_pts, dk_pts, dv_pts, dX, dXT, catT, part;
 };
 
 ModuleBwdLayout module_bwd_layout(const fipa_desc &d, int d_s)
@@ -486,7 +515,7 @@ ModuleBwdLayout module_bwd_layout(const fipa_desc &d, int d_s)
     w.w_outT = take(n_cat * d_s * 2);
     w.w_inT = take(n_in * d_s * 2);
     w.sT = take(Mp * d_s * 2);
-    w.dcat = take(M * n_cat * 4);
+    w.d_norm = take(M * d.H * d.Pv * 4);
     w.d_o = take(M * d.H * d.c * 4);
     w.d_o_pts = take(M * d.H * d.Pv * 3 * 4);
     w.d_o_pair = take(M * d.H * d.cz * 4);
@@ -498,7 +527,6 @@ ModuleBwdLayout module_bwd_layout(const fipa_desc &d, int d_s)
     w.dv_pts = take(M * d.H * d.Pv * 3 * 2);
     w.dX = take(M * n_in * 2);
     w.dXT = take(Mp * n_in * 2);
-    w.cat = take(M * n_cat * 2);
     w.catT = take(Mp * n_cat * 2);
     const size_t nsplit = ((M + kGK - 1) / kGK + kWgradChunks - 1) / kWgradChunks;
     w.part = take(nsplit * (n_cat > n_in ? n_cat : n_in) * d_s * 4);
@@ -544,11 +572,11 @@ hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void
     const size_t offs[6] = {w.q, w.k, w.v, w.q_pts, w.k_pts, w.v_pts};
     g1.seg_start[0] = 0;
     for (int s = 0; s < 6; ++s) {
-        g1.seg_ptr[s] = (bf16_t *)(base + offs[s]);
+        g1.seg_ptr[s] = base + offs[s];
         g1.seg_start[s + 1] = g1.seg_start[s] + widths[s];
     }
     g1.N = g1.seg_start[6];
-    hipError_t e = launch_gemm<GemmTile<2, 2, 1, 1>, false, true>(g1, stream);
+    hipError_t e = launch_gemm<GemmTile<2, 2, 1, 1>, false, bf16_t>(g1, stream);
     if (e != hipSuccess) return e;
 
     // ---- the core (Algorithm 1 steps 2-9) ------------------------------------------------------------
@@ -569,11 +597,11 @@ hipError_t module_forward(const fipa_desc &d, int d_s, const ModuleArgs &a, void
     const OutSplit os = out_projection_split(M, d_s, g2.K);
     if (os.nsplit == 1) {
         g2.C = a.s_out;
-        return launch_gemm<OutTile, true, false>(g2, stream);
+        return launch_gemm<OutTile, true, void>(g2, stream);
     }
     g2.C = (float *)(base + w.part);
     g2.chunks_per_split = os.chunks_per_split;
-    e = launch_gemm<OutTile, true, false>(g2, stream);
+    e = launch_gemm<OutTile, true, void>(g2, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fipa_sum_partials_kernel, dim3((unsigned)(((size_t)M * d_s / 4 + 255) / 256)), dim3(256), 0, stream,
                        g2.C, a.s_out, (size_t)M * d_s, os.nsplit);
@@ -611,13 +639,13 @@ hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, con
     const size_t in_offs[6] = {w.f.q, w.f.k, w.f.v, w.f.q_pts, w.f.k_pts, w.f.v_pts};
     g1.seg_start[0] = 0;
     for (int s = 0; s < 6; ++s) {
-        g1.seg_ptr[s] = (bf16_t *)(base + in_offs[s]);
+        g1.seg_ptr[s] = base + in_offs[s];
         g1.seg_start[s + 1] = g1.seg_start[s] + widths[s];
     }
     g1.N = g1.seg_start[6];
     const int n_in = g1.N;
     const bool kept = (d.flags & FIPA_FLAG_KEEP_FORWARD) != 0;  // the forward call left all of this in the workspace
-    if (!kept) FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, true>(g1, stream)));
+    if (!kept) FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, bf16_t>(g1, stream)));
     FwdArgs f{base + w.f.q, base + w.f.k, base + w.f.v, base + w.f.q_pts, base + w.f.k_pts, base + w.f.v_pts,
               a.rot, a.trans, a.z1, a.z2, a.w_b, a.gamma, a.mask,
               (float *)(base + w.f.o), (float *)(base + w.f.o_pts), (float *)(base + w.f.o_pair), nullptr};
@@ -626,27 +654,37 @@ hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, con
     if (!kept) FIPA_TRY(bf16_backward_begin(d, f, base + w.f.core, ws_bytes - w.f.core, stream));
 
     // ---- through Eq. 5: d cat = d s_out W_out; d W_out = d s_out^T cat; d b_out = column sums ----------
-    bf16_t *g16 = (bf16_t *)(base + w.g16), *gT = (bf16_t *)(base + w.gT);
-    hipLaunchKernelGGL(fipa_to_bf16_kernel, dim3((unsigned)(((size_t)M * d_s + 255) / 256)), dim3(256), 0, stream,
-                       g.d_s_out, g16, (size_t)M * d_s);
-    FIPA_TRY(launch_transpose<float>(g.d_s_out, gT, M, d_s, Mp, stream));                                // [d_s, Mp]
-    FIPA_TRY(launch_transpose<bf16_t>((const bf16_t *)a.w_out, (bf16_t *)(base + w.w_outT), d_s, n_cat, d_s, stream));  // [N_cat, d_s]
-    GemmParams gc = {};
-    gc.M = M; gc.N = n_cat; gc.K = d_s;
-    gc.A = g16; gc.W = (const bf16_t *)(base + w.w_outT); gc.C = (float *)(base + w.dcat);
-    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, false>(gc, stream)));
     GemmParams cp = {};  // description of the concatenation (as for the forward's output projection)
     cp.M = M; cp.o_pair = f.o_pair; cp.o = f.o; cp.o_pts = f.o_pts;
     cp.k_pair = d.H * d.cz; cp.k_o = d.H * d.c; cp.k_pts = d.H * d.Pv * 3; cp.K = n_cat;
-    hipLaunchKernelGGL(fipa_split_dcat_kernel, dim3(M), dim3(256), 0, stream, gc.C, f.o_pts, (float *)(base + w.d_o_pair),
-                       (float *)(base + w.d_o), (float *)(base + w.d_o_pts), cp.k_pair, cp.k_o, cp.k_pts);
-    hipLaunchKernelGGL(fipa_concat_bf16_kernel, dim3(M), dim3(256), 0, stream, cp, (bf16_t *)(base + w.cat));
-    FIPA_TRY(launch_transpose<bf16_t>((const bf16_t *)(base + w.cat), (bf16_t *)(base + w.catT), M, n_cat, Mp, stream));  // [N_cat, Mp]
+    bf16_t *g16 = (bf16_t *)(base + w.g16), *gT = (bf16_t *)(base + w.gT);
+    TransposeParams tp = {};
+    tp.g = cp;
+    add_transpose(tp, TransposeSource::kFloat, g.d_s_out, g16, gT, M, d_s, Mp);                                          // [d_s, Mp]
+    add_transpose(tp, TransposeSource::kBf16, a.w_out, nullptr, (bf16_t *)(base + w.w_outT), d_s, n_cat, d_s);           // [N_cat, d_s]
+    add_transpose(tp, TransposeSource::kConcat, nullptr, nullptr, (bf16_t *)(base + w.catT), M, n_cat, Mp);              // [N_cat, Mp]
+    add_transpose(tp, TransposeSource::kBf16, a.w_in, nullptr, (bf16_t *)(base + w.w_inT), n_in, d_s, n_in);             // [d_s, N_in]
+    add_transpose(tp, TransposeSource::kBf16, a.s, nullptr, (bf16_t *)(base + w.sT), M, d_s, Mp);                        // [d_s, Mp]
+    FIPA_TRY(launch_transposes(tp, stream));
+    GemmParams gc = {};  // its columns are the core's upstream gradients and the norms' one
+    gc.M = M; gc.N = n_cat; gc.K = d_s;
+    gc.A = g16; gc.W = (const bf16_t *)(base + w.w_outT);
+    const size_t up_offs[4] = {w.d_o_pair, w.d_o, w.d_o_pts, w.d_norm};
+    const int up_widths[4] = {cp.k_pair, cp.k_o, cp.k_pts, d.H * d.Pv};
+    for (int x = 0; x < 4; ++x) {
+        gc.seg_ptr[x] = base + up_offs[x];
+        gc.seg_start[x + 1] = gc.seg_start[x] + up_widths[x];
+    }
+    gc.seg_start[5] = gc.seg_start[6] = n_cat;
+    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, float>(gc, stream)));
+    const size_t n_pts = (size_t)M * d.H * d.Pv;
+    hipLaunchKernelGGL(fipa_norm_gradient_kernel, dim3((unsigned)((n_pts + 255) / 256)), dim3(256), 0, stream,
+                       (const float *)(base + w.d_norm), f.o_pts, (float *)(base + w.d_o_pts), n_pts);
     const int nkc = Mp / kGK, nsplit = (nkc + kWgradChunks - 1) / kWgradChunks;
     GemmParams gw = {};
     gw.M = d_s; gw.N = n_cat; gw.K = Mp;
     gw.A = gT; gw.W = (const bf16_t *)(base + w.catT); gw.C = (float *)(base + w.part); gw.chunks_per_split = kWgradChunks;
-    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, false>(gw, stream)));
+    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, void>(gw, stream)));
     hipLaunchKernelGGL(fipa_sum_partials_kernel, dim3((unsigned)(((size_t)d_s * n_cat / 4 + 255) / 256)), dim3(256), 0, stream,
                        gw.C, g.d_w_out, (size_t)d_s * n_cat, nsplit);
     if (g.d_b_out) hipLaunchKernelGGL(fipa_rowsum_bf16_kernel, dim3(d_s), dim3(256), 0, stream, gT, g.d_b_out, Mp);
@@ -668,22 +706,22 @@ hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, con
     const size_t gr_offs[6] = {w.dq, w.dk, w.dv, w.dq_pts, w.dk_pts, w.dv_pts};
     gx.seg_start[0] = 0;
     for (int s = 0; s < 6; ++s) {
-        gx.seg_ptr[s] = (bf16_t *)(base + gr_offs[s]);
+        gx.seg_ptr[s] = base + gr_offs[s];
         gx.seg_start[s + 1] = gx.seg_start[s] + widths[s];
     }
     bf16_t *dX = (bf16_t *)(base + w.dX), *dXT = (bf16_t *)(base + w.dXT);
-    hipLaunchKernelGGL(fipa_gather6_kernel, dim3(M), dim3(256), 0, stream, gx, dX);
-    FIPA_TRY(launch_transpose<bf16_t>(dX, dXT, M, n_in, Mp, stream));                                                  // [N_in, Mp]
-    FIPA_TRY(launch_transpose<bf16_t>((const bf16_t *)a.w_in, (bf16_t *)(base + w.w_inT), n_in, d_s, n_in, stream));  // [d_s, N_in]
-    FIPA_TRY(launch_transpose<bf16_t>((const bf16_t *)a.s, (bf16_t *)(base + w.sT), M, d_s, Mp, stream));              // [d_s, Mp]
+    TransposeParams tx = {};
+    tx.g = gx;
+    add_transpose(tx, TransposeSource::kSegments, nullptr, dX, dXT, M, n_in, Mp);  // [N_in, Mp]
+    FIPA_TRY(launch_transposes(tx, stream));
     GemmParams gs = {};
     gs.M = M; gs.N = d_s; gs.K = n_in;
     gs.A = dX; gs.W = (const bf16_t *)(base + w.w_inT); gs.C = g.d_s_in;
-    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, false>(gs, stream)));
+    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, void>(gs, stream)));
     GemmParams gi = {};
     gi.M = n_in; gi.N = d_s; gi.K = Mp;
     gi.A = dXT; gi.W = (const bf16_t *)(base + w.sT); gi.C = (float *)(base + w.part); gi.chunks_per_split = kWgradChunks;
-    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, false>(gi, stream)));
+    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, void>(gi, stream)));
     hipLaunchKernelGGL(fipa_sum_partials_kernel, dim3((unsigned)(((size_t)n_in * d_s / 4 + 255) / 256)), dim3(256), 0, stream,
                        gi.C, g.d_w_in, (size_t)n_in * d_s, nsplit);
     if (g.d_b_in) hipLaunchKernelGGL(fipa_rowsum_bf16_kernel, dim3(n_in), dim3(256), 0, stream, dXT, g.d_b_in, Mp);
