@@ -448,17 +448,22 @@ __global__ __launch_bounds__(1024) void fipa_bwd_gamma_kernel(const float *gpart
 // sum over chunks and rho.
 constexpr int kWbChunk = 32;
 
-// One workgroup per (chunk, head): a thread takes four neighbouring lifted columns (16 bytes of
-// dQ^, 8 of z1) of every NRG-th residue of the chunk, all loads independent; the NRG partial sums
-// per column meet in LDS and are added in a fixed order.  r c_z <= 512 here, so NRG >= 2.
+// One workgroup per (chunk, NH heads): a thread takes four neighbouring lifted columns (16 bytes of
+// dQ^ per head, 8 of z1) of every NRG-th residue of the chunk, all loads independent; the NRG partial sums
+// per column meet in LDS and are added in a fixed order.  r c_z <= 512 here, so NRG >= 2.  Bound by reading dQ^: 32 packed
+// chains of 64 to 512 residues, H = 12, r c_z = 256 22.9 us for 111 MB, four chains of 2.7k to 7.1k residues at r c_z = 512 121 for
+// 484 MB (a workgroup per head, which finds every residue's place and reads z1 again: 30 and 138).
+template <int NH>
 __global__ __launch_bounds__(256) void fipa_bwd_wb_partial_kernel(BwdUnpackParams p)
 {
-    __shared__ float red[256 * 4];  // [residue group][DZ], NRG * DZ = 1024 entries
-    const int h = blockIdx.y, chunk = blockIdx.x, D = kDH + p.DZ;
+    __shared__ f32x4 red[NH][256];  // [head][residue group][DZ]: NRG * DZ = 1024 numbers per head
+    const int h0 = blockIdx.y * NH, chunk = blockIdx.x, D = kDH + p.DZ;
     const int nres = p.total_rows;  // rows of the caller's tensors: B L, or the packed batch's total
     const int NG = p.DZ / 4, NRG = 256 / NG;
     const int cg = threadIdx.x % NG, rg = threadIdx.x / NG, x0 = 4 * cg;
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    f32x4 s[NH];
+#pragma unroll
+    for (int u = 0; u < NH; ++u) s[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
     int b0 = 0;  // packed batch: the chain that holds the chunk's first row, the last b with cu[b] <= it
     if (p.cu) {
         int hi = p.B - 1;
@@ -482,21 +487,28 @@ __global__ __launch_bounds__(256) void fipa_bwd_wb_partial_kernel(BwdUnpackParam
         const bool valid = chunk * kWbChunk + t < nres && (p.mask ? p.mask[bi] != 0 : true);
         // (a residue that does not count takes the first row of all, so that the loads need no branch and padding costs no traffic)
         const uint2 zr = *reinterpret_cast<const uint2 *>(p.z1 + (valid ? (size_t)bi * p.DZ : 0) + x0);
-        const f32x4 dq = *reinterpret_cast<const f32x4 *>(p.dQhat + (valid ? (((size_t)b * p.H + h) * p.Lp + i) * D : 0) + kDH + x0);
-        if (valid) {
-            s[0] += __uint_as_float(zr.x << 16) * dq[0];
-            s[1] += __uint_as_float(zr.x & 0xFFFF0000u) * dq[1];
-            s[2] += __uint_as_float(zr.y << 16) * dq[2];
-            s[3] += __uint_as_float(zr.y & 0xFFFF0000u) * dq[3];
+        const f32x4 z = bf16x4_to_f32(zr);
+        f32x4 dq[NH];
+#pragma unroll
+        for (int u = 0; u < NH; ++u) {
+            const int h = min(h0 + u, p.H - 1);
+            dq[u] = *reinterpret_cast<const f32x4 *>(p.dQhat + (valid ? (((size_t)b * p.H + h) * p.Lp + i) * D : 0) + kDH + x0);
         }
+        if (valid)
+#pragma unroll
+            for (int u = 0; u < NH; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[u][e] += z[e] * dq[u][e];
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) red[rg * p.DZ + x0 + e] = s[e];
+    for (int u = 0; u < NH; ++u) red[u][threadIdx.x] = s[u];
     __syncthreads();
-    for (int x = threadIdx.x; x < p.DZ; x += 256) {
-        float t = 0.f;
-        for (int g = 0; g < NRG; ++g) t += red[g * p.DZ + x];
-        p.wpart[((size_t)h * gridDim.x + chunk) * p.DZ + x] = t;
+    for (int x = threadIdx.x; x < NH * NG; x += 256) {
+        const int u = x / NG, col = x - u * NG;
+        if (h0 + u >= p.H) break;
+        f32x4 t = {0.f, 0.f, 0.f, 0.f};
+        for (int g = 0; g < NRG; ++g) t += red[u][g * NG + col];
+        *reinterpret_cast<f32x4 *>(p.wpart + ((size_t)(h0 + u) * gridDim.x + chunk) * p.DZ + 4 * col) = t;
     }
 }
 
@@ -649,7 +661,12 @@ hipError_t launch_bwd_unpack_bf16(const BwdUnpackParams &p, hipStream_t stream)
                        p.Lp, p.cu, -0.5f * p.w_L * p.w_C);
     if (p.d_w_b) {
         const int nchunk = (p.total_rows + kWbChunk - 1) / kWbChunk;
-        hipLaunchKernelGGL(fipa_bwd_wb_partial_kernel, dim3(nchunk, p.H), dim3(256), 0, stream, p);
+        // (four heads at a time from as many chunks on as fill the chip that way: 4096 residues, r c_z = 256, one 12.2 us, two 14.6, four 15.0;
+        // 9080 residues 30, 23.1, 22.9; 32768 residues padded, 512 columns, 138, 133, 121)
+        if (nchunk < 256)
+            hipLaunchKernelGGL(fipa_bwd_wb_partial_kernel<1>, dim3(nchunk, p.H), dim3(256), 0, stream, p);
+        else
+            hipLaunchKernelGGL(fipa_bwd_wb_partial_kernel<4>, dim3(nchunk, (p.H + 3) / 4), dim3(256), 0, stream, p);
         hipLaunchKernelGGL(fipa_bwd_wb_reduce_kernel, dim3(p.H, p.cz / wb_columns(p.cz)), dim3(1024), 0, stream, p, nchunk);
     }
     return hipGetLastError();

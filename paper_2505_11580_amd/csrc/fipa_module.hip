@@ -468,9 +468,14 @@ __global__ __launch_bounds__(256) void fipa_rowsum_bf16_kernel(const bf16_t *__r
 {   // (rows may carry a zero tail: C is the stored row length)
     __shared__ float red[256];
     const int r = blockIdx.x;
-    float s = 0.f;
-    for (int c = threadIdx.x; c < C; c += 256) s += bf2f(src[(size_t)r * C + c]);
-    red[threadIdx.x] = s;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    for (int c = 8 * threadIdx.x; c < C; c += 8 * 256) {  // (the stored length is a multiple of 64)
+        const uint4 v = *reinterpret_cast<const uint4 *>(src + (size_t)r * C + c);
+        const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int x = 0; x < 4; ++x) s[x] += __uint_as_float(w[x] << 16) + __uint_as_float(w[x] & 0xFFFF0000u);
+    }
+    red[threadIdx.x] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
     for (int st = 128; st > 0; st >>= 1) {
         if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];

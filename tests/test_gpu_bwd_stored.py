@@ -70,3 +70,11 @@ def test_backward_width128_in_the_least_workspace(kw):
 def test_backward_behind_the_one_pass_forward():
     # r c_z = 512 with more than 128 tiles of queries: O^ and the log-sum-exp come from the one-pass forward
     check_backward(wl.make_inputs(4, B=11, L=100, H=12, cz=128, r=4, varlen=True, min_len=40, trans_scale=0.3), "bwd behind the one-pass forward")
+
+
+@pytest.mark.parametrize("kw", [dict(B=64, L=129, H=5, cz=32, r=1), dict(B=66, L=130, H=3, cz=32, r=2, varlen=True, min_len=20)])
+def test_backward_bias_weights_four_heads_at_a_time(kw):
+    # from 256 chunks of 32 residues on, a number of heads that is no multiple of four
+    assert kw["B"] * kw["L"] > 255 * 32
+    inp = wl.make_inputs(4, trans_scale=0.3, **kw)
+    check_backward(inp, "bwd bias weights %s" % kw, samples=wl.select_rows(inp, 4))

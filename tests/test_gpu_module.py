@@ -104,3 +104,11 @@ def test_module_backward_masked_and_without_biases():
     check_module_backward(m, "module bwd varlen")
     m["b_in"], m["b_out"] = None, None
     check_module_backward(m, "module bwd varlen, no biases")
+
+
+@pytest.mark.parametrize("d_s,kw", [
+    (16, dict(B=1, L=9, H=4)), (80, dict(B=1, L=64, H=4, cz=32)), (48, dict(B=3, L=43, H=4, Pq=3)), (144, dict(B=1, L=65, H=8, Pq=3, cz=16))])
+def test_module_backward_transposed_tiles(d_s, kw):
+    # rows and columns at the edges of the 64 x 64 tiles; three query points: pieces of a gathered row that straddle two tensors
+    # (not one residue alone: its weight is constant, d_gamma zero and without a relative error; the other gradients agree there)
+    check_module_backward(wl.make_module_inputs(4, d_s=d_s, trans_scale=0.3, **kw), "module bwd d_s=%d %s" % (d_s, kw))
