@@ -32,7 +32,7 @@ __device__ __forceinline__ f32x4 bf16x4_to_f32(uint2 v)
 }
 __device__ __forceinline__ unsigned bf16_pair(float lo, float hi) { return (unsigned)f2bf(lo) | ((unsigned)f2bf(hi) << 16); }
 
-// One workgroup per (batch, residue < Lp): the lifted upstream gradient rows of its heads, D_i, -lse, and the part of the gradient of
+// One workgroup per (batch, residue < Lp; the batch over two grid dimensions, 32768 at most in the first): the lifted upstream gradient rows of its heads, D_i, -lse, and the part of the gradient of
 // z1 that comes through o~ = z1^T U, sum_h d_o_pair (.) U: the lifted output passes by here once.  That sum, float32, lies in the
 // residue's rows of the outputs d_z1 (upper halves) and d_z2 (lower halves) until the unpack kernel writes them.
 // Four waves with every fourth head (group of heads) each; all loads of a wave's three heads are independent of each other and in
@@ -44,7 +44,8 @@ template <int NG>
 __global__ __launch_bounds__(256, 4) void fipa_bwd_pack_bf16_kernel(BwdPackParams p)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b = blockIdx.x / (unsigned)p.Lp, i = blockIdx.x - (unsigned)b * p.Lp;
+    const int b = blockIdx.y + 32768 * blockIdx.z, i = blockIdx.x;
+    if (b >= p.B) return;
     if (i >= ((p.kvlen[b] + 31) & ~31)) return;  // (the gradient kernels stream whole blocks of 32 rows and no further)
     const int c = p.c, D = kDH + p.DZ, PH = (p.Pv + 1) / 2;
     constexpr int HG = 64 / NG;
@@ -647,7 +648,7 @@ BwdLayout bwd_layout(const fipa_desc &d, size_t bytes)
 hipError_t launch_bwd_pack_bf16(const BwdPackParams &p, hipStream_t stream)
 {
     return with_column_lanes(p.DZ, [&](auto N) {
-        hipLaunchKernelGGL(fipa_bwd_pack_bf16_kernel<decltype(N)::value>, dim3((unsigned)p.Lp * p.B), dim3(256), 0, stream, p);
+        hipLaunchKernelGGL(fipa_bwd_pack_bf16_kernel<decltype(N)::value>, dim3(p.Lp, p.B < 32768 ? p.B : 32768, (p.B + 32767) / 32768), dim3(256), 0, stream, p);
     });
 }
 
