@@ -84,24 +84,36 @@ __device__ __forceinline__ void batch_reference(const P &p, int b, float (&cen)[
     const size_t row0 = user_row(p, b, 0);
     int last = len;
     if (p.mask) {
-        // 16 bytes per lane at a time between the first and the last aligned address (byte by byte every wave of the pack kernel
-        // walked 128 loads of a chain of 8192: pack kernel of four of them 138 us, now 54)
         const uint8_t *m = p.mask + row0;
-        const int head = min(len, (int)(-(uintptr_t)m & 15)), chunks = (len - head) / 16, tail = head + 16 * chunks;
-        last = lane < head && m[lane] != 0 ? lane + 1 : 0;
-        int at = -1;  // this lane's last 16 bytes with one
+        last = 0;
+        if (len <= 256) {  // byte by byte: no more loads than the other way's, and 0.2 us less in calls of 20
+            unsigned char byte[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) byte[u] = lane + 64 * u < len ? m[lane + 64 * u] : 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) last = byte[u] != 0 ? lane + 64 * u + 1 : last;
+        } else {
+            // 16 bytes per lane at a time between the first and the last aligned address (byte by byte every wave of the pack kernel
+            // walked 128 loads of a chain of 8192: pack kernel of four of them 138 us, now 54)
+            const int head = min(len, (int)(-(uintptr_t)m & 15)), chunks = (len - head) / 16, tail = head + 16 * chunks;
+            // (all loads of a short chain in flight at once: nothing is read again to find the byte)
+            const unsigned first = lane < head ? m[lane] : 0u, rest = tail + lane < len ? m[tail + lane] : 0u;
+            int at = 0;  // this lane's last 16 bytes with one that is not zero, the last such word of them and its index
+            unsigned word = 0u, words = 0u;
 #pragma unroll 4
-        for (int x = lane; x < chunks; x += 64) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(m + head + 16 * x);
-            at = (v.x | v.y | v.z | v.w) != 0u ? x : at;
-        }
-        if (at >= 0)
-            for (int k = 15; k >= 0; --k)
-                if (m[head + 16 * at + k] != 0) {
-                    last = head + 16 * at + k + 1;
-                    break;
+            for (int x = lane; x < chunks; x += 64) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(m + head + 16 * x);
+                const unsigned top = v.w ? v.w : v.z ? v.z : v.y ? v.y : v.x;
+                if (top) {
+                    at = x;
+                    word = top;
+                    words = v.w ? 3u : v.z ? 2u : v.y ? 1u : 0u;
                 }
-        if (tail + lane < len && m[tail + lane] != 0) last = tail + lane + 1;
+            }
+            if (first != 0u) last = lane + 1;
+            if (word) last = head + 16 * at + 4 * (int)words + (31 - __clz(word)) / 8 + 1;
+            if (rest != 0u) last = tail + lane + 1;
+        }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
     }

@@ -260,3 +260,18 @@ def test_masked_batches_with_odd_pair_counts(B, H, L):
     gu.check(inp, label="bf16 masked B=%d H=%d L=%d" % (B, H, L))
     inp = wl.make_inputs(1, B=B, H=H, L=L, varlen=True, min_len=L, cz=32)   # a mask, all chains full length
     gu.check(inp, label="bf16 masked, equal lengths B=%d H=%d" % (B, H))
+
+
+@pytest.mark.parametrize("L", [255, 257, 275, 1100])
+def test_bf16_last_valid_residue_at_every_byte(L):
+    # chains that start at every offset from a 16-byte boundary (L is odd, or 12 past one), the last valid residue in the unaligned
+    # start, in any byte of the pieces between, in the unaligned end; a compact chain, so that every key has weight
+    B = 40 if L < 1000 else 9
+    inp = wl.make_inputs(1, B=B, L=L, H=1, cz=16, r=2, trans_scale=0.05)
+    m = np.zeros((B, L), dtype=np.uint8)
+    for b in range(B):
+        last = [b, L - 1 - b, (7 * b) % L, (L // 2 + 29 * b) % L][b % 4]
+        m[b, :last:3] = 1
+        m[b, last] = 1
+    inp["mask"] = m
+    gu.check(inp, label="bf16 last valid residue L=%d" % L)
