@@ -72,101 +72,126 @@ __global__ __launch_bounds__(256) void fipa_factor_project_kernel(const int *__r
     *reinterpret_cast<uint4 *>(z + row * n_out + ch * 8) = o;
 }
 
-
 // The same with the tables of 32 columns (64 bytes per row) in LDS, where a workgroup then adds up many residues: the rows of
-// a residue come out of LDS instead of L2.  1024 threads, four per residue; the LDS rows of the next 256 residues are looked up while the
-// previous ones are added (one barrier per 256 residues); an empty slot takes a row of zeros.  Same sums in the same order.
-// 32768 residues, 20 slots, 81 rows per slot, 512 columns: 99 us from L2, 59 us here (bound by the vector unit, two
-// instructions per value, and by the loading of the table; 72 us while a thread looked up every slot by divisions).  Used where every
-// workgroup has at least kFpRows residues to add for the table that it loads and the table fits.
-constexpr int kFpThreads = 1024, kFpPass = kFpThreads / 4, kFpRows = 1024;
+// a residue come out of LDS instead of L2.  1024 threads, four per residue; a wave takes groups of 16 residues that lie gridDim.y * 16 groups
+// apart, so that the masked ends of a padded batch (no slot filled: nothing to add) are spread over all workgroups, and needs no other wave
+// behind the loading of the table: it looks up the table rows of its own residues.  An empty slot takes a row of zeros.  The two rows of a slot are
+// added by one instruction per value (a product with ones), where unpacking the halves and adding them took four per pair.
+// 32768 residues (60 % of them valid), 20 slots, 81 rows per slot, 512 columns: 99 us from L2; from LDS 60 us with contiguous ranges of
+// residues per workgroup, a barrier per 256 of them and indices that were loaded where they were looked at, 38 us so.  What is left is the
+// LDS reads of rows that meet in the banks (64 bytes each, any of four places) and the loading of the table (about 5 us).
+// Used where every workgroup has at least kFpRows residues to add for the table that it loads and the table fits: one chain of 4096
+// residues, 512 columns, 16.6 us from L2, 11.0 so; 2048 11.6 and 9.1; 8192 residues of 128 columns 11.2 and 8.8.
+constexpr int kFpThreads = 1024, kFpPass = kFpThreads / 4, kFpRows = 128;
+constexpr int kFpAhead = 8;  // slots of a thread whose indices and bins wait in registers: 32 of a residue
 inline size_t factor_lds_bytes(int k, int n_bins, int n_pos)
 {
-    return 64 * ((size_t)k * (n_bins + n_pos) + 1) + 2 * (size_t)kFpPass * k * 4;
+    return 64 * ((size_t)k * (n_bins + n_pos) + 1) + (size_t)kFpPass * k * 4;
 }
 
 __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(const int *__restrict__ nbr_idx, const int *__restrict__ nbr_bin,
                                                                              const bf16_t *__restrict__ e_bin, const bf16_t *__restrict__ e_pos,
                                                                              const float *__restrict__ bias, bf16_t *__restrict__ z, int rows,
-                                                                             int L, int k, int n_bins, int n_pos, int pos_mode, int n_out,
-                                                                             int per_wg)
+                                                                             int L, int k, int n_bins, int n_pos, int pos_mode, int n_out)
 {
-    extern __shared__ __attribute__((aligned(16))) char fp_smem[];  // table rows [k][n_bins + n_pos], the row of zeros | two passes of row numbers
+    extern __shared__ __attribute__((aligned(16))) char fp_smem[];  // table rows [k][n_bins + n_pos], the row of zeros | row numbers [k][residue of the pass]
     const int tid = threadIdx.x, per = n_bins + n_pos, nrow = k * per, half = (n_pos - 1) >> 1;
     const int col0 = blockIdx.x * 32;
-    const int first = blockIdx.y * per_wg, last = min(first + per_wg, rows);
     unsigned *const codes = reinterpret_cast<unsigned *>(fp_smem + 64 * ((size_t)nrow + 1));
     const int part = tid & 3, col = col0 + 8 * part;
-    for (int x = tid; x < 4 * (nrow + 1); x += kFpThreads) {
-        const int row = x >> 2, c = col0 + 8 * (x & 3);
-        uint4 v = {0u, 0u, 0u, 0u};
-        if (row < nrow && c < n_out) {
-            const int s = row / per, m = row - s * per;
-            v = m < n_bins ? *reinterpret_cast<const uint4 *>(e_bin + ((size_t)s * n_bins + m) * n_out + c)
-                           : *reinterpret_cast<const uint4 *>(e_pos + ((size_t)s * n_pos + m - n_bins) * n_out + c);
+    // A wave takes every 16 gridDim.y-th group of 16 residues, four lanes each, and looks up the rows (bin, position) of their slots itself, a lane
+    // every fourth slot: codes[slot][residue].  The indices and bins of the first kFpAhead of those slots are requested (ask) before the
+    // group before is added up, and looked at (look_up) behind it.
+    const int rr = tid >> 2, stride = kFpPass * gridDim.y, turn = stride % L;
+    const int first = 16 * (blockIdx.y + gridDim.y * (tid >> 6)) + (rr & 15);  // this lane's residues: first, first + stride, ..
+    int i_next = first % L;  // place in the chain of the one that is looked up next
+    int nbr[kFpAhead], bins[kFpAhead];
+    auto ask = [&](int res) {
+        const size_t at = (size_t)min(res, rows - 1) * k;
+#pragma unroll
+        for (int u = 0; u < kFpAhead; ++u) {
+            const int s = min(part + 4 * u, k - 1);
+            nbr[u] = nbr_idx[at + s];
+            bins[u] = nbr_bin[at + s];
         }
-        *reinterpret_cast<uint4 *>(fp_smem + 16 * (size_t)x) = v;
-    }
-    // rows (bin, position) of every slot of the pass that starts at residue r0: codes[buf][slot][residue].  The thread's own residue, every
-    // fourth slot; whether any residue of the wave has a neighbour.
-    const int rr = tid >> 2, turn = kFpPass % L;
-    int i_next = (first + rr) % L;  // place in the chain of the residue that is looked up next
-    auto look_up = [&](int r0, int buf) {
-        unsigned *dst = codes + buf * kFpPass * k;
-        const size_t at = (size_t)min(r0 + rr, rows - 1) * k;
-        const int i = r0 + rr < rows ? i_next : L - 1;
+    };
+    auto look_up = [&](int res) {
+        const size_t at = (size_t)min(res, rows - 1) * k;
+        const int i = i_next;
         bool any = false;
-        for (int s = part; s < k; s += 4) {
-            const int j = nbr_idx[at + s], bn = nbr_bin[at + s];
+        auto one = [&](int s, int j, int bn) {
             unsigned bin_row = nrow, pos_row = nrow;  // zeros
             if (j >= 0 && j < L) {
                 any = true;
                 bin_row = s * per + min(max(bn, 0), n_bins - 1);
                 if (n_pos > 0) pos_row = s * per + n_bins + (pos_mode == 0 ? min(j, n_pos - 1) : min(max(j - i, -half), half) + half);
             }
-            dst[s * kFpPass + rr] = bin_row | (pos_row << 16);
-        }
+            codes[s * kFpPass + rr] = bin_row | (pos_row << 16);
+        };
+#pragma unroll
+        for (int u = 0; u < kFpAhead; ++u)
+            if (part + 4 * u < k) one(part + 4 * u, nbr[u], bins[u]);
+        for (int s = part + 4 * kFpAhead; s < k; s += 4) one(s, nbr_idx[at + s], nbr_bin[at + s]);
         i_next += turn;
         if (i_next >= L) i_next -= L;
         return __any(any) != 0;
     };
+    ask(first);
+    for (int x0 = tid; x0 < 4 * (nrow + 1); x0 += 8 * kFpThreads) {  // (eight loads in flight)
+        uint4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int x = x0 + u * kFpThreads, row = min(x >> 2, nrow - 1), c = col0 + 8 * (x & 3);
+            const int s = row / per, m = row - s * per;
+            const bf16_t *src = m < n_bins ? e_bin + ((size_t)s * n_bins + m) * n_out : e_pos + ((size_t)s * n_pos + m - n_bins) * n_out;
+            v[u] = *reinterpret_cast<const uint4 *>(src + min(c, n_out - 8));
+            if (x >= 4 * nrow || c >= n_out) v[u] = (uint4){0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int x = x0 + u * kFpThreads;
+            if (x < 4 * (nrow + 1)) *reinterpret_cast<uint4 *>(fp_smem + 16 * (size_t)x) = v[u];
+        }
+    }
     float b8[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) b8[q] = bias && col < n_out ? bias[col + q] : 0.f;
-    auto add = [](float (&acc)[8], const char *row) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(row);
-        const unsigned w[4] = {v.x, v.y, v.z, v.w};
+    // a bin row and a position row: two columns of each side by side, a product with ones adds both
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+    auto add = [&](float (&acc)[8], const char *bin_row, const char *pos_row) {
+        const uint4 u = *reinterpret_cast<const uint4 *>(bin_row), v = *reinterpret_cast<const uint4 *>(pos_row);
+        const unsigned a[4] = {u.x, u.y, u.z, u.w}, b[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            acc[2 * q] += __uint_as_float(w[q] << 16);
-            acc[2 * q + 1] += __uint_as_float(w[q] & 0xffff0000u);
+            const unsigned even = __builtin_amdgcn_perm(b[q], a[q], 0x05040100u), odd = __builtin_amdgcn_perm(b[q], a[q], 0x07060302u);
+            acc[2 * q] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, even), ones, acc[2 * q], false);
+            acc[2 * q + 1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, odd), ones, acc[2 * q + 1], false);
         }
     };
-    bool some = first < last && look_up(first, 0);
-    int buf = 0;
-    for (int r0 = first; r0 < last; r0 += kFpPass, buf ^= 1) {
-        __syncthreads();  // this pass's rows are there, the pass before is done with the other buffer
-        const bool here = some;  // (a wave looks up the residues that it adds)
-        if (r0 + kFpPass < last) some = look_up(r0 + kFpPass, buf ^ 1);
-        const int res = r0 + rr;
-        if (res >= last || col >= n_out) continue;
-        const unsigned *src = codes + buf * kFpPass * k + rr;
-        float acc[8];
+    __syncthreads();  // the table is there
+    const int whole = 16 * (blockIdx.y + gridDim.y * (tid >> 6));  // (the wave's first residue)
+    for (int r0 = whole, res = first; r0 < rows; r0 += stride, res += stride) {
+        const bool some = look_up(res);
+        ask(res + stride);
+        asm volatile("" ::: "memory");  // (the LDS accesses of a wave execute in order)
+        if (res < rows && col < n_out) {
+            float acc[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] = b8[q];
-        const int slots = here ? k : 0;
+            for (int q = 0; q < 8; ++q) acc[q] = b8[q];
+            const int slots = some ? k : 0;
 #pragma unroll 4
-        for (int s = 0; s < slots; ++s) {
-            const unsigned c = src[s * kFpPass];
-            add(acc, fp_smem + 64 * (c & 0xFFFFu) + 16 * part);
-            add(acc, fp_smem + 64 * (c >> 16) + 16 * part);
+            for (int s = 0; s < slots; ++s) {
+                const unsigned c = codes[s * kFpPass + rr];
+                add(acc, fp_smem + 64 * (c & 0xFFFFu) + 16 * part, fp_smem + 64 * (c >> 16) + 16 * part);
+            }
+            uint4 o;
+            o.x = (unsigned)f2bf(acc[0]) | ((unsigned)f2bf(acc[1]) << 16);
+            o.y = (unsigned)f2bf(acc[2]) | ((unsigned)f2bf(acc[3]) << 16);
+            o.z = (unsigned)f2bf(acc[4]) | ((unsigned)f2bf(acc[5]) << 16);
+            o.w = (unsigned)f2bf(acc[6]) | ((unsigned)f2bf(acc[7]) << 16);
+            *reinterpret_cast<uint4 *>(z + (size_t)res * n_out + col) = o;
         }
-        uint4 o;
-        o.x = (unsigned)f2bf(acc[0]) | ((unsigned)f2bf(acc[1]) << 16);
-        o.y = (unsigned)f2bf(acc[2]) | ((unsigned)f2bf(acc[3]) << 16);
-        o.z = (unsigned)f2bf(acc[4]) | ((unsigned)f2bf(acc[5]) << 16);
-        o.w = (unsigned)f2bf(acc[6]) | ((unsigned)f2bf(acc[7]) << 16);
-        *reinterpret_cast<uint4 *>(z + (size_t)res * n_out + col) = o;
+        asm volatile("" ::: "memory");
     }
 }
 
@@ -459,12 +484,12 @@ extern "C" int fipa_factor_project(int32_t B, int32_t L, int32_t k, int32_t n_bi
     // One workgroup per compute unit and 32 columns; worth the loading of its table (about 100 KB) from kFpRows residues on.
     const int groups = (n_out + 31) / 32, parts = groups < 256 ? 256 / groups : 1;
     const size_t lds = fipa::factor_lds_bytes(k, n_bins, n_pos);
-    if (lds <= 160 * 1024 && (long long)k * (n_bins + n_pos) < 0xFFFF && rows >= (long long)parts * fipa::kFpRows) {
+    if (lds <= 160 * 1024 && (long long)k * (n_bins + n_pos) < 0xFFFF && rows >= (long long)parts * fipa::kFpRows && rows <= (1LL << 30)) {
         static fipa::LdsLimit limit;
         if (fipa::raise_lds_limit(limit, (const void *)fipa::fipa_factor_project_lds_kernel, (int)lds) != hipSuccess) return FIPA_ERR_LAUNCH;
         hipLaunchKernelGGL(fipa::fipa_factor_project_lds_kernel, dim3(groups, parts), dim3(fipa::kFpThreads), lds, stream, nbr_idx, nbr_bin,
                            (const fipa::bf16_t *)e_bin, (const fipa::bf16_t *)e_pos, bias, (fipa::bf16_t *)z, (int)rows, L, k, n_bins, n_pos,
-                           pos_mode, n_out, (int)((rows + parts - 1) / parts));
+                           pos_mode, n_out);
         return hipGetLastError() == hipSuccess ? FIPA_OK : FIPA_ERR_LAUNCH;
     }
     if (n_pos > 0)

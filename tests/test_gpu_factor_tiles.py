@@ -1,11 +1,12 @@
 """GPU parity of fipa_factor_project_backward at the edges of its residue tiles (32 per wave, eight waves) and row
-blocks (32 table rows), with masked residues that hold NaN, against the oracle."""
+blocks (32 table rows), with masked residues that hold NaN, against the oracle; and of fipa_factor_project with its tables in
+LDS at the edges of its groups of 16 residues."""
 import numpy as np
 import pytest
 
 from oracle import factor_ref
 from paper_2505_11580_amd import binding
-from tests.test_gpu_factor import _bf16
+from tests.test_gpu_factor import _bf16, check, make_tables
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +37,14 @@ def test_factor_backward_tiles(B, L, k, n_bins, n_pos, n_out, masked):
         if g is not None:
             # float32 sums against float64: a few 1e-7 of the largest sum of magnitudes (the bound of test_gpu_factor)
             assert np.abs(g.cpu().numpy().astype(np.float64) - w).max() <= 2e-6 * scale
+
+
+# 128 residues or more for each of 256 / ceil(n_out / 32) workgroups of a column group
+@pytest.mark.parametrize("B,L,k,n_bins,n_pos,n_out,pos_mode", [
+    (1, 1920, 33, 4, 5, 520, 1), (400, 5, 2, 3, 9, 520, 1), (1, 2049, 4, 16, 0, 512, 0), (3, 691, 64, 9, 25, 488, 1)])
+def test_projection_groups(B, L, k, n_bins, n_pos, n_out, pos_mode):
+    rng = np.random.default_rng(L)
+    idx = rng.integers(-1, L, size=(B, L, k))
+    idx[-1, L // 2:] = -1  # groups without neighbours
+    bins = np.where(idx < 0, -1, rng.integers(0, n_bins, size=(B, L, k)))
+    check(idx, bins, *make_tables(rng, k, n_bins, n_pos, n_out), pos_mode, "groups %d x %d" % (B, L))
