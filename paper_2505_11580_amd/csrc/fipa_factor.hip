@@ -221,7 +221,7 @@ constexpr int kFbZ = 32 * 128;                          // a tile's d_z: 32 rows
 constexpr int kFbCodes = 256 + 256;                     // 32 indices, 32 bins | 64 mask values
 template <int RB>
 struct FbCfg {
-    static constexpr int kStages = RB <= 3 ? 3 : 2, kCodeStages = kStages + 1;
+    static constexpr int kStages = RB <= 3 ? 3 : 2, kCodeStages = 4;
     static constexpr int kOnes = kStages * kFbZ + kCodeStages * kFbCodes;  // one-hot tile: 64 bytes per table row, its 16-byte slots c at c ^ (row / 4 mod 4)
     static constexpr int kWaveBytes = kOnes + 32 * RB * 64;
     static constexpr int kSum = RB * 2 * 16 * 64 * 4;   // bytes of a wave's sums
@@ -247,7 +247,7 @@ __device__ __forceinline__ void fb_load_at(const void *base, unsigned voff, unsi
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
 
-template <int RB>
+template <int RB, bool MASK>
 __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(const int *__restrict__ nbr_idx, const int *__restrict__ nbr_bin,
                                                                                const bf16_t *__restrict__ d_z, const uint8_t *__restrict__ mask,
                                                                                float *__restrict__ d_e_bin, float *__restrict__ d_e_pos,
@@ -265,10 +265,40 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
     const int ntiles = (rows + 31) / 32;
     const int own = wave < ntiles ? (ntiles - wave + kFbWaves - 1) / kFbWaves : 0;  // tiles wave, wave + 8, ...
 
-    // Loads of this wave's tile n, d_z of it and the indices, bins and mask of the next one (past the last tile: the last one again, so that
-    // every tile has as many).  Tiles are kFbWaves apart; rows and columns past the end: addresses of existing ones, what they bring is
-    // not used.
-    constexpr int kLoads = 6;
+    // ---- the wave's tiles, those without a residue that counts left out: 64 of them looked at at a time, a lane each --------------
+    int base = 0;  // the first of those 64
+    unsigned long long rest = 0ull;
+    auto look = [&] {
+        const int tile = wave + kFbWaves * (base + lane), r0 = 32 * tile;
+        unsigned any = 0u;
+        if (base + lane < own) {
+            if (r0 + 32 <= rows && (reinterpret_cast<uintptr_t>(mask) & 3u) == 0) {
+                const unsigned *m = reinterpret_cast<const unsigned *>(mask + r0);
+#pragma unroll
+                for (int x = 0; x < 8; ++x) any |= m[x];
+            } else {
+                for (int r = r0; r < min(r0 + 32, rows); ++r) any |= mask[r];
+            }
+        }
+        rest = __ballot(any != 0u);
+    };
+    int seen = 0;  // (no mask: the next tile)
+    auto next_tile = [&]() -> int {  // -1: no more
+        if constexpr (!MASK) return seen < own ? wave + kFbWaves * seen++ : -1;
+        while (rest == 0ull) {
+            if (base + 64 >= own) return -1;
+            base += 64;
+            look();
+        }
+        const int n = base + __builtin_ctzll(rest);
+        rest &= rest - 1ull;
+        return wave + kFbWaves * n;
+    };
+    if constexpr (MASK) look();
+
+    // Loads of a tile's indices, bins and mask, and of its d_z (past the last tile: the last one again, so that every step has as many).
+    // Rows and columns past the end: addresses of existing ones, what they bring is not used.
+    constexpr int kLoads = MASK ? 6 : 5;
     unsigned vz[4];
     const int l8 = lane >> 3, l7 = lane & 7;
 #pragma unroll
@@ -276,24 +306,22 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
         const int rr = 8 * q + l8;
         vz[q] = (unsigned)(rr * n_out + min(8 * (l7 ^ (((rr >> 1) & 1) << 2)), n_out - 8 - col0)) * 2;
     }
-    const int *const codes = g ? nbr_bin : nbr_idx;
-    auto issue_codes = [&](int n) {
-        const unsigned st = mine_lds + (n % C::kCodeStages) * kFbCodes + C::kStages * kFbZ;
-        const size_t res = min(32 * (wave + kFbWaves * min(n, own - 1)) + li, rows - 1);
-        fb_load<4>(codes + res * k + s, st);
-        if (mask) fb_load<1>(mask + res, st + 256);
-        else fb_load<4>(nbr_idx + res * k + s, st + 256);  // (not used)
+    const int *const codes = (g ? nbr_bin : nbr_idx) + s;
+    auto issue_codes = [&](int tile, int stage) {
+        const unsigned st = mine_lds + stage * kFbCodes + C::kStages * kFbZ;
+        const size_t res = min(32 * tile + li, rows - 1);
+        fb_load<4>(codes + res * k, st);
+        if constexpr (MASK) fb_load<1>(mask + res, st + 256);
     };
-    auto issue = [&](int n) {
-        issue_codes(n + 1);
-        const unsigned st = mine_lds + (n % C::kStages) * kFbZ;
-        const int res0 = 32 * (wave + kFbWaves * min(n, own - 1));
-        const bf16_t *base = d_z + (size_t)res0 * n_out + col0;
+    auto issue_z = [&](int tile, int stage) {
+        const unsigned st = mine_lds + stage * kFbZ;
+        const bf16_t *from = d_z + (size_t)tile * 32 * n_out + col0;
+        if (32 * tile + 32 <= rows) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            unsigned v = vz[q];
-            if (res0 + 32 > rows) v -= (unsigned)(max(8 * q + l8 - (rows - 1 - res0), 0) * n_out) * 2;
-            fb_load_at(base, v, st + 1024 * q);
+            for (int q = 0; q < 4; ++q) fb_load_at(from, vz[q], st + 1024 * q);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) fb_load_at(from, vz[q] - (unsigned)(max(8 * q + l8 - (rows - 1 - 32 * tile), 0) * n_out) * 2, st + 1024 * q);
         }
     };
 
@@ -309,54 +337,86 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
     for (int x = lane; x < 32 * RB * 4; x += 64) *reinterpret_cast<uint4 *>(ones + 16 * x) = (uint4){0u, 0u, 0u, 0u};
     // residue q of a group of 16 is value q mod 4 + 4 (q / 8) of the lanes of half q / 4 mod 2 (the order of the transposing read)
     const int slot = 2 * (li >> 4) + ((li >> 2) & 1), within = 2 * (4 * ((li >> 3) & 1) + (li & 3));
-    auto one_at = [&](int row) { return reinterpret_cast<bf16_t *>(ones + row * 64 + ((slot ^ ((row >> 2) & 3)) << 4) + within); };
+    auto one_at = [&](int row) { return row * 64 + ((slot ^ ((row >> 2) & 3)) << 4) + within; };
     const int aone = li * 64 + ((g ^ ((li >> 2) & 3)) << 4);  // (k-step t: slot 2 t + g)
-    const int turn = 32 * kFbWaves % L;
-    int i = (32 * wave + li) % L;  // place of this lane's residue in its chain
     const int e4 = (lane & 15) >> 2, grp2 = (lane >> 4) & 1, j4 = lane & 3;
     int az[2];
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) az[nb] = (4 * g + e4) * 128 + (nb ^ (e4 >> 1)) * 64 + (16 * grp2 + 4 * j4) * 2;
 
-    // of tile n, from its indices, bins and mask: this lane's one, whether it is set, and which residues count
-    bf16_t *one = one_at(0), *const one_b = one_at(R - 1);
-    bool filled = false;
+    // of a tile, from its indices, bins and mask: where this lane's one goes (a residue whose slot is empty or that does not count: to a place
+    // in the masks' room that nothing reads), and which residues count
+    const int nowhere = C::kStages * kFbZ + 384 + within - C::kOnes, bias_one = one_at(R - 1);
+    const bool my_table = g == 0 || n_pos > 0;
+    const int pos_lo = pos_mode ? -half : 0, pos_hi = pos_mode ? half : n_pos - 1, pos_0 = n_bins + (pos_mode ? half : 0);
+    const int row_lo = g ? pos_lo : 0, row_hi = g ? pos_hi : n_bins - 1, row_0 = g ? pos_0 : 0;
+    const unsigned inv_L = 0xFFFFFFFFu / (unsigned)L;
+    const int li_L = li % L;
+    int one = nowhere, j, bn, mk = 1;
     unsigned vmask = 0u;
-    int j, bn, mk;
-    auto read_codes = [&](int n) {
-        const char *const st = mine + C::kStages * kFbZ + (n % C::kCodeStages) * kFbCodes;
+    auto read_codes = [&](int stage) {
+        const char *const st = mine + C::kStages * kFbZ + stage * kFbCodes;
         j = *reinterpret_cast<const int *>(st + 4 * li);
         bn = *reinterpret_cast<const int *>(st + 128 + 4 * li);
-        mk = *reinterpret_cast<const int *>(st + 256 + 4 * li);
+        if constexpr (MASK) mk = *reinterpret_cast<const int *>(st + 256 + 4 * li);
     };
-    auto decode = [&](int n) {
-        const int res = 32 * (wave + kFbWaves * n) + li;
-        const bool valid = res < rows && (mask ? mk != 0 : true);
+    auto decode = [&](int tile) {
+        const bool valid = 32 * tile + li < rows && mk != 0;
         vmask = (unsigned)__ballot(valid);  // (the two halves agree)
-        const int pc = pos_mode == 0 ? min(j, n_pos - 1) : min(max(j - i, -half), half) + half;
-        i += turn;
+        unsigned r0 = 32u * tile;  // place of the tile's first residue in its chain
+        r0 -= __umulhi(r0, inv_L) * (unsigned)L;
+        if (r0 >= (unsigned)L) r0 -= L;
+        int i = (int)r0 + li_L;
         if (i >= L) i -= L;
-        filled = valid && j >= 0 && j < L && (g == 0 || n_pos > 0);
-        one = one_at(filled ? (g ? n_bins + pc : min(max(bn, 0), n_bins - 1)) : 0);
+        const int code = g ? (pos_mode ? j - i : j) : bn;
+        const bool filled = valid && (unsigned)j < (unsigned)L && my_table;
+        one = filled ? one_at(min(max(code, row_lo), row_hi) + row_0) : nowhere;
     };
-    if (own > 0) {
-        issue_codes(0);
-        for (int n = 0; n < C::kStages - 1; ++n) issue(n);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::kStages - 1) * kLoads) : "memory");
+    auto advance = [](int stage, int n) { return stage + 1 == n ? 0 : stage + 1; };
+    // tiles n, n + 1, .. of the wave (n: the one that is multiplied); where there is none, the one before again
+    constexpr int S = C::kStages;
+    int now = next_tile(), ahead[S], zs = 0, cs = 0;  // stages of tile n
+    if (now >= 0) {
+        bool more = true;
+        int prev = now;
+#pragma unroll
+        for (int x = 0; x < S; ++x) {
+            ahead[x] = more ? next_tile() : -1;
+            more = ahead[x] >= 0;
+        }
+        issue_codes(now, 0);
+#pragma unroll
+        for (int x = 0; x < S - 1; ++x) {  // codes of tile n + 1 + x, d_z of tile n + x
+            const int z_tile = prev;
+            if (ahead[x] >= 0) prev = ahead[x];
+            issue_codes(prev, x + 1);
+            issue_z(z_tile, x);
+        }
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * kLoads) : "memory");
         read_codes(0);
-        decode(0);
+        decode(now);
     }
-    for (int n = 0; n < own; ++n) {
+    int last = now;  // the tile whose loads are repeated past the end
+#pragma unroll
+    for (int x = 0; x < S - 1; ++x) last = now >= 0 && ahead[x] >= 0 ? ahead[x] : last;  // tile n + S - 1, or the last one
+    while (now >= 0) {
         // d_z of tile n and the codes of tile n + 1 have landed; the reads of tile n - 1, whose stage the next loads take, are done
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((C::kStages - 2) * kLoads) : "memory");
-        issue(n + C::kStages - 1);
-        char *const st = mine + (n % C::kStages) * kFbZ;
-        read_codes(n + 1);  // (past the last tile: not used)
-        if (vmask != 0u) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * kLoads) : "memory");
+        {
+            const int z_tile = last;
+            if (ahead[S - 1] >= 0) last = ahead[S - 1];
+            issue_codes(last, (cs + S) & (C::kCodeStages - 1));
+            issue_z(z_tile, zs == 0 ? S - 1 : zs - 1);
+        }
+        unsigned z0 = zs * kFbZ;
+        asm volatile("" : "+s"(z0));  // (so that what follows is an address and constants)
+        char *const st = mine + z0;
+        read_codes((cs + 1) & (C::kCodeStages - 1));  // (past the last tile: not used)
+        {
             const bool counts = (vmask >> li) & 1u;
             auto set = [&](bf16_t v) {
-                if (filled) *one = v;
-                if (s == 0 && g == 0 && counts) *one_b = v;
+                *reinterpret_cast<bf16_t *>(ones + one) = v;
+                if (s == 0 && g == 0 && counts) *reinterpret_cast<bf16_t *>(ones + bias_one) = v;
                 asm volatile("" ::: "memory");  // (the LDS accesses of a wave execute in order)
             };
             set(0x3F80);
@@ -368,17 +428,11 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
                 asm volatile("" ::: "memory");
             }
             bf16x8 bz[2][2], a[2][RB];
+            const char *zp[2] = {st + az[0], st + az[1]};
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    const bf16x4 lo = lds_read_tr(st + az[nb] + 16 * t * 128), hi = lds_read_tr(st + az[nb] + (16 * t + 8) * 128);
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        bz[t][nb][x] = lo[x];
-                        bz[t][nb][4 + x] = hi[x];
-                    }
-                }
+                for (int nb = 0; nb < 2; ++nb) bz[t][nb] = lds_read_tr(zp[nb] + 16 * t * 128, zp[nb] + (16 * t + 8) * 128);
 #pragma unroll
                 for (int mb = 0; mb < RB; ++mb) a[t][mb] = *reinterpret_cast<const bf16x8 *>(ones + 32 * 64 * mb + (aone ^ (32 * t)));
             }
@@ -391,7 +445,13 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
 #pragma unroll
                     for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][mb], bz[t][nb], acc[mb][nb], 0, 0, 0);
         }
-        decode(n + 1);
+        now = ahead[0];
+        decode(now);  // (past the last tile: not used)
+#pragma unroll
+        for (int x = 0; x < S - 1; ++x) ahead[x] = ahead[x + 1];
+        ahead[S - 1] = ahead[S - 1] >= 0 ? next_tile() : -1;
+        zs = advance(zs, S);
+        cs = (cs + 1) & (C::kCodeStages - 1);
     }
     wait_vmem<0>();  // (loads past the last tile still write LDS)
     // the waves' sums, in a fixed order: 4..7 to 0..3, 2..3 to 0..1, 1 to 0
@@ -446,16 +506,16 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
     }
 }
 
-template <int RB>
+template <int RB, bool MASK>
 hipError_t launch_factor_backward(dim3 grid, hipStream_t stream, const int *nbr_idx, const int *nbr_bin, const bf16_t *d_z, const uint8_t *mask,
                                   float *d_e_bin, float *d_e_pos, float *d_bias, int rows, int L, int k, int n_bins, int n_pos, int pos_mode,
                                   int n_out)
 {
     constexpr int lds = FbCfg<RB>::kBytes;
     static LdsLimit limit;
-    const hipError_t e = raise_lds_limit(limit, (const void *)fipa_factor_backward_kernel<RB>, lds);
+    const hipError_t e = raise_lds_limit(limit, (const void *)fipa_factor_backward_kernel<RB, MASK>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fipa_factor_backward_kernel<RB>, grid, dim3(64 * kFbWaves), lds, stream, nbr_idx, nbr_bin, d_z, mask, d_e_bin, d_e_pos,
+    hipLaunchKernelGGL((fipa_factor_backward_kernel<RB, MASK>), grid, dim3(64 * kFbWaves), lds, stream, nbr_idx, nbr_bin, d_z, mask, d_e_bin, d_e_pos,
                        d_bias, rows, L, k, n_bins, n_pos, pos_mode, n_out);
     return hipGetLastError();
 }
@@ -523,11 +583,15 @@ extern "C" int fipa_factor_project_backward(int32_t B, int32_t L, int32_t k, int
     if ((reinterpret_cast<uintptr_t>(nbr_idx) & 3u) != 0 || (reinterpret_cast<uintptr_t>(nbr_bin) & 3u) != 0) return FIPA_ERR_ALIGNMENT;
     const dim3 grid((unsigned)((n_out + 63) / 64), (unsigned)k);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const auto launch = RB == 1   ? fipa::launch_factor_backward<1>
-                        : RB == 2 ? fipa::launch_factor_backward<2>
-                        : RB == 3 ? fipa::launch_factor_backward<3>
-                        : RB == 4 ? fipa::launch_factor_backward<4>
-                                  : fipa::launch_factor_backward<5>;
+    const auto with = [&](auto M) {
+        constexpr bool masked = decltype(M)::value;
+        return RB == 1   ? fipa::launch_factor_backward<1, masked>
+               : RB == 2 ? fipa::launch_factor_backward<2, masked>
+               : RB == 3 ? fipa::launch_factor_backward<3, masked>
+               : RB == 4 ? fipa::launch_factor_backward<4, masked>
+                         : fipa::launch_factor_backward<5, masked>;
+    };
+    const auto launch = mask ? with(std::true_type{}) : with(std::false_type{});
     return launch(grid, stream, nbr_idx, nbr_bin, (const fipa::bf16_t *)d_z, mask, d_e_bin, n_pos > 0 ? d_e_pos : nullptr, d_bias, B * L, L, k,
                   n_bins, n_pos, pos_mode, n_out) == hipSuccess
                ? FIPA_OK
