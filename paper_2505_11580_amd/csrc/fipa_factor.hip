@@ -206,14 +206,16 @@ __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(con
 //
 // One workgroup per (slot, 64 output columns), eight waves, each of which takes every eighth tile of 32
 // residues with all rows of the tables: nothing is shared between waves until their sums are added at the
-// end, so there is no barrier in the loop, and two waves per SIMD cover each other.  A tile's d_z rows
-// arrive by direct loads two tiles ahead, its indices, bins and mask one tile earlier; d_z is read with the transposing LDS
+// end, so there is no barrier in the loop, and two waves per SIMD cover each other.  A tile without a residue that counts is left out.
+// A tile's d_z rows arrive by direct loads two tiles ahead, its indices, bins and mask one tile earlier; d_z is read with the transposing LDS
 // read.  The one-hot operand is a tile of the wave in LDS, [table row][residue], read as it stands: a tile's residues set their
-// ones and take them back behind it.
+// ones and take them back behind it.  The operands of a tile are read while the tile before is multiplied, each into the registers
+// of the one that has just been used (two sets of registers: spilled).
 // 32768 residues (60 % of them valid), 20 slots, 82 rows, 512 columns: 555 us with four waves that shared each tile and its one-hot tile
 // (one barrier per tile, the mask on the way of every load) -> 131 us with the operand formed by comparing 16-bit codes in
-// registers (16 vector instructions per operand) -> 103 us, of which 36 go with the loads of d_z (every slot streams it again) and 25
-// with the matrix instructions.  A bit per residue and row, set with LDS or, and a table of
+// registers (16 vector instructions per operand) -> 103 us with the tile of ones -> 60 us without the masked tiles and with fewer instructions
+// around the products.  Without a mask 110 -> 99 -> 86 us (operands read ahead), of which 41 are matrix instructions; loads of the indices
+// and bins from neighbouring addresses would save 4.  A bit per residue and row, set with LDS or, and a table of
 // the 256 possible operands: 165 us (many residues share a row, and the or's on one address run one after the other).
 // rows = n_bins + n_pos + 1 (the last one collects the bias gradient, in slot 0's workgroups).
 constexpr int kFbWaves = 8, kFbMaxRowBlocks = 5;
@@ -399,7 +401,10 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
     int last = now;  // the tile whose loads are repeated past the end
 #pragma unroll
     for (int x = 0; x < S - 1; ++x) last = now >= 0 && ahead[x] >= 0 ? ahead[x] : last;  // tile n + S - 1, or the last one
-    while (now >= 0) {
+    // The operands of a tile are read while the tile before is multiplied, each into the registers of the one that has just been used.
+    bf16x8 bz[2][2], a[2][RB];
+    auto step = [&](auto First) {
+        constexpr bool first = decltype(First)::value;
         // d_z of tile n and the codes of tile n + 1 have landed; the reads of tile n - 1, whose stage the next loads take, are done
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * kLoads) : "memory");
         {
@@ -412,39 +417,38 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
         asm volatile("" : "+s"(z0));  // (so that what follows is an address and constants)
         char *const st = mine + z0;
         read_codes((cs + 1) & (C::kCodeStages - 1));  // (past the last tile: not used)
-        {
-            const bool counts = (vmask >> li) & 1u;
-            auto set = [&](bf16_t v) {
-                *reinterpret_cast<bf16_t *>(ones + one) = v;
-                if (s == 0 && g == 0 && counts) *reinterpret_cast<bf16_t *>(ones + bias_one) = v;
-                asm volatile("" ::: "memory");  // (the LDS accesses of a wave execute in order)
-            };
-            set(0x3F80);
-            if (vmask != 0xFFFFFFFFu) {
-                // what a masked or missing residue holds must not reach the products: 0 x NaN would
+        const bool counts = (vmask >> li) & 1u;
+        auto set = [&](bf16_t v) {
+            *reinterpret_cast<bf16_t *>(ones + one) = v;
+            if (s == 0 && g == 0 && counts) *reinterpret_cast<bf16_t *>(ones + bias_one) = v;
+            asm volatile("" ::: "memory");  // (the LDS accesses of a wave execute in order)
+        };
+        set(0x3F80);
+        if (vmask != 0xFFFFFFFFu) {
+            // what a masked or missing residue holds must not reach the products: 0 x NaN would
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (!((vmask >> (8 * q + l8)) & 1u)) *reinterpret_cast<uint4 *>(st + 1024 * q + 16 * lane) = (uint4){0u, 0u, 0u, 0u};
-                asm volatile("" ::: "memory");
-            }
-            bf16x8 bz[2][2], a[2][RB];
-            const char *zp[2] = {st + az[0], st + az[1]};
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) bz[t][nb] = lds_read_tr(zp[nb] + 16 * t * 128, zp[nb] + (16 * t + 8) * 128);
-#pragma unroll
-                for (int mb = 0; mb < RB; ++mb) a[t][mb] = *reinterpret_cast<const bf16x8 *>(ones + 32 * 64 * mb + (aone ^ (32 * t)));
-            }
+            for (int q = 0; q < 4; ++q)
+                if (!((vmask >> (8 * q + l8)) & 1u)) *reinterpret_cast<uint4 *>(st + 1024 * q + 16 * lane) = (uint4){0u, 0u, 0u, 0u};
             asm volatile("" ::: "memory");
-            set(0);
+        }
+        const char *const zp[2] = {st + az[0], st + az[1]};
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t) {
 #pragma unroll
-                for (int mb = 0; mb < RB; ++mb)
+            for (int mb = 0; mb < RB; ++mb) {
+                if constexpr (!first) {
 #pragma unroll
                     for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][mb], bz[t][nb], acc[mb][nb], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                a[t][mb] = *reinterpret_cast<const bf16x8 *>(ones + 32 * 64 * mb + (aone ^ (32 * t)));
+            }
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) bz[t][nb] = lds_read_tr(zp[nb] + 16 * t * 128, zp[nb] + (16 * t + 8) * 128);
+            if constexpr (!first) __builtin_amdgcn_sched_barrier(0);
         }
+        asm volatile("" ::: "memory");
+        set(0);
         now = ahead[0];
         decode(now);  // (past the last tile: not used)
 #pragma unroll
@@ -452,6 +456,16 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
         ahead[S - 1] = ahead[S - 1] >= 0 ? next_tile() : -1;
         zs = advance(zs, S);
         cs = (cs + 1) & (C::kCodeStages - 1);
+    };
+    if (now >= 0) {
+        step(std::true_type{});
+        while (now >= 0) step(std::false_type{});
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int mb = 0; mb < RB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][mb], bz[t][nb], acc[mb][nb], 0, 0, 0);
     }
     wait_vmem<0>();  // (loads past the last tile still write LDS)
     // the waves' sums, in a fixed order: 4..7 to 0..3, 2..3 to 0..1, 1 to 0
