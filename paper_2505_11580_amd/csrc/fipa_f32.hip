@@ -144,7 +144,9 @@ __device__ __forceinline__ float group_sum(float x)
 // shares per workgroup the units are small (16 or 32 rows) and every CU gets several.
 // B = 2, L = 1024, H = 12, r c_z = 256: 0.44 ms, 43 % of the 157 TFLOP/s of the fp32 matrix pipe (the
 // vector-ALU form, one wave per four rows, 5.32 ms); L = 64, H = 4, r c_z = 32: 8 us (40 us).
-template <int NCH, int NT, bool EXACT, int RG>
+// PACK (EXACT, RG = 1): short chains, no records in memory: a workgroup forms those of the keys that it loads, and the batch's reference
+// point, itself, and the call is one launch (see f32_one_launch).  One chain of 64 residues, H = 4, r c_z = 32: 13.2 -> 10.2 us.
+template <int NCH, int NT, bool EXACT, int RG, bool PACK>
 __global__ __launch_bounds__(256, EXACT && (NCH + NT) * 4 + 60 <= 256 ? 2 : 1) void fipa_attn_f32_kernel(F32Params p)
 {
     constexpr int KS = 4 / RG;
@@ -164,7 +166,14 @@ __global__ __launch_bounds__(256, EXACT && (NCH + NT) * 4 + 60 <= 256 ? 2 : 1) v
     const int rg = wave % RG, ks = wave / RG;
     const int i_wg = (unit - bh * p.n_rt) * (16 * RG);
     const int L = p.L, H = p.H, DZ = p.DZ, nq = 3 * p.Pq, nv = 3 * p.Pv;
-    const int kvlen = p.kvlen[b];
+    float cen[3];
+    int kvlen;
+    if constexpr (PACK) {
+        batch_reference(p, b, cen, kvlen);
+    } else {
+        kvlen = p.kvlen[b];
+        for (int a = 0; a < 3; ++a) cen[a] = p.cen[4 * b + a];
+    }
     const int nch = G.nch, nt = G.nt;
     const int zoff = G.zoff, voff = G.voff, cch = G.c16 / 16;
     const float coef = kLog2e * 0.5f * p.gamma[h] * p.w_L * p.w_C;
@@ -203,7 +212,7 @@ __global__ __launch_bounds__(256, EXACT && (NCH + NT) * 4 + 60 <= 256 ? 2 : 1) v
     float qg[12];
     const float *qg_mem = hr + (size_t)iq * G.HRW + G.c16 + G.nq4 + G.nh16;
     if (EXACT) {
-        const float *R = p.rot + urow * 9, *t = p.trans + urow * 3, *cen = p.cen + 4 * b, *src = p.q_pts + row * nq;
+        const float *R = p.rot + urow * 9, *t = p.trans + urow * 3, *src = p.q_pts + row * nq;
 #pragma unroll
         for (int x = 0; x < 12; ++x) {
             const int pp = x / 3, a = x % 3;
@@ -222,6 +231,34 @@ __global__ __launch_bounds__(256, EXACT && (NCH + NT) * 4 + 60 <= 256 ? 2 : 1) v
     for (int j0 = 0; j0 < kvlen; j0 += 16 * KS) {
         __syncthreads();
         const int nj = min(16 * KS, kvlen - j0);  // rows past it are zero and masked
+        if constexpr (PACK) {
+            // the record of every key: a thread per point, then one per 16 bytes of scalars or padding
+            constexpr int kPts = 12, kRest = 10;
+#pragma unroll
+            for (int it = 0; it < 16 * KS * kPts / 256; ++it) {
+                const int idx = threadIdx.x + 256 * it, jj = idx / kPts, pt = idx - kPts * jj;
+                const size_t ukey = (size_t)b * L + min(j0 + jj, L - 1);
+                const bool ok = jj < nj && (p.mask ? p.mask[ukey] != 0 : true);
+                const float *src = pt < 4 ? p.k_pts + (ukey * H + h) * 12 + 3 * pt : p.v_pts + (ukey * H + h) * 24 + 3 * (pt - 4);
+                const float *R = p.rot + ukey * 9, *t = p.trans + ukey * 3;
+                float *dst = tiles + jj * S + (pt < 4 ? 16 + 3 * pt : 44 + 3 * (pt - 4));
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const float val = R[3 * a] * src[0] + R[3 * a + 1] * src[1] + R[3 * a + 2] * src[2] + (t[a] - cen[a]);
+                    dst[a] = ok ? val : 0.f;
+                }
+            }
+#pragma unroll
+            for (int it = 0; it < (16 * KS * kRest + 255) / 256; ++it) {
+                const int idx = threadIdx.x + 256 * it, jj = idx / kRest, x = idx - kRest * jj;
+                if (jj >= 16 * KS) break;
+                const size_t ukey = (size_t)b * L + min(j0 + jj, L - 1);
+                const bool ok = jj < nj && (p.mask ? p.mask[ukey] != 0 : true);
+                const f32x4 val = *reinterpret_cast<const f32x4 *>((x < 4 ? p.k : p.v) + (ukey * H + h) * 16 + 4 * (x & 3));
+                *reinterpret_cast<f32x4 *>(tiles + jj * S + (x < 4 ? 4 * x : x < 8 ? 28 + 4 * (x - 4) : 68 + 4 * (x - 8))) =
+                    ok && x < 8 ? val : (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
+        } else
 #pragma unroll 4
         for (int idx = threadIdx.x; idx < 16 * KS * nhr; idx += 256) {
             const int jj = idx / nhr, x = 4 * (idx - jj * nhr);
@@ -379,7 +416,7 @@ __global__ __launch_bounds__(256, EXACT && (NCH + NT) * 4 + 60 <= 256 ? 2 : 1) v
         for (int idx = x0; idx < nv; idx += 16) {
             const int pp = idx / 3, x = idx - 3 * pp;
             float val = 0.f;
-            for (int y = 0; y < 3; ++y) val += R[3 * y + x] * (rb[p.c + 3 * pp + y] - (t[y] - p.cen[4 * b + y]));
+            for (int y = 0; y < 3; ++y) val += R[3 * y + x] * (rb[p.c + 3 * pp + y] - (t[y] - cen[y]));
             p.o_pts[ro * nv + idx] = valid ? val : 0.f;
         }
         const float *z1 = p.z1 + ui * DZ;
@@ -423,17 +460,23 @@ F32Layout f32_layout(const fipa_desc &d)
     return w;
 }
 
+// Chains short enough that every workgroup forms the records of all keys itself (fipa_attn_f32_kernel<.., PACK>) in less than a launch takes.
+// Two launches | one, us per call: r c_z = 32, H = 4, L = 64 14.0 | 11.1, 256 21.7 | 17.2; B = 2, H = 12, L = 256 24.8 | 20.0, 384 34.4 | 46.5;
+// r c_z = 128, B = 2, H = 12, L = 64 16.8 | 12.3, 256 37.4 | 32.0, 384 76.0 | 74.5; r c_z = 256, H = 12, L = 64 20.8 | 18.1, 128 27.3 | 26.6,
+// 192 34.2 | 35.1, 256 40.9 | 43.8; r c_z = 512, H = 12, L = 64 30.8 | 29.1, 128 43.2 | 43.9.
+bool f32_one_launch(int L, int DZ) { return L <= (DZ <= 128 ? 256 : DZ <= 256 ? 128 : 64); }
+
 size_t f32_lds_bytes(const F32Geom &g, int KS) { return ((size_t)KS * 16 * g.S + KS * 16 + 128) * sizeof(float); }
 
-template <int NCH, int NT, bool EXACT, int RG>
+template <int NCH, int NT, bool EXACT, int RG, bool PACK = false>
 hipError_t launch_attn(const F32Params &p, hipStream_t stream)
 {
     const int KS = 4 / RG;
     const size_t lds = f32_lds_bytes(p.g, KS);
     static LdsLimit lim;
-    const hipError_t e = raise_lds_limit(lim, (const void *)fipa_attn_f32_kernel<NCH, NT, EXACT, RG>, (int)lds);
+    const hipError_t e = raise_lds_limit(lim, (const void *)fipa_attn_f32_kernel<NCH, NT, EXACT, RG, PACK>, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((fipa_attn_f32_kernel<NCH, NT, EXACT, RG>), dim3((p.n_units + 7) / 8 * 8), dim3(256), lds, stream, p);
+    hipLaunchKernelGGL((fipa_attn_f32_kernel<NCH, NT, EXACT, RG, PACK>), dim3((p.n_units + 7) / 8 * 8), dim3(256), lds, stream, p);
     return hipGetLastError();
 }
 
@@ -463,19 +506,23 @@ hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, hipStream
 
     StageTimer timer(stream);
     timer.begin(0);
-    const unsigned per_head = ((unsigned)d.L * (p.g.HRW / 4) + 255u) / 256u;
-    hipLaunchKernelGGL(fipa_pack_f32_kernel, dim3(d.H * per_head, d.B), dim3(256), 0, stream, p);
-    timer.end(0);
-
-    timer.begin(1);  // the fp32 kernel contains the epilogue; stage 2 stays empty
     const long long bh = (long long)d.B * d.H;
     // 16-row workgroups where 32-row ones would not give every CU two (the widest records fit LDS only as 32-key tiles)
     const bool small = bh * ((d.L + 31) / 32) < 512 && f32_lds_bytes(p.g, 4) <= 160 * 1024;
+    const bool one_launch = exact && small && f32_one_launch(d.L, p.DZ);
+    if (!one_launch) {
+        const unsigned per_head = ((unsigned)d.L * (p.g.HRW / 4) + 255u) / 256u;
+        hipLaunchKernelGGL(fipa_pack_f32_kernel, dim3(d.H * per_head, d.B), dim3(256), 0, stream, p);
+    }
+    timer.end(0);
+
+    timer.begin(1);  // the fp32 kernel contains the epilogue; stage 2 stays empty
     p.n_rt = small ? (d.L + 15) / 16 : (d.L + 31) / 32;
     p.n_units = (int)(bh * p.n_rt);
     hipError_t e;
 #define FIPA_F32_RUN(NCH, NT, EXACT) \
-    e = small ? launch_attn<NCH, NT, EXACT, 1>(p, stream) : launch_attn<NCH, NT, EXACT, 2>(p, stream)
+    e = one_launch ? launch_attn<NCH, NT, EXACT, 1, EXACT>(p, stream) \
+        : small    ? launch_attn<NCH, NT, EXACT, 1>(p, stream) : launch_attn<NCH, NT, EXACT, 2>(p, stream)
     if (exact && p.g.nch == 2) FIPA_F32_RUN(2, 4, true);
     else if (exact && p.g.nch == 3) FIPA_F32_RUN(3, 5, true);
     else if (exact && p.g.nch == 5) FIPA_F32_RUN(5, 7, true);
