@@ -36,6 +36,7 @@ PER_FILE = {
     "fipa_bf16_bwd_kernel.hip": _VGPR_FORM,
     "fipa_bf16_bwd_stored.hip": _VGPR_FORM,
     "fipa_bf16_bwd_keys.hip": _VGPR_FORM,
+    "fipa_f32_split.hip": _VGPR_FORM,
     # the neighbour search specifies its distance arithmetic with one rounding per operation
     "fipa_knn.hip": ["-ffp-contract=off"],
 }

@@ -50,7 +50,7 @@ int check_forward_args(const fipa_desc *desc, const FwdArgs &a)
 
 hipError_t enqueue_forward(const fipa_desc &desc, const FwdArgs &a, void *workspace, size_t workspace_bytes, hipStream_t stream)
 {
-    return desc.dtype == FIPA_DTYPE_F32 ? f32_forward(desc, a, workspace, stream) : bf16_forward(desc, a, workspace, workspace_bytes, stream);
+    return desc.dtype == FIPA_DTYPE_F32 ? f32_forward(desc, a, workspace, workspace_bytes, stream) : bf16_forward(desc, a, workspace, workspace_bytes, stream);
 }
 
 }  // namespace fipa
@@ -106,7 +106,7 @@ int fipa_forward(const fipa_desc *desc, const void *q, const void *k, const void
                    ? FIPA_OK
                    : FIPA_ERR_LAUNCH;
     }
-    const size_t need = desc->dtype == FIPA_DTYPE_F32 ? f32_forward_workspace(*desc) : bf16_forward_workspace_min(*desc);
+    const size_t need = desc->dtype == FIPA_DTYPE_F32 ? f32_forward_workspace_min(*desc) : bf16_forward_workspace_min(*desc);
     if (workspace_bytes < need) return FIPA_ERR_WORKSPACE;
     return enqueue_forward(*desc, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? FIPA_OK
                                                                                                   : FIPA_ERR_LAUNCH;

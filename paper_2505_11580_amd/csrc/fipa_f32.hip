@@ -5,6 +5,7 @@
 // 1e-4); the squared distances stay explicit differences on the vector ALU, because the expanded
 // form cancels at global coordinates.
 #include "fipa_bf16_common.h"
+#include "fipa_f32.h"
 
 namespace fipa {
 
@@ -143,7 +144,8 @@ __device__ __forceinline__ float group_sum(float x)
 // needs one 4-byte LDS operand per lane, so LDS and the vector ALU have room to spare.  With KS key
 // shares per workgroup the units are small (16 or 32 rows) and every CU gets several.
 // B = 2, L = 1024, H = 12, r c_z = 256: 0.44 ms, 43 % of the 157 TFLOP/s of the fp32 matrix pipe (the
-// vector-ALU form, one wave per four rows, 5.32 ms); L = 64, H = 4, r c_z = 32: 8 us (40 us).
+// vector-ALU form, one wave per four rows, 5.32 ms); L = 64, H = 4, r c_z = 32: 8 us (40 us).  Longer chains of
+// AlphaFold2's head shape at r c_z = 64 to 256 run on split operands (fipa_f32_split.hip).
 // PACK (EXACT, RG = 1): short chains, no records in memory: a workgroup forms those of the keys that it loads, and the batch's reference
 // point, itself, and the call is one launch (see f32_one_launch).  One chain of 64 residues, H = 4, r c_z = 32: 13.2 -> 10.2 us.
 template <int NCH, int NT, bool EXACT, int RG, bool PACK>
@@ -482,10 +484,17 @@ hipError_t launch_attn(const F32Params &p, hipStream_t stream)
 
 }  // namespace
 
-size_t f32_forward_workspace(const fipa_desc &d) { return f32_layout(d).total; }
+size_t f32_forward_workspace_min(const fipa_desc &d) { return f32_layout(d).total; }
 
-hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, hipStream_t stream)
+size_t f32_forward_workspace(const fipa_desc &d)
 {
+    const size_t least = f32_forward_workspace_min(d), split = f32_split_applies(d) ? f32_split_workspace(d) : 0;
+    return split > least ? split : least;
+}
+
+hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
+{
+    if (f32_split_applies(d) && ws_bytes >= f32_split_workspace_min(d)) return f32_split_forward(d, a, ws, ws_bytes, stream);
     const F32Layout w = f32_layout(d);
     char *base = static_cast<char *>(ws);
     F32Params p;

@@ -115,7 +115,8 @@ hipError_t launch_prep(const fipa_desc &d, const float *trans, const uint8_t *ma
 
 // fp32 direct path (fipa_f32.hip)
 size_t f32_forward_workspace(const fipa_desc &d);
-hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, hipStream_t stream);
+size_t f32_forward_workspace_min(const fipa_desc &d);  // what the forward runs in, if not at its best
+hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream);
 
 // bf16 MFMA path (fipa_bf16_*.hip)
 size_t bf16_forward_workspace(const fipa_desc &d);

@@ -90,7 +90,7 @@ int packed_plan(const fipa_desc *desc, const int32_t *cu, bool backward, PackedP
     if (!pl.one_launch) pl.d.B = 1;
     rc = fipa_workspace_bytes(&pl.d, &pl.fwd_bytes, backward ? &pl.bwd_bytes : nullptr);
     if (rc != FIPA_OK) return rc;
-    pl.fwd_least = desc->dtype == FIPA_DTYPE_F32 ? f32_forward_workspace(pl.d) : bf16_forward_workspace_min(pl.d);
+    pl.fwd_least = desc->dtype == FIPA_DTYPE_F32 ? f32_forward_workspace_min(pl.d) : bf16_forward_workspace_min(pl.d);
     pl.part_stride = (desc->H + desc->H * desc->cz + 3) / 4 * 4;
     const size_t cu_bytes = align_up((size_t)(desc->B + 1) * sizeof(int), 256);
     pl.fwd_head = pl.one_launch ? cu_bytes : 0;

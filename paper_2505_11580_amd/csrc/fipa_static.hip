@@ -54,7 +54,7 @@ extern "C" int fipa_forward_static(const fipa_desc *desc, const void *q, const v
     const int rc = fipa::check_forward_args(desc, a);
     if (rc != FIPA_OK) return rc;
     if (desc->flags & FIPA_FLAG_KEEP_FORWARD) return FIPA_ERR_UNSUPPORTED;  // (nothing is kept in the shared scratch)
-    const size_t need = desc->dtype == FIPA_DTYPE_F32 ? fipa::f32_forward_workspace(*desc) : fipa::bf16_forward_workspace_min(*desc);
+    const size_t need = desc->dtype == FIPA_DTYPE_F32 ? fipa::f32_forward_workspace_min(*desc) : fipa::bf16_forward_workspace_min(*desc);
     if (need > (size_t)FIPA_STATIC_SCRATCH_BYTES) return FIPA_ERR_WORKSPACE;  // problem too large for the static scratch
     hipError_t e = hipSuccess;
     void *ws = scratch_address(&e);

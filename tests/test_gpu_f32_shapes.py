@@ -41,3 +41,38 @@ def test_f32_lse_and_far_keys():
     inp = wl.make_inputs(0, L=150, H=3, cz=64, chain=True)
     inp["mask"] = (np.random.default_rng(3).random((1, 150)) < 0.7).astype(np.uint8)
     gu.check(inp, label="fp32 scattered mask, chain")
+
+
+# split operands: every width, one residue past a block and a tile, blocks and whole tiles without a valid residue, key ranges in one and
+# several parts (fewer and more than 128 tiles), columns of one rank narrower than 64
+@pytest.mark.parametrize("kw", [
+    dict(L=384, cz=128, r=2, H=1), dict(L=417, cz=64, r=2, H=2, B=2, varlen=True, min_len=1), dict(L=513, cz=64, r=1, H=3),
+    dict(L=545, cz=16, r=4, H=2, B=2, varlen=True, min_len=40), dict(L=385, cz=8, r=16, H=1), dict(L=161, B=4, H=6, cz=32, r=8),
+    dict(L=170, B=8, H=12, cz=256, r=1, varlen=True, min_len=1), dict(L=520, B=3, H=12, cz=128, r=1, varlen=True, min_len=100)])
+def test_f32_split_operands(kw):
+    kw = dict(dict(B=1, H=4, chain=True, trans_scale=0.3), **kw)
+    gu.check(wl.make_inputs(0, **kw), label="fp32 split %s" % kw)
+
+
+def test_f32_split_operands_in_every_workspace():
+    # the space that the query asks for, without the split key range's, and without the key blocks (fp32 matrix instructions)
+    import torch
+    from paper_2505_11580_amd import binding
+    inp = wl.make_inputs(0, B=1, L=450, H=3, cz=64, r=2, chain=True, trans_scale=0.3)
+    inp["mask"] = (np.random.default_rng(5).random((1, 450)) < 0.6).astype(np.uint8)
+    desc, dev = binding.upload(inp)
+    want = gu.oracle_forward_chunked(inp)
+    full = binding.workspace_bytes(desc)[0]
+    parts, least = 256 * 128 * (44 + 64) * 4, (3 * 450 * 76 * 4 + 255) // 256 * 256 + 2 * 256
+    for size in (full, full - parts, full - parts - 256, least):
+        out = binding.alloc_outputs(desc)
+        for n in gu.NAMES:
+            out[n].fill_(float("nan"))
+        out["workspace"] = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+        binding.forward(desc, dev, out)
+        torch.cuda.synchronize()
+        for n in gu.NAMES:
+            assert gu.rel_err(out[n].cpu().numpy().astype(np.float64), want[n]) <= gu.TOL["fp32"], (size, n)
+    out["workspace"] = torch.empty(least - 256, dtype=torch.uint8, device="cuda:0")
+    with pytest.raises(binding.FipaError):
+        binding.forward(desc, dev, out)
