@@ -172,31 +172,28 @@ __global__ __launch_bounds__(256, 4) void fipa_bwd_pack_bf16_kernel(BwdPackParam
     }
 }
 
-// One wave per (batch, residue), four residues per workgroup: chain rule from dQ^, dK^, dV^ back to
-// the inputs.  Nothing is exchanged between the waves, so there is no workgroup barrier: sums over
-// the lanes of a wave go through shuffles in a fixed order.
-//   first the per-head tasks -- 2 Pq + Pv point gradients and the three scalar rows of each head --
+// Two waves per (batch, residue): chain rule from dQ^, dK^, dV^ back to the inputs.  Nothing is exchanged between the waves, so
+// there is no workgroup barrier: sums over the lanes of a wave go through shuffles in a fixed order.
+//   one takes the per-head tasks -- 2 Pq + Pv point gradients and the three scalar rows of each head --
 //   dealt to the lanes kind by kind (few bytes, many small scattered accesses);
-//   then the pair factors (the bulk of the bytes): a lane owns four neighbouring lifted columns and
+//   the other (`pair`) the pair factors (the bulk of the bytes): a lane owns four neighbouring lifted columns and
 //   adds up the heads one after the other (16-byte loads of the four big arrays, all independent);
 //   where the lifted width is below 256 the lanes form 64 / (DZ / 4) groups that take every
 //   group-th head and are added at the end, above it a lane takes DZ / 256 sets of columns.
 // A residue that does not count reads nothing and writes zeros.
-// Measured at B = 2, L = 4096, H = 12, r c_z = 256 (330 MB moved): 80 us; 32 packed chains of 64 to 512 residues 102; four chains of 2.7k to
-// 7.1k residues padded to 8192, r c_z = 512, 307 (with the lifted output read here as well, and for padding too: 108, 138, 670).
 // One workgroup per residue with the sums of its threads meeting in LDS behind workgroup barriers was slower (191 us against 139).
 template <int NG>
-__global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackParams p)
+__device__ __forceinline__ void unpack_residue(const BwdUnpackParams &p, unsigned residue, bool pair)
 {
     const int lane = threadIdx.x & 63;
-    const long long rr = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (b, i)
-    if (rr >= (long long)p.B * p.L) return;
-    const int b = (int)(rr / p.L), i = (int)(rr - (long long)b * p.L);
+    if (residue >= (unsigned)p.B * p.L) return;
+    const int rr = (int)residue, b = rr / p.L, i = rr - b * p.L;  // (b, i)
     const int c = p.c, Pq = p.Pq, Pv = p.Pv, nq = 3 * Pq, D = kDH + p.DZ;
     if (i >= user_len(p, b)) return;  // (packed batch: the grid covers the longest chain)
     const size_t urow = user_row(p, b, i);
     const bool valid = p.mask ? p.mask[urow] != 0 : true;
     if (!valid) {  // (nothing was formed for it)
+        if (pair) return;
         const int nc = p.H * c / 8, nk = p.H * Pq * 3, nv = p.H * Pv * 3;
         for (int x = lane; x < nc; x += 64) {
             const uint4 zero = {0u, 0u, 0u, 0u};
@@ -214,6 +211,49 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
         if (p.d_rot) {
             if (lane < 3) p.d_trans[urow * 3 + lane] = 0.f;
             if (lane < 9) p.d_rot[urow * 9 + lane] = 0.f;
+        }
+        return;
+    }
+
+    if (pair) {  // ---- pair factors: sums over heads
+        constexpr int HG = 64 / NG;
+        const int grp = lane % NG, hg = HG == 1 ? 0 : lane / NG;
+        for (int x0 = 4 * grp; x0 < p.DZ; x0 += 256) {
+            const int d0 = x0 % p.cz;
+            f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
+            const float kscale = p.dVz ? kLn2 : 1.f, qscale = p.w_L * p.ds_inv;
+            // through o~ = z1^T U (see the pack kernel)
+            const uint2 up = *reinterpret_cast<const uint2 *>(p.d_z1 + urow * p.DZ + x0), low = *reinterpret_cast<const uint2 *>(p.d_z2 + urow * p.DZ + x0);
+#pragma unroll 4
+            for (int h = hg; h < p.H; h += HG) {
+                const size_t bh = (size_t)b * p.H + h;
+                const size_t row = (bh * p.Lp + i) * D + kDH + x0;
+                const f32x4 dq = *reinterpret_cast<const f32x4 *>(p.dQhat + row);
+                const size_t zrow = (bh * p.Lp + i) * p.z_pitch + x0;
+                const f32x4 dk = *reinterpret_cast<const f32x4 *>(p.dKz + zrow);
+                f32x4 dv = {0.f, 0.f, 0.f, 0.f};
+                if (p.dVz) dv = *reinterpret_cast<const f32x4 *>(p.dVz + zrow);
+                const f32x4 wb = *reinterpret_cast<const f32x4 *>(p.w_b + (size_t)h * p.cz + d0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s1[e] += qscale * wb[e] * dq[e];   // z1: through the bias vector b^{h1} = w_L w_b z1
+                    s2[e] += kscale * dk[e] + dv[e];   // z2: as key feature (the log2e sits on the query side) and as value feature
+                }
+            }
+            for (int o = NG; o < 64; o <<= 1)  // (HG > 1: the head groups, added pairwise in a fixed order)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s1[e] += __shfl_xor(s1[e], o);
+                    s2[e] += __shfl_xor(s2[e], o);
+                }
+            if (hg == 0) {
+                s1[0] += __uint_as_float((up.x << 16) | (low.x & 0xFFFFu));
+                s1[1] += __uint_as_float((up.x & 0xFFFF0000u) | (low.x >> 16));
+                s1[2] += __uint_as_float((up.y << 16) | (low.y & 0xFFFFu));
+                s1[3] += __uint_as_float((up.y & 0xFFFF0000u) | (low.y >> 16));
+                *reinterpret_cast<uint2 *>(p.d_z1 + urow * p.DZ + x0) = (uint2){bf16_pair(s1[0], s1[1]), bf16_pair(s1[2], s1[3])};
+                *reinterpret_cast<uint2 *>(p.d_z2 + urow * p.DZ + x0) = (uint2){bf16_pair(s2[0], s2[1]), bf16_pair(s2[2], s2[3])};
+            }
         }
         return;
     }
@@ -346,49 +386,6 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
         }
     }
 
-    // ---- pair factors: sums over heads -------------------------------------------------------------
-    {
-        constexpr int HG = 64 / NG;
-        const int grp = lane % NG, hg = HG == 1 ? 0 : lane / NG;
-        for (int x0 = 4 * grp; x0 < p.DZ; x0 += 256) {
-            const int d0 = x0 % p.cz;
-            f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
-            const float kscale = p.dVz ? kLn2 : 1.f, qscale = p.w_L * p.ds_inv;
-            // through o~ = z1^T U (see the pack kernel)
-            const uint2 up = *reinterpret_cast<const uint2 *>(p.d_z1 + urow * p.DZ + x0), low = *reinterpret_cast<const uint2 *>(p.d_z2 + urow * p.DZ + x0);
-#pragma unroll 4
-            for (int h = hg; h < p.H; h += HG) {
-                const size_t bh = (size_t)b * p.H + h;
-                const size_t row = (bh * p.Lp + i) * D + kDH + x0;
-                const f32x4 dq = *reinterpret_cast<const f32x4 *>(p.dQhat + row);
-                const size_t zrow = (bh * p.Lp + i) * p.z_pitch + x0;
-                const f32x4 dk = *reinterpret_cast<const f32x4 *>(p.dKz + zrow);
-                f32x4 dv = {0.f, 0.f, 0.f, 0.f};
-                if (p.dVz) dv = *reinterpret_cast<const f32x4 *>(p.dVz + zrow);
-                const f32x4 wb = *reinterpret_cast<const f32x4 *>(p.w_b + (size_t)h * p.cz + d0);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    s1[e] += qscale * wb[e] * dq[e];   // z1: through the bias vector b^{h1} = w_L w_b z1
-                    s2[e] += kscale * dk[e] + dv[e];   // z2: as key feature (the log2e sits on the query side) and as value feature
-                }
-            }
-            for (int o = NG; o < 64; o <<= 1)  // (HG > 1: the head groups, added pairwise in a fixed order)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    s1[e] += __shfl_xor(s1[e], o);
-                    s2[e] += __shfl_xor(s2[e], o);
-                }
-            if (hg == 0) {
-                s1[0] += __uint_as_float((up.x << 16) | (low.x & 0xFFFFu));
-                s1[1] += __uint_as_float((up.x & 0xFFFF0000u) | (low.x >> 16));
-                s1[2] += __uint_as_float((up.y << 16) | (low.y & 0xFFFFu));
-                s1[3] += __uint_as_float((up.y & 0xFFFF0000u) | (low.y >> 16));
-                *reinterpret_cast<uint2 *>(p.d_z1 + urow * p.DZ + x0) = (uint2){bf16_pair(s1[0], s1[1]), bf16_pair(s1[2], s1[3])};
-                *reinterpret_cast<uint2 *>(p.d_z2 + urow * p.DZ + x0) = (uint2){bf16_pair(s2[0], s2[1]), bf16_pair(s2[2], s2[3])};
-            }
-        }
-    }
-
     // frame gradients of this residue: sum over the lanes in a fixed order
     if (p.d_rot) {
 #pragma unroll
@@ -411,8 +408,7 @@ __global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackPara
 // d gamma^h = -(w_L w_C / 2) * sum over (batch, residue) of the partial sums, in a fixed order:
 // one workgroup of 1024 threads per head, four independent chains of loads per thread.
 // (cu: row offsets of a packed batch, whose chain b has cu[b+1] - cu[b] residues, or null.)
-__global__ __launch_bounds__(1024) void fipa_bwd_gamma_kernel(const float *gpart, float *d_gamma, int B, int H,
-                                                              int L, int Lp, const int *cu, float coef)
+__device__ __forceinline__ void gamma_sum(const float *gpart, float *d_gamma, int B, int H, int L, int Lp, const int *cu, float coef)
 {
     __shared__ float red[1024];
     const int h = blockIdx.x, tid = threadIdx.x;
@@ -455,14 +451,14 @@ constexpr int kWbChunk = 32;
 
 // One workgroup per (chunk, NH heads): a thread takes four neighbouring lifted columns (16 bytes of
 // dQ^ per head, 8 of z1) of every NRG-th residue of the chunk, all loads independent; the NRG partial sums
-// per column meet in LDS and are added in a fixed order.  r c_z <= 512 here, so NRG >= 2.  Bound by reading dQ^: 32 packed
+// per column meet in LDS and are added in a fixed order.  r c_z <= 512 here, so NRG >= 2.  Bound by reading dQ^; in a launch of its own 32 packed
 // chains of 64 to 512 residues, H = 12, r c_z = 256 22.9 us for 111 MB, four chains of 2.7k to 7.1k residues at r c_z = 512 121 for
 // 484 MB (a workgroup per head, which finds every residue's place and reads z1 again: 30 and 138).
 template <int NH>
-__global__ __launch_bounds__(256) void fipa_bwd_wb_partial_kernel(BwdUnpackParams p)
+__device__ __forceinline__ void wb_partial(const BwdUnpackParams &p, int chunk, int h0, int nchunk)
 {
     __shared__ f32x4 red[NH][256];  // [head][residue group][DZ]: NRG * DZ = 1024 numbers per head
-    const int h0 = blockIdx.y * NH, chunk = blockIdx.x, D = kDH + p.DZ;
+    const int D = kDH + p.DZ;
     const int nres = p.total_rows;  // rows of the caller's tensors: B L, or the packed batch's total
     const int NG = p.DZ / 4, NRG = 256 / NG;
     const int cg = threadIdx.x % NG, rg = threadIdx.x / NG, x0 = 4 * cg;
@@ -513,19 +509,37 @@ __global__ __launch_bounds__(256) void fipa_bwd_wb_partial_kernel(BwdUnpackParam
         if (h0 + u >= p.H) break;
         f32x4 t = {0.f, 0.f, 0.f, 0.f};
         for (int g = 0; g < NRG; ++g) t += red[u][g * NG + col];
-        *reinterpret_cast<f32x4 *>(p.wpart + ((size_t)(h0 + u) * gridDim.x + chunk) * p.DZ + 4 * col) = t;
+        *reinterpret_cast<f32x4 *>(p.wpart + ((size_t)(h0 + u) * nchunk + chunk) * p.DZ + 4 * col) = t;
     }
 }
+
+// For every 32 residues 16 workgroups of four waves (two residues each), then the workgroups that form the partial sums of d_w_b over 32
+// rows, which read the same dQ^ at about the same time.  With the sums kernel behind it, us (a wave per residue that took its heads
+// first and then its pair factors, the partial sums and the two last sums in launches of their own | this): 32 packed chains of 64 to 512
+// residues, r c_z = 256 136 | 121, B = 2, L = 4096 108 | 94, B = 2, L = 2048 60 | 60, four chains of 2.7k to 7.1k residues, r c_z = 512 455 | 374.
+// Of the first one's 114 us the pair factors take 46 (5.0 TB/s), the heads 61 and the partial sums 14 where they run alone.
+template <int NG, int NH>
+__global__ __launch_bounds__(256) void fipa_bwd_unpack_bf16_kernel(BwdUnpackParams p, int nchunk)
+{
+    const unsigned group = blockIdx.y + 32768 * blockIdx.z, y = blockIdx.x;
+    if (y < 16) {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        unpack_residue<NG>(p, 32u * group + 2 * y + (wave >> 1), (wave & 1) != 0);
+    } else if (group < (unsigned)nchunk) {
+        wb_partial<NH>(p, group, (y - 16) * NH, nchunk);
+    }
+}
+
 
 // One workgroup of 1024 threads per head and 32 (where c_z is no multiple of 32: 8) of its c_z columns, of every factor slice: the
 // chunks are dealt to the groups of threads that hold those columns (four independent chains of loads each); groups and
 // slices are added in a fixed order.  (One workgroup per head: 82 us for 12 heads of 1024 chunks of 512 columns -> 25 us.)
 __host__ __device__ inline int wb_columns(int cz) { return cz % 32 == 0 ? 32 : 8; }
 
-__global__ __launch_bounds__(1024) void fipa_bwd_wb_reduce_kernel(BwdUnpackParams p, int nchunk)
+__device__ __forceinline__ void wb_reduce(const BwdUnpackParams &p, int block, int nchunk)
 {
     __shared__ float part[1024];  // [chunk group][slice][column]
-    const int h = blockIdx.x, CB = wb_columns(p.cz), d0 = blockIdx.y * CB;
+    const int h = blockIdx.x, CB = wb_columns(p.cz), d0 = block * CB;
     const int NCOL = CB * p.r, NCG = 1024 / NCOL;  // (r c_z <= 512 here)
     const int cidx = threadIdx.x % NCOL, grp = threadIdx.x / NCOL;
     if (grp < NCG) {
@@ -547,6 +561,13 @@ __global__ __launch_bounds__(1024) void fipa_bwd_wb_reduce_kernel(BwdUnpackParam
             for (int g = 0; g < NCG; ++g) t += part[g * NCOL + rho * CB + threadIdx.x];
         p.d_w_b[(size_t)h * p.cz + d0 + threadIdx.x] = p.w_L * p.ds_inv * t;
     }
+}
+
+// The two of them in one launch (5 us each, most of it start-up): a head's d gamma first, then its column blocks of d_w_b.
+__global__ __launch_bounds__(1024) void fipa_bwd_sums_kernel(BwdUnpackParams p, int nchunk)
+{
+    if (blockIdx.y == 0) gamma_sum(p.gpart, p.d_gamma, p.B, p.H, p.L, p.Lp, p.cu, -0.5f * p.w_L * p.w_C);
+    else wb_reduce(p, blockIdx.y - 1, nchunk);
 }
 
 // The lifted widths whose gradients go through stored weights (fipa_bf16_bwd_keys.hip, fipa_bf16_bwd_stored.hip), at any length (width 128:
@@ -720,22 +741,19 @@ hipError_t launch_bwd_pack_bf16(const BwdPackParams &p, hipStream_t stream)
 
 hipError_t launch_bwd_unpack_bf16(const BwdUnpackParams &p, hipStream_t stream)
 {
+    const int nchunk = (p.total_rows + kWbChunk - 1) / kWbChunk;
+    // (four heads at a time from as many chunks on as fill the chip that way: 4096 residues, r c_z = 256, one 12.2 us, two 14.6, four 15.0;
+    // 9080 residues 30, 23.1, 22.9; 32768 residues padded, 512 columns, 138, 133, 121; fewer heads than four: one)
+    const int NH = nchunk < 256 || p.H < 4 ? 1 : 4, nw = p.d_w_b ? (p.H + NH - 1) / NH : 0;
+    const int groups = (int)(((long long)p.B * p.L + 31) / 32);
+    const dim3 grid(16 + nw, groups < 32768 ? groups : 32768, (groups + 32767) / 32768);
     const hipError_t e = with_column_lanes(p.DZ, [&](auto N) {
-        hipLaunchKernelGGL(fipa_bwd_unpack_bf16_kernel<decltype(N)::value>, dim3((unsigned)(((long long)p.B * p.L + 3) / 4)), dim3(256), 0, stream, p);
+        const auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p, nchunk); };
+        if (NH == 1) run(fipa_bwd_unpack_bf16_kernel<decltype(N)::value, 1>);
+        else run(fipa_bwd_unpack_bf16_kernel<decltype(N)::value, 4>);
     });
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fipa_bwd_gamma_kernel, dim3(p.H), dim3(1024), 0, stream, p.gpart, p.d_gamma, p.B, p.H, p.L,
-                       p.Lp, p.cu, -0.5f * p.w_L * p.w_C);
-    if (p.d_w_b) {
-        const int nchunk = (p.total_rows + kWbChunk - 1) / kWbChunk;
-        // (four heads at a time from as many chunks on as fill the chip that way: 4096 residues, r c_z = 256, one 12.2 us, two 14.6, four 15.0;
-        // 9080 residues 30, 23.1, 22.9; 32768 residues padded, 512 columns, 138, 133, 121; fewer heads than four: one)
-        if (nchunk < 256 || p.H < 4)
-            hipLaunchKernelGGL(fipa_bwd_wb_partial_kernel<1>, dim3(nchunk, p.H), dim3(256), 0, stream, p);
-        else
-            hipLaunchKernelGGL(fipa_bwd_wb_partial_kernel<4>, dim3(nchunk, (p.H + 3) / 4), dim3(256), 0, stream, p);
-        hipLaunchKernelGGL(fipa_bwd_wb_reduce_kernel, dim3(p.H, p.cz / wb_columns(p.cz)), dim3(1024), 0, stream, p, nchunk);
-    }
+    hipLaunchKernelGGL(fipa_bwd_sums_kernel, dim3(p.H, p.d_w_b ? 1 + p.cz / wb_columns(p.cz) : 1), dim3(1024), 0, stream, p, nchunk);
     return hipGetLastError();
 }
 
