@@ -105,18 +105,18 @@ struct GemmTile {
 
 // Seg: type of the tensors that the columns are scattered to; void: one float32 matrix C.
 template <class T, bool CONCAT_A, class Seg>
-__global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
+__device__ __forceinline__ void gemm_tile(const GemmParams &p, int bx, int by, int bz)  // (bx, by, bz): row tile, column tile, part of K
 {
     constexpr bool SCATTER = !std::is_void_v<Seg>;
     extern __shared__ __attribute__((aligned(16))) char lds[];  // [buffer][A tile | W tile]
     constexpr int kBuf = (T::TM + T::TN) * kGRS;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 31, kg = lane >> 5;
-    const int m0 = blockIdx.x * T::TM, n0 = blockIdx.y * T::TN;
+    const int m0 = bx * T::TM, n0 = by * T::TN;
     // the tile's slice of the bias (zero where there is none; a split-K product adds it in its first part only);
     // the first barrier below publishes it
     float *bias_l = reinterpret_cast<float *>(lds + T::LDS_BYTES);
-    if (tid < T::TN) bias_l[tid] = (p.bias && n0 + tid < p.N && blockIdx.z == 0) ? p.bias[n0 + tid] : 0.f;
+    if (tid < T::TN) bias_l[tid] = (p.bias && n0 + tid < p.N && bz == 0) ? p.bias[n0 + tid] : 0.f;
 
     // staging: thread t moves chunks (row t/8 + 32 j, 8 k-values t%8): j < CA of A, j < CW of W
     // (fetch only requests; whatever needs the loaded values -- the float -> bfloat16 conversion
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
     int kc0 = 0, nkc = (p.K + kGK - 1) / kGK;
     if (p.chunks_per_split > 0) {
-        kc0 = blockIdx.z * p.chunks_per_split;
+        kc0 = bz * p.chunks_per_split;
         nkc = min(nkc, kc0 + p.chunks_per_split);
     }
     Staged st;
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
                 }
             }
         } else {
-            float *C = p.C + (p.chunks_per_split > 0 ? (size_t)blockIdx.z * p.M * p.N : 0);
+            float *C = p.C + (p.chunks_per_split > 0 ? (size_t)bz * p.M * p.N : 0);
             if (col + kPer <= p.N && (p.N & (kPer - 1)) == 0) {
                 *reinterpret_cast<uint4 *>(C + (size_t)row * p.N + col) = piece;
             } else {
@@ -271,15 +271,25 @@ __global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
 }
 
 template <class T, bool CONCAT_A, class Seg>
+__global__ __launch_bounds__(256) void fipa_gemm_kernel(GemmParams p)
+{
+    gemm_tile<T, CONCAT_A, Seg>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+int gemm_splits(const GemmParams &g)
+{
+    const int nkc = (g.K + kGK - 1) / kGK;
+    return g.chunks_per_split > 0 ? (nkc + g.chunks_per_split - 1) / g.chunks_per_split : 1;
+}
+
+template <class T, bool CONCAT_A, class Seg>
 hipError_t launch_gemm(const GemmParams &g, hipStream_t stream)
 {
     static LdsLimit lds_limit;
     hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_gemm_kernel<T, CONCAT_A, Seg>, T::LDS_TOTAL);
     if (e != hipSuccess) return e;
-    const int nkc = (g.K + kGK - 1) / kGK;
-    const int nsplit = g.chunks_per_split > 0 ? (nkc + g.chunks_per_split - 1) / g.chunks_per_split : 1;
     hipLaunchKernelGGL((fipa_gemm_kernel<T, CONCAT_A, Seg>),
-                       dim3((g.M + T::TM - 1) / T::TM, (g.N + T::TN - 1) / T::TN, nsplit), dim3(256), T::LDS_TOTAL,
+                       dim3((g.M + T::TM - 1) / T::TM, (g.N + T::TN - 1) / T::TN, gemm_splits(g)), dim3(256), T::LDS_TOTAL,
                        stream, g);
     return hipGetLastError();
 }
@@ -437,10 +447,10 @@ hipError_t launch_transposes(const TransposeParams &p, hipStream_t stream)
 }
 
 // The norms' part of the gradient of the concatenation: d_o_pts += d_norm * o_pts / |o_pts| (nothing at a zero vector).
-__global__ __launch_bounds__(256) void fipa_norm_gradient_kernel(const float *__restrict__ d_norm, const float *__restrict__ o_pts,
-                                                                  float *__restrict__ d_o_pts, size_t n)
+__device__ __forceinline__ void norm_gradient(const float *__restrict__ d_norm, const float *__restrict__ o_pts, float *__restrict__ d_o_pts,
+                                              size_t n, unsigned block)
 {
-    const size_t pt = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t pt = (size_t)block * 256 + threadIdx.x;
     if (pt >= n) return;
     const float *op = o_pts + 3 * pt;
     const float nrm = sqrtf(op[0] * op[0] + op[1] * op[1] + op[2] * op[2]);
@@ -450,10 +460,9 @@ __global__ __launch_bounds__(256) void fipa_norm_gradient_kernel(const float *__
 
 // out[i] = sum over the nsplit partial matrices (fixed order), n entries each; n is a multiple of 4
 // (every matrix summed here has d_s, a multiple of 16, as one of its dimensions).
-__global__ __launch_bounds__(256) void fipa_sum_partials_kernel(const float *__restrict__ part, float *__restrict__ out,
-                                                                 size_t n, int nsplit)
+__device__ __forceinline__ void sum_partials(const float *__restrict__ part, float *__restrict__ out, size_t n, int nsplit, unsigned block)
 {
-    const size_t i = 4 * ((size_t)blockIdx.x * 256 + threadIdx.x);
+    const size_t i = 4 * ((size_t)block * 256 + threadIdx.x);
     if (i >= n) return;
     f32x4 s = *reinterpret_cast<const f32x4 *>(part + i);
     for (int z = 1; z < nsplit; ++z) {
@@ -464,11 +473,26 @@ __global__ __launch_bounds__(256) void fipa_sum_partials_kernel(const float *__r
     *reinterpret_cast<f32x4 *>(out + i) = s;
 }
 
+__global__ __launch_bounds__(256) void fipa_sum_partials_kernel(const float *__restrict__ part, float *__restrict__ out,
+                                                                 size_t n, int nsplit)
+{
+    sum_partials(part, out, n, nsplit, blockIdx.x);
+}
+
+// Both in one launch (5 us each alone).
+__global__ __launch_bounds__(256) void fipa_sum_and_norm_kernel(const float *__restrict__ part, float *__restrict__ out, size_t n, int nsplit,
+                                                                unsigned sum_blocks, const float *__restrict__ d_norm,
+                                                                const float *__restrict__ o_pts, float *__restrict__ d_o_pts, size_t n_pts)
+{
+    if (blockIdx.x < sum_blocks) sum_partials(part, out, n, nsplit, blockIdx.x);
+    else norm_gradient(d_norm, o_pts, d_o_pts, n_pts, blockIdx.x - sum_blocks);
+}
+
 // out[r] = sum over the C entries of row r of a bf16 matrix [R, C] (one workgroup per row, fixed order).
-__global__ __launch_bounds__(256) void fipa_rowsum_bf16_kernel(const bf16_t *__restrict__ src, float *__restrict__ out, int C)
+__device__ __forceinline__ void row_sum(const bf16_t *__restrict__ src, float *__restrict__ out, int C, int r)
 {   // (rows may carry a zero tail: C is the stored row length)
-    __shared__ float red[256];
-    const int r = blockIdx.x;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    float *const red = reinterpret_cast<float *>(lds);
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
     for (int c = 8 * threadIdx.x; c < C; c += 8 * 256) {  // (the stored length is a multiple of 64)
         const uint4 v = *reinterpret_cast<const uint4 *>(src + (size_t)r * C + c);
@@ -483,6 +507,48 @@ __global__ __launch_bounds__(256) void fipa_rowsum_bf16_kernel(const bf16_t *__r
         __syncthreads();
     }
     if (threadIdx.x == 0) out[r] = red[0];
+}
+
+// Two products that do not need each other, and the row sums of a transposed matrix (a bias gradient), in one launch: each of the
+// products leaves most of the chip waiting for its chain of round trips.  Seg: what the columns of the second one are scattered to.
+// B = 2, L = 2048, d_s = 256, us in three launches | in this one: d W_out, d cat, d b_out 41 | 33; d s, d W_in, d b_in 40 | 23.
+using PairTile = GemmTile<2, 2, 1, 1>;
+struct PairParams {
+    GemmParams a, b;
+    const bf16_t *rows;  // [n_rows, C]
+    float *row_sums;
+    int C, tiles_a, tiles_b;
+};
+
+template <class Seg>
+__global__ __launch_bounds__(256) void fipa_gemm_pair_kernel(PairParams p)
+{
+    int t = blockIdx.x;
+    if (t < p.tiles_a) {
+        const int gx = (p.a.M + PairTile::TM - 1) / PairTile::TM, gy = (p.a.N + PairTile::TN - 1) / PairTile::TN;
+        gemm_tile<PairTile, false, void>(p.a, t % gx, t / gx % gy, t / gx / gy);
+    } else if (t < p.tiles_a + p.tiles_b) {
+        t -= p.tiles_a;
+        const int gx = (p.b.M + PairTile::TM - 1) / PairTile::TM, gy = (p.b.N + PairTile::TN - 1) / PairTile::TN;
+        gemm_tile<PairTile, false, Seg>(p.b, t % gx, t / gx % gy, t / gx / gy);
+    } else {
+        row_sum(p.rows, p.row_sums, p.C, t - p.tiles_a - p.tiles_b);
+    }
+}
+
+// row_sums may be null; n_rows: of the matrix whose rows are summed.
+template <class Seg>
+hipError_t launch_gemm_pair(const GemmParams &a, const GemmParams &b, const bf16_t *rows, float *row_sums, int n_rows, int C, hipStream_t stream)
+{
+    static LdsLimit lds_limit;
+    const hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_gemm_pair_kernel<Seg>, PairTile::LDS_TOTAL);
+    if (e != hipSuccess) return e;
+    const auto tiles = [](const GemmParams &g) {
+        return ((g.M + PairTile::TM - 1) / PairTile::TM) * ((g.N + PairTile::TN - 1) / PairTile::TN) * gemm_splits(g);
+    };
+    const PairParams p{a, b, rows, row_sums, C, tiles(a), tiles(b)};
+    hipLaunchKernelGGL(fipa_gemm_pair_kernel<Seg>, dim3(p.tiles_a + p.tiles_b + (row_sums ? n_rows : 0)), dim3(256), PairTile::LDS_TOTAL, stream, p);
+    return hipGetLastError();
 }
 
 constexpr int kWgradChunks = 8;  // K chunks (of 64 rows of the batch) per workgroup of a weight-gradient product
@@ -682,18 +748,15 @@ hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, con
         gc.seg_start[x + 1] = gc.seg_start[x] + up_widths[x];
     }
     gc.seg_start[5] = gc.seg_start[6] = n_cat;
-    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, float>(gc, stream)));
-    const size_t n_pts = (size_t)M * d.H * d.Pv;
-    hipLaunchKernelGGL(fipa_norm_gradient_kernel, dim3((unsigned)((n_pts + 255) / 256)), dim3(256), 0, stream,
-                       (const float *)(base + w.d_norm), f.o_pts, (float *)(base + w.d_o_pts), n_pts);
     const int nkc = Mp / kGK, nsplit = (nkc + kWgradChunks - 1) / kWgradChunks;
     GemmParams gw = {};
     gw.M = d_s; gw.N = n_cat; gw.K = Mp;
     gw.A = gT; gw.W = (const bf16_t *)(base + w.catT); gw.C = (float *)(base + w.part); gw.chunks_per_split = kWgradChunks;
-    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, void>(gw, stream)));
-    hipLaunchKernelGGL(fipa_sum_partials_kernel, dim3((unsigned)(((size_t)d_s * n_cat / 4 + 255) / 256)), dim3(256), 0, stream,
-                       gw.C, g.d_w_out, (size_t)d_s * n_cat, nsplit);
-    if (g.d_b_out) hipLaunchKernelGGL(fipa_rowsum_bf16_kernel, dim3(d_s), dim3(256), 0, stream, gT, g.d_b_out, Mp);
+    FIPA_TRY(launch_gemm_pair<float>(gw, gc, gT, g.d_b_out, d_s, Mp, stream));
+    const size_t n_pts = (size_t)M * d.H * d.Pv, n_w = (size_t)d_s * n_cat;
+    const unsigned sum_blocks = (unsigned)((n_w / 4 + 255) / 256);
+    hipLaunchKernelGGL(fipa_sum_and_norm_kernel, dim3(sum_blocks + (unsigned)((n_pts + 255) / 256)), dim3(256), 0, stream, gw.C, g.d_w_out, n_w, nsplit,
+                       sum_blocks, (const float *)(base + w.d_norm), f.o_pts, (float *)(base + w.d_o_pts), n_pts);
     FIPA_TRY(hipGetLastError());
 
     // ---- the core's backward -----------------------------------------------------------------------
@@ -723,14 +786,12 @@ hipError_t module_backward(const fipa_desc &d, int d_s, const ModuleArgs &a, con
     GemmParams gs = {};
     gs.M = M; gs.N = d_s; gs.K = n_in;
     gs.A = dX; gs.W = (const bf16_t *)(base + w.w_inT); gs.C = g.d_s_in;
-    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, void>(gs, stream)));
     GemmParams gi = {};
     gi.M = n_in; gi.N = d_s; gi.K = Mp;
     gi.A = dXT; gi.W = (const bf16_t *)(base + w.sT); gi.C = (float *)(base + w.part); gi.chunks_per_split = kWgradChunks;
-    FIPA_TRY((launch_gemm<GemmTile<2, 2, 1, 1>, false, void>(gi, stream)));
+    FIPA_TRY(launch_gemm_pair<void>(gs, gi, dXT, g.d_b_in, n_in, Mp, stream));
     hipLaunchKernelGGL(fipa_sum_partials_kernel, dim3((unsigned)(((size_t)n_in * d_s / 4 + 255) / 256)), dim3(256), 0, stream,
                        gi.C, g.d_w_in, (size_t)n_in * d_s, nsplit);
-    if (g.d_b_in) hipLaunchKernelGGL(fipa_rowsum_bf16_kernel, dim3(n_in), dim3(256), 0, stream, dXT, g.d_b_in, Mp);
 #undef FIPA_TRY
     return hipGetLastError();
 }
