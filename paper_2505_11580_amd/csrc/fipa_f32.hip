@@ -145,7 +145,7 @@ __device__ __forceinline__ float group_sum(float x)
 // shares per workgroup the units are small (16 or 32 rows) and every CU gets several.
 // B = 2, L = 1024, H = 12, r c_z = 256: 0.44 ms, 43 % of the 157 TFLOP/s of the fp32 matrix pipe (the
 // vector-ALU form, one wave per four rows, 5.32 ms); L = 64, H = 4, r c_z = 32: 8 us (40 us).  Longer chains of
-// AlphaFold2's head shape at r c_z = 64 to 256 run on split operands (fipa_f32_split.hip).
+// AlphaFold2's head shape at r c_z = 32 to 256 run on split operands (fipa_f32_split.hip).
 // PACK (EXACT, RG = 1): short chains, no records in memory: a workgroup forms those of the keys that it loads, and the batch's reference
 // point, itself, and the call is one launch (see f32_one_launch).  One chain of 64 residues, H = 4, r c_z = 32: 13.2 -> 10.2 us.
 template <int NCH, int NT, bool EXACT, int RG, bool PACK>

@@ -11,7 +11,7 @@
 // B = 2, L = 1024, H = 12, r c_z = 256: 448 us on the fp32 matrix instructions (fipa_f32.hip) -> 184; 4.9 us per key block, of
 // which the 222 matrix instructions take 3.8 at the clock that they leave (17.3 ns each), 32 us before and behind the loop.
 // Distance from float64 (2-norm, o | o_pts | o_pair | lse): 4.50e-7 | 2.40e-6 | 4.49e-7 | 3.78e-7 -> 4.40e-7 | 2.39e-6 | 4.43e-7 |
-// 3.73e-7; no larger at any of the sizes compared (200 to 2048 residues, r c_z = 64 to 256).
+// 3.73e-7; no larger at any of the sizes compared (450 to 2048 residues, r c_z = 32 to 256).
 #include "fipa_gfx950.h"
 #include "fipa_f32.h"
 
@@ -28,7 +28,8 @@ struct Fs {
     static constexpr int ZROW = 2 * DZ, ZP = 32 * ZROW, ZBLK = 3 * ZP;
     static constexpr int K = 0, KP = 1024, V = 3 * KP, VP = 4096, G = V + 3 * VP, M = G + 1536, HBLK = 17408;  // (M + 128, to whole KiB)
     static constexpr int STAGE = ZBLK + HBLK;
-    static constexpr int kDma = ZBLK / 4096 + HBLK / 4096 + 1;  // 1 KiB pieces that a wave requests of a block
+    static constexpr int kDma = (ZBLK + 4095) / 4096 + HBLK / 4096 + 1;  // 1 KiB pieces that a wave requests of a block
+    static constexpr bool apart(int cb) { return cb >= NB || DZ == 32; }  // column blocks that are summed apart for 16 keys
     static constexpr int RS = DZ + 44;  // floats of a row of results: pair part, v | Vg (40), reference and sum
     static constexpr int kLds = 2 * STAGE > 128 * RS * 4 ? 2 * STAGE : 128 * RS * 4;
 };
@@ -61,6 +62,9 @@ __device__ __forceinline__ void split3(float x, unsigned &hi, unsigned &mid, uns
     mid = __builtin_bit_cast(unsigned short, m);
     lo = __builtin_bit_cast(unsigned short, l);
 }
+
+// Swizzle of the 16-byte slots of row `row` of a z2 plane: rows of 256 bytes and more, of 128 and of 64 bytes.
+__device__ __forceinline__ int swz_row(int DZ, int row) { return DZ >= 128 ? swz_z(row) : DZ == 64 ? swz_h(row) : (row >> 2) & 3; }
 
 // Eight floats -> one 16-byte slot of each plane.
 __device__ __forceinline__ void split_slot(const float (&x)[8], u32x4 (&out)[3])
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(256) void fipa_pack_split_kernel(SplitParams p)
         }
         u32x4 out[3];
         split_slot(x, out);
-        const int row = j & 31, at = p.DZ >= 128 ? slot ^ swz_z(row) : slot ^ swz_h(row);
+        const int row = j & 31, at = slot ^ swz_row(p.DZ, row);
         const int plane = 64 * p.DZ;
         char *dst = p.zb + ((size_t)b * p.n_kb + j / 32) * (3 * plane) + row * (2 * p.DZ) + 16 * at;
 #pragma unroll
@@ -242,18 +246,20 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
     };
     auto source = [&](int kb) { return Source{buffer_desc(zsrc + (size_t)kb * F::ZBLK), buffer_desc(hsrc + (size_t)kb * F::HBLK)}; };
     auto request = [&](const Source &s, int stage, auto c_) {
-        constexpr int c = decltype(c_)::value, nz = F::ZBLK / 4096, nh = F::HBLK / 4096;
+        constexpr int c = decltype(c_)::value, nz = (F::ZBLK + 4095) / 4096, nh = F::HBLK / 4096;
         const unsigned dst = lds0 + stage * F::STAGE;
         int voff;  // 16 * lane, formed again each time: a register kept for it would be spilled
         asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0\n\tv_lshlrev_b32 %0, 4, %0" : "=v"(voff));
-        if constexpr (c < nz)
-            dma16b(s.z, voff, (4 * c + wave) * 1024, dst + (4 * c + wave) * 1024);
+        if constexpr (c < nz) {
+            const int piece = min(4 * c + wave, F::ZBLK / 1024 - 1);  // (surplus waves: the last piece again)
+            dma16b(s.z, voff, piece * 1024, dst + piece * 1024);
+        }
         else if constexpr (c < nz + nh)
             dma16b(s.h, voff, (4 * (c - nz) + wave) * 1024, dst + F::ZBLK + (4 * (c - nz) + wave) * 1024);
         else  // (every wave: the same bytes to the same place)
             dma16b(s.h, voff, 4 * nh * 1024, dst + F::ZBLK + 4 * nh * 1024);
     };
-    static_assert(F::ZBLK % 4096 == 0 && F::HBLK % 4096 == 1024);
+    static_assert(F::ZBLK % 1024 == 0 && F::HBLK % 4096 == 1024);
     if (len > 0) {
         const Source src = source(blk);
         static_for<F::kDma>([&](auto c) { request(src, 0, c); });
@@ -320,14 +326,14 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
 
     // lane addresses within a stage
     constexpr bool kWide = DZ >= 128;
-    const int at_z = n * F::ZROW + 16 * (hf ^ (kWide ? swz_z(n) : swz_h(n)));  // rows of the z2 planes, ^ 32 ks
+    const int at_z = n * F::ZROW + 16 * (hf ^ swz_row(DZ, n));  // rows of the z2 planes, ^ 32 ks
     const int at_k = F::ZBLK + F::K + 32 * n + 16 * hf;
     const int j4 = (lane >> 2) & 3, gq = (lane >> 4) & 1;  // transposing reads: row 4 hf + j4, 16 columns 16 gq
     int at_vz[2], at_vh[2];
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
         const int r0 = 8 * x + 4 * hf + j4, c0 = 2 * gq + ((lane >> 1) & 1), in = 8 * (lane & 1);
-        at_vz[x] = r0 * F::ZROW + 16 * (c0 ^ (kWide ? swz_z(r0) : swz_h(r0))) + in;
+        at_vz[x] = r0 * F::ZROW + 16 * (c0 ^ swz_row(DZ, r0)) + in;
         at_vh[x] = F::ZBLK + F::V + r0 * 128 + 16 * (c0 ^ swz_h(r0)) + in;
     }
     const int at_g = F::ZBLK + F::G + 4 * hf * 48, at_m = F::ZBLK + F::M + 16 * hf;
@@ -353,7 +359,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
                 const char *src = ks == 0 ? st + at_k + t * F::KP
-                                          : smem + (zk ^ (32 * ((ks - 1) & (kWide ? 7 : 3)))) + t * F::ZP + (kWide ? 256 * ((ks - 1) / 8) : 0);
+                                          : smem + (zk ^ (32 * ((ks - 1) & (DZ >= 128 ? 7 : DZ / 16 - 1)))) + t * F::ZP + (kWide ? 256 * ((ks - 1) / 8) : 0);
                 a[t] = *reinterpret_cast<const bf16x8 *>(src);
             }
         };
@@ -363,7 +369,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
                 const char *src[2];
 #pragma unroll
                 for (int x = 0; x < 2; ++x)
-                    src[x] = cb < F::NB ? smem + (zv[x] ^ (64 * (cb & (kWide ? 3 : 1)))) + t * F::ZP + 16 * kk * F::ZROW + (kWide ? 256 * (cb / 4) : 0)
+                    src[x] = cb < F::NB ? smem + (zv[x] ^ (64 * (cb & (DZ >= 128 ? 3 : DZ / 32 - 1)))) + t * F::ZP + 16 * kk * F::ZROW + (kWide ? 256 * (cb / 4) : 0)
                                         : smem + (hv[x] ^ (64 * (cb - F::NB))) + t * F::VP + 16 * kk * 128;
                 a[t] = lds_read_tr(src[0], src[1]);
             }
@@ -469,7 +475,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
         for (int e = 0; e < 4; ++e) weights(0, e);
         __builtin_amdgcn_sched_barrier(0);
 
-        // O^T += V^T P^T; the head's columns (points, whose sums cancel against the frame's origin) are summed apart for 16 keys
+        // O^T += V^T P^T; the head's columns (points, whose sums cancel against the frame's origin; at r c_z = 32 all) are summed apart for 16 keys
         // (o_pts 2.58e-6 from float64 where only their small products were, 2.39e-6 now)
         f32x16 small;
         static_for<2 * F::NA>([&](auto n_) {
@@ -481,7 +487,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
             for (int t = 0; t < 3; ++t) w[t] = __builtin_bit_cast(bf16x8, (u32x4){pw[kk][t][0], pw[kk][t][1], pw[kk][t][2], pw[kk][t][3]});
             constexpr int last = (nn + F::NA - 1) % F::NA;  // the column block of the step before
             f32x16 now;
-            if constexpr (cb < F::NB) {
+            if constexpr (!F::apart(cb)) {
                 now = acc[cb];
             } else {
 #pragma unroll
@@ -493,13 +499,17 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
             now = mfma(c[0], w[2], now);
             now = mfma(c[1], w[0], now);
             now = mfma(c[0], w[1], now);
-            if constexpr (nn > 0 && last >= F::NB) acc[last] += small;
-            if constexpr (cb < F::NB) {
+            if constexpr (nn > 0 && F::apart(last)) acc[last] += small;
+            if constexpr (!F::apart(cb)) {
                 acc[cb] = mfma(c[0], w[0], now);
             } else {
                 small = mfma(c[0], w[0], now);
             }
-            if constexpr (kk == 0 && cb < 4) weights(1, cb);
+            if constexpr (kk == 0) {  // (three column blocks at r c_z = 32)
+                constexpr int per = (4 + F::NA - 1) / F::NA;
+#pragma unroll
+                for (int e = per * cb; e < per * (cb + 1) && e < 4; ++e) weights(1, e);
+            }
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
@@ -534,7 +544,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
         const int rl = 4 * it + r4, i = i_wg + 32 * wave + rl;
         const size_t ui = (size_t)b * L + min(i, L - 1);
         const float *u = rows + rl * F::RS, *hr = u + DZ, *z1 = p.z1 + ui * DZ;
-        f32x4 zr[DZ / 64];
+        f32x4 zr[DZ / 64 > 0 ? DZ / 64 : 1];
 #pragma unroll
         for (int x = 0; x < DZ / 64; ++x) zr[x] = *reinterpret_cast<const f32x4 *>(z1 + 4 * x0 + 64 * x);
         const bool valid = p.mask ? p.mask[ui] != 0 : true;
@@ -546,8 +556,8 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
             for (int x = x0; x < 40; x += 16) ph[x] = hr[x];
             if (x0 < 2) ph[40 + p.cz + x0] = hr[40 + x0];
         }
-        if (p.cz >= 64) {  // a lane's columns of all ranks
-            f32x4 val[DZ / 64];
+        if (DZ >= 64 && p.cz >= 64) {  // a lane's columns of all ranks
+            f32x4 val[DZ / 64 > 0 ? DZ / 64 : 1];
 #pragma unroll
             for (int x = 0; x < DZ / 64; ++x) val[x] = zr[x] * *reinterpret_cast<const f32x4 *>(u + 4 * x0 + 64 * x);
             const int nc = p.cz / 64;
@@ -668,13 +678,13 @@ hipError_t run_split(const SplitParams &p, hipStream_t stream)
 // Against the fp32 matrix instructions, us per call (those | this): r c_z = 256, one chain of 256, H = 4 to 12 41 | 38 to 41, of 320
 // 48 | 41 to 49, of 384 54 to 98 | 42 to 49, of 1024 and H = 12 342 | 103; two chains, H = 12, of 160 34 | 43, of 192 60 | 44 (there
 // the other kernel's tiles of 16 queries pass one round of the chip); r c_z = 128, H = 12, of 320 36 | 41, of 384 45 | 43, of 1024
-// 174 | 80; r c_z = 64, H = 12, of 384 34 | 34, of 512 45 | 40, of 1024 90 | 70.  Short calls are bound by start-up, which is longer here.
+// 174 | 80; r c_z = 64, H = 12, of 384 34 | 34, of 512 45 | 40, of 1024 90 | 70; r c_z = 32, H = 12, of 384 29 | 29, of 512 37 | 34, of 1024 75 | 62.  Short calls are bound by start-up, which is longer here.
 bool f32_split_applies(const fipa_desc &d)
 {
     const int DZ = d.r * d.cz;
     if (d.c != 16 || d.Pq != 4 || d.Pv != 8 || d.cz % 4 != 0) return false;
     if (DZ == 256) return d.L >= 384 || (long long)d.B * d.H * ((d.L + 15) / 16) > 256;
-    return (DZ == 128 && d.L >= 384) || (DZ == 64 && d.L >= 512);
+    return (DZ == 128 && d.L >= 384) || ((DZ == 64 || DZ == 32) && d.L >= 512);
 }
 
 size_t f32_split_workspace(const fipa_desc &d) { return split_layout(d).total; }
@@ -709,7 +719,7 @@ hipError_t f32_split_forward(const fipa_desc &d, const FwdArgs &a, void *ws, siz
     hipLaunchKernelGGL(fipa_pack_split_kernel, dim3(p.H * p.n_kb + z_units, p.B), dim3(256), 0, stream, p);
     timer.end(0);
     timer.begin(1);
-    hipError_t e = p.DZ == 64 ? run_split<64>(p, stream) : p.DZ == 128 ? run_split<128>(p, stream) : run_split<256>(p, stream);
+    hipError_t e = p.DZ == 32 ? run_split<32>(p, stream) : p.DZ == 64 ? run_split<64>(p, stream) : p.DZ == 128 ? run_split<128>(p, stream) : run_split<256>(p, stream);
     if (e == hipSuccess && p.n_parts > 1) {
         const dim3 grid(p.n_units / p.n_parts * 8);
         if (p.n_parts == 2) hipLaunchKernelGGL(fipa_merge_split_kernel<2>, grid, dim3(256), 0, stream, p);

@@ -46,6 +46,7 @@ def test_f32_lse_and_far_keys():
 # split operands: every width, one residue past a block and a tile, blocks and whole tiles without a valid residue, key ranges in one and
 # several parts (fewer and more than 128 tiles), columns of one rank narrower than 64
 @pytest.mark.parametrize("kw", [
+    dict(L=512, cz=32, r=1, H=2), dict(L=600, cz=8, r=4, H=2, B=2, varlen=True, min_len=1),
     dict(L=384, cz=128, r=2, H=1), dict(L=417, cz=64, r=2, H=2, B=2, varlen=True, min_len=1), dict(L=513, cz=64, r=1, H=3),
     dict(L=545, cz=16, r=4, H=2, B=2, varlen=True, min_len=40), dict(L=385, cz=8, r=16, H=1), dict(L=161, B=4, H=6, cz=32, r=8),
     dict(L=170, B=8, H=12, cz=256, r=1, varlen=True, min_len=1), dict(L=520, B=3, H=12, cz=128, r=1, varlen=True, min_len=100)])
