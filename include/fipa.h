@@ -40,7 +40,7 @@ extern "C" {
 #define FIPA_ERR_ALIGNMENT (-4)   /* a tensor pointer is not 16-byte aligned                  */
 #define FIPA_ERR_LAUNCH (-5)      /* HIP reported an error when a kernel was enqueued         */
 
-#define FIPA_DTYPE_F32 0  /* q,k,v,points,z1,z2 float32; direct fp32 evaluation (no MFMA)      */
+#define FIPA_DTYPE_F32 0  /* q,k,v,points,z1,z2 float32; fp32 throughout (operands in full)    */
 #define FIPA_DTYPE_BF16 1 /* q,k,v,points,z1,z2 bfloat16; bf16 MFMA with fp32 accumulation      */
 
 /*

@@ -77,3 +77,15 @@ def test_f32_split_operands_in_every_workspace():
     out["workspace"] = torch.empty(least - 256, dtype=torch.uint8, device="cuda:0")
     with pytest.raises(binding.FipaError):
         binding.forward(desc, dev, out)
+
+
+def test_f32_split_operands_without_a_valid_residue():
+    inp = wl.make_inputs(0, B=2, L=390, H=2, cz=128, r=1, chain=True, trans_scale=0.3)
+    inp["mask"] = np.ones((2, 390), np.uint8)
+    want = gu.oracle_forward_chunked(inp)  # (which wants a valid key in every element)
+    inp["mask"][0] = 0
+    got = gu.run_gpu(inp)
+    for n in gu.NAMES:
+        assert not got[n][0].any(), n
+        assert gu.rel_err(got[n][1], want[n][1]) <= gu.TOL["fp32"], n
+    assert not got["lse"][0].any()
