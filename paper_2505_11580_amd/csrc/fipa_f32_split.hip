@@ -151,6 +151,10 @@ __global__ __launch_bounds__(256) void fipa_pack_split_kernel(SplitParams p)
             *reinterpret_cast<f32x4 *>(blk + F::G + 48 * row + 16 * (x0 - 10)) = (f32x4){x[0], x[1], x[2], x[3]};
             continue;
         }
+        if (x0 >= 2) {  // (values of which twice is infinite: left to direct_row like an infinity)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = fabsf(x[e]) <= 0x1p126f ? x[e] : INFINITY;
+        }
         u32x4 out[3];
         split_slot(x, out);
 #pragma unroll
@@ -212,10 +216,66 @@ __device__ __forceinline__ void finish_row(const SplitParams &p, int b, int h, i
     if (p.lse && x0 == 0) p.lse[((size_t)b * p.H + h) * p.L + i] = valid ? kLn2 * (m + __log2f(l)) : 0.f;
 }
 
+// One row against the keys j0 .. j1 - 1 from the inputs, by one wave on the vector ALU: what the tile leaves of it in LDS (`out`).  For rows
+// with an infinite operand, which six products of parts do not carry (an infinity has no second part, and a product far beyond the
+// largest float leaves parts of either sign): an infinite logit or value then gives what fp32 arithmetic gives.
+template <int DZ>
+__device__ __forceinline__ void direct_row(const SplitParams &p, int b, int h, int i, int j0, int j1, const float *cen, bool whole, float *out)
+{
+    const int lane = threadIdx.x & 63;
+    const size_t row0 = (size_t)b * p.L, ui = row0 + i;
+    const float *q = p.q + (ui * p.H + h) * 16, *z1 = p.z1 + ui * DZ, *wb = p.w_b + (size_t)h * p.cz;
+    const float sc = kLog2e * p.w_L * p.qk_scale, bz = kLog2e * p.w_L, coef = kLog2e * 0.5f * p.gamma[h] * p.w_L * p.w_C;
+    auto point = [&](size_t u, const float *pts, int x) {  // global coordinate x of a residue's points
+        const float *R = p.rot + u * 9 + 3 * (x % 3), *l = pts + x / 3 * 3;
+        return R[0] * l[0] + R[1] * l[1] + R[2] * l[2] + (p.trans[u * 3 + x % 3] - cen[x % 3]);
+    };
+    auto counts = [&](int j) { return j < j1 && (p.mask ? p.mask[row0 + j] != 0 : true); };
+    auto logit = [&](int j) {
+        if (!counts(j)) return -INFINITY;
+        const size_t u = row0 + j, hrow = u * p.H + h;
+        float s = 0.f, dist = 0.f;
+#pragma unroll 1
+        for (int x = 0; x < 16; ++x) s += sc * q[x] * p.k[hrow * 16 + x];
+#pragma unroll 1
+        for (int x = 0; x < DZ; ++x) s += bz * wb[x & (p.cz - 1)] * z1[x] * p.z2[u * DZ + x];
+#pragma unroll 1
+        for (int x = 0; x < 12; ++x) {
+            const float df = point(ui, p.q_pts + (ui * p.H + h) * 12, x) - point(u, p.k_pts + hrow * 12, x);
+            dist += df * df;
+        }
+        return s - coef * dist;
+    };
+    float m = -INFINITY, l = 0.f, sum[(DZ + 40 + 63) / 64] = {};
+    for (int j = j0 + lane; j < j1; j += 64) m = fmaxf(m, logit(j));
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    const float m_use = m == -INFINITY ? 0.f : m;
+    for (int jb = j0; jb < j1; jb += 64) {
+        const float w = __builtin_amdgcn_exp2f(logit(jb + lane) - m_use);
+        l += w;
+        for (unsigned long long rest = __ballot(counts(jb + lane)); rest != 0ull; rest &= rest - 1ull) {
+            const int t = __builtin_ctzll(rest);
+            const size_t u = row0 + jb + t, hrow = u * p.H + h;
+            const float wt = __shfl(w, t);
+#pragma unroll
+            for (int x = 0; x < (DZ + 40 + 63) / 64; ++x) {
+                const int col = lane + 64 * x, hc = col - DZ;
+                if (hc < 40) sum[x] += wt * (hc < 0 ? p.z2[u * DZ + col] : hc < 16 ? p.v[hrow * 16 + hc] : point(u, p.v_pts + hrow * 24, hc - 16));
+            }
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+    const float scale = !whole ? 1.f : l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+    for (int x = 0; x < (DZ + 40 + 63) / 64; ++x)
+        if (lane + 64 * x < DZ + 40) out[lane + 64 * x] = scale * sum[x];
+    if (lane < 2) out[DZ + 40 + lane] = lane == 0 ? m : l;
+}
+
 constexpr float kRaise = 1.f;  // log2 units: an exponent of up to 1 is rounded no worse than one below 0 (30: lse 4.17e-7 from float64, 1: 3.73e-7)
 
 template <int DZ>
-__global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams p)
+__global__ __launch_bounds__(256, DZ == 32 ? 2 : 1) void fipa_attn_f32_split_kernel(SplitParams p)
 {
     using F = Fs<DZ>;
     extern __shared__ __attribute__((aligned(256))) char smem[];
@@ -523,6 +583,15 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
     }
     l += other_half(l);
 
+    // Rows for direct_row.  An infinite factor of a logit (with one of z2 as a value too) makes a row's sum of weights a NaN, an infinite
+    // v or point the row's sum of that column.
+    f32x4 odd = {l - l, 0.f, 0.f, 0.f};  // 0, or NaN
+#pragma unroll
+    for (int x = 0; x < 20; ++x) odd[x & 3] = fmaf(acc[F::NB + x / 16][x % 16], 0.f, odd[x & 3]);
+    const float any_odd = (odd[0] + odd[1]) + (odd[2] + odd[3]);
+    const int own = i_wg + 32 * wave + n;
+    unsigned again = (unsigned)__ballot(any_odd + other_half(any_odd) != 0.f && own < L && (p.mask ? p.mask[(size_t)b * L + own] != 0 : true));
+
     // the wave's rows through LDS: 16 lanes per row
     const bool whole = p.n_parts == 1;
     const float scale = !whole ? 1.f : l > 0.f ? 1.f / l : 0.f;
@@ -538,6 +607,16 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
             *reinterpret_cast<f32x4 *>(rows + n * F::RS + 32 * cb + 2 * x + 4 * hf) =
                 (f32x4){acc[cb][x], acc[cb][x + 1], acc[cb][x + 2], acc[cb][x + 3]} * scale;
     if (hf == 0) *reinterpret_cast<f32x2 *>(rows + n * F::RS + DZ + 40) = (f32x2){m, l};
+    if (__builtin_expect(again != 0u, 0)) {
+        // (the arguments by a pointer that is formed here: kept for this they would take scalar registers through the loop)
+        uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        for (; again != 0u; again &= again - 1u) {
+            const int rl = __builtin_ctz(again);
+            direct_row<DZ>(*reinterpret_cast<const SplitParams *>(args), b, h, i_wg + 32 * wave + rl, 32 * lo, min(32 * (lo + len), L), cen, whole,
+                           rows + rl * F::RS);
+        }
+    }
     __syncthreads();
 #pragma unroll 2
     for (int it = 0; it < 8; ++it) {
@@ -547,7 +626,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_f32_split_kernel(SplitParams
         f32x4 zr[DZ / 64 > 0 ? DZ / 64 : 1];
 #pragma unroll
         for (int x = 0; x < DZ / 64; ++x) zr[x] = *reinterpret_cast<const f32x4 *>(z1 + 4 * x0 + 64 * x);
-        const bool valid = p.mask ? p.mask[ui] != 0 : true;
+        const bool valid = (p.mask ? p.mask[ui] != 0 : true) && (!whole || hr[41] > 0.f);
         float *dst = whole ? p.o_pair + (ui * H + h) * p.cz : out_part + (size_t)rl * prow + 40;
         if (whole) {
             finish_row(p, b, h, i, x0, cen, hr[40], hr[41], [&](int x) { return hr[x]; });
@@ -615,7 +694,7 @@ __global__ __launch_bounds__(256) void fipa_merge_split_kernel(SplitParams p)
         return v * inv;
     });
     const size_t ui = (size_t)b * p.L + i;
-    const bool valid = (p.mask ? p.mask[ui] != 0 : true);
+    const bool valid = (p.mask ? p.mask[ui] != 0 : true) && l > 0.f;
     for (int d = 4 * x0; d < p.cz; d += 64) {
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll

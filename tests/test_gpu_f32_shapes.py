@@ -89,3 +89,52 @@ def test_f32_split_operands_without_a_valid_residue():
         assert not got[n][0].any(), n
         assert gu.rel_err(got[n][1], want[n][1]) <= gu.TOL["fp32"], n
     assert not got["lse"][0].any()
+
+
+def _run_in(inp, size):
+    import torch
+    from paper_2505_11580_amd import binding
+    desc, dev = binding.upload(inp)
+    out = binding.alloc_outputs(desc)
+    for n in gu.NAMES + ("lse",):
+        out[n].fill_(float("nan"))
+    out["workspace"] = torch.empty(size or binding.workspace_bytes(desc)[0], dtype=torch.uint8, device="cuda:0")
+    binding.forward(desc, dev, out)
+    torch.cuda.synchronize()
+    return {n: out[n].cpu().numpy().astype(np.float64) for n in gu.NAMES + ("lse",)}
+
+
+# Infinite operands, on split operands (in several parts, and unsplit) as on the fp32 matrix instructions, which the least workspace gives
+@pytest.mark.parametrize("kw", [dict(L=450, H=4, cz=64, r=2), dict(L=520, H=2, cz=16, r=2), dict(L=385, H=2, cz=128, r=2),
+                                dict(L=512, B=11, H=3, cz=32, r=2)])
+def test_f32_split_operands_infinities(kw):
+    kw = dict(dict(B=1, chain=False, trans_scale=0.05), **kw)
+    B, L, H, cz, r = (kw[n] for n in ("B", "L", "H", "cz", "r"))
+    inp = wl.make_inputs(0, **kw)
+    inf, h = np.float32(np.inf), H - 1
+    inp["mask"] = (np.random.default_rng(1).random((B, L)) < 0.9).astype(np.uint8)
+    inp["mask"][0, [7, 9, 11, 20, 30, 40]] = 1
+    inp["mask"][0, 50] = 0
+    inp["q"][0, :, h, 3] = -np.abs(inp["q"][0, :, h, 3]) - 0.1
+    inp["k"][0, 7, h, 3] = inf               # a logit of -inf: left out
+    inp["v"][0, 9, h, 2] = inf               # an infinite sum
+    inp["v_pts"][0, 11, 0, 3, 1] = -inf
+    inp["q"][0, 20, 0, 1] = inf              # one row
+    inp["v"][0, 30, 0, 4] = 3e38
+    inp["k"][0, 40, 0, 5] = 3.4e38
+    inp["v"][0, 50] = inf                    # a masked residue
+    if B > 1:
+        inp["z2"][B - 1, 60, 0, 5] = -inf    # a logit and a value
+        inp["mask"][B - 1, 60] = 1
+    least = (B * H * L * 76 * 4 + 255) // 256 * 256 + (16 * B + 255) // 256 * 256 + 256
+    want, got = _run_in(inp, least), _run_in(inp, None)
+    for n in gu.NAMES + ("lse",):
+        w, g = want[n], got[n]
+        odd = ~np.isfinite(w)
+        assert np.array_equal(w[odd], g[odd], equal_nan=True) and np.isfinite(g[~odd]).all(), n
+        huge = np.abs(w) > 1e30  # (3e38 weighted: to the precision of a float)
+        for part in (~odd & ~huge, ~odd & huge):
+            if part.any():
+                assert np.abs(g[part] - w[part]).max() <= 1e-5 * np.abs(w[part]).max(), n
+    assert np.isinf(got["o"][0, 0, h, 2]) and np.isfinite(got["o"][0, 0, h, :2]).all()
+    assert not got["o"][0, 20, 0].any() and not got["o_pair"][0, 20, 0].any()
