@@ -75,13 +75,14 @@ __global__ __launch_bounds__(256) void fipa_factor_project_kernel(const int *__r
 // The same with the tables of 32 columns (64 bytes per row) in LDS, where a workgroup then adds up many residues: the rows of
 // a residue come out of LDS instead of L2.  1024 threads, four per residue; a wave takes groups of 16 residues that lie gridDim.y * 16 groups
 // apart, so that the masked ends of a padded batch (no slot filled: nothing to add) are spread over all workgroups, and needs no other wave
-// behind the loading of the table: it looks up the table rows of its own residues.  An empty slot takes a row of zeros.  The two rows of a slot are
-// added by one instruction per value (a product with ones), where unpacking the halves and adding them took four per pair.
+// behind the loading of the table: it looks up the table rows of its own residues.  An empty slot takes a row of zeros.  Same sums in the same
+// order.  (One instruction per value and slot, a product of the slot's two rows with ones, is 2 to 6 us faster at the size below, but it does
+// not round to nearest: of random sums with one row in five was off by a last place.)
 // 32768 residues (60 % of them valid), 20 slots, 81 rows per slot, 512 columns: 99 us from L2; from LDS 60 us with contiguous ranges of
-// residues per workgroup, a barrier per 256 of them and indices that were loaded where they were looked at, 38 us so.  What is left is the
-// LDS reads of rows that meet in the banks (64 bytes each, any of four places) and the loading of the table (about 5 us).
+// residues per workgroup, a barrier per 256 of them and indices that were loaded where they were looked at, 38 us so (all valid: 62, 53).
+// What is left is the LDS reads of rows that meet in the banks (64 bytes each, any of four places) and the loading of the table (about 5 us).
 // Used where every workgroup has at least kFpRows residues to add for the table that it loads and the table fits: one chain of 4096
-// residues, 512 columns, 16.6 us from L2, 11.0 so; 2048 11.6 and 9.1; 8192 residues of 128 columns 11.2 and 8.8.
+// residues, 512 columns, 16.8 us from L2, 12.0 so; 2048 11.5 and 9.9; 8192 residues of 128 columns, 16 slots 10.1 and 9.2.
 constexpr int kFpThreads = 1024, kFpPass = kFpThreads / 4, kFpRows = 128;
 constexpr int kFpAhead = 8;  // slots of a thread whose indices and bins wait in registers: 32 of a residue
 inline size_t factor_lds_bytes(int k, int n_bins, int n_pos)
@@ -156,16 +157,13 @@ __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(con
     float b8[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) b8[q] = bias && col < n_out ? bias[col + q] : 0.f;
-    // a bin row and a position row: two columns of each side by side, a product with ones adds both
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    auto add = [&](float (&acc)[8], const char *bin_row, const char *pos_row) {
-        const uint4 u = *reinterpret_cast<const uint4 *>(bin_row), v = *reinterpret_cast<const uint4 *>(pos_row);
-        const unsigned a[4] = {u.x, u.y, u.z, u.w}, b[4] = {v.x, v.y, v.z, v.w};
+    auto add = [](float (&acc)[8], const char *row) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(row);
+        const unsigned w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const unsigned even = __builtin_amdgcn_perm(b[q], a[q], 0x05040100u), odd = __builtin_amdgcn_perm(b[q], a[q], 0x07060302u);
-            acc[2 * q] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, even), ones, acc[2 * q], false);
-            acc[2 * q + 1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, odd), ones, acc[2 * q + 1], false);
+            acc[2 * q] += __uint_as_float(w[q] << 16);
+            acc[2 * q + 1] += __uint_as_float(w[q] & 0xffff0000u);
         }
     };
     __syncthreads();  // the table is there
@@ -182,7 +180,8 @@ __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(con
 #pragma unroll 4
             for (int s = 0; s < slots; ++s) {
                 const unsigned c = codes[s * kFpPass + rr];
-                add(acc, fp_smem + 64 * (c & 0xFFFFu) + 16 * part, fp_smem + 64 * (c >> 16) + 16 * part);
+                add(acc, fp_smem + 64 * (c & 0xFFFFu) + 16 * part);
+                add(acc, fp_smem + 64 * (c >> 16) + 16 * part);
             }
             uint4 o;
             o.x = (unsigned)f2bf(acc[0]) | ((unsigned)f2bf(acc[1]) << 16);

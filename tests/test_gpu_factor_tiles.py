@@ -39,7 +39,6 @@ def test_factor_backward_tiles(B, L, k, n_bins, n_pos, n_out, masked):
             assert np.abs(g.cpu().numpy().astype(np.float64) - w).max() <= 2e-6 * scale
 
 
-# 128 residues or more for each of 256 / ceil(n_out / 32) workgroups of a column group
 @pytest.mark.parametrize("B,L,k,n_bins,n_pos,n_out,pos_mode", [
     (1, 1920, 33, 4, 5, 520, 1), (400, 5, 2, 3, 9, 520, 1), (1, 2049, 4, 16, 0, 512, 0), (3, 691, 64, 9, 25, 488, 1)])
 def test_projection_groups(B, L, k, n_bins, n_pos, n_out, pos_mode):
@@ -48,3 +47,34 @@ def test_projection_groups(B, L, k, n_bins, n_pos, n_out, pos_mode):
     idx[-1, L // 2:] = -1  # groups without neighbours
     bins = np.where(idx < 0, -1, rng.integers(0, n_bins, size=(B, L, k)))
     check(idx, bins, *make_tables(rng, k, n_bins, n_pos, n_out), pos_mode, "groups %d x %d" % (B, L))
+
+
+def _in_lds(B, L, k, n_bins, n_pos, n_out):
+    """Whether the projection runs with its tables in LDS: they fit, and each workgroup has 128 residues or more to add."""
+    groups = (n_out + 31) // 32
+    parts = 256 // groups if groups < 256 else 1
+    return 64 * (k * (n_bins + n_pos) + 1) + 1024 * k <= 160 * 1024 and B * L >= parts * 128
+
+
+# One order of sums, float32 to the nearest, whichever kernel adds them: the values of a sum in that order, rounded once
+@pytest.mark.parametrize("B,L,k,n_bins,n_pos,n_out,pos_mode,in_lds", [
+    (1, 1920, 33, 4, 5, 520, 1, True), (800, 5, 2, 3, 9, 520, 1, True), (1, 4097, 4, 16, 0, 512, 0, True),
+    (3, 691, 64, 9, 13, 488, 1, True), (2, 2000, 10, 16, 33, 512, 1, True), (1, 700, 20, 16, 65, 512, 1, False)])
+def test_projection_order(B, L, k, n_bins, n_pos, n_out, pos_mode, in_lds):
+    import torch
+    from tests.test_gpu_factor import run_gpu
+    assert _in_lds(B, L, k, n_bins, n_pos, n_out) == in_lds
+    rng = np.random.default_rng(L + k)
+    idx = rng.integers(-1, L, size=(B, L, k))
+    idx[-1, L // 2:L // 2 + 40] = -1  # groups without neighbours
+    bins = np.where(idx < 0, -1, rng.integers(0, n_bins, size=(B, L, k)))
+    e_bin, e_pos, bias = make_tables(rng, k, n_bins, n_pos, n_out)
+    half = (n_pos - 1) // 2
+    code = np.minimum(idx, n_pos - 1) if pos_mode == 0 else np.clip(idx - np.arange(L)[None, :, None], -half, half) + half
+    want = np.broadcast_to(bias, (B, L, n_out)).astype(np.float32)
+    for s in range(k):
+        for table, at in ((e_bin, bins), (e_pos, code)):
+            if table is not None:
+                want += np.where((idx[..., s] >= 0)[..., None], table[s].float().numpy()[np.maximum(at[..., s], 0)], np.float32(0))
+    got = run_gpu(idx, bins, e_bin, e_pos, bias, pos_mode).cpu()
+    assert torch.equal(got, torch.from_numpy(want).to(torch.bfloat16))
