@@ -81,10 +81,14 @@ __global__ __launch_bounds__(256) void fipa_factor_project_kernel(const int *__r
 // 32768 residues (60 % of them valid), 20 slots, 81 rows per slot, 512 columns: 99 us from L2; from LDS 60 us with contiguous ranges of
 // residues per workgroup, a barrier per 256 of them and indices that were loaded where they were looked at, 38 us so (all valid: 62, 53).
 // What is left is the LDS reads of rows that meet in the banks (64 bytes each, any of four places) and the loading of the table (about 5 us).
-// Used where every workgroup has at least kFpRows residues to add for the table that it loads and the table fits: one chain of 4096
+// Used where every workgroup has enough residues to add for the table that it loads (factor_rows) and the table fits: one chain of 4096
 // residues, 512 columns, 16.8 us from L2, 12.0 so; 2048 11.5 and 9.9; 8192 residues of 128 columns, 16 slots 10.1 and 9.2.
-constexpr int kFpThreads = 1024, kFpPass = kFpThreads / 4, kFpRows = 128;
+constexpr int kFpThreads = 1024, kFpPass = kFpThreads / 4;
 constexpr int kFpAhead = 8;  // slots of a thread whose indices and bins wait in registers: 32 of a residue
+// Residues per workgroup from which the table is worth loading: 128 from 16 slots on, 256 up to 8.  From L2 | so, us, 512 columns, 33 + 16 rows per
+// slot: 128 residues per workgroup, 1 slot 4.6 | 5.5, 10 slots 8.2 | 8.3 (half of the residues masked 7.7 | 8.3), 16 10.1 | 9.2, 30 15.8 | 12.0;
+// 192, 4 slots 7.1 | 7.4, 7 8.9 | 8.3, 10 10.2 | 9.0; 256, 1 slot 6.9 | 6.1, 4 8.3 | 7.9, 10 11.9 | 9.7.
+inline int factor_rows(int k) { return std::clamp(2048 / k, 128, 256); }
 inline size_t factor_lds_bytes(int k, int n_bins, int n_pos)
 {
     return 64 * ((size_t)k * (n_bins + n_pos) + 1) + (size_t)kFpPass * k * 4;
@@ -111,6 +115,7 @@ __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(con
         const size_t at = (size_t)min(res, rows - 1) * k;
 #pragma unroll
         for (int u = 0; u < kFpAhead; ++u) {
+            if (4 * u >= k) break;
             const int s = min(part + 4 * u, k - 1);
             nbr[u] = nbr_idx[at + s];
             bins[u] = nbr_bin[at + s];
@@ -130,8 +135,10 @@ __global__ __launch_bounds__(kFpThreads) void fipa_factor_project_lds_kernel(con
             codes[s * kFpPass + rr] = bin_row | (pos_row << 16);
         };
 #pragma unroll
-        for (int u = 0; u < kFpAhead; ++u)
+        for (int u = 0; u < kFpAhead; ++u) {
+            if (4 * u >= k) break;
             if (part + 4 * u < k) one(part + 4 * u, nbr[u], bins[u]);
+        }
         for (int s = part + 4 * kFpAhead; s < k; s += 4) one(s, nbr_idx[at + s], nbr_bin[at + s]);
         i_next += turn;
         if (i_next >= L) i_next -= L;
@@ -554,10 +561,10 @@ extern "C" int fipa_factor_project(int32_t B, int32_t L, int32_t k, int32_t n_bi
     if ((reinterpret_cast<uintptr_t>(nbr_idx) & 3u) != 0 || (reinterpret_cast<uintptr_t>(nbr_bin) & 3u) != 0) return FIPA_ERR_ALIGNMENT;
     const dim3 grid((unsigned)((threads + 255) / 256));
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    // One workgroup per compute unit and 32 columns; worth the loading of its table (about 100 KB) from kFpRows residues on.
+    // One workgroup per compute unit and 32 columns; worth the loading of its table (about 100 KB) from factor_rows residues on.
     const int groups = (n_out + 31) / 32, parts = groups < 256 ? 256 / groups : 1;
     const size_t lds = fipa::factor_lds_bytes(k, n_bins, n_pos);
-    if (lds <= 160 * 1024 && (long long)k * (n_bins + n_pos) < 0xFFFF && rows >= (long long)parts * fipa::kFpRows && rows <= (1LL << 30)) {
+    if (lds <= 160 * 1024 && (long long)k * (n_bins + n_pos) < 0xFFFF && rows >= (long long)parts * fipa::factor_rows(k) && rows <= (1LL << 30)) {
         static fipa::LdsLimit limit;
         if (fipa::raise_lds_limit(limit, (const void *)fipa::fipa_factor_project_lds_kernel, (int)lds) != hipSuccess) return FIPA_ERR_LAUNCH;
         hipLaunchKernelGGL(fipa::fipa_factor_project_lds_kernel, dim3(groups, parts), dim3(fipa::kFpThreads), lds, stream, nbr_idx, nbr_bin,

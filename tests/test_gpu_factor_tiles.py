@@ -50,10 +50,10 @@ def test_projection_groups(B, L, k, n_bins, n_pos, n_out, pos_mode):
 
 
 def _in_lds(B, L, k, n_bins, n_pos, n_out):
-    """Whether the projection runs with its tables in LDS: they fit, and each workgroup has 128 residues or more to add."""
+    """Whether the projection runs with its tables in LDS: they fit, and each workgroup has enough residues to add."""
     groups = (n_out + 31) // 32
     parts = 256 // groups if groups < 256 else 1
-    return 64 * (k * (n_bins + n_pos) + 1) + 1024 * k <= 160 * 1024 and B * L >= parts * 128
+    return 64 * (k * (n_bins + n_pos) + 1) + 1024 * k <= 160 * 1024 and B * L >= parts * min(max(2048 // k, 128), 256)
 
 
 # One order of sums, float32 to the nearest, whichever kernel adds them: the values of a sum in that order, rounded once
