@@ -277,17 +277,24 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
     int base = 0;  // the first of those 64
     unsigned long long rest = 0ull;
     auto look = [&] {
-        const int tile = wave + kFbWaves * (base + lane), r0 = 32 * tile;
+        const int r0 = 32 * min(wave + kFbWaves * (base + lane), ntiles - 1), words = rows >> 2;
+        const unsigned *const m = reinterpret_cast<const unsigned *>(mask);
         unsigned any = 0u;
-        if (base + lane < own) {
-            if (r0 + 32 <= rows && (reinterpret_cast<uintptr_t>(mask) & 3u) == 0) {
-                const unsigned *m = reinterpret_cast<const unsigned *>(mask + r0);
+        if ((reinterpret_cast<uintptr_t>(mask) & 3u) != 0) {
+            any = 1u;
+        } else if ((rows & 31) == 0) {
 #pragma unroll
-                for (int x = 0; x < 8; ++x) any |= m[x];
-            } else {
-                for (int r = r0; r < min(r0 + 32, rows); ++r) any |= mask[r];
-            }
+            for (int x = 0; x < 8; ++x) any |= m[r0 / 4 + x];
+        } else {  // (one round trip here too; words past the end are the last one again, and the last tile takes the bytes behind it)
+            unsigned tail = 0u;
+#pragma unroll
+            for (int x = 0; x < 3; ++x) tail |= mask[min(4 * words + x, rows - 1)];
+            if (words > 0)
+#pragma unroll
+                for (int x = 0; x < 8; ++x) any |= m[min(r0 / 4 + x, words - 1)];
+            if (r0 + 32 > rows) any |= tail;
         }
+        if (base + lane >= own) any = 0u;
         rest = __ballot(any != 0u);
     };
     int seen = 0;  // (no mask: the next tile)
