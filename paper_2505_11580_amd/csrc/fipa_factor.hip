@@ -415,9 +415,16 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
 #pragma unroll
     for (int x = 0; x < S - 1; ++x) last = now >= 0 && ahead[x] >= 0 ? ahead[x] : last;  // tile n + S - 1, or the last one
     // The operands of a tile are read while the tile before is multiplied, each into the registers of the one that has just been used.
+    // (Not with five row blocks and a mask, where registers of the loop were spilled for it: 4 chains of 8192, 130 rows 123 us, 111 so; one
+    // of 500 14.2, 12.6.  Without a mask, 2 spilled outside of the loop: 108, 134 so.)
+    constexpr bool kReadAhead = RB <= 4 || !MASK;
     bf16x8 bz[2][2], a[2][RB];
+    auto multiply = [&](int t, int mb) {
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][mb], bz[t][nb], acc[mb][nb], 0, 0, 0);
+    };
     auto step = [&](auto First) {
-        constexpr bool first = decltype(First)::value;
+        constexpr bool first = !kReadAhead || decltype(First)::value;
         // d_z of tile n and the codes of tile n + 1 have landed; the reads of tile n - 1, whose stage the next loads take, are done
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * kLoads) : "memory");
         {
@@ -450,8 +457,7 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
 #pragma unroll
             for (int mb = 0; mb < RB; ++mb) {
                 if constexpr (!first) {
-#pragma unroll
-                    for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][mb], bz[t][nb], acc[mb][nb], 0, 0, 0);
+                    multiply(t, mb);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 a[t][mb] = *reinterpret_cast<const bf16x8 *>(ones + 32 * 64 * mb + (aone ^ (32 * t)));
@@ -462,6 +468,12 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
         }
         asm volatile("" ::: "memory");
         set(0);
+        if constexpr (!kReadAhead) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int mb = 0; mb < RB; ++mb) multiply(t, mb);
+        }
         now = ahead[0];
         decode(now);  // (past the last tile: not used)
 #pragma unroll
@@ -473,12 +485,12 @@ __global__ __launch_bounds__(64 * kFbWaves, 2) void fipa_factor_backward_kernel(
     if (now >= 0) {
         step(std::true_type{});
         while (now >= 0) step(std::false_type{});
+        if constexpr (kReadAhead) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int mb = 0; mb < RB; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][mb], bz[t][nb], acc[mb][nb], 0, 0, 0);
+                for (int mb = 0; mb < RB; ++mb) multiply(t, mb);
+        }
     }
     wait_vmem<0>();  // (loads past the last tile still write LDS)
     // the waves' sums, in a fixed order: 4..7 to 0..3, 2..3 to 0..1, 1 to 0
