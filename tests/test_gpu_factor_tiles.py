@@ -15,28 +15,58 @@ pytestmark = pytest.mark.gpu
     (1, 1, 1, 1, 0, 8, False), (1, 31, 2, 16, 15, 64, True), (1, 33, 3, 16, 33, 72, True), (2, 257, 2, 22, 33, 128, True),
     (1, 513, 2, 30, 95, 56, False), (3, 300, 1, 16, 111, 200, True)])
 def test_factor_backward_tiles(B, L, k, n_bins, n_pos, n_out, masked):
-    import torch
     rng = np.random.default_rng(900 + L)
     idx = rng.integers(-1, L, size=(B, L, k))
     bins = np.where(idx < 0, -1, rng.integers(0, n_bins, size=(B, L, k)))
     mask = (rng.random((B, L)) > 0.3).astype(np.uint8) if masked else None
     if masked:
         mask[:, L // 3:L // 3 + 40] = 0  # whole tiles without a valid residue
+    _check_backward(rng, idx, bins, n_bins, n_pos, n_out, mask)
+
+
+def _check_backward(rng, idx, bins, n_bins, n_pos, n_out, mask):
+    import torch
+    B, L, k = idx.shape
     d_z = _bf16(rng.standard_normal((B, L, n_out)))
     want = factor_ref.factor_project_backward(idx, bins, d_z.float().numpy(), n_bins, n_pos, 1, mask)
     scale = float(np.abs(d_z.float().numpy()).sum(axis=(0, 1)).max())
-    if masked:
+    if mask is not None:
         d_z[torch.from_numpy(mask == 0)] = float("nan")
     f = dict(dtype=torch.float32, device="cuda:0")
     got = [torch.full((k, n_bins, n_out), float("nan"), **f),
            torch.full((k, n_pos, n_out), float("nan"), **f) if n_pos else None, torch.full((n_out,), float("nan"), **f)]
     binding.fipa_factor_project_backward(1, torch.from_numpy(idx.astype(np.int32)).cuda(), torch.from_numpy(bins.astype(np.int32)).cuda(),
-                                         d_z.cuda(), torch.from_numpy(mask).cuda() if masked else None, *got)
+                                         d_z.cuda(), torch.from_numpy(mask).cuda() if mask is not None else None, *got)
     torch.cuda.synchronize()
     for g, w in zip(got, want):
         if g is not None:
             # float32 sums against float64: a few 1e-7 of the largest sum of magnitudes (the bound of test_gpu_factor)
             assert np.abs(g.cpu().numpy().astype(np.float64) - w).max() <= 2e-6 * scale
+
+
+# More than 64 tiles per wave (a second and third look at the masks), the middle ones without a residue that counts, the last one not whole; three
+# and two stages, the most row blocks
+@pytest.mark.parametrize("k,n_bins,n_pos", [(2, 4, 5), (1, 22, 91), (1, 16, 127)])
+def test_factor_backward_windows(k, n_bins, n_pos):
+    B, L = 5, 7001
+    rng = np.random.default_rng(n_pos)
+    idx = np.clip(np.arange(L)[None, :, None] + rng.integers(-80, 81, size=(B, L, k)), -1, L - 1)
+    bins = np.where(idx < 0, -1, rng.integers(0, n_bins, size=(B, L, k)))
+    mask = (rng.random(B * L) > 0.3).astype(np.uint8)
+    mask[64 * 8 * 32:2 * 64 * 8 * 32] = 0  # every tile of the second look
+    mask[64 * 8 * 32 - 3 * 32:64 * 8 * 32 - 32] = 0
+    _check_backward(rng, idx, bins, n_bins, n_pos, 72, mask.reshape(B, L))
+
+
+# Batches that end within a tile: one to three residues behind the last whole word of masks, the only valid ones
+@pytest.mark.parametrize("L", [1, 2, 3, 5, 39, 294, 515])
+def test_factor_backward_tail(L):
+    rng = np.random.default_rng(L)
+    idx = rng.integers(0, L, size=(1, L, 2))
+    bins = rng.integers(0, 16, size=(1, L, 2))
+    mask = np.zeros((1, L), np.uint8)
+    mask[0, L // 4 * 4:] = 1
+    _check_backward(rng, idx, bins, 16, 9, 64, mask)
 
 
 @pytest.mark.parametrize("B,L,k,n_bins,n_pos,n_out,pos_mode", [
