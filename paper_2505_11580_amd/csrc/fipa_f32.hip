@@ -168,14 +168,22 @@ __global__ __launch_bounds__(256, EXACT && (NCH + NT) * 4 + 60 <= 256 ? 2 : 1) v
     const int rg = wave % RG, ks = wave / RG;
     const int i_wg = (unit - bh * p.n_rt) * (16 * RG);
     const int L = p.L, H = p.H, DZ = p.DZ, nq = 3 * p.Pq, nv = 3 * p.Pv;
-    float cen[3];
+    // (The reference point is read where it is wanted up to r c_z = 256: kept to the end it took up to 1 % of one chain of 257 to 383
+    // residues.  At 512 it is the other way round.)
+    constexpr bool kKeepReference = PACK || NCH == 33;
+    [[maybe_unused]] float cen[3];
     int kvlen;
     if constexpr (PACK) {
         batch_reference(p, b, cen, kvlen);
     } else {
         kvlen = p.kvlen[b];
-        for (int a = 0; a < 3; ++a) cen[a] = p.cen[4 * b + a];
+        if constexpr (kKeepReference)
+            for (int a = 0; a < 3; ++a) cen[a] = p.cen[4 * b + a];
     }
+    const auto reference = [&](int a) {
+        if constexpr (kKeepReference) return cen[a];
+        else return p.cen[4 * b + a];
+    };
     const int nch = G.nch, nt = G.nt;
     const int zoff = G.zoff, voff = G.voff, cch = G.c16 / 16;
     const float coef = kLog2e * 0.5f * p.gamma[h] * p.w_L * p.w_C;
@@ -218,7 +226,7 @@ __global__ __launch_bounds__(256, EXACT && (NCH + NT) * 4 + 60 <= 256 ? 2 : 1) v
 #pragma unroll
         for (int x = 0; x < 12; ++x) {
             const int pp = x / 3, a = x % 3;
-            qg[x] = R[3 * a] * src[3 * pp] + R[3 * a + 1] * src[3 * pp + 1] + R[3 * a + 2] * src[3 * pp + 2] + (t[a] - cen[a]);
+            qg[x] = R[3 * a] * src[3 * pp] + R[3 * a + 1] * src[3 * pp + 1] + R[3 * a + 2] * src[3 * pp + 2] + (t[a] - reference(a));
         }
     }
 
@@ -418,7 +426,7 @@ __global__ __launch_bounds__(256, EXACT && (NCH + NT) * 4 + 60 <= 256 ? 2 : 1) v
         for (int idx = x0; idx < nv; idx += 16) {
             const int pp = idx / 3, x = idx - 3 * pp;
             float val = 0.f;
-            for (int y = 0; y < 3; ++y) val += R[3 * y + x] * (rb[p.c + 3 * pp + y] - (t[y] - cen[y]));
+            for (int y = 0; y < 3; ++y) val += R[3 * y + x] * (rb[p.c + 3 * pp + y] - (t[y] - reference(y)));
             p.o_pts[ro * nv + idx] = valid ? val : 0.f;
         }
         const float *z1 = p.z1 + ui * DZ;
