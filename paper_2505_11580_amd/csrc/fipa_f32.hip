@@ -474,7 +474,14 @@ F32Layout f32_layout(const fipa_desc &d)
 // Two launches | one, us per call: r c_z = 32, H = 4, L = 64 14.0 | 11.1, 256 21.7 | 17.2; B = 2, H = 12, L = 256 24.8 | 20.0, 384 34.4 | 46.5;
 // r c_z = 128, B = 2, H = 12, L = 64 16.8 | 12.3, 256 37.4 | 32.0, 384 76.0 | 74.5; r c_z = 256, H = 12, L = 64 20.8 | 18.1, 128 27.3 | 26.6,
 // 192 34.2 | 35.1, 256 40.9 | 43.8; r c_z = 512, H = 12, L = 64 30.8 | 29.1, 128 43.2 | 43.9.
-bool f32_one_launch(int L, int DZ) { return L <= (DZ <= 128 ? 256 : DZ <= 256 ? 128 : 64); }
+// The workgroups that repeat this work should all be resident: up to three per compute unit at r c_z = 16, two at 32 and 64, one from 256
+// on (of 128 it pays at any number).  B H = 48, L = 256, 768 workgroups: r c_z = 16 1 : 0.82 (1024 1.11), 32 34.1 | 42.7, 64 1 : 1.24, 128 1 : 0.91;
+// B H = 128, L = 64, 512: 32 1 : 0.65, 64 1 : 0.67; r c_z = 512, B H = 64, L = 64, 256 1 : 0.97, B H = 192, L = 33, 576 72 | 78.
+bool f32_one_launch(int L, int DZ, long long workgroups)
+{
+    const int resident = DZ == 16 ? 3 : DZ <= 64 ? 2 : DZ == 128 ? 4 : 1;
+    return L <= (DZ <= 128 ? 256 : DZ <= 256 ? 128 : 64) && workgroups <= 256 * resident;
+}
 
 size_t f32_lds_bytes(const F32Geom &g, int KS) { return ((size_t)KS * 16 * g.S + KS * 16 + 128) * sizeof(float); }
 
@@ -526,7 +533,7 @@ hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws
     const long long bh = (long long)d.B * d.H;
     // 16-row workgroups where 32-row ones would not give every CU two (the widest records fit LDS only as 32-key tiles)
     const bool small = bh * ((d.L + 31) / 32) < 512 && f32_lds_bytes(p.g, 4) <= 160 * 1024;
-    const bool one_launch = exact && small && f32_one_launch(d.L, p.DZ);
+    const bool one_launch = exact && small && f32_one_launch(d.L, p.DZ, bh * ((d.L + 15) / 16));
     if (!one_launch) {
         const unsigned per_head = ((unsigned)d.L * (p.g.HRW / 4) + 255u) / 256u;
         hipLaunchKernelGGL(fipa_pack_f32_kernel, dim3(d.H * per_head, d.B), dim3(256), 0, stream, p);
