@@ -757,13 +757,27 @@ hipError_t run_split(const SplitParams &p, hipStream_t stream)
 // Against the fp32 matrix instructions, us per call (those | this): r c_z = 256, one chain of 256, H = 4 to 12 41 | 38 to 41, of 320
 // 48 | 41 to 49, of 384 54 to 98 | 42 to 49, of 1024 and H = 12 342 | 103; two chains, H = 12, of 160 34 | 43, of 192 60 | 44 (there
 // the other kernel's tiles of 16 queries pass one round of the chip); r c_z = 128, H = 12, of 320 36 | 41, of 384 45 | 43, of 1024
-// 174 | 80; r c_z = 64, H = 12, of 384 34 | 34, of 512 45 | 40, of 1024 90 | 70; r c_z = 32, H = 12, of 384 29 | 29, of 512 37 | 34, of 1024 75 | 62.  Short calls are bound by start-up, which is longer here.
+// 174 | 80; r c_z = 64, H = 12, of 384 34 | 34, of 512 45 | 40, of 1024 90 | 70; r c_z = 32, H = 12, of 384 29 | 29, of 512 37 | 34, of 1024 75 | 62.
+// Short calls are bound by start-up, which is longer here.
+// Batches of short chains, r c_z = 256, whose tiles of 128 queries stand partly empty: up to 64 residues only where the other kernel's
+// tiles of 16 queries, which it takes below 512 tiles of 32, make more than two rounds and the tiles here make one (B H = 192, 64 residues
+// 52 | 38, 160 of 48 1 : 1.12, 256 of 64 37 | 41, 384 of 32 48 | 51, 768 of 32 48 | 73); from 65 to 96 residues not where a second round
+// would be less than half full (B H = 300, 65 residues 1 : 1.10, 96 1 : 1.02, 380 of 65 1 : 0.92, 513 1 : 1.02; 256 1 : 0.77).
+// r c_z = 32, up to 1024 residues: not where little more than half of the compute units get a tile (140 tiles of 513 residues 1 : 1.13, of 769
+// 1 : 1.07, of 600 1 : 0.94; 160 to 176 1 : 0.96 to 1.02; 256 1 : 0.65), up to 576 only for a few heads or many tiles (512 residues: B H = 4
+// 1 : 0.87, 10 1 : 0.97, 12 and 24 1 : 1.05, 40 1 : 0.98).  r c_z = 128, below 448 residues: B H = 6 1 : 0.98 at 384, 10 1 : 1.10, 12 1 : 1.01
+// and at 400 1 : 0.91, 16 1 : 1.05 and 0.96, 20 1 : 0.92.
 bool f32_split_applies(const fipa_desc &d)
 {
     const int DZ = d.r * d.cz;
     if (d.c != 16 || d.Pq != 4 || d.Pv != 8 || d.cz % 4 != 0) return false;
-    if (DZ == 256) return d.L >= 384 || (long long)d.B * d.H * ((d.L + 15) / 16) > 256;
-    return (DZ == 128 && d.L >= 384) || ((DZ == 64 || DZ == 32) && d.L >= 512);
+    const long long bh = (long long)d.B * d.H, tiles = bh * ((d.L + 127) / 128);
+    if (DZ == 256 && d.L <= 64) return bh <= kUnits && bh * ((d.L + 31) / 32) < 512 && bh * ((d.L + 15) / 16) > 512;
+    if (DZ == 256 && d.L <= 96 && bh > kUnits && bh < 384) return false;
+    if (DZ == 256) return d.L >= 384 || bh * ((d.L + 15) / 16) > 256;
+    if (DZ == 128) return d.L >= 448 || (d.L >= 384 && (bh <= 6 || bh >= 20 || (d.L >= 400 && bh >= 12)));
+    if (DZ == 32) return d.L >= 1024 || (d.L >= 512 && (tiles >= 160 || (tiles <= kUnits / 2 && (d.L >= 576 || bh <= 10))));
+    return DZ == 64 && d.L >= 512;
 }
 
 size_t f32_split_workspace(const fipa_desc &d) { return split_layout(d).total; }
