@@ -111,7 +111,10 @@ const char *fipa_status_string(int status);
  * whose weights are held follow the size that is given.  A training step of two chains of 4096
  * residues, H = 12, r c_z = 256: 1.75 ms in 1.5 GB (the query), 2.95 ms in 0.67 GB (the least); at
  * r c_z = 128, where few rows make the backward form the weights again in every product instead,
- * 1.25 ms in 1.3 GB and 1.60 ms in 0.41 GB.
+ * 1.25 ms in 1.3 GB and 1.60 ms in 0.41 GB.  The float32 forward of long chains asks for its keys as bfloat16 parts (two to three
+ * times its least with many heads) and, for B H <= 128, for the sums of parts of the key range (at most 256 x 128 x (44 + cz) floats); in
+ * less it takes fewer parts, below that form's size the slower kernel: one chain of 1024 residues, H = 12, r c_z = 256, 0.10 ms in 30 MB
+ * (the query), 0.34 ms in 3.7 MB (the least).
  * Either output pointer may be NULL.  Host-only, touches no device.
  */
 int fipa_workspace_bytes(const fipa_desc *desc, size_t *forward_bytes, size_t *backward_bytes);

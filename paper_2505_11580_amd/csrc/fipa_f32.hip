@@ -503,7 +503,7 @@ size_t f32_forward_workspace_min(const fipa_desc &d) { return f32_layout(d).tota
 
 size_t f32_forward_workspace(const fipa_desc &d)
 {
-    const size_t least = f32_forward_workspace_min(d), split = f32_split_applies(d) ? f32_split_workspace(d) : 0;
+    const size_t least = f32_forward_workspace_min(d), split = f32_split_workspace(d);
     return split > least ? split : least;
 }
 

@@ -15,6 +15,8 @@
 #include "fipa_gfx950.h"
 #include "fipa_f32.h"
 
+#include <algorithm>
+
 namespace fipa {
 
 namespace {
@@ -706,7 +708,7 @@ __global__ __launch_bounds__(256) void fipa_merge_split_kernel(SplitParams p)
 }
 
 struct SplitLayout {
-    size_t cen, kvlen, zb, hb, part, least, total;
+    size_t cen, kvlen, zb, hb, part;  // part: also the size without the space for the key ranges' sums
 };
 
 constexpr int kUnits = 256;  // one workgroup per compute unit: a call of at most half as many tiles splits its key range
@@ -725,21 +727,24 @@ SplitLayout split_layout(const fipa_desc &d)
     w.kvlen = take((size_t)d.B * sizeof(int));
     w.zb = take((size_t)d.B * n_kb * 3 * 64 * d.r * d.cz);
     w.hb = take((size_t)d.B * d.H * n_kb * kHeadBlock);
-    w.least = off;
-    w.part = take((size_t)kUnits * 128 * part_row(d.cz) * sizeof(float));
-    w.total = off;
+    w.part = off;
     return w;
 }
 
-int split_parts(const fipa_desc &d, size_t ws_bytes)
+long long split_tiles(const fipa_desc &d) { return (long long)d.B * d.H * ((d.L + 127) / 128); }
+
+size_t split_parts_bytes(const fipa_desc &d, int parts)
 {
-    const long long tiles = (long long)d.B * d.H * ((d.L + 127) / 128);
+    return parts > 1 ? (size_t)split_tiles(d) * parts * 128 * part_row(d.cz) * sizeof(float) : 0;
+}
+
+// Key ranges of a call; in less space than they take, as many as fit.
+int split_parts(const fipa_desc &d)
+{
+    const long long tiles = split_tiles(d);
     const int n_kb = (d.L + 31) / 32;
-    if (tiles > kUnits / 2 || ws_bytes < split_layout(d).total) return 1;
-    int parts = (int)(kUnits / tiles);
-    if (parts > 8) parts = 8;
-    if (parts > n_kb / 2) parts = n_kb / 2;
-    return parts > 1 ? parts : 1;
+    if (tiles > kUnits / 2) return 1;
+    return std::max(1, std::min({(int)(kUnits / tiles), 8, n_kb / 2}));
 }
 
 template <int DZ>
@@ -753,6 +758,15 @@ hipError_t run_split(const SplitParams &p, hipStream_t stream)
 }
 
 }  // namespace
+
+// The lengths from which on the kernel may be the faster one (f32_split_applies); they only grow with the batch's at r c_z = 256.
+static bool split_reaches(const fipa_desc &d)
+{
+    const int DZ = d.r * d.cz;
+    if (d.c != 16 || d.Pq != 4 || d.Pv != 8 || d.cz % 4 != 0) return false;
+    if (DZ == 256) return d.L >= 384 || (long long)d.B * d.H * ((d.L + 15) / 16) > 256;
+    return (DZ == 128 && d.L >= 384) || ((DZ == 64 || DZ == 32) && d.L >= 512);
+}
 
 // Against the fp32 matrix instructions, us per call (those | this): r c_z = 256, one chain of 256, H = 4 to 12 41 | 38 to 41, of 320
 // 48 | 41 to 49, of 384 54 to 98 | 42 to 49, of 1024 and H = 12 342 | 103; two chains, H = 12, of 160 34 | 43, of 192 60 | 44 (there
@@ -769,19 +783,31 @@ hipError_t run_split(const SplitParams &p, hipStream_t stream)
 // and at 400 1 : 0.91, 16 1 : 1.05 and 0.96, 20 1 : 0.92.
 bool f32_split_applies(const fipa_desc &d)
 {
+    if (!split_reaches(d)) return false;
     const int DZ = d.r * d.cz;
-    if (d.c != 16 || d.Pq != 4 || d.Pv != 8 || d.cz % 4 != 0) return false;
-    const long long bh = (long long)d.B * d.H, tiles = bh * ((d.L + 127) / 128);
+    const long long bh = (long long)d.B * d.H;
     if (DZ == 256 && d.L <= 64) return bh <= kUnits && bh * ((d.L + 31) / 32) < 512 && bh * ((d.L + 15) / 16) > 512;
-    if (DZ == 256 && d.L <= 96 && bh > kUnits && bh < 384) return false;
-    if (DZ == 256) return d.L >= 384 || bh * ((d.L + 15) / 16) > 256;
-    if (DZ == 128) return d.L >= 448 || (d.L >= 384 && (bh <= 6 || bh >= 20 || (d.L >= 400 && bh >= 12)));
-    if (DZ == 32) return d.L >= 1024 || (d.L >= 512 && (tiles >= 160 || (tiles <= kUnits / 2 && (d.L >= 576 || bh <= 10))));
-    return DZ == 64 && d.L >= 512;
+    if (DZ == 256 && d.L <= 96) return bh <= kUnits || bh >= 384;
+    if (DZ == 128 && d.L < 448) return bh <= 6 || bh >= 20 || (d.L >= 400 && bh >= 12);
+    if (DZ == 32 && d.L < 1024) return split_tiles(d) >= 160 || (split_tiles(d) <= kUnits / 2 && (d.L >= 576 || bh <= 10));
+    return true;
 }
 
-size_t f32_split_workspace(const fipa_desc &d) { return split_layout(d).total; }
-size_t f32_split_workspace_min(const fipa_desc &d) { return split_layout(d).least; }
+size_t f32_split_workspace_min(const fipa_desc &d) { return split_layout(d).part; }
+
+// The key blocks, and the most that the key ranges of a chain up to this length take: a workspace for the longest chain of a batch serves
+// the shorter ones too, and grows evenly with the length.
+size_t f32_split_workspace(const fipa_desc &d)
+{
+    if (!split_reaches(d)) return 0;
+    size_t parts = 0;
+    fipa_desc x = d;
+    for (int rt = 1; rt <= (d.L + 127) / 128 && (long long)d.B * d.H * rt <= kUnits / 2; ++rt) {
+        x.L = std::min(128 * rt, d.L);
+        if (split_reaches(x)) parts = std::max(parts, split_parts_bytes(x, split_parts(x)));
+    }
+    return split_layout(d).part + parts;
+}
 
 hipError_t f32_split_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
 {
@@ -802,7 +828,8 @@ hipError_t f32_split_forward(const fipa_desc &d, const FwdArgs &a, void *ws, siz
     p.DZ = d.r * d.cz;
     p.n_kb = (d.L + 31) / 32;
     p.n_rt = (d.L + 127) / 128;
-    p.n_parts = split_parts(d, ws_bytes);
+    p.n_parts = split_parts(d);
+    while (p.n_parts > 1 && w.part + split_parts_bytes(d, p.n_parts) > ws_bytes) --p.n_parts;
     p.n_units = d.B * d.H * p.n_rt * p.n_parts;
     p.w_L = d.w_L; p.w_C = d.w_C; p.qk_scale = d.qk_scale;
 

@@ -78,6 +78,25 @@ def test_f32_workspace_holds_the_record_of_the_kernel_that_runs():
         assert need == B * H * L * record * 4 + 2 * 256, (cz, r, need)
 
 
+def test_f32_split_workspace_asks_for_what_is_used():
+    # key blocks of 32 residues (three bf16 planes of z2, 17408 bytes per head) and, up to 128 tiles of 128 queries, the sums of
+    # two to eight key ranges of each: the most that a length up to the batch's takes, which is never less for a longer one
+    def need(B, L, H, cz, r):
+        return binding.workspace_bytes(binding.make_desc(B, L, H, 16, 4, 8, cz, r, binding.FIPA_DTYPE_F32))[0]
+
+    def blocks(B, L, H, DZ):
+        kb = (L + 31) // 32
+        return 2 * 256 + B * kb * (192 * DZ + H * 17408)
+
+    unit = 128 * (44 + 128) * 4
+    assert need(1, 384, 4, 128, 2) == blocks(1, 384, 4, 256) + 12 * 6 * unit     # 12 tiles, 12 key blocks
+    assert need(2, 2048, 12, 128, 2) == blocks(2, 2048, 12, 256) + 120 * 2 * unit  # at 640 residues
+    assert need(12, 512, 12, 128, 2) == blocks(12, 512, 12, 256)                 # 144 tiles from the shortest chain on
+    for B, H, cz, r in ((1, 12, 128, 2), (2, 12, 16, 2), (2, 8, 128, 1), (20, 12, 128, 2), (1, 4, 64, 1)):
+        sizes = [need(B, L, H, cz, r) for L in range(16, 3000, 31)]
+        assert sizes == sorted(sizes), (B, H, cz, r)
+
+
 def test_bad_descriptions_are_rejected_on_the_host():
     lib = binding.lib()
     sz = ctypes.c_size_t(0)

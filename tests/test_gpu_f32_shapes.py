@@ -64,8 +64,11 @@ def test_f32_split_operands_in_every_workspace():
     desc, dev = binding.upload(inp)
     want = gu.oracle_forward_chunked(inp)
     full = binding.workspace_bytes(desc)[0]
-    parts, least = 256 * 128 * (44 + 64) * 4, (3 * 450 * 76 * 4 + 255) // 256 * 256 + 2 * 256
-    for size in (full, full - parts, full - parts - 256, least):
+    # 12 tiles of 128 queries, seven key ranges; key blocks of 32 residues: three planes of z2, and 17408 bytes per head
+    tiles, unit, least = 12, 128 * (44 + 64) * 4, (3 * 450 * 76 * 4 + 255) // 256 * 256 + 2 * 256
+    blocks = 2 * 256 + 15 * 3 * 64 * 128 + 3 * 15 * 17408
+    assert full == blocks + 7 * tiles * unit
+    for size in (full, full - 256, blocks + 2 * tiles * unit, blocks, blocks - 256, least):
         out = binding.alloc_outputs(desc)
         for n in gu.NAMES:
             out[n].fill_(float("nan"))
