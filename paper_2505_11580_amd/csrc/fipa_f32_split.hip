@@ -1,14 +1,15 @@
 // fp32 forward of AlphaFold2's head shape on the bf16 matrix instructions.  Every operand of the two products is the exact
-// sum of three bf16 numbers (8 + 8 + 8 bits of a float's 24), and a product of two such sums is taken as the six products
-// of parts that reach 2^-24 of it; what is left out is at most 2^-25 of |a| |b|, below the rounding of an fp32 product.  The
-// squared distances stay explicit fp32 differences on the vector ALU, the softmax is fp32 throughout.
+// sum of three bf16 numbers (8 + 8 + 8 bits of a float's 24), and a product of two such sums is taken as its six largest
+// products of parts (Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision
+// Computations", 2019).  The three left out are at most 2^-24 of |a| |b| together, about the rounding of an fp32 product.
+// The squared distances stay explicit fp32 differences on the vector ALU, the softmax is fp32 throughout.
 //
 // Bound: bf16 matrix pipe, six instructions for one of the fp32 pipe's at 16 times its rate.  A wave owns 32 queries, whose
 // split features (51 fragments at r c_z = 256) stay in registers beside the 32 x (64 + r c_z) accumulator, one wave per SIMD;
 // an operand read from LDS feeds one to three instructions, so that LDS is half busy.  Key blocks of 32 residues come by
 // direct loads into two stages, in the order and swizzle in which the pack kernel left them.  Where the tiles of 128 queries
 // fill half of the compute units or less, the keys are cut into ranges whose sums a small kernel adds.
-// B = 2, L = 1024, H = 12, r c_z = 256: 448 us on the fp32 matrix instructions (fipa_f32.hip) -> 184; 4.9 us per key block, of
+// B = 2, L = 1024, H = 12, r c_z = 256: 448 us on the fp32 matrix instructions (fipa_f32.hip) -> 171; 4.9 us per key block, of
 // which the 222 matrix instructions take 3.8 at the clock that they leave (17.3 ns each), 32 us before and behind the loop.
 // Distance from float64 (2-norm, o | o_pts | o_pair | lse): 4.50e-7 | 2.40e-6 | 4.49e-7 | 3.78e-7 -> 4.40e-7 | 2.39e-6 | 4.43e-7 |
 // 3.73e-7; no larger at any of the sizes compared (450 to 2048 residues, r c_z = 32 to 256).
@@ -50,7 +51,7 @@ struct SplitParams {
     float w_L, w_C, qk_scale;
 };
 
-// x = hi + mid + lo, each a bf16: round to nearest, so that the parts fall by 2^-9.  (The largest floats would round up to
+// x = hi + mid + lo, each a bf16 to the nearest: |mid| is at most 2^-8 of |x|, |lo| 2^-17.  (The largest floats would round up to
 // infinity: the first part stops at the largest bf16.)
 __device__ __forceinline__ void split3(float x, unsigned &hi, unsigned &mid, unsigned &lo)
 {

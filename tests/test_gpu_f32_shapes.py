@@ -41,6 +41,8 @@ def test_f32_lse_and_far_keys():
     inp = wl.make_inputs(0, L=150, H=3, cz=64, chain=True)
     inp["mask"] = (np.random.default_rng(3).random((1, 150)) < 0.7).astype(np.uint8)
     gu.check(inp, label="fp32 scattered mask, chain")
+    from tests.test_gpu_f32_split import log_sum_exp
+    assert gu.rel_err(gu.run_gpu(inp)["lse"], log_sum_exp(inp)) <= gu.TOL["fp32"]
 
 
 # split operands: every width, one residue past a block and a tile, blocks and whole tiles without a valid residue, key ranges in one and
