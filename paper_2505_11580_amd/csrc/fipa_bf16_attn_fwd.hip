@@ -741,24 +741,20 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
         }
     }
 
-    // What the last step needs of a row besides its sums: its mask, frame and bias.  A kept forward requests them here: behind the stores of
-    // O^ they would wait for all of them (B = 2, L = 4096, r c_z = 256 485 -> 466 us, 32 packed chains 192 -> 188).  Without O^ they are
-    // read where they are used: requested together here or there it was 0.3 to 0.8 % slower.
+    // What the last step needs of a row besides its sums.  A kept forward requests it here: behind the stores of O^ it would wait
+    // for all of them (B = 2, L = 4096, r c_z = 256 485 -> 466 us, 32 packed chains 192 -> 188; without O^ it is no faster here).
     [[maybe_unused]] float Rm[9], tc[3], qb = 0.f;
     [[maybe_unused]] bool row_ok = true;
-    [[maybe_unused]] const auto request_frame = [&] {
+    [[maybe_unused]] const auto request_row = [&] {
         const size_t ur = urow0 + min(irow, ulen - 1);  // (rows past the end compute on a valid address and store nothing)
-        const float *R = p.rot + ur * 9, *tr = p.trans + ur * 3;
+        if (p.mask) row_ok = p.mask[ur] != 0;
 #pragma unroll
-        for (int a = 0; a < 9; ++a) Rm[a] = R[a];
+        for (int a = 0; a < 9; ++a) Rm[a] = p.rot[ur * 9 + a];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) tc[a] = tr[a] - p.cen[4 * b + a];
-    };
-    if constexpr (KEEP) {
-        if (p.mask) row_ok = p.mask[urow0 + min(irow, ulen - 1)] != 0;
-        request_frame();
+        for (int a = 0; a < 3; ++a) tc[a] = p.trans[ur * 3 + a] - p.cen[4 * b + a];
         qb = p.qbias[(size_t)bh * p.Lp + irow];
-    }
+    };
+    if constexpr (KEEP) request_row();
 
     // ---- drain: the last two blocks -----------------------------------------------------------------
     if (nblk > 1) {
@@ -943,10 +939,10 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
         }
 
         // ---- normalise, apply the inverse frame, store ---------------------------------------------
+        if constexpr (!KEEP) request_row();
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
         const float lse2 = l_tot > 0.f ? w.m_ref + __log2f(l_tot) : -INFINITY;
         const int h = bh - b * p.H;
-        if constexpr (!KEEP) row_ok = p.mask ? p.mask[urow0 + irow_c] != 0 : true;
         const bool valid = row_ok && l_tot > 0.f;
         const float sc = valid ? inv : 0.f;
         const size_t row = (urow0 + irow_c) * p.H + h;
@@ -961,7 +957,6 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
             }
         }
         {
-            if constexpr (!KEEP) request_frame();
             float outp[12];
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) {
@@ -1014,7 +1009,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
                 }
             }
             if (p.lse && g == 0)
-                p.lse[user_lse_index(p, b, h, irow)] = valid ? lse2 * kLn2 - (KEEP ? qb : p.qbias[(size_t)bh * p.Lp + irow]) : 0.f;
+                p.lse[user_lse_index(p, b, h, irow)] = valid ? lse2 * kLn2 - qb : 0.f;
         }
     }
 }
