@@ -743,6 +743,9 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
 
     // What the last step needs of a row besides its sums.  A kept forward requests it here: behind the stores of O^ it would wait
     // for all of them (B = 2, L = 4096, r c_z = 256 485 -> 466 us, 32 packed chains 192 -> 188; without O^ it is no faster here).
+    // A plain one requests it at the start of that step (r c_z <= 128, chains of 110 to 400 residues 2 to 3 % faster than where it is used), at
+    // 256, where that takes registers from the sums, where it is used (one chain of 131 22.3 us so, 22.6; 2633 residues, ragged, 168.9, 167.4).
+    constexpr bool kTogether = KEEP || DZ < 256;
     [[maybe_unused]] float Rm[9], tc[3], qb = 0.f;
     [[maybe_unused]] bool row_ok = true;
     [[maybe_unused]] const auto request_row = [&] {
@@ -939,10 +942,11 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
         }
 
         // ---- normalise, apply the inverse frame, store ---------------------------------------------
-        if constexpr (!KEEP) request_row();
+        if constexpr (!KEEP && kTogether) request_row();
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
         const float lse2 = l_tot > 0.f ? w.m_ref + __log2f(l_tot) : -INFINITY;
         const int h = bh - b * p.H;
+        if constexpr (!kTogether) row_ok = p.mask ? p.mask[urow0 + irow_c] != 0 : true;
         const bool valid = row_ok && l_tot > 0.f;
         const float sc = valid ? inv : 0.f;
         const size_t row = (urow0 + irow_c) * p.H + h;
@@ -957,6 +961,13 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
             }
         }
         {
+            if constexpr (!kTogether) {
+                const float *R = p.rot + (urow0 + irow_c) * 9, *tr = p.trans + (urow0 + irow_c) * 3;
+#pragma unroll
+                for (int a = 0; a < 9; ++a) Rm[a] = R[a];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) tc[a] = tr[a] - p.cen[4 * b + a];
+            }
             float outp[12];
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) {
@@ -1009,7 +1020,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
                 }
             }
             if (p.lse && g == 0)
-                p.lse[user_lse_index(p, b, h, irow)] = valid ? lse2 * kLn2 - qb : 0.f;
+                p.lse[user_lse_index(p, b, h, irow)] = valid ? lse2 * kLn2 - (kTogether ? qb : p.qbias[(size_t)bh * p.Lp + irow]) : 0.f;
         }
     }
 }
