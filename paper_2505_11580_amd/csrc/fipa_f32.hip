@@ -473,14 +473,14 @@ F32Layout f32_layout(const fipa_desc &d)
 // Chains short enough that every workgroup forms the records of all keys itself (fipa_attn_f32_kernel<.., PACK>) in less than a launch takes.
 // Two launches | one, us per call: r c_z = 32, H = 4, L = 64 14.0 | 11.1, 256 21.7 | 17.2; B = 2, H = 12, L = 256 24.8 | 20.0, 384 34.4 | 46.5;
 // r c_z = 128, B = 2, H = 12, L = 64 16.8 | 12.3, 256 37.4 | 32.0, 384 76.0 | 74.5; r c_z = 256, H = 12, L = 64 20.8 | 18.1, 128 27.3 | 26.6,
-// 192 34.2 | 35.1, 256 40.9 | 43.8; r c_z = 512, H = 12, L = 64 30.8 | 29.1, 128 43.2 | 43.9.
+// two chains of 117, H = 4 25.4 | 26.1, 192 34.2 | 35.1; r c_z = 512, H = 12, L = 64 30.8 | 29.1, 128 43.2 | 43.9.
 // The workgroups that repeat this work should all be resident: up to three per compute unit at r c_z = 16, two at 32 and 64, one from 256
 // on (of 128 it pays at any number).  B H = 48, L = 256, 768 workgroups: r c_z = 16 1 : 0.82 (1024 1.11), 32 34.1 | 42.7, 64 1 : 1.24, 128 1 : 0.91;
 // B H = 128, L = 64, 512: 32 1 : 0.65, 64 1 : 0.67; r c_z = 512, B H = 64, L = 64, 256 1 : 0.97, B H = 192, L = 33, 576 72 | 78.
 bool f32_one_launch(int L, int DZ, long long workgroups)
 {
     const int resident = DZ == 16 ? 3 : DZ <= 64 ? 2 : DZ == 128 ? 4 : 1;
-    return L <= (DZ <= 128 ? 256 : DZ <= 256 ? 128 : 64) && workgroups <= 256 * resident;
+    return L <= (DZ <= 128 ? 256 : 64) && workgroups <= 256 * resident;
 }
 
 size_t f32_lds_bytes(const F32Geom &g, int KS) { return ((size_t)KS * 16 * g.S + KS * 16 + 128) * sizeof(float); }
