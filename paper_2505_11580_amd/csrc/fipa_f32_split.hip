@@ -154,10 +154,6 @@ __global__ __launch_bounds__(256) void fipa_pack_split_kernel(SplitParams p)
             *reinterpret_cast<f32x4 *>(blk + F::G + 48 * row + 16 * (x0 - 10)) = (f32x4){x[0], x[1], x[2], x[3]};
             continue;
         }
-        if (x0 >= 2) {  // (values of which twice is infinite: left to direct_row like an infinity)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = fabsf(x[e]) <= 0x1p126f ? x[e] : INFINITY;
-        }
         u32x4 out[3];
         split_slot(x, out);
 #pragma unroll
@@ -219,60 +215,87 @@ __device__ __forceinline__ void finish_row(const SplitParams &p, int b, int h, i
     if (p.lse && x0 == 0) p.lse[((size_t)b * p.H + h) * p.L + i] = valid ? kLn2 * (m + __log2f(l)) : 0.f;
 }
 
-// One row against the keys j0 .. j1 - 1 from the inputs, by one wave on the vector ALU: what the tile leaves of it in LDS (`out`).  For rows
-// with an infinite operand, which six products of parts do not carry (an infinity has no second part, and a product far beyond the
-// largest float leaves parts of either sign): an infinite logit or value then gives what fp32 arithmetic gives.
+// A wave's rows `again` against the keys j0 .. j1 - 1 from the inputs, in fp32 on the vector ALU: a lane takes its row and every second key,
+// and leaves what the tile left of the row in LDS (`out`, also the room for the row's features).  For rows with an infinite operand, which
+// six products of parts do not carry (an infinity has no second part, and a product far beyond the largest float leaves parts of
+// either sign): an infinite logit or value then gives what fp32 arithmetic gives.  B = 2, L = 1024, H = 12, r c_z = 256, one infinite value:
+// 5.8 ms (one row after the other, a lane per key: 50; without it 0.17).
 template <int DZ>
-__device__ __forceinline__ void direct_row(const SplitParams &p, int b, int h, int i, int j0, int j1, const float *cen, bool whole, float *out)
+__device__ __forceinline__ void direct_rows(const SplitParams &p, int b, int h, int i, unsigned again, int j0, int j1, const float *cen, bool whole,
+                                            float *out)
 {
-    const int lane = threadIdx.x & 63;
+    constexpr int NC = (DZ + 40) / 4;
+    const int hf = (threadIdx.x >> 5) & 1;
+    const bool mine = (again >> (threadIdx.x & 31) & 1u) != 0u;
     const size_t row0 = (size_t)b * p.L, ui = row0 + i;
-    const float *q = p.q + (ui * p.H + h) * 16, *z1 = p.z1 + ui * DZ, *wb = p.w_b + (size_t)h * p.cz;
     const float sc = kLog2e * p.w_L * p.qk_scale, bz = kLog2e * p.w_L, coef = kLog2e * 0.5f * p.gamma[h] * p.w_L * p.w_C;
+    if (mine && hf == 0) {
+        const float *q = p.q + (ui * p.H + h) * 16, *z1 = p.z1 + ui * DZ, *wb = p.w_b + (size_t)h * p.cz;
+#pragma unroll 4
+        for (int x = 0; x < DZ + 16; ++x) out[x] = x < 16 ? sc * q[x] : bz * wb[(x - 16) & (p.cz - 1)] * z1[x - 16];
+    }
+    asm volatile("" ::: "memory");  // (the LDS accesses of a wave execute in order)
     auto point = [&](size_t u, const float *pts, int x) {  // global coordinate x of a residue's points
         const float *R = p.rot + u * 9 + 3 * (x % 3), *l = pts + x / 3 * 3;
         return R[0] * l[0] + R[1] * l[1] + R[2] * l[2] + (p.trans[u * 3 + x % 3] - cen[x % 3]);
     };
-    auto counts = [&](int j) { return j < j1 && (p.mask ? p.mask[row0 + j] != 0 : true); };
-    auto logit = [&](int j) {
-        if (!counts(j)) return -INFINITY;
-        const size_t u = row0 + j, hrow = u * p.H + h;
+    float qg[12];
+#pragma unroll
+    for (int x = 0; x < 12; ++x) qg[x] = point(ui, p.q_pts + (ui * p.H + h) * 12, x);
+    float m = -INFINITY, l = 0.f;
+    f32x4 acc[NC];
+#pragma unroll
+    for (int x = 0; x < NC; ++x) acc[x] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int t = j0; t < j1; t += 2) {
+        const int j = t + hf;
+        const size_t u = row0 + min(j, p.L - 1), hrow = u * p.H + h;
+        if (j >= j1 || (p.mask ? p.mask[u] == 0 : false)) continue;
+        const float *k = p.k + hrow * 16, *z2 = p.z2 + u * DZ, *v = p.v + hrow * 16;
         float s = 0.f, dist = 0.f;
-#pragma unroll 1
-        for (int x = 0; x < 16; ++x) s += sc * q[x] * p.k[hrow * 16 + x];
-#pragma unroll 1
-        for (int x = 0; x < DZ; ++x) s += bz * wb[x & (p.cz - 1)] * z1[x] * p.z2[u * DZ + x];
-#pragma unroll 1
+#pragma unroll
+        for (int x = 0; x < 16; x += 4) {
+            const f32x4 f = *reinterpret_cast<const f32x4 *>(out + x), y = *reinterpret_cast<const f32x4 *>(k + x);
+            for (int e = 0; e < 4; ++e) s += f[e] * y[e];
+        }
+#pragma unroll 8
+        for (int x = 0; x < DZ; x += 4) {
+            const f32x4 f = *reinterpret_cast<const f32x4 *>(out + 16 + x), y = *reinterpret_cast<const f32x4 *>(z2 + x);
+            for (int e = 0; e < 4; ++e) s += f[e] * y[e];
+        }
+#pragma unroll
         for (int x = 0; x < 12; ++x) {
-            const float df = point(ui, p.q_pts + (ui * p.H + h) * 12, x) - point(u, p.k_pts + hrow * 12, x);
+            const float df = qg[x] - point(u, p.k_pts + hrow * 12, x);
             dist += df * df;
         }
-        return s - coef * dist;
-    };
-    float m = -INFINITY, l = 0.f, sum[(DZ + 40 + 63) / 64] = {};
-    for (int j = j0 + lane; j < j1; j += 64) m = fmaxf(m, logit(j));
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    const float m_use = m == -INFINITY ? 0.f : m;
-    for (int jb = j0; jb < j1; jb += 64) {
-        const float w = __builtin_amdgcn_exp2f(logit(jb + lane) - m_use);
-        l += w;
-        for (unsigned long long rest = __ballot(counts(jb + lane)); rest != 0ull; rest &= rest - 1ull) {
-            const int t = __builtin_ctzll(rest);
-            const size_t u = row0 + jb + t, hrow = u * p.H + h;
-            const float wt = __shfl(w, t);
+        s -= coef * dist;
+        if (s > m) {
+            const float alpha = __builtin_amdgcn_exp2f(m - s);
+            l *= alpha;
+            m = s;
 #pragma unroll
-            for (int x = 0; x < (DZ + 40 + 63) / 64; ++x) {
-                const int col = lane + 64 * x, hc = col - DZ;
-                if (hc < 40) sum[x] += wt * (hc < 0 ? p.z2[u * DZ + col] : hc < 16 ? p.v[hrow * 16 + hc] : point(u, p.v_pts + hrow * 24, hc - 16));
-            }
+            for (int x = 0; x < NC; ++x) acc[x] *= alpha;
         }
+        const float w = __builtin_amdgcn_exp2f(s - (m == -INFINITY ? 0.f : m));
+        l += w;
+#pragma unroll
+        for (int x = 0; x < DZ / 4; ++x) acc[x] += w * *reinterpret_cast<const f32x4 *>(z2 + 4 * x);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[DZ / 4 + x] += w * *reinterpret_cast<const f32x4 *>(v + 4 * x);
+#pragma unroll
+        for (int x = 0; x < 24; ++x) acc[DZ / 4 + 4 + x / 4][x % 4] += w * point(u, p.v_pts + hrow * 24, x);
     }
-    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+    const float m_all = fmaxf(m, other_half(m)), wm = __builtin_amdgcn_exp2f(m - (m_all == -INFINITY ? 0.f : m_all));
+    l *= wm;
+    l += other_half(l);
     const float scale = !whole ? 1.f : l > 0.f ? 1.f / l : 0.f;
 #pragma unroll
-    for (int x = 0; x < (DZ + 40 + 63) / 64; ++x)
-        if (lane + 64 * x < DZ + 40) out[lane + 64 * x] = scale * sum[x];
-    if (lane < 2) out[DZ + 40 + lane] = lane == 0 ? m : l;
+    for (int x = 0; x < NC; ++x) {
+        f32x4 a = acc[x] * wm;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] = scale * (a[e] + other_half(a[e]));
+        if (mine && hf == 0) *reinterpret_cast<f32x4 *>(out + 4 * x) = a;
+    }
+    if (mine && hf == 0) *reinterpret_cast<f32x2 *>(out + DZ + 40) = (f32x2){m_all, l};
 }
 
 constexpr float kRaise = 1.f;  // log2 units: an exponent of up to 1 is rounded no worse than one below 0 (30: lse 4.17e-7 from float64, 1: 3.73e-7)
@@ -586,14 +609,14 @@ __global__ __launch_bounds__(256, DZ == 32 ? 2 : 1) void fipa_attn_f32_split_ker
     }
     l += other_half(l);
 
-    // Rows for direct_row.  An infinite factor of a logit (with one of z2 as a value too) makes a row's sum of weights a NaN, an infinite
-    // v or point the row's sum of that column.
+    // Rows for direct_rows.  An infinite factor of a logit (with one of z2 as a value too) makes a row's sum of weights a NaN; an infinite
+    // v or point the row's sum of that column, which a finite one of which twice is infinite can make an infinity.
     f32x4 odd = {l - l, 0.f, 0.f, 0.f};  // 0, or NaN
 #pragma unroll
     for (int x = 0; x < 20; ++x) odd[x & 3] = fmaf(acc[F::NB + x / 16][x % 16], 0.f, odd[x & 3]);
     const float any_odd = (odd[0] + odd[1]) + (odd[2] + odd[3]);
     const int own = i_wg + 32 * wave + n;
-    unsigned again = (unsigned)__ballot(any_odd + other_half(any_odd) != 0.f && own < L && (p.mask ? p.mask[(size_t)b * L + own] != 0 : true));
+    const unsigned again = (unsigned)__ballot(any_odd + other_half(any_odd) != 0.f && own < L && (p.mask ? p.mask[(size_t)b * L + own] != 0 : true));
 
     // the wave's rows through LDS: 16 lanes per row
     const bool whole = p.n_parts == 1;
@@ -614,11 +637,8 @@ __global__ __launch_bounds__(256, DZ == 32 ? 2 : 1) void fipa_attn_f32_split_ker
         // (the arguments by a pointer that is formed here: kept for this they would take scalar registers through the loop)
         uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(args));
-        for (; again != 0u; again &= again - 1u) {
-            const int rl = __builtin_ctz(again);
-            direct_row<DZ>(*reinterpret_cast<const SplitParams *>(args), b, h, i_wg + 32 * wave + rl, 32 * lo, min(32 * (lo + len), L), cen, whole,
-                           rows + rl * F::RS);
-        }
+        direct_rows<DZ>(*reinterpret_cast<const SplitParams *>(args), b, h, min(own, L - 1), again, 32 * lo, min(32 * (lo + len), L), cen, whole,
+                        rows + n * F::RS);
     }
     __syncthreads();
 #pragma unroll 2
@@ -629,9 +649,10 @@ __global__ __launch_bounds__(256, DZ == 32 ? 2 : 1) void fipa_attn_f32_split_ker
         f32x4 zr[DZ / 64 > 0 ? DZ / 64 : 1];
 #pragma unroll
         for (int x = 0; x < DZ / 64; ++x) zr[x] = *reinterpret_cast<const f32x4 *>(z1 + 4 * x0 + 64 * x);
-        const bool valid = (p.mask ? p.mask[ui] != 0 : true) && (!whole || hr[41] > 0.f);
+        bool valid = p.mask ? p.mask[ui] != 0 : true;
         float *dst = whole ? p.o_pair + (ui * H + h) * p.cz : out_part + (size_t)rl * prow + 40;
         if (whole) {
+            valid = valid && hr[41] > 0.f;
             finish_row(p, b, h, i, x0, cen, hr[40], hr[41], [&](int x) { return hr[x]; });
         } else if (i < L) {
             float *ph = out_part + (size_t)rl * prow;

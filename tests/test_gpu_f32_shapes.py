@@ -26,10 +26,11 @@ def test_f32_shapes(kw):
     gu.check(wl.make_inputs(0, **kw), label="fp32 %s" % kw)
 
 
-# the longest chains of the one-launch form (256, 128 and 64 residues by width), with and without a mask, and one residue more
+# the longest chains of the one-launch form (256 residues, 64 from r c_z = 256 on), with and without a mask, and one residue more
 @pytest.mark.parametrize("kw", [
     dict(L=256, cz=16, B=2, varlen=True, min_len=30), dict(L=257, cz=32, r=2), dict(L=256, cz=128, r=1, H=2),
     dict(L=128, cz=128, r=2, H=2, B=2, varlen=True, min_len=1), dict(L=129, cz=128, r=2, H=2), dict(L=64, cz=128, r=4, H=1),
+    dict(L=64, cz=64, r=4, H=5, B=2, varlen=True, min_len=3), dict(L=65, cz=64, r=4, H=5),
     dict(L=65, cz=128, r=4, H=1, B=2, varlen=True, min_len=20)])
 def test_f32_one_launch_edges(kw):
     kw = dict(dict(B=1, H=3, chain=True, trans_scale=0.3), **kw)
