@@ -800,9 +800,9 @@ static bool split_reaches(const fipa_desc &d)
 // 52 | 38, 160 of 48 1 : 1.12, 256 of 64 37 | 41, 384 of 32 48 | 51, 768 of 32 48 | 73); from 65 to 96 residues not where a second round
 // would be less than half full (B H = 300, 65 residues 1 : 1.10, 96 1 : 1.02, 380 of 65 1 : 0.92, 513 1 : 1.02; 256 1 : 0.77).
 // r c_z = 32, up to 704 residues: not where little more than half of the compute units get a tile (144 tiles of 641 residues 1 : 1.11, of 672
-// 1 : 1.09, of 704 1 : 0.96; 160 of 641 1 : 0.97), up to 528 only for a few heads (512 residues: B H = 4 1 : 0.87, 10 1 : 0.95, 12 1 : 1.02, 24
-// 1 : 1.03; 24 of 528 1 : 0.92).  r c_z = 128, below 432 residues: B H = 6 1 : 0.95 at 384, 8 1 : 1.02 (0.98 at 432), 10 1 : 1.05, 12 1 : 0.99 and
-// at 400 1 : 0.91, 16 1 : 1.04 and 0.96, 24 1 : 0.64.
+// 1 : 1.09, of 704 1 : 0.96; 160 of 641 1 : 0.97), nor at 512 where the key ranges of more than 10 heads leave compute units idle (B H = 10
+// 1 : 0.95, 12 1 : 1.02, 16 1 : 0.94, 24 1 : 1.03, 32 1 : 0.94, 60 1 : 0.66; of 528 12 1 : 0.91, 24 1 : 0.92).  r c_z = 128, below 432 residues:
+// B H = 6 1 : 0.95 at 384, 8 1 : 1.02 (0.98 at 432), 10 1 : 1.05 (416 0.95), 12 1 : 0.98, 16 1 : 1.04 and at 392 0.96, 24 1 : 0.64.
 bool f32_split_applies(const fipa_desc &d)
 {
     if (!split_reaches(d)) return false;
@@ -810,9 +810,9 @@ bool f32_split_applies(const fipa_desc &d)
     const long long bh = (long long)d.B * d.H;
     if (DZ == 256 && d.L <= 64) return bh <= kUnits && bh * ((d.L + 31) / 32) < 512 && bh * ((d.L + 15) / 16) > 512;
     if (DZ == 256 && d.L <= 96) return bh <= kUnits || bh >= 384;
-    if (DZ == 128 && d.L < 432) return bh <= 6 || bh >= 20 || (d.L >= 400 && bh >= 12);
-    if (DZ == 32 && d.L < 528 && bh > 10) return false;
-    if (DZ == 32 && d.L < 704) return split_tiles(d) <= kUnits / 2 || split_tiles(d) >= 160;
+    if (DZ == 128 && d.L < 432) return bh <= 6 || bh >= 20 || (bh >= 12 && (d.L > 384 || bh < 16)) || (d.L >= 416 && bh >= 10);
+    if (DZ == 32 && d.L <= 512 && bh > 10 && split_tiles(d) <= kUnits / 2) return split_tiles(d) * split_parts(d) == kUnits;
+    if (DZ == 32 && d.L > 512 && d.L < 704) return split_tiles(d) <= kUnits / 2 || split_tiles(d) >= 160;
     return true;
 }
 
