@@ -404,7 +404,7 @@ __device__ __forceinline__ f32x4 xchg_load(__amdgpu_buffer_rsrc_t rs, int off)
 }
 
 // KEEP (with FUSED; never split): the lifted output and the log2 log-sum-exp are left in memory as well, for the gradients.
-template <int DZ, bool FUSED, bool KEEP = false>
+template <int DZ, bool FUSED, bool KEEP = false, bool TOGETHER = true>
 __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p)
 {
     using C = AttnCfg<DZ>;
@@ -743,9 +743,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
 
     // What the last step needs of a row besides its sums.  A kept forward requests it here: behind the stores of O^ it would wait
     // for all of them (B = 2, L = 4096, r c_z = 256 485 -> 466 us, 32 packed chains 192 -> 188; without O^ it is no faster here).
-    // A plain one requests it at the start of that step (r c_z <= 128, chains of 110 to 400 residues 2 to 3 % faster than where it is used), at
-    // 256, where that takes registers from the sums, where it is used (one chain of 131 22.3 us so, 22.6; 2633 residues, ragged, 168.9, 167.4).
-    constexpr bool kTogether = KEEP || DZ < 256;
+    // A plain one requests it at the start of that step, or (!TOGETHER, see launch_dz) each thing where it is used.
     [[maybe_unused]] float Rm[9], tc[3], qb = 0.f;
     [[maybe_unused]] bool row_ok = true;
     [[maybe_unused]] const auto request_row = [&] {
@@ -942,11 +940,11 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
         }
 
         // ---- normalise, apply the inverse frame, store ---------------------------------------------
-        if constexpr (!KEEP && kTogether) request_row();
+        if constexpr (!KEEP && TOGETHER) request_row();
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
         const float lse2 = l_tot > 0.f ? w.m_ref + __log2f(l_tot) : -INFINITY;
         const int h = bh - b * p.H;
-        if constexpr (!kTogether) row_ok = p.mask ? p.mask[urow0 + irow_c] != 0 : true;
+        if constexpr (!TOGETHER) row_ok = p.mask ? p.mask[urow0 + irow_c] != 0 : true;
         const bool valid = row_ok && l_tot > 0.f;
         const float sc = valid ? inv : 0.f;
         const size_t row = (urow0 + irow_c) * p.H + h;
@@ -961,7 +959,7 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
             }
         }
         {
-            if constexpr (!kTogether) {
+            if constexpr (!TOGETHER) {
                 const float *R = p.rot + (urow0 + irow_c) * 9, *tr = p.trans + (urow0 + irow_c) * 3;
 #pragma unroll
                 for (int a = 0; a < 9; ++a) Rm[a] = R[a];
@@ -1020,29 +1018,35 @@ __global__ __launch_bounds__(256, 1) void fipa_attn_fwd_bf16_kernel(AttnParams p
                 }
             }
             if (p.lse && g == 0)
-                p.lse[user_lse_index(p, b, h, irow)] = valid ? lse2 * kLn2 - (kTogether ? qb : p.qbias[(size_t)bh * p.Lp + irow]) : 0.f;
+                p.lse[user_lse_index(p, b, h, irow)] = valid ? lse2 * kLn2 - (TOGETHER ? qb : p.qbias[(size_t)bh * p.Lp + irow]) : 0.f;
         }
     }
 }
 
-template <int DZ, bool FUSED, bool KEEP = false>
+template <int DZ, bool FUSED, bool KEEP = false, bool TOGETHER = true>
 hipError_t launch(const AttnParams &p, hipStream_t stream)
 {
     using C = AttnCfg<DZ>;
     static LdsLimit lds_limit;
-    hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_attn_fwd_bf16_kernel<DZ, FUSED, KEEP>, C::LDS_BYTES);
+    hipError_t e = raise_lds_limit(lds_limit, (const void *)fipa_attn_fwd_bf16_kernel<DZ, FUSED, KEEP, TOGETHER>, C::LDS_BYTES);
     if (e != hipSuccess) return e;
     if (p.plan.full % 8 != 0 || p.plan.full + p.plan.rem != p.total_tiles || p.plan.S < 1 ||
         (p.plan.S > 1 && (!FUSED || KEEP || p.cz < 32)))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL((fipa_attn_fwd_bf16_kernel<DZ, FUSED, KEEP>), dim3(p.plan.units()), dim3(256),
+    hipLaunchKernelGGL((fipa_attn_fwd_bf16_kernel<DZ, FUSED, KEEP, TOGETHER>), dim3(p.plan.units()), dim3(256),
                        C::LDS_BYTES, stream, p);
     return hipGetLastError();
 }
 
+// What a row's last step needs besides its sums, requested together: chains of 110 to 400 residues are 1 (r c_z = 256) to 3 % faster so, where it
+// is the end of a tile that takes the time.  At 256 it takes registers from the sums as well (150 instructions more), and long chains are
+// faster where each thing is read where it is used: one of 131 residues, H = 12 22.3 us together, 22.7 so, of 400 and of 800 the same, of 1000 0.5 %
+// and three ragged ones of 2633, H = 8 168.9 | 167.5.
 template <int DZ>
 hipError_t launch_dz(const AttnParams &p, bool fused, hipStream_t stream)
 {
+    if constexpr (DZ == 256)
+        if (fused && p.L > 640) return launch<DZ, true, false, false>(p, stream);
     return fused ? launch<DZ, true>(p, stream) : launch<DZ, false>(p, stream);
 }
 
