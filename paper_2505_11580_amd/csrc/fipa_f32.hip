@@ -509,7 +509,7 @@ size_t f32_forward_workspace(const fipa_desc &d)
 
 hipError_t f32_forward(const fipa_desc &d, const FwdArgs &a, void *ws, size_t ws_bytes, hipStream_t stream)
 {
-    if (f32_split_applies(d) && ws_bytes >= f32_split_workspace_min(d)) return f32_split_forward(d, a, ws, ws_bytes, stream);
+    if (f32_split_applies(d, a.mask != nullptr) && ws_bytes >= f32_split_workspace_min(d)) return f32_split_forward(d, a, ws, ws_bytes, stream);
     const F32Layout w = f32_layout(d);
     char *base = static_cast<char *>(ws);
     F32Params p;

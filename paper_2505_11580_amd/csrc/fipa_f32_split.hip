@@ -803,11 +803,15 @@ static bool split_reaches(const fipa_desc &d)
 // 1 : 1.09, of 704 1 : 0.96; 160 of 641 1 : 0.97), nor at 512 where the key ranges of more than 10 heads leave compute units idle (B H = 10
 // 1 : 0.95, 12 1 : 1.02, 16 1 : 0.94, 24 1 : 1.03, 32 1 : 0.94, 60 1 : 0.66; of 528 12 1 : 0.91, 24 1 : 0.92).  r c_z = 128, below 432 residues:
 // B H = 6 1 : 0.95 at 384, 8 1 : 1.02 (0.98 at 432), 10 1 : 1.05 (416 0.95), 12 1 : 0.98, 16 1 : 1.04 and at 392 0.96, 24 1 : 0.64.
-bool f32_split_applies(const fipa_desc &d)
+// Batches with a mask, whose chains are shorter than the batch (70, and 70 and 40 % of it valid below), of fewer than 20 (batch, head) pairs:
+// r c_z = 32 700 residues 1 : 0.90 to 1.02 (512 to 600 1 : 0.98 to 1.14), 64 560 residues 1 : 0.92 to 0.98 (512 1.00 to 1.10; B H = 8 1.04, 700 0.99), 128 above 512
+// 1 : 0.91 to 0.96 (449 1.04 to 1.21; B H = 16 480 1 : 0.93), 256 B H = 8 480 1 : 0.90 (384 to 449 1.02 to 1.07).
+bool f32_split_applies(const fipa_desc &d, bool masked)
 {
     if (!split_reaches(d)) return false;
     const int DZ = d.r * d.cz;
     const long long bh = (long long)d.B * d.H;
+    if (masked && bh < 20 && d.L < (DZ == 32 ? 700 : DZ == 64 ? (bh > 6 && bh < 12 ? 640 : 560) : DZ == 128 ? (bh >= 16 ? 480 : 513) : bh > 6 && bh < 12 ? 480 : 0)) return false;
     if (DZ == 256 && d.L <= 64) return bh <= kUnits && bh * ((d.L + 31) / 32) < 512 && bh * ((d.L + 15) / 16) > 512;
     if (DZ == 256 && d.L <= 96) return bh <= kUnits || bh >= 384;
     if (DZ == 128 && d.L < 432) return bh <= 6 || bh >= 20 || (bh >= 12 && (d.L > 384 || bh < 16)) || (d.L >= 416 && bh >= 10);

@@ -62,15 +62,15 @@ def test_f32_split_operands_in_every_workspace():
     # the space that the query asks for, without the split key range's, and without the key blocks (fp32 matrix instructions)
     import torch
     from paper_2505_11580_amd import binding
-    inp = wl.make_inputs(0, B=1, L=450, H=3, cz=64, r=2, chain=True, trans_scale=0.3)
-    inp["mask"] = (np.random.default_rng(5).random((1, 450)) < 0.6).astype(np.uint8)
+    inp = wl.make_inputs(0, B=1, L=545, H=3, cz=64, r=2, chain=True, trans_scale=0.3)
+    inp["mask"] = (np.random.default_rng(5).random((1, 545)) < 0.6).astype(np.uint8)
     desc, dev = binding.upload(inp)
     want = gu.oracle_forward_chunked(inp)
     full = binding.workspace_bytes(desc)[0]
-    # 12 tiles of 128 queries, seven key ranges; key blocks of 32 residues: three planes of z2, and 17408 bytes per head
-    tiles, unit, least = 12, 128 * (44 + 64) * 4, (3 * 450 * 76 * 4 + 255) // 256 * 256 + 2 * 256
-    blocks = 2 * 256 + 15 * 3 * 64 * 128 + 3 * 15 * 17408
-    assert full == blocks + 7 * tiles * unit
+    # 15 tiles of 128 queries, eight key ranges; key blocks of 32 residues: three planes of z2, and 17408 bytes per head
+    tiles, unit, least = 15, 128 * (44 + 64) * 4, (3 * 545 * 76 * 4 + 255) // 256 * 256 + 2 * 256
+    blocks = 2 * 256 + 18 * 3 * 64 * 128 + 3 * 18 * 17408
+    assert full == blocks + 8 * tiles * unit
     for size in (full, full - 256, blocks + 2 * tiles * unit, blocks, blocks - 256, least):
         out = binding.alloc_outputs(desc)
         for n in gu.NAMES:
@@ -86,8 +86,8 @@ def test_f32_split_operands_in_every_workspace():
 
 
 def test_f32_split_operands_without_a_valid_residue():
-    inp = wl.make_inputs(0, B=2, L=390, H=2, cz=128, r=1, chain=True, trans_scale=0.3)
-    inp["mask"] = np.ones((2, 390), np.uint8)
+    inp = wl.make_inputs(0, B=2, L=520, H=2, cz=128, r=1, chain=True, trans_scale=0.3)
+    inp["mask"] = np.ones((2, 520), np.uint8)
     want = gu.oracle_forward_chunked(inp)  # (which wants a valid key in every element)
     inp["mask"][0] = 0
     got = gu.run_gpu(inp)
@@ -111,7 +111,7 @@ def _run_in(inp, size):
 
 
 # Infinite operands, on split operands (in several parts, and unsplit) as on the fp32 matrix instructions, which the least workspace gives
-@pytest.mark.parametrize("kw", [dict(L=450, H=4, cz=64, r=2), dict(L=520, H=2, cz=16, r=2), dict(L=385, H=2, cz=128, r=2),
+@pytest.mark.parametrize("kw", [dict(L=530, H=4, cz=64, r=2), dict(L=710, H=2, cz=16, r=2), dict(L=385, H=2, cz=128, r=2),
                                 dict(L=512, B=11, H=3, cz=32, r=2)])
 def test_f32_split_operands_infinities(kw):
     kw = dict(dict(B=1, chain=False, trans_scale=0.05), **kw)

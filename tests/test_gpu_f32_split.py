@@ -50,7 +50,9 @@ def log_sum_exp(inp):
     (1, dict(L=530, B=4, H=10, cz=16, r=2)), (1, dict(L=512, B=11, H=3, cz=32, r=2, varlen=True, min_len=40)),
     (1, dict(L=450, B=11, H=3, cz=64, r=2)), (1, dict(L=384, B=4, H=11, cz=128, r=2, varlen=True, min_len=30)),
     (2, dict(L=512, B=2, H=12, cz=64, r=1)), (2, dict(L=1000, H=12, cz=16, r=8)), (2, dict(L=400, B=3, H=10, cz=128, r=2, varlen=True, min_len=1)),
-    (3, dict(L=640, H=14, cz=32, r=1)), (4, dict(L=500, B=2, H=7, cz=128, r=1, varlen=True, min_len=90)), (8, dict(L=600, H=2, cz=128, r=2))])
+    (3, dict(L=640, H=14, cz=32, r=1)), (4, dict(L=520, B=2, H=6, cz=128, r=1, varlen=True, min_len=90)), (8, dict(L=600, H=2, cz=128, r=2)),
+    (8, dict(L=710, B=2, H=2, cz=8, r=4, varlen=True, min_len=1)), (8, dict(L=590, B=2, H=2, cz=16, r=4, varlen=True, min_len=40)),
+    (8, dict(L=545, B=2, H=2, cz=64, r=2, varlen=True, min_len=1))])
 def test_accuracy_and_log_sum_exp(parts, kw):
     inp = _inputs(**kw)
     B, L, H = inp["q"].shape[:3]
