@@ -277,8 +277,8 @@ def test_bf16_last_valid_residue_at_every_byte(L):
     gu.check(inp, label="bf16 last valid residue L=%d" % L)
 
 
-@pytest.mark.parametrize("L", [640, 641])
+@pytest.mark.parametrize("L", [512, 513])
 def test_bf16_width_256_where_a_row_is_requested(L):
-    # the last step's reads of a row: together up to 640 residues, each where it is used above; with and without a mask
+    # the last step's reads of a row: together up to 512 residues, each where it is used above; with and without a mask
     gu.check(wl.make_inputs(1, B=1, L=L, H=2, trans_scale=0.3), label="bf16 width 256 L=%d" % L)
     gu.check(wl.make_inputs(1, B=3, L=L, H=2, trans_scale=0.3, varlen=True, min_len=1), label="bf16 width 256 masked L=%d" % L)
