@@ -1040,8 +1040,8 @@ hipError_t launch(const AttnParams &p, hipStream_t stream)
 
 // What a row's last step needs besides its sums, requested together: chains of 110 to 400 residues are 1 (r c_z = 256) to 3 % faster so, where it
 // is the end of a tile that takes the time.  At 256 it takes registers from the sums as well (150 instructions more), and long chains are
-// faster where each thing is read where it is used (one of 131 residues, H = 12 22.3 us together, 22.7 so; of 400 1 % for together, of 800 the
-// same, four of 600, H = 8 and one of 1000 0.5 to 1 % for so; three ragged ones of 2633, H = 8 168.9 | 167.5).
+// faster where each thing is read where it is used (one of 131 residues, H = 12 22.3 us together, 22.7 so; of 400 0.5 % for together, of 512 to
+// 800 the same, of 1000 0.5 % for so; three ragged ones of 2633, H = 8 168.9 | 167.5).
 template <int DZ>
 hipError_t launch_dz(const AttnParams &p, bool fused, hipStream_t stream)
 {
