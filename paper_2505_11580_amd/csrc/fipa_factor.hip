@@ -14,7 +14,6 @@
 #include "fipa_gfx950.h"
 #include "fipa_internal.h"
 
-#include <algorithm>
 #include <climits>
 
 namespace fipa {
@@ -85,10 +84,10 @@ __global__ __launch_bounds__(256) void fipa_factor_project_kernel(const int *__r
 // residues, 512 columns, 16.8 us from L2, 12.0 so; 2048 11.5 and 9.9; 8192 residues of 128 columns, 16 slots 10.1 and 9.2.
 constexpr int kFpThreads = 1024, kFpPass = kFpThreads / 4;
 constexpr int kFpAhead = 8;  // slots of a thread whose indices and bins wait in registers: 32 of a residue
-// Residues per workgroup from which the table is worth loading: 128 from 16 slots on, 256 up to 8.  From L2 | so, us, 512 columns, 33 + 16 rows per
-// slot: 128 residues per workgroup, 1 slot 4.6 | 5.5, 10 slots 8.2 | 8.3 (half of the residues masked 7.7 | 8.3), 16 10.1 | 9.2, 30 15.8 | 12.0;
-// 192, 4 slots 7.1 | 7.4, 7 8.9 | 8.3, 10 10.2 | 9.0; 256, 1 slot 6.9 | 6.1, 4 8.3 | 7.9, 10 11.9 | 9.7.
-inline int factor_rows(int k) { return std::clamp(2048 / k, 128, 256); }
+// Residues per workgroup from which the table is worth loading.  From L2 | so, 512 columns, 33 + 16 rows per slot, us or ratio: 16 slots, 128 residues
+// 10.1 | 9.2, 30 slots 15.8 | 12.0; just above 128 residues, where the kernel that reads from L2 needs a round of workgroups more, 10 slots 1 : 0.88 (at
+// 128 1.01 to 1.08), 6 1 : 0.95 to 0.98 (1.12 to 1.17), 4 1 : 1.01 to 1.07; just above 192, where it is another, 4 slots 1 : 0.91 to 0.97, 2 1 : 0.88.
+inline int factor_rows(int k) { return k >= 16 ? 128 : k >= 6 ? 136 : 200; }
 inline size_t factor_lds_bytes(int k, int n_bins, int n_pos)
 {
     return 64 * ((size_t)k * (n_bins + n_pos) + 1) + (size_t)kFpPass * k * 4;

@@ -83,13 +83,14 @@ def _in_lds(B, L, k, n_bins, n_pos, n_out):
     """Whether the projection runs with its tables in LDS: they fit, and each workgroup has enough residues to add."""
     groups = (n_out + 31) // 32
     parts = 256 // groups if groups < 256 else 1
-    return 64 * (k * (n_bins + n_pos) + 1) + 1024 * k <= 160 * 1024 and B * L >= parts * min(max(2048 // k, 128), 256)
+    return 64 * (k * (n_bins + n_pos) + 1) + 1024 * k <= 160 * 1024 and B * L >= parts * (128 if k >= 16 else 136 if k >= 6 else 200)
 
 
 # One order of sums, float32 to the nearest, whichever kernel adds them: the values of a sum in that order, rounded once
 @pytest.mark.parametrize("B,L,k,n_bins,n_pos,n_out,pos_mode,in_lds", [
     (1, 1920, 33, 4, 5, 520, 1, True), (800, 5, 2, 3, 9, 520, 1, True), (1, 4097, 4, 16, 0, 512, 0, True),
-    (3, 691, 64, 9, 13, 488, 1, True), (2, 2000, 10, 16, 33, 512, 1, True), (1, 700, 20, 16, 65, 512, 1, False)])
+    (3, 691, 64, 9, 13, 488, 1, True), (2, 2000, 10, 16, 33, 512, 1, True), (1, 700, 20, 16, 65, 512, 1, False),
+    (1, 2177, 10, 16, 33, 512, 0, True), (1, 2175, 10, 16, 33, 512, 0, False), (1, 3200, 3, 16, 0, 512, 1, True)])
 def test_projection_order(B, L, k, n_bins, n_pos, n_out, pos_mode, in_lds):
     import torch
     from tests.test_gpu_factor import run_gpu
